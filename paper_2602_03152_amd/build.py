@@ -36,7 +36,7 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfasa.so")
 LIB_TRACE = os.path.join(PKG, "libfasa_trace.so")
 FLOORS = os.path.join(PKG, "fasa_floors")      # stand-alone measurement program (csrc/floors.hip)
-SOURCES = ["api.hip", "pack.hip", "score.hip", "topk.hip", "attend.hip", "fused.hip", "offload.hip", "calib.hip"]
+SOURCES = ["api.hip", "pack.hip", "score.hip", "topk.hip", "attend.hip", "fused.hip", "step.hip", "offload.hip", "calib.hip"]
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 FLAGS = [

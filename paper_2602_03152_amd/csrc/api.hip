@@ -344,6 +344,11 @@ static int decode_step_common(const fasa_shape* shape, const fasa_paging* paging
   const bool select_all = !by_sequence && shape->budget >= shape->n_ctx;
   // the new row (if any) joins K, V and Kp inside the scoring kernel
   const AppendArgs ap{k_new, v_new, K, V, pm};
+  const StepForm form = plan_step(*shape, pm);
+  if (form != kStepNone) {
+    FASA_HIP(launch_step(*shape, form, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, st, rl, pm));
+    return FASA_OK;
+  }
   const FusePlan fp = plan_fused(*shape, by_sequence);
   if (fp.tpb != 0) {
     // two launches: scores + adaptive histogram, then selection and attention by token-range ownership

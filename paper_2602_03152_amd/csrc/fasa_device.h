@@ -21,6 +21,11 @@ __device__ __forceinline__ uint32_t score_key(float s) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// the score of a key (the inverse of score_key, -0 aside)
+__device__ __forceinline__ float key_score(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Adaptive histogram bins of the fused step.  The scoring kernel predicts where a row's B-th largest
 // score will lie - mu = location + z(B/N) * scale, from a robust location and scale of a small fixed

@@ -193,6 +193,15 @@ hipError_t launch_select_attend(const fasa_shape& s, const FusePlan& p, const vo
                                 int32_t* T, float* O, float* part_acc, float* part_ml, unsigned char* rec,
                                 hipStream_t st, RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
 
+// The step with one workgroup selecting and attending per row (step.hip): the whole step in one launch, or
+// after a scoring launch; plan_step: which of the two, if any, takes the shape.
+enum StepForm { kStepNone, kStepOne, kStepRow };
+constexpr int kStepMaxBudget = 1024;   // most selected tokens per row
+StepForm plan_step(const fasa_shape& s, const PageMap& pm);
+hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* K, void* V, void* Kp,
+                       const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
+                       RowCtl* ctl, hipStream_t st, RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
+
 // memory-optimised variant (offload.hip)
 hipError_t launch_offload_split(const fasa_shape& s, const void* K, const int32_t* fc_idx, void* Kp,
                                 void* Knd, int n_begin, int n_end, hipStream_t st);

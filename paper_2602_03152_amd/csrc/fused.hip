@@ -43,32 +43,6 @@ constexpr size_t kRecRowBytes = (size_t)kFuseRich * (kRecLogits * 4 + kHeadDim *
 static_assert(kRecRowBytes == kFuseRecBytesPerRow, "workspace carve-up and kernel disagree");
 
 
-// Rank of candidate i among the n candidates of an LDS list: how many of them sort before it (larger
-// key, or equal key and lower index).  Composites are distinct, so ranks are a permutation of 0..n-1
-// and "rank < need" takes exactly the `need` best.  32-bit compares only; the list is read eight
-// entries at a time (one LDS round trip per eight).  Thread t serves candidate t / PARTS and counts
-// the entries j = t % PARTS (mod PARTS); the PARTS partial counts of a candidate sit in adjacent lanes
-// and are added with DPP moves.  Returns the rank in every one of the candidate's threads.
-template <int PARTS>
-__device__ __forceinline__ int rank_in_list(const uint2* lc, int n, int i) {
-  const int t = threadIdx.x;
-  const uint2 me = lc[min(i, n - 1)];
-  int rank = 0;
-  for (int j0 = t % PARTS; j0 < n; j0 += 8 * PARTS) {
-    uint2 c[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) c[u] = lc[min(j0 + u * PARTS, n - 1)];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool before = c[u].x > me.x || (c[u].x == me.x && c[u].y < me.y);
-      rank += (j0 + u * PARTS < n && before) ? 1 : 0;
-    }
-  }
-  if constexpr (PARTS >= 2) rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
-  if constexpr (PARTS >= 4) rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-  return rank;
-}
-
 template <int G, int TPB>
 __global__ __launch_bounds__(256) void select_attend_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,

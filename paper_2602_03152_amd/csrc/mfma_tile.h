@@ -21,20 +21,25 @@
 
 namespace fasa {
 
+// 2^x on the hardware's own instruction: results below 2^-126 become 0 (the library function scales around
+// that at five instructions more).  Softmax weights are at most 1 and are summed with one that is 1.
+__device__ __forceinline__ float exp2_weight(float x) { return __builtin_amdgcn_exp2f(x); }
+
 struct TileKV { uint4 kc[4], vr[4]; };   // one lane's share of a tile: 4 chunks of its K row, 4 V rows x 16 bytes
 
-// G: query heads per KV head (1 .. 8; the tile is padded to 16 heads, lanes lo >= G carry zeros)
+// G: most query heads per KV head (1 .. 8; the tile is padded to 16 heads, lanes beyond carry zeros); kernels
+// with one instance for all group sizes pass the actual number as `heads` (<= G)
 template <int G>
 struct MfmaTile {
   bf16x8_t qb[4];        // B operands of the logits: Q^T, column lo, k-slots (hi, 0..7) of MFMA i = dims 8(hi+4i)..+7
   f32x4_t oc[8];         // oc[j][e]: weighted V of query head 4hi + e at head dim 8lo + j
   float m_run, l_run;    // of query head lo (log2 domain); l_run over this lane's rows only until finish()
 
-  __device__ __forceinline__ void load_q(const uint16_t* q_group /* [G][128] */, int lo, int hi) {
+  __device__ __forceinline__ void load_q(const uint16_t* q_group /* [heads][128] */, int lo, int hi, int heads = G) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       uint4 x = make_uint4(0, 0, 0, 0);
-      if (lo < G) x = *reinterpret_cast<const uint4*>(q_group + (size_t)lo * kHeadDim + 8 * (hi + 4 * i));
+      if (lo < heads) x = *reinterpret_cast<const uint4*>(q_group + (size_t)lo * kHeadDim + 8 * (hi + 4 * i));
       qb[i] = __builtin_bit_cast(bf16x8_t, x);
     }
   }
@@ -62,19 +67,24 @@ struct MfmaTile {
   // of LDS owned by this wave.
   __device__ __forceinline__ void accumulate(const TileKV& kv, const float (&sv)[4], const bool (&valid)[4],
                                              float* scs_wave, int lo, int hi) {
-#pragma clang fp contract(off)
-    float mx = kNegBig;
+    float x[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) mx = valid[e] ? fmaxf(mx, sv[e]) : mx;
+    for (int e = 0; e < 4; ++e) x[e] = valid[e] ? sv[e] : -INFINITY;   // weight exp2(-inf) = 0
+    accumulate_full(kv, x, scs_wave, lo, hi);
+  }
+  // a tile whose 16 rows all count (a logit of -inf: weight 0)
+  __device__ __forceinline__ void accumulate_full(const TileKV& kv, const float (&sv)[4], float* scs_wave, int lo, int hi) {
+#pragma clang fp contract(off)
+    float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
     mx = xor32_max(xor16_max(mx));
     const float m_new = fmaxf(m_run, mx);
-    const float sc = exp2f(m_run - m_new);
+    const float sc = exp2_weight(m_run - m_new);
     m_run = m_new;
     uint32_t ph[4], pl[4];
     float psum = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float pv = valid[e] ? exp2f(sv[e] - m_new) : 0.f;
+      const float pv = exp2_weight(sv[e] - m_new);
       psum += pv;
       ph[e] = __float_as_uint(pv) & 0xffff0000u;
       pl[e] = __float_as_uint(pv - __uint_as_float(ph[e]));      // exact; its own top 16 bits go in
@@ -116,13 +126,13 @@ struct MfmaTile {
   }
   // The wave's totals to LDS: sm_m_wave, sm_l_wave [G]; sm_o_wave [G][128].  (A block barrier must follow
   // before another wave reads them.)
-  __device__ __forceinline__ void finish(float* sm_m_wave, float* sm_l_wave, float* sm_o_wave, int lo, int hi) {
+  __device__ __forceinline__ void finish(float* sm_m_wave, float* sm_l_wave, float* sm_o_wave, int lo, int hi, int heads = G) {
     l_run = xor32_sum(xor16_sum(l_run));
-    if (hi == 0 && lo < G) { sm_m_wave[lo] = m_run; sm_l_wave[lo] = l_run; }
+    if (hi == 0 && lo < heads) { sm_m_wave[lo] = m_run; sm_l_wave[lo] = l_run; }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int g = 4 * hi + e;
-      if (g < G) {
+      if (g < heads) {
         float4* dst = reinterpret_cast<float4*>(sm_o_wave + g * kHeadDim + 8 * lo);
         dst[0] = make_float4(oc[0][e], oc[1][e], oc[2][e], oc[3][e]);
         dst[1] = make_float4(oc[4][e], oc[5][e], oc[6][e], oc[7][e]);

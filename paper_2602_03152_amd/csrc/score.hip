@@ -5,29 +5,9 @@
 
 #include "fasa_device.h"
 #include "fasa_internal.h"
+#include "score_common.h"
 
 namespace fasa {
-
-template <typename ET> struct ScoreTraits;
-template <> struct ScoreTraits<uint16_t> { static constexpr int TPT = 4; };  // tokens per 16-byte load
-template <> struct ScoreTraits<float> { static constexpr int TPT = 2; };
-
-template <typename ET>
-__device__ __forceinline__ void fma_pairs(const uint4& w, float qlo, float qhi, float* acc);
-
-template <>
-__device__ __forceinline__ void fma_pairs<uint16_t>(const uint4& w, float qlo, float qhi, float* acc) {
-  acc[0] = fmaf(qhi, bf16_hi(w.x), fmaf(qlo, bf16_lo(w.x), acc[0]));
-  acc[1] = fmaf(qhi, bf16_hi(w.y), fmaf(qlo, bf16_lo(w.y), acc[1]));
-  acc[2] = fmaf(qhi, bf16_hi(w.z), fmaf(qlo, bf16_lo(w.z), acc[2]));
-  acc[3] = fmaf(qhi, bf16_hi(w.w), fmaf(qlo, bf16_lo(w.w), acc[3]));
-}
-
-template <>
-__device__ __forceinline__ void fma_pairs<float>(const uint4& w, float qlo, float qhi, float* acc) {
-  acc[0] = fmaf(qhi, __uint_as_float(w.y), fmaf(qlo, __uint_as_float(w.x), acc[0]));
-  acc[1] = fmaf(qhi, __uint_as_float(w.w), fmaf(qlo, __uint_as_float(w.z), acc[1]));
-}
 
 constexpr int kScoreFB = 16;  // FC planes in flight per thread
 

@@ -1,0 +1,814 @@
+// The decode step for rows whose selected set one workgroup can attend over (paper Sec. 4.1 - 4.2, Alg. 2
+// order).  One workgroup selects a row's B best tokens, out of a list of the few scores that can be among
+// them, and attends over them; nothing is handed over between workgroups on the way from the scores to the
+// output.  Two forms:
+//
+//   step_kernel    the whole step in ONE launch.  A row of at most 512 * TPT tokens is scored, selected
+//                  and attended by one workgroup.  A longer row is scored by several; each publishes its
+//                  scores with write-through stores and takes the row's ticket, and the one that
+//                  finishes last selects and attends.  For small problems, where launches and
+//                  dependent round trips are the time.
+//   row_kernel     selection and attention of a row whose scores lie in S (after score_kernel without a
+//                  histogram): for problems that fill the machine, where scoring wants all its bandwidth.
+//
+// See plan_step for where the lines lie; beyond them fused.hip splits a row over many workgroups.
+#include "mfma_tile.h"
+#include "score_common.h"
+#include "select_common.h"
+
+namespace fasa {
+
+constexpr int kStepNT = 512;                 // threads per workgroup of step_kernel
+constexpr int kRowNT = 1024;                 // threads per workgroup of row_kernel
+constexpr int kListPerThread = 8;            // places of a row's list, per thread
+constexpr int kStepBins = 1024;
+constexpr int kStepCand = 256;               // candidates of the threshold bin ranked by counting
+
+struct StepArgs {
+  const void* q;
+  void* K;
+  void* V;
+  void* Kp;
+  const int32_t* fc_idx;
+  const void* k_new;       // readable even when nothing is appended (then q)
+  const void* v_new;
+  float* S;
+  int32_t* T;
+  float* O;
+  RowCtl* ctl;
+  const int32_t* n_ctx_seq;
+  const int32_t* budget_seq;
+  long long sb, sh, sn;    // K/V element strides
+  PageMap pm;
+  int rows, nslices, Hq, Hkv, F, N_max, n_cap, budget_max, t_pitch, append, pairing;
+  float scale_log2e;
+};
+
+// LDS of selection and attention; phases that never overlap share storage.
+template <int NT, int GM>
+struct RowLds {
+  static constexpr int kThreads = NT;
+  static constexpr int kWaves = NT / kWave;
+  static constexpr int kList = kListPerThread * NT;
+  union {
+    float o[kWaves][GM][kHeadDim];                           // weighted V per wave
+    uint2 list[kList];                                       // scores at or above the cut: (score bits, token)
+  };
+  union {
+    uint32_t hist[kStepBins];
+    uint32_t sample[kSample];
+  };
+  uint2 cand[kStepCand];
+  uint32_t ssort[kSample];                                   // keys of the sample, largest first
+  __align__(16) uint32_t wl[kStepMaxBudget + 16];            // selected tokens, then what the gather reads for them
+  float m[kWaves][GM], l[kWaves][GM];
+  float scs[kWaves][16];
+  uint32_t wtot[kWaves], wtot2[kWaves];
+  uint32_t thr[4];
+  uint32_t n_list;
+  int p_new;                                                 // place of the appended row in wl, or -1
+};
+
+// 16-byte store that goes through to the coherence point (see st_agent), counted by the compiler.  The
+// buffer is the same in all lanes (else every lane would become a store of its own).
+__device__ __forceinline__ void st_agent_f4(__amdgpu_buffer_rsrc_t rs, uint32_t byte_offset, float4 v) {
+  const u32x4_t w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+  __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)byte_offset, 0, kCachePolicySc1);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Selection: the B best of a set of scores to sm.wl[0 .. B).  A first range of keys klo .. 2^32 - 1 (no score
+// below it may be among the B best) is cut into 1024 bins of 2^shift keys:
+//   histogram  a suffix sum gives the threshold bin: bins above it hold fewer than B scores, bins from it
+//              upwards at least B.
+//   narrow     while the threshold bin holds more than kStepCand scores it becomes the next range, 1024
+//              times finer.  What the scores look like costs passes, never exactness.
+//   resolve    the bin's candidates are ranked by counting (key, then lower index).  A bin that is one key
+//              wide and still too full is a tie of that many tokens: they are taken in index order, out of
+//              the row's scores in memory.
+// ---------------------------------------------------------------------------------------------
+// After the counting: true once klo .. khi is the final range (need of its n_cand scores are taken, and all
+// above it); else the range to count next, the histogram zeroed.
+template <typename Lds>
+__device__ __forceinline__ bool find_threshold(Lds& sm, uint32_t& klo, uint32_t& khi, int& shift, int& need, int& n_cand) {
+  const int t = threadIdx.x;
+  __syncthreads();
+  constexpr int NT = Lds::kThreads, BPT = kStepBins / NT;     // bins per thread: 2 or 1
+  static_assert(BPT == 1 || BPT == 2, "");
+  const uint32_t h0 = sm.hist[BPT * t], h1 = BPT == 2 ? sm.hist[BPT * t + 1] : 0u;
+  const uint32_t incl = block_suffix_sum<NT>(h0 + h1, sm.wtot);
+  const uint32_t above = incl - h0 - h1;                      // scores in bins above this thread's
+  if (above < (uint32_t)need && (uint32_t)need <= incl) {
+    const bool up = BPT == 2 && above + h1 >= (uint32_t)need;
+    sm.thr[0] = (uint32_t)(BPT * t) + (up ? 1u : 0u);
+    sm.thr[1] = up ? above : above + h1;
+    sm.thr[2] = up ? h1 : h0;
+  }
+  __syncthreads();
+  n_cand = (int)sm.thr[2];
+  const uint32_t bin = sm.thr[0];
+  need -= (int)sm.thr[1];
+  klo += bin << shift;
+  if (bin + 1 < (uint32_t)kStepBins) khi = klo + ((1u << shift) - 1u);   // the last bin reaches up to khi
+  if (n_cand <= kStepCand || klo == khi) return true;
+  shift = max(0, 22 - __clz((int)(khi - klo)));               // (khi - klo) >> shift < 1024
+#pragma unroll
+  for (int j = 0; j < BPT; ++j) sm.hist[BPT * t + j] = 0;
+  __syncthreads();
+  return false;
+}
+// The threshold range's share of the set, after its candidates have been listed in sm.cand (if they fit)
+template <typename Lds>
+__device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bsel, int need, int n_cand,
+                                                  const float* srow, int N) {
+  constexpr int NT = Lds::kThreads;
+  const int t = threadIdx.x;
+  const int n_above = bsel - need;
+  auto place = [&](int p, uint32_t tok) {
+    if (p < bsel) sm.wl[p] = tok;
+  };
+  if (n_cand <= kStepCand) {   // taken iff fewer than `need` candidates sort before it
+    constexpr int P = NT / kStepCand;
+    const int ci = t / P;
+    const int rank = rank_in_list<P>(sm.cand, n_cand, ci);
+    if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
+  } else {                     // a tie of more than kStepCand tokens: the first `need` of them
+    int tied = 0;              // met so far
+    for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
+      const int n = i0 + t;
+      const bool tie = n < N && score_key(ld_agent(srow + min(n, N - 1))) == klo;
+      uint32_t tot;
+      const uint32_t before = block_prefix_sum<NT>(tie ? 1u : 0u, sm.wtot, tot);
+      if (tie && tied + (int)before < need) place(n_above + tied + (int)before, (uint32_t)n);
+      tied += (int)tot;
+    }
+  }
+  __syncthreads();
+}
+
+// All of a row's scores, out of memory: where there is no usable list.  Places go by wave.  The histogram is
+// zero at the call (a barrier ago); ends with a block barrier.
+template <typename Lds>
+__device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow, int N) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t klo = 0, khi = 0xffffffffu;
+  int shift = 22, need = bsel, n_cand;
+  for (;;) {
+    for (int i = t; i < N; i += NT) {
+      const uint32_t key = score_key(ld_agent(srow + i));
+      if (key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kStepBins - 1u)], 1u);
+    }
+    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+  }
+  uint32_t pw = 0, pc = 0;
+  for (int pass = 0; pass < 2; ++pass) {                      // count per wave, then place
+    for (int i0 = 0; i0 < N; i0 += NT) {
+      const int i = i0 + t;
+      const uint32_t key = score_key(ld_agent(srow + min(i, N - 1)));
+      const bool win = i < N && key > khi, cnd = i < N && key >= klo && key <= khi;
+      const unsigned long long mw = __ballot(win), mc = __ballot(cnd);
+      if (pass) {
+        const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, pw));
+        const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, pc));
+        if (win && p < (uint32_t)bsel) sm.wl[p] = (uint32_t)i;
+        if (cnd && c < (uint32_t)kStepCand) sm.cand[c] = make_uint2(key, (uint32_t)i);
+      }
+      pw += (uint32_t)__popcll(mw);
+      pc += (uint32_t)__popcll(mc);
+    }
+    __syncthreads();
+    if (!pass) {
+      if (lane == 0) { sm.wtot[wave] = pw; sm.wtot2[wave] = pc; }
+      __syncthreads();
+      pw = pc = 0;
+      for (int w = 0; w < NWV - 1; ++w) {
+        pw += w < wave ? sm.wtot[w] : 0u;
+        pc += w < wave ? sm.wtot2[w] : 0u;
+      }
+    }
+  }
+  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N);
+}
+
+// log2 of the bins' width for keys from kcut to twice the distance to ktop: span >> shift < 1024
+__device__ __forceinline__ int first_shift(uint32_t kcut, uint32_t ktop) {
+  const unsigned long long span = 2ull * (ktop - kcut) + kStepBins;
+  return max(0, 54 - __clzll((long long)span));
+}
+
+// The same inside a list of M <= EPT * NT scores that the threads hold: key[k], tok[k] of thread t are those of
+// entry k * NT + t.  Places go by thread.
+template <int EPT, typename Lds>
+__device__ __forceinline__ void list_select_regs(Lds& sm, int M, const uint32_t (&key)[EPT], const uint32_t (&tok)[EPT],
+                                                 uint32_t klo, int shift, int bsel, const float* srow, int N) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t khi = 0xffffffffu;
+  int need = bsel, n_cand;
+  for (;;) {
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      if (k * NT >= M) break;
+      if (k * NT + t < M && key[k] >= klo && key[k] <= khi)
+        atomicAdd(&sm.hist[min((key[k] - klo) >> shift, (uint32_t)kStepBins - 1u)], 1u);
+    }
+    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+  }
+  uint32_t win = 0, cnd = 0;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const bool in = k * NT + t < M;
+    win |= in && key[k] > khi ? 1u << k : 0u;
+    cnd |= in && key[k] >= klo && key[k] <= khi ? 1u << k : 0u;
+  }
+  // both counts of a thread fit 16 bits, and so do their sums (at most EPT * NT entries)
+  static_assert(EPT * NT < 65536, "packed counts");
+  const uint32_t mine = (uint32_t)__popc(win) | ((uint32_t)__popc(cnd) << 16);
+  const uint32_t incl = wave_prefix_sum(mine);
+  if (lane == kWave - 1) sm.wtot[wave] = incl;
+  __syncthreads();
+  uint32_t before = incl - mine;
+#pragma unroll
+  for (int w = 0; w < NWV - 1; ++w) before += w < wave ? sm.wtot[w] : 0u;
+  uint32_t pw = before & 0xffffu, pc = before >> 16;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    if (k * NT >= M) break;
+    if (win & (1u << k)) {
+      if (pw < (uint32_t)bsel) sm.wl[pw] = tok[k];
+      ++pw;
+    }
+    if (cnd & (1u << k)) {
+      if (pc < (uint32_t)kStepCand) sm.cand[pc] = make_uint2(key[k], tok[k]);
+      ++pc;
+    }
+  }
+  __syncthreads();
+  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N);
+}
+
+// Selection of a row inside its list of M scores that reach the cut kcut (0: everything does), or - should it be
+// shorter than B or longer than its room, because the sample misled or thousands of scores are equal - among
+// all of the row's scores in memory.
+template <typename Lds>
+__device__ __forceinline__ void select_row(Lds& sm, int M, uint32_t kcut, uint32_t ktop, int bsel, const float* srow, int N) {
+  if (M >= bsel && M <= Lds::kList) {
+    uint32_t key[kListPerThread], tok[kListPerThread];
+#pragma unroll
+    for (int k = 0; k < kListPerThread; ++k) {
+      const uint2 e = sm.list[k * Lds::kThreads + threadIdx.x];   // (beyond M: not looked at)
+      key[k] = score_key(__uint_as_float(e.x));
+      tok[k] = e.y;
+    }
+    list_select_regs<kListPerThread>(sm, M, key, tok, kcut, kcut ? first_shift(kcut, ktop) : 22, bsel, srow, N);
+  } else {
+    publish_barrier();                                        // this workgroup's own scores are in memory
+    row_select(sm, bsel, srow, N);
+  }
+}
+
+// Attention over the tokens in sm.wl[0 .. cnt): T is written, and every wave leaves its (max, sum, weighted V)
+// in LDS (a block barrier ago when this returns).  Wave w takes 16-row tiles w, w + waves, ... (bf16:
+// mfma_tile.h; float32: vector ALUs).
+template <typename ET, int GM, typename Lds>
+__device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, int b, int h, int G, int cnt, int n_app) {
+  constexpr int D = kHeadDim;
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const ET* q = (const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D;
+  // T, and what the gather reads: the row's element offset / 8, padded to whole tiles with the last row
+  const bool paged = a.pm.table != nullptr;
+  {
+    int32_t* trow = a.T + (size_t)row * a.t_pitch;
+    for (int i = t; i < cnt; i += NT) {
+      const int n = (int)sm.wl[i];
+      trow[i] = n;
+      if (n == n_app) sm.p_new = i;
+      const uint32_t e = (uint32_t)((unsigned long long)kv_row_offset(a.pm, paged ? b : 0, n, a.sb, a.sn) >> 3);
+      sm.wl[i] = e;
+      if (i == cnt - 1)
+        for (int j = cnt; j & 15; ++j) sm.wl[j] = e;
+    }
+  }
+  __syncthreads();
+  const ET* Kb = (const ET*)a.K + (paged ? 0 : b * a.sb) + h * a.sh;
+  const ET* Vb = (const ET*)a.V + (paged ? 0 : b * a.sb) + h * a.sh;
+  const ET* kn = (const ET*)a.k_new + (size_t)row * D;
+  const ET* vn = (const ET*)a.v_new + (size_t)row * D;
+  // the appended row is read from k_new / v_new: its place in the caches is being written in this launch
+  const int p_new = sm.p_new;
+  if constexpr (sizeof(ET) == 2) {
+    const int lo = lane & 15, hi = lane >> 4;
+    MfmaTile<GM> tile;
+    auto load_k = [&](TileKV& kv, int j0) {
+      const ET* kr = Kb + ((size_t)sm.wl[j0 + lo] << 3) + 8 * hi;
+      if (p_new >= j0 && p_new < j0 + 16) kr = p_new == j0 + lo ? kn + 8 * hi : kr;   // (wave-uniform test)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kv.kc[i] = *reinterpret_cast<const uint4*>(kr + 32 * i);
+    };
+    auto load_v = [&](TileKV& kv, int j0) {
+      const uint4 e4 = *reinterpret_cast<const uint4*>(&sm.wl[j0 + 4 * hi]);
+      const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
+      const ET* vp[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) vp[i] = Vb + ((size_t)e[i] << 3) + 8 * lo;
+      if (p_new >= j0 && p_new < j0 + 16) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) vp[i] = p_new == j0 + 4 * hi + i ? vn + 8 * lo : vp[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kv.vr[i] = *reinterpret_cast<const uint4*>(vp[i]);
+    };
+    const int jw = wave * 16;
+    tile.reset();
+    if (jw < cnt) {
+      const int n_tiles = (cnt - jw + 16 * NWV - 1) / (16 * NWV);
+      TileKV kv;
+      float sv[4];
+      tile.load_q(q, lo, hi, G);
+      load_k(kv, jw);
+      load_v(kv, jw);
+      for (int i = 0; i + 1 < n_tiles; ++i) {
+        const int j0 = jw + 16 * NWV * i;
+        tile.logits(kv, a.scale_log2e, sv);
+        // the next tile's K runs under this tile's P.V and its V under the next logits; the scheduler is
+        // kept from moving any of it (it would need 60 registers more than a wave has here, and spill)
+        __builtin_amdgcn_sched_barrier(0);
+        load_k(kv, j0 + 16 * NWV);
+        __builtin_amdgcn_sched_barrier(0);
+        tile.accumulate_full(kv, sv, &sm.scs[wave][0], lo, hi);
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(kv, j0 + 16 * NWV);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const int j0 = jw + 16 * NWV * (n_tiles - 1);
+      tile.logits(kv, a.scale_log2e, sv);
+      bool valid[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) valid[e] = j0 + 4 * hi + e < cnt;
+      tile.accumulate(kv, sv, valid, &sm.scs[wave][0], lo, hi);
+    }
+    tile.finish(&sm.m[wave][0], &sm.l[wave][0], &sm.o[wave][0][0], lo, hi, G);
+  } else {
+    // float32: a 16-lane group per row, lane c owning head dims 8c .. 8c+7
+    const int c = lane & 15, gr = lane >> 4;
+    constexpr int U = 2;                                      // rows in flight per group and batch
+    constexpr int GH = GM < 4 ? GM : 4;                       // query heads per pass over the rows (registers)
+    for (int g0 = 0; g0 < G; g0 += GH) {
+      float qr[GH][8], oc[GH][8], mr[GH], lr[GH];
+#pragma unroll
+      for (int g = 0; g < GH; ++g) {
+        const ET* qp = q + (size_t)min(g0 + g, G - 1) * D + 8 * c;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) { qr[g][k] = qp[k] * a.scale_log2e; oc[g][k] = 0.f; }
+        mr[g] = kNegBig;
+        lr[g] = 0.f;
+      }
+      for (int j0 = wave * 4 * U; j0 < cnt; j0 += 4 * U * NWV) {
+        float4 kr[U][2], vr[U][2];
+        bool valid[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int j = j0 + 4 * u + gr;
+          valid[u] = j < cnt;
+          const uint32_t e = sm.wl[min(j, cnt - 1)];
+          const float4* kp4 = reinterpret_cast<const float4*>((j == p_new ? kn : Kb + ((size_t)e << 3)) + 8 * c);
+          const float4* vp4 = reinterpret_cast<const float4*>((j == p_new ? vn : Vb + ((size_t)e << 3)) + 8 * c);
+          kr[u][0] = kp4[0]; kr[u][1] = kp4[1];
+          vr[u][0] = vp4[0]; vr[u][1] = vp4[1];
+        }
+#pragma unroll
+        for (int g = 0; g < GH; ++g) {
+          float s[U], mx = mr[g];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const float kf[8] = {kr[u][0].x, kr[u][0].y, kr[u][0].z, kr[u][0].w, kr[u][1].x, kr[u][1].y, kr[u][1].z, kr[u][1].w};
+            float d = 0.f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) d = fmaf(qr[g][k], kf[k], d);
+            s[u] = row16_sum(d);
+            mx = valid[u] ? fmaxf(mx, s[u]) : mx;
+          }
+          const float sc = exp2f(mr[g] - mx);
+          mr[g] = mx;
+          lr[g] *= sc;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) oc[g][k] *= sc;
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const float pv = valid[u] ? exp2f(s[u] - mx) : 0.f;
+            const float vf[8] = {vr[u][0].x, vr[u][0].y, vr[u][0].z, vr[u][0].w, vr[u][1].x, vr[u][1].y, vr[u][1].z, vr[u][1].w};
+            lr[g] += pv;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) oc[g][k] = fmaf(pv, vf[k], oc[g][k]);
+          }
+        }
+      }
+      // the four groups of the wave hold the same head dims
+#pragma unroll
+      for (int g = 0; g < GH; ++g) {
+        const float mn = xor32_max(xor16_max(mr[g])), sc = exp2f(mr[g] - mn);
+        lr[g] = xor32_sum(xor16_sum(lr[g] * sc));
+#pragma unroll
+        for (int k = 0; k < 8; ++k) oc[g][k] = xor32_sum(xor16_sum(oc[g][k] * sc));
+        if (gr == 0 && g0 + g < G) {
+          if (c == 0) { sm.m[wave][g0 + g] = mn; sm.l[wave][g0 + g] = lr[g]; }
+          float4* o4 = reinterpret_cast<float4*>(&sm.o[wave][g0 + g][8 * c]);
+          o4[0] = make_float4(oc[g][0], oc[g][1], oc[g][2], oc[g][3]);
+          o4[1] = make_float4(oc[g][4], oc[g][5], oc[g][6], oc[g][7]);
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Sum over the waves: thread (query head g, 4 head dims d4) gets max, sum of weights, weighted V.
+template <typename Lds>
+__device__ __forceinline__ void wave_totals(const Lds& sm, int g, int d4, float& mn, float& ls, float4& o) {
+  mn = sm.m[0][g];
+#pragma unroll
+  for (int i = 1; i < Lds::kWaves; ++i) mn = fmaxf(mn, sm.m[i][g]);
+  ls = 0.f;
+  o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int i = 0; i < Lds::kWaves; ++i) {
+    const float sc = exp2f(sm.m[i][g] - mn);
+    ls = fmaf(sm.l[i][g], sc, ls);
+    const float4 x = *reinterpret_cast<const float4*>(&sm.o[i][g][4 * d4]);
+    o.x = fmaf(x.x, sc, o.x); o.y = fmaf(x.y, sc, o.y); o.z = fmaf(x.z, sc, o.z); o.w = fmaf(x.w, sc, o.w);
+  }
+}
+template <typename Lds>
+__device__ __forceinline__ void write_output(const StepArgs& a, const Lds& sm, int b, int h, int G) {
+  constexpr int D = kHeadDim;
+  const int t = threadIdx.x;
+  if (t < G * (D / 4)) {
+    const int g = t / (D / 4), d4 = t % (D / 4);
+    float mn, ls;
+    float4 o;
+    wave_totals(sm, g, d4, mn, ls, o);
+    const float inv = 1.0f / ls;
+    *reinterpret_cast<float4*>(a.O + ((size_t)b * a.Hq + (size_t)h * G + g) * D + 4 * d4) =
+        make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+  }
+}
+
+// The list of a row whose scores the caller's threads hold in registers: score(k), k < NV, of token
+// token(k, c0) (a NaN where the row has ended); with more than `resident` tokens in the row they hold one
+// stretch of it at a time, and reload(c0) brings in the stretch that starts at c0.
+// 128 scores of the row, evenly spaced (`sval` of thread i < 128), are ranked; the sample_rank-th best is the cut.
+// Returns the list's length; kcut, ktop: keys of the cut (0: none) and of the sample's best.
+template <int NV, typename Lds, typename Score, typename Token, typename Reload>
+__device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, int resident, Score&& score, Token&& token,
+                                         Reload&& reload, uint32_t& kcut, uint32_t& ktop) {
+  constexpr int NT = Lds::kThreads;
+  const int t = threadIdx.x, lane = t & 63;
+  // the sample's keys are made distinct in their low bits: ranks are a permutation, a cut may be any value
+  if (t < kSample) sm.sample[t] = (score_key(sval) & ~(uint32_t)(kSample - 1)) | (uint32_t)t;
+  if (t == 0) { sm.n_list = 0; sm.p_new = -1; sm.thr[2] = 0; }
+  __syncthreads();
+  {
+    constexpr int P = NT / kSample;                           // threads per sample value
+    static_assert(P == 4 || P == 8, "a quad or half a row of lanes per value");
+    const uint32_t me = sm.sample[t / P];
+    int rank = 0;
+#pragma unroll
+    for (int u = 0; u < kSample / 4 / P; ++u) {
+      const uint4 o = reinterpret_cast<const uint4*>(sm.sample)[P * u + t % P];
+      rank += (o.x > me ? 1 : 0) + (o.y > me ? 1 : 0) + (o.z > me ? 1 : 0) + (o.w > me ? 1 : 0);
+    }
+    rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+    rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+    if constexpr (P == 8) rank += __builtin_amdgcn_update_dpp(0, rank, 0x141, 0xF, 0xF, true);   // row_half_mirror
+    if (t % P == 0) sm.ssort[rank & (kSample - 1)] = me & ~(uint32_t)(kSample - 1);
+  }
+  __syncthreads();
+  for (int i = t; i < kStepBins; i += NT) sm.hist[i] = 0;     // (shares storage with the sample)
+  const int r = sample_rank(bsel, N);
+  kcut = r > kSample ? 0u : sm.ssort[r - 1];
+  ktop = sm.ssort[0];
+  const float cut = r > kSample ? -INFINITY : key_score(kcut);
+  for (int c0 = 0; c0 < N; c0 += resident) {
+    if (N > resident) reload(c0);
+    unsigned long long m[NV];                                 // per wave: which lanes' k-th score reaches the cut
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      m[k] = __ballot(score(k) >= cut);
+      cnt += (uint32_t)__popcll(m[k]);
+    }
+    uint32_t base = 0;
+    if (lane == 0 && cnt) base = atomicAdd(&sm.n_list, cnt);
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
+      if (score(k) >= cut && pos < (uint32_t)Lds::kList) sm.list[pos] = make_uint2(__float_as_uint(score(k)), (uint32_t)token(k, c0));
+      base += (uint32_t)__popcll(m[k]);
+    }
+  }
+  __syncthreads();
+  return (int)sm.n_list;
+}
+
+// MULTI: rows of several slices (scores handed over through S and a ticket); else one slice per row.
+template <typename ET, int NB, int GM, bool MULTI>
+__global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
+  constexpr int D = kHeadDim;
+  constexpr int TPT = ScoreTraits<ET>::TPT;
+  constexpr int SL = kStepNT * TPT;
+  constexpr int NW = NB == 1 ? 8 : 16;       // planes in flight per thread
+  __shared__ union {
+    struct {
+      float ql[kMaxGroup][kHeadDim];                           // the group's queries
+      float2 qs[kHeadDim / 2];
+      float2 kpair[kHeadDim / 2];                              // the appended key's listed dims
+      uint32_t knew[kHeadDim];                                 // the appended key, as stored
+    };
+    RowLds<kStepNT, GM> row;
+  } sm;
+  __shared__ __align__(16) float srow_lds[MULTI ? 4 : SL];     // scores of a single-slice row, for the sample
+  __shared__ uint32_t ticket;
+
+  int row, slice;
+  row_slice_of_block(a.rows, MULTI ? a.nslices : 1, row, slice);
+  const int b = row / a.Hkv, h = row % a.Hkv;
+  const int G = min(a.Hq / a.Hkv, GM);
+  const int t = threadIdx.x;
+  const int N = seq_n_ctx(a.n_ctx_seq, b, a.N_max);
+  if (slice * SL >= N) return;                                // beyond this sequence (ragged batches only)
+  const int nvalid = (N + SL - 1) / SL;
+  const int bsel = min(seq_bsel(a.budget_seq, b, N, a.budget_max), kStepMaxBudget);
+  const ET* q = (const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D;
+
+  // ---- scores.  Order of issue as in score_kernel: what the planes do not depend on first, then all
+  // plane loads unconditionally, then a wait for the former only ----
+  ET qcol[2];                                                 // head dim t mod 128 of query heads t / 128 and + 4
+#pragma unroll
+  for (int j = 0; j < 2; ++j) qcol[j] = q[(size_t)min((t >> 7) + 4 * j, G - 1) * D + (t & (D - 1))];
+  const int fe = min(t, a.F - 1);
+  const int32_t fci = a.fc_idx[list_word(a.pairing, a.F, h, fe, 0)];
+  const int32_t fcj = a.fc_idx[list_word(a.pairing, a.F, h, fe, 1)];
+  const ET newkv = ((const ET*)((t & 255) < D ? a.k_new : a.v_new))[(size_t)row * D + (t & (D - 1))];
+  const int n0 = (slice * kStepNT + t) * TPT;
+  const bool active = n0 < N;
+  ET* Kp = (ET*)a.Kp + (size_t)row * a.F * a.n_cap * 2;
+  const ET* p = Kp + (size_t)(active ? n0 : 0) * 2;
+  const size_t plane = (size_t)a.n_cap * 2;
+  const int F = NB ? NB * 8 : a.F;
+  uint4 w[NW];
+#pragma unroll
+  for (int u = 0; u < NW; ++u)
+    w[u] = *reinterpret_cast<const uint4*>(p + (size_t)(NB ? u : min(u, F - 1)) * plane);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float x;
+    if constexpr (sizeof(ET) == 2) x = __uint_as_float((uint32_t)qcol[j] << 16);
+    else x = qcol[j];
+    sm.ql[(t >> 7) + 4 * j][t & (D - 1)] = x;                 // heads beyond the group: copies, not added
+  }
+  const int n_app = N - 1;
+  const bool own_wg = a.append && n_app / SL == slice;
+  if (t < D) {
+    if constexpr (sizeof(ET) == 2) sm.knew[t] = (uint32_t)newkv;
+    else sm.knew[t] = __float_as_uint(newkv);
+  }
+  __syncthreads();
+  uint32_t pair_x = 0, pair_y = 0;
+  if (t < F) {   // sum_g (q_g . k) = (sum_g q_g) . k, g ascending
+    const int pr = pair_dims(a.pairing, fci, fcj);
+    float lo = 0.f, hi = 0.f;
+#pragma unroll
+    for (int g = 0; g < kMaxGroup; ++g) {
+      const float x = sm.ql[g][pr & 255], y = sm.ql[g][pr >> 8];
+      lo += g < G ? x : 0.f;
+      hi += g < G ? y : 0.f;
+    }
+    sm.qs[t] = make_float2(lo, hi);
+    pair_x = sm.knew[pr & 255];
+    pair_y = sm.knew[pr >> 8];
+    if constexpr (sizeof(ET) == 2) sm.kpair[t] = make_float2(__uint_as_float(pair_x << 16), __uint_as_float(pair_y << 16));
+    else sm.kpair[t] = make_float2(__uint_as_float(pair_x), __uint_as_float(pair_y));
+  }
+  __syncthreads();
+  float acc[TPT];
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) acc[k] = 0.f;
+  if constexpr (NB > 0) {
+#pragma unroll
+    for (int u = 0; u < NB * 8; ++u) {
+      const float2 qf = sm.qs[u];
+      fma_pairs<ET>(w[u % NW], qf.x, qf.y, acc);
+      if (u + NW < NB * 8) w[u % NW] = *reinterpret_cast<const uint4*>(p + (size_t)(u + NW) * plane);
+    }
+  } else {
+    for (int f0 = 0; f0 < F; f0 += NW) {
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        if (f0 + u < F) {
+          const float2 qf = sm.qs[f0 + u];
+          fma_pairs<ET>(w[u], qf.x, qf.y, acc);
+          w[u] = *reinterpret_cast<const uint4*>(p + (size_t)min(f0 + NW + u, F - 1) * plane);
+        }
+      }
+    }
+  }
+  // the appended token's score comes from the new row itself: the planes did not hold it
+  if (own_wg && (n_app - slice * SL) / TPT == t) {
+    float s = 0.f;
+#pragma unroll 8
+    for (int f = 0; f < F; ++f) {
+      const float2 qf = sm.qs[f], kf = sm.kpair[f];
+      s = fmaf(qf.y, kf.y, fmaf(qf.x, kf.x, s));
+    }
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) acc[k] = n_app % TPT == k ? s : acc[k];
+  }
+  float* srow = a.S + (size_t)row * a.n_cap;
+  const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
+  if (active) {
+    float* out = srow + n0;
+    if (n0 + TPT <= N) {
+      if constexpr (TPT == 4) st_agent_f4(rs, (uint32_t)n0 * 4u, make_float4(acc[0], acc[1], acc[2], acc[3]));
+      else st_agent(reinterpret_cast<float2*>(out), make_float2(acc[0], acc[1]));
+    } else {
+#pragma unroll
+      for (int k = 0; k < TPT; ++k)
+        if (n0 + k < N) st_agent(out + k, acc[k]);
+    }
+  }
+  if constexpr (MULTI) {
+    publish_barrier();
+    if (t == 0) ticket = atomicAdd(&a.ctl[row].done_sel, 1u);
+  }
+  // Alg. 2, UpdateCache: the new row joins K, V and the planes.  Nothing in this launch reads it there
+  // (the gather takes it from k_new / v_new), so nothing waits for these stores.
+  if (own_wg) {
+    if (t < F) {
+      if constexpr (sizeof(ET) == 2)
+        *reinterpret_cast<uint32_t*>(Kp + ((size_t)t * a.n_cap + n_app) * 2) = pair_x | (pair_y << 16);
+      else
+        *reinterpret_cast<uint2*>(Kp + ((size_t)t * a.n_cap + n_app) * 2) = make_uint2(pair_x, pair_y);
+    }
+    if (t < 2 * D) {
+      ET* dst = (ET*)(t < D ? a.K : a.V) + kv_row_offset(a.pm, b, n_app, a.sb, a.sn) + h * a.sh + (t & (D - 1));
+      *dst = newkv;
+    }
+  }
+  int M;
+  uint32_t kcut, ktop;
+  if constexpr (MULTI) {
+    __syncthreads();
+    if (ticket != (uint32_t)nvalid - 1u) return;
+    if (t == 0) a.ctl[row].done_sel = 0;                      // clean for the next call
+    const int si = (int)(((long long)(t & (kSample - 1)) * N) >> 7);
+    const float sval = ld_agent(srow + si);
+    constexpr int CH = 4;
+    float v[4 * CH];
+    // the row is readable in 16-byte pieces: S is n_cap long, a multiple of 64
+    auto load_scores = [&](int c0) {
+#pragma unroll
+      for (int it = 0; it < CH; ++it) {
+        const int n = c0 + (it * kStepNT + t) * 4;
+        const uint4 x = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
+        v[4 * it] = n < N ? __uint_as_float(x.x) : NAN; v[4 * it + 1] = n + 1 < N ? __uint_as_float(x.y) : NAN;
+        v[4 * it + 2] = n + 2 < N ? __uint_as_float(x.z) : NAN; v[4 * it + 3] = n + 3 < N ? __uint_as_float(x.w) : NAN;
+      }
+    };
+    constexpr int R = CH * kStepNT * 4;
+    if (N <= R) load_scores(0);
+    M = make_list<4 * CH>(sm.row, N, bsel, sval, R, [&](int k) { return v[k]; },
+                          [&](int k, int c0) { return c0 + ((k >> 2) * kStepNT + t) * 4 + (k & 3); }, load_scores, kcut, ktop);
+  } else {
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) srow_lds[t * TPT + k] = acc[k];
+    __syncthreads();
+    const float sval = srow_lds[((t & (kSample - 1)) * N) >> 7];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) acc[k] = n0 + k < N ? acc[k] : NAN;
+    M = make_list<TPT>(sm.row, N, bsel, sval, SL, [&](int k) { return acc[k]; }, [&](int k, int) { return n0 + k; }, [](int) {},
+                       kcut, ktop);
+  }
+  select_row(sm.row, M, kcut, ktop, bsel, srow, N);
+  row_attend<ET, GM>(a, sm.row, row, b, h, G, bsel, a.append ? n_app : -1);
+  write_output(a, sm.row, b, h, G);
+}
+
+// One workgroup per row; the scores lie in S (an earlier launch).
+template <typename ET, int GM>
+__global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
+  __shared__ RowLds<kRowNT, GM> sm;
+  const int row = blockIdx.x;
+  const int b = row / a.Hkv, h = row % a.Hkv;
+  const int G = min(a.Hq / a.Hkv, GM);
+  const int t = threadIdx.x;
+  const int N = seq_n_ctx(a.n_ctx_seq, b, a.N_max);
+  const int bsel = min(seq_bsel(a.budget_seq, b, N, a.budget_max), kStepMaxBudget);
+  const float* srow = a.S + (size_t)row * a.n_cap;
+  const float sval = srow[(int)(((long long)(t & (kSample - 1)) * N) >> 7)];
+  constexpr int CH = 4;
+  float v[4 * CH];
+  auto load_scores = [&](int c0) {
+#pragma unroll
+    for (int it = 0; it < CH; ++it) {
+      const int n = c0 + (it * kRowNT + t) * 4;
+      const float4 x = *reinterpret_cast<const float4*>(srow + (n < N ? n : 0));
+      v[4 * it] = n < N ? x.x : NAN; v[4 * it + 1] = n + 1 < N ? x.y : NAN;
+      v[4 * it + 2] = n + 2 < N ? x.z : NAN; v[4 * it + 3] = n + 3 < N ? x.w : NAN;
+    }
+  };
+  constexpr int R = CH * kRowNT * 4;
+  if (N <= R) load_scores(0);
+  uint32_t kcut, ktop;
+  const int M = make_list<4 * CH>(sm, N, bsel, sval, R, [&](int k) { return v[k]; },
+                                  [&](int k, int c0) { return c0 + ((k >> 2) * kRowNT + t) * 4 + (k & 3); }, load_scores, kcut, ktop);
+  select_row(sm, M, kcut, ktop, bsel, srow, N);
+  row_attend<ET, GM>(a, sm, row, b, h, G, bsel, -1);
+  write_output(a, sm, b, h, G);
+}
+
+// ---------------------------------------------------------------------------------------------
+// launch
+// ---------------------------------------------------------------------------------------------
+StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
+  const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx;
+  if (bsel > kStepMaxBudget) return kStepNone;
+  // what the gather reads is a 32-bit offset in units of 8 elements
+  const long long most = pm.table ? (long long)pm.n_pool * s.kv_stride_b + (1ll << pm.shift) * s.kv_stride_n
+                                  : (long long)s.n_ctx * s.kv_stride_n;
+  if ((most >> 3) >= 0xfffffff0ll) return kStepNone;
+  // Lines measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step as (fused.hip or the
+  // staged kernels / one launch / row form).  One compute unit gathers about 50 KB per us, which is what
+  // ends these forms' reach in B; reading a row's scores back, and the workgroups of the last rows
+  // having the machine to themselves, is what ends it in N.
+  const long long rows = (long long)s.batch * s.n_kv_heads;
+  const int per = kStepNT * (s.dtype == FASA_BF16 ? 4 : 2);
+  const long long ns = (s.n_ctx + per - 1) / per;
+  if (s.dtype == FASA_BF16) {
+    // one slice: 8 rows of 2048, B = 64: 14.5 / 10.2 / 15.0, B = 512: 18.2 / 14.9 / 19.8; 512 rows: 29.4 / 20.5 / 36.3
+    if (ns == 1) return kStepOne;
+    // 8 rows of 8192, B = 256: 14.6 / 14.6 / 17.3, B = 512: 16.0 / 17.0 / 19.8; 128 rows of 4096: 22.3 / 20.4 / 21.9
+    if (ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320) return kStepOne;
+    // 128 rows of 16384, B = 256: 46.7 / 46.2 / 42.4, B = 1024: 58.0 / 71.3 / 54.2; 32 rows: 20.2 / 19.6 / 21.9
+    if (rows >= 128 && s.n_ctx >= 8192) return kStepRow;
+    return kStepNone;
+  }
+  // float32: the vector ALUs attend, in proportion to the query heads.
+  // 1 head, 1 row of 4096, B = 256: 16.6 / 12.1 / 13.5; 4 heads, 8 rows, B = 64: 18.4 / 15.3 / 17.2, B = 256: 20.5 / 19.8 / 20.7
+  if (ns <= 8 && rows * ns <= kAssumedCUs && bsel * (s.n_q_heads / s.n_kv_heads) <= 512) return kStepOne;
+  // 4 heads, 128 rows of 8192, B = 64: 44.6 / 49.6 / 40.6, B = 256: 51.5 / 69.4 / 47.4, B = 1024: 69.6 / 132.9 / 69.4
+  if (rows >= 128 && bsel <= 512) return kStepRow;
+  return kStepNone;
+}
+
+template <typename ET, int NB, int GM>
+static hipError_t launch_step_v(const StepArgs& a, hipStream_t st) {
+  if (a.nslices == 1) return launch("fasa_step", step_kernel<ET, NB, GM, false>, dim3(a.rows), dim3(kStepNT), st, a);
+  return launch("fasa_step", step_kernel<ET, NB, GM, true>, dim3(a.rows * a.nslices), dim3(kStepNT), st, a);
+}
+hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* K, void* V, void* Kp,
+                       const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
+                       RowCtl* ctl, hipStream_t st, RaggedLens rl, PageMap pm) {
+  StepArgs a;
+  a.q = q; a.K = K; a.V = V; a.Kp = Kp; a.fc_idx = fc_idx;
+  a.append = k_new != nullptr;
+  a.k_new = k_new ? k_new : q;      // rows * head_dim elements are there: the queries are no fewer
+  a.v_new = v_new ? v_new : q;
+  a.S = S; a.T = T; a.O = O; a.ctl = ctl;
+  a.n_ctx_seq = rl.n_ctx; a.budget_seq = rl.budget;
+  a.sb = s.kv_stride_b; a.sh = s.kv_stride_h; a.sn = s.kv_stride_n;
+  a.pm = pm;
+  a.rows = s.batch * s.n_kv_heads;
+  const int per = kStepNT * (s.dtype == FASA_BF16 ? 4 : 2);
+  a.nslices = (s.n_ctx + per - 1) / per;
+  a.Hq = s.n_q_heads; a.Hkv = s.n_kv_heads; a.F = s.n_fc; a.N_max = s.n_ctx; a.n_cap = s.n_cap;
+  a.budget_max = s.budget;
+  a.t_pitch = s.budget < s.n_ctx ? s.budget : s.n_ctx;
+  a.pairing = s.pairing;
+  a.scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
+  const int G = s.n_q_heads / s.n_kv_heads;
+  if (form == kStepRow) {
+    const hipError_t e = launch_score(s, q, Kp, fc_idx, S, nullptr, st, rl, AppendArgs{k_new, v_new, K, V, pm});
+    if (e != hipSuccess) return e;
+    if (s.dtype == FASA_BF16) return launch("fasa_row", row_kernel<uint16_t, 8>, dim3(a.rows), dim3(kRowNT), st, a);
+    if (G == 1) return launch("fasa_row", row_kernel<float, 1>, dim3(a.rows), dim3(kRowNT), st, a);
+    if (G <= 4) return launch("fasa_row", row_kernel<float, 4>, dim3(a.rows), dim3(kRowNT), st, a);
+    return launch("fasa_row", row_kernel<float, 8>, dim3(a.rows), dim3(kRowNT), st, a);
+  }
+  if (s.dtype == FASA_BF16) {
+    switch (s.n_fc) {
+      case 8: return launch_step_v<uint16_t, 1, 8>(a, st);
+      case 16: return launch_step_v<uint16_t, 2, 8>(a, st);
+      case 24: return launch_step_v<uint16_t, 3, 8>(a, st);
+      case 32: return launch_step_v<uint16_t, 4, 8>(a, st);
+      default: return launch_step_v<uint16_t, 0, 8>(a, st);
+    }
+  }
+  if (G == 1) return s.n_fc == 16 ? launch_step_v<float, 2, 1>(a, st) : launch_step_v<float, 0, 1>(a, st);
+  if (G <= 4) return launch_step_v<float, 0, 4>(a, st);
+  return launch_step_v<float, 0, 8>(a, st);
+}
+
+}  // namespace fasa
