@@ -1,107 +1,407 @@
 // Offline calibration (paper Sec. 3.3 eq. ca_k and Alg. 1): contextual agreement of every single
-// frequency chunk with the full head, computed on the device with the same scoring and selection
-// kernels as the decode step.  Trick: the FC-major packed copy of ALL d/2 FCs,
-// Kp_all[b][h][i][n][2], is bit for bit the packed copy of a "virtual" cache with Hkv * d/2 KV
-// heads and one FC each, so single-FC scoring of all FCs is ONE call of the ordinary scoring
-// kernel on that virtual shape (with the group's queries replicated per virtual head), and the d/2
-// top-K problems per head are one call of the ordinary selection kernel.
+// frequency chunk with the full head, for one query.  Kp_all holds all d/2 FCs, FC-major.  Three launches:
+//
+//   calib_full_kernel   full-head scores alpha (all planes, fp32 chain in FC order);
+//   calib_topk_kernel   one workgroup per (b, h): the top-K set of alpha, as a bitmap over the tokens;
+//   calib_fc_kernel     one workgroup per (b, h, FC): the scores of the one FC, their top-K threshold, and how
+//                       many of the top-K are in the bitmap.
+//
+// The single-FC scores and sets never exist in memory: a workgroup streams its plane once and writes one number.
+// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys): 13.6 + 11.3 + 21.7 us.  Scoring all FCs to memory
+// (67 MB of scores), selecting them with the decode step's kernels and intersecting index lists took 135 us.
+#include <type_traits>
+
 #include "fasa_device.h"
 #include "fasa_internal.h"
+#include "score_common.h"
+#include "select_common.h"
 
 namespace fasa {
 
-constexpr int kCalibMaxCtx = 262144;   // bitmap of the full-head top-K set lives in LDS (32 KB)
+constexpr int kCalibMaxCtx = 262144;   // the bitmap of the full-head top-K set lives in LDS (32 KB)
+constexpr int kCalibPerThread = 16;    // scores in flight per thread
 
-// grid = batch * Hkv * half workgroups of 128 threads: virtual KV head (h, i) gets the G query heads
-// of real KV head h; plus the two index lists.
-template <typename ET>
-__global__ __launch_bounds__(128) void calib_prepare_kernel(const ET* __restrict__ q,
-                                                            ET* __restrict__ q_v,
-                                                            int32_t* __restrict__ fc_all,
-                                                            int32_t* __restrict__ fc_v, int Hq,
-                                                            int Hkv, int half) {
-  constexpr int D = kHeadDim;
-  const int G = Hq / Hkv;
-  const int vb = blockIdx.x;                     // b * Hkv * half + h * half + i
-  const int i = vb % half, h = (vb / half) % Hkv, b = vb / (half * Hkv);
-  const int t = threadIdx.x;
-  for (int g = 0; g < G; ++g)
-    q_v[(((size_t)b * Hkv * half + (size_t)h * half + i) * G + g) * D + t] =
-        q[((size_t)b * Hq + (size_t)h * G + g) * D + t];
-  if (b == 0 && t == 0) {
-    fc_all[h * half + i] = i;
-    fc_v[h * half + i] = i;
-  }
-}
-
-constexpr int kCalibFcPerWg = 4;   // FCs counted by one workgroup (each workgroup rebuilds the row's bitmap)
-
-// grid = rows * ceil(half / kCalibFcPerWg) workgroups of 256 threads.
-// CA_sum[row][i] += |T_full[row] & T_v[row][i]| / kk for the workgroup's FCs i.  The index lists are
-// read 8 entries per thread at a time, all 8 loads issued before the first is used.
-__global__ __launch_bounds__(256) void calib_intersect_kernel(const int32_t* __restrict__ T_full,
-                                                              const int32_t* __restrict__ T_v,
-                                                              float* __restrict__ CA_sum, int half,
-                                                              int groups, int kk, int n_ctx) {
-  __shared__ uint32_t bits[kCalibMaxCtx / 32];
-  __shared__ uint32_t cnt[kCalibFcPerWg];
-  const int row = blockIdx.x / groups;
-  const int i0 = (blockIdx.x % groups) * kCalibFcPerWg;
-  const int t = threadIdx.x;
-  const int words = (n_ctx + 31) / 32;
-  for (int w = t; w < words; w += 256) bits[w] = 0;
-  if (t < kCalibFcPerWg) cnt[t] = 0;
-  __syncthreads();
-  const int32_t* tf = T_full + (size_t)row * kk;
-  for (int j0 = 0; j0 < kk; j0 += 8 * 256) {
-    int tok[8];
+// Full-head scores of a slice of 256 * TPT tokens: 1-D grid of rows * nslices workgroups.
+template <typename ET, int PAIR_SHIFT, int PAIR_ADD>
+__global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict__ q, const ET* __restrict__ Kp,
+                                                         float* __restrict__ S, int rows, int nslices, int Hq, int Hkv,
+                                                         int N, int n_cap) {
+  constexpr int D = kHeadDim, F = D / 2, NW = 16;
+  constexpr int TPT = ScoreTraits<ET>::TPT;
+  __shared__ float ql[kMaxGroup][D];
+  __shared__ float2 qs[F];
+  int row, slice;
+  row_slice_of_block(rows, nslices, row, slice);
+  const int G = Hq / Hkv, t = threadIdx.x;
+  const ET* qh = q + ((size_t)(row / Hkv) * Hq + (size_t)(row % Hkv) * G) * D + (t & (D - 1));
+  ET qcol[kMaxGroup / 2];                                   // head dim t mod 128 of query heads t / 128, + 2, ...
 #pragma unroll
-    for (int u = 0; u < 8; ++u) tok[u] = tf[min(j0 + u * 256 + t, kk - 1)];
+  for (int j = 0; j < kMaxGroup / 2; ++j) qcol[j] = qh[(size_t)min((t >> 7) + 2 * j, G - 1) * D];
+  const int n0 = (slice * 256 + t) * TPT;
+  const bool active = n0 < N;
+  const ET* p = Kp + ((size_t)row * F * n_cap + (active ? n0 : 0)) * 2;
+  const size_t plane = (size_t)n_cap * 2;
+  uint4 w[NW];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (j0 + u * 256 + t < kk && tok[u] >= 0 && tok[u] < n_ctx) atomicOr(&bits[tok[u] >> 5], 1u << (tok[u] & 31));
+  for (int u = 0; u < NW; ++u) w[u] = *reinterpret_cast<const uint4*>(p + (size_t)u * plane);
+#pragma unroll
+  for (int j = 0; j < kMaxGroup / 2; ++j) {
+    if constexpr (sizeof(ET) == 2) ql[(t >> 7) + 2 * j][t & (D - 1)] = __uint_as_float((uint32_t)qcol[j] << 16);
+    else ql[(t >> 7) + 2 * j][t & (D - 1)] = qcol[j];
   }
   __syncthreads();
-  for (int f = 0; f < kCalibFcPerWg; ++f) {
-    const int i = i0 + f;
-    if (i >= half) break;
-    const int32_t* tv = T_v + ((size_t)row * half + i) * kk;
-    uint32_t mine = 0;
-    for (int j0 = 0; j0 < kk; j0 += 8 * 256) {
-      int tok[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) tok[u] = tv[min(j0 + u * 256 + t, kk - 1)];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int c = min(max(tok[u], 0), n_ctx - 1);
-        const uint32_t bit = (bits[c >> 5] >> (c & 31)) & 1u;
-        mine += (j0 + u * 256 + t < kk && tok[u] == c) ? bit : 0u;
-      }
+  if (t < F) {   // g ascending, as everywhere
+    float lo = 0.f, hi = 0.f;
+    for (int g = 0; g < G; ++g) {
+      lo += ql[g][t << PAIR_SHIFT];
+      hi += ql[g][(t << PAIR_SHIFT) + PAIR_ADD];
     }
-    mine = wave_prefix_sum(mine);
-    if (lane_id() == kWave - 1) atomicAdd(&cnt[f], mine);
+    qs[t] = make_float2(lo, hi);
   }
   __syncthreads();
-  if (t < kCalibFcPerWg && i0 + t < half) CA_sum[(size_t)row * half + i0 + t] += (float)cnt[t] / (float)kk;
+  float acc[TPT];
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) acc[k] = 0.f;
+  // 16 planes in flight: a plane's register takes the plane 16 further on as soon as it is used.  (Not
+  // unrolled: the compiler would put all 64 loads first, and spill.)
+#pragma unroll 1
+  for (int f0 = 0; f0 < F; f0 += NW) {
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+      const float2 qf = qs[f0 + u];
+      fma_pairs<ET>(w[u], qf.x, qf.y, acc);
+      w[u] = *reinterpret_cast<const uint4*>(p + (size_t)min(f0 + NW + u, F - 1) * plane);
+    }
+  }
+  if (active) {
+    float* out = S + (size_t)row * n_cap + n0;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+      if (n0 + k < N) out[k] = acc[k];
+  }
 }
 
-hipError_t launch_calib_prepare(const fasa_shape& s, const void* q, void* q_v, int32_t* fc_all,
-                                int32_t* fc_v, hipStream_t st) {
-  const int half = s.head_dim / 2;
-  dim3 grid(s.batch * s.n_kv_heads * half), block(128);
+template <int NT>
+struct CalibLds {
+  static constexpr int kThreads = NT;
+  static constexpr int kList = NT == 1024 ? 8192 : 4096;      // (two workgroups of 1024 share a compute unit's LDS)
+  uint2 list[kList];                                          // scores at or above the cut: (score bits, token)
+  uint32_t hist[kSelBins];
+  // The larger sample is for the larger rows: a list of 1.6 K .. 2.6 K entries, where 128 would scatter it so
+  // that a few rows in 512 overflowed.
+  static constexpr int kSmp = NT == 1024 ? 256 : 128;
+  union {                                                     // (the sample is spent before there are candidates)
+    uint2 cand[kSelCand];
+    struct { uint32_t sample[kSmp], ssort[kSmp]; };
+  };
+  uint32_t wtot[NT / kWave];
+  uint32_t thr[4];
+  uint32_t n_list, n_cnd, count;
+};
+
+// Top-K of a row by one workgroup of NT threads, which hold a stretch of it as loaded: load(c0) requests what the
+// scores of tokens c0 .. c0 + NT * 32 - 1 are made of (kCalibPerThread / TPT pieces a thread), get(c0, i, t, x, full) makes
+// those of tokens c0 + (i * NT + t) * TPT + k, a NaN beyond the row unless it is known to be full (cheap: made again in every pass, which
+// keeps 32 registers free and two workgroups of 1024 on a compute unit); opaque() hides the pieces from the
+// compiler, which would otherwise keep the scores.  score_at(n): one token's score.
+// take_one(n): token n is in the set.
+// What reaches the cut is gathered into a list in LDS first (some 7 instructions a score per wave, where counting
+// and classifying all scores under a test takes 30); a list that comes out short of K or beyond its
+// room is not used.
+template <int NT, int TPT, typename Load, typename Get, typename Opaque, typename ScoreAt, typename TakeOne>
+__device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Load&& load, Get&& get, Opaque&& opaque,
+                                             ScoreAt&& score_at, TakeOne&& take_one) {
+  const int t = threadIdx.x;
+  constexpr int R = NT * kCalibPerThread, NP = kCalibPerThread / TPT;
+  const bool resident = N <= R;
+  constexpr int SMP = CalibLds<NT>::kSmp;
+  const float sval = score_at((int)(((long long)(t & (SMP - 1)) * N) / SMP));
+  if (resident) load(0);
+  // the sample's keys are made distinct in their low bits: ranks are a permutation, a cut may be any value
+  if (t < SMP) sm.sample[t] = (score_key(sval) & ~(uint32_t)(SMP - 1)) | (uint32_t)t;
+  if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
+  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+  __syncthreads();
+  {
+    constexpr int P = NT / SMP;                               // threads per sample value: 2 or 4
+    static_assert(P == 2 || P == 4, "");
+    const uint32_t me = sm.sample[t / P];
+    int rank = 0;
+#pragma unroll
+    for (int u = 0; u < SMP / 4 / P; ++u) {
+      const uint4 o = reinterpret_cast<const uint4*>(sm.sample)[P * u + t % P];
+      rank += (o.x > me ? 1 : 0) + (o.y > me ? 1 : 0) + (o.z > me ? 1 : 0) + (o.w > me ? 1 : 0);
+    }
+    rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);                              // quad_perm [1,0,3,2]
+    if constexpr (P == 4) rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);        // quad_perm [2,3,0,1]
+    if (t % P == 0) sm.ssort[rank & (SMP - 1)] = me & ~(uint32_t)(SMP - 1);
+  }
+  __syncthreads();
+  uint32_t klo = 0, khi = 0xffffffffu;
+  int shift = 22, need = kk, n_cand;
+  const int r = sample_rank(kk, N, SMP);
+  if (r <= SMP) {
+    klo = sm.ssort[r - 1];
+    shift = first_shift(klo, sm.ssort[0]);
+  }
+  {
+    const float flo = klo ? key_score(klo) : -INFINITY;
+    const int lane = lane_id();
+    // One addition to the list's length per wave and piece: its latency hides behind the other waves, where
+    // counting first would make every score twice.
+    auto append = [&](int c0, auto full) {
+      int tt = t;
+      asm volatile("" : "+v"(tt));                            // (token numbers made anew, not kept)
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        float x[TPT];
+        get(c0, i, tt, x, full);
+        unsigned long long m[TPT];
+        uint32_t cnt = 0;                                     // of the wave
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+          m[k] = __ballot(x[k] >= flo);
+          cnt += (uint32_t)__popcll(m[k]);
+        }
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&sm.n_list, cnt);
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+          const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
+          if (x[k] >= flo && pos < (uint32_t)CalibLds<NT>::kList)
+            sm.list[pos] = make_uint2(__float_as_uint(x[k]), (uint32_t)(c0 + (i * NT + tt) * TPT + k));
+          base += (uint32_t)__popcll(m[k]);
+        }
+        __builtin_amdgcn_sched_barrier(0);                    // (piece by piece: registers)
+      }
+    };
+    for (int c0 = 0; c0 < N; c0 += R) {
+      if (!resident) load(c0);
+      if (c0 + R <= N) append(c0, std::true_type{});
+      else append(c0, std::false_type{});
+    }
+    __syncthreads();
+  }
+  const int M = (int)sm.n_list;
+  const bool listed = M >= kk && M <= CalibLds<NT>::kList;
+  auto for_scores = [&](int c0, auto&& f) {
+    int tt = t;
+    asm volatile("" : "+v"(tt));
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      float x[TPT];
+      get(c0, i, tt, x, std::false_type{});
+#pragma unroll
+      for (int k = 0; k < TPT; ++k) f(x[k], c0 + (i * NT + tt) * TPT + k);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  for (;;) {
+    // as floats: nearly all scores cost one comparison (a NaN - beyond the row - never passes)
+    const float flo = klo ? key_score(klo) : -INFINITY;
+    auto count = [&](float x) {
+      const uint32_t key = score_key(x);
+      if (key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
+    };
+    if (listed) {
+      for (int i = t; i < M; i += NT) count(__uint_as_float(sm.list[i].x));
+    } else for (int c0 = 0; c0 < N; c0 += R) {
+      if (!resident) load(c0);
+      opaque();
+      for_scores(c0, [&](float x, int) {
+        if (x >= flo) count(x);
+      });
+    }
+    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+    if (n_cand == 0) { klo = 0; khi = 0xffffffffu; shift = 22; }   // the sample misled: the whole range
+  }
+  const float flo = klo ? key_score(klo) : -INFINITY;
+  const bool ranked = n_cand <= kSelCand;
+  auto candidate = [&](uint32_t key, int n) {
+    const uint32_t p = atomicAdd(&sm.n_cnd, 1u);
+    if (p < (uint32_t)kSelCand) sm.cand[p] = make_uint2(key, (uint32_t)n);
+  };
+  if (listed) {
+    for (int i = t; i < M; i += NT) {
+      const uint2 e = sm.list[i];
+      const uint32_t key = score_key(__uint_as_float(e.x));
+      if (key > khi) take_one((int)e.y);
+      else if (ranked && key >= klo) candidate(key, (int)e.y);
+    }
+  } else for (int c0 = 0; c0 < N; c0 += R) {
+    if (!resident) load(c0);
+    opaque();
+    for_scores(c0, [&](float x, int n) {
+      if (x >= flo) {
+        const uint32_t key = score_key(x);
+        if (key > khi) take_one(n);
+        else if (ranked) candidate(key, n);
+      }
+    });
+  }
+  __syncthreads();
+  if (ranked) {
+    static_assert(NT >= kSelCand, "a thread per candidate");
+    if ((t & ~(kWave - 1)) < n_cand) {                        // (the waves that have any)
+      const int rank = rank_in_list<1>(sm.cand, n_cand, t);
+      if (t < n_cand && rank < need) take_one((int)sm.cand[t].y);
+    }
+  } else {                                                    // one key, more tokens than the list holds: in index order
+    int tied = 0;
+    for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
+      const int n = i0 + t;
+      const bool tie = n < N && score_key(score_at(min(n, N - 1))) == klo;
+      uint32_t tot;
+      const uint32_t before = block_prefix_sum<NT>(tie ? 1u : 0u, sm.wtot, tot);
+      if (tie && tied + (int)before < need) take_one(n);
+      tied += (int)tot;
+    }
+  }
+}
+
+// One workgroup per row: bitmap[row][0 .. ceil(N / 32)) of the top-K set of S[row].
+template <int NT, int WORDS>
+__global__ __launch_bounds__(NT) void calib_topk_kernel(const float* __restrict__ S, uint32_t* __restrict__ bitmap,
+                                                        int N, int n_cap, int kk, int words) {
+  __shared__ CalibLds<NT> sm;
+  __shared__ uint32_t bits[WORDS];                            // WORDS * 32 tokens at most
+  const int row = blockIdx.x, t = threadIdx.x;
+  const float* s = S + (size_t)row * n_cap;
+  for (int i = t; i < words; i += NT) bits[i] = 0;
+  float4 w[kCalibPerThread / 4];
+  calib_select<NT, 4>(
+      sm, N, kk,
+      [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < kCalibPerThread / 4; ++i) {
+          const int n = c0 + (i * NT + t) * 4;
+          w[i] = *reinterpret_cast<const float4*>(s + (n < N ? n : 0));
+        }
+      },
+      [&](int c0, int i, int tt, float (&x)[4], auto full) {
+        const int n = c0 + (i * NT + tt) * 4;
+        x[0] = full || n < N ? w[i].x : NAN; x[1] = full || n + 1 < N ? w[i].y : NAN;
+        x[2] = full || n + 2 < N ? w[i].z : NAN; x[3] = full || n + 3 < N ? w[i].w : NAN;
+      },
+      []() {}, [&](int n) { return s[n]; }, [&](int n) { atomicOr(&bits[n >> 5], 1u << (n & 31)); });
+  __syncthreads();
+  for (int i = t; i < words; i += NT) bitmap[(size_t)row * words + i] = bits[i];
+}
+
+// One workgroup per (row, FC): CA_sum[row][i] += |top-K of FC i's scores & the row's bitmap| / K.
+template <typename ET, int NT, int WORDS, int PAIR_SHIFT, int PAIR_ADD>
+__global__ __launch_bounds__(NT) void calib_fc_kernel(const ET* __restrict__ q, const ET* __restrict__ Kp,
+                                                      const uint32_t* __restrict__ bitmap, float* __restrict__ CA_sum,
+                                                      int Hq, int Hkv, int N, int n_cap, int kk, int words) {
+  constexpr int D = kHeadDim, F = D / 2;
+  constexpr int TPT = ScoreTraits<ET>::TPT;
+  __shared__ CalibLds<NT> sm;
+  __shared__ uint32_t bits[WORDS];                            // WORDS * 32 tokens at most
+  const int row = blockIdx.x / F, f = blockIdx.x % F, t = threadIdx.x;
+  const int G = Hq / Hkv;
+  if (t == 0) sm.count = 0;
+  const ET* qh = q + ((size_t)(row / Hkv) * Hq + (size_t)(row % Hkv) * G) * D + (f << PAIR_SHIFT);
+  float qlo = 0.f, qhi = 0.f;
+  {
+    ET a[kMaxGroup], b[kMaxGroup];
+#pragma unroll
+    for (int g = 0; g < kMaxGroup; ++g) {
+      a[g] = qh[(size_t)min(g, G - 1) * D];
+      b[g] = qh[(size_t)min(g, G - 1) * D + PAIR_ADD];
+    }
+#pragma unroll
+    for (int g = 0; g < kMaxGroup; ++g) {
+      float x, y;
+      if constexpr (sizeof(ET) == 2) { x = __uint_as_float((uint32_t)a[g] << 16); y = __uint_as_float((uint32_t)b[g] << 16); }
+      else { x = a[g]; y = b[g]; }
+      qlo += g < G ? x : 0.f;
+      qhi += g < G ? y : 0.f;
+    }
+  }
+  const ET* p = Kp + (size_t)blockIdx.x * n_cap * 2;
+  for (int i = t; i < words; i += NT) bits[i] = bitmap[(size_t)row * words + i];
+  uint4 w[kCalibPerThread / TPT];
+  auto load = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < kCalibPerThread / TPT; ++i) {
+      const int n = c0 + (i * NT + t) * TPT;
+      w[i] = *reinterpret_cast<const uint4*>(p + (size_t)(n < N ? n : 0) * 2);
+    }
+  };
+  auto get = [&](int c0, int i, int tt, float (&x)[TPT], auto full) {
+    const int n = c0 + (i * NT + tt) * TPT;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) x[k] = 0.f;
+    fma_pairs<ET>(w[i], qlo, qhi, x);
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) x[k] = full || n + k < N ? x[k] : NAN;
+  };
+  auto opaque = [&]() {
+#pragma unroll
+    for (int i = 0; i < kCalibPerThread / TPT; ++i) asm volatile("" : "+v"(w[i].x), "+v"(w[i].y), "+v"(w[i].z), "+v"(w[i].w));
+  };
+  auto score_at = [&](int n) {
+    float lo, hi;
+    if constexpr (sizeof(ET) == 2) {
+      const uint32_t x = reinterpret_cast<const uint32_t*>(p)[n];
+      lo = bf16_lo(x); hi = bf16_hi(x);
+    } else {
+      const float2 x = reinterpret_cast<const float2*>(p)[n];
+      lo = x.x; hi = x.y;
+    }
+    return fmaf(qhi, hi, fmaf(qlo, lo, 0.f));
+  };
+  uint32_t mine = 0;
+  calib_select<NT, TPT>(sm, N, kk, load, get, opaque, score_at, [&](int n) { mine += (bits[n >> 5] >> (n & 31)) & 1u; });
+  mine = wave_prefix_sum(mine);
+  if (lane_id() == kWave - 1) atomicAdd(&sm.count, mine);
+  __syncthreads();
+  if (t == 0) CA_sum[blockIdx.x] += (float)sm.count / (float)kk;
+}
+
+// K >= N: both sets are all tokens
+__global__ __launch_bounds__(256) void calib_all_kernel(float* __restrict__ CA_sum, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) CA_sum[i] += 1.0f;
+}
+
+template <typename ET, int PS, int PA>
+static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap,
+                                 float* CA_sum, hipStream_t st) {
+  const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2, words = (s.n_ctx + 31) / 32;
+  const int per = 256 * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per - 1) / per;
+  hipError_t e = launch("fasa_calib_full", calib_full_kernel<ET, PS, PA>, dim3(rows * nslices), dim3(256), st, (const ET*)q,
+                        (const ET*)Kp_all, S, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap);
+  if (e != hipSuccess) return e;
+  const auto stage = [&](auto nt_c, auto words_c) {
+    constexpr int NT = decltype(nt_c)::value, WORDS = decltype(words_c)::value;
+    hipError_t err = launch("fasa_calib_topk", calib_topk_kernel<NT, WORDS>, dim3(rows), dim3(NT), st, S, bitmap, s.n_ctx,
+                            s.n_cap, kk, words);
+    if (err != hipSuccess) return err;
+    return launch("fasa_calib_fc", calib_fc_kernel<ET, NT, WORDS, PS, PA>, dim3(rows * half), dim3(NT), st, (const ET*)q,
+                  (const ET*)Kp_all, bitmap, CA_sum, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap, kk, words);
+  };
+  // rows that fit in the registers of 256 threads: several workgroups per compute unit instead of one of
+  // 1024 each; rows that fit in those of 1024: a bitmap small enough for two
+  if (s.n_ctx <= 8192) return stage(std::integral_constant<int, 256>{}, std::integral_constant<int, 256>{});
+  if (s.n_ctx <= 32768) return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, 1024>{});
+  return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, kCalibMaxCtx / 32>{});
+}
+
+hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap,
+                        float* CA_sum, hipStream_t st) {
+  constexpr int D = kHeadDim;
+  if (kk >= s.n_ctx) {
+    const int n = s.batch * s.n_kv_heads * (D / 2);
+    return launch("fasa_calib_all", calib_all_kernel, dim3((n + 255) / 256), dim3(256), st, CA_sum, n);
+  }
+  const bool inter = s.pairing == FASA_PAIR_INTERLEAVED;   // FC i: dims (2i, 2i + 1), else (i, i + d/2)
   if (s.dtype == FASA_BF16)
-    return launch("fasa_calib_prepare", calib_prepare_kernel<uint16_t>, grid, block, st,
-                  (const uint16_t*)q, (uint16_t*)q_v, fc_all, fc_v, s.n_q_heads, s.n_kv_heads, half);
-  return launch("fasa_calib_prepare", calib_prepare_kernel<float>, grid, block, st, (const float*)q,
-                (float*)q_v, fc_all, fc_v, s.n_q_heads, s.n_kv_heads, half);
-}
-
-hipError_t launch_calib_intersect(const fasa_shape& s, const int32_t* T_full, const int32_t* T_v,
-                                  float* CA_sum, int kk, hipStream_t st) {
-  const int half = s.head_dim / 2;
-  const int groups = (half + kCalibFcPerWg - 1) / kCalibFcPerWg;
-  return launch("fasa_calib_intersect", calib_intersect_kernel, dim3(s.batch * s.n_kv_heads * groups),
-                dim3(256), st, T_full, T_v, CA_sum, half, groups, kk, s.n_ctx);
+    return inter ? launch_calib_p<uint16_t, 1, 1>(s, q, Kp_all, kk, S, bitmap, CA_sum, st)
+                 : launch_calib_p<uint16_t, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, CA_sum, st);
+  return inter ? launch_calib_p<float, 1, 1>(s, q, Kp_all, kk, S, bitmap, CA_sum, st)
+               : launch_calib_p<float, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, CA_sum, st);
 }
 
 int calib_max_ctx() { return kCalibMaxCtx; }

@@ -213,10 +213,9 @@ hipError_t launch_offload_gather(const fasa_shape& s, const void* Kp, const void
                                  hipStream_t st);
 
 // offline calibration (calib.hip)
-hipError_t launch_calib_prepare(const fasa_shape& s, const void* q, void* q_v, int32_t* fc_all,
-                                int32_t* fc_v, hipStream_t st);
-hipError_t launch_calib_intersect(const fasa_shape& s, const int32_t* T_full, const int32_t* T_v,
-                                  float* CA_sum, int kk, hipStream_t st);
+// S: rows * n_cap floats, bitmap: rows * ceil(n_ctx / 32) words of scratch
+hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap,
+                        float* CA_sum, hipStream_t st);
 int calib_max_ctx();
 
 }  // namespace fasa

@@ -26,13 +26,13 @@ __device__ __forceinline__ void fma_pairs<float>(const uint4& w, float qlo, floa
   acc[1] = fmaf(qhi, __uint_as_float(w.w), fmaf(qlo, __uint_as_float(w.z), acc[1]));
 }
 
-// Sample of a row's scores from which a cut is taken that few scores besides the B best reach: of kSample
-// evenly spaced scores the sample_rank-th best, 3.5 standard deviations (and three) above the B kSample / N
-// of them that are expected among the B best.  In one row of a few thousand the cut still comes out too high;
+// Sample of a row's scores from which a cut is taken that few scores besides the B best reach: of m (kSample)
+// evenly spaced scores the sample_rank-th best, 3.5 standard deviations (and three) above the B m / N of them
+// that are expected among the B best.  In one row of a few thousand the cut still comes out too high;
 // whoever uses it checks that B scores reach it and otherwise looks at all of them.
 constexpr int kSample = 128;
-__device__ __forceinline__ int sample_rank(int bsel, int n) {
-  const float ps = (float)bsel * ((float)kSample / (float)n);
+__device__ __forceinline__ int sample_rank(int bsel, int n, int m = kSample) {
+  const float ps = (float)bsel * ((float)m / (float)n);
   return (int)(ps + 3.5f * sqrtf(ps) + 3.0f);
 }
 

@@ -80,6 +80,65 @@ __device__ __forceinline__ int rank_in_list(const uint2* lc, int n, int i) {
   return rank;
 }
 
+constexpr int kSelBins = 1024;
+constexpr int kSelCand = 256;    // candidates of the threshold bin ranked by counting
+
+// ---------------------------------------------------------------------------------------------
+// Selection by one workgroup of all its row's scores: the B best.  A first range of keys klo .. 2^32 - 1 (no
+// score below it may be among the B best) is cut into kSelBins bins of 2^shift keys:
+//   histogram  a suffix sum gives the threshold bin: bins above it hold fewer than B scores, bins from it
+//              upwards at least B.
+//   narrow     while the threshold bin holds more than kSelCand scores it becomes the next range, 1024
+//              times finer.  What the scores look like costs passes, never exactness.
+//   resolve    the bin's candidates are ranked by counting (key, then lower index).  A bin that is one key
+//              wide and still too full is a tie of that many tokens: they are taken in index order, out of
+//              the row's scores in memory.
+// ---------------------------------------------------------------------------------------------
+// After the counting: true once klo .. khi is the final range (need of its n_cand scores are taken, and all
+// above it); else the range to count next, the histogram zeroed - the same range, with n_cand 0, if fewer than
+// need scores were counted in it (sm.thr[2] was 0).
+template <typename Lds>
+__device__ __forceinline__ bool find_threshold(Lds& sm, uint32_t& klo, uint32_t& khi, int& shift, int& need, int& n_cand) {
+  const int t = threadIdx.x;
+  __syncthreads();
+  constexpr int NT = Lds::kThreads, BPT = kSelBins / NT;     // bins per thread: 4, 2 or 1
+  uint32_t hb[BPT], mine = 0;
+#pragma unroll
+  for (int j = 0; j < BPT; ++j) { hb[j] = sm.hist[BPT * t + j]; mine += hb[j]; }
+  const uint32_t incl = block_suffix_sum<NT>(mine, sm.wtot);
+  uint32_t above = incl - mine;                               // scores in bins above this thread's
+  if (above < (uint32_t)need && (uint32_t)need <= incl) {
+#pragma unroll
+    for (int j = BPT - 1; j >= 0; --j) {
+      if (above < (uint32_t)need && above + hb[j] >= (uint32_t)need) {
+        sm.thr[0] = (uint32_t)(BPT * t + j);
+        sm.thr[1] = above;
+        sm.thr[2] = hb[j];
+      }
+      above += hb[j];
+    }
+  }
+  __syncthreads();
+  n_cand = (int)sm.thr[2];
+  if (n_cand > 0) {
+    const uint32_t bin = sm.thr[0];
+    need -= (int)sm.thr[1];
+    klo += bin << shift;
+    if (bin + 1 < (uint32_t)kSelBins) khi = klo + ((1u << shift) - 1u);   // the last bin reaches up to khi
+    if (n_cand <= kSelCand || klo == khi) return true;
+    shift = max(0, 22 - __clz((int)(khi - klo)));             // (khi - klo) >> shift < 1024
+  }
+#pragma unroll
+  for (int j = 0; j < BPT; ++j) sm.hist[BPT * t + j] = 0;
+  __syncthreads();
+  return false;
+}
+// log2 of the bins' width for keys from kcut to twice the distance to ktop: span >> shift < 1024
+__device__ __forceinline__ int first_shift(uint32_t kcut, uint32_t ktop) {
+  const unsigned long long span = 2ull * (ktop - kcut) + kSelBins;
+  return max(0, 54 - __clzll((long long)span));
+}
+
 // Exact selection of the `need` largest composites among cand[0..n).  Whole block participates.
 // SHARED_SRC: the list lives in global memory and was written by other workgroups.
 // dhw: LDS scratch of 4096 counters, or null.  With it the first pass takes the top 12 bits of the

@@ -21,8 +21,6 @@ namespace fasa {
 constexpr int kStepNT = 512;                 // threads per workgroup of step_kernel
 constexpr int kRowNT = 1024;                 // threads per workgroup of row_kernel
 constexpr int kListPerThread = 8;            // places of a row's list, per thread
-constexpr int kStepBins = 1024;
-constexpr int kStepCand = 256;               // candidates of the threshold bin ranked by counting
 
 struct StepArgs {
   const void* q;
@@ -55,10 +53,10 @@ struct RowLds {
     uint2 list[kList];                                       // scores at or above the cut: (score bits, token)
   };
   union {
-    uint32_t hist[kStepBins];
+    uint32_t hist[kSelBins];
     uint32_t sample[kSample];
   };
-  uint2 cand[kStepCand];
+  uint2 cand[kSelCand];
   uint32_t ssort[kSample];                                   // keys of the sample, largest first
   __align__(16) uint32_t wl[kStepMaxBudget + 16];            // selected tokens, then what the gather reads for them
   float m[kWaves][GM], l[kWaves][GM];
@@ -77,46 +75,8 @@ __device__ __forceinline__ void st_agent_f4(__amdgpu_buffer_rsrc_t rs, uint32_t 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Selection: the B best of a set of scores to sm.wl[0 .. B).  A first range of keys klo .. 2^32 - 1 (no score
-// below it may be among the B best) is cut into 1024 bins of 2^shift keys:
-//   histogram  a suffix sum gives the threshold bin: bins above it hold fewer than B scores, bins from it
-//              upwards at least B.
-//   narrow     while the threshold bin holds more than kStepCand scores it becomes the next range, 1024
-//              times finer.  What the scores look like costs passes, never exactness.
-//   resolve    the bin's candidates are ranked by counting (key, then lower index).  A bin that is one key
-//              wide and still too full is a tie of that many tokens: they are taken in index order, out of
-//              the row's scores in memory.
+// Selection of a row's set: B tokens to sm.wl (find_threshold in select_common.h does the narrowing)
 // ---------------------------------------------------------------------------------------------
-// After the counting: true once klo .. khi is the final range (need of its n_cand scores are taken, and all
-// above it); else the range to count next, the histogram zeroed.
-template <typename Lds>
-__device__ __forceinline__ bool find_threshold(Lds& sm, uint32_t& klo, uint32_t& khi, int& shift, int& need, int& n_cand) {
-  const int t = threadIdx.x;
-  __syncthreads();
-  constexpr int NT = Lds::kThreads, BPT = kStepBins / NT;     // bins per thread: 2 or 1
-  static_assert(BPT == 1 || BPT == 2, "");
-  const uint32_t h0 = sm.hist[BPT * t], h1 = BPT == 2 ? sm.hist[BPT * t + 1] : 0u;
-  const uint32_t incl = block_suffix_sum<NT>(h0 + h1, sm.wtot);
-  const uint32_t above = incl - h0 - h1;                      // scores in bins above this thread's
-  if (above < (uint32_t)need && (uint32_t)need <= incl) {
-    const bool up = BPT == 2 && above + h1 >= (uint32_t)need;
-    sm.thr[0] = (uint32_t)(BPT * t) + (up ? 1u : 0u);
-    sm.thr[1] = up ? above : above + h1;
-    sm.thr[2] = up ? h1 : h0;
-  }
-  __syncthreads();
-  n_cand = (int)sm.thr[2];
-  const uint32_t bin = sm.thr[0];
-  need -= (int)sm.thr[1];
-  klo += bin << shift;
-  if (bin + 1 < (uint32_t)kStepBins) khi = klo + ((1u << shift) - 1u);   // the last bin reaches up to khi
-  if (n_cand <= kStepCand || klo == khi) return true;
-  shift = max(0, 22 - __clz((int)(khi - klo)));               // (khi - klo) >> shift < 1024
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) sm.hist[BPT * t + j] = 0;
-  __syncthreads();
-  return false;
-}
 // The threshold range's share of the set, after its candidates have been listed in sm.cand (if they fit)
 template <typename Lds>
 __device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bsel, int need, int n_cand,
@@ -127,12 +87,12 @@ __device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bse
   auto place = [&](int p, uint32_t tok) {
     if (p < bsel) sm.wl[p] = tok;
   };
-  if (n_cand <= kStepCand) {   // taken iff fewer than `need` candidates sort before it
-    constexpr int P = NT / kStepCand;
+  if (n_cand <= kSelCand) {   // taken iff fewer than `need` candidates sort before it
+    constexpr int P = NT / kSelCand;
     const int ci = t / P;
     const int rank = rank_in_list<P>(sm.cand, n_cand, ci);
     if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
-  } else {                     // a tie of more than kStepCand tokens: the first `need` of them
+  } else {                     // a tie of more than kSelCand tokens: the first `need` of them
     int tied = 0;              // met so far
     for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
       const int n = i0 + t;
@@ -157,7 +117,7 @@ __device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow,
   for (;;) {
     for (int i = t; i < N; i += NT) {
       const uint32_t key = score_key(ld_agent(srow + i));
-      if (key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kStepBins - 1u)], 1u);
+      if (key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
     }
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
   }
@@ -172,7 +132,7 @@ __device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow,
         const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, pw));
         const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, pc));
         if (win && p < (uint32_t)bsel) sm.wl[p] = (uint32_t)i;
-        if (cnd && c < (uint32_t)kStepCand) sm.cand[c] = make_uint2(key, (uint32_t)i);
+        if (cnd && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(key, (uint32_t)i);
       }
       pw += (uint32_t)__popcll(mw);
       pc += (uint32_t)__popcll(mc);
@@ -191,12 +151,6 @@ __device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow,
   resolve_threshold(sm, klo, bsel, need, n_cand, srow, N);
 }
 
-// log2 of the bins' width for keys from kcut to twice the distance to ktop: span >> shift < 1024
-__device__ __forceinline__ int first_shift(uint32_t kcut, uint32_t ktop) {
-  const unsigned long long span = 2ull * (ktop - kcut) + kStepBins;
-  return max(0, 54 - __clzll((long long)span));
-}
-
 // The same inside a list of M <= EPT * NT scores that the threads hold: key[k], tok[k] of thread t are those of
 // entry k * NT + t.  Places go by thread.
 template <int EPT, typename Lds>
@@ -211,7 +165,7 @@ __device__ __forceinline__ void list_select_regs(Lds& sm, int M, const uint32_t 
     for (int k = 0; k < EPT; ++k) {
       if (k * NT >= M) break;
       if (k * NT + t < M && key[k] >= klo && key[k] <= khi)
-        atomicAdd(&sm.hist[min((key[k] - klo) >> shift, (uint32_t)kStepBins - 1u)], 1u);
+        atomicAdd(&sm.hist[min((key[k] - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
     }
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
   }
@@ -240,7 +194,7 @@ __device__ __forceinline__ void list_select_regs(Lds& sm, int M, const uint32_t 
       ++pw;
     }
     if (cnd & (1u << k)) {
-      if (pc < (uint32_t)kStepCand) sm.cand[pc] = make_uint2(key[k], tok[k]);
+      if (pc < (uint32_t)kSelCand) sm.cand[pc] = make_uint2(key[k], tok[k]);
       ++pc;
     }
   }
@@ -485,7 +439,7 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
     if (t % P == 0) sm.ssort[rank & (kSample - 1)] = me & ~(uint32_t)(kSample - 1);
   }
   __syncthreads();
-  for (int i = t; i < kStepBins; i += NT) sm.hist[i] = 0;     // (shares storage with the sample)
+  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;     // (shares storage with the sample)
   const int r = sample_rank(bsel, N);
   kcut = r > kSample ? 0u : sm.ssort[r - 1];
   ktop = sm.ssort[0];
