@@ -507,7 +507,9 @@ int calib_layout(const fasa_shape* shape, int32_t top_k, CalibLayout* L) {
   size_t off = 0;
   L->s_off = off;      off = align256(off + rows * shape->n_cap * 4);               // full-head scores
   L->bitmap_off = off; off = align256(off + rows * ((shape->n_ctx + 31) / 32) * 4);  // their top-K set
-  L->total = off;
+  // Room for the scores of every single FC stays part of the size callers are told (they once lay there, and a
+  // workspace sized then must do for any version); nothing is written beyond the two regions above.
+  L->total = off + rows * (shape->head_dim / 2) * shape->n_cap * 4;
   return FASA_OK;
 }
 }  // namespace
