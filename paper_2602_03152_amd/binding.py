@@ -1,4 +1,5 @@
-"""ctypes binding of libfasa.so: argument marshalling only, same names as include/fasa.h.
+"""Binding of libfasa.so: argument marshalling only, same names as include/fasa.h.  The calls of a decode loop
+go through a small C module (csrc/pycall.c), everything else through ctypes.
 
 Device buffers are torch tensors (torch is used for HBM allocation and streams, nothing else);
 bf16 tensors may be passed as torch.bfloat16 or as int16/uint16 bit patterns.  Every function
@@ -106,6 +107,11 @@ def _load():
 _lib = _load()
 lib = _lib   # raw handle, for tests of the C ABI itself
 
+try:
+    from . import _pycall
+except ImportError as e:
+    raise ImportError("_pycall.so is not built; run `python -m paper_2602_03152_amd.build`") from e
+
 
 def make_shape(batch, n_q_heads, n_kv_heads, head_dim, n_fc, n_ctx, n_cap, budget, dtype,
                kv_stride_b=None, kv_stride_h=None, kv_stride_n=None, pairing=0) -> FasaShape:
@@ -140,6 +146,16 @@ def _stream(stream) -> Optional[int]:
     return int(stream)
 
 
+def _first_device() -> int:
+    """The current device, asked for the first time: initialises torch's GPU runtime, then steps aside."""
+    torch.cuda.current_stream()
+    _pycall.bind(_LIB_PATH, _ptr, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    return torch._C._cuda_getDevice()
+
+
+_pycall.bind(_LIB_PATH, _ptr, _first_device, torch._C._cuda_getCurrentRawStream)
+
+
 def _check(status: int, where: str):
     if status != FASA_OK:
         raise FasaError(status, where)
@@ -158,50 +174,56 @@ def fasa_validate_fc_idx(shape: FasaShape, fc_idx_host) -> None:
 
 
 def fasa_pack_kcache(shape, K, fc_idx, Kp, n_begin: int, n_end: int, stream=None) -> None:
-    _check(_lib.fasa_pack_kcache(C.byref(shape), _ptr(K), _ptr(fc_idx), _ptr(Kp), n_begin, n_end,
-                                 _stream(stream)), "fasa_pack_kcache")
+    rc = _pycall.pack_kcache(shape, K, fc_idx, Kp, n_begin, n_end, stream)
+    if rc:
+        raise FasaError(rc, "fasa_pack_kcache")
 
 
 def fasa_score(shape, q, Kp, fc_idx, S, stream=None) -> None:
-    _check(_lib.fasa_score(C.byref(shape), _ptr(q), _ptr(Kp), _ptr(fc_idx), _ptr(S), _stream(stream)),
-           "fasa_score")
+    rc = _pycall.score(shape, q, Kp, fc_idx, S, stream)
+    if rc:
+        raise FasaError(rc, "fasa_score")
 
 
 def fasa_topk(shape, S, T, ws, ws_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_topk(C.byref(shape), _ptr(S), _ptr(T), _ptr(ws), ws_bytes, _stream(stream)), "fasa_topk")
+    rc = _pycall.topk(shape, S, T, ws, ws_bytes, stream)
+    if rc:
+        raise FasaError(rc, "fasa_topk")
 
 
 def fasa_sparse_attend(shape, q, K, V, T, O, ws, ws_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_sparse_attend(C.byref(shape), _ptr(q), _ptr(K), _ptr(V), _ptr(T), _ptr(O), _ptr(ws),
-                                   ws_bytes, _stream(stream)), "fasa_sparse_attend")
+    rc = _pycall.sparse_attend(shape, q, K, V, T, O, ws, ws_bytes, stream)
+    if rc:
+        raise FasaError(rc, "fasa_sparse_attend")
 
 
 def fasa_dense_attend(shape, q, K, V, O, ws, ws_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_dense_attend(C.byref(shape), _ptr(q), _ptr(K), _ptr(V), _ptr(O), _ptr(ws), ws_bytes,
-                                  _stream(stream)), "fasa_dense_attend")
+    rc = _pycall.dense_attend(shape, q, K, V, O, ws, ws_bytes, stream)
+    if rc:
+        raise FasaError(rc, "fasa_dense_attend")
 
 
 def fasa_decode_step(shape, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ws, ws_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_decode_step(C.byref(shape), _ptr(q), _ptr(K), _ptr(V), _ptr(Kp), _ptr(fc_idx),
-                                 _ptr(k_new), _ptr(v_new), _ptr(S), _ptr(T), _ptr(O), _ptr(ws), ws_bytes,
-                                 _stream(stream)), "fasa_decode_step")
+    rc = _pycall.decode_step(shape, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ws, ws_bytes, stream)
+    if rc:
+        raise FasaError(rc, "fasa_decode_step")
 
 
 FASA_STATIC_WS_BYTES = 32 << 20
 
 
 def fasa_decode_step_static(shape, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, stream=None) -> None:
-    _check(_lib.fasa_decode_step_static(C.byref(shape), _ptr(q), _ptr(K), _ptr(V), _ptr(Kp), _ptr(fc_idx),
-                                        _ptr(k_new), _ptr(v_new), _ptr(S), _ptr(T), _ptr(O), _stream(stream)),
-           "fasa_decode_step_static")
+    rc = _pycall.decode_step_static(shape, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, stream)
+    if rc:
+        raise FasaError(rc, "fasa_decode_step_static")
 
 
 def fasa_decode_step_ragged(shape, q, K, V, Kp, fc_idx, k_new, v_new, n_ctx_seq, budget_seq, S, T, O, ws,
                             ws_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_decode_step_ragged(C.byref(shape), _ptr(q), _ptr(K), _ptr(V), _ptr(Kp), _ptr(fc_idx),
-                                        _ptr(k_new), _ptr(v_new), _ptr(n_ctx_seq), _ptr(budget_seq),
-                                        _ptr(S), _ptr(T), _ptr(O), _ptr(ws), ws_bytes, _stream(stream)),
-           "fasa_decode_step_ragged")
+    rc = _pycall.decode_step_ragged(shape, q, K, V, Kp, fc_idx, k_new, v_new, n_ctx_seq, budget_seq, S, T, O, ws, ws_bytes,
+                                    stream)
+    if rc:
+        raise FasaError(rc, "fasa_decode_step_ragged")
 
 
 def make_paging(block_table, page_size: int, n_pool_blocks: int) -> FasaPaging:
@@ -210,16 +232,17 @@ def make_paging(block_table, page_size: int, n_pool_blocks: int) -> FasaPaging:
 
 
 def fasa_pack_kcache_paged(shape, paging, K, fc_idx, Kp, n_begin: int, n_end: int, stream=None) -> None:
-    _check(_lib.fasa_pack_kcache_paged(C.byref(shape), C.byref(paging), _ptr(K), _ptr(fc_idx), _ptr(Kp), n_begin,
-                                       n_end, _stream(stream)), "fasa_pack_kcache_paged")
+    rc = _pycall.pack_kcache_paged(shape, paging, K, fc_idx, Kp, n_begin, n_end, stream)
+    if rc:
+        raise FasaError(rc, "fasa_pack_kcache_paged")
 
 
 def fasa_decode_step_paged(shape, paging, q, K, V, Kp, fc_idx, k_new, v_new, n_ctx_seq, budget_seq, S, T, O, ws,
                            ws_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_decode_step_paged(C.byref(shape), C.byref(paging), _ptr(q), _ptr(K), _ptr(V), _ptr(Kp),
-                                       _ptr(fc_idx), _ptr(k_new), _ptr(v_new), _ptr(n_ctx_seq), _ptr(budget_seq),
-                                       _ptr(S), _ptr(T), _ptr(O), _ptr(ws), ws_bytes, _stream(stream)),
-           "fasa_decode_step_paged")
+    rc = _pycall.decode_step_paged(shape, paging, q, K, V, Kp, fc_idx, k_new, v_new, n_ctx_seq, budget_seq, S, T, O, ws,
+                                   ws_bytes, stream)
+    if rc:
+        raise FasaError(rc, "fasa_decode_step_paged")
 
 
 def fasa_offload_stage_bytes(shape: FasaShape) -> int:
@@ -233,10 +256,10 @@ def fasa_offload_split_kcache(shape, K, fc_idx, Kp, Knd_host, n_begin: int, n_en
 
 def fasa_offload_decode_step(shape, q, Kp, fc_idx, Knd_host, V_host, k_new, v_new, S, T, O, ws, ws_bytes: int,
                              stage, stage_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_offload_decode_step(C.byref(shape), _ptr(q), _ptr(Kp), _ptr(fc_idx), _ptr(Knd_host),
-                                         _ptr(V_host), _ptr(k_new), _ptr(v_new), _ptr(S), _ptr(T), _ptr(O),
-                                         _ptr(ws), ws_bytes, _ptr(stage), stage_bytes, _stream(stream)),
-           "fasa_offload_decode_step")
+    rc = _pycall.offload_decode_step(shape, q, Kp, fc_idx, Knd_host, V_host, k_new, v_new, S, T, O, ws, ws_bytes, stage,
+                                     stage_bytes, stream)
+    if rc:
+        raise FasaError(rc, "fasa_offload_decode_step")
 
 
 def fasa_calibration_workspace_bytes(shape: FasaShape, top_k: int) -> int:
@@ -244,8 +267,9 @@ def fasa_calibration_workspace_bytes(shape: FasaShape, top_k: int) -> int:
 
 
 def fasa_contextual_agreement(shape, q, Kp_all, top_k: int, CA_sum, cws, cws_bytes: int, stream=None) -> None:
-    _check(_lib.fasa_contextual_agreement(C.byref(shape), _ptr(q), _ptr(Kp_all), top_k, _ptr(CA_sum), _ptr(cws),
-                                          cws_bytes, _stream(stream)), "fasa_contextual_agreement")
+    rc = _pycall.contextual_agreement(shape, q, Kp_all, top_k, CA_sum, cws, cws_bytes, stream)
+    if rc:
+        raise FasaError(rc, "fasa_contextual_agreement")
 
 
 def fasa_select_dominant_fcs(shape, ca_mean_host, fc_idx_host_out) -> None:

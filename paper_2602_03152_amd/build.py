@@ -2,7 +2,8 @@
 
     python -m paper_2602_03152_amd.build
 
-Objects go to paper_2602_03152_amd/_build/, the library to paper_2602_03152_amd/libfasa.so.
+Objects go to paper_2602_03152_amd/_build/, the library to paper_2602_03152_amd/libfasa.so, the Python binding's
+marshalling module to paper_2602_03152_amd/_pycall.so.
 
     python -m paper_2602_03152_amd.build --sanitize
 
@@ -27,6 +28,7 @@ import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -35,6 +37,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfasa.so")
 LIB_TRACE = os.path.join(PKG, "libfasa_trace.so")
+PYCALL = os.path.join(PKG, "_pycall.so")       # argument marshalling of the Python binding (csrc/pycall.c)
 FLOORS = os.path.join(PKG, "fasa_floors")      # stand-alone measurement program (csrc/floors.hip)
 SOURCES = ["api.hip", "pack.hip", "score.hip", "topk.hip", "attend.hip", "fused.hip", "step.hip", "offload.hip", "calib.hip"]
 
@@ -245,6 +248,8 @@ def _build(verbose, extra_flags, trace) -> str:
     if not extra_flags:   # the floors program does not depend on the library's compile-time switches
         cmds.append([HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
                      "-packed-fp32-ops", os.path.join(CSRC, "floors.hip"), "-o", FLOORS])
+        cmds.append([shutil.which("gcc") or "cc", "-O2", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
+                     "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "pycall.c"), "-o", PYCALL, "-ldl"])
     jobs = [lambda c=c: _run(c, verbose) for c in cmds]
     jobs += [lambda f=f: _check_asm(f, tuple(extra_flags), bdir, verbose) for f in ASM_CHECKED]
     with ThreadPoolExecutor(max_workers=8) as ex:
