@@ -343,7 +343,7 @@ static int decode_step_common(const fasa_shape* shape, const fasa_paging* paging
   const bool by_sequence = n_ctx_seq != nullptr || budget_seq != nullptr;
   const bool select_all = !by_sequence && shape->budget >= shape->n_ctx;
   // the new row (if any) joins K, V and Kp inside the scoring kernel
-  const AppendArgs ap{k_new, v_new, K, V, pm};
+  const AppendArgs ap{k_new, v_new, K, V, pm, false};
   const StepForm form = plan_step(*shape, pm);
   if (form != kStepNone) {
     FASA_HIP(launch_step(*shape, form, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, st, rl, pm));
@@ -472,9 +472,15 @@ int fasa_offload_decode_step(const fasa_shape* shape, const void* q, void* Kp, c
   const size_t e = shape->dtype == FASA_BF16 ? 2 : 4;
   char* KT = (char*)stage;
   char* VT = KT + (size_t)shape->batch * shape->n_kv_heads * bsel * shape->head_dim * e;
-  if (k_new) FASA_HIP(launch_offload_append(*shape, Kp, Knd_host, V_host, fc_idx, k_new, v_new, st));
-  FASA_HIP(launch_score(*shape, q, Kp, fc_idx, S, select_all ? nullptr : hist, st));
+  // the new row (if any) joins Kp and the host parts inside the scoring kernel
+  const AppendArgs ap{k_new, v_new, Knd_host, V_host, kNoPaging, true};
+  FASA_HIP(launch_score(*shape, q, Kp, fc_idx, S, select_all ? nullptr : hist, st, {nullptr, nullptr}, ap));
   FASA_HIP(launch_select(*shape, S, hist, ctl, cand, T, st));
+  if (shape->dtype == FASA_BF16) {
+    FASA_HIP(launch_offload_attend(*shape, w.max_splits, q, Kp, Knd_host, V_host, fc_idx, T, KT, VT, O, ctl,
+                                   (float*)(base + w.part_acc_off), (float*)(base + w.part_ml_off), st));
+    return FASA_OK;
+  }
   FASA_HIP(launch_offload_gather(*shape, Kp, Knd_host, V_host, fc_idx, T, KT, VT, st));
   // exact attention over the rebuilt rows: the staging buffer is a dense cache of bsel tokens
   fasa_shape ss = *shape;

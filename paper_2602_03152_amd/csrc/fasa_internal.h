@@ -157,15 +157,17 @@ hipError_t launch_pack(const fasa_shape& s, const void* K, const int32_t* fc_idx
                        int n_begin, int n_end, hipStream_t st, PageMap pm = kNoPaging);
 // A freshly decoded K/V row per (b, h) ([batch][n_kv_heads][head_dim]) that the scoring kernel
 // appends at token n_ctx - 1 (K, V: the caches, with the shape's strides; Kp gets the dominant pairs).
-// k_new == nullptr: nothing to append.
+// k_new == nullptr: nothing to append.  split: K is the host part of the memory-optimised variant
+// ([row][n_cap][head_dim - 2 n_fc]) and receives the dims that are not dominant.
 struct AppendArgs {
   const void* k_new;
   const void* v_new;
   void* K;
   void* V;
   PageMap pm;
+  bool split;
 };
-constexpr AppendArgs kNoAppend = {nullptr, nullptr, nullptr, nullptr, {nullptr, 0, 0, 0}};
+constexpr AppendArgs kNoAppend = {nullptr, nullptr, nullptr, nullptr, {nullptr, 0, 0, 0}, false};
 // hist == nullptr: scores only.  adaptive_ctl != nullptr (with hist): the adaptive histogram of the
 // fused step (bins of lin_bin, location and scale left in the row counters) instead of the
 // exponent-based one the stand-alone selection reads.
@@ -205,12 +207,13 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
 // memory-optimised variant (offload.hip)
 hipError_t launch_offload_split(const fasa_shape& s, const void* K, const int32_t* fc_idx, void* Kp,
                                 void* Knd, int n_begin, int n_end, hipStream_t st);
-hipError_t launch_offload_append(const fasa_shape& s, void* Kp, void* Knd, void* Vh,
-                                 const int32_t* fc_idx, const void* k_new, const void* v_new,
-                                 hipStream_t st);
 hipError_t launch_offload_gather(const fasa_shape& s, const void* Kp, const void* Knd, const void* Vh,
                                  const int32_t* fc_idx, const int32_t* T, void* KT, void* VT,
                                  hipStream_t st);
+
+hipError_t launch_offload_attend(const fasa_shape& s, int max_splits, const void* q, const void* Kp, const void* Knd,
+                                 const void* Vh, const int32_t* fc_idx, const int32_t* T, void* KT, void* VT, float* O,
+                                 RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st);
 
 // offline calibration (calib.hip)
 // S: rows * n_cap floats, bitmap: rows * ceil(n_ctx / 32) words of scratch

@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
                                                     const ET* __restrict__ v_new, ET* Kc, ET* Vc,
                                                     long long sb, long long sh, long long sn,
                                                     PageMap pm, RowCtl* __restrict__ ctl, int budget_max,
-                                                    const int32_t* __restrict__ budget_seq) {
+                                                    const int32_t* __restrict__ budget_seq, int split) {
   constexpr int D = kHeadDim;
   constexpr int TPT = ScoreTraits<ET>::TPT;
   constexpr int NBINS = HIST == kHistAdaptive ? kLinBins : kHistBins;
@@ -70,6 +70,7 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
   __shared__ __align__(8) uint32_t lh[HIST ? NBINS : 2];
   __shared__ float2 sst[4];        // adaptive histogram: per wave, sum and sum of squares of its sample scores
   __shared__ ET knew[APPEND ? D : 1];          // the new key row
+  __shared__ uint32_t dmask[APPEND ? D / 32 : 1];   // split: bit per head dim, set if it is dominant
   __shared__ uint2 kpair[APPEND ? D / 2 : 1];  // per plane: the new key's (lo, hi) as stored in Kp
 
   int row, slice;
@@ -146,6 +147,7 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
     else fcl[t] = min(max(fci, 0), D / 2 - 1) << PAIR_SHIFT;
     if constexpr (APPEND) {
       if (t < D) knew[t] = newkv;
+      if (t < D / 32) dmask[t] = 0;
     }
   }
   if constexpr (HIST != 0) {
@@ -164,6 +166,10 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
         ET* o = Kp + (((size_t)row * F + t) * n_cap + n_app) * 2;
         o[0] = lo;
         o[1] = hi;
+        if (split) {
+          atomicOr(&dmask[dl >> 5], 1u << (dl & 31));
+          atomicOr(&dmask[dh >> 5], 1u << (dh & 31));
+        }
       }
     }
   }
@@ -278,7 +284,12 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
     }
   }
   if constexpr (APPEND) {
-    if (own_wg) {   // the whole new row to K (threads 0..127) and V (threads 128..255)
+    if (own_wg && split && t < D) {   // the non-dominant dims, in order, to the row's place in the host part
+      int pos = 0;
+#pragma unroll
+      for (int i = 0; i < D / 32; ++i) pos += __popc(~dmask[i] & (i < (t >> 5) ? ~0u : i > (t >> 5) ? 0u : (1u << (t & 31)) - 1u));
+      if (!((dmask[t >> 5] >> (t & 31)) & 1u)) Kc[((size_t)row * n_cap + n_app) * (D - 2 * F) + pos] = newkv;
+    } else if (own_wg) {   // the whole new row to K (threads 0..127) and V (threads 128..255)
       ET* dst = (t < D ? Kc : Vc) + kv_row_offset(pm, b, n_app, sb, sn) + h * sh + (t & (D - 1));
       *dst = newkv;
     }
@@ -355,7 +366,7 @@ static hipError_t launch_score_v(const fasa_shape& s, const void* q, void* Kp, c
                 dim3(rows * nslices), dim3(256), st, (const ET*)q, (ET*)Kp, fc_idx, S, hist, rows, nslices,
                 s.n_q_heads, s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, (const ET*)ap.k_new,
                 (const ET*)ap.v_new, (ET*)ap.K, (ET*)ap.V, (long long)s.kv_stride_b, (long long)s.kv_stride_h,
-                (long long)s.kv_stride_n, ap.pm, ctl, s.budget, rl.budget);
+                (long long)s.kv_stride_n, ap.pm, ctl, s.budget, rl.budget, ap.split ? 1 : 0);
 }
 
 template <typename ET, int HIST, bool APPEND, int PAIR>

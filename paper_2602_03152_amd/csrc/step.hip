@@ -744,7 +744,7 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
   const int G = s.n_q_heads / s.n_kv_heads;
   if (form == kStepRow) {
-    const hipError_t e = launch_score(s, q, Kp, fc_idx, S, nullptr, st, rl, AppendArgs{k_new, v_new, K, V, pm});
+    const hipError_t e = launch_score(s, q, Kp, fc_idx, S, nullptr, st, rl, AppendArgs{k_new, v_new, K, V, pm, false});
     if (e != hipSuccess) return e;
     if (s.dtype == FASA_BF16) return launch("fasa_row", row_kernel<uint16_t, 8>, dim3(a.rows), dim3(kRowNT), st, a);
     if (G == 1) return launch("fasa_row", row_kernel<float, 1>, dim3(a.rows), dim3(kRowNT), st, a);
