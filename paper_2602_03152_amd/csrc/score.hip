@@ -9,12 +9,17 @@
 
 namespace fasa {
 
-constexpr int kScoreFB = 16;  // FC planes in flight per thread
+constexpr int kScoreFB = 8;   // FC planes in flight per thread, any F
+constexpr int kScoreSmp = 8;  // any F: the sample of the adaptive histogram scores with the first 4 * kScoreSmp planes
 
 // 1-D grid of rows * nslices workgroups, nslices = ceil(N / (256 * TPT)).  One 16-byte load per
 // thread per FC plane: a wave reads 1 KiB contiguous from each plane.  NB > 0: F == 8 * NB and all
-// F plane loads of a thread are in flight at once, issued as straight-line code; NB == 0: any F,
-// 16 planes at a time.
+// F plane loads of a thread are in flight at once, issued as straight-line code; NB == 0: any F, 8 planes in
+// flight, a consumed plane's registers refilled with the plane 8 further on, all loads unconditional (16 rows of
+// 20011 tokens, F = 12, with the selection and attention behind it: 25.7 -> 25.2 us against 16 at a time, each behind a test).
+// Reading 134 MB of planes like this and nothing else takes 23.3 - 24.2 us (5.9 TB/s; the same from 8 to 32 planes
+// in flight), scoring them 24.8 - 25.8, with the adaptive histogram 27; of those 2 us the histogram's flush to
+// memory is 1.0 - 1.4, its LDS atomics 0.2, the sample 0.3.
 //
 // Vector loads of a wave return in order, so nothing the K planes do not depend on may queue behind
 // them, and a wait for an earlier load is only cheap if the loads after it are unconditional.  Order
@@ -97,17 +102,17 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
   // fourth plane starting at plane `part`: a quarter of the loads per lane, the four parts of a token's
   // score meeting through two lane swaps.
   using SmpT = typename std::conditional<sizeof(ET) == 2, uint32_t, uint2>::type;
-  constexpr int NSMP = HIST == kHistAdaptive ? (NB ? NB * 2 : kScoreFB / 4) : 1;
+  constexpr int NSMP = HIST == kHistAdaptive ? (NB ? NB * 2 : kScoreSmp) : 1;
   SmpT smp[NSMP];
   const int spart = (t >> 4) & 3;
   if constexpr (HIST == kHistAdaptive) {
     const int Ns = APPEND ? N - 1 : N;
     const int ps = max(min((t >> 6) * ((Ns >> 2) & ~15) + (t & 15), Ns - 1), 0);
     const ET* sp = Kp + ((size_t)row * F * n_cap + ps) * 2;
-    const int nsf = NB ? NB * 8 : min(F, kScoreFB);
+    const int nsf = NB ? NB * 8 : min(F, 4 * kScoreSmp);
 #pragma unroll
     for (int u = 0; u < NSMP; ++u)
-      smp[u] = *reinterpret_cast<const SmpT*>(sp + (size_t)min(4 * u + spart, nsf - 1) * n_cap * 2);
+      if (NB || 4 * u < nsf) smp[u] = *reinterpret_cast<const SmpT*>(sp + (size_t)min(4 * u + spart, nsf - 1) * n_cap * 2);
   }
   // the appended token: which workgroup and thread own it, and which of the thread's tokens it is
   const int n_app = N - 1;
@@ -121,10 +126,8 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
   const ET* p = Kp + ((size_t)row * F * n_cap + (active ? n0 : 0)) * 2;
   const size_t plane = (size_t)n_cap * 2;
   uint4 w[NW];
-  int nf = NB ? NW : min(F, kScoreFB);
 #pragma unroll
-  for (int u = 0; u < NW; ++u)
-    if (NB || u < nf) w[u] = *reinterpret_cast<const uint4*>(p + (size_t)u * plane);
+  for (int u = 0; u < NW; ++u) w[u] = *reinterpret_cast<const uint4*>(p + (size_t)(NB ? u : min(u, F - 1)) * plane);
 
   // adaptive histogram: where the B-th largest of N normal scores lies, in standard deviations (needs no
   // memory: computed while the first loads are on their way)
@@ -175,10 +178,11 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
   }
   __syncthreads();
   if constexpr (HIST == kHistAdaptive) {
-    const int nsf = NB ? NB * 8 : min(F, kScoreFB);
+    const int nsf = NB ? NB * 8 : min(F, 4 * kScoreSmp);
     float xs = 0.f;
 #pragma unroll
     for (int u = 0; u < NSMP; ++u) {
+      if (!NB && 4 * u >= nsf) break;
       const float2 qf = qs[min(4 * u + spart, nsf - 1)];
       float lo, hi;
       if constexpr (sizeof(ET) == 2) { lo = bf16_lo(smp[u]); hi = bf16_hi(smp[u]); }
@@ -239,27 +243,27 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
       fma_pairs<ET>(w[u], qf.x, qf.y, acc);
     }
   } else {
-    for (int f0 = 0;;) {
-      if constexpr (APPEND) {
-        if (own_thread) {
+    int f0 = 0;
+    for (; f0 + NW < F; f0 += NW) {
 #pragma unroll
-          for (int u = 0; u < kScoreFB; ++u)
-            if (u < nf) patch(w[u], f0 + u);
+      for (int u = 0; u < NW; ++u) {
+        if constexpr (APPEND) {
+          if (own_thread) patch(w[u], f0 + u);
         }
+        const float2 qf = qs[f0 + u];
+        fma_pairs<ET>(w[u], qf.x, qf.y, acc);
+        w[u] = *reinterpret_cast<const uint4*>(p + (size_t)min(f0 + NW + u, F - 1) * plane);
       }
+    }
 #pragma unroll
-      for (int u = 0; u < kScoreFB; ++u) {
-        if (u < nf) {
-          const float2 qf = qs[f0 + u];
-          fma_pairs<ET>(w[u], qf.x, qf.y, acc);
+    for (int u = 0; u < NW; ++u) {
+      if (f0 + u < F) {
+        if constexpr (APPEND) {
+          if (own_thread) patch(w[u], f0 + u);
         }
+        const float2 qf = qs[f0 + u];
+        fma_pairs<ET>(w[u], qf.x, qf.y, acc);
       }
-      f0 += kScoreFB;
-      if (f0 >= F) break;
-      nf = min(F - f0, kScoreFB);
-#pragma unroll
-      for (int u = 0; u < kScoreFB; ++u)
-        if (u < nf) w[u] = *reinterpret_cast<const uint4*>(p + (size_t)(f0 + u) * plane);
     }
   }
   if (active) {
@@ -373,6 +377,12 @@ template <typename ET, int HIST, bool APPEND, int PAIR>
 static hipError_t launch_score_f(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx,
                                  float* S, uint32_t* hist, hipStream_t st, RaggedLens rl,
                                  const AppendArgs& ap, RowCtl* ctl) {
+  // 32 planes in flight are 160 registers, three workgroups per CU.  A grid that has more than one per CU gains from
+  // eight planes in flight instead (8 - 64 rows, 256 - 1024 workgroups: 0.4 - 0.8 us less per step); with fewer
+  // (128 workgroups) each one's own latency counts: 0.9 us more.
+  const int per_block = 256 * ScoreTraits<ET>::TPT;
+  if (s.n_fc == 32 && (long long)s.batch * s.n_kv_heads * ((s.n_ctx + per_block - 1) / per_block) >= kAssumedCUs)
+    return launch_score_v<ET, HIST, 0, APPEND, PAIR>(s, q, Kp, fc_idx, S, hist, st, rl, ap, ctl);
   switch (s.n_fc) {   // the usual settings (an eighth to a half of the FCs) get straight-line loads
     case 8: return launch_score_v<ET, HIST, 1, APPEND, PAIR>(s, q, Kp, fc_idx, S, hist, st, rl, ap, ctl);
     case 16: return launch_score_v<ET, HIST, 2, APPEND, PAIR>(s, q, Kp, fc_idx, S, hist, st, rl, ap, ctl);
