@@ -10,17 +10,8 @@ namespace fasa {
 constexpr int kAttU = 4;                  // rows in flight per 16-lane group and batch
 constexpr int kAttBatch = 4 * kAttU;      // rows per wave and batch
 
-// 8 consecutive head dims of one cached row, widened to float32
-template <typename ET> struct Row8;
-template <> struct Row8<uint16_t> {
-  uint4 w;
-  __device__ __forceinline__ void load(const uint16_t* p) { w = *reinterpret_cast<const uint4*>(p); }
-  __device__ __forceinline__ void unpack(float* f) const {
-    f[0] = bf16_lo(w.x); f[1] = bf16_hi(w.x); f[2] = bf16_lo(w.y); f[3] = bf16_hi(w.y);
-    f[4] = bf16_lo(w.z); f[5] = bf16_hi(w.z); f[6] = bf16_lo(w.w); f[7] = bf16_hi(w.w);
-  }
-};
-template <> struct Row8<float> {
+// 8 consecutive head dims of one cached row
+struct Row8 {
   float4 a, b;
   __device__ __forceinline__ void load(const float* p) {
     a = *reinterpret_cast<const float4*>(p);
@@ -31,17 +22,17 @@ template <> struct Row8<float> {
   }
 };
 
-__device__ __forceinline__ float to_f32(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
-__device__ __forceinline__ float to_f32(float v) { return v; }
-
+// float32 caches with one or two query heads per KV head, on the vector ALUs: there the matrix cores, which always
+// compute 16 heads, take longer over a tile than its loads (full KV, 4 rows of 20000, one head: 18.0 us like this,
+// 20.2 on the matrix cores; two heads 14.9 / 15.8; from four heads on the matrix cores: 31.3 / 30.5, eight 24.5 / 19.1).
 // 1-D grid of rows * n_splits workgroups, 256 threads.  A wave is 4 groups of 16 lanes; a group
 // reads one cached row per load instruction (16 lanes x 16 bytes = one 256-byte bf16 row), lane c
 // owning head dims [8c, 8c+8) of K (for the logit) and of V (for the output).  The workgroup that
 // finishes a row last merges the row's partials into O.
-template <typename ET, int G, bool DENSE>
-__global__ __launch_bounds__(256) void attend_kernel(const ET* __restrict__ q,
-                                                     const ET* __restrict__ K,
-                                                     const ET* __restrict__ V,
+template <int G, bool DENSE>
+__global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restrict__ q,
+                                                     const float* __restrict__ K,
+                                                     const float* __restrict__ V,
                                                      const int32_t* __restrict__ T,
                                                      float* __restrict__ O,
                                                      RowCtl* __restrict__ ctl,
@@ -77,9 +68,9 @@ __global__ __launch_bounds__(256) void attend_kernel(const ET* __restrict__ q,
   float qr[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const ET* qp = q + ((size_t)b * Hq + (size_t)h * G + g) * D + 8 * c;
+    const float* qp = q + ((size_t)b * Hq + (size_t)h * G + g) * D + 8 * c;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) qr[g][k] = to_f32(qp[k]) * scale_log2e;
+    for (int k = 0; k < 8; ++k) qr[g][k] = qp[k] * scale_log2e;
   }
   float acc[G][8], m[G], l[G];
 #pragma unroll
@@ -95,13 +86,13 @@ __global__ __launch_bounds__(256) void attend_kernel(const ET* __restrict__ q,
   const int pshift = paged ? pm.shift : 31, pmask = paged ? (1 << pm.shift) - 1 : 0x7fffffff;
   const long long blk_stride = paged ? sb : 0;
   const int slot_max = paged ? (pm.n_pool << pm.shift) - 1 : n_ctx - 1;
-  const ET* Kb = K + (paged ? 0 : b * sb) + h * sh + 8 * c;
-  const ET* Vb = V + (paged ? 0 : b * sb) + h * sh + 8 * c;
+  const float* Kb = K + (paged ? 0 : b * sb) + h * sh + 8 * c;
+  const float* Vb = V + (paged ? 0 : b * sb) + h * sh + 8 * c;
   const int32_t* Trow = DENSE ? nullptr : T + (size_t)row * count_max;
 
   for (int j0 = s0 + wave * kAttBatch; j0 < s1; j0 += 4 * kAttBatch) {
     bool valid[kAttU];
-    Row8<ET> kv[kAttU], vv[kAttU];
+    Row8 kv[kAttU], vv[kAttU];
     long long off[kAttU];
 #pragma unroll
     for (int u = 0; u < kAttU; ++u) {
@@ -216,7 +207,7 @@ __global__ __launch_bounds__(256) void attend_kernel(const ET* __restrict__ q,
 }
 
 // ---------------------------------------------------------------------------------------------
-// bf16 variant with both products of a 16-row tile on the matrix cores (mfma_tile.h): the logits
+// Both products of a 16-row tile run on the matrix cores (mfma_tile.h): the logits
 // K_tile . Q^T of the GQA group and the weighted sum P . V_tile.  The tile loop is software-pipelined:
 // while a tile is computed, the next tile's K/V rows and the list entries of the tile after it are in
 // flight.  Loads inside the loop are unconditional (straight-line code keeps the compiler's wait
@@ -224,10 +215,10 @@ __global__ __launch_bounds__(256) void attend_kernel(const ET* __restrict__ q,
 // entries beyond the range are clamped into it and only fetched, the K/V prefetch is issued for real
 // tiles only (the last tile is peeled).
 // ---------------------------------------------------------------------------------------------
-template <int G, bool DENSE>
-__global__ __launch_bounds__(256) void attend_mfma_kernel(const uint16_t* __restrict__ q,
-                                                          const uint16_t* __restrict__ K,
-                                                          const uint16_t* __restrict__ V,
+template <typename ET, int G, bool DENSE>
+__global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(const ET* __restrict__ q,
+                                                          const ET* __restrict__ K,
+                                                          const ET* __restrict__ V,
                                                           const int32_t* __restrict__ T,
                                                           float* __restrict__ O,
                                                           RowCtl* __restrict__ ctl,
@@ -267,7 +258,7 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(const uint16_t* __rest
   FASA_T_DECL(5);
   FASA_T(0);
 
-  MfmaTile<G> tile;
+  MfmaTile<G, ET> tile;
   tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
   tile.reset();
 
@@ -276,8 +267,8 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(const uint16_t* __rest
   const int pshift = paged ? pm.shift : 31, pmask = paged ? (1 << pm.shift) - 1 : 0x7fffffff;
   const long long blk_stride = paged ? sb : 0;
   const int slot_max = paged ? (pm.n_pool << pm.shift) - 1 : n_ctx - 1;
-  const uint16_t* Kb = K + (paged ? 0 : b * sb) + h * sh;
-  const uint16_t* Vb = V + (paged ? 0 : b * sb) + h * sh + 8 * lo;
+  const ET* Kb = K + (paged ? 0 : b * sb) + h * sh + kChunk<ET> * hi;
+  const ET* Vb = V + (paged ? 0 : b * sb) + h * sh + 8 * lo;
   const int32_t* Trow = DENSE ? nullptr : T + (size_t)row * count_max;
 
   struct TileIdx { int k; int v[4]; };        // list entries of one tile: K row lo, V rows 4hi .. 4hi+3
@@ -296,19 +287,17 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(const uint16_t* __rest
     return r;
   };
   auto load_kv = [&](const TileIdx& ix) {
-    TileKV r;
+    TileKV<ET> r;
     auto row_off = [&](int e) {
       const int sl = min(max(e, 0), slot_max);
       return (long long)(sl >> pshift) * blk_stride + (long long)(sl & pmask) * sn;
     };
-    const long long koff = row_off(ix.k);
+    r.load_k(Kb + row_off(ix.k));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r.kc[i] = *reinterpret_cast<const uint4*>(Kb + koff + 8 * (hi + 4 * i));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r.vr[i] = *reinterpret_cast<const uint4*>(Vb + row_off(ix.v[i]));
+    for (int i = 0; i < 4; ++i) r.load_v(i, Vb + row_off(ix.v[i]));
     return r;
   };
-  auto compute_tile = [&](const TileKV& kv, int j0) {
+  auto compute_tile = [&](const TileKV<ET>& kv, int j0) {
     float sv[4];
     tile.logits(kv, scale_log2e, sv);
     bool valid[4];
@@ -321,10 +310,10 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(const uint16_t* __rest
   if (jw < s1) {
     const int n_tiles = (s1 - jw + 63) / 64;
     TileIdx ix_next = load_idx(jw + 64);
-    TileKV cur = load_kv(load_idx(jw));
+    TileKV<ET> cur = load_kv(load_idx(jw));
     for (int i = 0; i + 1 < n_tiles; ++i) {
       const int j0 = jw + 64 * i;
-      const TileKV nxt = load_kv(ix_next);
+      const TileKV<ET> nxt = load_kv(ix_next);
       ix_next = load_idx(j0 + 128);
       compute_tile(cur, j0);
       cur = nxt;
@@ -374,32 +363,15 @@ static hipError_t launch_attend_g(const fasa_shape& s, bool dense, const AttendP
                                   float* O, RowCtl* ctl, float* part_acc, float* part_ml,
                                   hipStream_t st, RaggedLens rl, PageMap pm) {
   const int rows = s.batch * s.n_kv_heads;
-  dim3 grid(rows * p.n_splits), block(256);
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
-  if constexpr (sizeof(ET) == 2) {
-    if (dense)
-      return launch("fasa_dense_attend", attend_mfma_kernel<G, true>, grid, block, st,
-                    (const uint16_t*)q, (const uint16_t*)K, (const uint16_t*)V, T, O, ctl, part_acc,
-                    part_ml, rows, p.n_splits, s.n_q_heads, s.n_kv_heads, p.count, s.n_ctx,
-                    p.tok_per_split, (long long)s.kv_stride_b, (long long)s.kv_stride_h,
-                    (long long)s.kv_stride_n, scale_log2e, rl.n_ctx, rl.budget, pm);
-    return launch("fasa_sparse_attend", attend_mfma_kernel<G, false>, grid, block, st,
-                  (const uint16_t*)q, (const uint16_t*)K, (const uint16_t*)V, T, O, ctl, part_acc,
-                  part_ml, rows, p.n_splits, s.n_q_heads, s.n_kv_heads, p.count, s.n_ctx,
-                  p.tok_per_split, (long long)s.kv_stride_b, (long long)s.kv_stride_h,
-                  (long long)s.kv_stride_n, scale_log2e, rl.n_ctx, rl.budget, pm);
-  }
-  if (dense)
-    return launch("fasa_dense_attend", attend_kernel<ET, G, true>, grid, block, st, (const ET*)q,
-                  (const ET*)K, (const ET*)V, T, O, ctl, part_acc, part_ml, rows, p.n_splits,
-                  s.n_q_heads, s.n_kv_heads, p.count, s.n_ctx, p.tok_per_split,
-                  (long long)s.kv_stride_b, (long long)s.kv_stride_h, (long long)s.kv_stride_n,
-                  scale_log2e, rl.n_ctx, rl.budget, pm);
-  return launch("fasa_sparse_attend", attend_kernel<ET, G, false>, grid, block, st, (const ET*)q,
-                (const ET*)K, (const ET*)V, T, O, ctl, part_acc, part_ml, rows, p.n_splits,
-                s.n_q_heads, s.n_kv_heads, p.count, s.n_ctx, p.tok_per_split,
-                (long long)s.kv_stride_b, (long long)s.kv_stride_h, (long long)s.kv_stride_n,
-                scale_log2e, rl.n_ctx, rl.budget, pm);
+  auto kernel = [&]() {
+    if constexpr (sizeof(ET) == 4 && G <= 2) return dense ? attend_valu_kernel<G, true> : attend_valu_kernel<G, false>;
+    else return dense ? attend_kernel<ET, G, true> : attend_kernel<ET, G, false>;
+  }();
+  return launch(dense ? "fasa_dense_attend" : "fasa_sparse_attend", kernel, dim3(rows * p.n_splits), dim3(256), st,
+                (const ET*)q, (const ET*)K, (const ET*)V, T, O, ctl, part_acc, part_ml, rows, p.n_splits,
+                s.n_q_heads, s.n_kv_heads, p.count, s.n_ctx, p.tok_per_split, (long long)s.kv_stride_b,
+                (long long)s.kv_stride_h, (long long)s.kv_stride_n, scale_log2e, rl.n_ctx, rl.budget, pm);
 }
 
 template <typename ET>

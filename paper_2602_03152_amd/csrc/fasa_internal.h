@@ -105,10 +105,10 @@ struct AttendPlan {
 AttendPlan plan_attend(int rows, int count, int group);
 
 // Fused selection + attention (fused.hip): tokens per workgroup and workgroups per row.
-// tpb == 0: this shape takes the staged kernels (float32 cache, everything selected, or a row longer
-// than the merge can take slices of).
+// tpb == 0: this shape takes the staged kernels (everything selected, or a row longer than the merge can
+// take slices of).
 // Candidates per row of the fused step that are handed over with a record (logits of the group's query
-// heads + V row), and the bytes of workspace a row's records take.
+// heads + V row), and the bytes of workspace a row's records take (bf16).
 constexpr int kFuseRich = 64;
 constexpr size_t kFuseRecBytesPerRow = (size_t)kFuseRich * (kMaxGroup * 4 + kHeadDim * 2);
 

@@ -39,13 +39,10 @@ constexpr int kFuseCountMax = 256;    // candidates ranked by counting; more: ra
 constexpr int kFuseMergeInFlight = FASA_FUSE_MERGE_IN_FLIGHT;   // partials per thread in flight in the merge
 constexpr int kStashRecs = 8;          // candidates of ONE workgroup that ride along with its winners
 constexpr int kRecLogits = kMaxGroup;
-constexpr size_t kRecRowBytes = (size_t)kFuseRich * (kRecLogits * 4 + kHeadDim * 2);
-static_assert(kRecRowBytes == kFuseRecBytesPerRow, "workspace carve-up and kernel disagree");
 
-
-template <int G, int TPB>
-__global__ __launch_bounds__(256) void select_attend_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+template <typename ET, int G, int TPB>
+__global__ __launch_bounds__(256, 2) void select_attend_kernel(
+    const ET* __restrict__ q, const ET* __restrict__ K, const ET* __restrict__ V,
     const float* __restrict__ S, uint32_t* __restrict__ hist, RowCtl* __restrict__ ctl,
     uint2* __restrict__ cand, int32_t* __restrict__ T, float* __restrict__ O, float* __restrict__ part_acc,
     float* __restrict__ part_ml, unsigned char* __restrict__ rec, int rows, int nslices, int slice_len, int Hq, int Hkv, int N_max,
@@ -53,10 +50,20 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
     const int32_t* __restrict__ n_ctx_seq, const int32_t* __restrict__ budget_seq, PageMap pm) {
   constexpr int D = kHeadDim;
   constexpr int PT = TPB / 256;                               // tokens per thread
+  constexpr int RICH = kFuseRich;
+  constexpr int VP = D * (int)sizeof(ET) / 16;                // 16-byte pieces of a V row
+  constexpr int REC_BYTES = RICH * (kRecLogits * 4 + VP * 16);
+  // Where a row's records lie: in their own region of the workspace, which holds kFuseRich of a bf16 cache but half as
+  // many of a float32 cache; there, of a row that is long enough, behind the first kFuseRich places of its
+  // candidate list, which are all that a row with records uses.
+  const bool rec_in_cand = sizeof(ET) == 4 && (size_t)n_cap * sizeof(uint2) >= RICH * sizeof(uint2) + REC_BYTES;
+  constexpr int RICH_OWN = sizeof(ET) == 2 ? RICH : RICH / 2;
+  static_assert((size_t)RICH_OWN * (kRecLogits * 4 + VP * 16) <= kFuseRecBytesPerRow, "records fit the workspace");
+  const int rich_max = sizeof(ET) == 2 || rec_in_cand ? RICH : RICH_OWN;
   constexpr int ACC_BYTES = 4 * G * D * 4;                    // [wave][G][D] floats
   constexpr int RES_BYTES = kFuseCandLds * 8 + kHistBins * 4; // candidate list + 4096 digit counters
-  static_assert(RES_BYTES >= kFuseRich * 8 + (int)kRecRowBytes, "the records of a row fit the resolve scratch");
-  constexpr int BIG = ACC_BYTES > RES_BYTES ? ACC_BYTES : RES_BYTES;
+  constexpr int CAND_BYTES = RES_BYTES > RICH * 8 + REC_BYTES ? RES_BYTES : RICH * 8 + REC_BYTES;   // or a row's records
+  constexpr int BIG = ACC_BYTES > CAND_BYTES ? ACC_BYTES : CAND_BYTES;
   __shared__ __align__(16) unsigned char big[BIG];            // tile sums, later the resolve's scratch
   __shared__ float sm_m[4][G], sm_l[4][G];
   __shared__ float red[G];
@@ -70,7 +77,7 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
   __shared__ __align__(16) float scs[4][16];                  // per wave: rescale factor of each head's running sums
   __shared__ int32_t wl[TPB];                                 // what the gather reads: winners from the front
   __shared__ __align__(16) float cst_s[kStashRecs][kRecLogits];   // this workgroup's candidates: logits
-  __shared__ __align__(16) uint4 cst_v[kStashRecs][16];           // ... and V rows, until their records are written
+  __shared__ __align__(16) uint4 cst_v[kStashRecs][VP];           // ... and V rows, until their records are written
   float (*sm_o)[G][D] = reinterpret_cast<float (*)[G][D]>(big);
   // the merge's split weights live in `big` too: beyond the merge's own partition scratch (< 8 KB); the
   // candidate records staged there are consumed before the weights are written
@@ -107,7 +114,7 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
   uint32_t* gh = hist + (size_t)row * kHistBins;
   const uint4 h4 = *reinterpret_cast<const uint4*>(gh + 4 * t);
   const float bin_mu = ctl[row].bin_mu, bin_inv = ctl[row].bin_inv;
-  MfmaTile<G> tile;
+  MfmaTile<G, ET> tile;
   tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
   const bool paged = pm.table != nullptr;
   int slot[PT];
@@ -140,7 +147,7 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
   uint32_t pw, pc, tw, tc;
   block256_prefix2(__popc(win), __popc(cnd), wtot, pw, pc, tw, tc);
   const int n_win = (int)min(tw, (uint32_t)TPB);
-  const bool rich = thr[2] <= (uint32_t)kFuseRich;      // the same decision in every workgroup of the row
+  const bool rich = thr[2] <= (uint32_t)rich_max;      // the same decision in every workgroup of the row
   const int n_ride = rich ? (int)min(min(tc, (uint32_t)kStashRecs), (uint32_t)(TPB - n_win)) : 0;
   const bool overflow = rich && tc > (uint32_t)n_ride;   // then the row's last workgroup gathers the taken rows itself
   const int n_list = n_win + n_ride;
@@ -155,16 +162,18 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
   }
   __syncthreads();
   FASA_T(2);
-  float* rec_s = reinterpret_cast<float*>(rec + (size_t)row * kRecRowBytes);                      // [kFuseRich][8]
-  uint2* rec_v = reinterpret_cast<uint2*>(rec + (size_t)row * kRecRowBytes + kFuseRich * kRecLogits * 4);  // [kFuseRich][32]
+  unsigned char* rec_row = rec_in_cand ? reinterpret_cast<unsigned char*>(cand + (size_t)row * n_cap + RICH)
+                                       : rec + (size_t)row * kFuseRecBytesPerRow;
+  float* rec_s = reinterpret_cast<float*>(rec_row);                                         // [rich_max][8]
+  uint2* rec_v = reinterpret_cast<uint2*>(rec_row + rich_max * kRecLogits * 4);             // [rich_max][2 VP]
 
   // ---- 3. attention over a list of rows; used for the winners and, by the last workgroup, for the
   // resolved candidates.  State per lane: query head lo, rows 4hi..4hi+3 of every tile. ----
   const int pshift = paged ? pm.shift : 31, pmask = paged ? (1 << pm.shift) - 1 : 0x7fffffff;
   const long long blk_stride = paged ? sb : 0;
   const int slot_max = paged ? (pm.n_pool << pm.shift) - 1 : N - 1;
-  const uint16_t* Kb = K + (paged ? 0 : b * sb) + h * sh;
-  const uint16_t* Vb = V + (paged ? 0 : b * sb) + h * sh + 8 * lo;
+  const ET* Kb = K + (paged ? 0 : b * sb) + h * sh + kChunk<ET> * hi;
+  const ET* Vb = V + (paged ? 0 : b * sb) + h * sh + 8 * lo;
 
   // One tile = 16 list entries, both products on the matrix cores (mfma_tile.h).
   auto row_off = [&](int e) {
@@ -173,20 +182,19 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
   };
   // idx(j): entry j of the list, j already clamped into it
   auto load_kv = [&](auto&& idx, int j0, int cnt) {
-    TileKV r;
+    TileKV<ET> r;
     const long long koff = row_off(idx(min(j0 + lo, cnt - 1)));
     long long voff[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) voff[i] = row_off(idx(min(j0 + 4 * hi + i, cnt - 1)));
+    r.load_k(Kb + koff);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r.kc[i] = *reinterpret_cast<const uint4*>(Kb + koff + 8 * (hi + 4 * i));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r.vr[i] = *reinterpret_cast<const uint4*>(Vb + voff[i]);
+    for (int i = 0; i < 4; ++i) r.load_v(i, Vb + voff[i]);
     return r;
   };
   // rows j0 .. j0+15 of a list whose first nw entries are attended and whose entries nw .. cnt-1 are
   // candidates: those only leave their logits and V row in the stash, entry (entry - nw)
-  auto compute_tile = [&](const TileKV& kv, int j0, int nw, int cnt) {
+  auto compute_tile = [&](const TileKV<ET>& kv, int j0, int nw, int cnt) {
     float sv[4];
     tile.logits(kv, scale_log2e, sv);
     bool valid[4];
@@ -198,7 +206,8 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
         const int r = j0 + 4 * hi + e - nw;
         if (r >= 0 && r < cnt - nw && r < kStashRecs) {
           if (lo < G) cst_s[r][lo] = sv[e];
-          cst_v[r][lo] = kv.vr[e];
+#pragma unroll
+          for (int i = 0; i < VP / 16; ++i) cst_v[r][VP / 16 * lo + i] = kv.v_piece(e, i);
         }
       }
     }
@@ -215,10 +224,10 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
     const int jw = wave * 16;
     if (jw < cnt) {
       const int n_tiles = (cnt - jw + 63) / 64;
-      TileKV cur = load_kv(idx, jw, cnt);
+      TileKV<ET> cur = load_kv(idx, jw, cnt);
       under_first_load();
       for (int i = 0; i + 1 < n_tiles; ++i) {
-        const TileKV nxt = load_kv(idx, jw + 64 * (i + 1), cnt);
+        const TileKV<ET> nxt = load_kv(idx, jw + 64 * (i + 1), cnt);
         compute_tile(cur, jw + 64 * i, nw, cnt);
         cur = nxt;
       }
@@ -263,13 +272,14 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
       if ((cnd & (1u << k)) && bcand < (uint32_t)n_cap) st_agent(&crow[bcand++], make_uint2(key[k], (uint32_t)n));
     }
     // the stash becomes records at the candidates' places in the list: thread t writes 8 bytes
-    // (36 per record: 4 of logits, 32 of the V row)
-    for (int i = t; i < n_ride * 36; i += 256) {
-      const int r = i / 36, piece = i % 36, place = (int)bc[1] + r;
-      if (place < kFuseRich) {
+    // (36 per record of a bf16 cache: 4 of logits, 32 of the V row)
+    constexpr int PR = 4 + 2 * VP;
+    for (int i = t; i < n_ride * PR; i += 256) {
+      const int r = i / PR, piece = i % PR, place = (int)bc[1] + r;
+      if (place < rich_max) {
         if (piece < 4) st_agent(reinterpret_cast<uint2*>(rec_s + place * kRecLogits) + piece,
                                 reinterpret_cast<const uint2*>(&cst_s[r][0])[piece]);
-        else st_agent(&rec_v[place * 32 + piece - 4], reinterpret_cast<const uint2*>(&cst_v[r][0])[piece - 4]);
+        else st_agent(&rec_v[place * 2 * VP + piece - 4], reinterpret_cast<const uint2*>(&cst_v[r][0])[piece - 4]);
       }
     }
   }
@@ -312,26 +322,26 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
     // and the t-th eight bytes of every 2 KB of V rows.
     const uint2 ce = ld_agent(&crow[min(t, n_cand - 1)]);
     const float2 cs = ld_agent(reinterpret_cast<const float2*>(rec_s) + min(t, 4 * n_cand - 1));
-    constexpr int NV = kFuseRich * 16 / 256;          // 16-byte pieces of V rows per thread
+    constexpr int NV = RICH * VP / 256;               // 16-byte pieces of V rows per thread
     const __amdgpu_buffer_rsrc_t rv = agent_buffer(rec_v);
     uint4 cv[NV];
 #pragma unroll
     for (int u = 0; u < NV; ++u)
-      if (u * 256 < 16 * n_cand) cv[u] = agent_load_u128(rv, (uint32_t)min(u * 256 + t, 16 * n_cand - 1) * 16u);
-    uint2* lc = reinterpret_cast<uint2*>(big);                                          // [kFuseRich]
-    float* lsm = reinterpret_cast<float*>(big + kFuseRich * 8);                          // [kFuseRich][8]
-    uint4* lvm = reinterpret_cast<uint4*>(big + kFuseRich * 8 + kFuseRich * kRecLogits * 4);   // [kFuseRich][16]
+      if (u * 256 < VP * n_cand) cv[u] = agent_load_u128(rv, (uint32_t)min(u * 256 + t, VP * n_cand - 1) * 16u);
+    uint2* lc = reinterpret_cast<uint2*>(big);                                          // [RICH]
+    float* lsm = reinterpret_cast<float*>(big + RICH * 8);                               // [RICH][8]
+    uint4* lvm = reinterpret_cast<uint4*>(big + RICH * 8 + RICH * kRecLogits * 4);       // [RICH][VP]
     int32_t* tk = reinterpret_cast<int32_t*>(dh);                                        // taken candidates, by rank
     auto under_loads = [&]() {
-      if (t < kFuseRich) lc[t] = ce;
-      reinterpret_cast<float2*>(lsm)[t] = cs;
+      if (t < RICH) lc[t] = ce;
+      if (t < 4 * RICH) reinterpret_cast<float2*>(lsm)[t] = cs;
 #pragma unroll
       for (int u = 0; u < NV; ++u)
-        if (u * 256 < 16 * n_cand) lvm[u * 256 + t] = cv[u];
+        if (u * 256 < VP * n_cand) lvm[u * 256 + t] = cv[u];
       __syncthreads();
       FASA_T(6);
-      // rank by counting, four threads per candidate (at most kFuseRich = 64 candidates here)
-      static_assert(kFuseRich * 4 <= 256, "four threads per candidate");
+      // rank by counting, four threads per candidate (at most RICH <= 64 candidates here)
+      static_assert(RICH * 4 <= 256, "four threads per candidate");
       const int ci = t >> 2;
       const int rank = rank_in_list<4>(lc, n_cand, ci);
       if ((t & 3) == 0 && ci < n_cand && rank < need) {
@@ -349,13 +359,18 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
         for (int j0 = 0; j0 < need; j0 += 4) {
           int c[4];
           float sj[4];
-          uint2 vw[4];
+          float4 vw[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) c[u] = tk[min(j0 + u, need - 1)];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             sj[u] = j0 + u < need ? lsm[c[u] * kRecLogits + g] : kNegBig;
-            vw[u] = reinterpret_cast<const uint2*>(lvm)[c[u] * 32 + d4];
+            if constexpr (sizeof(ET) == 2) {
+              const uint2 x = reinterpret_cast<const uint2*>(lvm)[c[u] * 32 + d4];
+              vw[u] = make_float4(bf16_lo(x.x), bf16_hi(x.x), bf16_lo(x.y), bf16_hi(x.y));
+            } else {
+              vw[u] = reinterpret_cast<const float4*>(lvm)[c[u] * 32 + d4];
+            }
           }
           const float m4 = fmaxf(fmaxf(sj[0], sj[1]), fmaxf(sj[2], sj[3]));
           const float m_new = fmaxf(mn, m4);
@@ -366,8 +381,8 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
           for (int u = 0; u < 4; ++u) {
             const float wgt = j0 + u < need ? exp2f(sj[u] - m_new) : 0.f;
             ls += wgt;
-            a.x = fmaf(wgt, bf16_lo(vw[u].x), a.x); a.y = fmaf(wgt, bf16_hi(vw[u].x), a.y);
-            a.z = fmaf(wgt, bf16_lo(vw[u].y), a.z); a.w = fmaf(wgt, bf16_hi(vw[u].y), a.w);
+            a.x = fmaf(wgt, vw[u].x, a.x); a.y = fmaf(wgt, vw[u].y, a.y);
+            a.z = fmaf(wgt, vw[u].z, a.z); a.w = fmaf(wgt, vw[u].w, a.w);
           }
         }
         *reinterpret_cast<float4*>(&ex_acc[g][4 * d4]) = a;
@@ -460,8 +475,11 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
 // ---------------------------------------------------------------------------------------------
 FusePlan plan_fused(const fasa_shape& s, bool by_sequence) {
   FusePlan p{0, 0, 0};
-  if (s.dtype != FASA_BF16) return p;                       // float32 caches take the staged kernels
   if (!by_sequence && s.budget >= s.n_ctx) return p;        // everything selected: nothing to select
+  // float32 with one or two query heads per KV head and more than an eighth selected: the tiles are what the kernel
+  // spends its time on, and the vector ALUs of the staged attention are faster at them (attend.hip; one head, 4 rows
+  // of 20000, 3000 selected: 22.8 / 20.2 us; 5 % of 30000: 17.5 / 19.1; four heads, 16 rows, 3000 of 16000: 31.0 / 38.9)
+  if (s.dtype == FASA_F32 && s.n_q_heads / s.n_kv_heads <= 2 && (long long)s.budget * 8 > s.n_ctx) return p;
   const long long rows = (long long)s.batch * s.n_kv_heads;
   const long long N = s.n_ctx;
   // The kernel runs two workgroups per CU, so a grid of up to 2 * 256 workgroups is resident at once and
@@ -488,7 +506,7 @@ FusePlan plan_fused(const fasa_shape& s, bool by_sequence) {
   return p;
 }
 
-template <int G, int TPB>
+template <typename ET, int G, int TPB>
 static hipError_t launch_fused_gt(const fasa_shape& s, const FusePlan& p, const void* q, const void* K,
                                   const void* V, const float* S, uint32_t* hist, RowCtl* ctl, uint2* cand,
                                   int32_t* T, float* O, float* part_acc, float* part_ml, unsigned char* rec,
@@ -496,23 +514,41 @@ static hipError_t launch_fused_gt(const fasa_shape& s, const FusePlan& p, const 
   const int rows = s.batch * s.n_kv_heads;
   const int t_pitch = s.budget < s.n_ctx ? s.budget : s.n_ctx;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
-  return launch("fasa_select_attend", select_attend_kernel<G, TPB>, dim3(rows * p.nslices), dim3(256), st,
-                (const uint16_t*)q, (const uint16_t*)K, (const uint16_t*)V, S, hist, ctl, cand, T, O, part_acc,
+  return launch("fasa_select_attend", select_attend_kernel<ET, G, TPB>, dim3(rows * p.nslices), dim3(256), st,
+                (const ET*)q, (const ET*)K, (const ET*)V, S, hist, ctl, cand, T, O, part_acc,
                 part_ml, rec, rows, p.nslices, p.slice_len, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap, s.budget, t_pitch,
                 (long long)s.kv_stride_b, (long long)s.kv_stride_h, (long long)s.kv_stride_n, scale_log2e,
                 rl.n_ctx, rl.budget, pm);
 }
 
-template <int G>
+template <typename ET, int G>
 static hipError_t launch_fused_g(const fasa_shape& s, const FusePlan& p, const void* q, const void* K,
                                  const void* V, const float* S, uint32_t* hist, RowCtl* ctl, uint2* cand,
                                  int32_t* T, float* O, float* part_acc, float* part_ml, unsigned char* rec,
                                  hipStream_t st, RaggedLens rl, PageMap pm) {
   switch (p.tpb) {
-    case 1024: return launch_fused_gt<G, 1024>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 2048: return launch_fused_gt<G, 2048>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 3072: return launch_fused_gt<G, 3072>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 4096: return launch_fused_gt<G, 4096>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 1024: return launch_fused_gt<ET, G, 1024>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 2048: return launch_fused_gt<ET, G, 2048>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 3072: return launch_fused_gt<ET, G, 3072>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 4096: return launch_fused_gt<ET, G, 4096>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename ET>
+static hipError_t launch_fused_t(const fasa_shape& s, const FusePlan& p, const void* q, const void* K,
+                                const void* V, const float* S, uint32_t* hist, RowCtl* ctl, uint2* cand,
+                                int32_t* T, float* O, float* part_acc, float* part_ml, unsigned char* rec,
+                                hipStream_t st, RaggedLens rl, PageMap pm) {
+  switch (s.n_q_heads / s.n_kv_heads) {
+    case 1: return launch_fused_g<ET, 1>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 2: return launch_fused_g<ET, 2>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 3: return launch_fused_g<ET, 3>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 4: return launch_fused_g<ET, 4>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 5: return launch_fused_g<ET, 5>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 6: return launch_fused_g<ET, 6>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 7: return launch_fused_g<ET, 7>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
+    case 8: return launch_fused_g<ET, 8>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
     default: return hipErrorInvalidValue;
   }
 }
@@ -521,17 +557,9 @@ hipError_t launch_select_attend(const fasa_shape& s, const FusePlan& p, const vo
                                 const void* V, const float* S, uint32_t* hist, RowCtl* ctl, uint2* cand,
                                 int32_t* T, float* O, float* part_acc, float* part_ml, unsigned char* rec,
                                 hipStream_t st, RaggedLens rl, PageMap pm) {
-  switch (s.n_q_heads / s.n_kv_heads) {
-    case 1: return launch_fused_g<1>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 2: return launch_fused_g<2>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 3: return launch_fused_g<3>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 4: return launch_fused_g<4>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 5: return launch_fused_g<5>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 6: return launch_fused_g<6>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 7: return launch_fused_g<7>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    case 8: return launch_fused_g<8>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
-    default: return hipErrorInvalidValue;
-  }
+  return s.dtype == FASA_BF16
+             ? launch_fused_t<uint16_t>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm)
+             : launch_fused_t<float>(s, p, q, K, V, S, hist, ctl, cand, T, O, part_acc, part_ml, rec, st, rl, pm);
 }
 
 }  // namespace fasa

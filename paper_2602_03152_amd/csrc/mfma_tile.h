@@ -1,6 +1,6 @@
 // The attention tile engine shared by the stand-alone attention kernels and the fused selection +
-// attention kernel (paper Sec. 4.2, eq. fac_output; bf16 caches): 16 cached rows at a time, both
-// products of a tile on the matrix cores, a running softmax per query head of the GQA group.
+// attention kernel (paper Sec. 4.2, eq. fac_output): 16 cached rows at a time, both products of a tile on the
+// matrix cores, a running softmax per query head of the GQA group.  bf16 caches:
 //
 //   logits  C[row][head] = K_tile (16 rows x 128 dims) . Q^T: four v_mfma_f32_16x16x32_bf16; lane
 //           (lo = lane mod 16, hi = lane / 16) supplies chunks hi, hi+4, hi+8, hi+12 (16 bytes each) of
@@ -15,7 +15,16 @@
 // hi + lo, hi = its top 16 bits, lo = the top 16 bits of the exact remainder: k-slots 0-3 of the 32-deep
 // MFMA carry the hi parts, slots 4-7 the lo parts, against the same four V values twice.  What is
 // dropped is below 2^-16 of the weight; V is bf16 already, products are exact, sums float32.
+//
+// float32 caches: v_mfma_f32_16x16x4_f32, float32 throughout, 32 for each product.
+//   logits  lane (lo, hi) supplies chunks hi, hi+4, .., hi+28 (16 bytes each) of K row lo; MFMA (i, j) takes float
+//           j of chunk hi + 4i from all lanes: head dims 4 (hi + 4i) + j in k-slot hi.
+//   output  k-slot hi of MFMA (e, j) is row 4hi + e: the lane's own weight of it (head lo) as the A operand, and head
+//           dim 8lo + j of it as the B operand: the lane's 32 bytes of V row 4hi + e.  Nothing is permuted.
+// One tile is 64 MFMAs of 32 cycles; a CU's four matrix cores keep up with 75 KB per us, more than a CU loads.
 #pragma once
+
+#include <type_traits>
 
 #include "attend_common.h"
 
@@ -25,22 +34,51 @@ namespace fasa {
 // that at five instructions more).  Softmax weights are at most 1 and are summed with one that is 1.
 __device__ __forceinline__ float exp2_weight(float x) { return __builtin_amdgcn_exp2f(x); }
 
-struct TileKV { uint4 kc[4], vr[4]; };   // one lane's share of a tile: 4 chunks of its K row, 4 V rows x 16 bytes
+// One lane's share of a tile: the chunks hi, hi + 4, .. of K row lo and head dims 8lo .. 8lo+7 of V rows 4hi .. 4hi+3.
+// load_k: row lo of K, from its chunk hi on; load_v: V row 4hi + e, from its head dim 8lo on.
+template <typename ET> struct TileKV;
+template <> struct TileKV<uint16_t> {
+  static constexpr int kPieces = 1;      // 16-byte pieces of a lane's share of a V row
+  uint4 kc[4], vr[4];
+  __device__ __forceinline__ void load_k(const uint16_t* p) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kc[i] = *reinterpret_cast<const uint4*>(p + 32 * i);
+  }
+  __device__ __forceinline__ void load_v(int e, const uint16_t* p) { vr[e] = *reinterpret_cast<const uint4*>(p); }
+  __device__ __forceinline__ uint4 v_piece(int e, int) const { return vr[e]; }
+};
+template <> struct TileKV<float> {
+  static constexpr int kPieces = 2;
+  f32x4_t kc[8], vr[4][2];
+  __device__ __forceinline__ void load_k(const float* p) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) kc[i] = *reinterpret_cast<const f32x4_t*>(p + 16 * i);
+  }
+  __device__ __forceinline__ void load_v(int e, const float* p) {
+    vr[e][0] = *reinterpret_cast<const f32x4_t*>(p);
+    vr[e][1] = *reinterpret_cast<const f32x4_t*>(p + 4);
+  }
+  __device__ __forceinline__ uint4 v_piece(int e, int i) const { return __builtin_bit_cast(uint4, vr[e][i]); }
+};
+template <typename ET> constexpr int kChunk = 16 / (int)sizeof(ET);   // head dims per chunk of a K row
 
 // G: most query heads per KV head (1 .. 8; the tile is padded to 16 heads, lanes beyond carry zeros); kernels
 // with one instance for all group sizes pass the actual number as `heads` (<= G)
-template <int G>
+template <int G, typename ET = uint16_t>
 struct MfmaTile {
-  bf16x8_t qb[4];        // B operands of the logits: Q^T, column lo, k-slots (hi, 0..7) of MFMA i = dims 8(hi+4i)..+7
+  static constexpr bool F32 = sizeof(ET) == 4;
+  using QT = typename std::conditional<F32, f32x4_t, bf16x8_t>::type;
+  using KV = TileKV<ET>;
+  QT qb[F32 ? 8 : 4];    // B operands of the logits: Q^T, column lo, chunks hi + 4i
   f32x4_t oc[8];         // oc[j][e]: weighted V of query head 4hi + e at head dim 8lo + j
   float m_run, l_run;    // of query head lo (log2 domain); l_run over this lane's rows only until finish()
 
-  __device__ __forceinline__ void load_q(const uint16_t* q_group /* [heads][128] */, int lo, int hi, int heads = G) {
+  __device__ __forceinline__ void load_q(const ET* q_group /* [heads][128] */, int lo, int hi, int heads = G) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < (F32 ? 8 : 4); ++i) {
       uint4 x = make_uint4(0, 0, 0, 0);
-      if (lo < heads) x = *reinterpret_cast<const uint4*>(q_group + (size_t)lo * kHeadDim + 8 * (hi + 4 * i));
-      qb[i] = __builtin_bit_cast(bf16x8_t, x);
+      if (lo < heads) x = *reinterpret_cast<const uint4*>(q_group + (size_t)lo * kHeadDim + kChunk<ET> * (hi + 4 * i));
+      qb[i] = __builtin_bit_cast(QT, x);
     }
   }
   __device__ __forceinline__ void reset() {
@@ -50,22 +88,32 @@ struct MfmaTile {
     l_run = 0.f;
   }
   // scaled logits (log2 domain) of rows 4hi .. 4hi+3 of the tile for query head lo
-  __device__ __forceinline__ void logits(const TileKV& kv, float scale_log2e, float (&sv)[4]) const {
+  __device__ __forceinline__ void logits(const KV& kv, float scale_log2e, float (&sv)[4]) const {
     // The scaled logit is rounded once and that rounded value is what the running maximum and the
     // exponent see: the scaling is never fused into the subtraction of the maximum (the weight of
     // the maximal row must be exactly 1).
 #pragma clang fp contract(off)
     f32x4_t c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};   // two chains of two: half the latency
-    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[0]), qb[0], c0, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[1]), qb[1], c1, 0, 0, 0);
-    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[2]), qb[2], c0, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[3]), qb[3], c1, 0, 0, 0);
+    if constexpr (F32) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv.kc[i][0], qb[i][0], c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv.kc[i][1], qb[i][1], c1, 0, 0, 0);
+        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv.kc[i][2], qb[i][2], c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv.kc[i][3], qb[i][3], c1, 0, 0, 0);
+      }
+    } else {
+      c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[0]), qb[0], c0, 0, 0, 0);
+      c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[1]), qb[1], c1, 0, 0, 0);
+      c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[2]), qb[2], c0, 0, 0, 0);
+      c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv.kc[3]), qb[3], c1, 0, 0, 0);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) sv[e] = (c0[e] + c1[e]) * scale_log2e;
   }
   // Folds the tile into the running softmax: rows with valid[e] false get weight 0.  scs_wave: 16 floats
   // of LDS owned by this wave.
-  __device__ __forceinline__ void accumulate(const TileKV& kv, const float (&sv)[4], const bool (&valid)[4],
+  __device__ __forceinline__ void accumulate(const KV& kv, const float (&sv)[4], const bool (&valid)[4],
                                              float* scs_wave, int lo, int hi) {
     float x[4];
 #pragma unroll
@@ -73,21 +121,22 @@ struct MfmaTile {
     accumulate_full(kv, x, scs_wave, lo, hi);
   }
   // a tile whose 16 rows all count (a logit of -inf: weight 0)
-  __device__ __forceinline__ void accumulate_full(const TileKV& kv, const float (&sv)[4], float* scs_wave, int lo, int hi) {
+  __device__ __forceinline__ void accumulate_full(const KV& kv, const float (&sv)[4], float* scs_wave, int lo, int hi) {
 #pragma clang fp contract(off)
     float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
     mx = xor32_max(xor16_max(mx));
     const float m_new = fmaxf(m_run, mx);
     const float sc = exp2_weight(m_run - m_new);
     m_run = m_new;
+    float pv[4];
     uint32_t ph[4], pl[4];
     float psum = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float pv = exp2_weight(sv[e] - m_new);
-      psum += pv;
-      ph[e] = __float_as_uint(pv) & 0xffff0000u;
-      pl[e] = __float_as_uint(pv - __uint_as_float(ph[e]));      // exact; its own top 16 bits go in
+      pv[e] = exp2_weight(sv[e] - m_new);
+      psum += pv[e];
+      ph[e] = __float_as_uint(pv[e]) & 0xffff0000u;
+      pl[e] = __float_as_uint(pv[e] - __uint_as_float(ph[e]));   // exact; its own top 16 bits go in
     }
     l_run = fmaf(l_run, sc, psum);
     // A operand: k-slots (hi, 0..3) = hi parts of rows 4hi .. 4hi+3, (hi, 4..7) = lo parts
@@ -112,16 +161,24 @@ struct MfmaTile {
         oc[j][0] *= s4.x; oc[j][1] *= s4.y; oc[j][2] *= s4.z; oc[j][3] *= s4.w;
       }
     }
+    if constexpr (F32) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;   // which half of word j / 2
-      const uint32_t w0 = j < 2 ? kv.vr[0].x : j < 4 ? kv.vr[0].y : j < 6 ? kv.vr[0].z : kv.vr[0].w;
-      const uint32_t w1 = j < 2 ? kv.vr[1].x : j < 4 ? kv.vr[1].y : j < 6 ? kv.vr[1].z : kv.vr[1].w;
-      const uint32_t w2 = j < 2 ? kv.vr[2].x : j < 4 ? kv.vr[2].y : j < 6 ? kv.vr[2].z : kv.vr[2].w;
-      const uint32_t w3 = j < 2 ? kv.vr[3].x : j < 4 ? kv.vr[3].y : j < 6 ? kv.vr[3].z : kv.vr[3].w;
-      const uint32_t b01 = __builtin_amdgcn_perm(w1, w0, sel), b23 = __builtin_amdgcn_perm(w3, w2, sel);
-      const bf16x8_t vb = __builtin_bit_cast(bf16x8_t, make_uint4(b01, b23, b01, b23));
-      oc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, vb, oc[j], 0, 0, 0);
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          oc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[e], kv.vr[e][j >> 2][j & 3], oc[j], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;   // which half of word j / 2
+        const uint32_t w0 = j < 2 ? kv.vr[0].x : j < 4 ? kv.vr[0].y : j < 6 ? kv.vr[0].z : kv.vr[0].w;
+        const uint32_t w1 = j < 2 ? kv.vr[1].x : j < 4 ? kv.vr[1].y : j < 6 ? kv.vr[1].z : kv.vr[1].w;
+        const uint32_t w2 = j < 2 ? kv.vr[2].x : j < 4 ? kv.vr[2].y : j < 6 ? kv.vr[2].z : kv.vr[2].w;
+        const uint32_t w3 = j < 2 ? kv.vr[3].x : j < 4 ? kv.vr[3].y : j < 6 ? kv.vr[3].z : kv.vr[3].w;
+        const uint32_t b01 = __builtin_amdgcn_perm(w1, w0, sel), b23 = __builtin_amdgcn_perm(w3, w2, sel);
+        const bf16x8_t vb = __builtin_bit_cast(bf16x8_t, make_uint4(b01, b23, b01, b23));
+        oc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, vb, oc[j], 0, 0, 0);
+      }
     }
   }
   // The wave's totals to LDS: sm_m_wave, sm_l_wave [G]; sm_o_wave [G][128].  (A block barrier must follow

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256) void offload_attend_kernel(
   const uint32_t inv = per ? (65536u + (uint32_t)per - 1) / (uint32_t)per : 0u;   // i / per = i * inv >> 16 for i < 1024
 
   for (; tile_no < t1; tile_no += 4) {
-    TileKV kv;
+    TileKV<uint16_t> kv;
     uint32_t nd[NR][UW], dom[16];
 #pragma unroll
     for (int e = 0; e < 4; ++e)

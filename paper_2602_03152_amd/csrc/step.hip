@@ -255,13 +255,13 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
   if constexpr (sizeof(ET) == 2) {
     const int lo = lane & 15, hi = lane >> 4;
     MfmaTile<GM> tile;
-    auto load_k = [&](TileKV& kv, int j0) {
+    auto load_k = [&](TileKV<uint16_t>& kv, int j0) {
       const ET* kr = Kb + ((size_t)sm.wl[j0 + lo] << 3) + 8 * hi;
       if (p_new >= j0 && p_new < j0 + 16) kr = p_new == j0 + lo ? kn + 8 * hi : kr;   // (wave-uniform test)
 #pragma unroll
       for (int i = 0; i < 4; ++i) kv.kc[i] = *reinterpret_cast<const uint4*>(kr + 32 * i);
     };
-    auto load_v = [&](TileKV& kv, int j0) {
+    auto load_v = [&](TileKV<uint16_t>& kv, int j0) {
       const uint4 e4 = *reinterpret_cast<const uint4*>(&sm.wl[j0 + 4 * hi]);
       const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
       const ET* vp[4];
@@ -278,7 +278,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
     tile.reset();
     if (jw < cnt) {
       const int n_tiles = (cnt - jw + 16 * NWV - 1) / (16 * NWV);
-      TileKV kv;
+      TileKV<uint16_t> kv;
       float sv[4];
       tile.load_q(q, lo, hi, G);
       load_k(kv, jw);
@@ -693,8 +693,8 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
   const long long most = pm.table ? (long long)pm.n_pool * s.kv_stride_b + (1ll << pm.shift) * s.kv_stride_n
                                   : (long long)s.n_ctx * s.kv_stride_n;
   if ((most >> 3) >= 0xfffffff0ll) return kStepNone;
-  // Lines measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step as (fused.hip or the
-  // staged kernels / one launch / row form).  One compute unit gathers about 50 KB per us, which is what
+  // Lines measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step as (fused.hip / one launch /
+  // row form).  One compute unit gathers about 50 KB per us, which is what
   // ends these forms' reach in B; reading a row's scores back, and the workgroups of the last rows
   // having the machine to themselves, is what ends it in N.
   const long long rows = (long long)s.batch * s.n_kv_heads;
@@ -709,11 +709,15 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
     if (rows >= 128 && s.n_ctx >= 8192) return kStepRow;
     return kStepNone;
   }
-  // float32: the vector ALUs attend, in proportion to the query heads.
-  // 1 head, 1 row of 4096, B = 256: 16.6 / 12.1 / 13.5; 4 heads, 8 rows, B = 64: 18.4 / 15.3 / 17.2, B = 256: 20.5 / 19.8 / 20.7
-  if (ns <= 8 && rows * ns <= kAssumedCUs && bsel * (s.n_q_heads / s.n_kv_heads) <= 512) return kStepOne;
-  // 4 heads, 128 rows of 8192, B = 64: 44.6 / 49.6 / 40.6, B = 256: 51.5 / 69.4 / 47.4, B = 1024: 69.6 / 132.9 / 69.4
-  if (rows >= 128 && bsel <= 512) return kStepRow;
+  // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
+  // 1 row of 4096, B = 256: 17.3 / 12.7 / 15.5, 32 rows of 8192, B = 600: 22.2 / 22.1 / 26.3.  4 heads, 8 rows, B = 64:
+  // of 1024: 17.1 / 12.9 / 17.2, of 4096: 15.4 / 15.2 / 17.3, 32 rows of 4096: 17.0 / 18.1 / 19.1; 8 heads, 8 rows of
+  // 1024, B = 64: 18.1 / 16.5 / 21.5
+  const int group = s.n_q_heads / s.n_kv_heads;
+  if (ns <= (group == 1 ? 8 : 1) && rows * ns <= kAssumedCUs && bsel * group <= 512) return kStepOne;
+  // 128 rows, B = 256: 1 head, of 4096: 32.5 / 30.0 / 31.4, of 16384: 73.4 / 78.5 / 69.4; 4 heads, of 4096: 33.4 / 44.0 /
+  // 34.3, of 16384: 74.5 / 102.8 / 72.5; 8 heads, of 16384: 75.7 / 120.8 / 84.3
+  if (rows >= 128 && bsel <= 512 && group <= (s.n_ctx >= 8192 ? 4 : 1)) return kStepRow;
   return kStepNone;
 }
 
