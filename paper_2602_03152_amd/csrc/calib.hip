@@ -100,14 +100,14 @@ struct CalibLds {
 };
 
 // Top-K of a row by one workgroup of NT threads, which hold a stretch of it as loaded: load(c0) requests what the
-// scores of tokens c0 .. c0 + NT * 32 - 1 are made of (kCalibPerThread / TPT pieces a thread), get(c0, i, t, x, full) makes
-// those of tokens c0 + (i * NT + t) * TPT + k, a NaN beyond the row unless it is known to be full (cheap: made again in every pass, which
-// keeps 32 registers free and two workgroups of 1024 on a compute unit); opaque() hides the pieces from the
-// compiler, which would otherwise keep the scores.  score_at(n): one token's score.
-// take_one(n): token n is in the set.
+// scores of tokens c0 .. c0 + NT * kCalibPerThread - 1 are made of (kCalibPerThread / TPT pieces a thread),
+// get(c0, i, t, x, full) makes those of tokens c0 + (i * NT + t) * TPT + k, a NaN beyond the row unless it is said to
+// be full (cheap: made again in every pass, which keeps 16 registers free and two workgroups of 1024 on a
+// compute unit); opaque() hides the pieces from the compiler, which would otherwise keep the scores.
+// score_at(n): one token's score.  take_one(n): token n is in the set.
 // What reaches the cut is gathered into a list in LDS first (some 7 instructions a score per wave, where counting
 // and classifying all scores under a test takes 30); a list that comes out short of K or beyond its
-// room is not used.
+// room is not used.  Infinite scores rank like any others; where NaNs rank is unspecified, but the set has K tokens.
 template <int NT, int TPT, typename Load, typename Get, typename Opaque, typename ScoreAt, typename TakeOne>
 __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Load&& load, Get&& get, Opaque&& opaque,
                                              ScoreAt&& score_at, TakeOne&& take_one) {
@@ -119,7 +119,7 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
   if (resident) load(0);
   // the sample's keys are made distinct in their low bits: ranks are a permutation, a cut may be any value
   if (t < SMP) sm.sample[t] = (score_key(sval) & ~(uint32_t)(SMP - 1)) | (uint32_t)t;
-  if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
+  if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; }
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
   __syncthreads();
   {
@@ -185,60 +185,59 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
   }
   const int M = (int)sm.n_list;
   const bool listed = M >= kk && M <= CalibLds<NT>::kList;
+  // Without a list: all scores of the row, told from what lies beyond it by index.  As keys throughout: the key of
+  // a cut may be one that no score has (the sample's keys lost their low bits: below that of -inf lie those of
+  // NaNs), and a NaN score has a place in the order of keys like any other.
   auto for_scores = [&](int c0, auto&& f) {
     int tt = t;
     asm volatile("" : "+v"(tt));
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       float x[TPT];
-      get(c0, i, tt, x, std::false_type{});
+      get(c0, i, tt, x, std::true_type{});
 #pragma unroll
-      for (int k = 0; k < TPT; ++k) f(x[k], c0 + (i * NT + tt) * TPT + k);
+      for (int k = 0; k < TPT; ++k) {
+        const int n = c0 + (i * NT + tt) * TPT + k;
+        if (n < N) f(score_key(x[k]), n);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
   for (;;) {
-    // as floats: nearly all scores cost one comparison (a NaN - beyond the row - never passes)
-    const float flo = klo ? key_score(klo) : -INFINITY;
-    auto count = [&](float x) {
-      const uint32_t key = score_key(x);
+    const bool whole = klo == 0 && khi == 0xffffffffu;
+    auto count = [&](uint32_t key) {
       if (key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
     };
     if (listed) {
-      for (int i = t; i < M; i += NT) count(__uint_as_float(sm.list[i].x));
+      for (int i = t; i < M; i += NT) count(score_key(__uint_as_float(sm.list[i].x)));
     } else for (int c0 = 0; c0 < N; c0 += R) {
       if (!resident) load(c0);
       opaque();
-      for_scores(c0, [&](float x, int) {
-        if (x >= flo) count(x);
-      });
+      for_scores(c0, [&](uint32_t key, int) { count(key); });
     }
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
-    if (n_cand == 0) { klo = 0; khi = 0xffffffffu; shift = 22; }   // the sample misled: the whole range
+    if (n_cand == 0) {
+      if (whole) return;                                           // (fewer than K scores: the callers pass K < N)
+      klo = 0; khi = 0xffffffffu; shift = 22;                      // the sample misled: the whole range
+    }
   }
-  const float flo = klo ? key_score(klo) : -INFINITY;
   const bool ranked = n_cand <= kSelCand;
-  auto candidate = [&](uint32_t key, int n) {
-    const uint32_t p = atomicAdd(&sm.n_cnd, 1u);
-    if (p < (uint32_t)kSelCand) sm.cand[p] = make_uint2(key, (uint32_t)n);
+  auto place = [&](uint32_t key, int n) {
+    if (key > khi) take_one(n);
+    else if (ranked && key >= klo) {
+      const uint32_t p = atomicAdd(&sm.n_cnd, 1u);
+      if (p < (uint32_t)kSelCand) sm.cand[p] = make_uint2(key, (uint32_t)n);
+    }
   };
   if (listed) {
     for (int i = t; i < M; i += NT) {
       const uint2 e = sm.list[i];
-      const uint32_t key = score_key(__uint_as_float(e.x));
-      if (key > khi) take_one((int)e.y);
-      else if (ranked && key >= klo) candidate(key, (int)e.y);
+      place(score_key(__uint_as_float(e.x)), (int)e.y);
     }
   } else for (int c0 = 0; c0 < N; c0 += R) {
     if (!resident) load(c0);
     opaque();
-    for_scores(c0, [&](float x, int n) {
-      if (x >= flo) {
-        const uint32_t key = score_key(x);
-        if (key > khi) take_one(n);
-        else if (ranked) candidate(key, n);
-      }
-    });
+    for_scores(c0, place);
   }
   __syncthreads();
   if (ranked) {

@@ -96,11 +96,12 @@ constexpr int kSelCand = 256;    // candidates of the threshold bin ranked by co
 // ---------------------------------------------------------------------------------------------
 // After the counting: true once klo .. khi is the final range (need of its n_cand scores are taken, and all
 // above it); else the range to count next, the histogram zeroed - the same range, with n_cand 0, if fewer than
-// need scores were counted in it (sm.thr[2] was 0).
+// need scores were counted in it.  A range with more than kSelCand scores of one key ends the search too.
 template <typename Lds>
 __device__ __forceinline__ bool find_threshold(Lds& sm, uint32_t& klo, uint32_t& khi, int& shift, int& need, int& n_cand) {
   const int t = threadIdx.x;
   __syncthreads();
+  if (t == 0) sm.thr[2] = 0;                                  // (no bin of an earlier pass stands for this one's)
   constexpr int NT = Lds::kThreads, BPT = kSelBins / NT;     // bins per thread: 4, 2 or 1
   uint32_t hb[BPT], mine = 0;
 #pragma unroll
