@@ -32,8 +32,9 @@ __device__ __forceinline__ float key_score(uint32_t k) {
 // sample of the row's scores and the normal quantile z - and counts every score in one of kLinBins
 // bins whose resolution is highest around that prediction; the selection reads (mu, inv = 1 / scale)
 // back and classifies with the same function, so both sides agree bit for bit.  The map is monotone
-// in s whatever mu and inv are: a poor prediction costs resolution (more candidates to resolve
-// exactly), never correctness.  With u = (s - mu) * inv, in units of the scale:
+// in s, infinite scores included, whatever mu and inv > 0 are: a poor prediction costs resolution (more
+// candidates to resolve exactly), never correctness.  (With inv = 0 the bin of an infinite score would be that of
+// a NaN, the same one for both signs.)  With u = (s - mu) * inv, in units of the scale:
 //   |u| <= 0.75        128 bins per unit          (the threshold bin then holds N * pdf / 128 tokens)
 //   0.75 < |u| <= 2     32 bins per unit
 //   2 < |u| <= 8         4 bins per unit

@@ -209,7 +209,8 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
     const float second = fminf(fmaxf(d01, d23), fminf(D01, D23));             // second smallest of four
     const float sigma = 1.373f * second;
     bin_mu = fmaf(zq, sigma, loc);
-    bin_inv = sigma > 1e-30f ? 1.0f / sigma : 0.f;
+    // never 0: an infinite score then has an infinite u of its sign, and its bin lies where it ranks
+    bin_inv = sigma > 1e-30f ? fmaxf(1.0f / sigma, 1e-30f) : 1e-30f;
   }
   // the planes did not hold the appended token yet: its owner takes the pairs from LDS
   auto patch = [&](uint4& wv, int pf) {
