@@ -67,8 +67,9 @@ def _run(cmd, verbose):
 # 16-byte loads with the sc1 bit, csrc/attend_common.h).  Their destination registers may only be
 # touched after the explicit wait that follows them; check_untracked_loads() verifies that in the
 # generated device assembly, along every path of the control-flow graph, and build() refuses to link a
-# library for which it does not hold.
-ASM_CHECKED = ["attend.hip", "fused.hip"]
+# library for which it does not hold.  Which sources those are is read from the sources: all that call the merge.
+UNTRACKED_CALLS = re.compile(r"\b(combine_row|agent_b128_issue)\b")
+ASM_CHECKED = [s for s in SOURCES if UNTRACKED_CALLS.search(open(os.path.join(CSRC, s)).read())]
 
 
 def check_untracked_loads(asm_text: str):
@@ -185,7 +186,7 @@ def _check_asm(source, extra_flags, bdir, verbose):
             raise RuntimeError("%s: inline-assembly sc1 loads in a build that asked for none" % source)
         return
     if loads == 0 or waits == 0:
-        raise RuntimeError("%s: no inline-assembly sc1 loads found: remove it from ASM_CHECKED" % source)
+        raise RuntimeError("%s: no inline-assembly sc1 loads found where UNTRACKED_CALLS says there are" % source)
     if bad:
         raise UntrackedLoadsTouched("%s: registers of uncounted loads are touched before their wait: %s" % (source, bad[:5]))
 
