@@ -3,8 +3,8 @@
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 1] [--no-cpu-baseline]
 
-A "step" is one fasa_decode_step (scores + histogram, then selection and sparse attention in one
-kernel) over one batch of synthetic, HBM-resident input shaped like the chosen workload (default: the
+A "step" is one fasa_decode_step (scores, selection and sparse attention; one or two kernels, by the
+workload's size) over one batch of synthetic, HBM-resident input shaped like the chosen workload (default: the
 Llama-3-8B-shaped layer at 32k context, budget 2048, 16 dominant FCs).  The step rotates over R
 independent buffer sets so that the bytes a step touches have left the 256 MB last-level cache before
 their set comes round again.
@@ -177,7 +177,9 @@ def offload(args, w, fb, W, np, torch):
     prof = fb.profile_summary()
     fb.fasa_profile_enable(False); fb.fasa_profile_reset()
     pcie_bytes = rows * bsel * (nd + w.head_dim) * e
-    g_us = prof["fasa_offload_gather"][1] / prof["fasa_offload_gather"][0] * 1e3
+    # the kernel that reads host memory: bf16 attends in it, float32 only gathers
+    link = "fasa_offload_attend" if "fasa_offload_attend" in prof else "fasa_offload_gather"
+    g_us = prof[link][1] / prof[link][0] * 1e3
     gpu_cache = rows * (w.n_ctx * 2 * w.n_fc + bsel * nd + bsel * w.head_dim) * e      # App. C memory model
     full_cache = rows * w.n_ctx * 2 * w.head_dim * e
     out = {
@@ -187,7 +189,7 @@ def offload(args, w, fb, W, np, torch):
         "config": {"workload": w.name + "_offload", "batch": w.batch, "n_q_heads": w.n_q_heads,
                    "n_kv_heads": w.n_kv_heads, "head_dim": w.head_dim, "n_ctx": w.n_ctx, "budget": bsel,
                    "n_fc": w.n_fc, "storage_dtype": w.dtype, "launch": "eager", "buffer_sets": 1},
-        "roofline": {"bound": "pcie", "kernel": "fasa_offload_gather", "achieved": round(pcie_bytes / g_us / 1e3, 2),
+        "roofline": {"bound": "pcie", "kernel": link, "achieved": round(pcie_bytes / g_us / 1e3, 2),
                      "peak": PCIE_PEAK_GBPS, "unit": "GB/s", "frac": round(pcie_bytes / g_us / 1e3 / PCIE_PEAK_GBPS, 4),
                      "traffic": None},
         "kernels": {k: {"launches": n, "avg_us": round(ms / n * 1e3, 3)} for k, (n, ms) in prof.items()},
@@ -652,6 +654,25 @@ def stage_timers(args, w, fb, W, np, torch):
         print("---- step %d (cold: 1 GiB read since the step before) ----" % (3 + i), flush=True)
 
 
+def kernel_bytes(w):
+    """Algorithmic bytes per launch (what the method itself must move) of every kernel that scores, selects or attends
+    in a decode step of workload w or in its full-KV baseline."""
+    rows, e, bsel = w.batch * w.n_kv_heads, w.elem_bytes, min(w.budget, w.n_ctx)
+    planes, scores = rows * w.n_ctx * 2 * w.n_fc * e, rows * w.n_ctx * 4
+    gather = rows * 2 * bsel * w.head_dim * e
+    return {
+        "fasa_score_hist": planes,
+        "fasa_score": planes,
+        "fasa_select": scores,
+        "fasa_select_all": rows * bsel * 4,
+        "fasa_sparse_attend": gather,
+        "fasa_select_attend": scores + gather,      # scores read + rows gathered
+        "fasa_row": scores + gather,
+        "fasa_step": planes + gather,               # the whole step: its scores need not leave the chip
+        "fasa_dense_attend": rows * 2 * w.n_ctx * w.head_dim * e,
+    }
+
+
 def source_hash():
     """Hash of the kernel sources: measured HBM traffic is only quoted for the sources it was measured on."""
     import hashlib
@@ -821,15 +842,7 @@ def measure(args, w, fb, W, np, torch, steps, warmup, full):
     fb.fasa_profile_enable(False)
     fb.fasa_profile_reset()
 
-    alg_bytes = {   # algorithmic bytes per launch of each kernel (what the method itself must move)
-        "fasa_score_hist": rows * w.n_ctx * 2 * w.n_fc * e,
-        "fasa_score": rows * w.n_ctx * 2 * w.n_fc * e,
-        "fasa_select": rows * w.n_ctx * 4,
-        "fasa_select_all": rows * bsel * 4,
-        "fasa_sparse_attend": rows * 2 * bsel * w.head_dim * e,
-        "fasa_select_attend": rows * w.n_ctx * 4 + rows * 2 * bsel * w.head_dim * e,    # scores read + rows gathered
-        "fasa_dense_attend": rows * 2 * w.n_ctx * w.head_dim * e,
-    }
+    alg_bytes = kernel_bytes(w)
     kernels = {}
     for name, (launches, ms) in {**prof, **prof_dense}.items():
         us = ms / launches * 1e3
