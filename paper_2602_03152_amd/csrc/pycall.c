@@ -69,16 +69,14 @@ static void* structure(PyObject* x, size_t size, int* ok) {
   return p;
 }
 
-static size_t bytes_of(PyObject* x, int* ok) {
-  const size_t n = PyLong_AsSize_t(x);
-  if (n == (size_t)-1 && PyErr_Occurred()) *ok = 0;
+/* integers as ctypes converts them: anything with __index__ (numpy's integers too), reduced to the type's width */
+static unsigned long int_bits(PyObject* x, int* ok) {
+  const unsigned long n = PyLong_AsUnsignedLongMask(x);
+  if (n == (unsigned long)-1 && PyErr_Occurred()) *ok = 0;
   return n;
 }
-static int32_t int_of(PyObject* x, int* ok) {
-  const long n = PyLong_AsLong(x);
-  if (n == -1 && PyErr_Occurred()) *ok = 0;
-  return (int32_t)n;
-}
+static size_t bytes_of(PyObject* x, int* ok) { return (size_t)int_bits(x, ok); }
+static int32_t int_of(PyObject* x, int* ok) { return (int32_t)int_bits(x, ok); }
 
 #define SHAPE(i) ((const fasa_shape*)structure(a[i], sizeof(fasa_shape), &ok))
 #define PAGING(i) ((const fasa_paging*)structure(a[i], sizeof(fasa_paging), &ok))

@@ -1,0 +1,41 @@
+"""The marshalling module takes what ctypes takes for the same declarations, and refuses what ctypes refuses.
+(No GPU: every call ends in the library's own argument checks.)"""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from tests.test_abi_cpu import A, _shape, fb
+
+
+def _status(fn, *a):
+    try:
+        fn(*a)
+    except fb.FasaError as e:
+        return e.status
+    return 0
+
+
+@pytest.mark.parametrize("as_int", [int, np.int64, np.uint64, np.int32], ids=lambda t: t.__name__)
+def test_sizes_and_ranges_are_any_integer(as_int):
+    s = _shape()
+    need = fb.fasa_workspace_bytes(s)
+    for size in (as_int(0), as_int(need - 1)):
+        assert _status(fb.fasa_topk, s, A, A, A, size, 0) == fb.FASA_EWORKSPACE
+    # large enough a size gets past its check: to the pointer's
+    assert _status(fb.fasa_topk, s, A, A, None, as_int(need), 0) == fb.FASA_EINVAL
+    assert _status(fb.fasa_pack_kcache, s, A, A, A, as_int(7), as_int(7), 0) == 0          # empty range
+    assert _status(fb.fasa_pack_kcache, s, A, A, A, as_int(9), as_int(7), 0) == fb.FASA_EINVAL
+    assert _status(fb.fasa_offload_decode_step, s, A, A, A, A, A, None, None, A, A, A, A, as_int(need), A, as_int(16), 0) == fb.FASA_EWORKSPACE
+    assert _status(fb.fasa_contextual_agreement, s, A, A, as_int(64), A, A, as_int(16), 0) == fb.FASA_EWORKSPACE
+
+
+def test_integers_are_reduced_as_by_ctypes():
+    s = _shape()
+    for n0, n1 in ((-1, 5), ((1 << 32) + 9, 7), ((1 << 65) + 9, 7), (True, 0)):       # (all of them refused)
+        want = fb.lib.fasa_pack_kcache(C.byref(s), A, A, A, n0, n1, None)
+        assert want == fb.FASA_EINVAL and _status(fb.fasa_pack_kcache, s, A, A, A, n0, n1, 0) == want
+    assert _status(fb.fasa_topk, s, A, A, None, -1, 0) == fb.FASA_EINVAL
+    for bad in (5.0, "5", None, np.float64(5)):
+        with pytest.raises(TypeError):
+            fb.fasa_topk(s, A, A, A, bad, 0)
