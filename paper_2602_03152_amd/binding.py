@@ -146,14 +146,24 @@ def _stream(stream) -> Optional[int]:
     return int(stream)
 
 
+def _refuse(x, struct) -> None:
+    """Raises what ctypes raises for x where a call takes a pointer to struct."""
+    C.byref(x)                                     # TypeError unless x is a ctypes object
+    raise C.ArgumentError("expected a %s, not a %s" % (struct.__name__, type(x).__name__))
+
+
+def _bind(device) -> None:
+    _pycall.bind(_LIB_PATH, _ptr, device, torch._C._cuda_getCurrentRawStream, FasaShape, FasaPaging, _refuse)
+
+
 def _first_device() -> int:
     """The current device, asked for the first time: initialises torch's GPU runtime, then steps aside."""
     torch.cuda.current_stream()
-    _pycall.bind(_LIB_PATH, _ptr, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    _bind(torch._C._cuda_getDevice)
     return torch._C._cuda_getDevice()
 
 
-_pycall.bind(_LIB_PATH, _ptr, _first_device, torch._C._cuda_getCurrentRawStream)
+_bind(_first_device)
 
 
 def _check(status: int, where: str):

@@ -15,10 +15,13 @@
 static PyObject *s_data_ptr, *s_cuda_stream; /* interned method and attribute names */
 static PyObject *f_address;                  /* Python: address of anything else */
 static PyObject *f_device, *f_raw_stream;    /* torch._C: current device, its current stream */
+static PyObject *t_shape, *t_paging;         /* the binding's ctypes structures */
+static PyObject* f_refuse;                   /* Python: raises what ctypes raises for another object in their place */
 
-/* address of x, *ok = 0 with an exception set if there is none */
+/* The conversions below leave *ok = 0 and an exception behind when they fail, and do nothing once that has
+ * happened: the first argument that is refused is the one reported. */
 static void* address(PyObject* x, int* ok) {
-  if (x == Py_None) return NULL;
+  if (!*ok || x == Py_None) return NULL;
   PyObject* v;
   if (PyLong_Check(x)) {
     v = x;
@@ -40,6 +43,7 @@ static void* address(PyObject* x, int* ok) {
 
 static void* stream_of(PyObject* x, int* ok) {
   PyObject* v;
+  if (!*ok) return NULL;
   if (x == Py_None) {
     PyObject* dev = PyObject_CallNoArgs(f_device);
     if (!dev) { *ok = 0; return NULL; }
@@ -59,18 +63,25 @@ static void* stream_of(PyObject* x, int* ok) {
   return p;
 }
 
-/* memory of a ctypes structure (it exports its own bytes) */
-static void* structure(PyObject* x, size_t size, int* ok) {
+/* memory of a ctypes structure of that type (it exports its own bytes) */
+static void* structure(PyObject* x, PyObject* type, int* ok) {
   Py_buffer b;
+  if (!*ok) return NULL;
+  if (!PyObject_TypeCheck(x, (PyTypeObject*)type)) {
+    PyObject* r = PyObject_CallFunctionObjArgs(f_refuse, x, type, NULL);
+    if (r) { Py_DECREF(r); PyErr_SetString(PyExc_TypeError, "wrong structure"); }
+    *ok = 0;
+    return NULL;
+  }
   if (PyObject_GetBuffer(x, &b, PyBUF_SIMPLE) != 0) { *ok = 0; return NULL; }
   void* p = b.buf;
-  if ((size_t)b.len < size) { PyErr_SetString(PyExc_TypeError, "structure too small"); *ok = 0; }
   PyBuffer_Release(&b); /* x is alive for the length of the call: it is one of its arguments */
   return p;
 }
 
 /* integers as ctypes converts them: anything with __index__ (numpy's integers too), reduced to the type's width */
 static unsigned long int_bits(PyObject* x, int* ok) {
+  if (!*ok) return 0;
   const unsigned long n = PyLong_AsUnsignedLongMask(x);
   if (n == (unsigned long)-1 && PyErr_Occurred()) *ok = 0;
   return n;
@@ -78,8 +89,8 @@ static unsigned long int_bits(PyObject* x, int* ok) {
 static size_t bytes_of(PyObject* x, int* ok) { return (size_t)int_bits(x, ok); }
 static int32_t int_of(PyObject* x, int* ok) { return (int32_t)int_bits(x, ok); }
 
-#define SHAPE(i) ((const fasa_shape*)structure(a[i], sizeof(fasa_shape), &ok))
-#define PAGING(i) ((const fasa_paging*)structure(a[i], sizeof(fasa_paging), &ok))
+#define SHAPE(i) ((const fasa_shape*)structure(a[i], t_shape, &ok))
+#define PAGING(i) ((const fasa_paging*)structure(a[i], t_paging, &ok))
 #define P(i) address(a[i], &ok)
 #define I(i) int_of(a[i], &ok)
 #define Z(i) bytes_of(a[i], &ok)
@@ -131,12 +142,13 @@ ENTRY(offload_decode_step, 16, const fasa_shape* s = SHAPE(0); void* q = P(1); v
 ENTRY(contextual_agreement, 8, const fasa_shape* s = SHAPE(0); void* q = P(1); void* Kp = P(2); int32_t k = I(3);
       float* ca = P(4); void* ws = P(5); size_t z = Z(6); void* st = STREAM(7), s, q, Kp, k, ca, ws, z, st)
 
-/* bind(library path, address function, current device function, raw stream function) */
+/* bind(library path, address function, current device function, raw stream function, shape type, paging type, refusal) */
 static PyObject* py_bind(PyObject* self, PyObject* args) {
   (void)self;
   const char* path;
-  PyObject *adr, *dev, *raw;
-  if (!PyArg_ParseTuple(args, "sOOO", &path, &adr, &dev, &raw)) return NULL;
+  PyObject *adr, *dev, *raw, *shape, *paging, *refuse;
+  if (!PyArg_ParseTuple(args, "sOOOO!O!O", &path, &adr, &dev, &raw, &PyType_Type, &shape, &PyType_Type, &paging, &refuse))
+    return NULL;
   void* h = dlopen(path, RTLD_NOW); /* the copy that is loaded already */
   if (!h) { PyErr_SetString(PyExc_ImportError, dlerror()); return NULL; }
 #define BIND(name)                                                                             \
@@ -147,10 +159,13 @@ static PyObject* py_bind(PyObject* self, PyObject* args) {
   BIND(pack_kcache) BIND(score) BIND(topk) BIND(sparse_attend) BIND(dense_attend) BIND(decode_step)
   BIND(decode_step_static) BIND(decode_step_ragged) BIND(pack_kcache_paged) BIND(decode_step_paged)
   BIND(offload_decode_step) BIND(contextual_agreement)
-  Py_INCREF(adr); Py_INCREF(dev); Py_INCREF(raw);
+  Py_INCREF(adr); Py_INCREF(dev); Py_INCREF(raw); Py_INCREF(shape); Py_INCREF(paging); Py_INCREF(refuse);
   Py_XSETREF(f_address, adr);
   Py_XSETREF(f_device, dev);
   Py_XSETREF(f_raw_stream, raw);
+  Py_XSETREF(t_shape, shape);
+  Py_XSETREF(t_paging, paging);
+  Py_XSETREF(f_refuse, refuse);
   Py_RETURN_NONE;
 }
 

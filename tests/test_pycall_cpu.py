@@ -39,3 +39,35 @@ def test_integers_are_reduced_as_by_ctypes():
     for bad in (5.0, "5", None, np.float64(5)):
         with pytest.raises(TypeError):
             fb.fasa_topk(s, A, A, A, bad, 0)
+
+
+def test_structures_are_checked_by_type():
+    """A call takes the binding's own structures (and what derives from them), nothing that merely has as many bytes."""
+    class Shape(fb.FasaShape):
+        pass
+
+    s, pg = _shape(), fb.FasaPaging(A, 64, 16, 100, 0)
+    own = Shape.from_buffer_copy(s)
+    assert _status(fb.fasa_topk, own, A, A, A, 0, 0) == fb.FASA_EWORKSPACE
+    step = lambda shape, paging: fb.fasa_decode_step_paged(shape, paging, A, A, A, A, A, None, None, None, None, A, A, A, A, 0, 0)
+    assert _status(step, own, pg) == fb.FASA_EWORKSPACE
+    for other in (bytearray(bytes(s)), bytes(s), np.zeros(64, np.uint8), None, 0, A):
+        with pytest.raises(TypeError):
+            fb.fasa_topk(other, A, A, A, 0, 0)
+        with pytest.raises(TypeError):
+            step(s, other)
+    for other in (pg, C.pointer(s), (fb.FasaShape * 1)(s), C.create_string_buffer(bytes(s))):
+        with pytest.raises(C.ArgumentError):
+            fb.lib.fasa_topk(C.byref(other), A, A, A, 0, None)
+        with pytest.raises(C.ArgumentError):
+            fb.fasa_topk(other, A, A, A, 0, 0)
+    with pytest.raises(C.ArgumentError):
+        step(s, s)
+
+
+def test_the_first_refused_argument_is_reported():
+    """Also where a later argument goes through a path of its own (an array's address, a bad size, a bad stream)."""
+    with pytest.raises(TypeError, match="ctypes instance"):
+        fb.fasa_topk("no shape", np.zeros(4, np.float32), object(), A, "no size", "no stream")
+    with pytest.raises(TypeError, match="address"):
+        fb.fasa_topk(_shape(), object(), np.zeros(4, np.int32), A, "no size", "no stream")
