@@ -9,6 +9,7 @@ been built (python -m paper_2602_03152_amd.build): there is no fallback path.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional
 
@@ -110,7 +111,9 @@ lib = _lib   # raw handle, for tests of the C ABI itself
 try:
     from . import _pycall
 except ImportError as e:
-    raise ImportError("_pycall.so is not built; run `python -m paper_2602_03152_amd.build`") from e
+    if importlib.util.find_spec(__package__ + "._pycall") is None:
+        raise ImportError("the _pycall module is not built for this interpreter; run `python -m paper_2602_03152_amd.build`") from e
+    raise ImportError("the _pycall module is built but cannot be loaded: %s" % e) from e
 
 
 def make_shape(batch, n_q_heads, n_kv_heads, head_dim, n_fc, n_ctx, n_cap, budget, dtype,

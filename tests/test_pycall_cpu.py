@@ -71,3 +71,28 @@ def test_the_first_refused_argument_is_reported():
         fb.fasa_topk("no shape", np.zeros(4, np.float32), object(), A, "no size", "no stream")
     with pytest.raises(TypeError, match="address"):
         fb.fasa_topk(_shape(), object(), np.zeros(4, np.int32), A, "no size", "no stream")
+
+
+def _import_error(tmp_path, module):
+    """The message of importing a copy of the package whose marshalling module is the given bytes (None: not there)."""
+    import os
+    import subprocess
+    import sys
+    pkg = tmp_path / "paper_2602_03152_amd"
+    pkg.mkdir(parents=True)
+    src = os.path.dirname(fb.__file__)
+    for name in ("__init__.py", "binding.py"):
+        (pkg / name).write_bytes(open(os.path.join(src, name), "rb").read())
+    os.symlink(fb._LIB_PATH, pkg / "libfasa.so")
+    if module is not None:
+        (pkg / os.path.basename(fb._pycall.__file__)).write_bytes(module)
+    p = subprocess.run([sys.executable, "-c", "import paper_2602_03152_amd.binding"], cwd=tmp_path, text=True,
+                       env={k: v for k, v in os.environ.items() if k != "FASA_LIB"}, stderr=subprocess.PIPE, timeout=100)
+    assert p.returncode != 0
+    return p.stderr.strip().splitlines()[-1]
+
+
+def test_a_module_that_is_missing_is_told_from_one_that_does_not_load(tmp_path):
+    assert "not built" in _import_error(tmp_path / "a", None)
+    msg = _import_error(tmp_path / "b", b"not a shared object")
+    assert "not built" not in msg and "cannot be loaded" in msg
