@@ -3,7 +3,7 @@
     python -m paper_2602_03152_amd.build
 
 Objects go to paper_2602_03152_amd/_build/, the library to paper_2602_03152_amd/libfasa.so, the Python binding's
-marshalling module to paper_2602_03152_amd/_pycall.so.
+marshalling module to paper_2602_03152_amd/_pycall.<ABI>.so.
 
     python -m paper_2602_03152_amd.build --sanitize
 
@@ -37,7 +37,9 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfasa.so")
 LIB_TRACE = os.path.join(PKG, "libfasa_trace.so")
-PYCALL = os.path.join(PKG, "_pycall.so")       # argument marshalling of the Python binding (csrc/pycall.c)
+# argument marshalling of the Python binding (csrc/pycall.c), under the name that only this interpreter's ABI loads
+PYCALL = os.path.join(PKG, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
+PYCALL_UNTAGGED = os.path.join(PKG, "_pycall.so")   # as it was once built: any interpreter would load it
 FLOORS = os.path.join(PKG, "fasa_floors")      # stand-alone measurement program (csrc/floors.hip)
 SOURCES = ["api.hip", "pack.hip", "score.hip", "topk.hip", "attend.hip", "fused.hip", "step.hip", "offload.hip", "calib.hip"]
 
@@ -256,6 +258,8 @@ def _build(verbose, extra_flags, trace) -> str:
     with ThreadPoolExecutor(max_workers=8) as ex:
         for fut in [ex.submit(j) for j in jobs]:
             fut.result()
+    if not extra_flags and os.path.exists(PYCALL_UNTAGGED):
+        os.remove(PYCALL_UNTAGGED)
     _run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", lib, *objs], verbose)
     return lib
 
