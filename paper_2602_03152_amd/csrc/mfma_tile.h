@@ -62,7 +62,7 @@ template <> struct TileKV<float> {
 };
 template <typename ET> constexpr int kChunk = 16 / (int)sizeof(ET);   // head dims per chunk of a K row
 
-// G: most query heads per KV head (1 .. 8; the tile is padded to 16 heads, lanes beyond carry zeros); kernels
+// G: most query heads per KV head (1 .. 8; the tile is padded to 16 heads, whose results nobody reads); kernels
 // with one instance for all group sizes pass the actual number as `heads` (<= G)
 template <int G, typename ET = uint16_t>
 struct MfmaTile {
@@ -73,7 +73,18 @@ struct MfmaTile {
   f32x4_t oc[8];         // oc[j][e]: weighted V of query head 4hi + e at head dim 8lo + j
   float m_run, l_run;    // of query head lo (log2 domain); l_run over this lane's rows only until finish()
 
-  __device__ __forceinline__ void load_q(const ET* q_group /* [heads][128] */, int lo, int hi, int heads = G) {
+  // The group's queries.  Lanes beyond the group take its last head again, whose results nobody reads: no load stands
+  // under a test, because the compiler may wait for it where the branches meet, and did: the first rows were only
+  // requested when the queries were there (2 x 8 rows, 1250 of 20011 tokens selected: 8.33 us, like this 8.00).
+  __device__ __forceinline__ void load_q(const ET* q_group /* [G][128] */, int lo, int hi) {
+    const ET* p = q_group + (size_t)min(lo, G - 1) * kHeadDim + kChunk<ET> * hi;
+#pragma unroll
+    for (int i = 0; i < (F32 ? 8 : 4); ++i) qb[i] = __builtin_bit_cast(QT, *reinterpret_cast<const uint4*>(p + 4 * i * kChunk<ET>));
+  }
+  // With a run-time group size: only the lanes that have a head load, the others carry zeros.  The kernels that use this
+  // have 8 or 16 waves on a compute unit at it, whose requests for the copies would take longer than the wait
+  // (decode step in one launch, 8 rows of 1531, 192 selected: 11.59 us, with copies 11.75; of 6000, 250: 14.80 / 15.08).
+  __device__ __forceinline__ void load_q(const ET* q_group /* [heads][128] */, int lo, int hi, int heads) {
 #pragma unroll
     for (int i = 0; i < (F32 ? 8 : 4); ++i) {
       uint4 x = make_uint4(0, 0, 0, 0);
