@@ -119,7 +119,7 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
   if (resident) load(0);
   // the sample's keys are made distinct in their low bits: ranks are a permutation, a cut may be any value
   if (t < SMP) sm.sample[t] = (score_key(sval) & ~(uint32_t)(SMP - 1)) | (uint32_t)t;
-  if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; }
+  if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
   __syncthreads();
   {

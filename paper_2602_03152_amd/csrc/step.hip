@@ -421,7 +421,7 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
   const int t = threadIdx.x, lane = t & 63;
   // the sample's keys are made distinct in their low bits: ranks are a permutation, a cut may be any value
   if (t < kSample) sm.sample[t] = (score_key(sval) & ~(uint32_t)(kSample - 1)) | (uint32_t)t;
-  if (t == 0) { sm.n_list = 0; sm.p_new = -1; }
+  if (t == 0) { sm.n_list = 0; sm.p_new = -1; sm.thr[2] = 0; }
   __syncthreads();
   {
     constexpr int P = NT / kSample;                           // threads per sample value
