@@ -31,7 +31,7 @@ __device__ __forceinline__ void fma_pairs<float>(const uint4& w, float qlo, floa
 // that are expected among the B best.  In one row of a few thousand the cut still comes out too high;
 // whoever uses it checks that B scores reach it and otherwise looks at all of them.
 constexpr int kSample = 128;
-__device__ __forceinline__ int sample_rank(int bsel, int n, int m = kSample) {
+__host__ __device__ __forceinline__ int sample_rank(int bsel, int n, int m = kSample) {
   const float ps = (float)bsel * ((float)m / (float)n);
   return (int)(ps + 3.5f * sqrtf(ps) + 3.0f);
 }

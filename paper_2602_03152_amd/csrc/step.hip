@@ -686,6 +686,35 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // ---------------------------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------------------------
+// Where the row form is the faster one after the scores.  It pays where the workgroups of the split form (fused.hip; two
+// per compute unit, at most 4096 tokens each) no longer fit at once, and while reading the scores, not
+// gathering on one compute unit, is what a row takes: the line in B falls with rows * N.
+static bool row_form(const fasa_shape& s, long long rows, int bsel) {
+  const long long n = s.n_ctx, cells = rows * n;
+  if (rows <= 64 && rows * ((n + 4095) / 4096) <= 2 * kAssumedCUs) return false;
+  // A row whose list overflows is read again from memory several times over, and holds up the launch: its expected length
+  // plus four standard deviations has to fit.  64 rows of 65536, us (fused.hip / row form): B = 64: 76.6 / 68.1, B = 512:
+  // 79.4 / 99.0; 40 rows of 100000, B = 512: 79 / 153
+  const float r = (float)sample_rank(bsel, s.n_ctx);
+  if ((r + 4.f * sqrtf(r)) * (float)n > (float)(kSample * kListPerThread * kRowNT)) return false;
+  // us (fused.hip / row form), bf16.  N = 5000 .. 8192, B = 64 .. 300: 96 rows 19.7 / 19.7, 22.4 / 21.2, 160: 26.5 / 25.4,
+  // 512: 71.0 / 67.6, but of 4096: 54.7 / 59.3.  N = 8192, B = 256: 64 rows 21.9 / 23.6, 72: 24.7 / 24.8, 80: 25.7 / 25.2;
+  // B = 512: 80 rows 28.0 / 28.9, 128: 35.2 / 34.8; B = 1024: 128 rows 42.0 / 43.0, 256: 70.1 / 63.1.  N = 16384, B = 512: 64
+  // rows 31.1 / 32.1, 72: 34.3 / 34.0, 96: 40.8 / 39.2, 128: 48.9 / 46.0; B = 1024: 80 rows 40.9 / 42.9, 128: 55.6 / 54.0.
+  // N = 32768, B = 512: 64 rows 45.9 / 45.4, 72: 54.7 / 49.1, 128: 83.3 / 71.5; 56 rows of 40000: 51.8 / 48.6
+  const bool few = bsel * 2048ll <= cells;
+  if (s.dtype == FASA_BF16) return n >= 5120 && few;
+  // float32, 1 head.  N = 4096, B = 64: 64 rows 20.5 / 20.8, 80: 23.5 / 22.6; B = 512: 128 rows 40.3 / 41.7; 1024 rows, B = 200:
+  // 164 / 170.  N = 8192, B = 256: 80 rows 34.3 / 33.8, 96: 38.3 / 37.3; B = 512: 96 rows 43.5 / 44.9.  N = 16384, B = 256:
+  // 128 rows 72.8 / 67.5; 64 rows of 33000, B = 512: 81.6 / 76.6
+  const int group = s.n_q_heads / s.n_kv_heads;
+  if (group == 1) return (n >= 5120 || rows <= kAssumedCUs) && few;
+  // up to 4 heads (the vector ALUs attend there).  2 heads, B = 256: 128 rows of 8192 46.7 / 47.0, of 16384 72.5 / 70.4; 4 heads,
+  // B = 256: 128 rows of 8192 46.4 / 47.5, 256: 77.8 / 74.6; 96 rows of 16384 58.8 / 59.1, 128: 72.4 / 70.9; 64 rows of 33000,
+  // B = 512: 80.6 / 79.4, 48 of 50000: 85.4 / 88.1.  8 heads, 128 rows of 16384: 75.7 / 84.3
+  return rows >= 64 && n >= 8192 && cells > 3 << 19 && bsel <= 512 && group <= 4;
+}
+
 StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
   const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx;
   if (bsel > kStepMaxBudget) return kStepNone;
@@ -693,10 +722,9 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
   const long long most = pm.table ? (long long)pm.n_pool * s.kv_stride_b + (1ll << pm.shift) * s.kv_stride_n
                                   : (long long)s.n_ctx * s.kv_stride_n;
   if ((most >> 3) >= 0xfffffff0ll) return kStepNone;
-  // Lines measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step as (fused.hip / one launch /
-  // row form).  One compute unit gathers about 50 KB per us, which is what
-  // ends these forms' reach in B; reading a row's scores back, and the workgroups of the last rows
-  // having the machine to themselves, is what ends it in N.
+  // Lines of the one-launch form, measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step as
+  // (fused.hip / one launch / row form).  One compute unit gathers about 50 KB per us, which is what ends its reach
+  // in B; reading a row's scores back is what ends it in N.
   const long long rows = (long long)s.batch * s.n_kv_heads;
   const int per = kStepNT * (s.dtype == FASA_BF16 ? 4 : 2);
   const long long ns = (s.n_ctx + per - 1) / per;
@@ -705,20 +733,15 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
     if (ns == 1) return kStepOne;
     // 8 rows of 8192, B = 256: 14.6 / 14.6 / 17.3, B = 512: 16.0 / 17.0 / 19.8; 128 rows of 4096: 22.3 / 20.4 / 21.9
     if (ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320) return kStepOne;
-    // 128 rows of 16384, B = 256: 46.7 / 46.2 / 42.4, B = 1024: 58.0 / 71.3 / 54.2; 32 rows: 20.2 / 19.6 / 21.9
-    if (rows >= 128 && s.n_ctx >= 8192) return kStepRow;
-    return kStepNone;
+  } else {
+    // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
+    // 1 row of 4096, B = 256: 17.3 / 12.7 / 15.5, 32 rows of 8192, B = 600: 22.2 / 22.1 / 26.3.  4 heads, 8 rows, B = 64:
+    // of 1024: 17.1 / 12.9 / 17.2, of 4096: 15.4 / 15.2 / 17.3, 32 rows of 4096: 17.0 / 18.1 / 19.1; 8 heads, 8 rows of
+    // 1024, B = 64: 18.1 / 16.5 / 21.5
+    const int group = s.n_q_heads / s.n_kv_heads;
+    if (ns <= (group == 1 ? 8 : 1) && rows * ns <= kAssumedCUs && bsel * group <= 512) return kStepOne;
   }
-  // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
-  // 1 row of 4096, B = 256: 17.3 / 12.7 / 15.5, 32 rows of 8192, B = 600: 22.2 / 22.1 / 26.3.  4 heads, 8 rows, B = 64:
-  // of 1024: 17.1 / 12.9 / 17.2, of 4096: 15.4 / 15.2 / 17.3, 32 rows of 4096: 17.0 / 18.1 / 19.1; 8 heads, 8 rows of
-  // 1024, B = 64: 18.1 / 16.5 / 21.5
-  const int group = s.n_q_heads / s.n_kv_heads;
-  if (ns <= (group == 1 ? 8 : 1) && rows * ns <= kAssumedCUs && bsel * group <= 512) return kStepOne;
-  // 128 rows, B = 256: 1 head, of 4096: 32.5 / 30.0 / 31.4, of 16384: 73.4 / 78.5 / 69.4; 4 heads, of 4096: 33.4 / 44.0 /
-  // 34.3, of 16384: 74.5 / 102.8 / 72.5; 8 heads, of 16384: 75.7 / 120.8 / 84.3
-  if (rows >= 128 && bsel <= 512 && group <= (s.n_ctx >= 8192 ? 4 : 1)) return kStepRow;
-  return kStepNone;
+  return row_form(s, rows, bsel) ? kStepRow : kStepNone;
 }
 
 template <typename ET, int NB, int GM>
