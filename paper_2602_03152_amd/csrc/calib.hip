@@ -216,6 +216,7 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
       for_scores(c0, [&](uint32_t key, int) { count(key); });
     }
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+    if (t == 0) sm.thr[2] = 0;                                     // (all have read it)
     if (n_cand == 0) {
       if (whole) return;                                           // (fewer than K scores: the callers pass K < N)
       klo = 0; khi = 0xffffffffu; shift = 22;                      // the sample misled: the whole range

@@ -96,8 +96,8 @@ constexpr int kSelCand = 256;    // candidates of the threshold bin ranked by co
 // ---------------------------------------------------------------------------------------------
 // After the counting: true once klo .. khi is the final range (need of its n_cand scores are taken, and all
 // above it); else the range to count next, the histogram zeroed - the same range, with n_cand 0, if fewer than
-// need scores were counted in it.  sm.thr[2] has to be 0 at the first call and is 0 again before each further one.  A
-// range of one key with more than kSelCand scores ends the search too.
+// need scores were counted in it.  sm.thr[2] has to be 0 at the call then; where every score of the range is counted
+// (need is met in all passes) only at the first.  A range of one key with more than kSelCand scores ends the search too.
 template <typename Lds>
 __device__ __forceinline__ bool find_threshold(Lds& sm, uint32_t& klo, uint32_t& khi, int& shift, int& need, int& n_cand) {
   const int t = threadIdx.x;
@@ -129,10 +129,8 @@ __device__ __forceinline__ bool find_threshold(Lds& sm, uint32_t& klo, uint32_t&
     if (n_cand <= kSelCand || klo == khi) return true;
     shift = max(0, 22 - __clz((int)(khi - klo)));             // (khi - klo) >> shift < 1024
   }
-  __syncthreads();                                            // (all have read this pass's result)
 #pragma unroll
   for (int j = 0; j < BPT; ++j) sm.hist[BPT * t + j] = 0;
-  if (t == 0) sm.thr[2] = 0;                                  // no bin of this pass stands for the next one's
   __syncthreads();
   return false;
 }
