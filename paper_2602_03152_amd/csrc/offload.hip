@@ -92,32 +92,31 @@ constexpr int kOffInFlight = 1 << 20;
 // float32 caches.  grid = (workgroups, rows), TOK = 256 / (D / VEC) tokens per workgroup at a time.
 // Reads the selected tokens' non-dominant key part and value row from host memory, their dominant
 // pairs from Kp, and writes full rows KT[row][j][:], VT[row][j][:] (j = position in the index list).
-template <typename ET>
-__global__ __launch_bounds__(256) void offload_gather_kernel(const ET* __restrict__ Kp,
-                                                             const ET* __restrict__ Knd,
-                                                             const ET* __restrict__ Vh,
+__global__ __launch_bounds__(256) void offload_gather_kernel(const float* __restrict__ Kp,
+                                                             const float* __restrict__ Knd,
+                                                             const float* __restrict__ Vh,
                                                              const int32_t* __restrict__ fc_idx,
                                                              const int32_t* __restrict__ T,
-                                                             ET* __restrict__ KT, ET* __restrict__ VT,
+                                                             float* __restrict__ KT, float* __restrict__ VT,
                                                              int Hkv, int F, int n_cap, int n_ctx,
                                                              int count, long long sb, long long sh,
                                                              long long sn, int pairing) {
   constexpr int D = kHeadDim;
-  constexpr int VEC = 16 / sizeof(ET);
+  constexpr int VEC = 16 / (int)sizeof(float);
   constexpr int LPR = D / VEC;
   constexpr int TOK = 256 / LPR;
   __shared__ uint16_t src[D];
   __shared__ uint8_t is_dom[D];
   __shared__ int toks[TOK];
-  __shared__ ET l_nd[TOK][D];
-  __shared__ ET l_dom[TOK][D];
+  __shared__ float l_nd[TOK][D];
+  __shared__ float l_dom[TOK][D];
   const int row = blockIdx.y;
   const int b = row / Hkv, h = row % Hkv;
   const int t = threadIdx.x;
   build_dim_map(fc_idx + h * F, F, pairing, src, is_dom);
   const int nd = D - 2 * F;
-  const ET* knd = Knd + (long long)row * n_cap * nd;
-  const ET* kp = Kp + ((long long)row * F) * n_cap * 2;
+  const float* knd = Knd + (long long)row * n_cap * nd;
+  const float* kp = Kp + ((long long)row * F) * n_cap * 2;
   const int s = t / LPR, c = t % LPR;
   for (int j0 = blockIdx.x * TOK; j0 < count; j0 += gridDim.x * TOK) {
     const int nt = min(TOK, count - j0);
@@ -135,7 +134,7 @@ __global__ __launch_bounds__(256) void offload_gather_kernel(const ET* __restric
     if (s < nt) vrow = *reinterpret_cast<const uint4*>(Vh + b * sb + h * sh + (long long)toks[s] * sn + c * VEC);
     __syncthreads();
     if (s < nt) {
-      ET out[VEC];
+      float out[VEC];
 #pragma unroll
       for (int k = 0; k < VEC; ++k) {
         const uint32_t m = src[c * VEC + k];
@@ -339,7 +338,7 @@ hipError_t launch_offload_gather(const fasa_shape& s, const void* Kp, const void
   const int count = s.budget < s.n_ctx ? s.budget : s.n_ctx;
   const int wgs = kOffInFlight / (8 * 1024);              // 8 tokens of at most 1 KB each per workgroup
   const int want = wgs / rows > 1 ? wgs / rows : 1, most = (count + 7) / 8;
-  return launch("fasa_offload_gather", offload_gather_kernel<float>, dim3(want < most ? want : most, rows), dim3(256), st,
+  return launch("fasa_offload_gather", offload_gather_kernel, dim3(want < most ? want : most, rows), dim3(256), st,
                 (const float*)Kp, (const float*)Knd, (const float*)Vh, fc_idx, T, (float*)KT, (float*)VT, s.n_kv_heads,
                 s.n_fc, s.n_cap, s.n_ctx, count, (long long)s.kv_stride_b, (long long)s.kv_stride_h,
                 (long long)s.kv_stride_n, s.pairing);

@@ -21,6 +21,7 @@ namespace fasa {
 constexpr int kStepNT = 512;                 // threads per workgroup of step_kernel
 constexpr int kRowNT = 1024;                 // threads per workgroup of row_kernel
 constexpr int kListPerThread = 8;            // places of a row's list, per thread
+constexpr int kStepMaxCtx = 16 * kStepNT;    // longest row of step_kernel: what its last workgroup's registers hold
 
 struct StepArgs {
   const void* q;
@@ -410,11 +411,13 @@ __device__ __forceinline__ void write_output(const StepArgs& a, const Lds& sm, i
 }
 
 // The list of a row whose scores the caller's threads hold in registers: score(k), k < NV, of token
-// token(k, c0) (a NaN where the row has ended); with more than `resident` tokens in the row they hold one
-// stretch of it at a time, and reload(c0) brings in the stretch that starts at c0.
+// token(k, c0) (a NaN where the row has ended).  WHOLE: they hold the whole row, c0 is 0.  Else with more than
+// `resident` tokens in the row they hold one stretch of it at a time, and reload(c0) brings in the stretch that
+// starts at c0.  (A loop that never comes round costs the one-launch step 0.3 - 0.5 us: 8 rows of 6000 tokens, B = 250,
+// 14.85 us with it, 14.53 without.)
 // 128 scores of the row, evenly spaced (`sval` of thread i < 128), are ranked; the sample_rank-th best is the cut.
 // Returns the list's length; kcut, ktop: keys of the cut (0: none) and of the sample's best.
-template <int NV, typename Lds, typename Score, typename Token, typename Reload>
+template <int NV, bool WHOLE, typename Lds, typename Score, typename Token, typename Reload>
 __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, int resident, Score&& score, Token&& token,
                                          Reload&& reload, uint32_t& kcut, uint32_t& ktop) {
   constexpr int NT = Lds::kThreads;
@@ -444,8 +447,7 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
   kcut = r > kSample ? 0u : sm.ssort[r - 1];
   ktop = sm.ssort[0];
   const float cut = r > kSample ? -INFINITY : key_score(kcut);
-  for (int c0 = 0; c0 < N; c0 += resident) {
-    if (N > resident) reload(c0);
+  auto stretch = [&](int c0) {
     unsigned long long m[NV];                                 // per wave: which lanes' k-th score reaches the cut
     uint32_t cnt = 0;
 #pragma unroll
@@ -462,6 +464,11 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
       if (score(k) >= cut && pos < (uint32_t)Lds::kList) sm.list[pos] = make_uint2(__float_as_uint(score(k)), (uint32_t)token(k, c0));
       base += (uint32_t)__popcll(m[k]);
     }
+  };
+  if constexpr (WHOLE) stretch(0);
+  else for (int c0 = 0; c0 < N; c0 += resident) {
+    if (N > resident) reload(c0);
+    stretch(c0);
   }
   __syncthreads();
   return (int)sm.n_list;
@@ -619,22 +626,18 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
     if (t == 0) a.ctl[row].done_sel = 0;                      // clean for the next call
     const int si = (int)(((long long)(t & (kSample - 1)) * N) >> 7);
     const float sval = ld_agent(srow + si);
-    constexpr int CH = 4;
+    constexpr int CH = kStepMaxCtx / (4 * kStepNT);
     float v[4 * CH];
     // the row is readable in 16-byte pieces: S is n_cap long, a multiple of 64
-    auto load_scores = [&](int c0) {
 #pragma unroll
-      for (int it = 0; it < CH; ++it) {
-        const int n = c0 + (it * kStepNT + t) * 4;
-        const uint4 x = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
-        v[4 * it] = n < N ? __uint_as_float(x.x) : NAN; v[4 * it + 1] = n + 1 < N ? __uint_as_float(x.y) : NAN;
-        v[4 * it + 2] = n + 2 < N ? __uint_as_float(x.z) : NAN; v[4 * it + 3] = n + 3 < N ? __uint_as_float(x.w) : NAN;
-      }
-    };
-    constexpr int R = CH * kStepNT * 4;
-    if (N <= R) load_scores(0);
-    M = make_list<4 * CH>(sm.row, N, bsel, sval, R, [&](int k) { return v[k]; },
-                          [&](int k, int c0) { return c0 + ((k >> 2) * kStepNT + t) * 4 + (k & 3); }, load_scores, kcut, ktop);
+    for (int it = 0; it < CH; ++it) {
+      const int n = (it * kStepNT + t) * 4;
+      const uint4 x = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
+      v[4 * it] = n < N ? __uint_as_float(x.x) : NAN; v[4 * it + 1] = n + 1 < N ? __uint_as_float(x.y) : NAN;
+      v[4 * it + 2] = n + 2 < N ? __uint_as_float(x.z) : NAN; v[4 * it + 3] = n + 3 < N ? __uint_as_float(x.w) : NAN;
+    }
+    M = make_list<4 * CH, true>(sm.row, N, bsel, sval, 0, [&](int k) { return v[k]; },
+                                [&](int k, int) { return ((k >> 2) * kStepNT + t) * 4 + (k & 3); }, [](int) {}, kcut, ktop);
   } else {
 #pragma unroll
     for (int k = 0; k < TPT; ++k) srow_lds[t * TPT + k] = acc[k];
@@ -642,7 +645,7 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
     const float sval = srow_lds[((t & (kSample - 1)) * N) >> 7];
 #pragma unroll
     for (int k = 0; k < TPT; ++k) acc[k] = n0 + k < N ? acc[k] : NAN;
-    M = make_list<TPT>(sm.row, N, bsel, sval, SL, [&](int k) { return acc[k]; }, [&](int k, int) { return n0 + k; }, [](int) {},
+    M = make_list<TPT, true>(sm.row, N, bsel, sval, 0, [&](int k) { return acc[k]; }, [&](int k, int) { return n0 + k; }, [](int) {},
                        kcut, ktop);
   }
   select_row(sm.row, M, kcut, ktop, bsel, srow, N);
@@ -676,8 +679,8 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
   constexpr int R = CH * kRowNT * 4;
   if (N <= R) load_scores(0);
   uint32_t kcut, ktop;
-  const int M = make_list<4 * CH>(sm, N, bsel, sval, R, [&](int k) { return v[k]; },
-                                  [&](int k, int c0) { return c0 + ((k >> 2) * kRowNT + t) * 4 + (k & 3); }, load_scores, kcut, ktop);
+  const int M = make_list<4 * CH, false>(sm, N, bsel, sval, R, [&](int k) { return v[k]; },
+                                         [&](int k, int c0) { return c0 + ((k >> 2) * kRowNT + t) * 4 + (k & 3); }, load_scores, kcut, ktop);
   select_row(sm, M, kcut, ktop, bsel, srow, N);
   row_attend<ET, GM>(a, sm, row, b, h, G, bsel, -1);
   write_output(a, sm, b, h, G);
@@ -747,7 +750,10 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
 template <typename ET, int NB, int GM>
 static hipError_t launch_step_v(const StepArgs& a, hipStream_t st) {
   if (a.nslices == 1) return launch("fasa_step", step_kernel<ET, NB, GM, false>, dim3(a.rows), dim3(kStepNT), st, a);
-  return launch("fasa_step", step_kernel<ET, NB, GM, true>, dim3(a.rows * a.nslices), dim3(kStepNT), st, a);
+  // float32 rows of several slices: with one query head only (plan_step)
+  if constexpr (sizeof(ET) == 2 || GM == 1)
+    return launch("fasa_step", step_kernel<ET, NB, GM, true>, dim3(a.rows * a.nslices), dim3(kStepNT), st, a);
+  return hipErrorInvalidValue;
 }
 hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* K, void* V, void* Kp,
                        const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
@@ -776,8 +782,9 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
     if (s.dtype == FASA_BF16) return launch("fasa_row", row_kernel<uint16_t, 8>, dim3(a.rows), dim3(kRowNT), st, a);
     if (G == 1) return launch("fasa_row", row_kernel<float, 1>, dim3(a.rows), dim3(kRowNT), st, a);
     if (G <= 4) return launch("fasa_row", row_kernel<float, 4>, dim3(a.rows), dim3(kRowNT), st, a);
-    return launch("fasa_row", row_kernel<float, 8>, dim3(a.rows), dim3(kRowNT), st, a);
+    return hipErrorInvalidValue;                               // (row_form)
   }
+  if (s.n_ctx > kStepMaxCtx) return hipErrorInvalidValue;      // (plan_step)
   if (s.dtype == FASA_BF16) {
     switch (s.n_fc) {
       case 8: return launch_step_v<uint16_t, 1, 8>(a, st);
