@@ -755,6 +755,19 @@ static hipError_t launch_step_v(const StepArgs& a, hipStream_t st) {
     return launch("fasa_step", step_kernel<ET, NB, GM, true>, dim3(a.rows * a.nslices), dim3(kStepNT), st, a);
   return hipErrorInvalidValue;
 }
+// The list lengths in use have an instance each, where no load of the planes stands under a test.  float32, us, with the
+// instance for any length -> with its own: 1 row of 1000 tokens, B = 256: F = 8 11.9 -> 10.2, F = 16 12.5 -> 11.0, F = 24 13.4 ->
+// 11.7, F = 32 14.3 -> 12.5; of 4096, F = 16: 14.7 -> 13.2; 4 heads, 8 rows of 1000, B = 64, F = 16: 13.9 -> 12.4; 8 heads: 17.4 -> 16.0
+template <typename ET, int GM>
+static hipError_t launch_step_f(const StepArgs& a, hipStream_t st) {
+  switch (a.F) {
+    case 8: return launch_step_v<ET, 1, GM>(a, st);
+    case 16: return launch_step_v<ET, 2, GM>(a, st);
+    case 24: return launch_step_v<ET, 3, GM>(a, st);
+    case 32: return launch_step_v<ET, 4, GM>(a, st);
+    default: return launch_step_v<ET, 0, GM>(a, st);
+  }
+}
 hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* K, void* V, void* Kp,
                        const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                        RowCtl* ctl, hipStream_t st, RaggedLens rl, PageMap pm) {
@@ -785,18 +798,10 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
     return hipErrorInvalidValue;                               // (row_form)
   }
   if (s.n_ctx > kStepMaxCtx) return hipErrorInvalidValue;      // (plan_step)
-  if (s.dtype == FASA_BF16) {
-    switch (s.n_fc) {
-      case 8: return launch_step_v<uint16_t, 1, 8>(a, st);
-      case 16: return launch_step_v<uint16_t, 2, 8>(a, st);
-      case 24: return launch_step_v<uint16_t, 3, 8>(a, st);
-      case 32: return launch_step_v<uint16_t, 4, 8>(a, st);
-      default: return launch_step_v<uint16_t, 0, 8>(a, st);
-    }
-  }
-  if (G == 1) return s.n_fc == 16 ? launch_step_v<float, 2, 1>(a, st) : launch_step_v<float, 0, 1>(a, st);
-  if (G <= 4) return launch_step_v<float, 0, 4>(a, st);
-  return launch_step_v<float, 0, 8>(a, st);
+  if (s.dtype == FASA_BF16) return launch_step_f<uint16_t, 8>(a, st);
+  if (G == 1) return launch_step_f<float, 1>(a, st);
+  if (G <= 4) return launch_step_f<float, 4>(a, st);
+  return launch_step_f<float, 8>(a, st);
 }
 
 }  // namespace fasa
