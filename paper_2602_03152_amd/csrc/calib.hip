@@ -117,26 +117,9 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
   constexpr int SMP = CalibLds<NT>::kSmp;
   const float sval = score_at((int)(((long long)(t & (SMP - 1)) * N) / SMP));
   if (resident) load(0);
-  // the sample's keys are made distinct in their low bits: ranks are a permutation, a cut may be any value
-  if (t < SMP) sm.sample[t] = (score_key(sval) & ~(uint32_t)(SMP - 1)) | (uint32_t)t;
   if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  __syncthreads();
-  {
-    constexpr int P = NT / SMP;                               // threads per sample value: 2 or 4
-    static_assert(P == 2 || P == 4, "");
-    const uint32_t me = sm.sample[t / P];
-    int rank = 0;
-#pragma unroll
-    for (int u = 0; u < SMP / 4 / P; ++u) {
-      const uint4 o = reinterpret_cast<const uint4*>(sm.sample)[P * u + t % P];
-      rank += (o.x > me ? 1 : 0) + (o.y > me ? 1 : 0) + (o.z > me ? 1 : 0) + (o.w > me ? 1 : 0);
-    }
-    rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);                              // quad_perm [1,0,3,2]
-    if constexpr (P == 4) rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);        // quad_perm [2,3,0,1]
-    if (t % P == 0) sm.ssort[rank & (SMP - 1)] = me & ~(uint32_t)(SMP - 1);
-  }
-  __syncthreads();
+  rank_sample<NT, SMP>(sval, sm.sample, sm.ssort);
   uint32_t klo = 0, khi = 0xffffffffu;
   int shift = 22, need = kk, n_cand;
   const int r = sample_rank(kk, N, SMP);

@@ -83,6 +83,30 @@ __device__ __forceinline__ int rank_in_list(const uint2* lc, int n, int i) {
 constexpr int kSelBins = 1024;
 constexpr int kSelCand = 256;    // candidates of the threshold bin ranked by counting
 
+// The keys of SMP of a row's scores (thread i < SMP brings sval) in ssort, largest first, by all NT threads of a block.
+// They are made distinct in their low bits: ranks are a permutation, and a cut may be any value.  (The low bits are
+// cleared again in ssort: such a key need not be one that a score can have.)  Two block barriers, the last at the end.
+template <int NT, int SMP>
+__device__ __forceinline__ void rank_sample(float sval, uint32_t* sample, uint32_t* ssort) {
+  const int t = threadIdx.x;
+  if (t < SMP) sample[t] = (score_key(sval) & ~(uint32_t)(SMP - 1)) | (uint32_t)t;
+  __syncthreads();
+  constexpr int P = NT / SMP;                                 // threads per sample value: adjacent lanes
+  static_assert(P == 2 || P == 4 || P == 8, "a pair, a quad or half a row of lanes per value");
+  const uint32_t me = sample[t / P];
+  int rank = 0;
+#pragma unroll
+  for (int u = 0; u < SMP / 4 / P; ++u) {
+    const uint4 o = reinterpret_cast<const uint4*>(sample)[P * u + t % P];
+    rank += (o.x > me ? 1 : 0) + (o.y > me ? 1 : 0) + (o.z > me ? 1 : 0) + (o.w > me ? 1 : 0);
+  }
+  rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);                           // quad_perm [1,0,3,2]
+  if constexpr (P >= 4) rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);     // quad_perm [2,3,0,1]
+  if constexpr (P == 8) rank += __builtin_amdgcn_update_dpp(0, rank, 0x141, 0xF, 0xF, true);    // row_half_mirror
+  if (t % P == 0) ssort[rank & (SMP - 1)] = me & ~(uint32_t)(SMP - 1);
+  __syncthreads();
+}
+
 // ---------------------------------------------------------------------------------------------
 // Selection by one workgroup of all its row's scores: the B best.  A first range of keys klo .. 2^32 - 1 (no
 // score below it may be among the B best) is cut into kSelBins bins of 2^shift keys:

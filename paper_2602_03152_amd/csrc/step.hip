@@ -422,26 +422,8 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
                                          Reload&& reload, uint32_t& kcut, uint32_t& ktop) {
   constexpr int NT = Lds::kThreads;
   const int t = threadIdx.x, lane = t & 63;
-  // the sample's keys are made distinct in their low bits: ranks are a permutation, a cut may be any value
-  if (t < kSample) sm.sample[t] = (score_key(sval) & ~(uint32_t)(kSample - 1)) | (uint32_t)t;
   if (t == 0) { sm.n_list = 0; sm.p_new = -1; sm.thr[2] = 0; }
-  __syncthreads();
-  {
-    constexpr int P = NT / kSample;                           // threads per sample value
-    static_assert(P == 4 || P == 8, "a quad or half a row of lanes per value");
-    const uint32_t me = sm.sample[t / P];
-    int rank = 0;
-#pragma unroll
-    for (int u = 0; u < kSample / 4 / P; ++u) {
-      const uint4 o = reinterpret_cast<const uint4*>(sm.sample)[P * u + t % P];
-      rank += (o.x > me ? 1 : 0) + (o.y > me ? 1 : 0) + (o.z > me ? 1 : 0) + (o.w > me ? 1 : 0);
-    }
-    rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
-    rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-    if constexpr (P == 8) rank += __builtin_amdgcn_update_dpp(0, rank, 0x141, 0xF, 0xF, true);   // row_half_mirror
-    if (t % P == 0) sm.ssort[rank & (kSample - 1)] = me & ~(uint32_t)(kSample - 1);
-  }
-  __syncthreads();
+  rank_sample<NT, kSample>(sval, sm.sample, sm.ssort);
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;     // (shares storage with the sample)
   const int r = sample_rank(bsel, N);
   kcut = r > kSample ? 0u : sm.ssort[r - 1];
