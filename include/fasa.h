@@ -147,11 +147,13 @@ int fasa_dense_attend(const fasa_shape* shape, const void* q, const void* K, con
  *   then S, T and O exactly as fasa_score -> S, fasa_topk -> T, fasa_sparse_attend -> O define them
  *   (T the same set, ties towards the lower index; O up to the order of float32 additions).
  * S and T are outputs the caller may inspect (S doubles as the score scratch).
- * How it runs: bf16 caches take two launches - the scoring kernel, which also counts a histogram of
- * the scores, then one kernel in which every workgroup classifies a range of tokens against the
- * B-th score's histogram bin and attends at once over the winners it owns, the row's last workgroup
- * settling the ties of that bin and merging the partial results.  float32 caches, rows longer than
- * 2^20 tokens and budget >= n_ctx run the three stand-alone kernels back to back. */
+ * How it runs, by the shape: short rows with small budgets take one launch, in which the workgroup that
+ * finishes a row's scores selects and attends; many rows take a scoring launch and one workgroup per row behind
+ * it; everything else a scoring launch that also counts a histogram of the scores, then one kernel in which every
+ * workgroup classifies a range of tokens against the B-th score's bin and attends at once over the winners it
+ * owns, the row's last workgroup settling the ties of that bin and merging the partial results.  Rows longer
+ * than 2^20 tokens, budget >= n_ctx, and float32 caches with one or two query heads per KV head and more
+ * than an eighth of the tokens selected run the three stand-alone kernels back to back. */
 int fasa_decode_step(const fasa_shape* shape, const void* q, void* K, void* V, void* Kp,
                      const int32_t* fc_idx, const void* k_new, const void* v_new, float* S,
                      int32_t* T, float* O, void* ws, size_t ws_bytes, void* stream);
@@ -232,7 +234,7 @@ int fasa_decode_step_paged(const fasa_shape* shape, const fasa_paging* paging, c
  *     V_host   [batch][n_kv_heads][tokens][head_dim]           dtype, strides kv_stride_{b,h,n}
  * Per step the device itself fetches the selected rows over PCIe (Alg. 2: SelectTokens,
  * TransferToGPU), rebuilds the full key rows from both parts (Combine) into `stage`, a DEVICE
- * buffer of fasa_offload_stage_bytes(), and runs the same attention over it.  Results equal those
+ * buffer of fasa_offload_stage_bytes(), and attends over them.  Results equal those
  * of fasa_decode_step on the same cache (same T; O up to float32 summation order). */
 
 /* Bytes of the device staging buffer for the gathered rows (host-only, pure; 0 on a bad shape). */

@@ -513,8 +513,9 @@ int calib_layout(const fasa_shape* shape, int32_t top_k, CalibLayout* L) {
   size_t off = 0;
   L->s_off = off;      off = align256(off + rows * shape->n_cap * 4);               // full-head scores
   L->bitmap_off = off; off = align256(off + rows * ((shape->n_ctx + 31) / 32) * 4);  // their top-K set
-  // Room for the scores of every single FC stays part of the size callers are told (they once lay there, and a
-  // workspace sized then must do for any version); nothing is written beyond the two regions above.
+  // The kernels use the two regions above.  The size callers are told, and that the call insists on, also has room for the
+  // scores of every single FC, which an earlier form of the calibration kept there: what
+  // fasa_calibration_workspace_bytes() returns for a shape does not change.
   L->total = off + rows * (shape->head_dim / 2) * shape->n_cap * 4;
   return FASA_OK;
 }

@@ -26,9 +26,8 @@ struct Row8 {
 // compute 16 heads, take longer over a tile than its loads (full KV, 4 rows of 20000, one head: 18.0 us like this,
 // 20.2 on the matrix cores; two heads 14.9 / 15.8; from four heads on the matrix cores: 31.3 / 30.5, eight 24.5 / 19.1).
 // 1-D grid of rows * n_splits workgroups, 256 threads.  A wave is 4 groups of 16 lanes; a group
-// reads one cached row per load instruction (16 lanes x 16 bytes = one 256-byte bf16 row), lane c
-// owning head dims [8c, 8c+8) of K (for the logit) and of V (for the output).  The workgroup that
-// finishes a row last merges the row's partials into O.
+// reads one cached row of 512 bytes with two load instructions, lane c owning head dims [8c, 8c+8) of K (for
+// the logit) and of V (for the output).  The workgroup that finishes a row last merges the row's partials into O.
 template <int G, bool DENSE>
 __global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restrict__ q,
                                                      const float* __restrict__ K,

@@ -105,8 +105,8 @@ struct AttendPlan {
 AttendPlan plan_attend(int rows, int count, int group);
 
 // Fused selection + attention (fused.hip): tokens per workgroup and workgroups per row.
-// tpb == 0: this shape takes the staged kernels (everything selected, or a row longer than the merge can
-// take slices of).
+// tpb == 0: this shape takes the stand-alone kernels (everything selected, a row longer than the merge can take slices
+// of, or float32 with few query heads and a large share selected).
 // Candidates per row of the fused step that are handed over with a record (logits of the group's query
 // heads + V row), and the bytes of workspace a row's records take (bf16).
 constexpr int kFuseRich = 64;

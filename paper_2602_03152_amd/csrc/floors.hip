@@ -25,12 +25,15 @@
 
 __global__ void empty_kernel(int* p) { if (p == reinterpret_cast<int*>(1)) *p = 0; }
 
-// every thread reads 16 x 16 bytes, all in flight at once; a workgroup covers 64 KB: 16 chunks of 4 KB,
-// `chunk16` uint4 apart (256 = one contiguous 64 KB block per workgroup; the scoring kernel's planes
-// are n_cap * 4 bytes apart instead)
-__global__ __launch_bounds__(256) void read_kernel(const uint4* __restrict__ src, size_t chunk16, size_t wg16,
+// every thread reads 16 x 16 bytes, all in flight at once; a workgroup covers 64 KB.  rows == 0: one contiguous block.
+// Else 16 chunks of 4 KB, one of each of a row's 16 planes, as the scoring kernel reads them: [rows][16][nslices * 4 KB],
+// with a multiple of eight rows whose workgroups lie on one XCD each.
+__global__ __launch_bounds__(256) void read_kernel(const uint4* __restrict__ src, unsigned rows, unsigned nslices,
                                                   uint32_t* __restrict__ sink) {
-  const size_t i = (size_t)blockIdx.x * wg16 + threadIdx.x;
+  const unsigned id = blockIdx.x, k = id >> 3;
+  const size_t row = k / nslices * 8 + (id & 7u), slice = k % nslices;
+  const size_t chunk16 = rows ? (size_t)nslices * 256 : 256;
+  const size_t i = (rows ? row * 16 * chunk16 + slice * 256 : (size_t)id * 4096) + threadIdx.x;
   uint4 v[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) v[u] = src[i + u * chunk16];
@@ -148,18 +151,15 @@ int main() {
   for (size_t mib : {(size_t)16, (size_t)128}) {
     const size_t bytes = mib << 20, n16 = bytes / 16;
     const int nbuf = (int)(pool_bytes / bytes);
-    for (int planes = 0; planes < 2; ++planes) {
-      // one contiguous 64 KB block per workgroup, or 16 planes of a [16][bytes / 16] array
-      const size_t wgs = n16 / 4096;
-      const size_t chunk16 = planes ? wgs * 256 : 256, wg16 = planes ? 256 : 4096;
+    for (unsigned rows : {0u, 8u, 128u}) {         // contiguous; 8 or 128 rows of 16 planes
+      const unsigned wgs = (unsigned)(n16 / 4096), nslices = rows ? wgs / rows : 1;   // whole: both are powers of two
       int k = 0;
       const double us = time_us(st, 4, [&] {
         for (int i = 0; i < nbuf; ++i, ++k)
-          hipLaunchKernelGGL(read_kernel, dim3((unsigned)wgs), dim3(256), 0, st, pool + (size_t)(k % nbuf) * n16,
-                             chunk16, wg16, sink);
+          hipLaunchKernelGGL(read_kernel, dim3(wgs), dim3(256), 0, st, pool + (size_t)(k % nbuf) * n16, rows, nslices, sink);
       }) / nbuf;
-      std::printf("read        %4zu MiB plain read, %-10s : %6.2f us  (%.2f TB/s)\n", mib,
-                  planes ? "16 planes" : "contiguous", us, bytes / us * 1e-6);
+      std::printf("read        %4zu MiB plain read, %3u rows of 16 planes (0: contiguous) : %6.2f us  (%.2f TB/s)\n", mib, rows, us,
+                  bytes / us * 1e-6);
     }
   }
   {
