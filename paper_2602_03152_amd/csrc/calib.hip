@@ -117,9 +117,10 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
   constexpr int SMP = CalibLds<NT>::kSmp;
   const float sval = score_at((int)(((long long)(t & (SMP - 1)) * N) / SMP));
   if (resident) load(0);
-  if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
-  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  rank_sample<NT, SMP>(sval, sm.sample, sm.ssort);
+  rank_sample<NT, SMP>(sval, sm.sample, sm.ssort, [&]() {
+    if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
+    for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+  });
   uint32_t klo = 0, khi = 0xffffffffu;
   int shift = 22, need = kk, n_cand;
   const int r = sample_rank(kk, N, SMP);

@@ -85,11 +85,13 @@ constexpr int kSelCand = 256;    // candidates of the threshold bin ranked by co
 
 // The keys of SMP of a row's scores (thread i < SMP brings sval) in ssort, largest first, by all NT threads of a block.
 // They are made distinct in their low bits: ranks are a permutation, and a cut may be any value.  (The low bits are
-// cleared again in ssort: such a key need not be one that a score can have.)  Two block barriers, the last at the end.
-template <int NT, int SMP>
-__device__ __forceinline__ void rank_sample(float sval, uint32_t* sample, uint32_t* ssort) {
+// cleared again in ssort: such a key need not be one that a score can have.)  Two block barriers, the last at the end;
+// init() runs ahead of the first (ahead of this call it costs one instance of the step a spilled register).
+template <int NT, int SMP, typename Init>
+__device__ __forceinline__ void rank_sample(float sval, uint32_t* sample, uint32_t* ssort, Init&& init) {
   const int t = threadIdx.x;
   if (t < SMP) sample[t] = (score_key(sval) & ~(uint32_t)(SMP - 1)) | (uint32_t)t;
+  init();
   __syncthreads();
   constexpr int P = NT / SMP;                                 // threads per sample value: adjacent lanes
   static_assert(P == 2 || P == 4 || P == 8, "a pair, a quad or half a row of lanes per value");

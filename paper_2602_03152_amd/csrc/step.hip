@@ -422,8 +422,9 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
                                          Reload&& reload, uint32_t& kcut, uint32_t& ktop) {
   constexpr int NT = Lds::kThreads;
   const int t = threadIdx.x, lane = t & 63;
-  if (t == 0) { sm.n_list = 0; sm.p_new = -1; sm.thr[2] = 0; }
-  rank_sample<NT, kSample>(sval, sm.sample, sm.ssort);
+  rank_sample<NT, kSample>(sval, sm.sample, sm.ssort, [&]() {
+    if (t == 0) { sm.n_list = 0; sm.p_new = -1; sm.thr[2] = 0; }
+  });
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;     // (shares storage with the sample)
   const int r = sample_rank(bsel, N);
   kcut = r > kSample ? 0u : sm.ssort[r - 1];
