@@ -310,24 +310,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
     const int n_tiles = (s1 - jw + 63) / 64;
     TileIdx ix_next = load_idx(jw + 64);
     TileKV<ET> cur = load_kv(load_idx(jw));
-    int i = 0;
-    if constexpr (DENSE) {
-      // Two tiles a round, each into registers of its own: moving the next tile's rows to where this one's were makes
-      // the compiler wait for them before this tile's last products are issued (8 rows of 32768: 32.8 -> 30.7 us,
-      // 4.4 TB/s; 16 rows of 16000, 7 heads: 29.5 -> 29.4; the short lists of the sparse form, a few tiles
-      // a wave, lose 0.1 us to the longer code).
-      TileKV<ET> nxt;
-      for (; i + 2 < n_tiles; i += 2) {
-        const int j0 = jw + 64 * i;
-        nxt = load_kv(ix_next);
-        ix_next = load_idx(j0 + 128);
-        compute_tile(cur, j0);
-        cur = load_kv(ix_next);
-        ix_next = load_idx(j0 + 192);
-        compute_tile(nxt, j0 + 64);
-      }
-    }
-    for (; i + 1 < n_tiles; ++i) {
+    for (int i = 0; i + 1 < n_tiles; ++i) {
       const int j0 = jw + 64 * i;
       const TileKV<ET> nxt = load_kv(ix_next);
       ix_next = load_idx(j0 + 128);
