@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restric
 // ---------------------------------------------------------------------------------------------
 // Both products of a 16-row tile run on the matrix cores (mfma_tile.h): the logits
 // K_tile . Q^T of the GQA group and the weighted sum P . V_tile.  The tile loop is software-pipelined:
-// while a tile is computed, the next tile's K/V rows and the list entries of the tile after it are in
+// while a tile is computed, the next tile's K/V rows and, of a list, the entries of the tile after it are in
 // flight.  Loads inside the loop are unconditional (straight-line code keeps the compiler's wait
 // counts exact: a test around a load would turn every later wait into a wait for everything);
 // entries beyond the range are clamped into it and only fetched, the K/V prefetch is issued for real
@@ -285,12 +285,12 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
     }
     return r;
   };
+  auto row_off = [&](int e) {
+    const int sl = min(max(e, 0), slot_max);
+    return (long long)(sl >> pshift) * blk_stride + (long long)(sl & pmask) * sn;
+  };
   auto load_kv = [&](const TileIdx& ix) {
     TileKV<ET> r;
-    auto row_off = [&](int e) {
-      const int sl = min(max(e, 0), slot_max);
-      return (long long)(sl >> pshift) * blk_stride + (long long)(sl & pmask) * sn;
-    };
     r.load_k(Kb + row_off(ix.k));
 #pragma unroll
     for (int i = 0; i < 4; ++i) r.load_v(i, Vb + row_off(ix.v[i]));
@@ -310,12 +310,32 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
     const int n_tiles = (s1 - jw + 63) / 64;
     TileIdx ix_next = load_idx(jw + 64);
     TileKV<ET> cur = load_kv(load_idx(jw));
-    for (int i = 0; i + 1 < n_tiles; ++i) {
+    for (int i = 0; i + 1 < n_tiles; ++i) {     // (a tile with another behind it is full)
       const int j0 = jw + 64 * i;
-      const TileKV<ET> nxt = load_kv(ix_next);
-      ix_next = load_idx(j0 + 128);
-      compute_tile(cur, j0);
-      cur = nxt;
+      if constexpr (DENSE) {
+        // One set of registers: the next tile's K goes where this one's has been used, and runs under this tile's
+        // P . V, its V under the next logits.  With a second set, as below, the compiler waits for all of it before
+        // this tile's last products, to move it over (8 rows of 8192: 12.00 us, like this 11.58; of 32768: 32.4 / 30.3,
+        // 4.4 TB/s; of 65536: 50.7 / 50.1; 32 rows of 32768, 7 heads: 96.7 / 98.4; over 36 drawn shapes 1.2 % less,
+        // from 4 % less to 2 % more).  Two sets used in turn wait for nothing and are 3 % slower where much is read.
+        float sv[4];
+        tile.logits(cur, scale_log2e, sv);
+        __builtin_amdgcn_sched_barrier(0);
+        cur.load_k(Kb + row_off(ix_next.k));
+        __builtin_amdgcn_sched_barrier(0);
+        tile.accumulate_full(cur, sv, &scs[wave][0], lo, hi);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) cur.load_v(k, Vb + row_off(ix_next.v[k]));
+        ix_next = load_idx(j0 + 128);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        // (one set of registers measured the same: 16 rows, 1250 of 20011: 8.00 / 7.98, 32 rows, 6219 of 32905: 22.5 / 22.7)
+        const TileKV<ET> nxt = load_kv(ix_next);
+        ix_next = load_idx(j0 + 128);
+        compute_tile(cur, j0);
+        cur = nxt;
+      }
     }
     compute_tile(cur, jw + 64 * (n_tiles - 1));
   }
