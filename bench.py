@@ -42,28 +42,26 @@ LLC_BYTES = 256 << 20         # last-level (memory-side) cache the rotation has 
 # what the same counters read for a plain copy kernel of known size (see profiles/).  Keyed by
 # (workload config id, kernel name); bytes per launch.  None = not measured yet.
 MEASURED_TRAFFIC = {
-    "source_hash": "edb18815d50a8b3a",   # source_hash() of the kernels the counters were taken on
+    "source_hash": "ca783c09964bbbb6",   # source_hash() of the kernels the counters were taken on
     # profiles/decode_step_tiny_1head_f32_n4096_hbm_counters.txt  (read + written)
-    (0, "fasa_dense_attend"): 4327810 + 39456,
-    (0, "fasa_score_hist"): 601133 + 21632,
-    (0, "fasa_select"): 135682 + 19860,
-    (0, "fasa_sparse_attend"): 321111 + 2976,
+    (0, "fasa_dense_attend"): 4324091 + 39456,
+    (0, "fasa_step"): 869627 + 18080,
     # profiles/decode_step_llama3_8b_layer_n32768_b2048_hbm_counters.txt  (read + written)
-    (1, "fasa_dense_attend"): 135500293 + 2162944,
-    (1, "fasa_score_hist"): 16890367 + 1323072,
-    (1, "fasa_select_attend"): 10539073 + 1277719,
+    (1, "fasa_dense_attend"): 135474281 + 2162944,
+    (1, "fasa_score_hist"): 16889991 + 1323072,
+    (1, "fasa_select_attend"): 10492651 + 1277715,
     # profiles/decode_step_batch16_n16384_b256_hbm_counters.txt  (read + written)
-    (2, "fasa_dense_attend"): 1076170460 + 4558848,
-    (2, "fasa_score_hist"): 134446381 + 10223337,
-    (2, "fasa_select_attend"): 27812435 + 3344355,
+    (2, "fasa_dense_attend"): 1076126552 + 4558848,
+    (2, "fasa_row"): 25568615 + 393216,
+    (2, "fasa_score"): 134401652 + 8392239,
     # profiles/decode_step_longcot_batch8_gqa7_n32768_hbm_counters.txt  (read + written)
-    (3, "fasa_dense_attend"): 538972426 + 3879936,
-    (3, "fasa_score_hist"): 67269630 + 5386022,
-    (3, "fasa_select_attend"): 108590458 + 5034110,
+    (3, "fasa_dense_attend"): 538938146 + 3879936,
+    (3, "fasa_score_hist"): 67269035 + 5385955,
+    (3, "fasa_select_attend"): 108505577 + 5034115,
     # profiles/decode_step_verylong_n131072_f32fc_b1024_hbm_counters.txt  (read + written)
-    (4, "fasa_dense_attend"): 538112279 + 2162944,
-    (4, "fasa_score_hist"): 134514100 + 4998817,
-    (4, "fasa_select_attend"): 9948239 + 2300813,
+    (4, "fasa_dense_attend"): 538079043 + 2162944,
+    (4, "fasa_score_hist"): 134378707 + 4985984,
+    (4, "fasa_select_attend"): 9934817 + 2300813,
 }
 
 
@@ -423,7 +421,7 @@ def paged(args, w, fb, W, np, torch):
     s0 = sets[0]
     same_set = bool(np.array_equal(np.sort(s0["Tc"].cpu().numpy(), -1), np.sort(s0["Tp"].cpu().numpy(), -1)))
     o_diff = float((s0["Oc"] - s0["Op"]).abs().max())
-    assert same_set and o_diff <= 2e-5, (same_set, o_diff)
+    assert same_set and o_diff <= same_output_tol(np, W, x["V"]), (same_set, o_diff)
     us = res["paged"]["us_per_step"]
     out = {
         "metric": "us_per_decode_step", "value": us, "unit": "us", "n_gpus": 1, "steps": K_steps,
@@ -673,6 +671,13 @@ def kernel_bytes(w):
     }
 
 
+def same_output_tol(np, W, V):
+    """Most by which the outputs of two runs over the same set may differ: the order in which tokens are attended is not
+    fixed, and what a weight loses below 2^-16 of itself on the matrix cores depends on the running maximum it meets,
+    so each run is within 2^-16 of the largest value from the exact weighted mean (float32 sums: far below that)."""
+    return 2.0 ** -15 * float(np.abs(W.storage_to_f64(V)).max())
+
+
 def source_hash():
     """Hash of the kernel sources: measured HBM traffic is only quoted for the sources it was measured on."""
     import hashlib
@@ -771,6 +776,7 @@ def measure(args, w, fb, W, np, torch, steps, warmup, full):
         # the same steps as ONE captured graph (one step per buffer set), replayed; every replay is checked
         ref_T = np.sort(sets[0]["T"].cpu().numpy(), -1)
         ref_O = sets[0]["O"].cpu().numpy().copy()
+        o_tol = same_output_tol(np, W, x["V"])
         side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(side):
@@ -799,7 +805,7 @@ def measure(args, w, fb, W, np, torch, steps, warmup, full):
             g.replay()
             torch.cuda.synchronize()
             ok &= bool(np.array_equal(np.sort(sets[0]["T"].cpu().numpy(), -1), ref_T))
-            ok &= bool(np.abs(sets[0]["O"].cpu().numpy() - ref_O).max() <= 2e-5)
+            ok &= bool(np.abs(sets[0]["O"].cpu().numpy() - ref_O).max() <= o_tol)
             step(sets[1]); torch.cuda.synchronize()
         res["graph_ok"] = ok
         log("graph: %.2f us/step, replays match eager: %s" % (res["graph_us"], ok))

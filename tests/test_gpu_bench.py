@@ -30,6 +30,7 @@ def test_mode_runs(monkeypatch, capsys, argv, kernel):
     lines = [l for l in capsys.readouterr().out.splitlines() if l.startswith("{")]
     assert len(lines) == 1
     out = json.loads(lines[0])
+    assert out.get("graph_replays_match_eager") in (None, True)
     if kernel:
         assert kernel in out["kernels"]
         if out.get("roofline"):
