@@ -595,7 +595,7 @@ def main():
                    "head_dim": w.head_dim, "n_ctx": w.n_ctx, "budget": min(w.budget, w.n_ctx), "n_fc": w.n_fc,
                    "storage_dtype": w.dtype, "pairing": args.pairing, "buffer_sets": head["buffer_sets"],
                    "launch": "eager"},
-        # the whole step against the HBM roofline: what the benchmark spec's target is about
+        # the whole step against the HBM roofline
         "step_roofline": {"bound": "hbm", "bytes": model["alg"], "us": round(us, 3),
                           "achieved": round(model["alg"] / us / 1e3, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                           "frac": round(model["alg"] / us / 1e3 / HBM_PEAK_GBPS, 4)},
