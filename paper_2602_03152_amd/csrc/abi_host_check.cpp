@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "fasa.h"
+#include "fasa_internal.h"
 
 #define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED line %d: %s\n", __LINE__, #cond); return 1; } } while (0)
 
@@ -42,6 +43,25 @@ int main() {
                                     (float*)A, A, b, nullptr) == FASA_EINVAL);
             ++checked;
           }
+  // ---- the step's forms: every plan is one the kernels are built for ----
+  int forms[3] = {0, 0, 0};
+  for (int dtype : {FASA_BF16, FASA_F32})
+    for (int rows : {1, 3, 8, 64, 65, 72, 128, 256, 257, 512, 4096})
+      for (int g : {1, 2, 3, 4, 5, 8})
+        for (int n : {1, 1024, 1025, 2048, 2049, 4097, 5119, 5120, 8192, 8193, 16385, 32768, 32769, 65536, 140000, 1 << 20, (1 << 20) + 64})
+          for (int budget : {1, 63, 64, 320, 321, 512, 513, 1024, 1025, 6000}) {
+            const int cap = (n + 63) / 64 * 64, bsel = budget < n ? budget : n, per = dtype == FASA_BF16 ? 2048 : 1024;
+            const fasa_shape s = shape(rows, g, 1, 16, n, cap, budget, dtype);
+            const fasa::StepForm form = fasa::plan_step(s, fasa::kNoPaging);
+            ++forms[form];
+            if (form == fasa::kStepOne)     // the row fits the last workgroup's registers; several float32 slices: one head only
+              EXPECT(bsel <= fasa::kStepMaxBudget && n <= 8192 && (dtype == FASA_BF16 || n <= per || g == 1));
+            if (form == fasa::kStepRow) EXPECT(bsel <= fasa::kStepMaxBudget && (dtype == FASA_BF16 || g <= 4));
+            const fasa::FusePlan p = fasa::plan_fused(s, true);
+            if (p.tpb) EXPECT(p.slice_len <= p.tpb && p.nslices <= 256 && (long long)p.nslices * p.slice_len >= n &&
+                              (long long)(p.nslices - 1) * p.slice_len < n);
+          }
+  EXPECT(forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
   // ---- bad shapes ----
   {
     fasa_shape s = shape(1, 32, 8, 16, 1000, 1024, 100);
