@@ -661,11 +661,13 @@ def kernel_bytes(w):
     return {
         "fasa_score_hist": planes,
         "fasa_score": planes,
+        "fasa_score_list": planes,
         "fasa_select": scores,
         "fasa_select_all": rows * bsel * 4,
         "fasa_sparse_attend": gather,
-        "fasa_select_attend": scores + gather,      # scores read + rows gathered
-        "fasa_row": scores + gather,
+        # what these read to select (lists of a few scores, or a histogram and the scores) is an intermediate of the step
+        "fasa_select_attend": gather,
+        "fasa_row": gather,
         "fasa_step": planes + gather,               # the whole step: its scores need not leave the chip
         "fasa_dense_attend": rows * 2 * w.n_ctx * w.head_dim * e,
     }

@@ -44,7 +44,7 @@ int main() {
             ++checked;
           }
   // ---- the step's forms: every plan is one the kernels are built for ----
-  int forms[3] = {0, 0, 0};
+  int forms[3] = {0, 0, 0}, lists = 0;
   for (int dtype : {FASA_BF16, FASA_F32})
     for (int rows : {1, 3, 8, 64, 65, 72, 128, 256, 257, 512, 4096})
       for (int g : {1, 2, 3, 4, 5, 8})
@@ -57,11 +57,21 @@ int main() {
             if (form == fasa::kStepOne)     // the row fits the last workgroup's registers; several float32 slices: one head only
               EXPECT(bsel <= fasa::kStepMaxBudget && n <= 8192 && (dtype == FASA_BF16 || n <= per || g == 1));
             if (form == fasa::kStepRow) EXPECT(bsel <= fasa::kStepMaxBudget && (dtype == FASA_BF16 || g <= 4));
+            // the lists' loads fit the threads that make them, and the shares cover the budget
+            const fasa::ListPlan l = fasa::plan_list(s, fasa::kNoPaging, 256);
+            if (l.ept) {
+              const int nsegs = (n + 1023) / 1024, share = ((bsel + l.nwgs - 1) / l.nwgs + 15) / 16 * 16;
+              EXPECT(dtype == FASA_BF16 && nsegs <= 512 && l.lanes >= 2 && l.lanes <= 512 && nsegs * l.lanes <= l.ept / 2 * 512);
+              EXPECT((l.ept == 4 || l.ept == 8 || l.ept == 12 || l.ept == 16 || l.ept == 24 || l.ept == 32) && l.nwgs >= 1 &&
+                     l.nwgs <= 64 && share <= 2048 && (long long)share * l.nwgs >= bsel && share * (l.nwgs - 1) < bsel);
+              ++lists;
+            }
+            if (form == fasa::kStepRow && dtype == FASA_BF16) EXPECT(l.ept);    // (there is no other kernel for it)
             const fasa::FusePlan p = fasa::plan_fused(s, true);
             if (p.tpb) EXPECT(p.slice_len <= p.tpb && p.nslices <= 256 && (long long)p.nslices * p.slice_len >= n &&
                               (long long)(p.nslices - 1) * p.slice_len < n);
           }
-  EXPECT(forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
+  EXPECT(lists > 0 && forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
   // ---- bad shapes ----
   {
     fasa_shape s = shape(1, 32, 8, 16, 1000, 1024, 100);

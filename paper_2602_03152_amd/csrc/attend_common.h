@@ -65,7 +65,7 @@ struct ExtraSplit {
   float* w;           // [G]     scratch: receives the split's merge weight
 };
 
-// Merges the split partials of one row into O.  Called by the row's last workgroup (all 256
+// Merges the split partials of one row into O.  Called by the row's last workgroup (all NT
 // threads).  The partials were published by other workgroups with agent-scope stores and are read
 // with agent-scope loads, the weighted-V partials 16 bytes at a time (agent_b128_issue): one CU's rate
 // of load requests bounds this phase, so the wider the request the better (64 KB of fresh partials:
@@ -80,32 +80,34 @@ struct ExtraSplit {
 // memory round trip.  It must leave wsm, red and the extra split's arrays consistent behind a block
 // barrier of its own if it writes them.
 struct NothingUnderLoads { __device__ void operator()() const {} };
-template <int G, typename UnderLoads = NothingUnderLoads, int RS = 32 /* splits in flight per thread and round */>
+// NT: threads of the block; MS: most splits, a multiple of 64 (wsm is [G][MS]).
+template <int G, typename UnderLoads = NothingUnderLoads, int RS = 32 /* splits in flight per thread and round */, int NT = 256,
+          int MS = kMaxSplitsLds>
 __device__ __forceinline__ void combine_row(const float* __restrict__ part_acc,
                                             const float* __restrict__ part_ml,
                                             float* __restrict__ O, int row, int b, int h, int Hq,
-                                            int n_splits, int stride, float* wsm /* [G][kMaxSplitsLds] */,
+                                            int n_splits, int stride, float* wsm /* [G][MS] */,
                                             float* red /* [G] */, float* xbuf /* [P - 1][C][4] */,
                                             const ExtraSplit ex = {nullptr, nullptr, nullptr, nullptr},
                                             UnderLoads&& under_loads = NothingUnderLoads()) {
   constexpr int D = kHeadDim;
   constexpr int C = G * (D / 4);
-  constexpr int P = 256 / C >= 4 ? 4 : (256 / C >= 2 ? 2 : 1);
+  constexpr int P = NT / C >= 4 ? 4 : (NT / C >= 2 ? 2 : 1);
   static_assert(RS % 8 == 0 && RS >= 8, "whole chunks of eight");
-  constexpr int NG = (G + 3) / 4;
+  constexpr int NW = NT / kWave, NG = (G + NW - 1) / NW;
   const int t = threadIdx.x;
   const int wave = t >> 6, lane = t & 63;
   const size_t rbase = (size_t)row * stride * G;
   FASA_T_DECL(8);
   FASA_T(0);
-  // (max, sum) pairs: wave w serves query heads w, w + 4; lane = split (+ 64 i).  Indices are
+  // (max, sum) pairs: wave w serves query heads w, w + NW; lane = split (+ 64 i).  Indices are
   // clamped, not tested: the duplicates are masked below.
-  float2 ml[NG][kMaxSplitsLds / 64];
+  float2 ml[NG][MS / 64];
 #pragma unroll
   for (int gi = 0; gi < NG; ++gi) {
-    const int g = min(wave + 4 * gi, G - 1);
+    const int g = min(wave + NW * gi, G - 1);
 #pragma unroll
-    for (int i = 0; i < kMaxSplitsLds / 64; ++i) {
+    for (int i = 0; i < MS / 64; ++i) {
       const int sp = min(lane + 64 * i, n_splits - 1);
       ml[gi][i] = ld_agent(reinterpret_cast<const float2*>(part_ml) + (rbase + (size_t)sp * G + g));
     }
@@ -136,19 +138,19 @@ __device__ __forceinline__ void combine_row(const float* __restrict__ part_acc,
 
 #pragma unroll
   for (int gi = 0; gi < NG; ++gi) {
-    const int g = wave + 4 * gi;
+    const int g = wave + NW * gi;
     const int gc = min(g, G - 1);
     float mx = ex.m ? ex.m[gc] : kNegBig;
 #pragma unroll
-    for (int i = 0; i < kMaxSplitsLds / 64; ++i)
+    for (int i = 0; i < MS / 64; ++i)
       mx = (lane + 64 * i < n_splits) ? fmaxf(mx, ml[gi][i].x) : mx;
     mx = wave_max(mx);
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < kMaxSplitsLds / 64; ++i) {
+    for (int i = 0; i < MS / 64; ++i) {
       const int sp = lane + 64 * i;
       const float wgt = sp < n_splits ? exp2f(ml[gi][i].x - mx) : 0.f;
-      wsm[gc * kMaxSplitsLds + sp] = wgt;   // waves beyond the group rewrite the last head's own values
+      wsm[gc * MS + sp] = wgt;   // waves beyond the group rewrite the last head's own values
       sum = fmaf(ml[gi][i].y, wgt, sum);
     }
     sum = wave_sum(sum);
@@ -181,7 +183,7 @@ __device__ __forceinline__ void combine_row(const float* __restrict__ part_acc,
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int sp = part + P * (k0 + u0 + u);
-          const float w0 = wsm[gcol * kMaxSplitsLds + min(sp, kMaxSplitsLds - 1)];
+          const float w0 = wsm[gcol * MS + min(sp, MS - 1)];
           wgt[u] = sp < n_splits ? w0 : 0.f;
         }
 #pragma unroll

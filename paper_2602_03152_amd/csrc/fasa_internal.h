@@ -34,7 +34,9 @@ struct RowCtl {
   uint32_t done_att;  // attention workgroups of this row that wrote their partial
   float bin_mu;       // adaptive histogram of the fused step: written by the scoring kernel of a call,
   float bin_inv;      // read by its selection kernel (never has to be zero)
-  uint32_t pad[26];
+  uint32_t list_cut;  // lists of a row (row_list.h): the key they were made with and the sample's largest; as the two above
+  uint32_t list_top;
+  uint32_t pad[24];
 };
 static_assert(sizeof(RowCtl) == 128, "one line per row");
 
@@ -168,12 +170,22 @@ struct AppendArgs {
   bool split;
 };
 constexpr AppendArgs kNoAppend = {nullptr, nullptr, nullptr, nullptr, {nullptr, 0, 0, 0}, false};
+// Where the scoring kernel leaves the lists of a row's largest scores (row_list.h): entries [row][n_cap], their numbers
+// [row][kListCntPitch]; load: entries of a segment that are read without asking.
+struct ListOut {
+  uint2* list;
+  uint32_t* cnt;
+  int load;
+};
 // hist == nullptr: scores only.  adaptive_ctl != nullptr (with hist): the adaptive histogram of the
 // fused step (bins of lin_bin, location and scale left in the row counters) instead of the
 // exponent-based one the stand-alone selection reads.
 hipError_t launch_score(const fasa_shape& s, const void* q, const void* Kp, const int32_t* fc_idx,
                         float* S, uint32_t* hist, hipStream_t st, RaggedLens rl = {nullptr, nullptr},
                         AppendArgs ap = kNoAppend, RowCtl* adaptive_ctl = nullptr);
+// scores and lists
+hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S, RowCtl* ctl,
+                             const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap);
 // zeroes the histogram and the row counters (workspace initialisation)
 hipError_t launch_ws_clear(const fasa_shape& s, uint32_t* hist, RowCtl* ctl, hipStream_t st);
 hipError_t launch_hist(const fasa_shape& s, const float* S, uint32_t* hist, hipStream_t st);
@@ -203,6 +215,19 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm);
 hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* K, void* V, void* Kp,
                        const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                        RowCtl* ctl, hipStream_t st, RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
+
+// Selection out of lists and attention by one or several workgroups per row, after a scoring launch that makes the
+// lists (step.hip).  ept == 0: not for this shape.
+struct ListPlan {
+  int nwgs;        // workgroups per row
+  int ept;         // kernel instance: entries per thread
+  int lanes;       // threads that load a segment's first 2 * lanes entries
+};
+ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits);
+hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, bool row_form, const void* q, void* K, void* V, void* Kp,
+                            const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
+                            RowCtl* ctl, uint2* list, uint32_t* cnt, float* part_acc, float* part_ml, hipStream_t st,
+                            RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
 
 // memory-optimised variant (offload.hip)
 hipError_t launch_offload_split(const fasa_shape& s, const void* K, const int32_t* fc_idx, void* Kp,

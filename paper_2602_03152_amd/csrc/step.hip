@@ -1,18 +1,20 @@
-// The decode step for rows whose selected set one workgroup can attend over (paper Sec. 4.1 - 4.2, Alg. 2
-// order).  One workgroup selects a row's B best tokens, out of a list of the few scores that can be among
-// them, and attends over them; nothing is handed over between workgroups on the way from the scores to the
-// output.  Two forms:
+// The decode step by workgroups that know a row's whole set (paper Sec. 4.1 - 4.2, Alg. 2 order): they select the row's B best
+// tokens out of a list of the few scores that can be among them, and attend over them.  Three forms:
 //
 //   step_kernel    the whole step in ONE launch.  A row of at most 512 * TPT tokens is scored, selected
 //                  and attended by one workgroup.  A longer row is scored by several; each publishes its
 //                  scores with write-through stores and takes the row's ticket, and the one that
 //                  finishes last selects and attends.  For small problems, where launches and
 //                  dependent round trips are the time.
+//   list_kernel    selection and attention after a scoring launch that leaves such lists in memory (row_list.h; bf16).  One
+//                  workgroup per row, or several, each of which finds the same set and attends over an equal share
+//                  of it.
 //   row_kernel     selection and attention of a row whose scores lie in S (after score_kernel without a
-//                  histogram): for problems that fill the machine, where scoring wants all its bandwidth.
+//                  histogram), one workgroup per row: float32 problems that fill the machine.
 //
-// See plan_step for where the lines lie; beyond them fused.hip splits a row over many workgroups.
+// See plan_step and plan_list for where the lines lie; beyond them fused.hip splits a row over many workgroups.
 #include "mfma_tile.h"
+#include "row_list.h"
 #include "score_common.h"
 #include "select_common.h"
 
@@ -20,6 +22,9 @@ namespace fasa {
 
 constexpr int kStepNT = 512;                 // threads per workgroup of step_kernel
 constexpr int kRowNT = 1024;                 // threads per workgroup of row_kernel
+constexpr int kListNT = 512;                 // threads per workgroup of list_kernel
+constexpr int kListMaxWgs = 64;              // workgroups per row of it
+constexpr int kListMaxShare = 2048;          // most tokens that one of them attends over
 constexpr int kListPerThread = 8;            // places of a row's list, per thread
 constexpr int kStepMaxCtx = 16 * kStepNT;    // longest row of step_kernel: what its last workgroup's registers hold
 
@@ -41,17 +46,27 @@ struct StepArgs {
   PageMap pm;
   int rows, nslices, Hq, Hkv, F, N_max, n_cap, budget_max, t_pitch, append, pairing;
   float scale_log2e;
+  // list_kernel: the rows' lists (row_list.h), workgroups per row, their partials [row][nwgs]
+  uint2* list;             // [row][n_cap]
+  uint32_t* cnt;           // [row][kListCntPitch]
+  int lanes;
+  uint32_t magic;
+  int nwgs;
+  float* part_acc;
+  float* part_ml;
 };
 
 // LDS of selection and attention; phases that never overlap share storage.
-template <int NT, int GM>
+// LIST: places of a list in LDS; MOST: most selected tokens of the workgroup.
+template <int NT, int GM, int LIST = kListPerThread * NT, int MOST = kStepMaxBudget>
 struct RowLds {
   static constexpr int kThreads = NT;
   static constexpr int kWaves = NT / kWave;
-  static constexpr int kList = kListPerThread * NT;
+  static constexpr int kList = LIST;
   union {
     float o[kWaves][GM][kHeadDim];                           // weighted V per wave
     uint2 list[kList];                                       // scores at or above the cut: (score bits, token)
+    unsigned char merge[8192 + GM * kListMaxWgs * 4];        // combine_row: partitions, then weights
   };
   union {
     uint32_t hist[kSelBins];
@@ -59,10 +74,11 @@ struct RowLds {
   };
   uint2 cand[kSelCand];
   uint32_t ssort[kSample];                                   // keys of the sample, largest first
-  __align__(16) uint32_t wl[kStepMaxBudget + 16];            // selected tokens, then what the gather reads for them
+  __align__(16) uint32_t wl[MOST + 16];            // selected tokens, then what the gather reads for them
   float m[kWaves][GM], l[kWaves][GM];
   float scs[kWaves][16];
   uint32_t wtot[kWaves], wtot2[kWaves];
+  uint32_t seg_cnt[kListMaxSegs];                            // entries of the row's segments
   uint32_t thr[4];
   uint32_t n_list;
   int p_new;                                                 // place of the appended row in wl, or -1
@@ -78,21 +94,27 @@ __device__ __forceinline__ void st_agent_f4(__amdgpu_buffer_rsrc_t rs, uint32_t 
 // ---------------------------------------------------------------------------------------------
 // Selection of a row's set: B tokens to sm.wl (find_threshold in select_common.h does the narrowing)
 // ---------------------------------------------------------------------------------------------
+// Places of the set that a workgroup keeps in sm.wl: p0 .. p1 - 1 of 0 .. B - 1 (all of them where it attends alone)
+template <typename Lds>
+__device__ __forceinline__ void keep_place(Lds& sm, int p, int p0, int p1, uint32_t tok) {
+  if (p >= p0 && p < p1) sm.wl[p - p0] = tok;
+}
+
 // The threshold range's share of the set, after its candidates have been listed in sm.cand (if they fit)
 template <typename Lds>
 __device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bsel, int need, int n_cand,
-                                                  const float* srow, int N) {
+                                                  const float* srow, int N, int p0, int p1) {
   constexpr int NT = Lds::kThreads;
   const int t = threadIdx.x;
   const int n_above = bsel - need;
-  auto place = [&](int p, uint32_t tok) {
-    if (p < bsel) sm.wl[p] = tok;
-  };
+  auto place = [&](int p, uint32_t tok) { keep_place(sm, p, p0, p1, tok); };
   if (n_cand <= kSelCand) {   // taken iff fewer than `need` candidates sort before it
     constexpr int P = NT / kSelCand;
-    const int ci = t / P;
-    const int rank = rank_in_list<P>(sm.cand, n_cand, ci);
-    if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
+    if ((t & ~(kWave - 1)) / P < n_cand) {                    // (the waves that have any)
+      const int ci = t / P;
+      const int rank = rank_in_list<P>(sm.cand, n_cand, ci);
+      if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
+    }
   } else {                     // a tie of more than kSelCand tokens: the first `need` of them
     int tied = 0;              // met so far
     for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
@@ -107,37 +129,58 @@ __device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bse
   __syncthreads();
 }
 
-// All of a row's scores, out of memory: where there is no usable list.  Places go by wave.  The histogram is
-// zero at the call (a barrier ago); ends with a block barrier.
-template <typename Lds>
-__device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow, int N) {
+// All of a row's scores, out of memory: where there is no usable list.  klo, ktop: a key that B scores are likely to reach, and
+// one at the upper end (0, 0: nothing is known).  SHARED: other workgroups of this launch wrote the scores.  Places go by
+// wave.  The histogram is zero at the call (a barrier ago); ends with a block barrier.  The row is read in 16-byte
+// pieces, four in flight (S is n_cap long, a multiple of 64).
+template <bool SHARED, typename Lds>
+__device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow, int N, int p0, int p1, uint32_t klo = 0,
+                                           uint32_t ktop = 0) {
   constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t klo = 0, khi = 0xffffffffu;
-  int shift = 22, need = bsel, n_cand;
-  for (;;) {
-    for (int i = t; i < N; i += NT) {
-      const uint32_t key = score_key(ld_agent(srow + i));
-      if (key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
+  const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
+  auto for_scores = [&](auto&& f) {                           // f(key, token, token < N), all threads together
+    for (int i0 = 0; i0 < N; i0 += 16 * NT) {
+      uint4 x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = i0 + (u * NT + t) * 4;
+        if constexpr (SHARED) x[u] = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
+        else x[u] = *reinterpret_cast<const uint4*>(srow + (n < N ? n : 0));
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = i0 + (u * NT + t) * 4;
+        f(score_key(__uint_as_float(x[u].x)), n, n < N);
+        f(score_key(__uint_as_float(x[u].y)), n + 1, n + 1 < N);
+        f(score_key(__uint_as_float(x[u].z)), n + 2, n + 2 < N);
+        f(score_key(__uint_as_float(x[u].w)), n + 3, n + 3 < N);
+      }
     }
+  };
+  uint32_t khi = 0xffffffffu;
+  int shift = klo ? first_shift(klo, ktop) : 22, need = bsel, n_cand;
+  for (;;) {
+    for_scores([&](uint32_t key, int, bool in) {
+      if (in && key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
+    });
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+    if (n_cand == 0) { klo = 0; shift = 22; }                 // fewer reach it: the whole range
   }
   uint32_t pw = 0, pc = 0;
   for (int pass = 0; pass < 2; ++pass) {                      // count per wave, then place
-    for (int i0 = 0; i0 < N; i0 += NT) {
-      const int i = i0 + t;
-      const uint32_t key = score_key(ld_agent(srow + min(i, N - 1)));
-      const bool win = i < N && key > khi, cnd = i < N && key >= klo && key <= khi;
+    for_scores([&](uint32_t key, int n, bool in) {
+      const bool win = in && key > khi, cnd = in && key >= klo && key <= khi;
       const unsigned long long mw = __ballot(win), mc = __ballot(cnd);
       if (pass) {
         const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, pw));
         const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, pc));
-        if (win && p < (uint32_t)bsel) sm.wl[p] = (uint32_t)i;
-        if (cnd && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(key, (uint32_t)i);
+        if (win) keep_place(sm, (int)p, p0, p1, (uint32_t)n);
+        if (cnd && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(key, (uint32_t)n);
       }
       pw += (uint32_t)__popcll(mw);
       pc += (uint32_t)__popcll(mc);
-    }
+    });
     __syncthreads();
     if (!pass) {
       if (lane == 0) { sm.wtot[wave] = pw; sm.wtot2[wave] = pc; }
@@ -149,85 +192,207 @@ __device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow,
       }
     }
   }
-  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N);
+  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
 }
 
-// The same inside a list of M <= EPT * NT scores that the threads hold: key[k], tok[k] of thread t are those of
-// entry k * NT + t.  Places go by thread.
-template <int EPT, typename Lds>
-__device__ __forceinline__ void list_select_regs(Lds& sm, int M, const uint32_t (&key)[EPT], const uint32_t (&tok)[EPT],
-                                                 uint32_t klo, int shift, int bsel, const float* srow, int N) {
-  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+// The same among listed scores that the threads hold (key 0: none; klo > 0).
+// more(f): calls f(valid, key, token) for listed scores that nobody holds, whole waves at a time, in the same order
+// each time; `over` (the same in all threads) says that there are any.  Places go by thread, then by wave of the rest.
+// False: fewer than B scores are listed (the histogram is zero then).
+template <int EPT, typename Lds, typename More>
+__device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EPT], const uint32_t (&tok)[EPT], bool over,
+                                               More&& more, uint32_t klo, int shift, int bsel, const float* srow, int N,
+                                               int p0, int p1) {
+  constexpr int NWV = Lds::kWaves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   uint32_t khi = 0xffffffffu;
   int need = bsel, n_cand;
+  FASA_T_DECL(6);
+  FASA_T(0);
+  auto count = [&](uint32_t d) { atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kSelBins - 1u)], 1u); };   // d: key - klo
   for (;;) {
+    const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
-      if (k * NT >= M) break;
-      if (k * NT + t < M && key[k] >= klo && key[k] <= khi)
-        atomicAdd(&sm.hist[min((key[k] - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
+      const uint32_t d = key[k] - klo;
+      if (d <= span) count(d);
     }
+    if (over) more([&](bool valid, uint32_t k, uint32_t) { if (valid && k - klo <= span) count(k - klo); });
+    FASA_T(1);
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+    if (n_cand == 0) return false;
   }
-  uint32_t win = 0, cnd = 0;
+  FASA_T(2);
+  const uint32_t span = khi - klo;
+  uint32_t n_win = 0, cnd = 0;
 #pragma unroll
   for (int k = 0; k < EPT; ++k) {
-    const bool in = k * NT + t < M;
-    win |= in && key[k] > khi ? 1u << k : 0u;
-    cnd |= in && key[k] >= klo && key[k] <= khi ? 1u << k : 0u;
+    n_win += key[k] > khi ? 1u : 0u;
+    cnd |= key[k] - klo <= span ? 1u << k : 0u;
   }
   // both counts of a thread fit 16 bits, and so do their sums (at most EPT * NT entries)
-  static_assert(EPT * NT < 65536, "packed counts");
-  const uint32_t mine = (uint32_t)__popc(win) | ((uint32_t)__popc(cnd) << 16);
+  static_assert(EPT <= 32 && EPT * Lds::kThreads < 65536, "packed flags and counts");
+  const uint32_t mine = n_win | ((uint32_t)__popc(cnd) << 16);
   const uint32_t incl = wave_prefix_sum(mine);
   if (lane == kWave - 1) sm.wtot[wave] = incl;
   __syncthreads();
-  uint32_t before = incl - mine;
+  uint32_t before = incl - mine, all = 0;
 #pragma unroll
-  for (int w = 0; w < NWV - 1; ++w) before += w < wave ? sm.wtot[w] : 0u;
-  uint32_t pw = before & 0xffffu, pc = before >> 16;
+  for (int w = 0; w < NWV; ++w) {
+    const uint32_t x = sm.wtot[w];
+    before += w < wave ? x : 0u;
+    all += x;
+  }
+  // Winners: a wave whose winners are other workgroups' share skips the writing (of 32 workgroups a row, all but one or two
+  // waves).  Candidates: few threads have one, so each takes its own one by one.
+  {
+    uint32_t p = (before & 0xffffu) - (uint32_t)p0;           // place in this workgroup's share
+    const uint32_t len = (uint32_t)(p1 - p0);
+    if (__ballot((int)p < (int)len && (int)(p + n_win) > 0) != 0ull) {
 #pragma unroll
-  for (int k = 0; k < EPT; ++k) {
-    if (k * NT >= M) break;
-    if (win & (1u << k)) {
-      if (pw < (uint32_t)bsel) sm.wl[pw] = tok[k];
-      ++pw;
+      for (int k = 0; k < EPT; ++k) {
+        const bool w = key[k] > khi;
+        if (w && p < len) sm.wl[p] = tok[k];
+        p += w ? 1u : 0u;
+      }
     }
-    if (cnd & (1u << k)) {
-      if (pc < (uint32_t)kSelCand) sm.cand[pc] = make_uint2(key[k], tok[k]);
+    uint32_t pc = before >> 16;
+    while (__ballot(cnd != 0u) != 0ull) {
+      const int j = __ffs((int)cnd) - 1;                      // (-1: none)
+      uint2 e = make_uint2(0u, 0u);
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) e = j == k ? make_uint2(key[k], tok[k]) : e;
+      if (j >= 0 && pc < (uint32_t)kSelCand) sm.cand[pc] = e;
       ++pc;
+      cnd &= cnd - 1u;
     }
   }
+  if (over) {
+    uint32_t w0 = 0, c0 = 0;                                  // of this wave
+    more([&](bool valid, uint32_t k, uint32_t) {
+      w0 += (uint32_t)__popcll(__ballot(valid && k > khi));
+      c0 += (uint32_t)__popcll(__ballot(valid && k >= klo && k <= khi));
+    });
+    __syncthreads();                                          // all have read wtot
+    if (lane == 0) { sm.wtot[wave] = w0; sm.wtot2[wave] = c0; }
+    __syncthreads();
+    w0 = all & 0xffffu; c0 = all >> 16;
+    for (int w = 0; w < wave; ++w) { w0 += sm.wtot[w]; c0 += sm.wtot2[w]; }
+    more([&](bool valid, uint32_t k, uint32_t n) {
+      const bool win1 = valid && k > khi, cnd1 = valid && k >= klo && k <= khi;
+      const unsigned long long mw = __ballot(win1), mc = __ballot(cnd1);
+      const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, w0));
+      const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, c0));
+      if (win1) keep_place(sm, (int)p, p0, p1, n);
+      if (cnd1 && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(k, n);
+      w0 += (uint32_t)__popcll(mw);
+      c0 += (uint32_t)__popcll(mc);
+    });
+  }
   __syncthreads();
-  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N);
+  FASA_T(3);
+  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
+  FASA_T(4);
+  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "entries: count %llu threshold %llu place %llu resolve (%d of %d) %llu (x10ns)\n",
+               FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2), need, n_cand, FASA_T_D(4, 3));
+  return true;
 }
 
-// Selection of a row inside its list of M scores that reach the cut kcut (0: everything does), or - should it be
-// shorter than B or longer than its room, because the sample misled or thousands of scores are equal - among
-// all of the row's scores in memory.
+// Selection of a row inside its list of M <= EPT * NT scores in LDS (score bits, token) that reach the cut kcut (0: everything does)
+template <int EPT, typename Lds>
+__device__ __forceinline__ bool select_list(Lds& sm, int M, uint32_t kcut, uint32_t ktop, int bsel, const float* srow, int N) {
+  uint32_t key[EPT], tok[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int i = k * Lds::kThreads + threadIdx.x;
+    const uint2 e = sm.list[i];                               // (beyond M: whatever it holds)
+    key[k] = i < M ? score_key(__uint_as_float(e.x)) : 0u;
+    tok[k] = e.y;
+  }
+  return select_entries<EPT>(sm, key, tok, false, [](auto&&) {}, max(kcut, 1u), kcut ? first_shift(kcut, ktop) : 22, bsel, srow, N,
+                             0, bsel);
+}
+
+// Selection of a row inside its list, or - should it be shorter than B or longer than its room, because the sample misled or
+// thousands of scores are equal - among all of the row's scores in memory.
 template <typename Lds>
 __device__ __forceinline__ void select_row(Lds& sm, int M, uint32_t kcut, uint32_t ktop, int bsel, const float* srow, int N) {
   if (M >= bsel && M <= Lds::kList) {
-    uint32_t key[kListPerThread], tok[kListPerThread];
-#pragma unroll
-    for (int k = 0; k < kListPerThread; ++k) {
-      const uint2 e = sm.list[k * Lds::kThreads + threadIdx.x];   // (beyond M: not looked at)
-      key[k] = score_key(__uint_as_float(e.x));
-      tok[k] = e.y;
-    }
-    list_select_regs<kListPerThread>(sm, M, key, tok, kcut, kcut ? first_shift(kcut, ktop) : 22, bsel, srow, N);
-  } else {
-    publish_barrier();                                        // this workgroup's own scores are in memory
-    row_select(sm, bsel, srow, N);
+    // Instances for short lists, which nearly all are: 1 row of 4096, B = 256, float32: 13.0 -> 12.6 us, 8 rows of 1531, B = 192:
+    // 11.55 -> 11.28, 128 rows of 16384, 4 heads, B = 256, float32: 70.6 -> 69.7
+    const bool ok = M <= 2 * Lds::kThreads ? select_list<2>(sm, M, kcut, ktop, bsel, srow, N)
+                    : M <= 4 * Lds::kThreads ? select_list<4>(sm, M, kcut, ktop, bsel, srow, N)
+                                             : select_list<kListPerThread>(sm, M, kcut, ktop, bsel, srow, N);
+    if (ok) return;
   }
+  publish_barrier();                                          // this workgroup's own scores are in memory
+  row_select<true>(sm, bsel, srow, N, 0, bsel);
+}
+
+// Selection of a row out of its segments' lists in memory (row_list.h).  kcut: what they were made with; ktop: the sample's
+// largest key.
+template <int EPT, typename Lds>
+__device__ __forceinline__ void select_listed(Lds& sm, const ListView& v, const uint32_t* cnt, uint32_t kcut, uint32_t ktop,
+                                              int bsel, const float* srow, int N, int p0, int p1) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves, CPT = kListMaxSegs / NT;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t key[EPT], tok[EPT], c1[CPT];
+#pragma unroll
+  for (int i = 0; i < CPT; ++i) c1[i] = cnt[min(i * NT + t, v.nsegs - 1)];
+  list_load<NT, EPT>(v, key, tok);
+  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+  if (t == 0) { sm.p_new = -1; sm.thr[2] = 0; }
+  uint32_t c = 0;
+  bool beyond = false;
+#pragma unroll
+  for (int i = 0; i < CPT; ++i) {
+    const uint32_t x = i * NT + t < v.nsegs ? c1[i] : 0u;
+    sm.seg_cnt[i * NT + t] = x;
+    c += x;
+    beyond |= x > 2u * (uint32_t)v.lanes;
+  }
+  FASA_T_DECL(5);
+  FASA_T(0);
+  const uint32_t sum = wave_prefix_sum(c);
+  const bool more_here = __ballot(beyond) != 0ull;
+  if (lane == kWave - 1) { sm.wtot[wave] = sum; sm.wtot2[wave] = more_here ? 1u : 0u; }
+  __syncthreads();
+  uint32_t M = 0, over = 0;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) { M += sm.wtot[w]; over |= sm.wtot2[w]; }
+  auto more = [&](auto&& f) {
+    for (int s0 = 0; s0 < v.nsegs; s0 += kWave * NWV) {       // this wave's segments are s0 + wave, + NWV, ..
+      const int sl = s0 + lane * NWV + wave;
+      unsigned long long m = __ballot(sl < v.nsegs && sm.seg_cnt[min(sl, kListMaxSegs - 1)] > 2u * (uint32_t)v.lanes);
+      for (; m; m &= m - 1ull) {
+        const int s = s0 + (__ffsll((long long)m) - 1) * NWV + wave;
+        const int n = (int)min(sm.seg_cnt[s], (uint32_t)v.seg_tokens);
+        for (int i0 = 2 * v.lanes; i0 < n; i0 += kWave) {
+          const uint2 x = v.list[(size_t)s * v.seg_tokens + min(i0 + lane, n - 1)];
+          f(i0 + lane < n, x.x, min(x.y, (uint32_t)N - 1u));
+        }
+      }
+    }
+  };
+  list_mask<NT, EPT>(v, sm.seg_cnt, key, tok);
+  FASA_T(1);
+  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "list counts arrive + barrier %llu M %d over %d of %d\n", FASA_T_D(1, 0), (int)M, (int)over, EPT * NT);
+  if ((int)M >= bsel && select_entries<EPT>(sm, key, tok, over != 0, more, max(kcut, 1u), kcut ? first_shift(kcut, ktop) : 22,
+                                            bsel, srow, N, p0, p1))
+    return;
+  // The sample misled (one row in a hundred thousand where tokens are exchangeable): the threshold lies below the cut, as
+  // a first guess by no more than the sample's best lies above.
+  __syncthreads();                                            // (all have read the counts)
+  const float cut = key_score(kcut), down = cut - (key_score(ktop) - cut);
+  row_select<false>(sm, bsel, srow, N, p0, p1, down > -INFINITY ? score_key(down) : 0u, ktop);
 }
 
 // Attention over the tokens in sm.wl[0 .. cnt): T is written, and every wave leaves its (max, sum, weighted V)
-// in LDS (a block barrier ago when this returns).  Wave w takes 16-row tiles w, w + waves, ... (bf16:
+// in LDS (a block barrier ago when this returns).  p0: place of the first of them in T; with_q: a tile that has the queries.  Wave w takes 16-row tiles w, w + waves, ... (bf16:
 // mfma_tile.h; float32: vector ALUs).
 template <typename ET, int GM, typename Lds>
-__device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, int b, int h, int G, int cnt, int n_app) {
+__device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, int b, int h, int G, int cnt, int n_app,
+                                           int p0 = 0, const MfmaTile<GM>* with_q = nullptr) {
   constexpr int D = kHeadDim;
   constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -235,7 +400,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
   // T, and what the gather reads: the row's element offset / 8, padded to whole tiles with the last row
   const bool paged = a.pm.table != nullptr;
   {
-    int32_t* trow = a.T + (size_t)row * a.t_pitch;
+    int32_t* trow = a.T + (size_t)row * a.t_pitch + p0;
     for (int i = t; i < cnt; i += NT) {
       const int n = (int)sm.wl[i];
       trow[i] = n;
@@ -256,6 +421,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
   if constexpr (sizeof(ET) == 2) {
     const int lo = lane & 15, hi = lane >> 4;
     MfmaTile<GM> tile;
+    if (with_q) tile = *with_q;
     auto load_k = [&](TileKV<uint16_t>& kv, int j0) {
       const ET* kr = Kb + ((size_t)sm.wl[j0 + lo] << 3) + 8 * hi;
       if (p_new >= j0 && p_new < j0 + 16) kr = p_new == j0 + lo ? kn + 8 * hi : kr;   // (wave-uniform test)
@@ -281,7 +447,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
       const int n_tiles = (cnt - jw + 16 * NWV - 1) / (16 * NWV);
       TileKV<uint16_t> kv;
       float sv[4];
-      tile.load_q(q, lo, hi, G);
+      if (!with_q) tile.load_q(q, lo, hi, G);
       load_k(kv, jw);
       load_v(kv, jw);
       for (int i = 0; i + 1 < n_tiles; ++i) {
@@ -669,6 +835,69 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
   write_output(a, sm, b, h, G);
 }
 
+// nwgs workgroups per row; the scores lie in S, the lists of the largest in `list` (score_list_kernel).  Every workgroup of a
+// row finds the row's set, out of the same lists and so in the same order, and attends over its share of it: nothing about
+// the selection is left open for the workgroup that merges, and all gather the same number of rows (fused.hip's slices
+// differ by 14 %, and leave a threshold bin to resolve at the end).  A chain of round trips: lists and counts 0.7 us, their
+// histogram 0.2 - 1.1 by length, threshold 0.5, places 0.6 - 2, candidates 0.5 - 1, rows 2.3 (388 rows a workgroup: 10.5), partial
+// and ticket 1.2, merge 1.2.  us, both launches, fused.hip or row_kernel / like this: 8 rows of 32768, 4 heads, B = 2048:
+// 21.2 / 19.0; 32 rows, 7 heads, B = 6200: 53.0 / 49.4; 8 rows of 131072, F = 32, B = 1024: 41.8 / 39.8; 64 rows of 65536, B = 700:
+// 80.9 / 71.9; 128 rows of 16384, B = 256: 41.7 / 41.3, 512 rows of 8192, F = 8: 62.1 / 49.1.
+template <typename ET, int G, int EPT>
+__global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
+  constexpr int D = kHeadDim, SEG = kListScoreNT * ScoreTraits<ET>::TPT;
+  __shared__ RowLds<kListNT, G, 1, kListMaxShare> sm;
+  __shared__ float red[G];
+  __shared__ uint32_t ticket;
+  int row, wg;
+  row_slice_of_block(a.rows, a.nwgs, row, wg);
+  const int b = row / a.Hkv, h = row % a.Hkv;
+  const int t = threadIdx.x, lane = t & 63;
+  const int N = seq_n_ctx(a.n_ctx_seq, b, a.N_max);
+  const int bsel = seq_bsel(a.budget_seq, b, N, a.budget_max);
+  const int share = ((bsel + a.nwgs - 1) / a.nwgs + 15) & ~15;      // whole tiles
+  const int p0 = wg * share, p1 = min(bsel, p0 + share), nvalid = (bsel + share - 1) / share;
+  if (p0 >= bsel) return;
+  FASA_T_DECL(8);
+  FASA_T(0);
+  const uint32_t kcut = a.ctl[row].list_cut, ktop = a.ctl[row].list_top;
+  MfmaTile<G> tile;
+  tile.load_q((const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D, lane & 15, lane >> 4);
+  const ListView v = {a.list + (size_t)row * a.n_cap, (N + SEG - 1) / SEG, SEG, a.lanes, a.magic, a.n_cap, N};
+  select_listed<EPT>(sm, v, a.cnt + (size_t)row * kListCntPitch, kcut, ktop, bsel, a.S + (size_t)row * a.n_cap, N, p0, p1);
+  FASA_T(1);
+  row_attend<ET, G>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile);
+  FASA_T(2);
+  if (nvalid == 1) {
+    write_output(a, sm, b, h, G);
+    return;
+  }
+  const size_t pbase = ((size_t)row * a.nwgs + wg) * G;
+  if (t < G * (D / 4)) {
+    const int g = t / (D / 4), d4 = t % (D / 4);
+    float mn, ls;
+    float4 o;
+    wave_totals(sm, g, d4, mn, ls, o);
+    float2* pa = reinterpret_cast<float2*>(a.part_acc + (pbase + g) * D + 4 * d4);
+    st_agent(pa, make_float2(o.x, o.y));
+    st_agent(pa + 1, make_float2(o.z, o.w));
+    if (d4 == 0) st_agent(reinterpret_cast<float2*>(a.part_ml + (pbase + g) * 2), make_float2(mn, ls));
+  }
+  FASA_T(3);
+  publish_barrier();
+  if (t == 0) ticket = atomicAdd(&a.ctl[row].done_att, 1u);
+  __syncthreads();
+  FASA_T(4);
+  FASA_T_PRINT(t == 0 && row == 0 && (wg == 0 || ticket == (uint32_t)nvalid - 1u),
+               "list wg %d: select %llu attend %llu partial %llu publish+ticket %llu (x10ns)\n", wg, FASA_T_D(1, 0),
+               FASA_T_D(2, 1), FASA_T_D(3, 2), FASA_T_D(4, 3));
+  if (ticket != (uint32_t)nvalid - 1u) return;
+  if (t == 0) a.ctl[row].done_att = 0;                        // clean for the next call
+  combine_row<G, NothingUnderLoads, 16, kListNT, kListMaxWgs>(a.part_acc, a.part_ml, a.O, row, b, h, a.Hq, nvalid, a.nwgs,
+                                                              reinterpret_cast<float*>(sm.merge + 8192), red,
+                                                              reinterpret_cast<float*>(sm.merge));
+}
+
 // ---------------------------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------------------------
@@ -718,7 +947,10 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
     // one slice: 8 rows of 2048, B = 64: 14.5 / 10.2 / 15.0, B = 512: 18.2 / 14.9 / 19.8; 512 rows: 29.4 / 20.5 / 36.3
     if (ns == 1) return kStepOne;
     // 8 rows of 8192, B = 256: 14.6 / 14.6 / 17.3, B = 512: 16.0 / 17.0 / 19.8; 128 rows of 4096: 22.3 / 20.4 / 21.9
-    if (ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320) return kStepOne;
+        // Several slices, where the lists of a scoring launch do not do better (list_kernel): 8 rows of 8192, F = 16 / 32: 13.6 / 14.9
+    // against 14.4 / 16.5, 32 rows: 17.1 / 19.9 against 17.0 / 20.5, 40 rows: 18.6 against 17.5; 8 rows of 6000, B = 40: 12.2
+    // against 12.3, of 3000: 12.2 against 11.8
+    if (ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320 && (rows > 32 || ns < 4)) return kStepOne;
   } else {
     // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
     // 1 row of 4096, B = 256: 17.3 / 12.7 / 15.5, 32 rows of 8192, B = 600: 22.2 / 22.1 / 26.3.  4 heads, 8 rows, B = 64:
@@ -751,10 +983,97 @@ static hipError_t launch_step_f(const StepArgs& a, hipStream_t st) {
     default: return launch_step_v<ET, 0, GM>(a, st);
   }
 }
-hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* K, void* V, void* Kp,
-                       const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
-                       RowCtl* ctl, hipStream_t st, RaggedLens rl, PageMap pm) {
-  StepArgs a;
+// What the selection loads of a row's lists without asking: `lanes` threads a segment, two entries each, so that a
+// segment's list as the sample should make it, and two and a half standard deviations (of the sample and of the segment) more, is
+// loaded.  Returns the entries per thread (even), 0: more than fit.
+static int list_loads(int n, int bsel, int seg_tokens, int sample, int nt, int most, int* lanes_out) {
+  const int nsegs = (n + seg_tokens - 1) / seg_tokens;
+  if (nsegs > kListMaxSegs) return 0;
+  const float r = (float)list_rank(bsel, n, sample);
+  const float frac = n < kListMinCtx || r > (float)sample ? 1.f : r / (float)sample, seg = (float)(n < seg_tokens ? n : seg_tokens);
+  const float want = fminf(seg * frac + 2.5f * seg * sqrtf(r) / (float)sample + 3.5f * sqrtf(seg * frac) + 2.f, (float)seg_tokens);
+  const int rounds = (nsegs * (((int)want + 1) / 2) + nt - 1) / nt;
+  if (rounds > most / 2) return 0;
+  int lanes = rounds * nt / nsegs;
+  if (lanes > seg_tokens / 2) lanes = seg_tokens / 2;
+  if (lanes < 2) return 0;
+  *lanes_out = lanes;
+  return 2 * rounds;
+}
+
+ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
+  ListPlan p{0, 0, 0};
+  if (s.dtype != FASA_BF16) return p;                          // (float32 rows are attended on the vector ALUs here)
+  const long long most = pm.table ? (long long)pm.n_pool * s.kv_stride_b + (1ll << pm.shift) * s.kv_stride_n
+                                  : (long long)s.n_ctx * s.kv_stride_n;
+  if ((most >> 3) >= 0xfffffff0ll) return p;
+  const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx, rows = s.batch * s.n_kv_heads;
+  int lanes = 0;
+  const int need = list_loads(s.n_ctx, bsel, 1024, 256, kListNT, 32, &lanes);
+  if (!need) return p;
+  // One workgroup up to B = 256: what it gathers (50 KB per us) takes less than a hand-over and a merge.  us with 1 / 2 / as many as
+  // fit: 8 rows of 16384, B = 128: 12.7 / 14.3 / 14.3, 256: 14.6 / 15.5 / 15.1, 320: 15.3 / 16.0 / 15.1; 128 rows, 256: 41.7 / 42.9.
+  // Beyond, as many as fit at once, one per compute unit, with at least 64 tokens each: 80 rows, B = 700: 36.6 / 35.6 / 34.5 (3) /
+  // 36.2 (4); 8 rows of 32768, B = 2048, 4 / 8 / 16 / 32: 23.7 / 20.8 / 19.4 / 19.0; 32 rows, B = 6200, 4 / 8 / 16: 54.2 / 49.5 / 60.5
+  int w = bsel <= 256 ? 1 : kAssumedCUs / rows;
+  if (w > (bsel + 63) / 64) w = (bsel + 63) / 64;
+  if (w > kListMaxWgs) w = kListMaxWgs;
+  if (w > max_splits) w = max_splits;
+  if (w < 1) w = 1;
+  const int share = ((bsel + w - 1) / w + 15) / 16 * 16;
+  if (share > kListMaxShare) return p;
+  p.nwgs = (bsel + share - 1) / share;
+  p.ept = need <= 4 ? 4 : need <= 8 ? 8 : need <= 12 ? 12 : need <= 16 ? 16 : need <= 24 ? 24 : 32;
+  p.lanes = lanes;
+  return p;
+}
+
+template <typename ET, int G>
+static hipError_t launch_list_g(const StepArgs& a, int ept, const char* name, hipStream_t st) {
+  switch (ept) {
+    case 4: return launch(name, list_kernel<ET, G, 4>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 12: return launch(name, list_kernel<ET, G, 12>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 24: return launch(name, list_kernel<ET, G, 24>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 8: return launch(name, list_kernel<ET, G, 8>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 16: return launch(name, list_kernel<ET, G, 16>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 32: return launch(name, list_kernel<ET, G, 32>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+static StepArgs step_args(const fasa_shape& s, const void* q, void* K, void* V, void* Kp, const int32_t* fc_idx, const void* k_new,
+                          const void* v_new, float* S, int32_t* T, float* O, RowCtl* ctl, RaggedLens rl, PageMap pm);
+
+hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, bool row_form, const void* q, void* K, void* V, void* Kp,
+                            const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
+                            RowCtl* ctl, uint2* list, uint32_t* cnt, float* part_acc, float* part_ml, hipStream_t st,
+                            RaggedLens rl, PageMap pm) {
+  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ctl, ListOut{list, cnt, 2 * p.lanes}, st, rl,
+                                         AppendArgs{k_new, v_new, K, V, pm, false});
+  if (e != hipSuccess) return e;
+  StepArgs a = step_args(s, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, rl, pm);
+  a.list = list; a.cnt = cnt;
+  a.lanes = p.lanes;
+  a.magic = (uint32_t)((1ull << 32) / (unsigned)p.lanes) + 1u;
+  a.nwgs = p.nwgs;
+  a.part_acc = part_acc; a.part_ml = part_ml;
+  const char* name = row_form ? "fasa_row" : "fasa_select_attend";
+  switch (s.n_q_heads / s.n_kv_heads) {
+    case 1: return launch_list_g<uint16_t, 1>(a, p.ept, name, st);
+    case 2: return launch_list_g<uint16_t, 2>(a, p.ept, name, st);
+    case 3: return launch_list_g<uint16_t, 3>(a, p.ept, name, st);
+    case 4: return launch_list_g<uint16_t, 4>(a, p.ept, name, st);
+    case 5: return launch_list_g<uint16_t, 5>(a, p.ept, name, st);
+    case 6: return launch_list_g<uint16_t, 6>(a, p.ept, name, st);
+    case 7: return launch_list_g<uint16_t, 7>(a, p.ept, name, st);
+    case 8: return launch_list_g<uint16_t, 8>(a, p.ept, name, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+static StepArgs step_args(const fasa_shape& s, const void* q, void* K, void* V, void* Kp, const int32_t* fc_idx, const void* k_new,
+                          const void* v_new, float* S, int32_t* T, float* O, RowCtl* ctl, RaggedLens rl, PageMap pm) {
+  StepArgs a{};
   a.q = q; a.K = K; a.V = V; a.Kp = Kp; a.fc_idx = fc_idx;
   a.append = k_new != nullptr;
   a.k_new = k_new ? k_new : q;      // rows * head_dim elements are there: the queries are no fewer
@@ -771,11 +1090,17 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
   a.t_pitch = s.budget < s.n_ctx ? s.budget : s.n_ctx;
   a.pairing = s.pairing;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
+  return a;
+}
+
+hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* K, void* V, void* Kp,
+                       const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
+                       RowCtl* ctl, hipStream_t st, RaggedLens rl, PageMap pm) {
+  const StepArgs a = step_args(s, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, rl, pm);
   const int G = s.n_q_heads / s.n_kv_heads;
-  if (form == kStepRow) {
+  if (form == kStepRow) {                                      // (float32: a bf16 cache's lists come from the scoring launch)
     const hipError_t e = launch_score(s, q, Kp, fc_idx, S, nullptr, st, rl, AppendArgs{k_new, v_new, K, V, pm, false});
     if (e != hipSuccess) return e;
-    if (s.dtype == FASA_BF16) return launch("fasa_row", row_kernel<uint16_t, 8>, dim3(a.rows), dim3(kRowNT), st, a);
     if (G == 1) return launch("fasa_row", row_kernel<float, 1>, dim3(a.rows), dim3(kRowNT), st, a);
     if (G <= 4) return launch("fasa_row", row_kernel<float, 4>, dim3(a.rows), dim3(kRowNT), st, a);
     return hipErrorInvalidValue;                               // (row_form)
