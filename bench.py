@@ -663,6 +663,7 @@ def kernel_bytes(w):
         "fasa_score": planes,
         "fasa_score_list": planes,
         "fasa_select": scores,
+        "fasa_topk": scores,
         "fasa_select_all": rows * bsel * 4,
         "fasa_sparse_attend": gather,
         # what these read to select (lists of a few scores, or a histogram and the scores) is an intermediate of the step

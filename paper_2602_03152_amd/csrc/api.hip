@@ -274,6 +274,13 @@ int fasa_topk(const fasa_shape* shape, const float* S, int32_t* T, void* ws, siz
   RowCtl* ctl = (RowCtl*)(base + w.ctl_off);
   uint2* cand = (uint2*)(base + w.cand_off);
   hipStream_t st = (hipStream_t)stream;
+  const TopkPlan tp = plan_topk(shape->n_ctx, shape->budget);
+  if (tp.ept != 0) {
+    // lists go where the candidates go, their counts where the records go
+    FASA_HIP(launch_topk(tp, w.rows, shape->n_ctx, shape->n_cap, shape->budget, S, T, nullptr, cand, (uint32_t*)(base + w.rec_off),
+                         (int)(kFuseRecBytesPerRow / sizeof(uint32_t)), &ctl->done_sel, (int)(sizeof(RowCtl) / sizeof(uint32_t)), st));
+    return FASA_OK;
+  }
   if (shape->budget < shape->n_ctx) FASA_HIP(launch_hist(*shape, S, hist, st));
   FASA_HIP(launch_select(*shape, S, hist, ctl, cand, T, st));
   return FASA_OK;
@@ -482,6 +489,8 @@ int fasa_offload_decode_step(const fasa_shape* shape, const void* q, void* Kp, c
   char* VT = KT + (size_t)shape->batch * shape->n_kv_heads * bsel * shape->head_dim * e;
   // the new row (if any) joins Kp and the host parts inside the scoring kernel
   const AppendArgs ap{k_new, v_new, Knd_host, V_host, kNoPaging, true};
+  // (not the one-launch TopK-I: the rows are fetched over the host link in the order of T, and with its order, or that of
+  // the tokens, that takes 2 - 4 us more than with this one: 182.7 us per step, 184.4, 183.0)
   FASA_HIP(launch_score(*shape, q, Kp, fc_idx, S, select_all ? nullptr : hist, st, {nullptr, nullptr}, ap));
   FASA_HIP(launch_select(*shape, S, hist, ctl, cand, T, st));
   if (shape->dtype == FASA_BF16) {
@@ -505,7 +514,7 @@ int fasa_offload_decode_step(const fasa_shape* shape, const void* q, void* Kp, c
 // ---- offline calibration -------------------------------------------------------------------------
 namespace {
 struct CalibLayout {
-  size_t s_off, bitmap_off, total;
+  size_t s_off, bitmap_off, scratch_off, total;
   int kk;
 };
 
@@ -521,10 +530,13 @@ int calib_layout(const fasa_shape* shape, int32_t top_k, CalibLayout* L) {
   size_t off = 0;
   L->s_off = off;      off = align256(off + rows * shape->n_cap * 4);               // full-head scores
   L->bitmap_off = off; off = align256(off + rows * ((shape->n_ctx + 31) / 32) * 4);  // their top-K set
-  // The kernels use the two regions above.  The size callers are told, and that the call insists on, also has room for the
-  // scores of every single FC, which an earlier form of the calibration kept there: what
-  // fasa_calibration_workspace_bytes() returns for a shape does not change.
+  // Lists, counts and tickets of the top-K (calib_scratch_bytes).  The size callers are told, and that the call insists on, has
+  // room here for the scores of every single FC, which an earlier form of the calibration kept: what
+  // fasa_calibration_workspace_bytes() returns for a shape does not change.  (256 bytes per token of capacity, at least
+  // 64 of them per row; the scratch takes 8, and 2176 per row.)
+  L->scratch_off = off;
   L->total = off + rows * (shape->head_dim / 2) * shape->n_cap * 4;
+  if (off + calib_scratch_bytes((int)rows, shape->n_cap) > L->total) return FASA_EUNSUPPORTED;
   return FASA_OK;
 }
 }  // namespace
@@ -543,8 +555,8 @@ int fasa_contextual_agreement(const fasa_shape* shape, const void* q, const void
   if (!aligned16(q) || !aligned16(Kp_all) || !aligned16(CA_sum) || !aligned16(cws)) return FASA_EINVAL;
   if (cws_bytes < L.total) return FASA_EWORKSPACE;
   char* base = (char*)cws;
-  FASA_HIP(launch_calib(*shape, q, Kp_all, L.kk, (float*)(base + L.s_off), (uint32_t*)(base + L.bitmap_off), CA_sum,
-                        (hipStream_t)stream));
+  FASA_HIP(launch_calib(*shape, q, Kp_all, L.kk, (float*)(base + L.s_off), (uint32_t*)(base + L.bitmap_off),
+                        base + L.scratch_off, CA_sum, (hipStream_t)stream));
   return FASA_OK;
 }
 

@@ -2,30 +2,34 @@
 // frequency chunk with the full head, for one query.  Kp_all holds all d/2 FCs, FC-major.  Three launches:
 //
 //   calib_full_kernel   full-head scores alpha (all planes, fp32 chain in FC order);
-//   calib_topk_kernel   one workgroup per (b, h): the top-K set of alpha, as a bitmap over the tokens;
+//   topk_kernel         (topk.hip) the top-K set of alpha, as a bitmap over the tokens; calib_topk_kernel, one workgroup per
+//                       (b, h), where K is too large for it;
 //   calib_fc_kernel     one workgroup per (b, h, FC): the scores of the one FC, their top-K threshold, and how
 //                       many of the top-K are in the bitmap.
 //
 // The single-FC scores and sets never exist in memory: a workgroup streams its plane once and writes one number.
-// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys): 13.6 + 11.3 + 21.7 us.  Scoring all FCs to memory
+// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys): 13.6 + 8.9 + 21.7 us (calib_topk_kernel took 11.3 in between:
+// one compute unit a row).  Scoring all FCs to memory
 // (67 MB of scores), selecting them with the decode step's kernels and intersecting index lists took 135 us.
 #include <type_traits>
 
 #include "fasa_device.h"
 #include "fasa_internal.h"
+#include "row_list.h"
 #include "score_common.h"
 #include "select_common.h"
 
 namespace fasa {
 
 constexpr int kCalibMaxCtx = 262144;   // the bitmap of the full-head top-K set lives in LDS (32 KB)
+constexpr int kCalibTicketStride = 32; // one 128-byte line per row
 constexpr int kCalibPerThread = 16;    // scores in flight per thread
 
 // Full-head scores of a slice of 256 * TPT tokens: 1-D grid of rows * nslices workgroups.
 template <typename ET, int PAIR_SHIFT, int PAIR_ADD>
 __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict__ q, const ET* __restrict__ Kp,
-                                                         float* __restrict__ S, int rows, int nslices, int Hq, int Hkv,
-                                                         int N, int n_cap) {
+                                                         float* __restrict__ S, uint32_t* __restrict__ tickets, int rows,
+                                                         int nslices, int Hq, int Hkv, int N, int n_cap) {
   constexpr int D = kHeadDim, F = D / 2, NW = 16;
   constexpr int TPT = ScoreTraits<ET>::TPT;
   __shared__ float ql[kMaxGroup][D];
@@ -33,6 +37,7 @@ __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict
   int row, slice;
   row_slice_of_block(rows, nslices, row, slice);
   const int G = Hq / Hkv, t = threadIdx.x;
+  if (slice == 0 && t == 0) tickets[row * kCalibTicketStride] = 0;     // of the top-K launch behind this one
   const ET* qh = q + ((size_t)(row / Hkv) * Hq + (size_t)(row % Hkv) * G) * D + (t & (D - 1));
   ET qcol[kMaxGroup / 2];                                   // head dim t mod 128 of query heads t / 128, + 2, ...
 #pragma unroll
@@ -352,15 +357,18 @@ __global__ __launch_bounds__(256) void calib_all_kernel(float* __restrict__ CA_s
 
 template <typename ET, int PS, int PA>
 static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap,
-                                 float* CA_sum, hipStream_t st) {
+                                 uint2* list, uint32_t* cnt, uint32_t* tickets, float* CA_sum, hipStream_t st) {
   const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2, words = (s.n_ctx + 31) / 32;
   const int per = 256 * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per - 1) / per;
   hipError_t e = launch("fasa_calib_full", calib_full_kernel<ET, PS, PA>, dim3(rows * nslices), dim3(256), st, (const ET*)q,
-                        (const ET*)Kp_all, S, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap);
+                        (const ET*)Kp_all, S, tickets, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap);
   if (e != hipSuccess) return e;
   const auto stage = [&](auto nt_c, auto words_c) {
     constexpr int NT = decltype(nt_c)::value, WORDS = decltype(words_c)::value;
-    hipError_t err = launch("fasa_calib_topk", calib_topk_kernel<NT, WORDS>, dim3(rows), dim3(NT), st, S, bitmap, s.n_ctx,
+    const TopkPlan tp = plan_topk(s.n_ctx, kk);
+    hipError_t err = tp.ept ? launch_topk(tp, rows, s.n_ctx, s.n_cap, kk, S, nullptr, bitmap, list, cnt, kListMaxSegs, tickets,
+                                          kCalibTicketStride, st)
+                     : launch("fasa_calib_topk", calib_topk_kernel<NT, WORDS>, dim3(rows), dim3(NT), st, S, bitmap, s.n_ctx,
                             s.n_cap, kk, words);
     if (err != hipSuccess) return err;
     return launch("fasa_calib_fc", calib_fc_kernel<ET, NT, WORDS, PS, PA>, dim3(rows * half), dim3(NT), st, (const ET*)q,
@@ -373,8 +381,17 @@ static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void*
   return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, kCalibMaxCtx / 32>{});
 }
 
-hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap,
+// list [rows][n_cap], cnt [rows][kListMaxSegs], tickets [rows][kCalibTicketStride]
+size_t calib_scratch_bytes(int rows, int n_cap) {
+  return (size_t)rows * ((size_t)n_cap * sizeof(uint2) + (kListMaxSegs + kCalibTicketStride) * sizeof(uint32_t));
+}
+
+hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap, void* scratch,
                         float* CA_sum, hipStream_t st) {
+  const size_t rows = (size_t)s.batch * s.n_kv_heads;
+  uint2* list = (uint2*)scratch;
+  uint32_t* cnt = (uint32_t*)(list + rows * s.n_cap);
+  uint32_t* tickets = cnt + rows * kListMaxSegs;
   constexpr int D = kHeadDim;
   if (kk >= s.n_ctx) {
     const int n = s.batch * s.n_kv_heads * (D / 2);
@@ -382,10 +399,10 @@ hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, 
   }
   const bool inter = s.pairing == FASA_PAIR_INTERLEAVED;   // FC i: dims (2i, 2i + 1), else (i, i + d/2)
   if (s.dtype == FASA_BF16)
-    return inter ? launch_calib_p<uint16_t, 1, 1>(s, q, Kp_all, kk, S, bitmap, CA_sum, st)
-                 : launch_calib_p<uint16_t, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, CA_sum, st);
-  return inter ? launch_calib_p<float, 1, 1>(s, q, Kp_all, kk, S, bitmap, CA_sum, st)
-               : launch_calib_p<float, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, CA_sum, st);
+    return inter ? launch_calib_p<uint16_t, 1, 1>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st)
+                 : launch_calib_p<uint16_t, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st);
+  return inter ? launch_calib_p<float, 1, 1>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st)
+               : launch_calib_p<float, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st);
 }
 
 int calib_max_ctx() { return kCalibMaxCtx; }

@@ -188,6 +188,14 @@ hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const
                              const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap);
 // zeroes the histogram and the row counters (workspace initialisation)
 hipError_t launch_ws_clear(const fasa_shape& s, uint32_t* hist, RowCtl* ctl, hipStream_t st);
+// TopK-I of given scores in one launch (topk.hip): the set of every row to T, or as a bitmap of ceil(n_ctx / 32) words
+// (up to 262144 tokens).  ept == 0: not for this shape.  list [row][n_cap], cnt [row][cnt_pitch]; tickets [row * ticket_stride], zero.
+struct TopkPlan {
+  int ept, lanes;
+};
+TopkPlan plan_topk(int n_ctx, int bsel);
+hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint32_t* bitmap,
+                       uint2* list, uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st);
 hipError_t launch_hist(const fasa_shape& s, const float* S, uint32_t* hist, hipStream_t st);
 // Tslot (paged caches only, else null): receives the pool slot of every entry of T, same layout
 hipError_t launch_select(const fasa_shape& s, const float* S, const uint32_t* hist, RowCtl* ctl,
@@ -224,6 +232,9 @@ struct ListPlan {
   int lanes;       // threads that load a segment's first 2 * lanes entries
 };
 ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits);
+// Entries per thread (even, at most `most`) of nt threads that load what a row's lists are likely to hold, 0: more than
+// fit; lanes: threads per segment, two entries each.
+int list_loads(int n, int bsel, int seg_tokens, int sample, int nt, int most, int* lanes);
 hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, bool row_form, const void* q, void* K, void* V, void* Kp,
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                             RowCtl* ctl, uint2* list, uint32_t* cnt, float* part_acc, float* part_ml, hipStream_t st,
@@ -241,8 +252,9 @@ hipError_t launch_offload_attend(const fasa_shape& s, int max_splits, const void
                                  RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st);
 
 // offline calibration (calib.hip)
-// S: rows * n_cap floats, bitmap: rows * ceil(n_ctx / 32) words of scratch
-hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap,
+// S: rows * n_cap floats, bitmap: rows * ceil(n_ctx / 32) words, scratch: calib_scratch_bytes()
+size_t calib_scratch_bytes(int rows, int n_cap);
+hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap, void* scratch,
                         float* CA_sum, hipStream_t st);
 int calib_max_ctx();
 

@@ -6,8 +6,9 @@
 //   list     a workgroup writes the scores of its segment of the row that reach the cut, as (key, token), to the
 //            segment's own stretch of the row's list, and their number (list_count, list_write): no position is shared, so there is no
 //            atomic, and a stretch has room for the whole segment.
-//   select   list_load, select_entries: whoever selects holds the entries in registers.  A segment that has more than
-//            `load` is read on from memory in every pass; a list shorter than B, because the sample misled, is not used.
+//   select   list_load, select_entries: whoever selects holds the entries in registers, as many of each segment as are likely;
+//            a segment that has more is read on from memory in every pass.  A list shorter than B, because the sample
+//            misled, or far too long is not used: row_select.
 // What the scores look like costs time, never exactness.
 #pragma once
 
@@ -42,9 +43,9 @@ __host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m) {
 }
 
 // The cut: a score that at least r (1 .. 64 KPL) of the sample's scores reach and hardly more, in steps of a 256th of
-// their spread, by one wave whose lanes hold KPL of them each: a histogram in `bins` (256 words of LDS) and one suffix sum
-// (what it takes is its latency: four rounds of ballots, two bits each, take twice as long).  Infinite scores in the
-// sample, or all equal: no cut (-inf).  `top`: the sample's largest score.
+// the spread of the finite ones, by one wave whose lanes hold KPL of them each: a histogram in `bins` (256 words of LDS)
+// and one suffix sum (what it takes is its latency: four rounds of ballots, two bits each, take twice as long).  No
+// more than r finite scores, or hardly: no cut (-inf).  `top`: the sample's largest finite score.
 template <int KPL>
 __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t* bins, float& top) {
   const int lane = lane_id();
@@ -52,8 +53,9 @@ __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t
   float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
   for (int k = 0; k < KPL; ++k) {
-    hi = fmaxf(hi, x[k]);
-    lo = fminf(lo, x[k]);
+    const bool finite = fabsf(x[k]) < INFINITY;
+    hi = finite ? fmaxf(hi, x[k]) : hi;
+    lo = finite ? fminf(lo, x[k]) : lo;
   }
   hi = wave_max(hi);
   lo = -wave_max(-lo);
@@ -62,7 +64,8 @@ __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t
   // same wave writes and reads: its LDS operations complete in order; the fences only keep the compiler from moving them
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-  for (int k = 0; k < KPL; ++k) atomicAdd(&bins[min((uint32_t)(int)((x[k] - lo) * inv), 255u)], 1u);
+  for (int k = 0; k < KPL; ++k)    // (infinite scores: the bins at the ends; NaNs: the lowest)
+    atomicAdd(&bins[(uint32_t)fminf(fmaxf((x[k] - lo) * inv, 0.0f), 255.0f)], 1u);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   const uint4 c = *reinterpret_cast<const uint4*>(bins + 4 * lane);
   const uint32_t s2 = c.w + c.z, s1 = s2 + c.y, s0 = s1 + c.x;
@@ -72,11 +75,11 @@ __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t
   const unsigned long long m = __ballot(above + s0 >= need);   // a run of low lanes
   const int last = m ? 63 - __clzll((long long)m) : 0;
   const int bin = 4 * last + __builtin_amdgcn_readlane(j, last);
-  return spread > 0.0f && spread < INFINITY ? fmaf((float)bin, spread * (1.0f / 256.0f), lo) : -INFINITY;
+  return bin > 0 && spread < INFINITY ? fmaf((float)bin, spread * (1.0f / 256.0f), lo) : -INFINITY;
 }
 
 // A segment's list, all its waves together: acc[k] is the score of token n0 + k, which counts if it is below N.  wcnt: LDS,
-// one word a wave.  list_count, a block barrier, list_write.
+// one word a wave.  list_count, a block barrier, list_write.  SHARED: read in the same launch.
 template <int TPT>
 __device__ __forceinline__ void list_count(const float (&acc)[TPT], int n0, int N, float cut, uint32_t* wcnt,
                                            unsigned long long (&m)[TPT]) {
@@ -88,7 +91,7 @@ __device__ __forceinline__ void list_count(const float (&acc)[TPT], int n0, int 
   }
   if (lane_id() == 0) wcnt[threadIdx.x >> 6] = mine;
 }
-template <int NT, int TPT>
+template <bool SHARED, int NT, int TPT>
 __device__ __forceinline__ void list_write(const float (&acc)[TPT], int n0, const unsigned long long (&m)[TPT], const uint32_t* wcnt,
                                            uint2* seg, uint32_t* count) {
   const int wave = (int)(threadIdx.x >> 6);
@@ -102,10 +105,17 @@ __device__ __forceinline__ void list_write(const float (&acc)[TPT], int n0, cons
 #pragma unroll
   for (int k = 0; k < TPT; ++k) {
     const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
-    if ((m[k] >> lane_id()) & 1ull) seg[pos] = make_uint2(score_key(acc[k]), (uint32_t)(n0 + k));
+    if ((m[k] >> lane_id()) & 1ull) {
+      const uint2 e = make_uint2(score_key(acc[k]), (uint32_t)(n0 + k));
+      if constexpr (SHARED) st_agent(&seg[pos], e);
+      else seg[pos] = e;
+    }
     base += (uint32_t)__popcll(m[k]);
   }
-  if (threadIdx.x == 0) *count = total;
+  if (threadIdx.x == 0) {
+    if constexpr (SHARED) st_agent(count, total);
+    else *count = total;
+  }
 }
 
 // A row's lists as the selection sees them
@@ -120,13 +130,17 @@ struct ListView {
 };
 
 // Entries 2j, 2j + 1 of the thread: two adjacent ones of a segment, whatever the memory holds there (list_mask)
-template <int NT, int EPT>
+template <bool SHARED, int NT, int EPT>
 __device__ __forceinline__ void list_load(const ListView& v, uint32_t (&key)[EPT], uint32_t (&tok)[EPT]) {
+  const __amdgpu_buffer_rsrc_t rs = agent_buffer(v.list);
 #pragma unroll
   for (int j = 0; j < EPT / 2; ++j) {
     const uint32_t g = (uint32_t)(j * NT) + threadIdx.x, seg = __umulhi(g, v.magic);
     const int pos = (int)seg * v.seg_tokens + (int)(g - seg * (uint32_t)v.lanes) * 2;
-    const uint4 x = *reinterpret_cast<const uint4*>(v.list + ((int)seg < v.nsegs && pos < v.n_cap ? pos : 0));
+    const int at = (int)seg < v.nsegs && pos < v.n_cap ? pos : 0;
+    uint4 x;
+    if constexpr (SHARED) x = agent_load_u128(rs, (uint32_t)at * 8u);
+    else x = *reinterpret_cast<const uint4*>(v.list + at);
     key[2 * j] = x.x;
     tok[2 * j] = x.y;
     key[2 * j + 1] = x.z;
@@ -146,6 +160,276 @@ __device__ __forceinline__ void list_mask(const ListView& v, const uint32_t* seg
     tok[2 * j] = min(tok[2 * j], (uint32_t)v.n - 1u);        // (a stray entry can never become a stray address)
     tok[2 * j + 1] = min(tok[2 * j + 1], (uint32_t)v.n - 1u);
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Selection of a row's set: B tokens to sm.put (find_threshold in select_common.h does the narrowing)
+// ---------------------------------------------------------------------------------------------
+// Places of the set that a workgroup keeps: p0 .. p1 - 1 of 0 .. B - 1 (all of them where it works alone)
+template <typename Lds>
+__device__ __forceinline__ void keep_place(Lds& sm, int p, int p0, int p1, uint32_t tok) {
+  if (p >= p0 && p < p1) sm.put(p - p0, tok);
+}
+
+// The threshold range's share of the set, after its candidates have been listed in sm.cand (if they fit)
+template <typename Lds>
+__device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bsel, int need, int n_cand,
+                                                  const float* srow, int N, int p0, int p1) {
+  constexpr int NT = Lds::kThreads;
+  const int t = threadIdx.x;
+  const int n_above = bsel - need;
+  auto place = [&](int p, uint32_t tok) { keep_place(sm, p, p0, p1, tok); };
+  if (n_cand <= kSelCand) {   // taken iff fewer than `need` candidates sort before it
+    constexpr int P = NT / kSelCand;
+    if ((t & ~(kWave - 1)) / P < n_cand) {                    // (the waves that have any)
+      const int ci = t / P;
+      const int rank = rank_in_list<P>(sm.cand, n_cand, ci);
+      if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
+    }
+  } else {                     // a tie of more than kSelCand tokens: the first `need` of them
+    int tied = 0;              // met so far
+    for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
+      const int n = i0 + t;
+      const bool tie = n < N && score_key(ld_agent(srow + min(n, N - 1))) == klo;
+      uint32_t tot;
+      const uint32_t before = block_prefix_sum<NT>(tie ? 1u : 0u, sm.wtot, tot);
+      if (tie && tied + (int)before < need) place(n_above + tied + (int)before, (uint32_t)n);
+      tied += (int)tot;
+    }
+  }
+  __syncthreads();
+}
+
+// All of a row's scores, out of memory: where there is no usable list.  klo, ktop: a key that B scores are likely to reach, and
+// one at the upper end (0, 0: nothing is known).  SHARED: other workgroups of this launch wrote the scores.  Places go by
+// wave.  The histogram is zero at the call (a barrier ago); ends with a block barrier.  The row is read in 16-byte
+// pieces, four in flight (S is n_cap long, a multiple of 64).
+template <bool SHARED, typename Lds>
+__device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow, int N, int p0, int p1, uint32_t klo = 0,
+                                           uint32_t ktop = 0) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
+  auto for_scores = [&](auto&& f) {                           // f(key, token, token < N), all threads together
+    for (int i0 = 0; i0 < N; i0 += 16 * NT) {
+      uint4 x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = i0 + (u * NT + t) * 4;
+        if constexpr (SHARED) x[u] = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
+        else x[u] = *reinterpret_cast<const uint4*>(srow + (n < N ? n : 0));
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = i0 + (u * NT + t) * 4;
+        f(score_key(__uint_as_float(x[u].x)), n, n < N);
+        f(score_key(__uint_as_float(x[u].y)), n + 1, n + 1 < N);
+        f(score_key(__uint_as_float(x[u].z)), n + 2, n + 2 < N);
+        f(score_key(__uint_as_float(x[u].w)), n + 3, n + 3 < N);
+      }
+    }
+  };
+  uint32_t khi = 0xffffffffu;
+  int shift = klo ? first_shift(klo, ktop) : 22, need = bsel, n_cand;
+  for (;;) {
+    for_scores([&](uint32_t key, int, bool in) {
+      if (in && key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
+    });
+    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+    if (n_cand == 0) { klo = 0; shift = 22; }                 // fewer reach it: the whole range
+  }
+  uint32_t pw = 0, pc = 0;
+  for (int pass = 0; pass < 2; ++pass) {                      // count per wave, then place
+    for_scores([&](uint32_t key, int n, bool in) {
+      const bool win = in && key > khi, cnd = in && key >= klo && key <= khi;
+      const unsigned long long mw = __ballot(win), mc = __ballot(cnd);
+      if (pass) {
+        const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, pw));
+        const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, pc));
+        if (win) keep_place(sm, (int)p, p0, p1, (uint32_t)n);
+        if (cnd && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(key, (uint32_t)n);
+      }
+      pw += (uint32_t)__popcll(mw);
+      pc += (uint32_t)__popcll(mc);
+    });
+    __syncthreads();
+    if (!pass) {
+      if (lane == 0) { sm.wtot[wave] = pw; sm.wtot2[wave] = pc; }
+      __syncthreads();
+      pw = pc = 0;
+      for (int w = 0; w < NWV - 1; ++w) {
+        pw += w < wave ? sm.wtot[w] : 0u;
+        pc += w < wave ? sm.wtot2[w] : 0u;
+      }
+    }
+  }
+  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
+}
+
+// The same among listed scores that the threads hold (key 0: none; klo > 0).
+// more(f): calls f(valid, key, token) for listed scores that nobody holds, whole waves at a time, in the same order
+// each time; `over` (the same in all threads) says that there are any.  Places go by thread, then by wave of the rest.
+// False: fewer than B scores are listed (the histogram is zero then).
+template <int EPT, typename Lds, typename More>
+__device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EPT], const uint32_t (&tok)[EPT], bool over,
+                                               More&& more, uint32_t klo, int shift, int bsel, const float* srow, int N,
+                                               int p0, int p1) {
+  constexpr int NWV = Lds::kWaves;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t khi = 0xffffffffu;
+  int need = bsel, n_cand;
+  FASA_T_DECL(6);
+  FASA_T(0);
+  auto count = [&](uint32_t d) { atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kSelBins - 1u)], 1u); };   // d: key - klo
+  for (;;) {
+    const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const uint32_t d = key[k] - klo;
+      if (d <= span) count(d);
+    }
+    if (over) more([&](bool valid, uint32_t k, uint32_t) { if (valid && k - klo <= span) count(k - klo); });
+    FASA_T(1);
+    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+    if (n_cand == 0) return false;
+  }
+  FASA_T(2);
+  const uint32_t span = khi - klo;
+  uint32_t n_win = 0, cnd = 0;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    n_win += key[k] > khi ? 1u : 0u;
+    cnd |= key[k] - klo <= span ? 1u << k : 0u;
+  }
+  // both counts of a thread fit 16 bits, and so do their sums (at most EPT * NT entries)
+  static_assert(EPT <= 32 && EPT * Lds::kThreads < 65536, "packed flags and counts");
+  const uint32_t mine = n_win | ((uint32_t)__popc(cnd) << 16);
+  const uint32_t incl = wave_prefix_sum(mine);
+  if (lane == kWave - 1) sm.wtot[wave] = incl;
+  __syncthreads();
+  uint32_t before = incl - mine, all = 0;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) {
+    const uint32_t x = sm.wtot[w];
+    before += w < wave ? x : 0u;
+    all += x;
+  }
+  // Winners: a wave whose winners are other workgroups' share skips the writing (of 32 workgroups a row, all but one or two
+  // waves).  Candidates: few threads have one, so each takes its own one by one.
+  {
+    uint32_t p = (before & 0xffffu) - (uint32_t)p0;           // place in this workgroup's share
+    const uint32_t len = (uint32_t)(p1 - p0);
+    if (__ballot((int)p < (int)len && (int)(p + n_win) > 0) != 0ull) {
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) {
+        const bool w = key[k] > khi;
+        if (w && p < len) sm.put((int)p, tok[k]);
+        p += w ? 1u : 0u;
+      }
+    }
+    uint32_t pc = before >> 16;
+    while (__ballot(cnd != 0u) != 0ull) {
+      const int j = __ffs((int)cnd) - 1;                      // (-1: none)
+      uint2 e = make_uint2(0u, 0u);
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) e = j == k ? make_uint2(key[k], tok[k]) : e;
+      if (j >= 0 && pc < (uint32_t)kSelCand) sm.cand[pc] = e;
+      ++pc;
+      cnd &= cnd - 1u;
+    }
+  }
+  if (over) {
+    uint32_t w0 = 0, c0 = 0;                                  // of this wave
+    more([&](bool valid, uint32_t k, uint32_t) {
+      w0 += (uint32_t)__popcll(__ballot(valid && k > khi));
+      c0 += (uint32_t)__popcll(__ballot(valid && k >= klo && k <= khi));
+    });
+    __syncthreads();                                          // all have read wtot
+    if (lane == 0) { sm.wtot[wave] = w0; sm.wtot2[wave] = c0; }
+    __syncthreads();
+    w0 = all & 0xffffu; c0 = all >> 16;
+    for (int w = 0; w < wave; ++w) { w0 += sm.wtot[w]; c0 += sm.wtot2[w]; }
+    more([&](bool valid, uint32_t k, uint32_t n) {
+      const bool win1 = valid && k > khi, cnd1 = valid && k >= klo && k <= khi;
+      const unsigned long long mw = __ballot(win1), mc = __ballot(cnd1);
+      const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, w0));
+      const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, c0));
+      if (win1) keep_place(sm, (int)p, p0, p1, n);
+      if (cnd1 && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(k, n);
+      w0 += (uint32_t)__popcll(mw);
+      c0 += (uint32_t)__popcll(mc);
+    });
+  }
+  __syncthreads();
+  FASA_T(3);
+  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
+  FASA_T(4);
+  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "entries: count %llu threshold %llu place %llu resolve (%d of %d) %llu (x10ns)\n",
+               FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2), need, n_cand, FASA_T_D(4, 3));
+  return true;
+}
+
+// Selection of a row out of its segments' lists in memory (row_list.h).  kcut: what they were made with; ktop: the sample's
+// largest key.  SHARED: the lists were made in this launch.
+template <bool SHARED, int EPT, typename Lds>
+__device__ __forceinline__ void select_listed(Lds& sm, const ListView& v, const uint32_t* cnt, uint32_t kcut, uint32_t ktop,
+                                              int bsel, const float* srow, int N, int p0, int p1) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves, CPT = kListMaxSegs / NT;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t key[EPT], tok[EPT], c1[CPT];
+#pragma unroll
+  for (int i = 0; i < CPT; ++i) {
+    const uint32_t* p = cnt + min(i * NT + t, v.nsegs - 1);
+    c1[i] = SHARED ? ld_agent(p) : *p;
+  }
+  list_load<SHARED, NT, EPT>(v, key, tok);
+  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+  if (t == 0) sm.thr[2] = 0;
+  uint32_t c = 0;
+  bool beyond = false;
+#pragma unroll
+  for (int i = 0; i < CPT; ++i) {
+    const uint32_t x = i * NT + t < v.nsegs ? c1[i] : 0u;
+    sm.seg_cnt[i * NT + t] = x;
+    c += x;
+    beyond |= x > 2u * (uint32_t)v.lanes;
+  }
+  FASA_T_DECL(5);
+  FASA_T(0);
+  const uint32_t sum = wave_prefix_sum(c);
+  const bool more_here = __ballot(beyond) != 0ull;
+  if (lane == kWave - 1) { sm.wtot[wave] = sum; sm.wtot2[wave] = more_here ? 1u : 0u; }
+  __syncthreads();
+  uint32_t M = 0, over = 0;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) { M += sm.wtot[w]; over |= sm.wtot2[w]; }
+  auto more = [&](auto&& f) {
+    for (int s0 = 0; s0 < v.nsegs; s0 += kWave * NWV) {       // this wave's segments are s0 + wave, + NWV, ..
+      const int sl = s0 + lane * NWV + wave;
+      unsigned long long m = __ballot(sl < v.nsegs && sm.seg_cnt[min(sl, kListMaxSegs - 1)] > 2u * (uint32_t)v.lanes);
+      for (; m; m &= m - 1ull) {
+        const int s = s0 + (__ffsll((long long)m) - 1) * NWV + wave;
+        const int n = (int)min(sm.seg_cnt[s], (uint32_t)v.seg_tokens);
+        for (int i0 = 2 * v.lanes; i0 < n; i0 += kWave) {
+          const uint2* e = v.list + (size_t)s * v.seg_tokens + min(i0 + lane, n - 1);
+          const uint2 x = SHARED ? ld_agent(e) : *e;
+          f(i0 + lane < n, x.x, min(x.y, (uint32_t)N - 1u));
+        }
+      }
+    }
+  };
+  list_mask<NT, EPT>(v, sm.seg_cnt, key, tok);
+  FASA_T(1);
+  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "list counts arrive + barrier %llu M %d over %d of %d\n", FASA_T_D(1, 0), (int)M, (int)over, EPT * NT);
+  // far more than are held (ties, a cut that could not be made): the row's scores are the faster ones to read
+  const bool usable = (int)M >= bsel && (int)M <= 2 * EPT * NT;
+  if (usable && select_entries<EPT>(sm, key, tok, over != 0, more, max(kcut, 1u), kcut ? first_shift(kcut, ktop) : 22, bsel, srow,
+                                    N, p0, p1))
+    return;
+  // Or the sample misled, and the threshold lies below the cut, as a first guess by no more than its best lies above.
+  __syncthreads();                                            // (all have read the counts)
+  const float cut = key_score(kcut), down = (int)M >= bsel ? cut : cut - (key_score(ktop) - cut);
+  row_select<false>(sm, bsel, srow, N, p0, p1, down > -INFINITY ? score_key(down) : 0u, ktop);
 }
 
 }  // namespace fasa

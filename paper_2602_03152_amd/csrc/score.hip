@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
   if (!sampler) list_count(acc, n0, N, cut_top.x, wcnt, m);
   __syncthreads();
   if (sampler) return;
-  list_write<NT>(acc, n0, m, wcnt, lists.list + (size_t)row * n_cap + slice * SL, lists.cnt + (size_t)row * kListCntPitch + slice);
+  list_write<false, NT>(acc, n0, m, wcnt, lists.list + (size_t)row * n_cap + slice * SL, lists.cnt + (size_t)row * kListCntPitch + slice);
   if constexpr (APPEND) {
     if (own_wg) {   // the whole new row to K (threads 0..127) and V (threads 128..255)
       ET* dst = (t < D ? Kc : Vc) + kv_row_offset(pm, b, n_app, sb, sn) + h * sh + (t & (D - 1));

@@ -82,6 +82,7 @@ struct RowLds {
   uint32_t thr[4];
   uint32_t n_list;
   int p_new;                                                 // place of the appended row in wl, or -1
+  __device__ __forceinline__ void put(int place, uint32_t tok) { wl[place] = tok; }
 };
 
 // 16-byte store that goes through to the coherence point (see st_agent), counted by the compiler.  The
@@ -89,213 +90,6 @@ struct RowLds {
 __device__ __forceinline__ void st_agent_f4(__amdgpu_buffer_rsrc_t rs, uint32_t byte_offset, float4 v) {
   const u32x4_t w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
   __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)byte_offset, 0, kCachePolicySc1);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Selection of a row's set: B tokens to sm.wl (find_threshold in select_common.h does the narrowing)
-// ---------------------------------------------------------------------------------------------
-// Places of the set that a workgroup keeps in sm.wl: p0 .. p1 - 1 of 0 .. B - 1 (all of them where it attends alone)
-template <typename Lds>
-__device__ __forceinline__ void keep_place(Lds& sm, int p, int p0, int p1, uint32_t tok) {
-  if (p >= p0 && p < p1) sm.wl[p - p0] = tok;
-}
-
-// The threshold range's share of the set, after its candidates have been listed in sm.cand (if they fit)
-template <typename Lds>
-__device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bsel, int need, int n_cand,
-                                                  const float* srow, int N, int p0, int p1) {
-  constexpr int NT = Lds::kThreads;
-  const int t = threadIdx.x;
-  const int n_above = bsel - need;
-  auto place = [&](int p, uint32_t tok) { keep_place(sm, p, p0, p1, tok); };
-  if (n_cand <= kSelCand) {   // taken iff fewer than `need` candidates sort before it
-    constexpr int P = NT / kSelCand;
-    if ((t & ~(kWave - 1)) / P < n_cand) {                    // (the waves that have any)
-      const int ci = t / P;
-      const int rank = rank_in_list<P>(sm.cand, n_cand, ci);
-      if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
-    }
-  } else {                     // a tie of more than kSelCand tokens: the first `need` of them
-    int tied = 0;              // met so far
-    for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
-      const int n = i0 + t;
-      const bool tie = n < N && score_key(ld_agent(srow + min(n, N - 1))) == klo;
-      uint32_t tot;
-      const uint32_t before = block_prefix_sum<NT>(tie ? 1u : 0u, sm.wtot, tot);
-      if (tie && tied + (int)before < need) place(n_above + tied + (int)before, (uint32_t)n);
-      tied += (int)tot;
-    }
-  }
-  __syncthreads();
-}
-
-// All of a row's scores, out of memory: where there is no usable list.  klo, ktop: a key that B scores are likely to reach, and
-// one at the upper end (0, 0: nothing is known).  SHARED: other workgroups of this launch wrote the scores.  Places go by
-// wave.  The histogram is zero at the call (a barrier ago); ends with a block barrier.  The row is read in 16-byte
-// pieces, four in flight (S is n_cap long, a multiple of 64).
-template <bool SHARED, typename Lds>
-__device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow, int N, int p0, int p1, uint32_t klo = 0,
-                                           uint32_t ktop = 0) {
-  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
-  auto for_scores = [&](auto&& f) {                           // f(key, token, token < N), all threads together
-    for (int i0 = 0; i0 < N; i0 += 16 * NT) {
-      uint4 x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int n = i0 + (u * NT + t) * 4;
-        if constexpr (SHARED) x[u] = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
-        else x[u] = *reinterpret_cast<const uint4*>(srow + (n < N ? n : 0));
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int n = i0 + (u * NT + t) * 4;
-        f(score_key(__uint_as_float(x[u].x)), n, n < N);
-        f(score_key(__uint_as_float(x[u].y)), n + 1, n + 1 < N);
-        f(score_key(__uint_as_float(x[u].z)), n + 2, n + 2 < N);
-        f(score_key(__uint_as_float(x[u].w)), n + 3, n + 3 < N);
-      }
-    }
-  };
-  uint32_t khi = 0xffffffffu;
-  int shift = klo ? first_shift(klo, ktop) : 22, need = bsel, n_cand;
-  for (;;) {
-    for_scores([&](uint32_t key, int, bool in) {
-      if (in && key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
-    });
-    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
-    if (n_cand == 0) { klo = 0; shift = 22; }                 // fewer reach it: the whole range
-  }
-  uint32_t pw = 0, pc = 0;
-  for (int pass = 0; pass < 2; ++pass) {                      // count per wave, then place
-    for_scores([&](uint32_t key, int n, bool in) {
-      const bool win = in && key > khi, cnd = in && key >= klo && key <= khi;
-      const unsigned long long mw = __ballot(win), mc = __ballot(cnd);
-      if (pass) {
-        const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, pw));
-        const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, pc));
-        if (win) keep_place(sm, (int)p, p0, p1, (uint32_t)n);
-        if (cnd && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(key, (uint32_t)n);
-      }
-      pw += (uint32_t)__popcll(mw);
-      pc += (uint32_t)__popcll(mc);
-    });
-    __syncthreads();
-    if (!pass) {
-      if (lane == 0) { sm.wtot[wave] = pw; sm.wtot2[wave] = pc; }
-      __syncthreads();
-      pw = pc = 0;
-      for (int w = 0; w < NWV - 1; ++w) {
-        pw += w < wave ? sm.wtot[w] : 0u;
-        pc += w < wave ? sm.wtot2[w] : 0u;
-      }
-    }
-  }
-  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
-}
-
-// The same among listed scores that the threads hold (key 0: none; klo > 0).
-// more(f): calls f(valid, key, token) for listed scores that nobody holds, whole waves at a time, in the same order
-// each time; `over` (the same in all threads) says that there are any.  Places go by thread, then by wave of the rest.
-// False: fewer than B scores are listed (the histogram is zero then).
-template <int EPT, typename Lds, typename More>
-__device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EPT], const uint32_t (&tok)[EPT], bool over,
-                                               More&& more, uint32_t klo, int shift, int bsel, const float* srow, int N,
-                                               int p0, int p1) {
-  constexpr int NWV = Lds::kWaves;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t khi = 0xffffffffu;
-  int need = bsel, n_cand;
-  FASA_T_DECL(6);
-  FASA_T(0);
-  auto count = [&](uint32_t d) { atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kSelBins - 1u)], 1u); };   // d: key - klo
-  for (;;) {
-    const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-      const uint32_t d = key[k] - klo;
-      if (d <= span) count(d);
-    }
-    if (over) more([&](bool valid, uint32_t k, uint32_t) { if (valid && k - klo <= span) count(k - klo); });
-    FASA_T(1);
-    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
-    if (n_cand == 0) return false;
-  }
-  FASA_T(2);
-  const uint32_t span = khi - klo;
-  uint32_t n_win = 0, cnd = 0;
-#pragma unroll
-  for (int k = 0; k < EPT; ++k) {
-    n_win += key[k] > khi ? 1u : 0u;
-    cnd |= key[k] - klo <= span ? 1u << k : 0u;
-  }
-  // both counts of a thread fit 16 bits, and so do their sums (at most EPT * NT entries)
-  static_assert(EPT <= 32 && EPT * Lds::kThreads < 65536, "packed flags and counts");
-  const uint32_t mine = n_win | ((uint32_t)__popc(cnd) << 16);
-  const uint32_t incl = wave_prefix_sum(mine);
-  if (lane == kWave - 1) sm.wtot[wave] = incl;
-  __syncthreads();
-  uint32_t before = incl - mine, all = 0;
-#pragma unroll
-  for (int w = 0; w < NWV; ++w) {
-    const uint32_t x = sm.wtot[w];
-    before += w < wave ? x : 0u;
-    all += x;
-  }
-  // Winners: a wave whose winners are other workgroups' share skips the writing (of 32 workgroups a row, all but one or two
-  // waves).  Candidates: few threads have one, so each takes its own one by one.
-  {
-    uint32_t p = (before & 0xffffu) - (uint32_t)p0;           // place in this workgroup's share
-    const uint32_t len = (uint32_t)(p1 - p0);
-    if (__ballot((int)p < (int)len && (int)(p + n_win) > 0) != 0ull) {
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) {
-        const bool w = key[k] > khi;
-        if (w && p < len) sm.wl[p] = tok[k];
-        p += w ? 1u : 0u;
-      }
-    }
-    uint32_t pc = before >> 16;
-    while (__ballot(cnd != 0u) != 0ull) {
-      const int j = __ffs((int)cnd) - 1;                      // (-1: none)
-      uint2 e = make_uint2(0u, 0u);
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) e = j == k ? make_uint2(key[k], tok[k]) : e;
-      if (j >= 0 && pc < (uint32_t)kSelCand) sm.cand[pc] = e;
-      ++pc;
-      cnd &= cnd - 1u;
-    }
-  }
-  if (over) {
-    uint32_t w0 = 0, c0 = 0;                                  // of this wave
-    more([&](bool valid, uint32_t k, uint32_t) {
-      w0 += (uint32_t)__popcll(__ballot(valid && k > khi));
-      c0 += (uint32_t)__popcll(__ballot(valid && k >= klo && k <= khi));
-    });
-    __syncthreads();                                          // all have read wtot
-    if (lane == 0) { sm.wtot[wave] = w0; sm.wtot2[wave] = c0; }
-    __syncthreads();
-    w0 = all & 0xffffu; c0 = all >> 16;
-    for (int w = 0; w < wave; ++w) { w0 += sm.wtot[w]; c0 += sm.wtot2[w]; }
-    more([&](bool valid, uint32_t k, uint32_t n) {
-      const bool win1 = valid && k > khi, cnd1 = valid && k >= klo && k <= khi;
-      const unsigned long long mw = __ballot(win1), mc = __ballot(cnd1);
-      const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, w0));
-      const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, c0));
-      if (win1) keep_place(sm, (int)p, p0, p1, n);
-      if (cnd1 && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(k, n);
-      w0 += (uint32_t)__popcll(mw);
-      c0 += (uint32_t)__popcll(mc);
-    });
-  }
-  __syncthreads();
-  FASA_T(3);
-  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
-  FASA_T(4);
-  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "entries: count %llu threshold %llu place %llu resolve (%d of %d) %llu (x10ns)\n",
-               FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2), need, n_cand, FASA_T_D(4, 3));
-  return true;
 }
 
 // Selection of a row inside its list of M <= EPT * NT scores in LDS (score bits, token) that reach the cut kcut (0: everything does)
@@ -327,64 +121,6 @@ __device__ __forceinline__ void select_row(Lds& sm, int M, uint32_t kcut, uint32
   }
   publish_barrier();                                          // this workgroup's own scores are in memory
   row_select<true>(sm, bsel, srow, N, 0, bsel);
-}
-
-// Selection of a row out of its segments' lists in memory (row_list.h).  kcut: what they were made with; ktop: the sample's
-// largest key.
-template <int EPT, typename Lds>
-__device__ __forceinline__ void select_listed(Lds& sm, const ListView& v, const uint32_t* cnt, uint32_t kcut, uint32_t ktop,
-                                              int bsel, const float* srow, int N, int p0, int p1) {
-  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves, CPT = kListMaxSegs / NT;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t key[EPT], tok[EPT], c1[CPT];
-#pragma unroll
-  for (int i = 0; i < CPT; ++i) c1[i] = cnt[min(i * NT + t, v.nsegs - 1)];
-  list_load<NT, EPT>(v, key, tok);
-  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  if (t == 0) { sm.p_new = -1; sm.thr[2] = 0; }
-  uint32_t c = 0;
-  bool beyond = false;
-#pragma unroll
-  for (int i = 0; i < CPT; ++i) {
-    const uint32_t x = i * NT + t < v.nsegs ? c1[i] : 0u;
-    sm.seg_cnt[i * NT + t] = x;
-    c += x;
-    beyond |= x > 2u * (uint32_t)v.lanes;
-  }
-  FASA_T_DECL(5);
-  FASA_T(0);
-  const uint32_t sum = wave_prefix_sum(c);
-  const bool more_here = __ballot(beyond) != 0ull;
-  if (lane == kWave - 1) { sm.wtot[wave] = sum; sm.wtot2[wave] = more_here ? 1u : 0u; }
-  __syncthreads();
-  uint32_t M = 0, over = 0;
-#pragma unroll
-  for (int w = 0; w < NWV; ++w) { M += sm.wtot[w]; over |= sm.wtot2[w]; }
-  auto more = [&](auto&& f) {
-    for (int s0 = 0; s0 < v.nsegs; s0 += kWave * NWV) {       // this wave's segments are s0 + wave, + NWV, ..
-      const int sl = s0 + lane * NWV + wave;
-      unsigned long long m = __ballot(sl < v.nsegs && sm.seg_cnt[min(sl, kListMaxSegs - 1)] > 2u * (uint32_t)v.lanes);
-      for (; m; m &= m - 1ull) {
-        const int s = s0 + (__ffsll((long long)m) - 1) * NWV + wave;
-        const int n = (int)min(sm.seg_cnt[s], (uint32_t)v.seg_tokens);
-        for (int i0 = 2 * v.lanes; i0 < n; i0 += kWave) {
-          const uint2 x = v.list[(size_t)s * v.seg_tokens + min(i0 + lane, n - 1)];
-          f(i0 + lane < n, x.x, min(x.y, (uint32_t)N - 1u));
-        }
-      }
-    }
-  };
-  list_mask<NT, EPT>(v, sm.seg_cnt, key, tok);
-  FASA_T(1);
-  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "list counts arrive + barrier %llu M %d over %d of %d\n", FASA_T_D(1, 0), (int)M, (int)over, EPT * NT);
-  if ((int)M >= bsel && select_entries<EPT>(sm, key, tok, over != 0, more, max(kcut, 1u), kcut ? first_shift(kcut, ktop) : 22,
-                                            bsel, srow, N, p0, p1))
-    return;
-  // The sample misled (one row in a hundred thousand where tokens are exchangeable): the threshold lies below the cut, as
-  // a first guess by no more than the sample's best lies above.
-  __syncthreads();                                            // (all have read the counts)
-  const float cut = key_score(kcut), down = cut - (key_score(ktop) - cut);
-  row_select<false>(sm, bsel, srow, N, p0, p1, down > -INFINITY ? score_key(down) : 0u, ktop);
 }
 
 // Attention over the tokens in sm.wl[0 .. cnt): T is written, and every wave leaves its (max, sum, weighted V)
@@ -864,7 +600,8 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
   MfmaTile<G> tile;
   tile.load_q((const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D, lane & 15, lane >> 4);
   const ListView v = {a.list + (size_t)row * a.n_cap, (N + SEG - 1) / SEG, SEG, a.lanes, a.magic, a.n_cap, N};
-  select_listed<EPT>(sm, v, a.cnt + (size_t)row * kListCntPitch, kcut, ktop, bsel, a.S + (size_t)row * a.n_cap, N, p0, p1);
+  if (t == 0) sm.p_new = -1;
+  select_listed<false, EPT>(sm, v, a.cnt + (size_t)row * kListCntPitch, kcut, ktop, bsel, a.S + (size_t)row * a.n_cap, N, p0, p1);
   FASA_T(1);
   row_attend<ET, G>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile);
   FASA_T(2);
@@ -986,7 +723,7 @@ static hipError_t launch_step_f(const StepArgs& a, hipStream_t st) {
 // What the selection loads of a row's lists without asking: `lanes` threads a segment, two entries each, so that a
 // segment's list as the sample should make it, and two and a half standard deviations (of the sample and of the segment) more, is
 // loaded.  Returns the entries per thread (even), 0: more than fit.
-static int list_loads(int n, int bsel, int seg_tokens, int sample, int nt, int most, int* lanes_out) {
+int list_loads(int n, int bsel, int seg_tokens, int sample, int nt, int most, int* lanes_out) {
   const int nsegs = (n + seg_tokens - 1) / seg_tokens;
   if (nsegs > kListMaxSegs) return 0;
   const float r = (float)list_rank(bsel, n, sample);

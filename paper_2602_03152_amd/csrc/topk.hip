@@ -14,6 +14,7 @@
 //            (low 20 key bits : ~index), which is unique per token, so exactly B - |winners|
 //            candidates come out.  It then zeroes the row's histogram and counters, which leaves
 //            the workspace clean for the next call.
+#include "row_list.h"
 #include "select_common.h"
 
 namespace fasa {
@@ -189,6 +190,142 @@ __global__ __launch_bounds__(256) void select_all_kernel(int32_t* __restrict__ T
     T[(size_t)row * N + n] = n;
     if (Tslot) Tslot[(size_t)row * N + n] = kv_slot(pm, row / Hkv, n);
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// TopK-I of given scores in one launch: a workgroup per segment of 2048 tokens takes the cut of a sample of the row's
+// scores and lists what reaches it (row_list.h); the one that comes last, by the row's ticket, selects out of the
+// lists.  No workgroup waits for another.  (A row of one segment is selected out of registers.)
+// ---------------------------------------------------------------------------------------------
+constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT, kTopkSample = 256;
+
+// WORDS: words of the bitmap that takes the set (then written to memory), 0: tokens go to T.
+template <int WORDS>
+struct TopkLds {
+  static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave;
+  __align__(16) float sample[kTopkSample];
+  __align__(16) uint32_t bins[256];
+  uint32_t hist[kSelBins];
+  uint2 cand[kSelCand];
+  uint32_t wtot[kWaves], wtot2[kWaves], wcnt[kWaves];
+  uint32_t seg_cnt[kListMaxSegs];
+  uint32_t thr[4];
+  uint32_t ticket;
+  float2 cut_top;
+  int32_t* out;
+  uint32_t bits[WORDS ? WORDS : 1];
+  __device__ __forceinline__ void put(int place, uint32_t tok) {
+    if constexpr (WORDS != 0) atomicOr(&bits[tok >> 5], 1u << (tok & 31u));
+    else out[place] = (int32_t)tok;
+  }
+};
+
+template <int WORDS>
+__device__ __forceinline__ void topk_bits_out(const TopkLds<WORDS>& sm, uint32_t* bitmap, int row, int words) {
+  __syncthreads();
+  for (int i = threadIdx.x; i < words; i += kTopkNT) bitmap[(size_t)row * words + i] = sm.bits[i];
+}
+
+template <int EPT, int WORDS, bool ONE>
+__global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int32_t* __restrict__ T,
+                                                       uint32_t* __restrict__ bitmap, uint2* list, uint32_t* cnt, int cnt_pitch,
+                                                       uint32_t* tickets, int ticket_stride, int rows, int nsegs, int N, int n_cap,
+                                                       int bsel, int words, int lanes, uint32_t magic) {
+  __shared__ TopkLds<WORDS> sm;
+  int row, seg;
+  row_slice_of_block(rows, nsegs, row, seg);
+  const int t = threadIdx.x;
+  const float* srow = S + (size_t)row * n_cap;
+  // one score out of each of 256 equal stretches, at uneven places: a mask of every second token must not hide from it
+  if (t < kTopkSample) sm.sample[t] = srow[(int)((((unsigned long long)t << 16 | (t * 40503u & 0xffffu)) * (unsigned)N) >> 24)];
+  const int n0 = seg * kTopkSeg + 4 * t;
+  const float4 x = *reinterpret_cast<const float4*>(srow + (n0 < N ? n0 : 0));   // (S is n_cap long, a multiple of 64)
+  __syncthreads();
+  if (t < kWave) {
+    const float smp[4] = {sm.sample[t], sm.sample[kWave + t], sm.sample[2 * kWave + t], sm.sample[3 * kWave + t]};
+    const int r = list_rank(bsel, N, kTopkSample);
+    float top = INFINITY, cut = -INFINITY;
+    if (r <= kTopkSample) cut = list_cut(smp, r, sm.bins, top);
+    if (t == 0) sm.cut_top = make_float2(cut, top);
+  }
+  __syncthreads();
+  const float cut = sm.cut_top.x, top = sm.cut_top.y;
+  const float acc[4] = {x.x, x.y, x.z, x.w};
+  unsigned long long m[4];
+  uint2* lrow = list + (size_t)row * n_cap;
+  uint32_t* crow = cnt + (size_t)row * cnt_pitch;
+  list_count(acc, n0, N, cut, sm.wcnt, m);
+  if constexpr (ONE) {
+    for (int i = t; i < kSelBins; i += kTopkNT) sm.hist[i] = 0;
+    if (t == 0) {
+      sm.thr[2] = 0;
+      sm.out = T + (size_t)row * bsel;
+    }
+    for (int i = t; i < words && WORDS != 0; i += kTopkNT) sm.bits[i] = 0;
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < kTopkNT / kWave; ++w) total += sm.wcnt[w];
+    const bool cut_it = (int)total >= bsel;
+    uint32_t key[4], tok[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      key[k] = n0 + k < N && (!cut_it || acc[k] >= cut) ? score_key(acc[k]) : 0u;
+      tok[k] = (uint32_t)(n0 + k);
+    }
+    const uint32_t kcut = cut_it ? score_key(cut) : 0u;
+    if (!select_entries<4>(sm, key, tok, false, [](auto&&) {}, max(kcut, 1u), kcut ? first_shift(kcut, score_key(top)) : 22, bsel, srow,
+                           N, 0, bsel))
+      row_select<false>(sm, bsel, srow, N, 0, bsel);           // (NaNs that have the key of nothing)
+    if constexpr (WORDS != 0) topk_bits_out(sm, bitmap, row, words);
+    return;
+  }
+  __syncthreads();
+  list_write<true, kTopkNT>(acc, n0, m, sm.wcnt, lrow + seg * kTopkSeg, crow + seg);
+  publish_barrier();
+  if (t == 0) sm.ticket = atomicAdd(&tickets[(size_t)row * ticket_stride], 1u);
+  __syncthreads();
+  if (sm.ticket != (uint32_t)nsegs - 1u) return;
+  if (t == 0) {
+    tickets[(size_t)row * ticket_stride] = 0;                  // clean for the next call
+    sm.out = T + (size_t)row * bsel;
+  }
+  if constexpr (WORDS != 0) {
+    for (int i = t; i < words; i += kTopkNT) sm.bits[i] = 0;
+  }
+  const ListView v = {lrow, nsegs, kTopkSeg, lanes, magic, n_cap, N};
+  select_listed<true, EPT>(sm, v, crow, score_key(cut), score_key(top), bsel, srow, N, 0, bsel);
+  if constexpr (WORDS != 0) topk_bits_out(sm, bitmap, row, words);
+}
+
+// us, histogram and selection launch / like this: 8 rows of 8192, B = 500: 11.3 / 6.8, 16 of 20011, 1250: 12.4 / 8.6, 8 of 32768,
+// 2048: 12.0 / 8.9, 128 of 16384, 256: 14.5 / 10.0.  The last workgroup's own work ends it: beyond 16 entries a thread (32 rows of
+// 32905, B = 6219: 13.7 / 17.8; 4 of 131072, 9000: 18.0 / 18.0) the row is selected by many workgroups.
+TopkPlan plan_topk(int n_ctx, int bsel) {
+  int lanes = 0;
+  const int need = bsel < n_ctx ? list_loads(n_ctx, bsel, kTopkSeg, kTopkSample, kTopkNT, 16, &lanes) : 0;
+  return TopkPlan{need == 0 ? 0 : need <= 4 ? 4 : need <= 8 ? 8 : 16, lanes};
+}
+
+template <int WORDS>
+static hipError_t launch_topk_w(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T,
+                                uint32_t* bitmap, uint2* list, uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride,
+                                hipStream_t st) {
+  const int nsegs = (n_ctx + kTopkSeg - 1) / kTopkSeg;
+  auto kernel = nsegs == 1 ? topk_kernel<4, WORDS, true> : p.ept == 4 ? topk_kernel<4, WORDS, false>
+                : p.ept == 8 ? topk_kernel<8, WORDS, false> : topk_kernel<16, WORDS, false>;
+  return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, T, bitmap, list, cnt, cnt_pitch, tickets,
+                ticket_stride, rows, nsegs, n_ctx, n_cap, bsel, (n_ctx + 31) / 32, p.lanes,
+                (uint32_t)((1ull << 32) / (unsigned)p.lanes) + 1u);
+}
+hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint32_t* bitmap,
+                       uint2* list, uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st) {
+  if (!bitmap) return launch_topk_w<0>(p, rows, n_ctx, n_cap, bsel, S, T, bitmap, list, cnt, cnt_pitch, tickets, ticket_stride, st);
+  if (n_ctx <= 32768)
+    return launch_topk_w<1024>(p, rows, n_ctx, n_cap, bsel, S, T, bitmap, list, cnt, cnt_pitch, tickets, ticket_stride, st);
+  if (n_ctx <= 262144)
+    return launch_topk_w<8192>(p, rows, n_ctx, n_cap, bsel, S, T, bitmap, list, cnt, cnt_pitch, tickets, ticket_stride, st);
+  return hipErrorInvalidValue;
 }
 
 // zeroes the histogram and the row counters: 1-D grid, one uint4 per thread
