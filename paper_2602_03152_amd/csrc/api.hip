@@ -88,6 +88,19 @@ AttendPlan plan_attend(int rows, int count, int group) {
   return p;
 }
 
+// One workgroup per compute unit, of at least 64 tokens, in as many rounds as it takes with 16384 each.
+AttendPlan plan_dense(int rows, int count) {
+  const long long slots = kAssumedCUs, total = (long long)rows * count;
+  long long nblocks = (total + 63) / 64;
+  if (nblocks > slots) nblocks = slots * ((total + slots * 16384 - 1) / (slots * 16384));
+  long long n_splits = nblocks / rows;                    // (rounded down: a few workgroups more would share compute units)
+  const int most = plan_attend(rows, count, 1).n_splits;
+  if (n_splits > most) n_splits = most;
+  if (n_splits < 1) n_splits = 1;
+  const long long tps = (count + n_splits - 1) / n_splits;
+  return AttendPlan{count, (int)tps, (int)((count + tps - 1) / tps)};
+}
+
 WsLayout ws_layout(const fasa_shape& s) {
   WsLayout w{};
   w.rows = s.batch * s.n_kv_heads;

@@ -313,11 +313,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
     for (int i = 0; i + 1 < n_tiles; ++i) {     // (a tile with another behind it is full)
       const int j0 = jw + 64 * i;
       if constexpr (DENSE) {
-        // One set of registers: the next tile's K goes where this one's has been used, and runs under this tile's
-        // P . V, its V under the next logits.  With a second set, as below, the compiler waits for all of it before
-        // this tile's last products, to move it over (8 rows of 8192: 12.00 us, like this 11.58; of 32768: 32.4 / 30.3,
-        // 4.4 TB/s; of 65536: 50.7 / 50.1; 32 rows of 32768, 7 heads: 96.7 / 98.4; over 36 drawn shapes 1.2 % less,
-        // from 4 % less to 2 % more).  Two sets used in turn wait for nothing and are 3 % slower where much is read.
+        // one set of registers, as in dense_kernel
         float sv[4];
         tile.logits(cur, scale_log2e, sv);
         __builtin_amdgcn_sched_barrier(0);
@@ -376,6 +372,127 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
                split, FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2), FASA_T_D(4, 3));
 }
 
+// Full-KV attention of a bf16 cache.  One workgroup of eight waves per compute unit: half the partial results that two
+// of four waves publish, and as many waves again to merge them, which is what a row's end costs (64 splits of 4 heads are
+// 128 KB for one compute unit to read back).  In 104 registers, so that a grid a little larger than the chip shares it.
+// us, two workgroups of four waves (attend_kernel's tiles) / like this: 8 rows of 32768, 4 heads: 30.9 / 26.4 (5.1 TB/s; 5.6 of
+// it without launch and merge); of 8192: 11.7 / 10.4; of 131072: 95.3 / 91.7; 4 rows of 20000, 7 heads: 22.8 / 14.4; two
+// workgroups of eight waves: 29.5 / 11.4 / 94.8 / 22.0; one of sixteen: 28.2 / 11.5 / 94.6 / 14.9.
+constexpr int kDenseNT = 512;
+template <int G>
+__global__ __launch_bounds__(kDenseNT, 4) void dense_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K,
+                                                            const uint16_t* __restrict__ V, float* __restrict__ O,
+                                                            RowCtl* __restrict__ ctl, float* __restrict__ part_acc,
+                                                            float* __restrict__ part_ml, int rows, int n_splits, int Hq, int Hkv,
+                                                            int N, int tok_per_split, long long sb, long long sh, long long sn,
+                                                            float scale_log2e) {
+  constexpr int D = kHeadDim, NWV = kDenseNT / kWave, STEP = 16 * NWV;   // rows of a round of tiles
+  constexpr int ACC_BYTES = NWV * G * D * 4, MERGE_BYTES = 8192 + G * kMaxSplitsLds * 4;
+  __shared__ __align__(16) unsigned char big[ACC_BYTES > MERGE_BYTES ? ACC_BYTES : MERGE_BYTES];
+  __shared__ float sm_m[NWV][G], sm_l[NWV][G];
+  __shared__ float red[G];
+  __shared__ uint32_t ticket;
+  __shared__ __align__(16) float scs[NWV][16];
+  float (*sm_o)[G][D] = reinterpret_cast<float (*)[G][D]>(big);
+
+  int row, split;
+  row_slice_of_block(rows, n_splits, row, split);
+  const int b = row / Hkv, h = row % Hkv;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lo = lane & 15, hi = lane >> 4;
+  const int s0 = split * tok_per_split, s1 = min(N, s0 + tok_per_split);
+
+  MfmaTile<G> tile;
+  tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
+  tile.reset();
+  const uint16_t* Kr = K + b * sb + h * sh + 8 * hi;
+  const uint16_t* Vr = V + b * sb + h * sh + 8 * lo;
+  TileKV<uint16_t> kv;
+  // rows j0 .. j0 + 15, clamped to the split's last
+  auto load_k = [&](int j0) { kv.load_k(Kr + (long long)min(j0 + lo, s1 - 1) * sn); };
+  auto load_v = [&](int j0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kv.load_v(i, Vr + (long long)min(j0 + 4 * hi + i, s1 - 1) * sn);
+  };
+  const int jw = s0 + wave * 16;
+  if (jw < s1) {
+    const int n_tiles = (s1 - jw + STEP - 1) / STEP;
+    float sv[4];
+    load_k(jw);
+    load_v(jw);
+    int j0 = jw;
+    for (int i = 0; i + 1 < n_tiles; ++i, j0 += STEP) {        // (a tile with another behind it is full)
+      // One set of registers: the next tile's K goes where this one's has been used, and runs under this tile's P . V, its V
+      // under the next logits.  (With a second set the compiler waits for all of the next tile before this one's last
+      // products, to move it over; two sets used in turn are slower where much is read.)
+      tile.logits(kv, scale_log2e, sv);
+      __builtin_amdgcn_sched_barrier(0);
+      load_k(j0 + STEP);
+      __builtin_amdgcn_sched_barrier(0);
+      tile.accumulate_full(kv, sv, &scs[wave][0], lo, hi);
+      __builtin_amdgcn_sched_barrier(0);
+      load_v(j0 + STEP);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    tile.logits(kv, scale_log2e, sv);
+    bool valid[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) valid[e] = j0 + 4 * hi + e < s1;
+    tile.accumulate(kv, sv, valid, &scs[wave][0], lo, hi);
+  }
+  tile.finish(&sm_m[wave][0], &sm_l[wave][0], &sm_o[wave][0][0], lo, hi);
+  __syncthreads();
+
+  const size_t pbase = ((size_t)row * n_splits + split) * G;
+  if (t < G * (D / 4)) {
+    const int g = t / (D / 4), d4 = t % (D / 4);
+    float mn, ls;
+    float4 a;
+    tile_wg_totals<G, NWV>(&sm_m[0][0], &sm_l[0][0], &sm_o[0][0][0], g, d4, mn, ls, a);
+    if (n_splits == 1) {
+      *reinterpret_cast<float4*>(O + ((size_t)b * Hq + (size_t)h * G + g) * D + 4 * d4) =
+          make_float4(a.x / ls, a.y / ls, a.z / ls, a.w / ls);
+    } else {
+      float2* pa = reinterpret_cast<float2*>(part_acc + (pbase + g) * D + 4 * d4);
+      st_agent(pa, make_float2(a.x, a.y));
+      st_agent(pa + 1, make_float2(a.z, a.w));
+      if (d4 == 0) st_agent(reinterpret_cast<float2*>(part_ml + (pbase + g) * 2), make_float2(mn, ls));
+    }
+  }
+  if (n_splits == 1) return;
+  publish_barrier();
+  if (t == 0) ticket = atomicAdd(&ctl[row].done_att, 1u);
+  __syncthreads();
+  if (ticket != (uint32_t)n_splits - 1u) return;
+  if (t == 0) ctl[row].done_att = 0;
+  combine_row<G, NothingUnderLoads, 16, kDenseNT>(part_acc, part_ml, O, row, b, h, Hq, n_splits, n_splits,
+                                                  reinterpret_cast<float*>(big + 8192), red, reinterpret_cast<float*>(big));
+}
+
+template <int G>
+static hipError_t launch_dense_g(const fasa_shape& s, const AttendPlan& p, const void* q, const void* K, const void* V, float* O,
+                                 RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st) {
+  const int rows = s.batch * s.n_kv_heads;
+  const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
+  return launch("fasa_dense_attend", dense_kernel<G>, dim3(rows * p.n_splits), dim3(kDenseNT), st, (const uint16_t*)q,
+                (const uint16_t*)K, (const uint16_t*)V, O, ctl, part_acc, part_ml, rows, p.n_splits, s.n_q_heads, s.n_kv_heads,
+                s.n_ctx, p.tok_per_split, (long long)s.kv_stride_b, (long long)s.kv_stride_h, (long long)s.kv_stride_n, scale_log2e);
+}
+static hipError_t launch_dense(const fasa_shape& s, const AttendPlan& p, const void* q, const void* K, const void* V, float* O,
+                               RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st) {
+  switch (s.n_q_heads / s.n_kv_heads) {
+    case 1: return launch_dense_g<1>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 2: return launch_dense_g<2>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 3: return launch_dense_g<3>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 4: return launch_dense_g<4>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 5: return launch_dense_g<5>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 6: return launch_dense_g<6>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 7: return launch_dense_g<7>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 8: return launch_dense_g<8>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <typename ET, int G>
 static hipError_t launch_attend_g(const fasa_shape& s, bool dense, const AttendPlan& p,
                                   const void* q, const void* K, const void* V, const int32_t* T,
@@ -385,6 +502,7 @@ static hipError_t launch_attend_g(const fasa_shape& s, bool dense, const AttendP
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
   auto kernel = [&]() {
     if constexpr (sizeof(ET) == 4 && G <= 2) return dense ? attend_valu_kernel<G, true> : attend_valu_kernel<G, false>;
+    else if constexpr (sizeof(ET) == 2) return attend_kernel<ET, G, false>;      // (full KV: dense_kernel)
     else return dense ? attend_kernel<ET, G, true> : attend_kernel<ET, G, false>;
   }();
   return launch(dense ? "fasa_dense_attend" : "fasa_sparse_attend", kernel, dim3(rows * p.n_splits), dim3(256), st,
@@ -417,6 +535,10 @@ hipError_t launch_attend(const fasa_shape& s, bool dense, const void* q, const v
   const int rows = s.batch * s.n_kv_heads;
   if (dense && pm.table != nullptr) return hipErrorInvalidValue;   // identity lists are token numbers
   const int count = dense ? s.n_ctx : (s.budget < s.n_ctx ? s.budget : s.n_ctx);
+  if (dense && s.dtype == FASA_BF16) {
+    if (rl.n_ctx || rl.budget) return hipErrorInvalidValue;       // (no caller has lengths by sequence)
+    return launch_dense(s, plan_dense(rows, count), q, K, V, O, ctl, part_acc, part_ml, st);
+  }
   const AttendPlan p = plan_attend(rows, count, s.n_q_heads / s.n_kv_heads);
   return s.dtype == FASA_BF16
              ? launch_attend_t<uint16_t>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm)

@@ -94,6 +94,7 @@ __device__ __forceinline__ void combine_row(const float* __restrict__ part_acc,
   constexpr int C = G * (D / 4);
   constexpr int P = NT / C >= 4 ? 4 : (NT / C >= 2 ? 2 : 1);
   static_assert(RS % 8 == 0 && RS >= 8, "whole chunks of eight");
+  static_assert((P - 1) * C * 16 <= 8192, "the partitions meet below the weights");
   constexpr int NW = NT / kWave, NG = (G + NW - 1) / NW;
   const int t = threadIdx.x;
   const int wave = t >> 6, lane = t & 63;

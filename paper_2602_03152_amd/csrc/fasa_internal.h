@@ -104,7 +104,8 @@ struct AttendPlan {
   int n_splits;
 };
 
-AttendPlan plan_attend(int rows, int count, int group);
+AttendPlan plan_attend(int rows, int count, int group);   // sizes the workspace
+AttendPlan plan_dense(int rows, int count);               // full KV, bf16: no more splits than plan_attend()
 
 // Fused selection + attention (fused.hip): tokens per workgroup and workgroups per row.
 // tpb == 0: this shape takes the stand-alone kernels (everything selected, a row longer than the merge can take slices

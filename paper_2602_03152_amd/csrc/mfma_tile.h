@@ -209,18 +209,18 @@ struct MfmaTile {
   }
 };
 
-// Workgroup totals from the four waves' finish() output, for thread (query head g, 4 head dims d4):
-// max, sum of weights at that max, weighted V.  sm_m, sm_l: [4][G]; sm_o: [4][G][128].
-template <int G>
+// Workgroup totals from the waves' finish() output, for thread (query head g, 4 head dims d4):
+// max, sum of weights at that max, weighted V.  sm_m, sm_l: [NWV][G]; sm_o: [NWV][G][128].
+template <int G, int NWV = 4>
 __device__ __forceinline__ void tile_wg_totals(const float* sm_m, const float* sm_l, const float* sm_o, int g, int d4,
                                                float& mn, float& ls, float4& a) {
   mn = sm_m[g];
 #pragma unroll
-  for (int w = 1; w < 4; ++w) mn = fmaxf(mn, sm_m[w * G + g]);
+  for (int w = 1; w < NWV; ++w) mn = fmaxf(mn, sm_m[w * G + g]);
   ls = 0.f;
   a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < NWV; ++w) {
     const float sc = exp2f(sm_m[w * G + g] - mn);
     ls = fmaf(sm_l[w * G + g], sc, ls);
     const float4 sw = *reinterpret_cast<const float4*>(sm_o + ((size_t)(w * G + g)) * kHeadDim + 4 * d4);
