@@ -89,7 +89,7 @@ AttendPlan plan_attend(int rows, int count, int group) {
 }
 
 // One workgroup per compute unit, of at least 64 tokens, in as many rounds as it takes with 16384 each.
-AttendPlan plan_dense(int rows, int count) {
+AttendPlan plan_attend_wide(int rows, int count) {
   const long long slots = kAssumedCUs, total = (long long)rows * count;
   long long nblocks = (total + 63) / 64;
   if (nblocks > slots) nblocks = slots * ((total + slots * 16384 - 1) / (slots * 16384));

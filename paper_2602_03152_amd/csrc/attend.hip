@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
     for (int i = 0; i + 1 < n_tiles; ++i) {     // (a tile with another behind it is full)
       const int j0 = jw + 64 * i;
       if constexpr (DENSE) {
-        // one set of registers, as in dense_kernel
+        // one set of registers, as in attend_wide_kernel
         float sv[4];
         tile.logits(cur, scale_log2e, sv);
         __builtin_amdgcn_sched_barrier(0);
@@ -372,21 +372,32 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
                split, FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2), FASA_T_D(4, 3));
 }
 
-// Full-KV attention of a bf16 cache.  One workgroup of eight waves per compute unit: half the partial results that two
-// of four waves publish, and as many waves again to merge them, which is what a row's end costs (64 splits of 4 heads are
-// 128 KB for one compute unit to read back).  In 104 registers, so that a grid a little larger than the chip shares it.
+// Attention of a bf16 cache where much of it is read.  One workgroup of eight waves per compute unit: half the partial
+// results that two of four waves publish, and as many waves again to merge them, which is what a row's end costs (64 splits
+// of 4 heads are 128 KB for one compute unit to read back).  In 104 registers (108 with a list), so that a grid a little
+// larger than the chip shares it.  Full KV,
 // us, two workgroups of four waves (attend_kernel's tiles) / like this: 8 rows of 32768, 4 heads: 30.9 / 26.4 (5.1 TB/s; 5.6 of
 // it without launch and merge); of 8192: 11.7 / 10.4; of 131072: 95.3 / 91.7; 4 rows of 20000, 7 heads: 22.8 / 14.4; two
 // workgroups of eight waves: 29.5 / 11.4 / 94.8 / 22.0; one of sixteen: 28.2 / 11.5 / 94.6 / 14.9.
-constexpr int kDenseNT = 512;
-template <int G>
-__global__ __launch_bounds__(kDenseNT, 4) void dense_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ K,
-                                                            const uint16_t* __restrict__ V, float* __restrict__ O,
-                                                            RowCtl* __restrict__ ctl, float* __restrict__ part_acc,
-                                                            float* __restrict__ part_ml, int rows, int n_splits, int Hq, int Hkv,
-                                                            int N, int tok_per_split, long long sb, long long sh, long long sn,
-                                                            float scale_log2e) {
-  constexpr int D = kHeadDim, NWV = kDenseNT / kWave, STEP = 16 * NWV;   // rows of a round of tiles
+//
+// L = NoList: all rows; SparseList: those that T names (token numbers, or pool slots of a paged cache: block << shift | offset).
+// (An empty argument: with the list's arguments unused, full KV of 8 rows of 8192 takes 0.3 us longer.)
+constexpr int kWideNT = 512;
+struct NoList { static constexpr bool used = false; };
+struct SparseList {
+  static constexpr bool used = true;
+  const int32_t* T;
+  const int32_t *n_ctx_seq, *budget_seq;
+  int count_max;
+  PageMap pm;
+};
+template <int G, class L>
+__global__ __launch_bounds__(kWideNT, 4) void attend_wide_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, float* __restrict__ O,
+    RowCtl* __restrict__ ctl, float* __restrict__ part_acc, float* __restrict__ part_ml, int rows, int n_splits, int Hq, int Hkv,
+    int N_max, int tok_per_split, long long sb, long long sh, long long sn, float scale_log2e, L list) {
+  constexpr bool LIST = L::used;
+  constexpr int D = kHeadDim, NWV = kWideNT / kWave, STEP = 16 * NWV;   // rows of a round of tiles
   constexpr int ACC_BYTES = NWV * G * D * 4, MERGE_BYTES = 8192 + G * kMaxSplitsLds * 4;
   __shared__ __align__(16) unsigned char big[ACC_BYTES > MERGE_BYTES ? ACC_BYTES : MERGE_BYTES];
   __shared__ float sm_m[NWV][G], sm_l[NWV][G];
@@ -400,26 +411,59 @@ __global__ __launch_bounds__(kDenseNT, 4) void dense_kernel(const uint16_t* __re
   const int b = row / Hkv, h = row % Hkv;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lo = lane & 15, hi = lane >> 4;
-  const int s0 = split * tok_per_split, s1 = min(N, s0 + tok_per_split);
+  int N = N_max, count = N_max;
+  PageMap pm = kNoPaging;
+  const int32_t* Trow = nullptr;
+  if constexpr (LIST) {
+    N = seq_n_ctx(list.n_ctx_seq, b, N_max);
+    count = seq_bsel(list.budget_seq, b, N, list.count_max);
+    pm = list.pm;
+    Trow = list.T + (size_t)row * list.count_max;
+  }
+  const int s0 = split * tok_per_split, s1 = min(count, s0 + tok_per_split);
 
   MfmaTile<G> tile;
   tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
   tile.reset();
-  const uint16_t* Kr = K + b * sb + h * sh + 8 * hi;
-  const uint16_t* Vr = V + b * sb + h * sh + 8 * lo;
+  const bool paged = pm.table != nullptr;
+  const int pshift = paged ? pm.shift : 31, pmask = paged ? (1 << pm.shift) - 1 : 0x7fffffff;
+  const int slot_max = paged ? (pm.n_pool << pm.shift) - 1 : N - 1;
+  const uint16_t* Kr = K + (paged ? 0 : b * sb) + h * sh + 8 * hi;
+  const uint16_t* Vr = V + (paged ? 0 : b * sb) + h * sh + 8 * lo;
   TileKV<uint16_t> kv;
-  // rows j0 .. j0 + 15, clamped to the split's last
-  auto load_k = [&](int j0) { kv.load_k(Kr + (long long)min(j0 + lo, s1 - 1) * sn); };
+  // Rows j0 .. j0 + 15, clamped to the split's last: K row lo, V rows 4hi .. 4hi + 3.  A list's entries (ek, ev) are requested a
+  // tile ahead of their rows.
+  int ek = 0, ev[4] = {0, 0, 0, 0};
+  auto load_idx = [&](int j0) {
+    if constexpr (LIST) {
+      ek = Trow[min(j0 + lo, s1 - 1)];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ev[i] = Trow[min(j0 + 4 * hi + i, s1 - 1)];
+    }
+  };
+  auto row_off = [&](int e) {
+    const int sl = min(max(e, 0), slot_max);                   // a stray index can never become a stray address
+    return (long long)(sl >> pshift) * (paged ? sb : 0) + (long long)(sl & pmask) * sn;
+  };
+  auto load_k = [&](int j0) {
+    if constexpr (LIST) kv.load_k(Kr + row_off(ek));
+    else kv.load_k(Kr + (long long)min(j0 + lo, s1 - 1) * sn);
+  };
   auto load_v = [&](int j0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) kv.load_v(i, Vr + (long long)min(j0 + 4 * hi + i, s1 - 1) * sn);
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (LIST) kv.load_v(i, Vr + row_off(ev[i]));
+      else kv.load_v(i, Vr + (long long)min(j0 + 4 * hi + i, s1 - 1) * sn);
+    }
   };
   const int jw = s0 + wave * 16;
   if (jw < s1) {
     const int n_tiles = (s1 - jw + STEP - 1) / STEP;
     float sv[4];
+    load_idx(jw);
     load_k(jw);
     load_v(jw);
+    load_idx(jw + STEP);
     int j0 = jw;
     for (int i = 0; i + 1 < n_tiles; ++i, j0 += STEP) {        // (a tile with another behind it is full)
       // One set of registers: the next tile's K goes where this one's has been used, and runs under this tile's P . V, its V
@@ -432,6 +476,7 @@ __global__ __launch_bounds__(kDenseNT, 4) void dense_kernel(const uint16_t* __re
       tile.accumulate_full(kv, sv, &scs[wave][0], lo, hi);
       __builtin_amdgcn_sched_barrier(0);
       load_v(j0 + STEP);
+      load_idx(j0 + 2 * STEP);
       __builtin_amdgcn_sched_barrier(0);
     }
     tile.logits(kv, scale_log2e, sv);
@@ -465,30 +510,38 @@ __global__ __launch_bounds__(kDenseNT, 4) void dense_kernel(const uint16_t* __re
   __syncthreads();
   if (ticket != (uint32_t)n_splits - 1u) return;
   if (t == 0) ctl[row].done_att = 0;
-  combine_row<G, NothingUnderLoads, 16, kDenseNT>(part_acc, part_ml, O, row, b, h, Hq, n_splits, n_splits,
+  combine_row<G, NothingUnderLoads, 16, kWideNT>(part_acc, part_ml, O, row, b, h, Hq, n_splits, n_splits,
                                                   reinterpret_cast<float*>(big + 8192), red, reinterpret_cast<float*>(big));
 }
 
 template <int G>
-static hipError_t launch_dense_g(const fasa_shape& s, const AttendPlan& p, const void* q, const void* K, const void* V, float* O,
-                                 RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st) {
+static hipError_t launch_wide_g(const fasa_shape& s, bool dense, const AttendPlan& p, const void* q, const void* K, const void* V,
+                                const int32_t* T, float* O, RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st,
+                                RaggedLens rl, PageMap pm) {
   const int rows = s.batch * s.n_kv_heads;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
-  return launch("fasa_dense_attend", dense_kernel<G>, dim3(rows * p.n_splits), dim3(kDenseNT), st, (const uint16_t*)q,
-                (const uint16_t*)K, (const uint16_t*)V, O, ctl, part_acc, part_ml, rows, p.n_splits, s.n_q_heads, s.n_kv_heads,
-                s.n_ctx, p.tok_per_split, (long long)s.kv_stride_b, (long long)s.kv_stride_h, (long long)s.kv_stride_n, scale_log2e);
+  const dim3 grid(rows * p.n_splits), block(kWideNT);
+  const uint16_t *q16 = (const uint16_t*)q, *k16 = (const uint16_t*)K, *v16 = (const uint16_t*)V;
+  const long long sb = s.kv_stride_b, sh = s.kv_stride_h, sn = s.kv_stride_n;
+  if (dense)
+    return launch("fasa_dense_attend", attend_wide_kernel<G, NoList>, grid, block, st, q16, k16, v16, O, ctl, part_acc, part_ml,
+                  rows, p.n_splits, s.n_q_heads, s.n_kv_heads, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e, NoList{});
+  return launch("fasa_sparse_attend", attend_wide_kernel<G, SparseList>, grid, block, st, q16, k16, v16, O, ctl, part_acc, part_ml,
+                rows, p.n_splits, s.n_q_heads, s.n_kv_heads, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e,
+                SparseList{T, rl.n_ctx, rl.budget, p.count, pm});
 }
-static hipError_t launch_dense(const fasa_shape& s, const AttendPlan& p, const void* q, const void* K, const void* V, float* O,
-                               RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st) {
+static hipError_t launch_wide(const fasa_shape& s, bool dense, const AttendPlan& p, const void* q, const void* K, const void* V,
+                              const int32_t* T, float* O, RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st,
+                              RaggedLens rl, PageMap pm) {
   switch (s.n_q_heads / s.n_kv_heads) {
-    case 1: return launch_dense_g<1>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
-    case 2: return launch_dense_g<2>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
-    case 3: return launch_dense_g<3>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
-    case 4: return launch_dense_g<4>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
-    case 5: return launch_dense_g<5>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
-    case 6: return launch_dense_g<6>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
-    case 7: return launch_dense_g<7>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
-    case 8: return launch_dense_g<8>(s, p, q, K, V, O, ctl, part_acc, part_ml, st);
+    case 1: return launch_wide_g<1>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
+    case 2: return launch_wide_g<2>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
+    case 3: return launch_wide_g<3>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
+    case 4: return launch_wide_g<4>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
+    case 5: return launch_wide_g<5>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
+    case 6: return launch_wide_g<6>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
+    case 7: return launch_wide_g<7>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
+    case 8: return launch_wide_g<8>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
     default: return hipErrorInvalidValue;
   }
 }
@@ -502,7 +555,7 @@ static hipError_t launch_attend_g(const fasa_shape& s, bool dense, const AttendP
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
   auto kernel = [&]() {
     if constexpr (sizeof(ET) == 4 && G <= 2) return dense ? attend_valu_kernel<G, true> : attend_valu_kernel<G, false>;
-    else if constexpr (sizeof(ET) == 2) return attend_kernel<ET, G, false>;      // (full KV: dense_kernel)
+    else if constexpr (sizeof(ET) == 2) return attend_kernel<ET, G, false>;      // (full KV: attend_wide_kernel)
     else return dense ? attend_kernel<ET, G, true> : attend_kernel<ET, G, false>;
   }();
   return launch(dense ? "fasa_dense_attend" : "fasa_sparse_attend", kernel, dim3(rows * p.n_splits), dim3(256), st,
@@ -535,11 +588,13 @@ hipError_t launch_attend(const fasa_shape& s, bool dense, const void* q, const v
   const int rows = s.batch * s.n_kv_heads;
   if (dense && pm.table != nullptr) return hipErrorInvalidValue;   // identity lists are token numbers
   const int count = dense ? s.n_ctx : (s.budget < s.n_ctx ? s.budget : s.n_ctx);
-  if (dense && s.dtype == FASA_BF16) {
-    if (rl.n_ctx || rl.budget) return hipErrorInvalidValue;       // (no caller has lengths by sequence)
-    return launch_dense(s, plan_dense(rows, count), q, K, V, O, ctl, part_acc, part_ml, st);
-  }
   const AttendPlan p = plan_attend(rows, count, s.n_q_heads / s.n_kv_heads);
+  if (s.dtype == FASA_BF16 && dense && (rl.n_ctx || rl.budget)) return hipErrorInvalidValue;   // (no caller has full KV of those)
+  // A list is attended like full KV where that halves many partials, attend_kernel / so: 4 rows, B = 6219, 7 heads (97 splits):
+  // 15.1 / 11.0 us; 1 row, 20000 (256): 17.3 / 14.7; 2 rows, 9000 (141): 17.4 / 13.5; 1 row, 3000 (47): 9.1 / 8.75; but 8 rows,
+  // 2048 (32): 7.3 / 7.4; 24 rows, 1000 (16): 8.1 / 8.4; 2 rows, 333 (6): 5.9 / 6.7
+  if (s.dtype == FASA_BF16 && (dense || p.n_splits > 40))
+    return launch_wide(s, dense, plan_attend_wide(rows, count), q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
   return s.dtype == FASA_BF16
              ? launch_attend_t<uint16_t>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm)
              : launch_attend_t<float>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);

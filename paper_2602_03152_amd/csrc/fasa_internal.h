@@ -105,7 +105,7 @@ struct AttendPlan {
 };
 
 AttendPlan plan_attend(int rows, int count, int group);   // sizes the workspace
-AttendPlan plan_dense(int rows, int count);               // full KV, bf16: no more splits than plan_attend()
+AttendPlan plan_attend_wide(int rows, int count);         // attend_wide_kernel: no more splits than plan_attend()
 
 // Fused selection + attention (fused.hip): tokens per workgroup and workgroups per row.
 // tpb == 0: this shape takes the stand-alone kernels (everything selected, a row longer than the merge can take slices
