@@ -290,7 +290,7 @@ int fasa_topk(const fasa_shape* shape, const float* S, int32_t* T, void* ws, siz
   const TopkPlan tp = plan_topk(shape->n_ctx, shape->budget);
   if (tp.ept != 0) {
     // lists go where the candidates go, their counts where the records go
-    FASA_HIP(launch_topk(tp, w.rows, shape->n_ctx, shape->n_cap, shape->budget, S, T, nullptr, cand, (uint32_t*)(base + w.rec_off),
+    FASA_HIP(launch_topk(tp, w.rows, shape->n_ctx, shape->n_cap, shape->budget, S, T, cand, (uint32_t*)(base + w.rec_off),
                          (int)(kFuseRecBytesPerRow / sizeof(uint32_t)), &ctl->done_sel, (int)(sizeof(RowCtl) / sizeof(uint32_t)), st));
     return FASA_OK;
   }
@@ -527,7 +527,7 @@ int fasa_offload_decode_step(const fasa_shape* shape, const void* q, void* Kp, c
 // ---- offline calibration -------------------------------------------------------------------------
 namespace {
 struct CalibLayout {
-  size_t s_off, bitmap_off, scratch_off, total;
+  size_t s_off, scratch_off, total;
   int kk;
 };
 
@@ -542,11 +542,11 @@ int calib_layout(const fasa_shape* shape, int32_t top_k, CalibLayout* L) {
   const size_t rows = (size_t)shape->batch * shape->n_kv_heads;
   size_t off = 0;
   L->s_off = off;      off = align256(off + rows * shape->n_cap * 4);               // full-head scores
-  L->bitmap_off = off; off = align256(off + rows * ((shape->n_ctx + 31) / 32) * 4);  // their top-K set
-  // Lists, counts and tickets of the top-K (calib_scratch_bytes).  The size callers are told, and that the call insists on, has
-  // room here for the scores of every single FC, which an earlier form of the calibration kept: what
+  off = align256(off + rows * ((shape->n_ctx + 31) / 32) * 4);
+  // The top-K sets and how they are found (calib_scratch_bytes).  The size callers are told, and that the call insists on, has
+  // room here for the scores of every single FC, and above for one set, which an earlier form of the calibration kept: what
   // fasa_calibration_workspace_bytes() returns for a shape does not change.  (256 bytes per token of capacity, at least
-  // 64 of them per row; the scratch takes 8, and 2176 per row.)
+  // 64 of them per row; the scratch takes 9, and 516 per row.)
   L->scratch_off = off;
   L->total = off + rows * (shape->head_dim / 2) * shape->n_cap * 4;
   if (off + calib_scratch_bytes((int)rows, shape->n_cap) > L->total) return FASA_EUNSUPPORTED;
@@ -568,8 +568,7 @@ int fasa_contextual_agreement(const fasa_shape* shape, const void* q, const void
   if (!aligned16(q) || !aligned16(Kp_all) || !aligned16(CA_sum) || !aligned16(cws)) return FASA_EINVAL;
   if (cws_bytes < L.total) return FASA_EWORKSPACE;
   char* base = (char*)cws;
-  FASA_HIP(launch_calib(*shape, q, Kp_all, L.kk, (float*)(base + L.s_off), (uint32_t*)(base + L.bitmap_off),
-                        base + L.scratch_off, CA_sum, (hipStream_t)stream));
+  FASA_HIP(launch_calib(*shape, q, Kp_all, L.kk, (float*)(base + L.s_off), base + L.scratch_off, CA_sum, (hipStream_t)stream));
   return FASA_OK;
 }
 

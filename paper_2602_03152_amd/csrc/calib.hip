@@ -1,35 +1,47 @@
 // Offline calibration (paper Sec. 3.3 eq. ca_k and Alg. 1): contextual agreement of every single
-// frequency chunk with the full head, for one query.  Kp_all holds all d/2 FCs, FC-major.  Three launches:
+// frequency chunk with the full head, for one query.  Kp_all holds all d/2 FCs, FC-major.  Two launches:
 //
 //   calib_full_kernel   full-head scores alpha (all planes, fp32 chain in FC order);
-//   topk_kernel         (topk.hip) the top-K set of alpha, as a bitmap over the tokens; calib_topk_kernel, one workgroup per
-//                       (b, h), where K is too large for it;
-//   calib_fc_kernel     one workgroup per (b, h, FC): the scores of the one FC, their top-K threshold, and how
-//                       many of the top-K are in the bitmap.
+//   calib_fc_kernel     one workgroup per (b, h): the top-K set of alpha; one per (b, h, FC): the scores of the one FC, their top-K
+//                       set, and how many of it are in that of alpha.
 //
-// The single-FC scores and sets never exist in memory: a workgroup streams its plane once and writes one number.
-// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys): 13.6 + 8.9 + 21.7 us (calib_topk_kernel took 11.3 in between:
-// one compute unit a row).  Scoring all FCs to memory
-// (67 MB of scores), selecting them with the decode step's kernels and intersecting index lists took 135 us.
+// The single-FC scores never exist in memory: a workgroup streams its plane once and writes one number.
+// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys): 13.6 + 26.1 us.  (The full head's set by a launch in between, one
+// workgroup a row: 13.6 + 11.3 + 21.7, several: 13.6 + 8.9 + 21.7.  Scoring all FCs to memory, 67 MB of scores, selecting them
+// with the decode step's kernels and intersecting index lists: 135.)
 #include <type_traits>
 
 #include "fasa_device.h"
 #include "fasa_internal.h"
-#include "row_list.h"
 #include "score_common.h"
 #include "select_common.h"
 
 namespace fasa {
 
-constexpr int kCalibMaxCtx = 262144;   // the bitmap of the full-head top-K set lives in LDS (32 KB)
-constexpr int kCalibTicketStride = 32; // one 128-byte line per row
+constexpr int kCalibMaxCtx = 262144;   // a row's set of an FC lives in LDS (33 KB)
 constexpr int kCalibPerThread = 16;    // scores in flight per thread
+constexpr int kCalibWords0 = (8192 + 30) / 31, kCalibWords1 = (32768 + 30) / 31;   // of a set (CalibSets)
+
+// The top-K sets.  A word has 31 tokens, and its top bit says that it is there: the full head's set is read with no other sign.
+struct CalibSets {
+  uint32_t* full;      // [row][words]: of the full head
+  uint32_t* fc;        // [row][FC][words]: of an FC whose workgroup did not find the full head's
+  uint32_t* state;     // [row][FC]: 0; 1: the FC's set is in fc; 2: the full head's is in full
+  int words;           // ceil(N / 31)
+  template <int NT>
+  __device__ __forceinline__ void clear(int row) const {
+    for (int i = threadIdx.x; i < words; i += NT) full[(size_t)row * words + i] = 0;
+    if (threadIdx.x < kHeadDim / 2) state[row * (kHeadDim / 2) + threadIdx.x] = 0;
+  }
+};
+constexpr uint32_t kCalibThere = 0x80000000u;
+__device__ __forceinline__ void set_bit(uint32_t* bits, uint32_t tok) { atomicOr(&bits[tok / 31u], 1u << (tok % 31u)); }
 
 // Full-head scores of a slice of 256 * TPT tokens: 1-D grid of rows * nslices workgroups.
 template <typename ET, int PAIR_SHIFT, int PAIR_ADD>
 __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict__ q, const ET* __restrict__ Kp,
-                                                         float* __restrict__ S, uint32_t* __restrict__ tickets, int rows,
-                                                         int nslices, int Hq, int Hkv, int N, int n_cap) {
+                                                         float* __restrict__ S, CalibSets sets, int rows, int nslices,
+                                                         int Hq, int Hkv, int N, int n_cap) {
   constexpr int D = kHeadDim, F = D / 2, NW = 16;
   constexpr int TPT = ScoreTraits<ET>::TPT;
   __shared__ float ql[kMaxGroup][D];
@@ -37,7 +49,7 @@ __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict
   int row, slice;
   row_slice_of_block(rows, nslices, row, slice);
   const int G = Hq / Hkv, t = threadIdx.x;
-  if (slice == 0 && t == 0) tickets[row * kCalibTicketStride] = 0;     // of the top-K launch behind this one
+  if (slice == 0) sets.clear<256>(row);                       // for the launch behind this one
   const ET* qh = q + ((size_t)(row / Hkv) * Hq + (size_t)(row % Hkv) * G) * D + (t & (D - 1));
   ET qcol[kMaxGroup / 2];                                   // head dim t mod 128 of query heads t / 128, + 2, ...
 #pragma unroll
@@ -101,7 +113,8 @@ struct CalibLds {
   };
   uint32_t wtot[NT / kWave];
   uint32_t thr[4];
-  uint32_t n_list, n_cnd, count;
+  uint32_t n_list, n_cnd, count, missing;
+  uint32_t early[kHeadDim / 2];
 };
 
 // Top-K of a row by one workgroup of NT threads, which hold a stretch of it as loaded: load(c0) requests what the
@@ -109,13 +122,15 @@ struct CalibLds {
 // get(c0, i, t, x, full) makes those of tokens c0 + (i * NT + t) * TPT + k, a NaN beyond the row unless it is said to
 // be full (cheap: made again in every pass, which keeps 16 registers free and two workgroups of 1024 on a
 // compute unit); opaque() hides the pieces from the compiler, which would otherwise keep the scores.
-// score_at(n): one token's score.  take_one(n): token n is in the set.
+// score_at(n): one token's score.  take_one(n): token n is in the set; early() and ready() run before it, with a barrier of the
+// workgroup between them.
 // What reaches the cut is gathered into a list in LDS first (some 7 instructions a score per wave, where counting
 // and classifying all scores under a test takes 30); a list that comes out short of K or beyond its
 // room is not used.  Infinite scores rank like any others; where NaNs rank is unspecified, but the set has K tokens.
-template <int NT, int TPT, typename Load, typename Get, typename Opaque, typename ScoreAt, typename TakeOne>
+template <int NT, int TPT, typename Load, typename Get, typename Opaque, typename ScoreAt, typename Early, typename Ready,
+          typename TakeOne>
 __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Load&& load, Get&& get, Opaque&& opaque,
-                                             ScoreAt&& score_at, TakeOne&& take_one) {
+                                             ScoreAt&& score_at, Early&& early, Ready&& ready, TakeOne&& take_one) {
   const int t = threadIdx.x;
   constexpr int R = NT * kCalibPerThread, NP = kCalibPerThread / TPT;
   const bool resident = N <= R;
@@ -126,6 +141,7 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
     if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
     for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
   });
+  early();
   uint32_t klo = 0, khi = 0xffffffffu;
   int shift = 22, need = kk, n_cand;
   const int r = sample_rank(kk, N, SMP);
@@ -211,6 +227,7 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
       klo = 0; khi = 0xffffffffu; shift = 22;                      // the sample misled: the whole range
     }
   }
+  ready();
   const bool ranked = n_cand <= kSelCand;
   auto place = [&](uint32_t key, int n) {
     if (key > khi) take_one(n);
@@ -249,14 +266,15 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
   }
 }
 
-// One workgroup per row: bitmap[row][0 .. ceil(N / 32)) of the top-K set of S[row].
-template <int NT, int WORDS>
-__global__ __launch_bounds__(NT) void calib_topk_kernel(const float* __restrict__ S, uint32_t* __restrict__ bitmap,
-                                                        int N, int n_cap, int kk, int words) {
-  __shared__ CalibLds<NT> sm;
-  __shared__ uint32_t bits[WORDS];                            // WORDS * 32 tokens at most
-  const int row = blockIdx.x, t = threadIdx.x;
+// The full head's top-K set, by one workgroup of calib_fc_kernel's launch per row, which then counts for the FCs that came first (a
+// wave each).
+template <int NT>
+__device__ __forceinline__ void calib_top(CalibLds<NT>& sm, uint32_t* bits, const float* __restrict__ S, const CalibSets& sets,
+                                          float* CA_sum, int row, int N, int n_cap, int kk) {
+  constexpr int F = kHeadDim / 2;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, words = sets.words;
   const float* s = S + (size_t)row * n_cap;
+  __builtin_amdgcn_s_setprio(3);                              // (64 workgroups may end up waiting to be counted)
   for (int i = t; i < words; i += NT) bits[i] = 0;
   float4 w[kCalibPerThread / 4];
   calib_select<NT, 4>(
@@ -273,23 +291,47 @@ __global__ __launch_bounds__(NT) void calib_topk_kernel(const float* __restrict_
         x[0] = full || n < N ? w[i].x : NAN; x[1] = full || n + 1 < N ? w[i].y : NAN;
         x[2] = full || n + 2 < N ? w[i].z : NAN; x[3] = full || n + 3 < N ? w[i].w : NAN;
       },
-      []() {}, [&](int n) { return s[n]; }, [&](int n) { atomicOr(&bits[n >> 5], 1u << (n & 31)); });
+      []() {}, [&](int n) { return s[n]; }, []() {}, []() {}, [&](int n) { set_bit(bits, (uint32_t)n); });
   __syncthreads();
-  for (int i = t; i < words; i += NT) bitmap[(size_t)row * words + i] = bits[i];
+  for (int i = t; i < words; i += NT) st_agent(sets.full + (size_t)row * words + i, bits[i] | kCalibThere);
+  publish_barrier();
+  if (t < F) sm.early[t] = atomicExch(&sets.state[row * F + t], 2u);
+  __syncthreads();
+  for (int f = wave; f < F; f += NT / kWave) {
+    if (sm.early[f] != 1u) continue;
+    const uint32_t* p = sets.fc + ((size_t)row * F + f) * words;
+    uint32_t sum = 0;
+#pragma unroll 8
+    for (int i = lane; i < words; i += kWave) sum += (uint32_t)__popc(ld_agent(p + i) & bits[i]);
+    sum = wave_prefix_sum(sum);
+    if (lane == kWave - 1) CA_sum[row * F + f] += (float)sum / (float)kk;
+  }
 }
 
-// One workgroup per (row, FC): CA_sum[row][i] += |top-K of FC i's scores & the row's bitmap| / K.
+// One workgroup per (row, FC): CA_sum[row][i] += |top-K of FC i's scores & the full head's| / K.  The first `rows` workgroups find
+// the full head's set meanwhile, which an FC needs at its end only.  Nobody waits: an FC that finds the set there when it starts
+// (a later round of workgroups) tests its tokens against it; one that does not makes its own set and compares the two at
+// its end; if the other is not there even then it leaves its own in memory, says so in its state word, and whoever of the
+// two comes second to that word counts.
+// us, with launches for the full head's set (the better of one or several workgroups a row) / like this: 8 rows of 32768, K = 2048:
+// 46.8 / 42.8, of 8192, 512: 26.9 / 21.6; 64 rows of 4096: 54.0 / 50.7; 1 row of 20000: 28.5 / 21.8; 2 of 100000: 108 / 77.  With
+// several workgroups a row here: 8 rows of 32768: 46.3, of 8192: 21.0 - they take the places of FCs where the chip is full.
 template <typename ET, int NT, int WORDS, int PAIR_SHIFT, int PAIR_ADD>
-__global__ __launch_bounds__(NT) void calib_fc_kernel(const ET* __restrict__ q, const ET* __restrict__ Kp,
-                                                      const uint32_t* __restrict__ bitmap, float* __restrict__ CA_sum,
-                                                      int Hq, int Hkv, int N, int n_cap, int kk, int words) {
-  constexpr int D = kHeadDim, F = D / 2;
+__global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCalibWords1 ? 8 : 4) void calib_fc_kernel(
+    const ET* __restrict__ q, const ET* __restrict__ Kp, const float* __restrict__ S, CalibSets sets, float* __restrict__ CA_sum,
+    int rows, int Hq, int Hkv, int N, int n_cap, int kk) {
+  constexpr int D = kHeadDim, F = D / 2, WPT = (WORDS + NT - 1) / NT;
   constexpr int TPT = ScoreTraits<ET>::TPT;
   __shared__ CalibLds<NT> sm;
-  __shared__ uint32_t bits[WORDS];                            // WORDS * 32 tokens at most
-  const int row = blockIdx.x / F, f = blockIdx.x % F, t = threadIdx.x;
+  __shared__ uint32_t bits[WORDS];
+  if ((int)blockIdx.x < rows) {
+    calib_top<NT>(sm, bits, S, sets, CA_sum, (int)blockIdx.x, N, n_cap, kk);
+    return;
+  }
+  const int id = (int)blockIdx.x - rows, words = sets.words;
+  const int row = id / F, f = id % F, t = threadIdx.x;
   const int G = Hq / Hkv;
-  if (t == 0) sm.count = 0;
+  if (t == 0) { sm.count = 0; sm.missing = 0; }
   const ET* qh = q + ((size_t)(row / Hkv) * Hq + (size_t)(row % Hkv) * G) * D + (f << PAIR_SHIFT);
   float qlo = 0.f, qhi = 0.f;
   {
@@ -308,8 +350,16 @@ __global__ __launch_bounds__(NT) void calib_fc_kernel(const ET* __restrict__ q, 
       qhi += g < G ? y : 0.f;
     }
   }
-  const ET* p = Kp + (size_t)blockIdx.x * n_cap * 2;
-  for (int i = t; i < words; i += NT) bits[i] = bitmap[(size_t)row * words + i];
+  const ET* p = Kp + (size_t)id * n_cap * 2;
+  const uint32_t* full = sets.full + (size_t)row * words;
+  uint32_t there = kCalibThere;
+#pragma unroll
+  for (int j = 0; j < WPT; ++j) {
+    const int i = min(j * NT + t, words - 1);
+    const uint32_t x = ld_agent(full + i);
+    bits[i] = x;
+    there &= x;
+  }
   uint4 w[kCalibPerThread / TPT];
   auto load = [&](int c0) {
 #pragma unroll
@@ -342,11 +392,47 @@ __global__ __launch_bounds__(NT) void calib_fc_kernel(const ET* __restrict__ q, 
     return fmaf(qhi, hi, fmaf(qlo, lo, 0.f));
   };
   uint32_t mine = 0;
-  calib_select<NT, TPT>(sm, N, kk, load, get, opaque, score_at, [&](int n) { mine += (bits[n >> 5] >> (n & 31)) & 1u; });
+  bool have = true;
+  calib_select<NT, TPT>(
+      sm, N, kk, load, get, opaque, score_at, [&]() { if (there == 0) sm.missing = 1; },
+      [&]() {
+        have = sm.missing == 0;
+        if (have) return;
+        for (int i = t; i < words; i += NT) bits[i] = 0;
+        __syncthreads();
+      },
+      [&](int n) {
+        if (have) mine += (bits[(uint32_t)n / 31u] >> ((uint32_t)n % 31u)) & 1u;
+        else set_bit(bits, (uint32_t)n);
+      });
+  if (!have) {
+    auto meet = [&]() {
+      there = kCalibThere;
+      mine = 0;
+      for (int i = t; i < words; i += NT) {
+        const uint32_t x = ld_agent(full + i);
+        there &= x;
+        mine += (uint32_t)__popc(x & bits[i]);
+      }
+    };
+    if (t == 0) sm.missing = 0;
+    __syncthreads();
+    meet();
+    if (there == 0) sm.missing = 1;
+    __syncthreads();
+    if (sm.missing) {
+      for (int i = t; i < words; i += NT) st_agent(sets.fc + (size_t)id * words + i, bits[i]);
+      publish_barrier();
+      if (t == 0) sm.missing = atomicExch(&sets.state[id], 1u);
+      __syncthreads();
+      if (sm.missing != 2u) return;                           // (counted by whoever publishes the full head's)
+      meet();
+    }
+  }
   mine = wave_prefix_sum(mine);
   if (lane_id() == kWave - 1) atomicAdd(&sm.count, mine);
   __syncthreads();
-  if (t == 0) CA_sum[blockIdx.x] += (float)sm.count / (float)kk;
+  if (t == 0) CA_sum[id] += (float)sm.count / (float)kk;
 }
 
 // K >= N: both sets are all tokens
@@ -356,42 +442,37 @@ __global__ __launch_bounds__(256) void calib_all_kernel(float* __restrict__ CA_s
 }
 
 template <typename ET, int PS, int PA>
-static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap,
-                                 uint2* list, uint32_t* cnt, uint32_t* tickets, float* CA_sum, hipStream_t st) {
-  const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2, words = (s.n_ctx + 31) / 32;
+static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, const CalibSets& sets,
+                                 float* CA_sum, hipStream_t st) {
+  const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2;
   const int per = 256 * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per - 1) / per;
   hipError_t e = launch("fasa_calib_full", calib_full_kernel<ET, PS, PA>, dim3(rows * nslices), dim3(256), st, (const ET*)q,
-                        (const ET*)Kp_all, S, tickets, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap);
+                        (const ET*)Kp_all, S, sets, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap);
   if (e != hipSuccess) return e;
   const auto stage = [&](auto nt_c, auto words_c) {
     constexpr int NT = decltype(nt_c)::value, WORDS = decltype(words_c)::value;
-    const TopkPlan tp = plan_topk(s.n_ctx, kk);
-    hipError_t err = tp.ept ? launch_topk(tp, rows, s.n_ctx, s.n_cap, kk, S, nullptr, bitmap, list, cnt, kListMaxSegs, tickets,
-                                          kCalibTicketStride, st)
-                     : launch("fasa_calib_topk", calib_topk_kernel<NT, WORDS>, dim3(rows), dim3(NT), st, S, bitmap, s.n_ctx,
-                            s.n_cap, kk, words);
-    if (err != hipSuccess) return err;
-    return launch("fasa_calib_fc", calib_fc_kernel<ET, NT, WORDS, PS, PA>, dim3(rows * half), dim3(NT), st, (const ET*)q,
-                  (const ET*)Kp_all, bitmap, CA_sum, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap, kk, words);
+    return launch("fasa_calib_fc", calib_fc_kernel<ET, NT, WORDS, PS, PA>, dim3(rows * (1 + half)), dim3(NT), st, (const ET*)q,
+                  (const ET*)Kp_all, S, sets, CA_sum, rows, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap, kk);
   };
   // rows that fit in the registers of 256 threads: several workgroups per compute unit instead of one of
-  // 1024 each; rows that fit in those of 1024: a bitmap small enough for two
-  if (s.n_ctx <= 8192) return stage(std::integral_constant<int, 256>{}, std::integral_constant<int, 256>{});
-  if (s.n_ctx <= 32768) return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, 1024>{});
-  return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, kCalibMaxCtx / 32>{});
+  // 1024 each; rows that fit in those of 1024: a set small enough for two
+  if (s.n_ctx <= 8192) return stage(std::integral_constant<int, 256>{}, std::integral_constant<int, kCalibWords0>{});
+  if (s.n_ctx <= 32768) return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, kCalibWords1>{});
+  return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, (kCalibMaxCtx + 30) / 31>{});
 }
 
-// list [rows][n_cap], cnt [rows][kListMaxSegs], tickets [rows][kCalibTicketStride]
 size_t calib_scratch_bytes(int rows, int n_cap) {
-  return (size_t)rows * ((size_t)n_cap * sizeof(uint2) + (kListMaxSegs + kCalibTicketStride) * sizeof(uint32_t));
+  return (size_t)rows * (kHeadDim / 2 + (1 + kHeadDim / 2) * (((size_t)n_cap + 30) / 31)) * sizeof(uint32_t);
 }
 
-hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap, void* scratch,
-                        float* CA_sum, hipStream_t st) {
+hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, void* scratch, float* CA_sum,
+                        hipStream_t st) {
   const size_t rows = (size_t)s.batch * s.n_kv_heads;
-  uint2* list = (uint2*)scratch;
-  uint32_t* cnt = (uint32_t*)(list + rows * s.n_cap);
-  uint32_t* tickets = cnt + rows * kListMaxSegs;
+  CalibSets sets;
+  sets.words = (s.n_ctx + 30) / 31;
+  sets.state = (uint32_t*)scratch;
+  sets.full = sets.state + rows * (kHeadDim / 2);
+  sets.fc = sets.full + rows * sets.words;
   constexpr int D = kHeadDim;
   if (kk >= s.n_ctx) {
     const int n = s.batch * s.n_kv_heads * (D / 2);
@@ -399,10 +480,10 @@ hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, 
   }
   const bool inter = s.pairing == FASA_PAIR_INTERLEAVED;   // FC i: dims (2i, 2i + 1), else (i, i + d/2)
   if (s.dtype == FASA_BF16)
-    return inter ? launch_calib_p<uint16_t, 1, 1>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st)
-                 : launch_calib_p<uint16_t, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st);
-  return inter ? launch_calib_p<float, 1, 1>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st)
-               : launch_calib_p<float, 0, D / 2>(s, q, Kp_all, kk, S, bitmap, list, cnt, tickets, CA_sum, st);
+    return inter ? launch_calib_p<uint16_t, 1, 1>(s, q, Kp_all, kk, S, sets, CA_sum, st)
+                 : launch_calib_p<uint16_t, 0, D / 2>(s, q, Kp_all, kk, S, sets, CA_sum, st);
+  return inter ? launch_calib_p<float, 1, 1>(s, q, Kp_all, kk, S, sets, CA_sum, st)
+               : launch_calib_p<float, 0, D / 2>(s, q, Kp_all, kk, S, sets, CA_sum, st);
 }
 
 int calib_max_ctx() { return kCalibMaxCtx; }

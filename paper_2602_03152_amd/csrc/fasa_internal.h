@@ -189,14 +189,13 @@ hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const
                              const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap);
 // zeroes the histogram and the row counters (workspace initialisation)
 hipError_t launch_ws_clear(const fasa_shape& s, uint32_t* hist, RowCtl* ctl, hipStream_t st);
-// TopK-I of given scores in one launch (topk.hip): the set of every row to T, or as a bitmap of ceil(n_ctx / 32) words
-// (up to 262144 tokens).  ept == 0: not for this shape.  list [row][n_cap], cnt [row][cnt_pitch]; tickets [row * ticket_stride], zero.
+// TopK-I of given scores in one launch (topk.hip): the set of every row to T.  ept == 0: not for this shape.  list [row][n_cap], cnt [row][cnt_pitch]; tickets [row * ticket_stride], zero.
 struct TopkPlan {
   int ept, lanes;
 };
 TopkPlan plan_topk(int n_ctx, int bsel);
-hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint32_t* bitmap,
-                       uint2* list, uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st);
+hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint2* list,
+                       uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st);
 hipError_t launch_hist(const fasa_shape& s, const float* S, uint32_t* hist, hipStream_t st);
 // Tslot (paged caches only, else null): receives the pool slot of every entry of T, same layout
 hipError_t launch_select(const fasa_shape& s, const float* S, const uint32_t* hist, RowCtl* ctl,
@@ -253,10 +252,10 @@ hipError_t launch_offload_attend(const fasa_shape& s, int max_splits, const void
                                  RowCtl* ctl, float* part_acc, float* part_ml, hipStream_t st);
 
 // offline calibration (calib.hip)
-// S: rows * n_cap floats, bitmap: rows * ceil(n_ctx / 32) words, scratch: calib_scratch_bytes()
+// S: rows * n_cap floats, scratch: calib_scratch_bytes()
 size_t calib_scratch_bytes(int rows, int n_cap);
-hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, uint32_t* bitmap, void* scratch,
-                        float* CA_sum, hipStream_t st);
+hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, void* scratch, float* CA_sum,
+                        hipStream_t st);
 int calib_max_ctx();
 
 }  // namespace fasa

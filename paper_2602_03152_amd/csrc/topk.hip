@@ -199,8 +199,6 @@ __global__ __launch_bounds__(256) void select_all_kernel(int32_t* __restrict__ T
 // ---------------------------------------------------------------------------------------------
 constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT, kTopkSample = 256;
 
-// WORDS: words of the bitmap that takes the set (then written to memory), 0: tokens go to T.
-template <int WORDS>
 struct TopkLds {
   static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave;
   __align__(16) float sample[kTopkSample];
@@ -213,32 +211,21 @@ struct TopkLds {
   uint32_t ticket;
   float2 cut_top;
   int32_t* out;
-  uint32_t bits[WORDS ? WORDS : 1];
-  __device__ __forceinline__ void put(int place, uint32_t tok) {
-    if constexpr (WORDS != 0) atomicOr(&bits[tok >> 5], 1u << (tok & 31u));
-    else out[place] = (int32_t)tok;
-  }
+  __device__ __forceinline__ void put(int place, uint32_t tok) { out[place] = (int32_t)tok; }
 };
 
-template <int WORDS>
-__device__ __forceinline__ void topk_bits_out(const TopkLds<WORDS>& sm, uint32_t* bitmap, int row, int words) {
-  __syncthreads();
-  for (int i = threadIdx.x; i < words; i += kTopkNT) bitmap[(size_t)row * words + i] = sm.bits[i];
-}
-
-template <int EPT, int WORDS, bool ONE>
-__global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int32_t* __restrict__ T,
-                                                       uint32_t* __restrict__ bitmap, uint2* list, uint32_t* cnt, int cnt_pitch,
-                                                       uint32_t* tickets, int ticket_stride, int rows, int nsegs, int N, int n_cap,
-                                                       int bsel, int words, int lanes, uint32_t magic) {
-  __shared__ TopkLds<WORDS> sm;
+template <int EPT, bool ONE>
+__global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int32_t* __restrict__ T, uint2* list, uint32_t* cnt,
+                                                       int cnt_pitch, uint32_t* tickets, int ticket_stride, int rows, int nsegs,
+                                                       int N, int n_cap, int bsel, int lanes, uint32_t magic) {
+  __shared__ TopkLds sm;
   int row, seg;
   row_slice_of_block(rows, nsegs, row, seg);
   const int t = threadIdx.x;
   const float* srow = S + (size_t)row * n_cap;
+  const int n0 = seg * kTopkSeg + 4 * t;
   // one score out of each of 256 equal stretches, at uneven places: a mask of every second token must not hide from it
   if (t < kTopkSample) sm.sample[t] = srow[(int)((((unsigned long long)t << 16 | (t * 40503u & 0xffffu)) * (unsigned)N) >> 24)];
-  const int n0 = seg * kTopkSeg + 4 * t;
   const float4 x = *reinterpret_cast<const float4*>(srow + (n0 < N ? n0 : 0));   // (S is n_cap long, a multiple of 64)
   __syncthreads();
   if (t < kWave) {
@@ -261,7 +248,6 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
       sm.thr[2] = 0;
       sm.out = T + (size_t)row * bsel;
     }
-    for (int i = t; i < words && WORDS != 0; i += kTopkNT) sm.bits[i] = 0;
     __syncthreads();
     uint32_t total = 0;
 #pragma unroll
@@ -277,7 +263,6 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
     if (!select_entries<4>(sm, key, tok, false, [](auto&&) {}, max(kcut, 1u), kcut ? first_shift(kcut, score_key(top)) : 22, bsel, srow,
                            N, 0, bsel))
       row_select<false>(sm, bsel, srow, N, 0, bsel);           // (NaNs that have the key of nothing)
-    if constexpr (WORDS != 0) topk_bits_out(sm, bitmap, row, words);
     return;
   }
   __syncthreads();
@@ -290,12 +275,8 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
     tickets[(size_t)row * ticket_stride] = 0;                  // clean for the next call
     sm.out = T + (size_t)row * bsel;
   }
-  if constexpr (WORDS != 0) {
-    for (int i = t; i < words; i += kTopkNT) sm.bits[i] = 0;
-  }
   const ListView v = {lrow, nsegs, kTopkSeg, lanes, magic, n_cap, N};
   select_listed<true, EPT>(sm, v, crow, score_key(cut), score_key(top), bsel, srow, N, 0, bsel);
-  if constexpr (WORDS != 0) topk_bits_out(sm, bitmap, row, words);
 }
 
 // us, histogram and selection launch / like this: 8 rows of 8192, B = 500: 11.3 / 6.8, 16 of 20011, 1250: 12.4 / 8.6, 8 of 32768,
@@ -307,25 +288,13 @@ TopkPlan plan_topk(int n_ctx, int bsel) {
   return TopkPlan{need == 0 ? 0 : need <= 4 ? 4 : need <= 8 ? 8 : 16, lanes};
 }
 
-template <int WORDS>
-static hipError_t launch_topk_w(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T,
-                                uint32_t* bitmap, uint2* list, uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride,
-                                hipStream_t st) {
+hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint2* list,
+                       uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st) {
   const int nsegs = (n_ctx + kTopkSeg - 1) / kTopkSeg;
-  auto kernel = nsegs == 1 ? topk_kernel<4, WORDS, true> : p.ept == 4 ? topk_kernel<4, WORDS, false>
-                : p.ept == 8 ? topk_kernel<8, WORDS, false> : topk_kernel<16, WORDS, false>;
-  return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, T, bitmap, list, cnt, cnt_pitch, tickets,
-                ticket_stride, rows, nsegs, n_ctx, n_cap, bsel, (n_ctx + 31) / 32, p.lanes,
-                (uint32_t)((1ull << 32) / (unsigned)p.lanes) + 1u);
-}
-hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint32_t* bitmap,
-                       uint2* list, uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st) {
-  if (!bitmap) return launch_topk_w<0>(p, rows, n_ctx, n_cap, bsel, S, T, bitmap, list, cnt, cnt_pitch, tickets, ticket_stride, st);
-  if (n_ctx <= 32768)
-    return launch_topk_w<1024>(p, rows, n_ctx, n_cap, bsel, S, T, bitmap, list, cnt, cnt_pitch, tickets, ticket_stride, st);
-  if (n_ctx <= 262144)
-    return launch_topk_w<8192>(p, rows, n_ctx, n_cap, bsel, S, T, bitmap, list, cnt, cnt_pitch, tickets, ticket_stride, st);
-  return hipErrorInvalidValue;
+  auto kernel = nsegs == 1 ? topk_kernel<4, true> : p.ept == 4 ? topk_kernel<4, false>
+                : p.ept == 8 ? topk_kernel<8, false> : topk_kernel<16, false>;
+  return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, T, list, cnt, cnt_pitch, tickets, ticket_stride, rows,
+                nsegs, n_ctx, n_cap, bsel, p.lanes, (uint32_t)((1ull << 32) / (unsigned)p.lanes) + 1u);
 }
 
 // zeroes the histogram and the row counters: 1-D grid, one uint4 per thread
