@@ -148,10 +148,12 @@ int fasa_dense_attend(const fasa_shape* shape, const void* q, const void* K, con
  *   (T the same set, ties towards the lower index; O up to the order of float32 additions).
  * S and T are outputs the caller may inspect (S doubles as the score scratch).
  * How it runs, by the shape: short rows with small budgets take one launch, in which the workgroup that
- * finishes a row's scores selects and attends; many rows take a scoring launch and one workgroup per row behind
- * it; everything else a scoring launch that also counts a histogram of the scores, then one kernel in which every
- * workgroup classifies a range of tokens against the B-th score's bin and attends at once over the winners it
- * owns, the row's last workgroup settling the ties of that bin and merging the partial results.  Rows longer
+ * finishes a row's scores selects and attends; other bf16 shapes a scoring launch that also lists the scores that
+ * can be among a row's best, then one kernel whose workgroups select out of the lists and attend over equal
+ * shares of the set; many float32 rows a scoring launch and one workgroup per row behind it; the rest a scoring
+ * launch that also counts a histogram of the scores, then one kernel in which every workgroup classifies a range of
+ * tokens against the B-th score's bin and attends at once over the winners it owns, the row's last workgroup
+ * settling the ties of that bin and merging the partial results.  Rows longer
  * than 2^20 tokens, budget >= n_ctx, and float32 caches with one or two query heads per KV head and more
  * than an eighth of the tokens selected run the three stand-alone kernels back to back. */
 int fasa_decode_step(const fasa_shape* shape, const void* q, void* K, void* V, void* Kp,

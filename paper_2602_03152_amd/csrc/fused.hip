@@ -24,6 +24,9 @@
 //        into one more partial.  Rows with more candidates (degenerate score distributions) resolve by
 //        counting or by the radix resolve and gather the taken rows themselves;
 //     6. merges all partials into O and leaves histogram and counters zeroed for the next call.
+//
+// It takes float32 steps between one launch and the row form, and the bf16 steps whose lists of large scores are too long
+// for list_kernel (plan_list).
 #include "mfma_tile.h"
 #include "select_common.h"
 

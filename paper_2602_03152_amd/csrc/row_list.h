@@ -1,5 +1,5 @@
 // Lists of the scores of a row that can be among its B best (paper Sec. 4.1, TopK-I), made by the workgroups that
-// score it: what TopK-I has to look at shrinks from N scores to one or two times B before the row is selected.
+// score it: what TopK-I has to look at shrinks from N scores to 1.6 to 4 times B before the row is selected.
 //
 //   cut      every workgroup of a row scores the same sample of the row's tokens and takes a score of it that a few
 //            more than B of the row's scores should reach (list_cut).  All arrive at the same bits.

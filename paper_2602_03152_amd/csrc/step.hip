@@ -649,11 +649,7 @@ static bool row_form(const fasa_shape& s, long long rows, int bsel) {
   // 79.4 / 99.0; 40 rows of 100000, B = 512: 79 / 153
   const float r = (float)sample_rank(bsel, s.n_ctx);
   if ((r + 4.f * sqrtf(r)) * (float)n > (float)(kSample * kListPerThread * kRowNT)) return false;
-  // us (fused.hip / row form), bf16.  N = 5000 .. 8192, B = 64 .. 300: 96 rows 19.7 / 19.7, 22.4 / 21.2, 160: 26.5 / 25.4,
-  // 512: 71.0 / 67.6, but of 4096: 54.7 / 59.3.  N = 8192, B = 256: 64 rows 21.9 / 23.6, 72: 24.7 / 24.8, 80: 25.7 / 25.2;
-  // B = 512: 80 rows 28.0 / 28.9, 128: 35.2 / 34.8; B = 1024: 128 rows 42.0 / 43.0, 256: 70.1 / 63.1.  N = 16384, B = 512: 64
-  // rows 31.1 / 32.1, 72: 34.3 / 34.0, 96: 40.8 / 39.2, 128: 48.9 / 46.0; B = 1024: 80 rows 40.9 / 42.9, 128: 55.6 / 54.0.
-  // N = 32768, B = 512: 64 rows 45.9 / 45.4, 72: 54.7 / 49.1, 128: 83.3 / 71.5; 56 rows of 40000: 51.8 / 48.6
+  // bf16: list_kernel runs these shapes and others alike; the line only says which of its launches are recorded as "fasa_row".
   const bool few = bsel * 2048ll <= cells;
   if (s.dtype == FASA_BF16) return n >= 5120 && few;
   // float32, 1 head.  N = 4096, B = 64: 64 rows 20.5 / 20.8, 80: 23.5 / 22.6; B = 512: 128 rows 40.3 / 41.7; 1024 rows, B = 200:
@@ -675,7 +671,7 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
                                   : (long long)s.n_ctx * s.kv_stride_n;
   if ((most >> 3) >= 0xfffffff0ll) return kStepNone;
   // Lines of the one-launch form, measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step as
-  // (fused.hip / one launch / row form).  One compute unit gathers about 50 KB per us, which is what ends its reach
+  // (fused.hip / one launch / row_kernel).  One compute unit gathers about 50 KB per us, which is what ends its reach
   // in B; reading a row's scores back is what ends it in N.
   const long long rows = (long long)s.batch * s.n_kv_heads;
   const int per = kStepNT * (s.dtype == FASA_BF16 ? 4 : 2);
