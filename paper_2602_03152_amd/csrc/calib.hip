@@ -13,6 +13,7 @@
 
 #include "fasa_device.h"
 #include "fasa_internal.h"
+#include "row_list.h"
 #include "score_common.h"
 #include "select_common.h"
 
@@ -98,69 +99,94 @@ __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict
   }
 }
 
-template <int NT>
+template <int NT, int WORDS>
 struct CalibLds {
   static constexpr int kThreads = NT;
-  static constexpr int kList = NT == 1024 ? 8192 : 4096;      // (two workgroups of 1024 share a compute unit's LDS)
+  // (two workgroups of 1024 share a compute unit's LDS, or one has it)
+  static constexpr int kList = NT != 1024 ? 4096 : WORDS <= kCalibWords1 ? 8192 : 13312;   // (8 rows of 131072, K = 4096: 212 -> 137 us)
   uint2 list[kList];                                          // scores at or above the cut: (score bits, token)
   uint32_t hist[kSelBins];
-  // The larger sample is for the larger rows: a list of 1.6 K .. 2.6 K entries, where 128 would scatter it so
-  // that a few rows in 512 overflowed.
-  static constexpr int kSmp = NT == 1024 ? 256 : 128;
+  // Places of the row that are sampled, the TPT consecutive tokens of one load each.  With 256 single tokens, ranked by counting,
+  // the list of K = 4096 of 32768 was 7000 entries long and one FC in twenty overflowed: 54.6 us, like this 45.6 (K = 2048: 42.9 / 42.7;
+  // 8 rows of 8192, 512, 128 single tokens: 22.2 / 20.8).
+  static constexpr int kSpots = NT == 1024 ? 256 : 64;
   union {                                                     // (the sample is spent before there are candidates)
     uint2 cand[kSelCand];
-    struct { uint32_t sample[kSmp], ssort[kSmp]; };
+    struct { __align__(16) float sample[4 * kSpots]; __align__(16) uint32_t bins[256]; };
   };
+  float2 cut_top;
   uint32_t wtot[NT / kWave];
   uint32_t thr[4];
   uint32_t n_list, n_cnd, count, missing;
   uint32_t early[kHeadDim / 2];
 };
 
-// Top-K of a row by one workgroup of NT threads, which hold a stretch of it as loaded: load(c0) requests what the
+// Top-K of a row by one workgroup of NT threads, which hold a stretch of it as loaded: load1(i, c0) requests piece i of what the
 // scores of tokens c0 .. c0 + NT * kCalibPerThread - 1 are made of (kCalibPerThread / TPT pieces a thread),
 // get(c0, i, t, x, full) makes those of tokens c0 + (i * NT + t) * TPT + k, a NaN beyond the row unless it is said to
 // be full (cheap: made again in every pass, which keeps 16 registers free and two workgroups of 1024 on a
 // compute unit); opaque() hides the pieces from the compiler, which would otherwise keep the scores.
-// score_at(n): one token's score.  take_one(n): token n is in the set; early() and ready() run before it, with a barrier of the
+// sample(n) requests the TPT tokens from n on, scores_of() makes their scores.  score_at(n): one token's score.  take_one(n): token n is in the set; early() and ready() run before it, with a barrier of the
 // workgroup between them.
 // What reaches the cut is gathered into a list in LDS first (some 7 instructions a score per wave, where counting
 // and classifying all scores under a test takes 30); a list that comes out short of K or beyond its
 // room is not used.  Infinite scores rank like any others; where NaNs rank is unspecified, but the set has K tokens.
-template <int NT, int TPT, typename Load, typename Get, typename Opaque, typename ScoreAt, typename Early, typename Ready,
-          typename TakeOne>
-__device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Load&& load, Get&& get, Opaque&& opaque,
-                                             ScoreAt&& score_at, Early&& early, Ready&& ready, TakeOne&& take_one) {
+template <int NT, int WORDS, int TPT, typename Load1, typename Get, typename Opaque, typename Sample, typename ScoresOf, typename ScoreAt,
+          typename Early, typename Ready, typename TakeOne>
+__device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int kk, Load1&& load1, Get&& get,
+                                             Opaque&& opaque, Sample&& sample, ScoresOf&& scores_of, ScoreAt&& score_at,
+                                             Early&& early, Ready&& ready, TakeOne&& take_one) {
   const int t = threadIdx.x;
   constexpr int R = NT * kCalibPerThread, NP = kCalibPerThread / TPT;
+  auto load = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) load1(i, c0);
+  };
   const bool resident = N <= R;
-  constexpr int SMP = CalibLds<NT>::kSmp;
-  const float sval = score_at((int)(((long long)(t & (SMP - 1)) * N) / SMP));
-  if (resident) load(0);
-  rank_sample<NT, SMP>(sval, sm.sample, sm.ssort, [&]() {
-    if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
-    for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  });
+  constexpr int SP = CalibLds<NT, WORDS>::kSpots, SMP = SP * TPT;
+  float sx[TPT];
+  const int n_spot = (int)(((long long)(t & (SP - 1)) * N) / SP) & ~(TPT - 1);
+  auto spot = sample(n_spot);                                 // (requested ahead of the stretch)
+  load(0);
+  if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
+  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+  scores_of(spot, sx);
+  if (t < SP) {
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) sm.sample[k * SP + t] = n_spot + k < N ? sx[k] : sx[0];
+  }
+  __syncthreads();
+  if (t < kWave) {
+    float x[SMP / kWave], top = 0.f, cut = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < SMP / kWave; ++k) x[k] = sm.sample[k * kWave + t];
+    // neighbours may be alike: a wider margin than independent ones would need
+    const float ps = (float)kk * ((float)SMP / (float)N);
+    const int r = (int)(ps + 5.0f * sqrtf(ps) + 3.0f);
+    if (r <= SMP) cut = list_cut(x, r, sm.bins, top);
+    if (t == 0) sm.cut_top = make_float2(cut, top);
+  }
+  __syncthreads();
+  const float flo = sm.cut_top.x;
   early();
   uint32_t klo = 0, khi = 0xffffffffu;
   int shift = 22, need = kk, n_cand;
-  const int r = sample_rank(kk, N, SMP);
-  if (r <= SMP) {
-    klo = sm.ssort[r - 1];
-    shift = first_shift(klo, sm.ssort[0]);
+  if (flo > -INFINITY) {
+    klo = score_key(flo);
+    shift = first_shift(klo, score_key(sm.cut_top.y));
   }
   {
-    const float flo = klo ? key_score(klo) : -INFINITY;
     const int lane = lane_id();
     // One addition to the list's length per wave and piece: its latency hides behind the other waves, where
     // counting first would make every score twice.
-    auto append = [&](int c0, auto full) {
+    auto append = [&](int c0, auto full, auto more) {
       int tt = t;
       asm volatile("" : "+v"(tt));                            // (token numbers made anew, not kept)
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
         float x[TPT];
         get(c0, i, tt, x, full);
+        if constexpr (more) load1(i, c0 + R);                 // a piece of the next stretch where this one's has been used
         unsigned long long m[TPT];
         uint32_t cnt = 0;                                     // of the wave
 #pragma unroll
@@ -174,25 +200,23 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
 #pragma unroll
         for (int k = 0; k < TPT; ++k) {
           const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
-          if (x[k] >= flo && pos < (uint32_t)CalibLds<NT>::kList)
+          if (x[k] >= flo && pos < (uint32_t)CalibLds<NT, WORDS>::kList)
             sm.list[pos] = make_uint2(__float_as_uint(x[k]), (uint32_t)(c0 + (i * NT + tt) * TPT + k));
           base += (uint32_t)__popcll(m[k]);
         }
         __builtin_amdgcn_sched_barrier(0);                    // (piece by piece: registers)
       }
     };
-    for (int c0 = 0; c0 < N; c0 += R) {
-      if (!resident) load(c0);
-      if (c0 + R <= N) append(c0, std::true_type{});
-      else append(c0, std::false_type{});
-    }
+    int c0 = 0;
+    for (; c0 + R < N; c0 += R) append(c0, std::true_type{}, std::true_type{});
+    if (c0 + R == N) append(c0, std::true_type{}, std::false_type{});
+    else append(c0, std::false_type{}, std::false_type{});
     __syncthreads();
   }
   const int M = (int)sm.n_list;
-  const bool listed = M >= kk && M <= CalibLds<NT>::kList;
-  // Without a list: all scores of the row, told from what lies beyond it by index.  As keys throughout: the key of
-  // a cut may be one that no score has (the sample's keys lost their low bits: below that of -inf lie those of
-  // NaNs), and a NaN score has a place in the order of keys like any other.
+  const bool listed = M >= kk && M <= CalibLds<NT, WORDS>::kList;
+  // Without a list: all scores of the row, told from what lies beyond it by index.  As keys throughout: a NaN score has
+  // a place in the order of keys like any other.
   auto for_scores = [&](int c0, auto&& f) {
     int tt = t;
     asm volatile("" : "+v"(tt));
@@ -268,8 +292,8 @@ __device__ __forceinline__ void calib_select(CalibLds<NT>& sm, int N, int kk, Lo
 
 // The full head's top-K set, by one workgroup of calib_fc_kernel's launch per row, which then counts for the FCs that came first (a
 // wave each).
-template <int NT>
-__device__ __forceinline__ void calib_top(CalibLds<NT>& sm, uint32_t* bits, const float* __restrict__ S, const CalibSets& sets,
+template <int NT, int WORDS>
+__device__ __forceinline__ void calib_top(CalibLds<NT, WORDS>& sm, uint32_t* bits, const float* __restrict__ S, const CalibSets& sets,
                                           float* CA_sum, int row, int N, int n_cap, int kk) {
   constexpr int F = kHeadDim / 2;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, words = sets.words;
@@ -277,21 +301,20 @@ __device__ __forceinline__ void calib_top(CalibLds<NT>& sm, uint32_t* bits, cons
   __builtin_amdgcn_s_setprio(3);                              // (64 workgroups may end up waiting to be counted)
   for (int i = t; i < words; i += NT) bits[i] = 0;
   float4 w[kCalibPerThread / 4];
-  calib_select<NT, 4>(
+  calib_select<NT, WORDS, 4>(
       sm, N, kk,
-      [&](int c0) {
-#pragma unroll
-        for (int i = 0; i < kCalibPerThread / 4; ++i) {
-          const int n = c0 + (i * NT + t) * 4;
-          w[i] = *reinterpret_cast<const float4*>(s + (n < N ? n : 0));
-        }
+      [&](int i, int c0) {
+        const int n = c0 + (i * NT + t) * 4;
+        w[i] = *reinterpret_cast<const float4*>(s + (n < N ? n : 0));
       },
       [&](int c0, int i, int tt, float (&x)[4], auto full) {
         const int n = c0 + (i * NT + tt) * 4;
         x[0] = full || n < N ? w[i].x : NAN; x[1] = full || n + 1 < N ? w[i].y : NAN;
         x[2] = full || n + 2 < N ? w[i].z : NAN; x[3] = full || n + 3 < N ? w[i].w : NAN;
       },
-      []() {}, [&](int n) { return s[n]; }, []() {}, []() {}, [&](int n) { set_bit(bits, (uint32_t)n); });
+      []() {}, [&](int n) { return *reinterpret_cast<const float4*>(s + n); },
+      [](const float4& v, float (&x)[4]) { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }, [&](int n) { return s[n]; }, []() {},
+      []() {}, [&](int n) { set_bit(bits, (uint32_t)n); });
   __syncthreads();
   for (int i = t; i < words; i += NT) st_agent(sets.full + (size_t)row * words + i, bits[i] | kCalibThere);
   publish_barrier();
@@ -322,10 +345,10 @@ __global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCali
     int rows, int Hq, int Hkv, int N, int n_cap, int kk) {
   constexpr int D = kHeadDim, F = D / 2, WPT = (WORDS + NT - 1) / NT;
   constexpr int TPT = ScoreTraits<ET>::TPT;
-  __shared__ CalibLds<NT> sm;
+  __shared__ CalibLds<NT, WORDS> sm;
   __shared__ uint32_t bits[WORDS];
   if ((int)blockIdx.x < rows) {
-    calib_top<NT>(sm, bits, S, sets, CA_sum, (int)blockIdx.x, N, n_cap, kk);
+    calib_top<NT, WORDS>(sm, bits, S, sets, CA_sum, (int)blockIdx.x, N, n_cap, kk);
     return;
   }
   const int id = (int)blockIdx.x - rows, words = sets.words;
@@ -361,12 +384,9 @@ __global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCali
     there &= x;
   }
   uint4 w[kCalibPerThread / TPT];
-  auto load = [&](int c0) {
-#pragma unroll
-    for (int i = 0; i < kCalibPerThread / TPT; ++i) {
-      const int n = c0 + (i * NT + t) * TPT;
-      w[i] = *reinterpret_cast<const uint4*>(p + (size_t)(n < N ? n : 0) * 2);
-    }
+  auto load1 = [&](int i, int c0) {
+    const int n = c0 + (i * NT + t) * TPT;
+    w[i] = *reinterpret_cast<const uint4*>(p + (size_t)(n < N ? n : 0) * 2);
   };
   auto get = [&](int c0, int i, int tt, float (&x)[TPT], auto full) {
     const int n = c0 + (i * NT + tt) * TPT;
@@ -393,8 +413,14 @@ __global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCali
   };
   uint32_t mine = 0;
   bool have = true;
-  calib_select<NT, TPT>(
-      sm, N, kk, load, get, opaque, score_at, [&]() { if (there == 0) sm.missing = 1; },
+  calib_select<NT, WORDS, TPT>(
+      sm, N, kk, load1, get, opaque, [&](int n) { return *reinterpret_cast<const uint4*>(p + (size_t)n * 2); },
+      [&](const uint4& v, float (&x)[TPT]) {
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) x[k] = 0.f;
+        fma_pairs<ET>(v, qlo, qhi, x);
+      },
+      score_at, [&]() { if (there == 0) sm.missing = 1; },
       [&]() {
         have = sm.missing == 0;
         if (have) return;

@@ -94,7 +94,7 @@ __device__ __forceinline__ void rank_sample(float sval, uint32_t* sample, uint32
   init();
   __syncthreads();
   constexpr int P = NT / SMP;                                 // threads per sample value: adjacent lanes
-  static_assert(P == 2 || P == 4 || P == 8, "a pair, a quad or half a row of lanes per value");
+  static_assert(P == 4 || P == 8, "a quad or half a row of lanes per value");
   const uint32_t me = sample[t / P];
   int rank = 0;
 #pragma unroll
@@ -103,7 +103,7 @@ __device__ __forceinline__ void rank_sample(float sval, uint32_t* sample, uint32
     rank += (o.x > me ? 1 : 0) + (o.y > me ? 1 : 0) + (o.z > me ? 1 : 0) + (o.w > me ? 1 : 0);
   }
   rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);                           // quad_perm [1,0,3,2]
-  if constexpr (P >= 4) rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);     // quad_perm [2,3,0,1]
+  rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);                           // quad_perm [2,3,0,1]
   if constexpr (P == 8) rank += __builtin_amdgcn_update_dpp(0, rank, 0x141, 0xF, 0xF, true);    // row_half_mirror
   if (t % P == 0) ssort[rank & (SMP - 1)] = me & ~(uint32_t)(SMP - 1);
   __syncthreads();
