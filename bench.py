@@ -42,26 +42,26 @@ LLC_BYTES = 256 << 20         # last-level (memory-side) cache the rotation has 
 # what the same counters read for a plain copy kernel of known size (see profiles/).  Keyed by
 # (workload config id, kernel name); bytes per launch.  None = not measured yet.
 MEASURED_TRAFFIC = {
-    "source_hash": "ca783c09964bbbb6",   # source_hash() of the kernels the counters were taken on
+    "source_hash": "8e677a8fa9d7f9c0",   # source_hash() of the kernels the counters were taken on
     # profiles/decode_step_tiny_1head_f32_n4096_hbm_counters.txt  (read + written)
-    (0, "fasa_dense_attend"): 4324091 + 39456,
-    (0, "fasa_step"): 869627 + 18080,
+    (0, "fasa_dense_attend"): 4316077 + 39456,
+    (0, "fasa_step"): 867608 + 18080,
     # profiles/decode_step_llama3_8b_layer_n32768_b2048_hbm_counters.txt  (read + written)
-    (1, "fasa_dense_attend"): 135474281 + 2162944,
-    (1, "fasa_score_hist"): 16889991 + 1323072,
-    (1, "fasa_select_attend"): 10492651 + 1277715,
+    (1, "fasa_dense_attend"): 134888776 + 1089792,
+    (1, "fasa_score_list"): 16891978 + 1327072,
+    (1, "fasa_select_attend"): 9752805 + 1155328,
     # profiles/decode_step_batch16_n16384_b256_hbm_counters.txt  (read + written)
-    (2, "fasa_dense_attend"): 1076126552 + 4558848,
-    (2, "fasa_row"): 25568615 + 393216,
-    (2, "fasa_score"): 134401652 + 8392239,
+    (2, "fasa_dense_attend"): 1074432304 + 1339392,
+    (2, "fasa_row"): 19285386 + 393216,
+    (2, "fasa_score_list"): 134740166 + 9463526,
     # profiles/decode_step_longcot_batch8_gqa7_n32768_hbm_counters.txt  (read + written)
-    (3, "fasa_dense_attend"): 538938146 + 3879936,
-    (3, "fasa_score_hist"): 67269035 + 5385955,
-    (3, "fasa_select_attend"): 108505577 + 5034115,
+    (3, "fasa_dense_attend"): 537976564 + 1997824,
+    (3, "fasa_score_list"): 67296065 + 6855218,
+    (3, "fasa_select_attend"): 106803075 + 2791424,
     # profiles/decode_step_verylong_n131072_f32fc_b1024_hbm_counters.txt  (read + written)
-    (4, "fasa_dense_attend"): 538079043 + 2162944,
-    (4, "fasa_score_hist"): 134378707 + 4985984,
-    (4, "fasa_select_attend"): 9934817 + 2300813,
+    (4, "fasa_dense_attend"): 537493940 + 1089792,
+    (4, "fasa_score_list"): 134384691 + 4521631,
+    (4, "fasa_select_attend"): 5638692 + 585984,
 }
 
 
