@@ -555,7 +555,6 @@ static hipError_t launch_attend_g(const fasa_shape& s, bool dense, const AttendP
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
   auto kernel = [&]() {
     if constexpr (sizeof(ET) == 4 && G <= 2) return dense ? attend_valu_kernel<G, true> : attend_valu_kernel<G, false>;
-    else if constexpr (sizeof(ET) == 2) return attend_kernel<ET, G, false>;      // (full KV: attend_wide_kernel)
     else return dense ? attend_kernel<ET, G, true> : attend_kernel<ET, G, false>;
   }();
   return launch(dense ? "fasa_dense_attend" : "fasa_sparse_attend", kernel, dim3(rows * p.n_splits), dim3(256), st,
@@ -593,7 +592,13 @@ hipError_t launch_attend(const fasa_shape& s, bool dense, const void* q, const v
   // A list is attended like full KV where that halves many partials, attend_kernel / so: 4 rows, B = 6219, 7 heads (97 splits):
   // 15.1 / 11.0 us; 1 row, 20000 (256): 17.3 / 14.7; 2 rows, 9000 (141): 17.4 / 13.5; 1 row, 3000 (47): 9.1 / 8.75; but 8 rows,
   // 2048 (32): 7.3 / 7.4; 24 rows, 1000 (16): 8.1 / 8.4; 2 rows, 333 (6): 5.9 / 6.7
-  if (s.dtype == FASA_BF16 && (dense || p.n_splits > 40))
+  // Short full KV has few partials to halve and no workgroups to share a compute unit with: up to 16 splits, while a
+  // workgroup has one for itself, attend_kernel is the faster one, attend_kernel / wide: 8 rows of 500 (8 splits):
+  // 5.75 / 6.28 us; of 1000 (16): 5.85 / 6.30; 16 rows of 700 (11): 5.86 / 6.37; 1 row of 700 (11): 5.76 / 5.93.  Beyond:
+  // 8 rows of 1500 (24), 7 heads: 7.20 / 7.29; of 2000 (32): 6.87 / 6.53; 32 rows of 1000 (16, 512 workgroups): 7.33 / 7.14;
+  // 32 rows of 600 (9, 288 workgroups), 8 heads: 8.33 / 6.70
+  const bool wide = dense ? p.n_splits > 16 || rows * p.n_splits > kAssumedCUs : p.n_splits > 40;
+  if (s.dtype == FASA_BF16 && wide)
     return launch_wide(s, dense, plan_attend_wide(rows, count), q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);
   return s.dtype == FASA_BF16
              ? launch_attend_t<uint16_t>(s, dense, p, q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm)
