@@ -409,7 +409,7 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
   if (t < D / 2) {
     const int dl = PAIRS ? fcl[t] & 255 : fcl[t];
     const int dh = PAIRS ? fcl[t] >> 8 : dl + PAIR_ADD;
-    qs[t] = t < F ? make_float2(qsum[dl], qsum[dh]) : make_float2(0.f, 0.f);
+    qs[t] = make_float2(qsum[dl], qsum[dh]);
     if constexpr (APPEND) {
       const ET lo = knew[dl], hi = knew[dh];
       if constexpr (sizeof(ET) == 2) kpair[t] = make_uint2((uint32_t)lo | ((uint32_t)hi << 16), 0u);
@@ -428,8 +428,10 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
   auto planes = [&](int f0, auto request) {
 #pragma unroll
     for (int u = 0; u < NW; ++u) {
-      const float2 qf = qs[f0 + u];
-      fma_pairs<ET>(w[u], qf.x, qf.y, acc);
+      if (NB || decltype(request)::value || f0 + u < F) {          // (a zero query would make a NaN of an infinite key)
+        const float2 qf = qs[f0 + u];
+        fma_pairs<ET>(w[u], qf.x, qf.y, acc);
+      }
       if constexpr (decltype(request)::value) w[u] = load(f0 + NW + u);
     }
   };

@@ -49,3 +49,28 @@ def test_infinite_scores_rank_in_every_form(fb, kw, n_pos, n_neg, equal):  # noq
     fb.fasa_topk(d.shape, d.S, d.T, d.ws, d.ws_bytes)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(np.sort(to_host(d.T), -1), want)
+
+
+@pytest.mark.parametrize("append", [False, True], ids=["", "append"])
+@pytest.mark.parametrize("n_fc", [4, 7, 12, 13, 20])
+@pytest.mark.parametrize("n_ctx", [2011, 9001], ids=["one_launch", "lists"])
+def test_infinite_keys_of_the_last_listed_pair(fb, n_ctx, n_fc, append):  # noqa: F811
+    """List lengths that are no multiple of the planes in flight: an infinite key makes an infinite score, and no NaN."""
+    from tests.gpu_util import to_host
+    w = W.WORKLOADS[1].scaled(n_ctx=n_ctx, budget=300, n_fc=n_fc)
+    x = W.make_inputs(w, n_cap=(n_ctx + 63) // 64 * 64)
+    rng = np.random.default_rng(n_fc)
+    one, neg, pos = W.to_storage(np.array([1.0, -np.inf, np.inf]), w.dtype)
+    odd = rng.permutation(n_ctx - 1)[:90]
+    for h in range(w.n_kv_heads):
+        dim = x["fc_idx"][h, n_fc - 1]
+        x["q"][:, h * w.group:(h + 1) * w.group, dim] = one
+        x["K"][:, h, odd[:40], dim] = pos
+        x["K"][:, h, odd[40:], dim] = neg
+    new = {k: x[k[0].upper()][:, :, n_ctx - 1].copy() for k in ("k_new", "v_new")} if append else {}
+    print("infinite keys", n_ctx, n_fc, append, flush=True)
+    d = run_step(fb, w, x, **new)
+    S = to_host(d.S)[:, :, :n_ctx]
+    assert np.isposinf(S[:, :, odd[:40]]).all() and np.isneginf(S[:, :, odd[40:]]).all()
+    assert not np.isnan(S).any()
+    np.testing.assert_array_equal(np.sort(to_host(d.T), -1), O.topk(S, w.budget, n_ctx))
