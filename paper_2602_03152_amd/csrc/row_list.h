@@ -1,14 +1,14 @@
 // Lists of the scores of a row that can be among its B best (paper Sec. 4.1, TopK-I), made by the workgroups that
-// score it: what TopK-I has to look at shrinks from N scores to 1.6 to 4 times B before the row is selected.
+// score it: what TopK-I has to look at shrinks from N scores to a few times B (list_rank) before the row is selected.
 //
 //   cut      every workgroup of a row scores the same sample of the row's tokens and takes a score of it that a few
 //            more than B of the row's scores should reach (list_cut).  All arrive at the same bits.
 //   list     a workgroup writes the scores of its segment of the row that reach the cut, as (key, token), to the
 //            segment's own stretch of the row's list, and their number (list_count, list_write): no position is shared, so there is no
 //            atomic, and a stretch has room for the whole segment.
-//   select   list_load, select_entries: whoever selects holds the entries in registers, as many of each segment as are likely;
-//            a segment that has more is read on from memory in every pass.  A list shorter than B, because the sample
-//            misled, or far too long is not used: row_select.
+//   select   list_load, select_listed: whoever selects holds the entries in registers, as many of each segment as are likely;
+//            what a segment has beyond, where a row's best lie together, goes through LDS.  A list shorter than B,
+//            because the sample misled, or far too long is not used: row_select.
 // What the scores look like costs time, never exactness.
 #pragma once
 
@@ -35,19 +35,36 @@ __device__ __forceinline__ int list_sample_token(int i, int n) {
 }
 
 // Which of m sample scores the cut is: four standard deviations (and three) above the B m / N of them that are expected
-// among the B best, half a deviation more than sample_rank(): a list that comes out short (two to five in 100000) costs
-// three passes over all scores of the row, in every one of its workgroups.
-__host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m) {
+// among the B best, half a deviation more than sample_rank(): a list that comes out short costs three passes over all
+// scores of the row, in every one of its workgroups.  alike: by how much a cluster's scores being alike widens the variance
+// (ListCut).  A list is N r / m long: of 256 scores, independent ones, 1.7 B for 6219 of 32905 tokens, 2.2 B for 2048 of 32768, 3.8 B
+// for 256 of 16384, 5 B for 1024 of 131072, 8.5 B for 64 of 20011.
+__host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m, float alike = 1.0f) {
   const float ps = (float)bsel * ((float)m / (float)n);
-  return (int)(ps + 4.0f * sqrtf(ps) + 3.0f);
+  return (int)(ps + 4.0f * sqrtf(ps * alike) + 3.0f);
 }
 
 // The cut: a score that at least r (1 .. 64 KPL) of the sample's scores reach and hardly more, in steps of a 256th of
 // the spread of the finite ones, by one wave whose lanes hold KPL of them each: a histogram in `bins` (256 words of LDS)
 // and one suffix sum (what it takes is its latency: four rounds of ballots, two bits each, take twice as long).  No
-// more than r finite scores, or hardly: no cut (-inf).  `top`: the sample's largest finite score.
+// more than r finite scores, or hardly: no cut (-inf).
+struct SampleBins {
+  float lo, spread;        // of the sample's finite scores
+};
+__device__ __forceinline__ float cut_of_bins(const SampleBins& sb, int r, const uint32_t* bins) {
+  const int lane = lane_id();
+  const uint4 c = *reinterpret_cast<const uint4*>(bins + 4 * lane);
+  const uint32_t s2 = c.w + c.z, s1 = s2 + c.y, s0 = s1 + c.x;
+  const uint32_t above = wave_suffix_sum(s0) - s0;             // in higher lanes' bins
+  const uint32_t need = (uint32_t)r;
+  const int j = above + c.w >= need ? 3 : above + s2 >= need ? 2 : above + s1 >= need ? 1 : 0;
+  const unsigned long long m = __ballot(above + s0 >= need);   // a run of low lanes
+  const int last = m ? 63 - __clzll((long long)m) : 0;
+  const int bin = 4 * last + __builtin_amdgcn_readlane(j, last);
+  return bin > 0 && sb.spread < INFINITY ? fmaf((float)bin, sb.spread * (1.0f / 256.0f), sb.lo) : -INFINITY;
+}
 template <int KPL>
-__device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t* bins, float& top) {
+__device__ __forceinline__ SampleBins sample_bins(const float (&x)[KPL], uint32_t* bins) {
   const int lane = lane_id();
   *reinterpret_cast<uint4*>(bins + 4 * lane) = make_uint4(0, 0, 0, 0);
   float hi = -INFINITY, lo = INFINITY;
@@ -59,7 +76,6 @@ __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t
   }
   hi = wave_max(hi);
   lo = -wave_max(-lo);
-  top = hi;
   const float spread = hi - lo, inv = 256.0f * __builtin_amdgcn_rcpf(spread);
   // same wave writes and reads: its LDS operations complete in order; the fences only keep the compiler from moving them
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -67,16 +83,57 @@ __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t
   for (int k = 0; k < KPL; ++k)    // (infinite scores: the bins at the ends; NaNs: the lowest)
     atomicAdd(&bins[(uint32_t)fminf(fmaxf((x[k] - lo) * inv, 0.0f), 255.0f)], 1u);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  const uint4 c = *reinterpret_cast<const uint4*>(bins + 4 * lane);
-  const uint32_t s2 = c.w + c.z, s1 = s2 + c.y, s0 = s1 + c.x;
-  const uint32_t above = wave_suffix_sum(s0) - s0;             // in higher lanes' bins
-  const uint32_t need = (uint32_t)r;
-  const int j = above + c.w >= need ? 3 : above + s2 >= need ? 2 : above + s1 >= need ? 1 : 0;
-  const unsigned long long m = __ballot(above + s0 >= need);   // a run of low lanes
-  const int last = m ? 63 - __clzll((long long)m) : 0;
-  const int bin = 4 * last + __builtin_amdgcn_readlane(j, last);
-  return bin > 0 && spread < INFINITY ? fmaf((float)bin, spread * (1.0f / 256.0f), lo) : -INFINITY;
+  return {lo, spread};
 }
+// `top`: the sample's largest finite score.
+template <int KPL>
+__device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t* bins, float& top) {
+  const SampleBins sb = sample_bins(x, bins);
+  top = sb.lo + sb.spread;
+  return cut_of_bins(sb, r, bins);
+}
+
+// The cut of a sample of clusters, TPT scores of one in each of four adjacent lanes.  Scores of neighbouring tokens may be
+// alike, and the sample is then worth little more than its clusters: few of them hold all that reaches the cut.  Of
+// independent scores 16 (1 - (1 - r / 256)^16) of the 16 clusters are expected to have one; where less than 0.85 of these do, and
+// two fewer, the cut is taken again, for a variance up to 16 times as wide.  Short lists, simulated, 400 - 4000 rows each of
+// 16384 tokens, B = 256, of 32768, 2048, of 32905, 6219, and 250 of 131072, 1024: independent scores none, and the cut is taken again
+// in 2 % of the rows; an autoregression of 0.9, 0.98 and 0.998: at most 0.05 %, 0.2 %, 0.4 % and 0.4 % (one row) - with one cut, 3 - 15 %.
+// (A sample of 64 places of 4 tokens needs no second cut and has as few short lists, but it reads four times as many lines: 128
+// rows of 16384: 41.1 -> 49.8 us.)
+struct ListCut {
+  int r, bsel, n;
+  float few;               // clusters
+  template <int TPT>
+  __device__ __forceinline__ static ListCut plan(int bsel, int n) {
+    constexpr int M = kWave * TPT;
+    const int r = list_rank(bsel, n, M);
+    float none = 1.0f - fminf((float)r, (float)M) * (1.0f / M), p = none * none;    // ^ (4 TPT), the size of a cluster
+    p *= p;
+#pragma unroll
+    for (int k = 1; k < TPT; k *= 2) p *= p;
+    const float expected = (kWave / 4) * (1.0f - p);
+    return {__builtin_amdgcn_readfirstlane(r), bsel, n, fminf(0.85f * expected, expected - 2.0f)};
+  }
+  template <int TPT>
+  __device__ __forceinline__ float take(const float (&x)[TPT], uint32_t* bins, float& top) const {
+    const SampleBins sb = sample_bins(x, bins);
+    top = sb.lo + sb.spread;
+    float cut = cut_of_bins(sb, r, bins);
+    bool mine = false;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) mine |= x[k] >= cut;
+    unsigned long long m = __ballot(mine);
+    m |= m >> 1;
+    m |= m >> 2;
+    const float hit = (float)__popcll(m & 0x1111111111111111ull);
+    if (__builtin_expect(hit < few, false)) {
+      const int wider = list_rank(bsel, n, kWave * TPT, fminf(25.0f - 24.0f * hit / few, 4.0f * TPT));
+      cut = wider <= kWave * TPT ? cut_of_bins(sb, wider, bins) : -INFINITY;
+    }
+    return cut;
+  }
+};
 
 // A segment's list, all its waves together: acc[k] is the score of token n0 + k, which counts if it is below N.  wcnt: LDS,
 // one word a wave.  list_count, a block barrier, list_write.  SHARED: read in the same launch.
@@ -267,7 +324,7 @@ __device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow,
 }
 
 // The same among listed scores that the threads hold (key 0: none; klo > 0).
-// more(f): calls f(valid, key, token) for listed scores that nobody holds, whole waves at a time, in the same order
+// more(f): calls f(valid, key, token) for listed scores that no thread holds, whole waves at a time, in the same order
 // each time; `over` (the same in all threads) says that there are any.  Places go by thread, then by wave of the rest.
 // False: fewer than B scores are listed (the histogram is zero then).
 template <int EPT, typename Lds, typename More>
@@ -369,62 +426,167 @@ __device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EP
   return true;
 }
 
+// What the threads do not hold.  Autoregressive scores of 0.98 have lists of 3 - 15 B, a segment's between none and all of it; us per
+// step, with one cut for all kinds of rows and lists read on from memory in every pass of the selection / like this: 8 rows of
+// 32768, 4 heads, B = 2048: 35.1 / 25.9, 128 rows of 16384, B = 256: 54.4 / 48.7, 32 rows of 32905, 7 heads, B = 6219: 75.2 / 59.9,
+// 8 rows of 131072, B = 1024: 121 / 57.2 (independent scores: 17.8, 41.4, 50.0, 40.6, either way).
+
+// What the lists of the wave's segments (lane l: segment l * waves + wave, c entries) hold beyond the threads' entries, to the
+// wave's own part of sm.extra, where it fits: 64 entries at a time, four times in flight.  Returns their number.
+template <bool SHARED, typename Lds>
+__device__ __forceinline__ uint32_t gather_own(Lds& sm, const ListView& v, uint32_t c) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6, first = 2 * v.lanes;
+  uint2* out = sm.extra + wave * Lds::kExtraPerWave;
+  uint32_t have = 0;
+  unsigned long long m = __ballot((int)c > first);
+  const uint2* list = v.list;
+  int i0 = 0, n = 0;                                          // of the segment at hand
+  while (m != 0ull || i0 < n) {
+    uint2 x[4];
+    int left[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (i0 >= n && m != 0ull) {
+        const int l = __ffsll((long long)m) - 1;
+        m &= m - 1ull;
+        n = min(__builtin_amdgcn_readlane((int)c, l), v.seg_tokens);
+        list = v.list + (size_t)(l * Lds::kWaves + wave) * v.seg_tokens;
+        i0 = first;
+      }
+      left[j] = max(n - i0, 0);
+      const uint2* e = list + min(i0 + lane, max(n, 1) - 1);
+      x[j] = SHARED ? ld_agent(e) : *e;
+      i0 += kWave;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (lane < left[j]) out[have + (uint32_t)lane] = make_uint2(x[j].x, min(x[j].y, (uint32_t)v.n - 1u));
+      have += (uint32_t)min(left[j], kWave);
+    }
+  }
+  return have;
+}
+
+// A key that the B-th best of the listed scores reaches, found among those that the threads hold, if there are B of them from klo
+// on (else klo).  The histogram is zero at the call and, with a block barrier, at the end.
+template <int EPT, typename Lds>
+__device__ __forceinline__ uint32_t held_threshold(Lds& sm, const uint32_t (&key)[EPT], uint32_t klo, int shift, int bsel) {
+  uint32_t khi = 0xffffffffu;
+  int need = bsel, n_cand;
+  for (;;) {
+    const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const uint32_t d = key[k] - klo;
+      if (d <= span) atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kSelBins - 1u)], 1u);
+    }
+    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
+    if (n_cand == 0) return klo;
+  }
+  __syncthreads();                                            // all have read thr
+  for (int i = threadIdx.x; i < kSelBins; i += Lds::kThreads) sm.hist[i] = 0;
+  if (threadIdx.x == 0) sm.thr[2] = 0;
+  __syncthreads();
+  return klo;
+}
+
+// What the lists hold beyond the threads' entries, from the key klo on, to LDS: pieces of 64 entries, numbered through all
+// segments; wave w takes pieces w, w + waves, ..., four in flight, to its own part of sm.extra.  Returns the wave's number of
+// entries; sm.thr[3] becomes 1 if there was no room.  The pieces' list lies in the histogram, which is zero at the call and, with a
+// block barrier, at the end.
+template <bool SHARED, typename Lds>
+__device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListView& v, uint32_t klo) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  static_assert(NT >= kListMaxSegs, "a thread a segment");
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t first = 2u * (uint32_t)v.lanes, c = t < v.nsegs ? min(sm.seg_cnt[t], (uint32_t)v.seg_tokens) : 0u;
+  const uint32_t mine = c > first ? (c - first + kWave - 1u) / kWave : 0u;
+  uint32_t pieces;
+  const uint32_t before = block_prefix_sum<NT>(mine, sm.wtot, pieces);
+  for (uint32_t i = 0; i < mine; ++i)
+    if (before + i < (uint32_t)kSelBins) sm.hist[before + i] = (uint32_t)t << 16 | i;
+  __syncthreads();
+  uint2* out = sm.extra + wave * Lds::kExtraPerWave;
+  uint32_t have = 0;
+  const int np = (int)min(pieces, (uint32_t)kSelBins);
+  for (int p0 = wave; p0 < np; p0 += 4 * NWV) {
+    uint2 x[4];
+    int left[4];                                              // entries of the piece
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int p = p0 + j * NWV;
+      const uint32_t d = sm.hist[min(p, np - 1)];
+      const int s = (int)(d >> 16), i0 = (int)(first + (d & 0xffffu) * kWave), n = (int)min(sm.seg_cnt[s], (uint32_t)v.seg_tokens);
+      left[j] = p < np ? n - i0 : 0;
+      const uint2* e = v.list + (size_t)s * v.seg_tokens + min(i0 + lane, n - 1);
+      x[j] = SHARED ? ld_agent(e) : *e;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = lane < left[j] && x[j].x >= klo;
+      const unsigned long long m = __ballot(in);
+      const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, have));
+      if (in && at < (uint32_t)Lds::kExtraPerWave) out[at] = make_uint2(x[j].x, min(x[j].y, (uint32_t)v.n - 1u));
+      have += (uint32_t)__popcll(m);
+    }
+  }
+  if (lane == 0 && (have > (uint32_t)Lds::kExtraPerWave || pieces > (uint32_t)kSelBins)) sm.thr[3] = 1;
+  __syncthreads();
+  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+  __syncthreads();
+  return have;
+}
+
 // Selection of a row out of its segments' lists in memory (row_list.h).  kcut: what they were made with; ktop: the sample's
 // largest key.  SHARED: the lists were made in this launch.
 template <bool SHARED, int EPT, typename Lds>
 __device__ __forceinline__ void select_listed(Lds& sm, const ListView& v, const uint32_t* cnt, uint32_t kcut, uint32_t ktop,
                                               int bsel, const float* srow, int N, int p0, int p1) {
-  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves, CPT = kListMaxSegs / NT;
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  static_assert(NT == kListMaxSegs, "a thread a segment");
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t key[EPT], tok[EPT], c1[CPT];
-#pragma unroll
-  for (int i = 0; i < CPT; ++i) {
-    const uint32_t* p = cnt + min(i * NT + t, v.nsegs - 1);
-    c1[i] = SHARED ? ld_agent(p) : *p;
-  }
+  uint32_t key[EPT], tok[EPT];
+  const int mine = lane * NWV + wave;                         // segment
+  uint32_t c = SHARED ? ld_agent(cnt + min(mine, v.nsegs - 1)) : cnt[min(mine, v.nsegs - 1)];
   list_load<SHARED, NT, EPT>(v, key, tok);
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  if (t == 0) sm.thr[2] = 0;
-  uint32_t c = 0;
-  bool beyond = false;
-#pragma unroll
-  for (int i = 0; i < CPT; ++i) {
-    const uint32_t x = i * NT + t < v.nsegs ? c1[i] : 0u;
-    sm.seg_cnt[i * NT + t] = x;
-    c += x;
-    beyond |= x > 2u * (uint32_t)v.lanes;
-  }
+  if (t == 0) sm.thr[2] = sm.thr[3] = 0;
+  c = mine < v.nsegs ? c : 0u;
+  sm.seg_cnt[mine] = c;
   FASA_T_DECL(5);
   FASA_T(0);
-  const uint32_t sum = wave_prefix_sum(c);
-  const bool more_here = __ballot(beyond) != 0ull;
-  if (lane == kWave - 1) { sm.wtot[wave] = sum; sm.wtot2[wave] = more_here ? 1u : 0u; }
+  const uint32_t sum = wave_prefix_sum(c), held = 2u * (uint32_t)v.lanes;
+  uint32_t beyond = 0;                                        // entries that the threads do not hold
+  if (__ballot(c > held) != 0ull) beyond = wave_prefix_sum(c > held ? min(c, (uint32_t)v.seg_tokens) - held : 0u);
+  if (lane == kWave - 1) { sm.wtot[wave] = sum; sm.wtot2[wave] = beyond; }
   __syncthreads();
   uint32_t M = 0, over = 0;
 #pragma unroll
-  for (int w = 0; w < NWV; ++w) { M += sm.wtot[w]; over |= sm.wtot2[w]; }
-  auto more = [&](auto&& f) {
-    for (int s0 = 0; s0 < v.nsegs; s0 += kWave * NWV) {       // this wave's segments are s0 + wave, + NWV, ..
-      const int sl = s0 + lane * NWV + wave;
-      unsigned long long m = __ballot(sl < v.nsegs && sm.seg_cnt[min(sl, kListMaxSegs - 1)] > 2u * (uint32_t)v.lanes);
-      for (; m; m &= m - 1ull) {
-        const int s = s0 + (__ffsll((long long)m) - 1) * NWV + wave;
-        const int n = (int)min(sm.seg_cnt[s], (uint32_t)v.seg_tokens);
-        for (int i0 = 2 * v.lanes; i0 < n; i0 += kWave) {
-          const uint2* e = v.list + (size_t)s * v.seg_tokens + min(i0 + lane, n - 1);
-          const uint2 x = SHARED ? ld_agent(e) : *e;
-          f(i0 + lane < n, x.x, min(x.y, (uint32_t)N - 1u));
-        }
-      }
-    }
-  };
+  for (int w = 0; w < NWV; ++w) { M += sm.wtot[w]; over = max(over, sm.wtot2[w]); }
   list_mask<NT, EPT>(v, sm.seg_cnt, key, tok);
   FASA_T(1);
   FASA_T_PRINT(t == 0 && blockIdx.x == 0, "list counts arrive + barrier %llu M %d over %d of %d\n", FASA_T_D(1, 0), (int)M, (int)over, EPT * NT);
-  // far more than are held (ties, a cut that could not be made): the row's scores are the faster ones to read
-  const bool usable = (int)M >= bsel && (int)M <= 2 * EPT * NT;
-  if (usable && select_entries<EPT>(sm, key, tok, over != 0, more, max(kcut, 1u), kcut ? first_shift(kcut, ktop) : 22, bsel, srow,
-                                    N, p0, p1))
+  uint32_t have = 0;                                          // entries of this wave in sm.extra
+  const uint2* extra = sm.extra + wave * Lds::kExtraPerWave;
+  auto more = [&](auto&& f) {                                 // (a wave reads what it wrote itself)
+    for (uint32_t i0 = 0; i0 < have; i0 += kWave) {
+      const uint2 x = extra[min(i0 + (uint32_t)lane, (uint32_t)Lds::kExtraPerWave - 1u)];
+      f(i0 + (uint32_t)lane < have, x.x, x.y);
+    }
+  };
+  uint32_t klo = max(kcut, 1u);
+  bool usable = (int)M >= bsel;
+  if (over != 0 && usable) {
+    if (over <= (uint32_t)Lds::kExtraPerWave) {
+      have = gather_own<SHARED>(sm, v, c);
+    } else {
+      klo = held_threshold<EPT>(sm, key, klo, kcut ? first_shift(kcut, ktop) : 22, bsel);
+      have = gather_beyond<SHARED>(sm, v, klo);
+      usable = sm.thr[3] == 0;                                // (not: ties, a cut that could not be made)
+    }
+  }
+  if (usable && select_entries<EPT>(sm, key, tok, over != 0, more, klo, kcut ? first_shift(klo, max(ktop, klo)) : 22, bsel, srow, N, p0,
+                                    p1))
     return;
   // Or the sample misled, and the threshold lies below the cut, as a first guess by no more than its best lies above.
   __syncthreads();                                            // (all have read the counts)

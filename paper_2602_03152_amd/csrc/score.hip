@@ -404,6 +404,7 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
       if (t < D) knew[t] = newkv;
     }
   }
+  const ListCut lc = ListCut::plan<TPT>(seq_bsel(budget_seq, b, N, budget_max), N);   // (under the loads)
   const bool own_wg = APPEND && n_app / SL == slice;
   __syncthreads();
   if (t < D / 2) {
@@ -444,9 +445,8 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
   }
   planes(FP - NW, std::false_type{});
   if (sampler) {
-    const int r = list_rank(seq_bsel(budget_seq, b, N, budget_max), N, SEG);
     float top = INFINITY, cut = -INFINITY;
-    if (N >= kListMinCtx && r <= SEG) cut = list_cut(acc, r, bins, top);
+    if (N >= kListMinCtx && lc.r <= SEG) cut = lc.take(acc, bins, top);
     if (t == NT) {
       cut_top = make_float2(cut, top);
       if (slice == 0) { ctl[row].list_cut = score_key(cut); ctl[row].list_top = score_key(top); }

@@ -63,9 +63,11 @@ struct RowLds {
   static constexpr int kThreads = NT;
   static constexpr int kWaves = NT / kWave;
   static constexpr int kList = LIST;
+  static constexpr int kExtraPerWave = LIST == 1 ? 896 : 1;  // (two workgroups still share a compute unit's LDS)
   union {
     float o[kWaves][GM][kHeadDim];                           // weighted V per wave
     uint2 list[kList];                                       // scores at or above the cut: (score bits, token)
+    uint2 extra[kWaves * kExtraPerWave];                     // entries of lists that no thread holds
     unsigned char merge[8192 + GM * kListMaxWgs * 4];        // combine_row: partitions, then weights
   };
   union {

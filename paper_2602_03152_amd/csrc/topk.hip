@@ -200,11 +200,12 @@ __global__ __launch_bounds__(256) void select_all_kernel(int32_t* __restrict__ T
 constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT, kTopkSample = 256;
 
 struct TopkLds {
-  static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave;
+  static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave, kExtraPerWave = 256;
   __align__(16) float sample[kTopkSample];
   __align__(16) uint32_t bins[256];
   uint32_t hist[kSelBins];
   uint2 cand[kSelCand];
+  uint2 extra[kWaves * kExtraPerWave];                       // entries of lists that no thread holds
   uint32_t wtot[kWaves], wtot2[kWaves], wcnt[kWaves];
   uint32_t seg_cnt[kListMaxSegs];
   uint32_t thr[4];

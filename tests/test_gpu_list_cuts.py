@@ -1,0 +1,123 @@
+"""The lists that the scoring launch of a bf16 step makes (csrc/row_list.h) where a row's best scores lie together, as those of
+attention do: rows of an autoregression, rows that rise, rows with all of their best in one segment of 1024 tokens or
+across the edge of two.  What a segment lists is then more than the selecting threads load, and a sample of neighbouring
+tokens says little about the row: a list shorter than B is exact too, but takes several passes over all scores of the
+row in every one of its workgroups, and has to stay the exception."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fasa_oracle as O
+from paper_2602_03152_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+D, HIST_BYTES, CTL_BYTES, CUT_WORD = 128, 4096 * 4, 128, 6     # of a row: histogram, counters, its cut (csrc/fasa_internal.h)
+
+
+@pytest.fixture(scope="module")
+def fb():
+    from paper_2602_03152_amd import binding
+    return binding
+
+
+def make_scores(kind, rows, n, budget):
+    rng = np.random.default_rng(n + budget)
+    x = rng.standard_normal((rows, n)).astype(np.float32)
+    if kind.startswith("ar"):
+        rho = np.float32(kind[2:])
+        x[:, 1:] *= np.sqrt(1 - rho * rho)
+        for i in range(1, n):
+            x[:, i] += rho * x[:, i - 1]
+    elif kind == "rising":
+        x = 0.01 * x + np.linspace(-3, 3, n, dtype=np.float32)
+    elif kind == "together":                         # as many as fit, then some, in one place of every row
+        for r in range(rows):
+            at = rng.integers(0, n - min(n, 2 * budget) + 1)
+            x[r, at:at + 2 * budget] += 8.0
+    elif kind == "one_segment_infinite":
+        x[:, 1024:2048] = np.inf
+    elif kind == "outliers":                         # one score far above the rest in every segment, or far below
+        x[:, 7::1024] = 3e4
+        x[:, 9::1024] = -3e30
+    elif kind == "levels":                           # ties in their thousands
+        x = np.round(x * 2) / 2
+    return x
+
+
+def step_of(fb, scores, budget, lens=None, budgets=None):
+    """One step over rows of these scores (one KV head each; K is 0 beside them, so every selected token weighs the same)."""
+    rows, n = scores.shape
+    cap = (n + 63) // 64 * 64
+    x = np.zeros((rows, 8, cap, 2), dtype=np.uint16)
+    x[:, 0, :n, 0] = W.to_storage(scores, "bf16")
+    Kp = torch.from_numpy(x.view(np.int16)).cuda()
+    q = torch.zeros(rows, 1, D, dtype=torch.bfloat16, device="cuda")
+    q[:, :, 0] = 1.0
+    K = torch.zeros(cap, D, dtype=torch.bfloat16, device="cuda")             # one K and V for all rows
+    V = torch.randn(cap, D, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda").bfloat16()
+    fc = torch.arange(8, dtype=torch.int32, device="cuda")
+    shape = fb.make_shape(rows, 1, 1, D, 8, n, cap, budget, "bf16", kv_stride_b=0, kv_stride_h=0, kv_stride_n=D)
+    ws = torch.empty(fb.fasa_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    fb.fasa_workspace_init(shape, ws, ws.numel())
+    S = torch.zeros(rows, 1, cap, device="cuda")
+    T = torch.full((rows, 1, budget), -1, dtype=torch.int32, device="cuda")
+    out = torch.zeros(rows, 1, D, device="cuda")
+
+    def run():
+        if lens is None:
+            fb.fasa_decode_step(shape, q, K, V, Kp, fc, None, None, S, T, out, ws, ws.numel())
+        else:
+            fb.fasa_decode_step_ragged(shape, q, K, V, Kp, fc, None, None, lens, budgets, S, T, out, ws, ws.numel())
+    return run, S, T, out, V, ws
+
+
+@pytest.mark.parametrize("kind", ["ar0.9", "ar0.98", "rising", "together", "one_segment_infinite", "outliers", "levels"])
+@pytest.mark.parametrize("rows,n_ctx,budget", [(128, 16384, 256), (9, 16385, 1023), (8, 32768, 2048), (4, 32905, 6219), (3, 3001, 650),
+                                               (5, 50001, 70)])
+def test_best_that_lie_together(fb, kind, rows, n_ctx, budget):
+    print("lists", kind, rows, n_ctx, budget, flush=True)
+    run, S, T, out, V, _ = step_of(fb, make_scores(kind, rows, n_ctx, budget), budget)
+    for again in range(2):                           # the workspace is left as it has to be
+        T.fill_(-1)
+        out.fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        some = sorted({0, 1, rows // 2, rows - 1})
+        got = np.sort(T[some].cpu().numpy(), -1)
+        np.testing.assert_array_equal(got, O.topk(S[some, :, :n_ctx].cpu().numpy(), budget, n_ctx))
+        want = V.double()[torch.from_numpy(got[:, 0]).long().cuda()].mean(1)
+        # float32 sums of 1e4 terms of at most about 5: well below 1e-4
+        assert (out[some, 0].double() - want).abs().max().item() <= 1e-4
+
+
+def test_ragged_rows_whose_best_lie_together(fb):
+    rows, n, budget = 16, 20000, 1500
+    lens = [n - 1201 * i for i in range(rows)]
+    budgets = [max(1, budget * x // n) if i % 3 else budget for i, x in enumerate(lens)]
+    dev = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")   # noqa: E731
+    run, S, T, out, V, _ = step_of(fb, make_scores("ar0.98", rows, n, budget), budget, dev(lens), dev(budgets))
+    print("ragged lists", flush=True)
+    run()
+    torch.cuda.synchronize()
+    for r in range(rows):
+        b = min(budgets[r], lens[r])
+        got = np.sort(T[r, 0, :b].cpu().numpy())
+        np.testing.assert_array_equal(got, O.topk(S[r:r + 1, :, :lens[r]].cpu().numpy(), b, lens[r])[0, 0])
+
+
+@pytest.mark.parametrize("rho", [0.0, 0.9, 0.98])
+@pytest.mark.parametrize("rows,n_ctx,budget", [(256, 16384, 256), (256, 16383, 1100), (64, 32905, 6219), (64, 50001, 700)])
+def test_few_lists_are_short(fb, rows, n_ctx, budget, rho):
+    print("short lists", rows, n_ctx, budget, rho, flush=True)
+    run, S, T, out, V, ws = step_of(fb, make_scores("ar%g" % rho, rows, n_ctx, budget), budget)
+    run()
+    torch.cuda.synchronize()
+    ctl = ws[rows * HIST_BYTES:rows * (HIST_BYTES + CTL_BYTES)].cpu().numpy().view(np.uint32).reshape(rows, -1)
+    key = ctl[:, CUT_WORD]
+    cut = np.where(key >> 31, key & 0x7fffffff, ~key).astype(np.uint32).view(np.float32)
+    listed = (S[:, 0, :n_ctx].cpu().numpy() >= cut[:, None]).sum(-1)
+    print("listed / B: least %.2f, mean %.2f, most %.2f" % (listed.min() / budget, listed.mean() / budget, listed.max() / budget),
+          flush=True)
+    # at most 0.4 % of any kind of row when simulated (with one cut for all kinds 3 - 10 % of the alike ones)
+    assert (listed < budget).sum() <= 2
