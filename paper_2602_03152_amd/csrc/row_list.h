@@ -49,7 +49,7 @@ __host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m, float 
 // and one suffix sum (what it takes is its latency: four rounds of ballots, two bits each, take twice as long).  No
 // more than r finite scores, or hardly: no cut (-inf).
 struct SampleBins {
-  float lo, spread;        // of the sample's finite scores
+  float lo, hi, spread;    // of the sample's finite scores
 };
 __device__ __forceinline__ float cut_of_bins(const SampleBins& sb, int r, const uint32_t* bins) {
   const int lane = lane_id();
@@ -83,13 +83,13 @@ __device__ __forceinline__ SampleBins sample_bins(const float (&x)[KPL], uint32_
   for (int k = 0; k < KPL; ++k)    // (infinite scores: the bins at the ends; NaNs: the lowest)
     atomicAdd(&bins[(uint32_t)fminf(fmaxf((x[k] - lo) * inv, 0.0f), 255.0f)], 1u);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  return {lo, spread};
+  return {lo, hi, spread};
 }
 // `top`: the sample's largest finite score.
 template <int KPL>
 __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t* bins, float& top) {
   const SampleBins sb = sample_bins(x, bins);
-  top = sb.lo + sb.spread;
+  top = sb.hi;
   return cut_of_bins(sb, r, bins);
 }
 
@@ -118,7 +118,7 @@ struct ListCut {
   template <int TPT>
   __device__ __forceinline__ float take(const float (&x)[TPT], uint32_t* bins, float& top) const {
     const SampleBins sb = sample_bins(x, bins);
-    top = sb.lo + sb.spread;
+    top = sb.hi;
     float cut = cut_of_bins(sb, r, bins);
     bool mine = false;
 #pragma unroll
