@@ -72,6 +72,15 @@ int main() {
                               (long long)(p.nslices - 1) * p.slice_len < n);
           }
   EXPECT(lists > 0 && forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
+  // ---- eight waves per compute unit: the splits cover the tokens, the workspace holds them, and they fill their rounds ----
+  for (int rows = 1; rows <= 600; ++rows)
+    for (int count : {1, 17, 700, 1500, 3000, 4096, 8192, 30001, 131072}) {
+      const fasa::AttendPlan p = fasa::plan_attend_wide(rows, count), most = fasa::plan_attend(rows, count, 4);
+      EXPECT(p.n_splits >= 1 && p.n_splits <= most.n_splits && (long long)p.n_splits * p.tok_per_split >= count &&
+             (long long)(p.n_splits - 1) * p.tok_per_split < count);
+      const long long wgs = (long long)rows * p.n_splits, rounds = (wgs + 255) / 256;
+      if (rows > 128 && count >= 3000 && most.n_splits >= 4) EXPECT(wgs * 10 >= rounds * 256 * 6);
+    }
   // ---- bad shapes ----
   {
     fasa_shape s = shape(1, 32, 8, 16, 1000, 1024, 100);

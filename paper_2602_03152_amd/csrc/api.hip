@@ -88,15 +88,30 @@ AttendPlan plan_attend(int rows, int count, int group) {
   return p;
 }
 
-// One workgroup per compute unit, of at least 64 tokens, in as many rounds as it takes with 16384 each.
+// One workgroup per compute unit, of at least 64 tokens, in as many rounds as it takes with 16384 each.  Rows a little more than
+// half as many as the compute units, or a little more than all of them, would leave nearly half of these idle for a
+// round, one workgroup a row: then as many a row as fill four fifths of their rounds, of 256 tokens or more.  us, one / so / two
+// workgroups of four waves per compute unit: 136 rows of 8192, 4 heads: 112.4 / 104.4 (5 a row) / 108.2; 264 of 4096: 133.1 / 106.2
+// (4) / 106.5; 288 of 3000, 7 heads: 98.8 / 90.3 (3) / 93.2; 288 of 1500, 4 heads: 51.8 / 47.5 (3) / 49.0.  Not from 0.6 of a round on: 160
+// rows of 6000: 85.3 / 87.5 (3) / 86.1; 400 of 3000: 107.0 / 113.2 (3) / 118.0.
 AttendPlan plan_attend_wide(int rows, int count) {
   const long long slots = kAssumedCUs, total = (long long)rows * count;
   long long nblocks = (total + 63) / 64;
-  if (nblocks > slots) nblocks = slots * ((total + slots * 16384 - 1) / (slots * 16384));
+  const bool much = nblocks > slots;
+  if (much) nblocks = slots * ((total + slots * 16384 - 1) / (slots * 16384));
   long long n_splits = nblocks / rows;                    // (rounded down: a few workgroups more would share compute units)
   const int most = plan_attend(rows, count, 1).n_splits;
   if (n_splits > most) n_splits = most;
   if (n_splits < 1) n_splits = 1;
+  const auto fills = [&](long long n, long long tenths) {
+    const long long rounds = (rows * n + slots - 1) / slots;
+    return rows * n * 10 >= tenths * rounds * slots;
+  };
+  if (much && !fills(n_splits, 6)) {
+    long long n = n_splits + 1;
+    while (n < most && !fills(n, 8)) ++n;
+    if (n <= most && count / n >= 256) n_splits = n;
+  }
   const long long tps = (count + n_splits - 1) / n_splits;
   return AttendPlan{count, (int)tps, (int)((count + tps - 1) / tps)};
 }

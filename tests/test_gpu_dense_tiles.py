@@ -31,3 +31,22 @@ def test_dense_at_the_edges_of_the_tiles(fb, cid, heads, n_ctx):  # noqa: F811
     torch.cuda.synchronize()
     ref = O.dense_attend(x["q"], x["K"], x["V"], n_ctx)
     assert np.abs(to_host(d.O) - ref).max() <= 2e-3
+
+
+@pytest.mark.parametrize("batch,heads,n_ctx", [(17, (32, 8), 1300), (33, (16, 8), 1040), (129, (7, 1), 2050), (20, (8, 8), 777)])
+def test_dense_rows_around_the_compute_units(fb, batch, heads, n_ctx):  # noqa: F811
+    """129 to 264 rows: several workgroups a row where one would leave half of the compute units idle."""
+    from tests.gpu_util import Device, to_host
+    w = W.WORKLOADS[1].scaled(batch=1, n_ctx=n_ctx, budget=n_ctx, n_q_heads=heads[0], n_kv_heads=heads[1])
+    x = W.make_inputs(w, n_cap=(n_ctx + 63) // 64 * 64)
+    # one sequence, its tokens in another rotation for every entry of the batch: the same attention
+    for name in ("K", "V"):
+        x[name] = np.stack([np.concatenate([np.roll(x[name][0][:, :n_ctx], 13 * b, axis=1), x[name][0][:, n_ctx:]], axis=1)
+                            for b in range(batch)])
+    ref = O.dense_attend(x["q"], x["K"][:1], x["V"][:1], n_ctx)
+    x["q"] = np.repeat(x["q"], batch, axis=0)
+    print("dense rows", batch, heads, n_ctx, flush=True)
+    d = Device(w.scaled(batch=batch), x)
+    fb.fasa_dense_attend(d.shape, d.q, d.K, d.V, d.O, d.ws, d.ws_bytes)
+    torch.cuda.synchronize()
+    assert np.abs(to_host(d.O) - ref).max() <= 2e-3
