@@ -594,9 +594,12 @@ hipError_t launch_attend(const fasa_shape& s, bool dense, const void* q, const v
   // 2048 (32): 7.3 / 7.4; 24 rows, 1000 (16): 8.1 / 8.4; 2 rows, 333 (6): 5.9 / 6.7
   // Short full KV has few partials to halve and no workgroups to share a compute unit with: up to 16 splits, while a
   // workgroup has one for itself, attend_kernel is the faster one, attend_kernel / wide: 8 rows of 500 (8 splits):
-  // 5.75 / 6.28 us; of 1000 (16): 5.85 / 6.30; 16 rows of 700 (11): 5.86 / 6.37; 1 row of 700 (11): 5.76 / 5.93.  Beyond:
-  // 8 rows of 1500 (24), 7 heads: 7.20 / 7.29; of 2000 (32): 6.87 / 6.53; 32 rows of 1000 (16, 512 workgroups): 7.33 / 7.14;
-  // 32 rows of 600 (9, 288 workgroups), 8 heads: 8.33 / 6.70
+  // 5.75 / 6.28 us; of 1000 (16): 5.85 / 6.30; 16 rows of 700 (11): 5.86 / 6.37; 1 row of 700 (11): 5.76 / 5.93.  From 17 to 36 the two are
+  // as good as each other: over 16 shapes of 1 - 8 rows and 1 - 8 heads, called one after another, 1.027 times as fast with this
+  // one (0.95 - 1.08: 8 rows, 4 heads, of 1100: 6.73 / 6.31, of 1500: 6.35 / 6.39, 7 heads: 7.23 / 7.31, 2 heads, of 1200: 5.69 / 5.99), while in
+  // graphs attend_kernel leads by 3 - 10 % where there are up to 4 heads (of 1200: 6.01 / 6.27) and up to 200 workgroups.  Beyond: 8 rows
+  // of 2000 (32): 6.88 / 6.60; of 2300, 7 heads: 9.43 / 7.93; 32 rows of 1000 (16, 512 workgroups): 7.33 / 7.14; 32 rows of 600 (9, 288
+  // workgroups), 8 heads: 8.33 / 6.70
   const bool wide = dense ? p.n_splits > 16 || rows * p.n_splits > kAssumedCUs : p.n_splits > 40;
   if (s.dtype == FASA_BF16 && wide)
     return launch_wide(s, dense, plan_attend_wide(rows, count), q, K, V, T, O, ctl, part_acc, part_ml, st, rl, pm);

@@ -50,3 +50,17 @@ def test_dense_rows_around_the_compute_units(fb, batch, heads, n_ctx):  # noqa: 
     fb.fasa_dense_attend(d.shape, d.q, d.K, d.V, d.O, d.ws, d.ws_bytes)
     torch.cuda.synchronize()
     assert np.abs(to_host(d.O) - ref).max() <= 2e-3
+
+
+# full KV of few splits: which kernel is told by its partials' number, so both sides of each line are compared with the oracle
+@pytest.mark.parametrize("batch,heads,n_ctx", [
+    (1, (10, 2), 1024), (1, (10, 2), 1025), (1, (32, 8), 1024), (1, (32, 8), 1025), (4, (8, 4), 1024), (4, (8, 4), 1025), (4, (20, 5), 832)])
+def test_dense_at_the_lines_of_short_rows(fb, batch, heads, n_ctx):  # noqa: F811
+    from tests.gpu_util import Device, to_host
+    w = W.WORKLOADS[1].scaled(batch=batch, n_ctx=n_ctx, budget=n_ctx, n_q_heads=heads[0], n_kv_heads=heads[1])
+    x = W.make_inputs(w, n_cap=(n_ctx + 63) // 64 * 64)
+    print("dense lines", batch, heads, n_ctx, flush=True)
+    d = Device(w, x)
+    fb.fasa_dense_attend(d.shape, d.q, d.K, d.V, d.O, d.ws, d.ws_bytes)
+    torch.cuda.synchronize()
+    assert np.abs(to_host(d.O) - O.dense_attend(x["q"], x["K"], x["V"], n_ctx)).max() <= 2e-3
