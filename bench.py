@@ -669,6 +669,7 @@ def kernel_bytes(w):
         # what these read to select (lists of a few scores, or a histogram and the scores) is an intermediate of the step
         "fasa_select_attend": gather,
         "fasa_row": gather,
+        "fasa_list": gather,
         "fasa_step": planes + gather,               # the whole step: its scores need not leave the chip
         "fasa_dense_attend": rows * 2 * w.n_ctx * w.head_dim * e,
     }

@@ -383,12 +383,12 @@ static int decode_step_common(const fasa_shape* shape, const fasa_paging* paging
   const ListPlan lp = form == kStepOne || select_all ? ListPlan{0, 0, 0} : plan_list(*shape, pm, w.max_splits);
   if (lp.ept != 0) {
     // two launches: scores + lists of the largest, then selection out of the lists and attention by equal shares
-    FASA_HIP(launch_list_step(*shape, lp, form == kStepRow, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, cand,
+    FASA_HIP(launch_list_step(*shape, lp, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, cand,
                               (uint32_t*)(base + w.rec_off), (float*)(base + w.part_acc_off), (float*)(base + w.part_ml_off), st,
                               rl, pm));
     return FASA_OK;
   }
-  if (form == kStepOne || (form == kStepRow && shape->dtype == FASA_F32)) {
+  if (form != kStepNone) {
     FASA_HIP(launch_step(*shape, form, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, st, rl, pm));
     return FASA_OK;
   }

@@ -172,11 +172,10 @@ struct AppendArgs {
 };
 constexpr AppendArgs kNoAppend = {nullptr, nullptr, nullptr, nullptr, {nullptr, 0, 0, 0}, false};
 // Where the scoring kernel leaves the lists of a row's largest scores (row_list.h): entries [row][n_cap], their numbers
-// [row][kListCntPitch]; load: entries of a segment that are read without asking.
+// [row][kListCntPitch].
 struct ListOut {
   uint2* list;
   uint32_t* cnt;
-  int load;
 };
 // hist == nullptr: scores only.  adaptive_ctl != nullptr (with hist): the adaptive histogram of the
 // fused step (bins of lin_bin, location and scale left in the row counters) instead of the
@@ -189,7 +188,8 @@ hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const
                              const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap);
 // zeroes the histogram and the row counters (workspace initialisation)
 hipError_t launch_ws_clear(const fasa_shape& s, uint32_t* hist, RowCtl* ctl, hipStream_t st);
-// TopK-I of given scores in one launch (topk.hip): the set of every row to T.  ept == 0: not for this shape.  list [row][n_cap], cnt [row][cnt_pitch]; tickets [row * ticket_stride], zero.
+// TopK-I of given scores in one launch (topk.hip): the set of every row to T.  ept == 0: not for this shape.
+// list [row][n_cap], cnt [row][cnt_pitch]; tickets [row * ticket_stride], zero.
 struct TopkPlan {
   int ept, lanes;
 };
@@ -215,7 +215,7 @@ hipError_t launch_select_attend(const fasa_shape& s, const FusePlan& p, const vo
                                 int32_t* T, float* O, float* part_acc, float* part_ml, unsigned char* rec,
                                 hipStream_t st, RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
 
-// The step with one workgroup selecting and attending per row (step.hip): the whole step in one launch, or
+// The step with one workgroup selecting and attending per row (step.hip): the whole step in one launch, or (float32)
 // after a scoring launch; plan_step: which of the two, if any, takes the shape.
 enum StepForm { kStepNone, kStepOne, kStepRow };
 constexpr int kStepMaxBudget = 1024;   // most selected tokens per row
@@ -235,7 +235,7 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits);
 // Entries per thread (even, at most `most`) of nt threads that load what a row's lists are likely to hold, 0: more than
 // fit; lanes: threads per segment, two entries each.
 int list_loads(int n, int bsel, int seg_tokens, int sample, int nt, int most, int* lanes);
-hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, bool row_form, const void* q, void* K, void* V, void* Kp,
+hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* q, void* K, void* V, void* Kp,
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                             RowCtl* ctl, uint2* list, uint32_t* cnt, float* part_acc, float* part_ml, hipStream_t st,
                             RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);

@@ -541,8 +541,9 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
 }
 
 // One workgroup per row; the scores lie in S (an earlier launch).
-template <typename ET, int GM>
+template <int GM>
 __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
+  using ET = float;
   __shared__ RowLds<kRowNT, GM> sm;
   const int row = blockIdx.x;
   const int b = row / a.Hkv, h = row % a.Hkv;
@@ -581,8 +582,9 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // and ticket 1.2, merge 1.2.  us, both launches, fused.hip or row_kernel / like this: 8 rows of 32768, 4 heads, B = 2048:
 // 21.2 / 19.0; 32 rows, 7 heads, B = 6200: 53.0 / 49.4; 8 rows of 131072, F = 32, B = 1024: 41.8 / 39.8; 64 rows of 65536, B = 700:
 // 80.9 / 71.9; 128 rows of 16384, B = 256: 41.7 / 41.3, 512 rows of 8192, F = 8: 62.1 / 49.1.
-template <typename ET, int G, int EPT>
+template <int G, int EPT>
 __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
+  using ET = uint16_t;
   constexpr int D = kHeadDim, SEG = kListScoreNT * ScoreTraits<ET>::TPT;
   __shared__ RowLds<kListNT, G, 1, kListMaxShare> sm;
   __shared__ float red[G];
@@ -640,7 +642,7 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
 // ---------------------------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------------------------
-// Where the row form is the faster one after the scores.  It pays where the workgroups of the split form (fused.hip; two
+// Where the row form is the faster one after the scores of a float32 cache (a bf16 cache's rows have lists).  It pays where the workgroups of the split form (fused.hip; two
 // per compute unit, at most 4096 tokens each) no longer fit at once, and while reading the scores, not
 // gathering on one compute unit, is what a row takes: the line in B falls with rows * N.
 static bool row_form(const fasa_shape& s, long long rows, int bsel) {
@@ -651,10 +653,8 @@ static bool row_form(const fasa_shape& s, long long rows, int bsel) {
   // 79.4 / 99.0; 40 rows of 100000, B = 512: 79 / 153
   const float r = (float)sample_rank(bsel, s.n_ctx);
   if ((r + 4.f * sqrtf(r)) * (float)n > (float)(kSample * kListPerThread * kRowNT)) return false;
-  // bf16: list_kernel runs these shapes and others alike; the line only says which of its launches are recorded as "fasa_row".
   const bool few = bsel * 2048ll <= cells;
-  if (s.dtype == FASA_BF16) return n >= 5120 && few;
-  // float32, 1 head.  N = 4096, B = 64: 64 rows 20.5 / 20.8, 80: 23.5 / 22.6; B = 512: 128 rows 40.3 / 41.7; 1024 rows, B = 200:
+  // 1 head.  N = 4096, B = 64: 64 rows 20.5 / 20.8, 80: 23.5 / 22.6; B = 512: 128 rows 40.3 / 41.7; 1024 rows, B = 200:
   // 164 / 170.  N = 8192, B = 256: 80 rows 34.3 / 33.8, 96: 38.3 / 37.3; B = 512: 96 rows 43.5 / 44.9.  N = 16384, B = 256:
   // 128 rows 72.8 / 67.5; 64 rows of 33000, B = 512: 81.6 / 76.6
   const int group = s.n_q_heads / s.n_kv_heads;
@@ -682,10 +682,10 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
     // one slice: 8 rows of 2048, B = 64: 14.5 / 10.2 / 15.0, B = 512: 18.2 / 14.9 / 19.8; 512 rows: 29.4 / 20.5 / 36.3
     if (ns == 1) return kStepOne;
     // 8 rows of 8192, B = 256: 14.6 / 14.6 / 17.3, B = 512: 16.0 / 17.0 / 19.8; 128 rows of 4096: 22.3 / 20.4 / 21.9
-        // Several slices, where the lists of a scoring launch do not do better (list_kernel): 8 rows of 8192, F = 16 / 32: 13.6 / 14.9
+    // Several slices, where the lists of a scoring launch do not do better (list_kernel): 8 rows of 8192, F = 16 / 32: 13.6 / 14.9
     // against 14.4 / 16.5, 32 rows: 17.1 / 19.9 against 17.0 / 20.5, 40 rows: 18.6 against 17.5; 8 rows of 6000, B = 40: 12.2
     // against 12.3, of 3000: 12.2 against 11.8
-    if (ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320 && (rows > 32 || ns < 4)) return kStepOne;
+    return ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320 && (rows > 32 || ns < 4) ? kStepOne : kStepNone;
   } else {
     // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
     // 1 row of 4096, B = 256: 17.3 / 12.7 / 15.5, 32 rows of 8192, B = 600: 22.2 / 22.1 / 26.3.  4 heads, 8 rows, B = 64:
@@ -763,15 +763,15 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   return p;
 }
 
-template <typename ET, int G>
-static hipError_t launch_list_g(const StepArgs& a, int ept, const char* name, hipStream_t st) {
+template <int G>
+static hipError_t launch_list_g(const StepArgs& a, int ept, hipStream_t st) {
   switch (ept) {
-    case 4: return launch(name, list_kernel<ET, G, 4>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 12: return launch(name, list_kernel<ET, G, 12>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 24: return launch(name, list_kernel<ET, G, 24>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 8: return launch(name, list_kernel<ET, G, 8>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 16: return launch(name, list_kernel<ET, G, 16>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 32: return launch(name, list_kernel<ET, G, 32>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 4: return launch("fasa_list", list_kernel<G, 4>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 8: return launch("fasa_list", list_kernel<G, 8>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 12: return launch("fasa_list", list_kernel<G, 12>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 16: return launch("fasa_list", list_kernel<G, 16>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 24: return launch("fasa_list", list_kernel<G, 24>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 32: return launch("fasa_list", list_kernel<G, 32>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
     default: return hipErrorInvalidValue;
   }
 }
@@ -779,11 +779,11 @@ static hipError_t launch_list_g(const StepArgs& a, int ept, const char* name, hi
 static StepArgs step_args(const fasa_shape& s, const void* q, void* K, void* V, void* Kp, const int32_t* fc_idx, const void* k_new,
                           const void* v_new, float* S, int32_t* T, float* O, RowCtl* ctl, RaggedLens rl, PageMap pm);
 
-hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, bool row_form, const void* q, void* K, void* V, void* Kp,
+hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* q, void* K, void* V, void* Kp,
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                             RowCtl* ctl, uint2* list, uint32_t* cnt, float* part_acc, float* part_ml, hipStream_t st,
                             RaggedLens rl, PageMap pm) {
-  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ctl, ListOut{list, cnt, 2 * p.lanes}, st, rl,
+  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ctl, ListOut{list, cnt}, st, rl,
                                          AppendArgs{k_new, v_new, K, V, pm, false});
   if (e != hipSuccess) return e;
   StepArgs a = step_args(s, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, rl, pm);
@@ -792,16 +792,15 @@ hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, bool row_for
   a.magic = (uint32_t)((1ull << 32) / (unsigned)p.lanes) + 1u;
   a.nwgs = p.nwgs;
   a.part_acc = part_acc; a.part_ml = part_ml;
-  const char* name = row_form ? "fasa_row" : "fasa_select_attend";
   switch (s.n_q_heads / s.n_kv_heads) {
-    case 1: return launch_list_g<uint16_t, 1>(a, p.ept, name, st);
-    case 2: return launch_list_g<uint16_t, 2>(a, p.ept, name, st);
-    case 3: return launch_list_g<uint16_t, 3>(a, p.ept, name, st);
-    case 4: return launch_list_g<uint16_t, 4>(a, p.ept, name, st);
-    case 5: return launch_list_g<uint16_t, 5>(a, p.ept, name, st);
-    case 6: return launch_list_g<uint16_t, 6>(a, p.ept, name, st);
-    case 7: return launch_list_g<uint16_t, 7>(a, p.ept, name, st);
-    case 8: return launch_list_g<uint16_t, 8>(a, p.ept, name, st);
+    case 1: return launch_list_g<1>(a, p.ept, st);
+    case 2: return launch_list_g<2>(a, p.ept, st);
+    case 3: return launch_list_g<3>(a, p.ept, st);
+    case 4: return launch_list_g<4>(a, p.ept, st);
+    case 5: return launch_list_g<5>(a, p.ept, st);
+    case 6: return launch_list_g<6>(a, p.ept, st);
+    case 7: return launch_list_g<7>(a, p.ept, st);
+    case 8: return launch_list_g<8>(a, p.ept, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -836,8 +835,8 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
   if (form == kStepRow) {                                      // (float32: a bf16 cache's lists come from the scoring launch)
     const hipError_t e = launch_score(s, q, Kp, fc_idx, S, nullptr, st, rl, AppendArgs{k_new, v_new, K, V, pm, false});
     if (e != hipSuccess) return e;
-    if (G == 1) return launch("fasa_row", row_kernel<float, 1>, dim3(a.rows), dim3(kRowNT), st, a);
-    if (G <= 4) return launch("fasa_row", row_kernel<float, 4>, dim3(a.rows), dim3(kRowNT), st, a);
+    if (G == 1) return launch("fasa_row", row_kernel<1>, dim3(a.rows), dim3(kRowNT), st, a);
+    if (G <= 4) return launch("fasa_row", row_kernel<4>, dim3(a.rows), dim3(kRowNT), st, a);
     return hipErrorInvalidValue;                               // (row_form)
   }
   if (s.n_ctx > kStepMaxCtx) return hipErrorInvalidValue;      // (plan_step)

@@ -13,8 +13,8 @@ SMALL = {0: dict(), 1: dict(n_ctx=9024, budget=700), 2: dict(batch=16, n_ctx=825
 
 
 @pytest.mark.parametrize("argv,kernel", [
-    (["--config", "0"], "fasa_step"), (["--config", "1"], "fasa_select_attend"), (["--config", "2"], "fasa_row"),
-    (["--config", "1", "--pairing", "interleaved"], "fasa_select_attend"), (["--config", "3"], "fasa_select_attend"),
+    (["--config", "0"], "fasa_step"), (["--config", "1"], "fasa_list"), (["--config", "2"], "fasa_list"),
+    (["--config", "1", "--pairing", "interleaved"], "fasa_list"), (["--config", "3"], "fasa_list"),
     (["--config", "1", "--offload"], "fasa_offload_attend"), (["--config", "0", "--offload"], "fasa_offload_gather"),
     (["--config", "1", "--calibrate", "2"], "fasa_calib_fc"), (["--config", "1", "--paged", "16"], None),
     (["--config", "2", "--ragged", "8"], None), (["--config", "3", "--growing", "8"], None),
