@@ -9,7 +9,7 @@ from oracle import fasa_oracle as O
 from paper_2602_03152_amd import workload as W
 from tests.test_gpu_decode_step import compare_step, fb  # noqa: F401
 from tests.test_gpu_paged import PagedDevice
-from tests.test_gpu_ragged import compare_ragged, i32_dev
+from tests.test_gpu_ragged import i32_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -49,14 +49,36 @@ def test_list_of_pool_slots(fb, page, layout):  # noqa: F811
 
 
 def test_list_with_empty_splits(fb):  # noqa: F811
-    from tests.gpu_util import Device
-    lens, budgets = [524289, 40000], [9000, 300]     # (too long for the step's two-launch forms)
-    w = W.WORKLOADS[1].scaled(batch=2, n_ctx=524289, budget=9000, n_q_heads=4, n_kv_heads=1)
-    x = _inputs(w)
+    """Rows of more than 2^20 tokens run the stages one after another; a short second sequence leaves most of its splits empty.
+    (Drawn on the GPU, one K and V for both sequences: the reference is float64 torch.)"""
+    D, n, B, lens, budgets = 128, (1 << 20) + 1, 9000, [(1 << 20) + 1, 40000], [9000, 300]
+    cap = (n + 63) // 64 * 64
     print("empty splits", flush=True)
-    d = Device(w, x)
-    d.pack()
-    fb.fasa_decode_step_ragged(d.shape, d.q, d.K, d.V, d.Kp, d.fc_idx, None, None, i32_dev(lens), i32_dev(budgets),
-                               d.S, d.T, d.O, d.ws, d.ws_bytes)
-    torch.cuda.synchronize()
-    compare_ragged(w, x["q"], x["K"], x["V"], x["fc_idx"], d, lens, budgets, 9000)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").bfloat16()   # noqa: E731
+    q, K, V, Kp = rnd(2, 4, D), rnd(cap, D), rnd(cap, D), rnd(2, 1, 8, cap, 2)
+    fc = torch.arange(8, dtype=torch.int32, device="cuda")
+    shape = fb.make_shape(2, 4, 1, D, 8, n, cap, B, "bf16", kv_stride_b=0, kv_stride_h=0, kv_stride_n=D)
+    ws = torch.empty(fb.fasa_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    fb.fasa_workspace_init(shape, ws, ws.numel())
+    S = torch.zeros(2, 1, cap, device="cuda")
+    T = torch.full((2, 1, B), -1, dtype=torch.int32, device="cuda")
+    out = torch.full((2, 4, D), float("nan"), device="cuda")
+    fb.fasa_profile_reset()
+    fb.fasa_profile_enable(True)
+    try:
+        for _ in range(2):                            # the workspace is left as it has to be
+            fb.fasa_decode_step_ragged(shape, q, K, V, Kp, fc, None, None, i32_dev(lens), i32_dev(budgets), S, T, out, ws, ws.numel())
+        torch.cuda.synchronize()
+        names = set(fb.profile_summary())
+    finally:
+        fb.fasa_profile_enable(False)
+        fb.fasa_profile_reset()
+    assert "fasa_sparse_attend" in names and "fasa_select_attend" not in names and "fasa_list" not in names, names
+    for b in range(2):
+        t = T[b, 0, :budgets[b]].long()
+        assert t.min() >= 0 and t.max() < lens[b] and t.unique().numel() == budgets[b]
+        best = S[b, 0, :lens[b]].topk(budgets[b]).values
+        assert torch.equal(S[b, 0, t].sort(descending=True).values, best)
+        p = torch.softmax(q[b].double() @ K[t].double().T / D ** 0.5, -1)
+        assert (out[b].double() - p @ V[t].double()).abs().max().item() <= 2e-3
