@@ -10,6 +10,7 @@
 
 #include "fasa.h"
 #include "fasa_internal.h"
+#include "select_common.h"
 
 #define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED line %d: %s\n", __LINE__, #cond); return 1; } } while (0)
 
@@ -80,6 +81,21 @@ int main() {
       const long long wgs = (long long)rows * p.n_splits, rounds = (wgs + 255) / 256;
       if (rows > 128 && count >= 3000 && most.n_splits >= 4) EXPECT(wgs * 10 >= rounds * 256 * 6);
     }
+  // ---- the threshold's range only narrows, whatever key the threshold bin holds (a NaN's is the largest there is) ----
+  for (uint32_t key : {0u, 1u, 0x007fffffu, 0x3d3dffffu, 0x7fffffffu, 0x80000000u, 0xbf800000u, 0xff7fffffu, 0xff800000u, 0xffc00000u, 0xffffffffu})
+    for (uint32_t from : {1u, 0x007fffffu, 0x3d3dffffu, 0x3fbfffffu, 0x7fffffffu, 0x80000001u, 0xbe4ccccdu, 0xc0000000u, 0xff800000u})
+      for (int first : {22, 23, 16, 1}) {
+        if (from > key) continue;
+        uint32_t klo = from, khi = 0xffffffffu;
+        int shift = first;
+        for (int pass = 0; pass < 6 && klo != khi; ++pass) {
+          const uint32_t d = (key - klo) >> shift, bin = d < 1023u ? d : 1023u, lo = klo, hi = khi;
+          fasa::narrow_range(klo, khi, bin, shift);
+          EXPECT(lo <= klo && klo <= key && key <= khi && khi <= hi);
+          shift = 22 - __builtin_clz((khi - klo) | 1u);
+          if (shift < 0) shift = 0;
+        }
+      }
   // ---- bad shapes ----
   {
     fasa_shape s = shape(1, 32, 8, 16, 1000, 1024, 100);

@@ -120,6 +120,13 @@ __device__ __forceinline__ void rank_sample(float sval, uint32_t* sample, uint32
 //              wide and still too full is a tie of that many tokens: they are taken in index order, out of
 //              the row's scores in memory.
 // ---------------------------------------------------------------------------------------------
+// The threshold bin, which holds a key of klo .. khi, as the next range.  The last bin reaches up to khi; no other beyond it: a
+// bin that a NaN's key lies in may end past the largest key there is.
+__host__ __device__ __forceinline__ void narrow_range(uint32_t& klo, uint32_t& khi, uint32_t bin, int shift) {
+  klo += bin << shift;
+  const uint32_t left = khi - klo, width = (1u << shift) - 1u;
+  if (bin + 1 < (uint32_t)kSelBins) khi = klo + (width < left ? width : left);
+}
 // After the counting: true once klo .. khi is the final range (need of its n_cand scores are taken, and all
 // above it); else the range to count next, the histogram zeroed - the same range, with n_cand 0, if fewer than
 // need scores were counted in it.  sm.thr[2] has to be 0 at the call then; where every score of the range is counted
@@ -150,8 +157,7 @@ __device__ __forceinline__ bool find_threshold(Lds& sm, uint32_t& klo, uint32_t&
   if (n_cand > 0) {
     const uint32_t bin = sm.thr[0];
     need -= (int)sm.thr[1];
-    klo += bin << shift;
-    if (bin + 1 < (uint32_t)kSelBins) khi = klo + ((1u << shift) - 1u);   // the last bin reaches up to khi
+    narrow_range(klo, khi, bin, shift);
     if (n_cand <= kSelCand || klo == khi) return true;
     shift = max(0, 22 - __clz((int)(khi - klo)));             // (khi - klo) >> shift < 1024
   }

@@ -45,12 +45,14 @@ def make_scores(kind, rows, n, budget):
     return x
 
 
-def step_of(fb, scores, budget, lens=None, budgets=None):
+def step_of(fb, scores, budget, lens=None, budgets=None, planes=None):
     """One step over rows of these scores (one KV head each; K is 0 beside them, so every selected token weighs the same)."""
     rows, n = scores.shape
     cap = (n + 63) // 64 * 64
     x = np.zeros((rows, 8, cap, 2), dtype=np.uint16)
     x[:, 0, :n, 0] = W.to_storage(scores, "bf16")
+    if planes:
+        planes(x)
     Kp = torch.from_numpy(x.view(np.int16)).cuda()
     q = torch.zeros(rows, 1, D, dtype=torch.bfloat16, device="cuda")
     q[:, :, 0] = 1.0
@@ -121,3 +123,35 @@ def test_few_lists_are_short(fb, rows, n_ctx, budget, rho):
           flush=True)
     # at most 0.4 % of any kind of row when simulated (with one cut for all kinds 3 - 10 % of the alike ones)
     assert (listed < budget).sum() <= 2
+
+
+# Where NaN scores rank is unspecified, but a set has B tokens and every call ends: a list is short here (the finite scores are the
+# sample's), and the search for the threshold starts at a key below zero, from which bins are wide.  (csrc/abi_host_check.cpp
+# goes through the ranges.)
+@pytest.mark.parametrize("nan", [0x7fc0, 0xffc0, 0x7fff], ids=hex)
+@pytest.mark.parametrize("n_ctx,budget", [(9001, 200), (16384, 700), (20000, 3000)])
+def test_nan_scores_end(fb, n_ctx, budget, nan):
+    rows = 8
+    print("lists, NaN", n_ctx, budget, hex(nan), flush=True)
+    scores = np.zeros((rows, n_ctx), dtype=np.float32)
+    run, S, T, out, V, ws = step_of(fb, scores, budget, planes=lambda x: _nan_beside_the_sample(x, n_ctx, nan))
+    for again in range(2):
+        T.fill_(-1)
+        run()
+        torch.cuda.synchronize()
+        for r in range(rows):
+            t = T[r, 0].long()
+            assert t.min() >= 0 and t.max() < n_ctx and t.unique().numel() == budget
+            want = V.double()[t].mean(0)
+            assert (out[r, 0].double() - want).abs().max().item() <= 1e-4
+
+
+def _nan_beside_the_sample(x, n, nan):
+    """Scores of the 16 clusters of 16 tokens that the scoring launch samples: ordinary, one of a row far above; else NaN."""
+    rng = np.random.default_rng(n)
+    x[:, 0, :n, 0] = nan
+    at = np.concatenate([((n * (2 * c + 1) // 32) & ~15) + np.arange(16) for c in range(16)])
+    for r in range(x.shape[0]):
+        s = rng.standard_normal(256)
+        s[rng.integers(256)] = 100.0
+        x[r, 0, at, 0] = W.to_storage(s, "bf16")

@@ -46,3 +46,24 @@ def test_topk_lists(fb, rows, n, b, kind):  # noqa: F811
     s = np.full(rows + (n_cap,), 1e30, dtype=np.float32)          # what lies beyond the row must not count
     s[..., :n] = _scores(kind, rows, n, b, rng)
     _check_topk_exact(fb, s, n, b)
+
+
+@pytest.mark.parametrize("rows,n,b", [((1, 2), 2047, 300), ((1, 2), 4097, 300), ((3, 3), 20011, 1250), ((1, 1), 70000, 40)])
+def test_nan_scores_end(fb, rows, n, b):  # noqa: F811
+    """Where NaNs rank is unspecified, but a set has B tokens: finite scores at the sampled places only, so that the list is short,
+    and one far above the others, so that the search for the threshold starts below zero."""
+    import torch
+    print("topk lists, NaN", rows, n, b, flush=True)
+    rng = np.random.default_rng(n)
+    n_cap = (n + 63) // 64 * 64
+    s = np.full(rows + (n_cap,), np.nan, dtype=np.float32)
+    s[..., _sampled(n)] = rng.normal(0, 1, size=rows + (256,))
+    s[..., _sampled(n)[7]] = 100.0
+    shape = fb.make_shape(rows[0], rows[1], rows[1], 128, 16, n, n_cap, b, "bf16")
+    ws = torch.empty(fb.fasa_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    fb.fasa_workspace_init(shape, ws, ws.numel())
+    T = torch.full(rows + (b,), -1, dtype=torch.int32, device="cuda")
+    fb.fasa_topk(shape, torch.from_numpy(s).cuda(), T, ws, ws.numel())
+    torch.cuda.synchronize()
+    for t in T.reshape(-1, b):
+        assert t.min() >= 0 and t.max() < n and t.unique().numel() == b
