@@ -42,26 +42,26 @@ LLC_BYTES = 256 << 20         # last-level (memory-side) cache the rotation has 
 # what the same counters read for a plain copy kernel of known size (see profiles/).  Keyed by
 # (workload config id, kernel name); bytes per launch.  None = not measured yet.
 MEASURED_TRAFFIC = {
-    "source_hash": "a8eb066ad40c8ccd",   # source_hash() of the kernels the counters were taken on
+    "source_hash": "b59ce5917d677cd1",   # source_hash() of the kernels the counters were taken on
     # profiles/decode_step_tiny_1head_f32_n4096_hbm_counters.txt  (read + written)
-    (0, "fasa_dense_attend"): 4320540 + 39456,
-    (0, "fasa_step"): 869838 + 18080,
+    (0, "fasa_dense_attend"): 4320501 + 39456,
+    (0, "fasa_step"): 871501 + 18080,
     # profiles/decode_step_llama3_8b_layer_n32768_b2048_hbm_counters.txt  (read + written)
-    (1, "fasa_dense_attend"): 134901714 + 1089792,
-    (1, "fasa_list"): 9841913 + 1155328,
-    (1, "fasa_score_list"): 16904392 + 1327072,
+    (1, "fasa_dense_attend"): 134899758 + 1089792,
+    (1, "fasa_list"): 9812441 + 1155328,
+    (1, "fasa_score_list"): 16904478 + 1327072,
     # profiles/decode_step_batch16_n16384_b256_hbm_counters.txt  (read + written)
-    (2, "fasa_dense_attend"): 1074457927 + 1339392,
-    (2, "fasa_list"): 19348802 + 393216,
-    (2, "fasa_score_list"): 134700807 + 9461959,
+    (2, "fasa_dense_attend"): 1074442560 + 1339392,
+    (2, "fasa_list"): 19338286 + 393216,
+    (2, "fasa_score_list"): 134691980 + 9462103,
     # profiles/decode_step_longcot_batch8_gqa7_n32768_hbm_counters.txt  (read + written)
-    (3, "fasa_dense_attend"): 537973821 + 1997824,
-    (3, "fasa_list"): 106821783 + 2791424,
-    (3, "fasa_score_list"): 67283248 + 6855193,
+    (3, "fasa_dense_attend"): 537958234 + 1997824,
+    (3, "fasa_list"): 106803376 + 2791424,
+    (3, "fasa_score_list"): 67282142 + 6855194,
     # profiles/decode_step_verylong_n131072_f32fc_b1024_hbm_counters.txt  (read + written)
-    (4, "fasa_dense_attend"): 537511972 + 1089792,
-    (4, "fasa_list"): 5675623 + 585984,
-    (4, "fasa_score_list"): 134389395 + 4521539,
+    (4, "fasa_dense_attend"): 537504068 + 1089792,
+    (4, "fasa_list"): 5671751 + 585984,
+    (4, "fasa_score_list"): 134387698 + 4521453,
 }
 
 
