@@ -577,10 +577,10 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // nwgs workgroups per row; the scores lie in S, the lists of the largest in `list` (score_list_kernel).  Every workgroup of a
 // row finds the row's set, out of the same lists and so in the same order, and attends over its share of it: nothing about
 // the selection is left open for the workgroup that merges, and all gather the same number of rows (fused.hip's slices
-// differ by 14 %, and leave a threshold bin to resolve at the end).  A chain of round trips: lists and counts 0.7 us, their
-// histogram 0.2 - 1.1 by length, threshold 0.5, places 0.6 - 2, candidates 0.5 - 1, rows 2.3 (388 rows a workgroup: 10.5), partial
-// and ticket 1.2, merge 1.2.  us, both launches, fused.hip or row_kernel / like this: 8 rows of 32768, 4 heads, B = 2048:
-// 21.2 / 19.0; 32 rows, 7 heads, B = 6200: 53.0 / 49.4; 8 rows of 131072, F = 32, B = 1024: 41.8 / 39.8; 64 rows of 65536, B = 700:
+// differ by 14 %, and leave a threshold bin to resolve at the end).  A chain of round trips: once the lists are there, counts
+// 0.5 - 1.2 us by length, histogram 0.5 - 0.9, threshold 0.5 - 0.8, places 1.2 - 2.6, candidates 0.4 - 1, rows 2.3 (784 rows a
+// workgroup: 10.4), partial and ticket 1.4, merge 0.9 - 1.3.  us, both launches, fused.hip or row_kernel / like this: 8 rows of 32768, 4 heads, B = 2048:
+// 21.2 / 19.0; 32 rows, 7 heads, B = 6200: 53.0 / 49.4; 8 rows of 131072, F = 32, B = 1024: 40.8 / 41.2; 64 rows of 65536, B = 700:
 // 80.9 / 71.9; 128 rows of 16384, B = 256: 41.7 / 41.3, 512 rows of 8192, F = 8: 62.1 / 49.1.
 template <int G, int EPT>
 __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
