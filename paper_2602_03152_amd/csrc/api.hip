@@ -303,10 +303,10 @@ int fasa_topk(const fasa_shape* shape, const float* S, int32_t* T, void* ws, siz
   uint2* cand = (uint2*)(base + w.cand_off);
   hipStream_t st = (hipStream_t)stream;
   const TopkPlan tp = plan_topk(shape->n_ctx, shape->budget);
-  if (tp.ept != 0) {
-    // lists go where the candidates go, their counts where the records go
-    FASA_HIP(launch_topk(tp, w.rows, shape->n_ctx, shape->n_cap, shape->budget, S, T, cand, (uint32_t*)(base + w.rec_off),
-                         (int)(kFuseRecBytesPerRow / sizeof(uint32_t)), &ctl->done_sel, (int)(sizeof(RowCtl) / sizeof(uint32_t)), st));
+  if (tp.cap != 0) {
+    // lists go where the candidates go, the segments' descriptions where the records go
+    FASA_HIP(launch_topk(tp, w.rows, shape->n_ctx, shape->n_cap, shape->budget, S, T, cand, (uint2*)(base + w.rec_off),
+                         &ctl->done_sel, (int)(sizeof(RowCtl) / sizeof(uint32_t)), st));
     return FASA_OK;
   }
   if (shape->budget < shape->n_ctx) FASA_HIP(launch_hist(*shape, S, hist, st));
@@ -380,11 +380,11 @@ static int decode_step_common(const fasa_shape* shape, const fasa_paging* paging
   // the new row (if any) joins K, V and Kp inside the scoring kernel
   const AppendArgs ap{k_new, v_new, K, V, pm, false};
   const StepForm form = plan_step(*shape, pm);
-  const ListPlan lp = form == kStepOne || select_all ? ListPlan{0, 0, 0} : plan_list(*shape, pm, w.max_splits);
-  if (lp.ept != 0) {
+  const ListPlan lp = form == kStepOne || select_all ? ListPlan{0, 0} : plan_list(*shape, pm, w.max_splits);
+  if (lp.cap != 0) {
     // two launches: scores + lists of the largest, then selection out of the lists and attention by equal shares
     FASA_HIP(launch_list_step(*shape, lp, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, cand,
-                              (uint32_t*)(base + w.rec_off), (float*)(base + w.part_acc_off), (float*)(base + w.part_ml_off), st,
+                              (uint2*)(base + w.rec_off), (float*)(base + w.part_acc_off), (float*)(base + w.part_ml_off), st,
                               rl, pm));
     return FASA_OK;
   }

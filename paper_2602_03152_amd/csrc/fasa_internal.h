@@ -34,9 +34,8 @@ struct RowCtl {
   uint32_t done_att;  // attention workgroups of this row that wrote their partial
   float bin_mu;       // adaptive histogram of the fused step: written by the scoring kernel of a call,
   float bin_inv;      // read by its selection kernel (never has to be zero)
-  uint32_t list_cut;  // lists of a row (row_list.h): the key they were made with and the sample's largest; as the two above
-  uint32_t list_top;
-  uint32_t pad[24];
+  uint32_t list_cut;  // lists of a row (row_list.h): the key from which on the selection looked at its scores; written only
+  uint32_t pad[25];
 };
 static_assert(sizeof(RowCtl) == 128, "one line per row");
 
@@ -171,11 +170,12 @@ struct AppendArgs {
   bool split;
 };
 constexpr AppendArgs kNoAppend = {nullptr, nullptr, nullptr, nullptr, {nullptr, 0, 0, 0}, false};
-// Where the scoring kernel leaves the lists of a row's largest scores (row_list.h): entries [row][n_cap], their numbers
-// [row][kListCntPitch].
+// Where the scoring kernel leaves the lists of a row's largest scores (row_list.h: ListRow): [row][n_cap] 8 bytes a token, and
+// [row][kListLimPitch] segments.  room: places of a segment's list, or 0 where list_room() gives each row its own; cap: what it fits into.
 struct ListOut {
   uint2* list;
-  uint32_t* cnt;
+  uint2* lims;
+  int room, cap;
 };
 // hist == nullptr: scores only.  adaptive_ctl != nullptr (with hist): the adaptive histogram of the
 // fused step (bins of lin_bin, location and scale left in the row counters) instead of the
@@ -184,18 +184,18 @@ hipError_t launch_score(const fasa_shape& s, const void* q, const void* Kp, cons
                         float* S, uint32_t* hist, hipStream_t st, RaggedLens rl = {nullptr, nullptr},
                         AppendArgs ap = kNoAppend, RowCtl* adaptive_ctl = nullptr);
 // scores and lists
-hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S, RowCtl* ctl,
+hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S,
                              const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap);
 // zeroes the histogram and the row counters (workspace initialisation)
 hipError_t launch_ws_clear(const fasa_shape& s, uint32_t* hist, RowCtl* ctl, hipStream_t st);
-// TopK-I of given scores in one launch (topk.hip): the set of every row to T.  ept == 0: not for this shape.
-// list [row][n_cap], cnt [row][cnt_pitch]; tickets [row * ticket_stride], zero.
+// TopK-I of given scores in one launch (topk.hip): the set of every row to T.  cap == 0: not for this shape.
+// list, lims: as ListOut; tickets [row * ticket_stride], zero.
 struct TopkPlan {
-  int ept, lanes;
+  int cap;         // places of a row's list that the selecting threads hold
 };
 TopkPlan plan_topk(int n_ctx, int bsel);
 hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint2* list,
-                       uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st);
+                       uint2* lims, uint32_t* tickets, int ticket_stride, hipStream_t st);
 hipError_t launch_hist(const fasa_shape& s, const float* S, uint32_t* hist, hipStream_t st);
 // Tslot (paged caches only, else null): receives the pool slot of every entry of T, same layout
 hipError_t launch_select(const fasa_shape& s, const float* S, const uint32_t* hist, RowCtl* ctl,
@@ -225,19 +225,17 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
                        RowCtl* ctl, hipStream_t st, RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
 
 // Selection out of lists and attention by one or several workgroups per row, after a scoring launch that makes the
-// lists (step.hip).  ept == 0: not for this shape.
+// lists (step.hip).  cap == 0: not for this shape.
 struct ListPlan {
   int nwgs;        // workgroups per row
-  int ept;         // kernel instance: entries per thread
-  int lanes;       // threads that load a segment's first 2 * lanes entries
+  int cap;         // places of a row's list that a workgroup's threads hold
 };
 ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits);
-// Entries per thread (even, at most `most`) of nt threads that load what a row's lists are likely to hold, 0: more than
-// fit; lanes: threads per segment, two entries each.
-int list_loads(int n, int bsel, int seg_tokens, int sample, int nt, int most, int* lanes);
+// Places of a row's list that nt threads hold, at most `most` quads each; 0: more than fit.
+int list_cap(int n, int bsel, int nt, int most);
 hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* q, void* K, void* V, void* Kp,
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
-                            RowCtl* ctl, uint2* list, uint32_t* cnt, float* part_acc, float* part_ml, hipStream_t st,
+                            RowCtl* ctl, uint2* list, uint2* lims, float* part_acc, float* part_ml, hipStream_t st,
                             RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
 
 // memory-optimised variant (offload.hip)

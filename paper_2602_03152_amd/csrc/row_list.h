@@ -1,14 +1,15 @@
-// Lists of the scores of a row that can be among its B best (paper Sec. 4.1, TopK-I), made by the workgroups that
-// score it: what TopK-I has to look at shrinks from N scores to a few times B (list_rank) before the row is selected.
+// Lists of the scores of a row that can be among its B best (paper Sec. 4.1, TopK-I), made by the waves that
+// score it: what TopK-I has to look at shrinks from N scores to a few times B (list_room) before the row is selected.
 //
-//   cut      every workgroup of a row scores the same sample of the row's tokens and takes a score of it that a few
-//            more than B of the row's scores should reach (list_cut).  All arrive at the same bits.
-//   list     a workgroup writes the scores of its segment of the row that reach the cut, as (key, token), to the
-//            segment's own stretch of the row's list, and their number (list_count, list_write): no position is shared, so there is no
-//            atomic, and a stretch has room for the whole segment.
-//   select   list_load, select_listed: whoever selects holds the entries in registers, as many of each segment as are likely;
-//            what a segment has beyond, where a row's best lie together, goes through LDS.  A list shorter than B,
-//            because the sample misled, or far too long is not used: row_select.
+//   list     a wave that holds the scores of a segment of 256 tokens writes the largest of them, `room` at most, as keys and
+//            tokens to the segment's own places of the row's list (seg_list), the places left over as keys 0, and the key from
+//            which on the segment is listed completely.  Nothing is shared between waves: no sample, no barrier, no atomic, and all
+//            segments' lists are equally long.
+//   select   select_listed: whoever selects holds the row's list in registers.  From the highest of the segments' completeness
+//            keys on the list holds all of the row's scores; if B of its entries reach that key, the B best of the row are among
+//            them.  If not, a row's best lie together, in segments with more of them than there was room for: those
+//            segments' scores are read again, from a key on that B listed ones reach, into LDS.  row_select, which reads all
+//            of a row's scores, is left for what does not fit there (ties in their thousands, NaNs).
 // What the scores look like costs time, never exactness.
 #pragma once
 
@@ -18,30 +19,32 @@
 
 namespace fasa {
 
-constexpr int kListMaxSegs = 512;       // segments of a row
-constexpr int kListScoreNT = 256;       // scoring threads of a workgroup that makes lists
-constexpr int kListMinCtx = 1024;       // shorter rows are listed whole: the sample's clusters would meet
-constexpr int kListCntPitch = (int)(kFuseRecBytesPerRow / sizeof(uint32_t));
-static_assert(kListCntPitch >= kListMaxSegs, "a row's counts lie where the split form has its records");
+constexpr int kListSeg = 256;           // tokens of a segment: four per lane of a wave
+constexpr int kListMaxSegs = 2048;      // segments of a row
+constexpr int kListBins = 512;          // of the selection's histogram
+constexpr uint32_t kListAll = 0x007fffffu;   // the key of -inf: a segment is listed whole
+constexpr int kListLimPitch = (int)(kFuseRecBytesPerRow / sizeof(uint2));
+static_assert(kListLimPitch >= kListMaxSegs, "a row's segments are described where the split form has its records");
 
-// The sample: kWave * TPT tokens, in clusters of consecutive ones (64 bytes of a plane) that are evenly spaced over the row.
-// First token of lane i's TPT; n: tokens of the row that lie in the planes.  In range of the row's capacity for any n, and of
-// the row itself for n >= kListMinCtx - 1.
-template <typename ET>
-__device__ __forceinline__ int list_sample_token(int i, int n) {
-  constexpr int TPT = ScoreTraits<ET>::TPT, CL = 32 / (int)sizeof(ET), NC = kWave * TPT / CL;
-  const int c = i * TPT / CL;
-  return ((n * (2 * c + 1) / (2 * NC)) & ~(CL - 1)) + (i * TPT & (CL - 1));
+// Which of m sample scores a row's cut is: four standard deviations (and three) above the B m / N of them that are expected
+// among the B best, half a deviation more than sample_rank().
+__host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m) {
+  const float ps = (float)bsel * ((float)m / (float)n);
+  return (int)(ps + 4.0f * sqrtf(ps) + 3.0f);
 }
 
-// Which of m sample scores the cut is: four standard deviations (and three) above the B m / N of them that are expected
-// among the B best, half a deviation more than sample_rank(): a list that comes out short costs three passes over all
-// scores of the row, in every one of its workgroups.  alike: by how much a cluster's scores being alike widens the variance
-// (ListCut).  A list is N r / m long: of 256 scores, independent ones, 1.7 B for 6219 of 32905 tokens, 2.2 B for 2048 of 32768, 3.8 B
-// for 256 of 16384, 5 B for 1024 of 131072, 8.5 B for 64 of 20011.
-__host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m, float alike = 1.0f) {
-  const float ps = (float)bsel * ((float)m / (float)n);
-  return (int)(ps + 4.0f * sqrtf(ps * alike) + 3.0f);
+// Places of a segment's list (a multiple of 4): four standard deviations and five above the 256 B / N of its scores that are expected among
+// the B best.  Of independent scores hardly one segment in 10^6 has more of them than that, and a row's list is 1.7 B long
+// for 6219 of 32905 tokens, 2.5 B for 2048 of 32768, 5 B for 256 of 16384, 6 B for 1024 of 131072.  cap: places that the
+// selecting threads hold.  The launch that lists and the one that selects both come to the same number: nothing is contracted.
+__host__ __device__ __forceinline__ int list_room(int bsel, int n, int cap) {
+#pragma clang fp contract(off)
+  const int nsegs = (n + kListSeg - 1) / kListSeg;
+  const float p = (float)bsel * ((float)kListSeg / (float)n), r = p + 4.0f * sqrtf(p);
+  int room = ((int)r + 5 + 3) & ~3;
+  room = room < kListSeg ? room : kListSeg;
+  const int most = (cap / nsegs) & ~3;
+  return room < most ? room : most;
 }
 
 // The cut: a score that at least r (1 .. 64 KPL) of the sample's scores reach and hardly more, in steps of a 256th of
@@ -93,129 +96,141 @@ __device__ __forceinline__ float list_cut(const float (&x)[KPL], int r, uint32_t
   return cut_of_bins(sb, r, bins);
 }
 
-// The cut of a sample of clusters, TPT scores of one in each of four adjacent lanes.  Scores of neighbouring tokens may be
-// alike, and the sample is then worth little more than its clusters: few of them hold all that reaches the cut.  Of
-// independent scores 16 (1 - (1 - r / 256)^16) of the 16 clusters are expected to have one; where less than 0.85 of these do, and
-// two fewer, the cut is taken again, for a variance up to 16 times as wide.  Short lists, simulated, 400 - 4000 rows each of
-// 16384 tokens, B = 256, of 32768, 2048, of 32905, 6219, and 250 of 131072, 1024: independent scores none, and the cut is taken again
-// in 2 % of the rows; an autoregression of 0.9, 0.98 and 0.998: at most 0.05 %, 0.2 %, 0.4 % and 0.4 % (one row) - with one cut, 3 - 15 %.
-// (A sample of 64 places of 4 tokens needs no second cut and has as few short lists, but it reads four times as many lines: 128
-// rows of 16384: 41.1 -> 49.8 us.)
-struct ListCut {
-  int r, bsel, n;
-  float few;               // clusters
-  template <int TPT>
-  __device__ __forceinline__ static ListCut plan(int bsel, int n) {
-    constexpr int M = kWave * TPT;
-    const int r = list_rank(bsel, n, M);
-    float none = 1.0f - fminf((float)r, (float)M) * (1.0f / M), p = none * none;    // ^ (4 TPT), the size of a cluster
-    p *= p;
-#pragma unroll
-    for (int k = 1; k < TPT; k *= 2) p *= p;
-    const float expected = (kWave / 4) * (1.0f - p);
-    return {__builtin_amdgcn_readfirstlane(r), bsel, n, fminf(0.85f * expected, expected - 2.0f)};
-  }
-  template <int TPT>
-  __device__ __forceinline__ float take(const float (&x)[TPT], uint32_t* bins, float& top) const {
-    const SampleBins sb = sample_bins(x, bins);
-    top = sb.hi;
-    float cut = cut_of_bins(sb, r, bins);
-    bool mine = false;
-#pragma unroll
-    for (int k = 0; k < TPT; ++k) mine |= x[k] >= cut;
-    unsigned long long m = __ballot(mine);
-    m |= m >> 1;
-    m |= m >> 2;
-    const float hit = (float)__popcll(m & 0x1111111111111111ull);
-    if (__builtin_expect(hit < few, false)) {
-      const int wider = list_rank(bsel, n, kWave * TPT, fminf(25.0f - 24.0f * hit / few, 4.0f * TPT));
-      cut = wider <= kWave * TPT ? cut_of_bins(sb, wider, bins) : -INFINITY;
-    }
-    return cut;
+// ---------------------------------------------------------------------------------------------
+// A segment's list, by one wave
+// ---------------------------------------------------------------------------------------------
+struct SegLds {
+  union {
+    __align__(16) uint32_t bins[256];
+    __align__(16) uint32_t keys[kListSeg];
+  };
+  union {
+    __align__(16) uint8_t toks[kListSeg];
+    uint32_t toks4[kListSeg / 4];
+  };
+};
+
+// Where a row's lists lie: [segment][room] keys, then as many token numbers inside the segment, a byte each, and per segment the
+// key from which on it is listed completely and its largest finite score's.
+struct ListRow {
+  uint32_t* keys;
+  uint32_t* toks;          // four a word
+  uint2* lims;
+  int room;
+  // 5 bytes a place: no more than the row's 8 bytes per token of capacity (a multiple of 64), however short the row
+  __host__ __device__ __forceinline__ static ListRow at(uint2* list, uint2* lims, int row, int n_cap, int n, int room) {
+    uint32_t* keys = (uint32_t*)(list + (size_t)row * n_cap);
+    return {keys, keys + (size_t)((n + kListSeg - 1) / kListSeg) * room, lims + (size_t)row * kListLimPitch, room};
   }
 };
 
-// A segment's list, all its waves together: acc[k] is the score of token n0 + k, which counts if it is below N.  wcnt: LDS,
-// one word a wave.  list_count, a block barrier, list_write.  SHARED: read in the same launch.
-template <int TPT>
-__device__ __forceinline__ void list_count(const float (&acc)[TPT], int n0, int N, float cut, uint32_t* wcnt,
-                                           unsigned long long (&m)[TPT]) {
-  uint32_t mine = 0;
-#pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    m[k] = __ballot(n0 + k < N && acc[k] >= cut);
-    mine += (uint32_t)__popcll(m[k]);
-  }
-  if (lane_id() == 0) wcnt[threadIdx.x >> 6] = mine;
+// The lowest of the 256 bins from which on there are at most `room` scores (1 .. 256).  Bin 0 and those above hold more.
+__device__ __forceinline__ int seg_bin(const uint32_t* bins, uint32_t room) {
+  const int lane = lane_id();
+  const uint4 c = *reinterpret_cast<const uint4*>(bins + 4 * lane);
+  const uint32_t s2 = c.w + c.z, s1 = s2 + c.y, s0 = s1 + c.x;
+  const uint32_t above = wave_suffix_sum(s0) - s0;             // in higher lanes' bins
+  const int j = above + s1 <= room ? 1 : above + s2 <= room ? 2 : above + c.w <= room ? 3 : 4;
+  const unsigned long long m = __ballot(above + s0 > room);    // a run of low lanes, lane 0 among them
+  const int last = 63 - __clzll((long long)(m | 1ull));
+  return 4 * last + __builtin_amdgcn_readlane(j, last);
 }
-template <bool SHARED, int NT, int TPT>
-__device__ __forceinline__ void list_write(const float (&acc)[TPT], int n0, const unsigned long long (&m)[TPT], const uint32_t* wcnt,
-                                           uint2* seg, uint32_t* count) {
-  const int wave = (int)(threadIdx.x >> 6);
-  uint32_t base = 0, total = 0;
+
+// Lists the segment of `tokens` tokens whose score 4 lane + k is x[k].  The cut is the lowest edge of a bin (256 over the
+// spread of the scores) that no more than `room` scores reach; where the bins are so coarse that a quarter of the room is
+// left, because one score lies far from all others, the bin below the cut is cut into 256 again.  SHARED: read in this launch.
+template <bool SHARED>
+__device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int seg, const ListRow& l, SegLds& sm) {
+  const int lane = lane_id(), room = l.room;
+  bool in[4];
+  float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
-  for (int w = 0; w < NT / kWave; ++w) {
-    const uint32_t c = wcnt[w];
-    base += w < wave ? c : 0u;
-    total += c;
+  for (int k = 0; k < 4; ++k) {
+    in[k] = 4 * lane + k < tokens;
+    const bool finite = in[k] && fabsf(x[k]) < INFINITY;
+    hi = finite ? fmaxf(hi, x[k]) : hi;
+    lo = finite ? fminf(lo, x[k]) : lo;
   }
+  // Up to half a segment's room: the lowest of the lanes' highest, which at least 64 scores reach and one far below the rest does not move
+  if (room <= kListSeg / 2) lo = hi > -INFINITY ? hi : INFINITY;
+  hi = wave_max(hi);
+  lo = -wave_max(-lo);
+  const uint32_t top = hi > -INFINITY ? score_key(hi) : 0u;
+  unsigned long long m[4];
+  int n = 0;
+  auto reach = [&](float c) {
+    n = 0;
 #pragma unroll
-  for (int k = 0; k < TPT; ++k) {
+    for (int k = 0; k < 4; ++k) {
+      m[k] = __ballot(in[k] && x[k] >= c);
+      n += __popcll(m[k]);
+    }
+  };
+  float cut = -INFINITY;
+  bool fits = true;
+  if (tokens > room) {
+    for (int zoom = 0;; ++zoom) {
+      *reinterpret_cast<uint4*>(sm.bins + 4 * lane) = make_uint4(0, 0, 0, 0);
+      const float spread = hi - lo, inv = 256.0f * __builtin_amdgcn_rcpf(spread);
+      // the wave's LDS operations complete in order; the fences only keep the compiler from moving them
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int k = 0; k < 4; ++k)  // (infinite scores: the bins at the ends; NaNs: the lowest)
+        if (in[k]) atomicAdd(&sm.bins[(uint32_t)fminf(fmaxf((x[k] - lo) * inv, 0.0f), 255.0f)], 1u);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int bin = seg_bin(sm.bins, (uint32_t)room);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const float step = spread * (1.0f / 256.0f);
+      cut = fmaf((float)bin, step, lo);
+      reach(cut);
+      if (n > room) {              // (the edge as a score and the edge between bins differ by a rounding; or all scores are equal)
+        cut = fmaf((float)(bin + 1), step, lo);
+        reach(cut);
+      }
+      fits = n <= room && cut == cut;      // (no cut: no score is finite)
+      if (!fits && zoom > 0) {     // (ties: the cut that they lie below)
+        cut = hi;
+        reach(cut);
+        fits = true;
+        break;
+      }
+      if (!fits || 4 * n >= 3 * room || zoom == 2 || !(spread < INFINITY)) break;
+      hi = cut;
+      lo = cut - step;
+    }
+  } else {
+    reach(cut);
+  }
+  *reinterpret_cast<uint4*>(sm.keys + 4 * lane) = make_uint4(0, 0, 0, 0);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  uint32_t base = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
     const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
-    if ((m[k] >> lane_id()) & 1ull) {
-      const uint2 e = make_uint2(score_key(acc[k]), (uint32_t)(n0 + k));
-      if constexpr (SHARED) st_agent(&seg[pos], e);
-      else seg[pos] = e;
+    if (fits && ((m[k] >> lane) & 1ull)) {
+      sm.keys[pos] = score_key(x[k]);
+      sm.toks[pos] = (uint8_t)(4 * lane + k);
     }
     base += (uint32_t)__popcll(m[k]);
   }
-  if (threadIdx.x == 0) {
-    if constexpr (SHARED) st_agent(count, total);
-    else *count = total;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const uint2 lim = make_uint2(fits ? score_key(cut) : 0xffffffffu, top);
+  if (4 * lane < room) {
+    const uint4 k4 = *reinterpret_cast<const uint4*>(sm.keys + 4 * lane);
+    const uint32_t t4 = sm.toks4[lane];
+    const size_t at = (size_t)seg * (room / 4) + lane;
+    if constexpr (SHARED) {
+      st_agent(reinterpret_cast<uint2*>(l.keys) + 2 * at, make_uint2(k4.x, k4.y));
+      st_agent(reinterpret_cast<uint2*>(l.keys) + 2 * at + 1, make_uint2(k4.z, k4.w));
+      st_agent(l.toks + at, t4);
+    } else {
+      reinterpret_cast<uint4*>(l.keys)[at] = k4;
+      l.toks[at] = t4;
+    }
   }
-}
-
-// A row's lists as the selection sees them
-struct ListView {
-  const uint2* list;     // of the row
-  int nsegs;             // segments of it
-  int seg_tokens;        // tokens (and entries of room) of a segment
-  int lanes;             // of those that load a segment's first 2 * lanes entries
-  uint32_t magic;        // 2^32 / lanes + 1
-  int n_cap;
-  int n;                 // tokens of the row
-};
-
-// Entries 2j, 2j + 1 of the thread: two adjacent ones of a segment, whatever the memory holds there (list_mask)
-template <bool SHARED, int NT, int EPT>
-__device__ __forceinline__ void list_load(const ListView& v, uint32_t (&key)[EPT], uint32_t (&tok)[EPT]) {
-  const __amdgpu_buffer_rsrc_t rs = agent_buffer(v.list);
-#pragma unroll
-  for (int j = 0; j < EPT / 2; ++j) {
-    const uint32_t g = (uint32_t)(j * NT) + threadIdx.x, seg = __umulhi(g, v.magic);
-    const int pos = (int)seg * v.seg_tokens + (int)(g - seg * (uint32_t)v.lanes) * 2;
-    const int at = (int)seg < v.nsegs && pos < v.n_cap ? pos : 0;
-    uint4 x;
-    if constexpr (SHARED) x = agent_load_u128(rs, (uint32_t)at * 8u);
-    else x = *reinterpret_cast<const uint4*>(v.list + at);
-    key[2 * j] = x.x;
-    tok[2 * j] = x.y;
-    key[2 * j + 1] = x.z;
-    tok[2 * j + 1] = x.w;
-  }
-}
-// ... and key 0 where there is no entry.  seg_cnt: entries of the segments.
-template <int NT, int EPT>
-__device__ __forceinline__ void list_mask(const ListView& v, const uint32_t* seg_cnt, uint32_t (&key)[EPT], uint32_t (&tok)[EPT]) {
-#pragma unroll
-  for (int j = 0; j < EPT / 2; ++j) {
-    const uint32_t g = (uint32_t)(j * NT) + threadIdx.x, seg = __umulhi(g, v.magic);
-    const uint32_t off = (g - seg * (uint32_t)v.lanes) * 2;
-    const uint32_t c = (int)seg < v.nsegs ? seg_cnt[min((int)seg, kListMaxSegs - 1)] : 0u;
-    key[2 * j] = off < c ? key[2 * j] : 0u;
-    key[2 * j + 1] = off + 1 < c ? key[2 * j + 1] : 0u;
-    tok[2 * j] = min(tok[2 * j], (uint32_t)v.n - 1u);        // (a stray entry can never become a stray address)
-    tok[2 * j + 1] = min(tok[2 * j + 1], (uint32_t)v.n - 1u);
+  if (lane == 0) {
+    if constexpr (SHARED) st_agent(l.lims + seg, lim);
+    else l.lims[seg] = lim;
   }
 }
 
@@ -323,34 +338,25 @@ __device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow,
   resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
 }
 
-// The same among listed scores that the threads hold (key 0: none; klo > 0).
-// more(f): calls f(valid, key, token) for listed scores that no thread holds, whole waves at a time, in the same order
-// each time; `over` (the same in all threads) says that there are any.  Places go by thread, then by wave of the rest.
+// The same among listed scores that the threads hold (key 0: none; klo > 0).  Places go by thread.
 // False: fewer than B scores are listed (the histogram is zero then).
-template <int EPT, typename Lds, typename More>
-__device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EPT], const uint32_t (&tok)[EPT], bool over,
-                                               More&& more, uint32_t klo, int shift, int bsel, const float* srow, int N,
-                                               int p0, int p1) {
+template <int EPT, typename Lds>
+__device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EPT], const uint32_t (&tok)[EPT], uint32_t klo, int shift,
+                                               int bsel, const float* srow, int N) {
   constexpr int NWV = Lds::kWaves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   uint32_t khi = 0xffffffffu;
   int need = bsel, n_cand;
-  FASA_T_DECL(6);
-  FASA_T(0);
-  auto count = [&](uint32_t d) { atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kSelBins - 1u)], 1u); };   // d: key - klo
   for (;;) {
     const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
       const uint32_t d = key[k] - klo;
-      if (d <= span) count(d);
+      if (d <= span) atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kSelBins - 1u)], 1u);
     }
-    if (over) more([&](bool valid, uint32_t k, uint32_t) { if (valid && k - klo <= span) count(k - klo); });
-    FASA_T(1);
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
     if (n_cand == 0) return false;
   }
-  FASA_T(2);
   const uint32_t span = khi - klo;
   uint32_t n_win = 0, cnd = 0;
 #pragma unroll
@@ -364,209 +370,196 @@ __device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EP
   const uint32_t incl = wave_prefix_sum(mine);
   if (lane == kWave - 1) sm.wtot[wave] = incl;
   __syncthreads();
-  uint32_t before = incl - mine, all = 0;
+  uint32_t before = incl - mine;
 #pragma unroll
-  for (int w = 0; w < NWV; ++w) {
-    const uint32_t x = sm.wtot[w];
-    before += w < wave ? x : 0u;
-    all += x;
+  for (int w = 0; w < NWV; ++w) before += w < wave ? sm.wtot[w] : 0u;
+  uint32_t p = before & 0xffffu, pc = before >> 16;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const bool w = key[k] > khi;
+    if (w) keep_place(sm, (int)p, 0, bsel, tok[k]);
+    p += w ? 1u : 0u;
   }
-  // Winners: a wave whose winners are other workgroups' share skips the writing (of 32 workgroups a row, all but one or two
-  // waves).  Candidates: few threads have one, so each takes its own one by one.
-  {
-    uint32_t p = (before & 0xffffu) - (uint32_t)p0;           // place in this workgroup's share
-    const uint32_t len = (uint32_t)(p1 - p0);
-    if (__ballot((int)p < (int)len && (int)(p + n_win) > 0) != 0ull) {
+  while (__ballot(cnd != 0u) != 0ull) {                       // few threads have a candidate: each takes its own one by one
+    const int j = __ffs((int)cnd) - 1;                        // (-1: none)
+    uint2 e = make_uint2(0u, 0u);
 #pragma unroll
-      for (int k = 0; k < EPT; ++k) {
-        const bool w = key[k] > khi;
-        if (w && p < len) sm.put((int)p, tok[k]);
-        p += w ? 1u : 0u;
-      }
-    }
-    uint32_t pc = before >> 16;
-    while (__ballot(cnd != 0u) != 0ull) {
-      const int j = __ffs((int)cnd) - 1;                      // (-1: none)
-      uint2 e = make_uint2(0u, 0u);
-#pragma unroll
-      for (int k = 0; k < EPT; ++k) e = j == k ? make_uint2(key[k], tok[k]) : e;
-      if (j >= 0 && pc < (uint32_t)kSelCand) sm.cand[pc] = e;
-      ++pc;
-      cnd &= cnd - 1u;
-    }
-  }
-  if (over) {
-    uint32_t w0 = 0, c0 = 0;                                  // of this wave
-    more([&](bool valid, uint32_t k, uint32_t) {
-      w0 += (uint32_t)__popcll(__ballot(valid && k > khi));
-      c0 += (uint32_t)__popcll(__ballot(valid && k >= klo && k <= khi));
-    });
-    __syncthreads();                                          // all have read wtot
-    if (lane == 0) { sm.wtot[wave] = w0; sm.wtot2[wave] = c0; }
-    __syncthreads();
-    w0 = all & 0xffffu; c0 = all >> 16;
-    for (int w = 0; w < wave; ++w) { w0 += sm.wtot[w]; c0 += sm.wtot2[w]; }
-    more([&](bool valid, uint32_t k, uint32_t n) {
-      const bool win1 = valid && k > khi, cnd1 = valid && k >= klo && k <= khi;
-      const unsigned long long mw = __ballot(win1), mc = __ballot(cnd1);
-      const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mw, w0));
-      const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, c0));
-      if (win1) keep_place(sm, (int)p, p0, p1, n);
-      if (cnd1 && c < (uint32_t)kSelCand) sm.cand[c] = make_uint2(k, n);
-      w0 += (uint32_t)__popcll(mw);
-      c0 += (uint32_t)__popcll(mc);
-    });
+    for (int k = 0; k < EPT; ++k) e = j == k ? make_uint2(key[k], tok[k]) : e;
+    if (j >= 0 && pc < (uint32_t)kSelCand) sm.cand[pc] = e;
+    ++pc;
+    cnd &= cnd - 1u;
   }
   __syncthreads();
-  FASA_T(3);
-  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
-  FASA_T(4);
-  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "entries: count %llu threshold %llu place %llu resolve (%d of %d) %llu (x10ns)\n",
-               FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2), need, n_cand, FASA_T_D(4, 3));
+  resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, 0, bsel);
   return true;
 }
 
-// What the threads do not hold.  Autoregressive scores of 0.98 have lists of 3 - 15 B, a segment's between none and all of it; us per
-// step, with one cut for all kinds of rows and lists read on from memory in every pass of the selection / like this: 8 rows of
-// 32768, 4 heads, B = 2048: 35.1 / 25.9, 128 rows of 16384, B = 256: 54.4 / 48.7, 32 rows of 32905, 7 heads, B = 6219: 75.2 / 59.9,
-// 8 rows of 131072, B = 1024: 121 / 57.2 (independent scores: 17.8, 41.4, 50.0, 40.6, either way).
+// ---------------------------------------------------------------------------------------------
+// Selection of a row out of its segments' lists
+// ---------------------------------------------------------------------------------------------
+// The bin of kListBins with (entries in bins above it) < need <= (entries from it on), found by every wave for itself: a round trip
+// to LDS and a scan, where the search that shares it among all threads has four barriers.  n = 0: fewer than `need` in all.
+struct BinAt {
+  int bin, above, n;
+};
+__device__ __forceinline__ BinAt wave_find_bin(const uint32_t* hist, uint32_t need) {
+  const int lane = lane_id();
+  const uint4 a = reinterpret_cast<const uint4*>(hist)[lane], b = reinterpret_cast<const uint4*>(hist)[kWave + lane];
+  const uint32_t sa = a.x + a.y + a.z + a.w, sb = b.x + b.y + b.z + b.w;
+  const uint32_t ib = wave_suffix_sum(sb), tb = (uint32_t)__builtin_amdgcn_readlane((int)ib, 0), ia = wave_suffix_sum(sa) + tb;
+  const bool up = tb >= need;
+  const uint4 c = up ? b : a;
+  const uint32_t incl = up ? ib : ia, s4 = incl - (up ? sb : sa);         // s4: in bins above this lane's four
+  const uint32_t s3 = s4 + c.w, s2 = s3 + c.z, s1 = s2 + c.y;
+  const unsigned long long m = __ballot(s4 < need && need <= incl);
+  if (m == 0ull) return {0, 0, 0};
+  const int l = __ffsll((long long)m) - 1;
+  const int j = s3 >= need ? 3 : s2 >= need ? 2 : s1 >= need ? 1 : 0;
+  const uint32_t above = j == 3 ? s4 : j == 2 ? s3 : j == 1 ? s2 : s1, n = j == 3 ? c.w : j == 2 ? c.z : j == 1 ? c.y : c.x;
+  return {(up ? kListBins / 2 : 0) + 4 * l + __builtin_amdgcn_readlane(j, l), __builtin_amdgcn_readlane((int)above, l),
+          __builtin_amdgcn_readlane((int)n, l)};
+}
+// log2 of the bins' width for keys from klo to ktop
+__device__ __forceinline__ int list_shift(uint32_t klo, uint32_t ktop) {
+  return max(0, 23 - __clz((int)(ktop > klo ? ktop - klo : 0u)));
+}
+__device__ __forceinline__ uint32_t wave_max_key(uint32_t v) {            // (in lane 63)
+  v = max(v, dpp_u32<0x111, 0xF>(v));
+  v = max(v, dpp_u32<0x112, 0xF>(v));
+  v = max(v, dpp_u32<0x114, 0xF>(v));
+  v = max(v, dpp_u32<0x118, 0xF>(v));
+  v = max(v, dpp_u32<0x142, 0xA>(v));
+  v = max(v, dpp_u32<0x143, 0xC>(v));
+  return v;
+}
 
-// What the lists of the wave's segments (lane l: segment l * waves + wave, c entries) hold beyond the threads' entries, to the
-// wave's own part of sm.extra, where it fits: 64 entries at a time, four times in flight.  Returns their number.
-template <bool SHARED, typename Lds>
-__device__ __forceinline__ uint32_t gather_own(Lds& sm, const ListView& v, uint32_t c) {
-  const int lane = lane_id(), wave = threadIdx.x >> 6, first = 2 * v.lanes;
-  uint2* out = sm.extra + wave * Lds::kExtraPerWave;
-  uint32_t have = 0;
-  unsigned long long m = __ballot((int)c > first);
-  const uint2* list = v.list;
-  int i0 = 0, n = 0;                                          // of the segment at hand
-  while (m != 0ull || i0 < n) {
-    uint2 x[4];
-    int left[4];
+// What select_listed has found: places 0 .. n_above - 1 of the set are filled, the others belong to the `need` best of the n_cand
+// candidates in sm.cand (as many as fit there), whose keys are klo and above.
+struct ListSet {
+  bool usable;
+  uint32_t klo;
+  int n_above, need, n_cand;
+  uint32_t from;           // the key from which on the row's scores were looked at
+};
+
+// Scores of segments that are not listed completely from klo on, from there to where their lists begin: f(in, key, token) for all lanes
+// of a wave, which takes 256 / waves tokens of every such segment, so that waves share what lies together; 16 segments at a time,
+// in two loads.  All threads call; there is a barrier ahead of the first f.
+template <bool SHARED, typename Lds, typename F>
+__device__ __forceinline__ void for_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo, F&& f) {
+  constexpr int NT = Lds::kThreads, LPS = kWave / Lds::kWaves, SPL = kWave / LPS;   // lanes per segment, segments per load
+  const int t = threadIdx.x, lane = t & 63, off = (t >> 6) * (4 * LPS) + 4 * (lane % LPS);
+  for (int c0 = 0; c0 < nsegs; c0 += NT) {
+    const uint2* p = l.lims + min(c0 + t, nsegs - 1);
+    const uint32_t mine = (SHARED ? ld_agent(p) : *p).x;
+    __syncthreads();                                          // all have read the last ones
+    sm.lim[t] = c0 + t < nsegs ? mine : 0u;
+    __syncthreads();
+    for (int s0 = 0; s0 < min(nsegs - c0, NT); s0 += kWave) {
+      const uint32_t lim = sm.lim[s0 + lane];
+      unsigned long long m = __ballot(lim > klo);
+      while (m != 0ull) {
+        float4 x[2];
+        int at[2];
+        uint32_t end[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (i0 >= n && m != 0ull) {
-        const int l = __ffsll((long long)m) - 1;
-        m &= m - 1ull;
-        n = min(__builtin_amdgcn_readlane((int)c, l), v.seg_tokens);
-        list = v.list + (size_t)(l * Lds::kWaves + wave) * v.seg_tokens;
-        i0 = first;
+        for (int j = 0; j < 2; ++j) {
+          at[j] = N;
+          end[j] = 0;
+#pragma unroll
+          for (int i = 0; i < SPL; ++i) {
+            if (m != 0ull) {
+              const int b = __ffsll((long long)m) - 1;
+              m &= m - 1ull;
+              const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)lim, b);
+              at[j] = lane / LPS == i ? (c0 + s0 + b) * kListSeg + off : at[j];
+              end[j] = lane / LPS == i ? e : end[j];
+            }
+          }
+          x[j] = *reinterpret_cast<const float4*>(srow + (at[j] < N ? at[j] : 0));   // (S is n_cap long, a multiple of 64)
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float xs[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t key = score_key(xs[k]);
+            f(at[j] + k < N && key >= klo && key < end[j], key, (uint32_t)(at[j] + k));
+          }
+        }
       }
-      left[j] = max(n - i0, 0);
-      const uint2* e = list + min(i0 + lane, max(n, 1) - 1);
-      x[j] = SHARED ? ld_agent(e) : *e;
-      i0 += kWave;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (lane < left[j]) out[have + (uint32_t)lane] = make_uint2(x[j].x, min(x[j].y, (uint32_t)v.n - 1u));
-      have += (uint32_t)min(left[j], kWave);
     }
   }
-  return have;
 }
-
-// A key that the B-th best of the listed scores reaches, found among those that the threads hold, if there are B of them from klo
-// on (else klo).  The histogram is zero at the call and, with a block barrier, at the end.
-template <int EPT, typename Lds>
-__device__ __forceinline__ uint32_t held_threshold(Lds& sm, const uint32_t (&key)[EPT], uint32_t klo, int shift, int bsel) {
-  uint32_t khi = 0xffffffffu;
-  int need = bsel, n_cand;
-  for (;;) {
-    const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-      const uint32_t d = key[k] - klo;
-      if (d <= span) atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kSelBins - 1u)], 1u);
-    }
-    if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
-    if (n_cand == 0) return klo;
-  }
-  __syncthreads();                                            // all have read thr
-  for (int i = threadIdx.x; i < kSelBins; i += Lds::kThreads) sm.hist[i] = 0;
-  if (threadIdx.x == 0) sm.thr[2] = 0;
-  __syncthreads();
-  return klo;
-}
-
-// What the lists hold beyond the threads' entries, from the key klo on, to LDS: pieces of 64 entries, numbered through all
-// segments; wave w takes pieces w, w + waves, ..., four in flight, to its own part of sm.extra.  Returns the wave's number of
-// entries; sm.thr[3] becomes 1 if there was no room.  The pieces' list lies in the histogram, which is zero at the call and, with a
-// block barrier, at the end.
+// The same to the wave's own part of sm.extra.  Returns their number; sm.thr[3] becomes 1 if there was no room.  The caller has a barrier
+// behind it.
 template <bool SHARED, typename Lds>
-__device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListView& v, uint32_t klo) {
-  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
-  static_assert(NT >= kListMaxSegs, "a thread a segment");
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const uint32_t first = 2u * (uint32_t)v.lanes, c = t < v.nsegs ? min(sm.seg_cnt[t], (uint32_t)v.seg_tokens) : 0u;
-  const uint32_t mine = c > first ? (c - first + kWave - 1u) / kWave : 0u;
-  uint32_t pieces;
-  const uint32_t before = block_prefix_sum<NT>(mine, sm.wtot, pieces);
-  for (uint32_t i = 0; i < mine; ++i)
-    if (before + i < (uint32_t)kSelBins) sm.hist[before + i] = (uint32_t)t << 16 | i;
-  __syncthreads();
-  uint2* out = sm.extra + wave * Lds::kExtraPerWave;
+__device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo) {
+  uint2* out = sm.extra + (threadIdx.x >> 6) * Lds::kExtraPerWave;
   uint32_t have = 0;
-  const int np = (int)min(pieces, (uint32_t)kSelBins);
-  for (int p0 = wave; p0 < np; p0 += 4 * NWV) {
-    uint2 x[4];
-    int left[4];                                              // entries of the piece
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int p = p0 + j * NWV;
-      const uint32_t d = sm.hist[min(p, np - 1)];
-      const int s = (int)(d >> 16), i0 = (int)(first + (d & 0xffffu) * kWave), n = (int)min(sm.seg_cnt[s], (uint32_t)v.seg_tokens);
-      left[j] = p < np ? n - i0 : 0;
-      const uint2* e = v.list + (size_t)s * v.seg_tokens + min(i0 + lane, n - 1);
-      x[j] = SHARED ? ld_agent(e) : *e;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bool in = lane < left[j] && x[j].x >= klo;
-      const unsigned long long m = __ballot(in);
-      const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, have));
-      if (in && at < (uint32_t)Lds::kExtraPerWave) out[at] = make_uint2(x[j].x, min(x[j].y, (uint32_t)v.n - 1u));
-      have += (uint32_t)__popcll(m);
-    }
-  }
-  if (lane == 0 && (have > (uint32_t)Lds::kExtraPerWave || pieces > (uint32_t)kSelBins)) sm.thr[3] = 1;
-  __syncthreads();
-  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  __syncthreads();
-  return have;
+  for_beyond<SHARED>(sm, l, nsegs, srow, N, klo, [&](bool in, uint32_t key, uint32_t tok) {
+    const unsigned long long b = __ballot(in);
+    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, have));
+    if (in && pos < (uint32_t)Lds::kExtraPerWave) out[pos] = make_uint2(key, tok);
+    have += (uint32_t)__popcll(b);
+  });
+  if (lane_id() == 0 && have > (uint32_t)Lds::kExtraPerWave) sm.thr[3] = 1;
+  return min(have, (uint32_t)Lds::kExtraPerWave);
 }
 
-// Selection of a row out of its segments' lists in memory (row_list.h).  kcut: what they were made with; ktop: the sample's
-// largest key.  SHARED: the lists were made in this launch.
-template <bool SHARED, int EPT, typename Lds>
-__device__ __forceinline__ void select_listed(Lds& sm, const ListView& v, const uint32_t* cnt, uint32_t kcut, uint32_t ktop,
-                                              int bsel, const float* srow, int N, int p0, int p1) {
-  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
-  static_assert(NT == kListMaxSegs, "a thread a segment");
+// Selection of a row out of its list (4 Q entries a thread) by all threads: places p0 .. p1 - 1 of its set to sm.put, as far as they
+// are known without ranking the candidates.  SHARED: listed in this launch.  Ends with a block barrier.
+template <bool SHARED, int Q, typename Lds>
+__device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, int bsel, const float* srow, int N, int p0, int p1) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves, EPT = 4 * Q;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t key[EPT], tok[EPT];
-  const int mine = lane * NWV + wave;                         // segment
-  uint32_t c = SHARED ? ld_agent(cnt + min(mine, v.nsegs - 1)) : cnt[min(mine, v.nsegs - 1)];
-  list_load<SHARED, NT, EPT>(v, key, tok);
+  const int nsegs = (N + kListSeg - 1) / kListSeg, per = l.room / 4, nq = nsegs * per;
+  const __amdgpu_buffer_rsrc_t rk = agent_buffer(l.keys);
+  uint2 lt = SHARED ? ld_agent(l.lims + min(t, nsegs - 1)) : l.lims[min(t, nsegs - 1)];
+  uint32_t key[EPT], tok4[Q];
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const int g = j * NT + t, at = g < nq ? g : 0;
+    uint4 x;
+    if constexpr (SHARED) x = agent_load_u128(rk, (uint32_t)at * 16u);
+    else x = reinterpret_cast<const uint4*>(l.keys)[at];
+    key[4 * j] = x.x; key[4 * j + 1] = x.y; key[4 * j + 2] = x.z; key[4 * j + 3] = x.w;
+  }
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const int g = j * NT + t, at = g < nq ? g : 0;
+    if constexpr (SHARED) tok4[j] = ld_agent(l.toks + at);
+    else tok4[j] = l.toks[at];
+  }
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  if (t == 0) sm.thr[2] = sm.thr[3] = 0;
-  c = mine < v.nsegs ? c : 0u;
-  sm.seg_cnt[mine] = c;
+  if (t == 0) { sm.thr[2] = sm.thr[3] = 0; sm.n_cnd = 0; }
+  for (int i = NT + t; i < nsegs; i += NT) {
+    const uint2 x = SHARED ? ld_agent(l.lims + i) : l.lims[i];
+    lt = make_uint2(max(lt.x, x.x), max(lt.y, x.y));
+  }
+  {
+    const uint32_t a = wave_max_key(lt.x), b = wave_max_key(lt.y);
+    if (lane == kWave - 1) { sm.wtot[wave] = a; sm.wtot2[wave] = b; }
+  }
+  // The tokens are needed much later, and only by the waves whose winners are in the share, so the compiler would move their loads
+  // there: 8 rows of 32768, B = 2048, 18.1 us, like this 17.0.
+#pragma unroll
+  for (int j = 0; j < Q; ++j) asm volatile("" : "+v"(tok4[j]));
+  __syncthreads();
   FASA_T_DECL(5);
   FASA_T(0);
-  const uint32_t sum = wave_prefix_sum(c), held = 2u * (uint32_t)v.lanes;
-  uint32_t beyond = 0;                                        // entries that the threads do not hold
-  if (__ballot(c > held) != 0ull) beyond = wave_prefix_sum(c > held ? min(c, (uint32_t)v.seg_tokens) - held : 0u);
-  if (lane == kWave - 1) { sm.wtot[wave] = sum; sm.wtot2[wave] = beyond; }
-  __syncthreads();
-  uint32_t M = 0, over = 0;
+  uint32_t klo = 1, ktop = 0;
 #pragma unroll
-  for (int w = 0; w < NWV; ++w) { M += sm.wtot[w]; over = max(over, sm.wtot2[w]); }
-  list_mask<NT, EPT>(v, sm.seg_cnt, key, tok);
-  FASA_T(1);
-  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "list counts arrive + barrier %llu M %d over %d of %d\n", FASA_T_D(1, 0), (int)M, (int)over, EPT * NT);
-  uint32_t have = 0;                                          // entries of this wave in sm.extra
+  for (int w = 0; w < NWV; ++w) { klo = max(klo, sm.wtot[w]); ktop = max(ktop, sm.wtot2[w]); }
+  uint32_t from = klo;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const bool in = j * NT + t < nq;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) key[4 * j + k] = in ? key[4 * j + k] : 0u;
+  }
+  bool over = false;                                          // there are entries that no thread holds:
+  uint32_t have = 0;                                          // so many of this wave's in sm.extra
   const uint2* extra = sm.extra + wave * Lds::kExtraPerWave;
   auto more = [&](auto&& f) {                                 // (a wave reads what it wrote itself)
     for (uint32_t i0 = 0; i0 < have; i0 += kWave) {
@@ -574,24 +567,149 @@ __device__ __forceinline__ void select_listed(Lds& sm, const ListView& v, const 
       f(i0 + (uint32_t)lane < have, x.x, x.y);
     }
   };
-  uint32_t klo = max(kcut, 1u);
-  bool usable = (int)M >= bsel;
-  if (over != 0 && usable) {
-    if (over <= (uint32_t)Lds::kExtraPerWave) {
-      have = gather_own<SHARED>(sm, v, c);
-    } else {
-      klo = held_threshold<EPT>(sm, key, klo, kcut ? first_shift(kcut, ktop) : 22, bsel);
-      have = gather_beyond<SHARED>(sm, v, klo);
-      usable = sm.thr[3] == 0;                                // (not: ties, a cut that could not be made)
+  uint32_t khi = 0;
+  int shift = 0, need = 0, n_cand = 0;
+  auto count = [&]() {
+    const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const uint32_t d = key[k] - klo;
+      if (d <= span) atomicAdd(&sm.hist[min(d >> shift, (uint32_t)kListBins - 1u)], 1u);
+    }
+    if (over) more([&](bool valid, uint32_t k, uint32_t) {
+      if (valid && k - klo <= span) atomicAdd(&sm.hist[min((k - klo) >> shift, (uint32_t)kListBins - 1u)], 1u);
+    });
+    __syncthreads();
+  };
+  auto clear = [&]() {
+    __syncthreads();                                          // all have read it
+    for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
+    __syncthreads();
+  };
+  // one range: true if it holds `need` entries
+  auto search = [&]() {
+    count();
+    const BinAt b = wave_find_bin(sm.hist, (uint32_t)need);
+    n_cand = b.n;
+    if (b.n == 0) return false;
+    need -= b.above;
+    narrow_range<kListBins>(klo, khi, (uint32_t)b.bin, shift);
+    shift = max(0, 23 - __clz((int)(khi - klo)));             // (khi - klo) >> shift < kListBins
+    return true;
+  };
+  // the range of the threshold among what is counted: all of it has at most kSelCand entries, or one key
+  auto narrow = [&](uint32_t lo) {
+    klo = lo; khi = 0xffffffffu; shift = list_shift(lo, ktop); need = bsel;
+    for (;;) {
+      if (!search()) return false;
+      if (n_cand <= kSelCand || klo == khi) return true;
+      clear();
+    }
+  };
+  if (__builtin_expect(!narrow(klo), false)) {
+    // Segments with more of the best than they had room for.  From a key that the B-th best of the listed entries reaches:
+    const ListSet none = {false, 0u, 0, 0, 0, from};
+    clear();
+    {
+      // no listed entry lies below the lowest of the completeness keys, but for those of a short last segment that is listed whole
+      const uint32_t a = wave_max_key(lt.x <= kListAll || nsegs > NT ? 0u : ~lt.x);
+      if (lane == kWave - 1) sm.wtot[wave] = a;
+      __syncthreads();
+      uint32_t b = 0;
+#pragma unroll
+      for (int w = 0; w < NWV; ++w) b = max(b, sm.wtot[w]);
+      bool enough = b != 0u && narrow(~b);
+      if (!enough) {
+        clear();
+        enough = narrow(1u);
+      }
+      clear();
+      if (!enough) return none;                                // fewer than B are listed
+    }
+    have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo);
+    __syncthreads();
+    if (sm.thr[3] != 0) {
+      // ... which so many of these segments' scores reach that they don't fit: they are counted, and those gathered that reach the
+      // bin of the threshold
+      const uint32_t lo = klo;
+      shift = list_shift(lo, ktop); need = bsel; khi = 0xffffffffu;
+      for_beyond<SHARED>(sm, l, nsegs, srow, N, lo, [&](bool in, uint32_t key, uint32_t) {
+        if (in) atomicAdd(&sm.hist[min((key - lo) >> shift, (uint32_t)kListBins - 1u)], 1u);
+      });
+      if (!search()) { clear(); return none; }
+      if (t == 0) sm.thr[3] = 0;
+      clear();
+      have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo);
+      __syncthreads();
+      if (sm.thr[3] != 0) return none;                         // (ties)
+    }
+    over = true;
+    from = klo;
+    if (!narrow(klo)) { clear(); return none; }                // (NaNs only)
+  }
+  const int n_above = bsel - need;
+  const uint32_t span = khi - klo;
+  uint32_t n_win = 0;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) n_win += key[k] > khi ? 1u : 0u;
+  const uint32_t incl = wave_prefix_sum(n_win);
+  uint32_t w0 = 0;                                            // winners of this wave in sm.extra
+  if (over) more([&](bool valid, uint32_t k, uint32_t) { w0 += (uint32_t)__popcll(__ballot(valid && k > khi)); });
+  if (lane == kWave - 1) { sm.wtot[wave] = incl; sm.wtot2[wave] = w0; }   // (all have read them: a barrier lies between)
+  const float inv_per = __builtin_amdgcn_rcpf((float)per);
+  auto token = [&](int j, int k) {                            // (quotients of at most 4096 by at most 64: exact)
+    const uint32_t seg = (uint32_t)(((float)(j * NT + t) + 0.5f) * inv_per);
+    return min(seg * (uint32_t)kListSeg + (tok4[j] >> (8 * k) & 255u), (uint32_t)N - 1u);
+  };
+  auto candidate = [&](uint32_t k, uint32_t tok) {
+    const uint32_t p = __builtin_amdgcn_atomic_inc32(&sm.n_cnd, 0xffffffffu, __ATOMIC_RELAXED, "workgroup");
+    if (p < (uint32_t)kSelCand) sm.cand[p] = make_uint2(k, tok);
+  };
+  if (p1 > n_above) {                                         // (of 32 workgroups a row, one or two)
+#pragma unroll
+    for (int j = 0; j < Q; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (key[4 * j + k] - klo <= span) candidate(key[4 * j + k], token(j, k));
+    if (over) more([&](bool valid, uint32_t k, uint32_t n) { if (valid && k - klo <= span) candidate(k, n); });
+  }
+  __syncthreads();
+  uint32_t before = incl - n_win, all = 0;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) {
+    const uint32_t x = sm.wtot[w];
+    before += w < wave ? x : 0u;
+    all += x;
+  }
+  {
+    uint32_t p = before - (uint32_t)p0;                       // place in this workgroup's share
+    const uint32_t len = (uint32_t)(p1 - p0);
+    if (__ballot((int)p < (int)len && (int)(p + n_win) > 0) != 0ull) {   // (of 32 workgroups a row, one or two waves)
+#pragma unroll
+      for (int j = 0; j < Q; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const bool w = key[4 * j + k] > khi;
+          if (w && p < len) sm.put((int)p, token(j, k));
+          p += w ? 1u : 0u;
+        }
     }
   }
-  if (usable && select_entries<EPT>(sm, key, tok, over != 0, more, klo, kcut ? first_shift(klo, max(ktop, klo)) : 22, bsel, srow, N, p0,
-                                    p1))
-    return;
-  // Or the sample misled, and the threshold lies below the cut, as a first guess by no more than its best lies above.
-  __syncthreads();                                            // (all have read the counts)
-  const float cut = key_score(kcut), down = (int)M >= bsel ? cut : cut - (key_score(ktop) - cut);
-  row_select<false>(sm, bsel, srow, N, p0, p1, down > -INFINITY ? score_key(down) : 0u, ktop);
+  if (over) {
+    uint32_t p = all;
+    for (int w = 0; w < wave; ++w) p += sm.wtot2[w];
+    more([&](bool valid, uint32_t k, uint32_t n) {
+      const unsigned long long b = __ballot(valid && k > khi);
+      const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, p));
+      if (valid && k > khi) keep_place(sm, (int)at, p0, p1, n);
+      p += (uint32_t)__popcll(b);
+    });
+  }
+  __syncthreads();
+  FASA_T(2);
+  FASA_T_PRINT(t == 0 && blockIdx.x == 0, "listed: threshold %llu places %llu (x10ns), %d entries, %d of %d candidates\n", FASA_T_D(1, 0),
+               FASA_T_D(2, 1), 4 * nq, need, n_cand);
+  return {true, klo, n_above, need, n_cand, from};
 }
 
 }  // namespace fasa

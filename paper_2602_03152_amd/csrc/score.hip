@@ -328,34 +328,29 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
   }
 }
 
-// Scores and lists (row_list.h).  1-D grid of rows * nslices workgroups of five waves: four score a slice of 256 * TPT tokens as
-// above; the fifth scores the row's sample with the same instructions - its lanes' tokens are the sample's - and has
-// the cut by the time the others have their scores.  What a workgroup does besides streaming costs its latency times the
-// rounds of workgroups, so there is little of it, and eight planes in flight (60 registers) for six workgroups per compute
-// unit: 128 rows of 16384, F = 16: 30.6 us with 16 in flight, 29.1 with 8.  (score_kernel alone 25.3; list writing is 1.4 of
-// the difference, the sample 1.4, the cut 0.9.  Several slices per workgroup, the next one's planes in the registers of
-// this one's: 29.1 / 29.7 / 33.0 for 1 / 2 / 4.)  The scores are stored non-temporal, since nothing reads them here: 0.7 us.
-// 8 rows of 32768: 5.9 us (with the adaptive histogram 6.3), 32 rows: 15.8 (15.4), 8 rows of 131072, F = 32: 25.6 (25.3).
+// Scores and lists (row_list.h).  1-D grid of rows * nslices workgroups of four waves, which score 1024 tokens as above; each lists its
+// own 256, with nothing to wait for.  Eight planes in flight leave room for eight workgroups per compute unit.  The scores are stored
+// non-temporal, since little of them is read again: 0.7 us of 29.
+constexpr int kListScoreNT = 256;
 template <typename ET, int NB, bool APPEND, int PAIR>
-__global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
+__global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
     const ET* __restrict__ q, ET* Kp, const int32_t* __restrict__ fc_idx, float* __restrict__ S, int rows, int nslices, int Hq, int Hkv,
     int F, int N_max, int n_cap, const int32_t* __restrict__ n_ctx_seq, const ET* __restrict__ k_new, const ET* __restrict__ v_new,
-    ET* Kc, ET* Vc, long long sb, long long sh, long long sn, PageMap pm, RowCtl* __restrict__ ctl, int budget_max,
+    ET* Kc, ET* Vc, long long sb, long long sh, long long sn, PageMap pm, int budget_max,
     const int32_t* __restrict__ budget_seq, ListOut lists) {
   constexpr int D = kHeadDim;
-  constexpr int TPT = ScoreTraits<ET>::TPT, NT = kListScoreNT, SL = NT * TPT, SEG = kWave * TPT;
+  constexpr int TPT = ScoreTraits<ET>::TPT, NT = kListScoreNT, SL = NT * TPT;
+  static_assert(TPT == 4, "a wave scores a segment");
   constexpr int NW = 8;                                            // planes in flight per thread
   constexpr bool PAIRS = PAIR == FASA_PAIR_LIST;
   constexpr int PAIR_SHIFT = PAIR == FASA_PAIR_INTERLEAVED ? 1 : 0;
   constexpr int PAIR_ADD = PAIR == FASA_PAIR_INTERLEAVED ? 1 : D / 2;
-  __shared__ float qsum[NT + kWave];
-  __shared__ int32_t fcl[NT + kWave];
+  __shared__ SegLds seg[NT / kWave];
+  __shared__ float qsum[NT];
+  __shared__ int32_t fcl[NT];
   __shared__ float2 qs[D / 2];
-  __shared__ float2 cut_top;
-  __shared__ uint32_t wcnt[NT / kWave];
-  __shared__ __align__(16) uint32_t bins[256];
   __shared__ ET knew[APPEND ? D : 1];
-  __shared__ uint2 kpair[APPEND ? D / 2 : 1];
+  __shared__ uint32_t kpair[APPEND ? D / 2 : 1];
 
   int row, slice;
   row_slice_of_block(rows, nslices, row, slice);
@@ -364,8 +359,6 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
   const int t = threadIdx.x;
   const int N = seq_n_ctx(n_ctx_seq, b, N_max);
   if (slice * SL >= N) return;
-  const bool sampler = __builtin_amdgcn_readfirstlane(t) >= NT;
-  if (sampler) __builtin_amdgcn_s_setprio(3);                      // the others wait for its cut
 
   const ET* qh = q + ((size_t)b * Hq + (size_t)h * G) * D + (t & (D - 1));
   ET qcol[kMaxGroup];
@@ -380,7 +373,7 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
   const int n_app = N - 1;
   const size_t plane = (size_t)n_cap * 2;
   const ET* base = Kp + (size_t)row * F * n_cap * 2;
-  const int n0 = sampler ? list_sample_token<ET>(t - NT, APPEND ? N - 1 : N) : (slice * NT + t) * TPT;
+  const int n0 = (slice * NT + t) * TPT;
   const uint32_t at = (uint32_t)(n0 < N ? n0 : 0) * (uint32_t)(2 * sizeof(ET));
   auto load = [&](int f) {
     return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base + (size_t)(NB ? f : min(f, F - 1)) * plane) + at);
@@ -404,7 +397,7 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
       if (t < D) knew[t] = newkv;
     }
   }
-  const ListCut lc = ListCut::plan<TPT>(seq_bsel(budget_seq, b, N, budget_max), N);   // (under the loads)
+  const int room = lists.room ? lists.room : list_room(seq_bsel(budget_seq, b, N, budget_max), N, lists.cap);   // (under the loads)
   const bool own_wg = APPEND && n_app / SL == slice;
   __syncthreads();
   if (t < D / 2) {
@@ -413,8 +406,7 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
     qs[t] = make_float2(qsum[dl], qsum[dh]);
     if constexpr (APPEND) {
       const ET lo = knew[dl], hi = knew[dh];
-      if constexpr (sizeof(ET) == 2) kpair[t] = make_uint2((uint32_t)lo | ((uint32_t)hi << 16), 0u);
-      else kpair[t] = make_uint2(__float_as_uint(lo), __float_as_uint(hi));
+      kpair[t] = (uint32_t)lo | ((uint32_t)hi << 16);
       if (own_wg && t < F) {
         ET* o = Kp + (((size_t)row * F + t) * n_cap + n_app) * 2;
         o[0] = lo;
@@ -444,43 +436,29 @@ __global__ __launch_bounds__(kListScoreNT + kWave, 6) void score_list_kernel(
     for (int f0 = 0; f0 + NW < FP; f0 += NW) planes(f0, std::true_type{});
   }
   planes(FP - NW, std::false_type{});
-  if (sampler) {
-    float top = INFINITY, cut = -INFINITY;
-    if (N >= kListMinCtx && lc.r <= SEG) cut = lc.take(acc, bins, top);
-    if (t == NT) {
-      cut_top = make_float2(cut, top);
-      if (slice == 0) { ctl[row].list_cut = score_key(cut); ctl[row].list_top = score_key(top); }
+  if (APPEND && n_app >= n0 && n_app < n0 + TPT) {               // the planes did not hold the appended token yet
+    float s = 0.f;
+    for (int f = 0; f < F; ++f) {
+      const float2 qf = qs[f];
+      const uint32_t x = kpair[f];
+      s = fmaf(qf.y, bf16_hi(x), fmaf(qf.x, bf16_lo(x), s));
     }
-  } else {
-    if (APPEND && n_app >= n0 && n_app < n0 + TPT) {           // the planes did not hold the appended token yet
-      float s = 0.f;
-      for (int f = 0; f < F; ++f) {
-        const float2 qf = qs[f];
-        const uint2 x = kpair[f];
-        if constexpr (sizeof(ET) == 2) s = fmaf(qf.y, bf16_hi(x.x), fmaf(qf.x, bf16_lo(x.x), s));
-        else s = fmaf(qf.y, __uint_as_float(x.y), fmaf(qf.x, __uint_as_float(x.x), s));
-      }
 #pragma unroll
-      for (int k = 0; k < TPT; ++k) acc[k] = n_app - n0 == k ? s : acc[k];
-    }
-    if (n0 < N) {
-      float* out = S + (size_t)row * n_cap + n0;
-      if (n0 + TPT <= N) {
-        if constexpr (TPT == 4) __builtin_nontemporal_store(f32x4_t{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<f32x4_t*>(out));
-        else *reinterpret_cast<float2*>(out) = make_float2(acc[0], acc[1]);
-      } else {
+    for (int k = 0; k < TPT; ++k) acc[k] = n_app - n0 == k ? s : acc[k];
+  }
+  if (n0 < N) {
+    float* out = S + (size_t)row * n_cap + n0;
+    if (n0 + TPT <= N) {
+      __builtin_nontemporal_store(f32x4_t{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<f32x4_t*>(out));
+    } else {
 #pragma unroll
-        for (int k = 0; k < TPT; ++k)
-          if (n0 + k < N) out[k] = acc[k];
-      }
+      for (int k = 0; k < TPT; ++k)
+        if (n0 + k < N) out[k] = acc[k];
     }
   }
-  __syncthreads();
-  unsigned long long m[TPT];
-  if (!sampler) list_count(acc, n0, N, cut_top.x, wcnt, m);
-  __syncthreads();
-  if (sampler) return;
-  list_write<false, NT>(acc, n0, m, wcnt, lists.list + (size_t)row * n_cap + slice * SL, lists.cnt + (size_t)row * kListCntPitch + slice);
+  const int ls = __builtin_amdgcn_readfirstlane(slice * (SL / kListSeg) + (t >> 6));
+  if (ls * kListSeg < N)
+    seg_list<false>(acc, min(N - ls * kListSeg, kListSeg), ls, ListRow::at(lists.list, lists.lims, row, n_cap, N, room), seg[t >> 6]);
   if constexpr (APPEND) {
     if (own_wg) {   // the whole new row to K (threads 0..127) and V (threads 128..255)
       ET* dst = (t < D ? Kc : Vc) + kv_row_offset(pm, b, n_app, sb, sn) + h * sh + (t & (D - 1));
@@ -596,41 +574,41 @@ hipError_t launch_score(const fasa_shape& s, const void* q, const void* Kp, cons
 }
 
 template <typename ET, int NB, bool APPEND, int PAIR>
-static hipError_t launch_score_list_v(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S, RowCtl* ctl,
+static hipError_t launch_score_list_v(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S,
                                       const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap) {
   const int rows = s.batch * s.n_kv_heads;
   const int per_block = kListScoreNT * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per_block - 1) / per_block;
-  return launch("fasa_score_list", score_list_kernel<ET, NB, APPEND, PAIR>, dim3(rows * nslices), dim3(kListScoreNT + kWave), st,
+  return launch("fasa_score_list", score_list_kernel<ET, NB, APPEND, PAIR>, dim3(rows * nslices), dim3(kListScoreNT), st,
                 (const ET*)q, (ET*)Kp,
                 fc_idx, S, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, (const ET*)ap.k_new,
                 (const ET*)ap.v_new, (ET*)ap.K, (ET*)ap.V, (long long)s.kv_stride_b, (long long)s.kv_stride_h,
-                (long long)s.kv_stride_n, ap.pm, ctl, s.budget, rl.budget, lists);
+                (long long)s.kv_stride_n, ap.pm, s.budget, rl.budget, lists);
 }
 template <typename ET, bool APPEND, int PAIR>
-static hipError_t launch_score_list_f(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S, RowCtl* ctl,
+static hipError_t launch_score_list_f(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S,
                                       const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap) {
   switch (s.n_fc) {
-    case 8: return launch_score_list_v<ET, 1, APPEND, PAIR>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
-    case 16: return launch_score_list_v<ET, 2, APPEND, PAIR>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
-    case 24: return launch_score_list_v<ET, 3, APPEND, PAIR>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
-    case 32: return launch_score_list_v<ET, 4, APPEND, PAIR>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
-    default: return launch_score_list_v<ET, 0, APPEND, PAIR>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
+    case 8: return launch_score_list_v<ET, 1, APPEND, PAIR>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
+    case 16: return launch_score_list_v<ET, 2, APPEND, PAIR>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
+    case 24: return launch_score_list_v<ET, 3, APPEND, PAIR>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
+    case 32: return launch_score_list_v<ET, 4, APPEND, PAIR>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
+    default: return launch_score_list_v<ET, 0, APPEND, PAIR>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
   }
 }
 template <typename ET, bool APPEND>
-static hipError_t launch_score_list_p(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S, RowCtl* ctl,
+static hipError_t launch_score_list_p(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S,
                                       const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap) {
   switch (s.pairing) {
-    case FASA_PAIR_INTERLEAVED: return launch_score_list_f<ET, APPEND, FASA_PAIR_INTERLEAVED>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
-    case FASA_PAIR_LIST: return launch_score_list_f<ET, APPEND, FASA_PAIR_LIST>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
-    default: return launch_score_list_f<ET, APPEND, FASA_PAIR_ROTATE_HALF>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
+    case FASA_PAIR_INTERLEAVED: return launch_score_list_f<ET, APPEND, FASA_PAIR_INTERLEAVED>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
+    case FASA_PAIR_LIST: return launch_score_list_f<ET, APPEND, FASA_PAIR_LIST>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
+    default: return launch_score_list_f<ET, APPEND, FASA_PAIR_ROTATE_HALF>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
   }
 }
-hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S, RowCtl* ctl,
+hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const int32_t* fc_idx, float* S,
                              const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap) {
   if (s.dtype != FASA_BF16) return hipErrorInvalidValue;       // (plan_list)
-  return ap.k_new ? launch_score_list_p<uint16_t, true>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap)
-                  : launch_score_list_p<uint16_t, false>(s, q, Kp, fc_idx, S, ctl, lists, st, rl, ap);
+  return ap.k_new ? launch_score_list_p<uint16_t, true>(s, q, Kp, fc_idx, S, lists, st, rl, ap)
+                  : launch_score_list_p<uint16_t, false>(s, q, Kp, fc_idx, S, lists, st, rl, ap);
 }
 
 hipError_t launch_hist(const fasa_shape& s, const float* S, uint32_t* hist, hipStream_t st) {

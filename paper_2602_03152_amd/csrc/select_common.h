@@ -122,10 +122,11 @@ __device__ __forceinline__ void rank_sample(float sval, uint32_t* sample, uint32
 // ---------------------------------------------------------------------------------------------
 // The threshold bin, which holds a key of klo .. khi, as the next range.  The last bin reaches up to khi; no other beyond it: a
 // bin that a NaN's key lies in may end past the largest key there is.
+template <int BINS = kSelBins>
 __host__ __device__ __forceinline__ void narrow_range(uint32_t& klo, uint32_t& khi, uint32_t bin, int shift) {
   klo += bin << shift;
   const uint32_t left = khi - klo, width = (1u << shift) - 1u;
-  if (bin + 1 < (uint32_t)kSelBins) khi = klo + (width < left ? width : left);
+  if (bin + 1 < (uint32_t)BINS) khi = klo + (width < left ? width : left);
 }
 // After the counting: true once klo .. khi is the final range (need of its n_cand scores are taken, and all
 // above it); else the range to count next, the histogram zeroed - the same range, with n_cand 0, if fewer than

@@ -13,6 +13,8 @@
 //                  histogram), one workgroup per row: float32 problems that fill the machine.
 //
 // See plan_step and plan_list for where the lines lie; beyond them fused.hip splits a row over many workgroups.
+#include <type_traits>
+
 #include "mfma_tile.h"
 #include "row_list.h"
 #include "score_common.h"
@@ -48,9 +50,9 @@ struct StepArgs {
   float scale_log2e;
   // list_kernel: the rows' lists (row_list.h), workgroups per row, their partials [row][nwgs]
   uint2* list;             // [row][n_cap]
-  uint32_t* cnt;           // [row][kListCntPitch]
-  int lanes;
-  uint32_t magic;
+  uint2* lims;             // [row][kListLimPitch]
+  int room;                // places of a segment's list; 0: sequences have lengths and budgets of their own (list_room)
+  int cap;                 // places that a workgroup's threads hold
   int nwgs;
   float* part_acc;
   float* part_ml;
@@ -80,9 +82,9 @@ struct RowLds {
   float m[kWaves][GM], l[kWaves][GM];
   float scs[kWaves][16];
   uint32_t wtot[kWaves], wtot2[kWaves];
-  uint32_t seg_cnt[kListMaxSegs];                            // entries of the row's segments
   uint32_t thr[4];
-  uint32_t n_list;
+  uint32_t lim[NT];                                          // where lists of segments begin (list_kernel)
+  uint32_t n_list, n_cnd;
   int p_new;                                                 // place of the appended row in wl, or -1
   __device__ __forceinline__ void put(int place, uint32_t tok) { wl[place] = tok; }
 };
@@ -105,8 +107,7 @@ __device__ __forceinline__ bool select_list(Lds& sm, int M, uint32_t kcut, uint3
     key[k] = i < M ? score_key(__uint_as_float(e.x)) : 0u;
     tok[k] = e.y;
   }
-  return select_entries<EPT>(sm, key, tok, false, [](auto&&) {}, max(kcut, 1u), kcut ? first_shift(kcut, ktop) : 22, bsel, srow, N,
-                             0, bsel);
+  return select_entries<EPT>(sm, key, tok, max(kcut, 1u), kcut ? first_shift(kcut, ktop) : 22, bsel, srow, N);
 }
 
 // Selection of a row inside its list, or - should it be shorter than B or longer than its room, because the sample misled or
@@ -128,27 +129,30 @@ __device__ __forceinline__ void select_row(Lds& sm, int M, uint32_t kcut, uint32
 // Attention over the tokens in sm.wl[0 .. cnt): T is written, and every wave leaves its (max, sum, weighted V)
 // in LDS (a block barrier ago when this returns).  p0: place of the first of them in T; with_q: a tile that has the queries.  Wave w takes 16-row tiles w, w + waves, ... (bf16:
 // mfma_tile.h; float32: vector ALUs).
-template <typename ET, int GM, typename Lds>
+// ready: how many of the tokens are known already; late(put), called by all threads if that is fewer than cnt, calls put(i, token) for the others.  Tiles
+// of known tokens alone are requested before that.
+struct NothingLate { template <typename Put> __device__ void operator()(Put&&) const {} };
+template <typename ET, int GM, typename Lds, typename Late = NothingLate>
 __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, int b, int h, int G, int cnt, int n_app,
-                                           int p0 = 0, const MfmaTile<GM>* with_q = nullptr) {
+                                           int p0 = 0, const MfmaTile<GM>* with_q = nullptr, int ready = 1 << 30, Late&& late = Late()) {
+  constexpr bool kLate = !std::is_same<typename std::decay<Late>::type, NothingLate>::value;
+  static_assert(!kLate || sizeof(ET) == 2, "float32 steps know all tokens");
   constexpr int D = kHeadDim;
   constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const ET* q = (const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D;
   // T, and what the gather reads: the row's element offset / 8, padded to whole tiles with the last row
   const bool paged = a.pm.table != nullptr;
-  {
-    int32_t* trow = a.T + (size_t)row * a.t_pitch + p0;
-    for (int i = t; i < cnt; i += NT) {
-      const int n = (int)sm.wl[i];
-      trow[i] = n;
-      if (n == n_app) sm.p_new = i;
-      const uint32_t e = (uint32_t)((unsigned long long)kv_row_offset(a.pm, paged ? b : 0, n, a.sb, a.sn) >> 3);
-      sm.wl[i] = e;
-      if (i == cnt - 1)
-        for (int j = cnt; j & 15; ++j) sm.wl[j] = e;
-    }
-  }
+  int32_t* trow = a.T + (size_t)row * a.t_pitch + p0;
+  auto known = [&](int i, int n) {
+    trow[i] = n;
+    if (n == n_app) sm.p_new = i;
+    const uint32_t e = (uint32_t)((unsigned long long)kv_row_offset(a.pm, paged ? b : 0, n, a.sb, a.sn) >> 3);
+    sm.wl[i] = e;
+    if (i == cnt - 1)
+      for (int j = cnt; j & 15; ++j) sm.wl[j] = e;
+  };
+  for (int i = t; i < (kLate ? min(ready, cnt) : cnt); i += NT) known(i, (int)sm.wl[i]);
   __syncthreads();
   const ET* Kb = (const ET*)a.K + (paged ? 0 : b * a.sb) + h * a.sh;
   const ET* Vb = (const ET*)a.V + (paged ? 0 : b * a.sb) + h * a.sh;
@@ -180,14 +184,31 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
       for (int i = 0; i < 4; ++i) kv.vr[i] = *reinterpret_cast<const uint4*>(vp[i]);
     };
     const int jw = wave * 16;
+    TileKV<uint16_t> kv;
+    if constexpr (kLate) {
+      const bool early = ready >= cnt || jw + 16 <= ready;
+      if (early && jw < cnt) {
+        load_k(kv, jw);
+        load_v(kv, jw);
+      }
+      if (ready < cnt) {
+        late(known);
+        __syncthreads();
+        if (!early && jw < cnt) {
+          load_k(kv, jw);
+          load_v(kv, jw);
+        }
+      }
+    }
     tile.reset();
     if (jw < cnt) {
       const int n_tiles = (cnt - jw + 16 * NWV - 1) / (16 * NWV);
-      TileKV<uint16_t> kv;
       float sv[4];
       if (!with_q) tile.load_q(q, lo, hi, G);
-      load_k(kv, jw);
-      load_v(kv, jw);
+      if constexpr (!kLate) {
+        load_k(kv, jw);
+        load_v(kv, jw);
+      }
       for (int i = 0; i + 1 < n_tiles; ++i) {
         const int j0 = jw + 16 * NWV * i;
         tile.logits(kv, a.scale_log2e, sv);
@@ -577,15 +598,16 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // nwgs workgroups per row; the scores lie in S, the lists of the largest in `list` (score_list_kernel).  Every workgroup of a
 // row finds the row's set, out of the same lists and so in the same order, and attends over its share of it: nothing about
 // the selection is left open for the workgroup that merges, and all gather the same number of rows (fused.hip's slices
-// differ by 14 %, and leave a threshold bin to resolve at the end).  A chain of round trips: once the lists are there, counts
-// 0.5 - 1.2 us by length, histogram 0.5 - 0.9, threshold 0.5 - 0.8, places 1.2 - 2.6, candidates 0.4 - 1, rows 2.3 (784 rows a
-// workgroup: 10.4), partial and ticket 1.4, merge 0.9 - 1.3.  us, both launches, fused.hip or row_kernel / like this: 8 rows of 32768, 4 heads, B = 2048:
-// 21.2 / 19.0; 32 rows, 7 heads, B = 6200: 53.0 / 49.4; 8 rows of 131072, F = 32, B = 1024: 40.8 / 41.2; 64 rows of 65536, B = 700:
-// 80.9 / 71.9; 128 rows of 16384, B = 256: 41.7 / 41.3, 512 rows of 8192, F = 8: 62.1 / 49.1.
-template <int G, int EPT>
+// differ by 14 %, and leave a threshold bin to resolve at the end).  A chain of round trips and of the instructions between them.
+// The candidates of the threshold bin are ranked by the one or two workgroups whose shares end in it, while the rows of the
+// tokens already known are under way.  us per step, lists of 1024 tokens by a cut of a sample of the row, and candidates ranked by all
+// workgroups ahead of the gather / like this: 8 rows of 32768, 4 heads, B = 2048: 17.8 / 16.9; 32 rows, 7 heads, B = 6219: 49.9 / 45.2;
+// 8 rows of 131072, F = 32, B = 1024: 40.5 / 37.4; 128 rows of 16384, B = 256: 41.3 / 38.4; 64 rows of 126490, 7 heads, B = 6250 (which had
+// the split form): 57.3 / 43.9; 3 rows of 96425, 4 heads, B = 3490: 26.4 / 20.6; 2 rows of 6987, F = 32, B = 911: 15.9 / 16.3.
+template <int G, int Q>
 __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
   using ET = uint16_t;
-  constexpr int D = kHeadDim, SEG = kListScoreNT * ScoreTraits<ET>::TPT;
+  constexpr int D = kHeadDim;
   __shared__ RowLds<kListNT, G, 1, kListMaxShare> sm;
   __shared__ float red[G];
   __shared__ uint32_t ticket;
@@ -600,15 +622,32 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
   if (p0 >= bsel) return;
   FASA_T_DECL(8);
   FASA_T(0);
-  const uint32_t kcut = a.ctl[row].list_cut, ktop = a.ctl[row].list_top;
+  const float* srow = a.S + (size_t)row * a.n_cap;
+  const ListRow list = ListRow::at(a.list, a.lims, row, a.n_cap, N, a.room ? a.room : list_room(bsel, N, a.cap));
   MfmaTile<G> tile;
-  tile.load_q((const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D, lane & 15, lane >> 4);
-  const ListView v = {a.list + (size_t)row * a.n_cap, (N + SEG - 1) / SEG, SEG, a.lanes, a.magic, a.n_cap, N};
   if (t == 0) sm.p_new = -1;
-  select_listed<false, EPT>(sm, v, a.cnt + (size_t)row * kListCntPitch, kcut, ktop, bsel, a.S + (size_t)row * a.n_cap, N, p0, p1);
+  const ListSet set = select_listed<false, Q>(sm, list, bsel, srow, N, p0, p1);
+  tile.load_q((const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D, lane & 15, lane >> 4);
+  int ready = set.n_above - p0;
+  if (!set.usable) {
+    row_select<false>(sm, bsel, srow, N, p0, p1);
+    ready = p1 - p0;
+  } else if (set.n_cand > kSelCand && ready < p1 - p0) {       // ties that no list of candidates holds
+    resolve_threshold(sm, set.klo, bsel, set.need, set.n_cand, srow, N, p0, p1);
+    ready = p1 - p0;
+  }
   FASA_T(1);
-  row_attend<ET, G>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile);
+  // the candidates are ranked while the rows of the others are under way
+  row_attend<ET, G>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile, ready, [&](auto&& put) {
+    constexpr int P = kListNT / kSelCand;
+    if ((t & ~(kWave - 1)) / P < set.n_cand) {                // (the waves that have any)
+      const int ci = t / P;
+      const int rank = rank_in_list<P>(sm.cand, set.n_cand, ci), p = set.n_above + rank;
+      if (t % P == 0 && ci < set.n_cand && rank < set.need && p >= p0 && p < p1) put(p - p0, (int)sm.cand[ci].y);
+    }
+  });
   FASA_T(2);
+  if (wg == 0 && t == 0) a.ctl[row].list_cut = set.from;      // (here: what waits for a load would wait for a store ahead of it too)
   if (nvalid == 1) {
     write_output(a, sm, b, h, G);
     return;
@@ -718,38 +757,26 @@ static hipError_t launch_step_f(const StepArgs& a, hipStream_t st) {
     default: return launch_step_v<ET, 0, GM>(a, st);
   }
 }
-// What the selection loads of a row's lists without asking: `lanes` threads a segment, two entries each, so that a
-// segment's list as the sample should make it, and two and a half standard deviations (of the sample and of the segment) more, is
-// loaded.  Returns the entries per thread (even), 0: more than fit.
-int list_loads(int n, int bsel, int seg_tokens, int sample, int nt, int most, int* lanes_out) {
-  const int nsegs = (n + seg_tokens - 1) / seg_tokens;
+// Places of the threads' lists, whole quads for each of nt threads, that a row's take; 0: more than `most` quads, or segments.
+int list_cap(int n, int bsel, int nt, int most) {
+  const int nsegs = (n + kListSeg - 1) / kListSeg;
   if (nsegs > kListMaxSegs) return 0;
-  const float r = (float)list_rank(bsel, n, sample);
-  const float frac = n < kListMinCtx || r > (float)sample ? 1.f : r / (float)sample, seg = (float)(n < seg_tokens ? n : seg_tokens);
-  const float want = fminf(seg * frac + 2.5f * seg * sqrtf(r) / (float)sample + 3.5f * sqrtf(seg * frac) + 2.f, (float)seg_tokens);
-  const int rounds = (nsegs * (((int)want + 1) / 2) + nt - 1) / nt;
-  if (rounds > most / 2) return 0;
-  int lanes = rounds * nt / nsegs;
-  if (lanes > seg_tokens / 2) lanes = seg_tokens / 2;
-  if (lanes < 2) return 0;
-  *lanes_out = lanes;
-  return 2 * rounds;
+  const int q = (nsegs * (list_room(bsel, n, 1 << 30) / 4) + nt - 1) / nt;
+  const int held = q <= 4 ? q : q <= 6 ? 6 : 8;                // (the instances there are)
+  return q <= most && held <= most ? held * 4 * nt : 0;
 }
 
 ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
-  ListPlan p{0, 0, 0};
+  ListPlan p{0, 0};
   if (s.dtype != FASA_BF16) return p;                          // (float32 rows are attended on the vector ALUs here)
   const long long most = pm.table ? (long long)pm.n_pool * s.kv_stride_b + (1ll << pm.shift) * s.kv_stride_n
                                   : (long long)s.n_ctx * s.kv_stride_n;
   if ((most >> 3) >= 0xfffffff0ll) return p;
   const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx, rows = s.batch * s.n_kv_heads;
-  // 32 entries a thread, which is what its registers hold beside the tiles: rows of up to 17408 tokens with half of them
-  // selected, 20480 with 40 %, 25600 with 30 %, 28672 with 25 %, 33792 with 20 %, 34816 with 18.9 %, 46080 with 12.5 %, 69632 with 6 %.
-  // Longer ones take the split form (18.9 %, us per step, of 34816 tokens / of 34817: 32 rows, 7 heads: 51.6 / 57.5; 8 rows, 4 heads:
-  // 24.6 / 27.6).
-  int lanes = 0;
-  const int need = list_loads(s.n_ctx, bsel, 1024, 256, kListNT, 32, &lanes);
-  if (!need) return p;
+  // 32 entries a thread, which is what its registers hold beside the tiles: rows of up to 22000 tokens with half of them
+  // selected, 49000 with 18.9 %, 67000 with 12.5 %.
+  const int cap = list_cap(s.n_ctx, bsel, kListNT, 8);
+  if (!cap) return p;
   // One workgroup up to B = 256: what it gathers (50 KB per us) takes less than a hand-over and a merge.  us with 1 / 2 / as many as
   // fit: 8 rows of 16384, B = 128: 12.7 / 14.3 / 14.3, 256: 14.6 / 15.5 / 15.1, 320: 15.3 / 16.0 / 15.1; 128 rows, 256: 41.7 / 42.9.
   // Beyond, as many as fit at once, one per compute unit, with at least 64 tokens each: 80 rows, B = 700: 36.6 / 35.6 / 34.5 (3) /
@@ -762,20 +789,19 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   const int share = ((bsel + w - 1) / w + 15) / 16 * 16;
   if (share > kListMaxShare) return p;
   p.nwgs = (bsel + share - 1) / share;
-  p.ept = need <= 4 ? 4 : need <= 8 ? 8 : need <= 12 ? 12 : need <= 16 ? 16 : need <= 24 ? 24 : 32;
-  p.lanes = lanes;
+  p.cap = cap;
   return p;
 }
 
 template <int G>
-static hipError_t launch_list_g(const StepArgs& a, int ept, hipStream_t st) {
-  switch (ept) {
+static hipError_t launch_list_g(const StepArgs& a, hipStream_t st) {
+  switch (a.cap / (4 * kListNT)) {
+    case 1: return launch("fasa_list", list_kernel<G, 1>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 2: return launch("fasa_list", list_kernel<G, 2>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 3: return launch("fasa_list", list_kernel<G, 3>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
     case 4: return launch("fasa_list", list_kernel<G, 4>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 6: return launch("fasa_list", list_kernel<G, 6>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
     case 8: return launch("fasa_list", list_kernel<G, 8>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 12: return launch("fasa_list", list_kernel<G, 12>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 16: return launch("fasa_list", list_kernel<G, 16>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 24: return launch("fasa_list", list_kernel<G, 24>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 32: return launch("fasa_list", list_kernel<G, 32>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
     default: return hipErrorInvalidValue;
   }
 }
@@ -785,26 +811,26 @@ static StepArgs step_args(const fasa_shape& s, const void* q, void* K, void* V, 
 
 hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* q, void* K, void* V, void* Kp,
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
-                            RowCtl* ctl, uint2* list, uint32_t* cnt, float* part_acc, float* part_ml, hipStream_t st,
+                            RowCtl* ctl, uint2* list, uint2* lims, float* part_acc, float* part_ml, hipStream_t st,
                             RaggedLens rl, PageMap pm) {
-  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ctl, ListOut{list, cnt}, st, rl,
+  const int room = rl.n_ctx || rl.budget ? 0 : list_room(s.budget < s.n_ctx ? s.budget : s.n_ctx, s.n_ctx, p.cap);
+  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ListOut{list, lims, room, p.cap}, st, rl,
                                          AppendArgs{k_new, v_new, K, V, pm, false});
   if (e != hipSuccess) return e;
   StepArgs a = step_args(s, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, rl, pm);
-  a.list = list; a.cnt = cnt;
-  a.lanes = p.lanes;
-  a.magic = (uint32_t)((1ull << 32) / (unsigned)p.lanes) + 1u;
+  a.list = list; a.lims = lims;
+  a.room = room; a.cap = p.cap;
   a.nwgs = p.nwgs;
   a.part_acc = part_acc; a.part_ml = part_ml;
   switch (s.n_q_heads / s.n_kv_heads) {
-    case 1: return launch_list_g<1>(a, p.ept, st);
-    case 2: return launch_list_g<2>(a, p.ept, st);
-    case 3: return launch_list_g<3>(a, p.ept, st);
-    case 4: return launch_list_g<4>(a, p.ept, st);
-    case 5: return launch_list_g<5>(a, p.ept, st);
-    case 6: return launch_list_g<6>(a, p.ept, st);
-    case 7: return launch_list_g<7>(a, p.ept, st);
-    case 8: return launch_list_g<8>(a, p.ept, st);
+    case 1: return launch_list_g<1>(a, st);
+    case 2: return launch_list_g<2>(a, st);
+    case 3: return launch_list_g<3>(a, st);
+    case 4: return launch_list_g<4>(a, st);
+    case 5: return launch_list_g<5>(a, st);
+    case 6: return launch_list_g<6>(a, st);
+    case 7: return launch_list_g<7>(a, st);
+    case 8: return launch_list_g<8>(a, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -193,9 +193,9 @@ __global__ __launch_bounds__(256) void select_all_kernel(int32_t* __restrict__ T
 }
 
 // ---------------------------------------------------------------------------------------------
-// TopK-I of given scores in one launch: a workgroup per segment of 2048 tokens takes the cut of a sample of the row's
-// scores and lists what reaches it (row_list.h); the one that comes last, by the row's ticket, selects out of the
-// lists.  No workgroup waits for another.  (A row of one segment is selected out of registers.)
+// TopK-I of given scores in one launch: the waves of a workgroup per 2048 tokens list their segments (row_list.h); the one
+// that comes last, by the row's ticket, selects out of the lists.  No workgroup waits for another.  (A row of one workgroup is selected
+// out of registers.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT, kTopkSample = 256;
 
@@ -206,49 +206,50 @@ struct TopkLds {
   uint32_t hist[kSelBins];
   uint2 cand[kSelCand];
   uint2 extra[kWaves * kExtraPerWave];                       // entries of lists that no thread holds
+  SegLds seg[kWaves];
+  uint32_t lim[kThreads];
   uint32_t wtot[kWaves], wtot2[kWaves], wcnt[kWaves];
-  uint32_t seg_cnt[kListMaxSegs];
   uint32_t thr[4];
-  uint32_t ticket;
+  uint32_t ticket, n_cnd;
   float2 cut_top;
   int32_t* out;
   __device__ __forceinline__ void put(int place, uint32_t tok) { out[place] = (int32_t)tok; }
 };
 
-template <int EPT, bool ONE>
-__global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int32_t* __restrict__ T, uint2* list, uint32_t* cnt,
-                                                       int cnt_pitch, uint32_t* tickets, int ticket_stride, int rows, int nsegs,
-                                                       int N, int n_cap, int bsel, int lanes, uint32_t magic) {
+template <int Q, bool ONE>
+__global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int32_t* __restrict__ T, uint2* list, uint2* lims,
+                                                       uint32_t* tickets, int ticket_stride, int rows, int nsegs,
+                                                       int N, int n_cap, int bsel, int room) {
   __shared__ TopkLds sm;
   int row, seg;
   row_slice_of_block(rows, nsegs, row, seg);
   const int t = threadIdx.x;
   const float* srow = S + (size_t)row * n_cap;
   const int n0 = seg * kTopkSeg + 4 * t;
-  // one score out of each of 256 equal stretches, at uneven places: a mask of every second token must not hide from it
-  if (t < kTopkSample) sm.sample[t] = srow[(int)((((unsigned long long)t << 16 | (t * 40503u & 0xffffu)) * (unsigned)N) >> 24)];
   const float4 x = *reinterpret_cast<const float4*>(srow + (n0 < N ? n0 : 0));   // (S is n_cap long, a multiple of 64)
-  __syncthreads();
-  if (t < kWave) {
-    const float smp[4] = {sm.sample[t], sm.sample[kWave + t], sm.sample[2 * kWave + t], sm.sample[3 * kWave + t]};
-    const int r = list_rank(bsel, N, kTopkSample);
-    float top = INFINITY, cut = -INFINITY;
-    if (r <= kTopkSample) cut = list_cut(smp, r, sm.bins, top);
-    if (t == 0) sm.cut_top = make_float2(cut, top);
-  }
-  __syncthreads();
-  const float cut = sm.cut_top.x, top = sm.cut_top.y;
   const float acc[4] = {x.x, x.y, x.z, x.w};
-  unsigned long long m[4];
-  uint2* lrow = list + (size_t)row * n_cap;
-  uint32_t* crow = cnt + (size_t)row * cnt_pitch;
-  list_count(acc, n0, N, cut, sm.wcnt, m);
   if constexpr (ONE) {
+    // one score out of each of 256 equal stretches, at uneven places: a mask of every second token must not hide from it
+    if (t < kTopkSample) sm.sample[t] = srow[(int)((((unsigned long long)t << 16 | (t * 40503u & 0xffffu)) * (unsigned)N) >> 24)];
     for (int i = t; i < kSelBins; i += kTopkNT) sm.hist[i] = 0;
     if (t == 0) {
       sm.thr[2] = 0;
       sm.out = T + (size_t)row * bsel;
     }
+    __syncthreads();
+    if (t < kWave) {
+      const float smp[4] = {sm.sample[t], sm.sample[kWave + t], sm.sample[2 * kWave + t], sm.sample[3 * kWave + t]};
+      const int r = list_rank(bsel, N, kTopkSample);
+      float top = INFINITY, cut = -INFINITY;
+      if (r <= kTopkSample) cut = list_cut(smp, r, sm.bins, top);
+      if (t == 0) sm.cut_top = make_float2(cut, top);
+    }
+    __syncthreads();
+    const float cut = sm.cut_top.x, top = sm.cut_top.y;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) mine += (uint32_t)__popcll(__ballot(n0 + k < N && acc[k] >= cut));
+    if (lane_id() == 0) sm.wcnt[t >> 6] = mine;
     __syncthreads();
     uint32_t total = 0;
 #pragma unroll
@@ -261,13 +262,13 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
       tok[k] = (uint32_t)(n0 + k);
     }
     const uint32_t kcut = cut_it ? score_key(cut) : 0u;
-    if (!select_entries<4>(sm, key, tok, false, [](auto&&) {}, max(kcut, 1u), kcut ? first_shift(kcut, score_key(top)) : 22, bsel, srow,
-                           N, 0, bsel))
+    if (!select_entries<4>(sm, key, tok, max(kcut, 1u), kcut ? first_shift(kcut, score_key(top)) : 22, bsel, srow, N))
       row_select<false>(sm, bsel, srow, N, 0, bsel);           // (NaNs that have the key of nothing)
     return;
   }
-  __syncthreads();
-  list_write<true, kTopkNT>(acc, n0, m, sm.wcnt, lrow + seg * kTopkSeg, crow + seg);
+  const ListRow l = ListRow::at(list, lims, row, n_cap, N, room);
+  const int ls = __builtin_amdgcn_readfirstlane(seg * (kTopkSeg / kListSeg) + (t >> 6));
+  if (ls * kListSeg < N) seg_list<true>(acc, min(N - ls * kListSeg, kListSeg), ls, l, sm.seg[t >> 6]);
   publish_barrier();
   if (t == 0) sm.ticket = atomicAdd(&tickets[(size_t)row * ticket_stride], 1u);
   __syncthreads();
@@ -276,26 +277,23 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
     tickets[(size_t)row * ticket_stride] = 0;                  // clean for the next call
     sm.out = T + (size_t)row * bsel;
   }
-  const ListView v = {lrow, nsegs, kTopkSeg, lanes, magic, n_cap, N};
-  select_listed<true, EPT>(sm, v, crow, score_key(cut), score_key(top), bsel, srow, N, 0, bsel);
+  const ListSet set = select_listed<true, Q>(sm, l, bsel, srow, N, 0, bsel);
+  if (set.usable) resolve_threshold(sm, set.klo, bsel, set.need, set.n_cand, srow, N, 0, bsel);
+  else row_select<false>(sm, bsel, srow, N, 0, bsel);
 }
 
-// us, histogram and selection launch / like this: 8 rows of 8192, B = 500: 11.3 / 6.8, 16 of 20011, 1250: 12.4 / 8.6, 8 of 32768,
-// 2048: 12.0 / 8.9, 128 of 16384, 256: 14.5 / 10.0.  The last workgroup's own work ends it: beyond 16 entries a thread (32 rows of
-// 32905, B = 6219: 13.7 / 17.8; 4 of 131072, 9000: 18.0 / 18.0) the row is selected by many workgroups.
-TopkPlan plan_topk(int n_ctx, int bsel) {
-  int lanes = 0;
-  const int need = bsel < n_ctx ? list_loads(n_ctx, bsel, kTopkSeg, kTopkSample, kTopkNT, 16, &lanes) : 0;
-  return TopkPlan{need == 0 ? 0 : need <= 4 ? 4 : need <= 8 ? 8 : 16, lanes};
-}
+// us, histogram and selection launch / like this: 8 rows of 8192, B = 500: 11.3 / 6.8, 16 of 20011, 1250: 12.4 / 8.2, 8 of 32768,
+// 2048: 12.0 / 8.9, 128 of 16384, 256: 14.5 / 10.0.  The last workgroup's own work ends it: beyond 16 entries a thread the row is
+// selected by many workgroups (32 rows of 32905, B = 6219: 13.7 / 17.8).
+TopkPlan plan_topk(int n_ctx, int bsel) { return TopkPlan{bsel < n_ctx ? list_cap(n_ctx, bsel, kTopkNT, 4) : 0}; }
 
 hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint2* list,
-                       uint32_t* cnt, int cnt_pitch, uint32_t* tickets, int ticket_stride, hipStream_t st) {
-  const int nsegs = (n_ctx + kTopkSeg - 1) / kTopkSeg;
-  auto kernel = nsegs == 1 ? topk_kernel<4, true> : p.ept == 4 ? topk_kernel<4, false>
-                : p.ept == 8 ? topk_kernel<8, false> : topk_kernel<16, false>;
-  return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, T, list, cnt, cnt_pitch, tickets, ticket_stride, rows,
-                nsegs, n_ctx, n_cap, bsel, p.lanes, (uint32_t)((1ull << 32) / (unsigned)p.lanes) + 1u);
+                       uint2* lims, uint32_t* tickets, int ticket_stride, hipStream_t st) {
+  const int nsegs = (n_ctx + kTopkSeg - 1) / kTopkSeg, q = p.cap / (4 * kTopkNT);
+  auto kernel = nsegs == 1 ? topk_kernel<1, true> : q == 1 ? topk_kernel<1, false>
+                : q == 2 ? topk_kernel<2, false> : q == 3 ? topk_kernel<3, false> : topk_kernel<4, false>;
+  return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, T, list, lims, tickets, ticket_stride, rows,
+                nsegs, n_ctx, n_cap, bsel, list_room(bsel, n_ctx, p.cap));
 }
 
 // zeroes the histogram and the row counters: 1-D grid, one uint4 per thread
