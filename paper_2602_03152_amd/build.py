@@ -48,6 +48,8 @@ FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     # packed-FP32 VALU forms stay off for every kernel of this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a kernel's first 16 words of arguments are in scalar registers when it starts (0.1 - 0.25 us per launch)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restric
                                                      RowCtl* __restrict__ ctl,
                                                      float* __restrict__ part_acc,
                                                      float* __restrict__ part_ml, int rows,
-                                                     int n_splits, int Hq, int Hkv, int count_max,
+                                                     int n_splits, uint32_t m_splits, int Hkv, uint32_t m_hkv, int count_max,
                                                      int n_ctx_max, int tok_per_split, long long sb,
                                                      long long sh, long long sn,
                                                      float scale_log2e,
@@ -52,8 +52,9 @@ __global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restric
   __shared__ uint32_t ticket;
 
   int row, split;
-  row_slice_of_block(rows, n_splits, row, split);
-  const int b = row / Hkv, h = row % Hkv;
+  row_slice_of_block(rows, n_splits, m_splits, row, split);
+  int b, h;
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int r = lane >> 4, c = lane & 15;
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restric
   float qr[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const float* qp = q + ((size_t)b * Hq + (size_t)h * G + g) * D + 8 * c;
+    const float* qp = q + ((size_t)row * G + g) * D + 8 * c;
 #pragma unroll
     for (int k = 0; k < 8; ++k) qr[g][k] = qp[k] * scale_log2e;
   }
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restric
       a = fmaf(sm_acc[w][g][dim], sc, a);
     }
     if (n_splits == 1) {
-      O[((size_t)b * Hq + (size_t)h * G + g) * D + dim] = a / ls;   // nothing to merge
+      O[((size_t)row * G + g) * D + dim] = a / ls;   // nothing to merge
     } else {
       // read by the row's last workgroup: published with agent-scope stores
       st_agent(&part_acc[(pbase + g) * D + dim], a);
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(256) void attend_valu_kernel(const float* __restric
   __syncthreads();
   if (ticket != (uint32_t)n_splits - 1u) return;
   if (t == 0) ctl[row].done_att = 0;   // clean for the next call
-  combine_row<G>(part_acc, part_ml, O, row, b, h, Hq, n_splits, n_splits, wsm, red, &sm_acc[0][0][0]);
+  combine_row<G>(part_acc, part_ml, O, row, n_splits, n_splits, wsm, red, &sm_acc[0][0][0]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
                                                           RowCtl* __restrict__ ctl,
                                                           float* __restrict__ part_acc,
                                                           float* __restrict__ part_ml, int rows,
-                                                          int n_splits, int Hq, int Hkv, int count_max,
+                                                          int n_splits, uint32_t m_splits, int Hkv, uint32_t m_hkv, int count_max,
                                                           int n_ctx_max, int tok_per_split, long long sb,
                                                           long long sh, long long sn,
                                                           float scale_log2e,
@@ -243,8 +244,9 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
   float* wsm = reinterpret_cast<float*>(big + 8192);
 
   int row, split;
-  row_slice_of_block(rows, n_splits, row, split);
-  const int b = row / Hkv, h = row % Hkv;
+  row_slice_of_block(rows, n_splits, m_splits, row, split);
+  int b, h;
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int lo = lane & 15, hi = lane >> 4;
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
   FASA_T(0);
 
   MfmaTile<G, ET> tile;
-  tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
+  tile.load_q(q + ((size_t)row * G) * D, lo, hi);
   tile.reset();
 
   // list entries are token numbers, or pool slots of a paged cache (block << shift | offset)
@@ -347,7 +349,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
     float4 a;
     tile_wg_totals<G>(&sm_m[0][0], &sm_l[0][0], &sm_o[0][0][0], g, d4, mn, ls, a);
     if (n_splits == 1) {
-      *reinterpret_cast<float4*>(O + ((size_t)b * Hq + (size_t)h * G + g) * D + 4 * d4) =
+      *reinterpret_cast<float4*>(O + ((size_t)row * G + g) * D + 4 * d4) =
           make_float4(a.x / ls, a.y / ls, a.z / ls, a.w / ls);
     } else {
       float2* pa = reinterpret_cast<float2*>(part_acc + (pbase + g) * D + 4 * d4);
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
                FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2));
   if (ticket != (uint32_t)n_splits - 1u) return;
   if (t == 0) ctl[row].done_att = 0;
-  combine_row<G>(part_acc, part_ml, O, row, b, h, Hq, n_splits, n_splits, wsm, red, reinterpret_cast<float*>(big));
+  combine_row<G>(part_acc, part_ml, O, row, n_splits, n_splits, wsm, red, reinterpret_cast<float*>(big));
   FASA_T(4);
   FASA_T_PRINT(t == 0 && row == 0, "attend last(row0, split %d): tiles %llu merge %llu publish+ticket %llu combine %llu (x10ns)\n",
                split, FASA_T_D(1, 0), FASA_T_D(2, 1), FASA_T_D(3, 2), FASA_T_D(4, 3));
@@ -394,8 +396,8 @@ struct SparseList {
 template <int G, class L>
 __global__ __launch_bounds__(kWideNT, 4) void attend_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, float* __restrict__ O,
-    RowCtl* __restrict__ ctl, float* __restrict__ part_acc, float* __restrict__ part_ml, int rows, int n_splits, int Hq, int Hkv,
-    int N_max, int tok_per_split, long long sb, long long sh, long long sn, float scale_log2e, L list) {
+    RowCtl* __restrict__ ctl, float* __restrict__ part_acc, float* __restrict__ part_ml, int rows, int n_splits, uint32_t m_splits,
+    int Hkv, uint32_t m_hkv, int N_max, int tok_per_split, long long sb, long long sh, long long sn, float scale_log2e, L list) {
   constexpr bool LIST = L::used;
   constexpr int D = kHeadDim, NWV = kWideNT / kWave, STEP = 16 * NWV;   // rows of a round of tiles
   constexpr int ACC_BYTES = NWV * G * D * 4, MERGE_BYTES = 8192 + G * kMaxSplitsLds * 4;
@@ -407,8 +409,9 @@ __global__ __launch_bounds__(kWideNT, 4) void attend_wide_kernel(
   float (*sm_o)[G][D] = reinterpret_cast<float (*)[G][D]>(big);
 
   int row, split;
-  row_slice_of_block(rows, n_splits, row, split);
-  const int b = row / Hkv, h = row % Hkv;
+  row_slice_of_block(rows, n_splits, m_splits, row, split);
+  int b, h;
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lo = lane & 15, hi = lane >> 4;
   int N = N_max, count = N_max;
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(kWideNT, 4) void attend_wide_kernel(
   const int s0 = split * tok_per_split, s1 = min(count, s0 + tok_per_split);
 
   MfmaTile<G> tile;
-  tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
+  tile.load_q(q + ((size_t)row * G) * D, lo, hi);
   tile.reset();
   const bool paged = pm.table != nullptr;
   const int pshift = paged ? pm.shift : 31, pmask = paged ? (1 << pm.shift) - 1 : 0x7fffffff;
@@ -495,7 +498,7 @@ __global__ __launch_bounds__(kWideNT, 4) void attend_wide_kernel(
     float4 a;
     tile_wg_totals<G, NWV>(&sm_m[0][0], &sm_l[0][0], &sm_o[0][0][0], g, d4, mn, ls, a);
     if (n_splits == 1) {
-      *reinterpret_cast<float4*>(O + ((size_t)b * Hq + (size_t)h * G + g) * D + 4 * d4) =
+      *reinterpret_cast<float4*>(O + ((size_t)row * G + g) * D + 4 * d4) =
           make_float4(a.x / ls, a.y / ls, a.z / ls, a.w / ls);
     } else {
       float2* pa = reinterpret_cast<float2*>(part_acc + (pbase + g) * D + 4 * d4);
@@ -510,7 +513,7 @@ __global__ __launch_bounds__(kWideNT, 4) void attend_wide_kernel(
   __syncthreads();
   if (ticket != (uint32_t)n_splits - 1u) return;
   if (t == 0) ctl[row].done_att = 0;
-  combine_row<G, NothingUnderLoads, 16, kWideNT>(part_acc, part_ml, O, row, b, h, Hq, n_splits, n_splits,
+  combine_row<G, NothingUnderLoads, 16, kWideNT>(part_acc, part_ml, O, row, n_splits, n_splits,
                                                   reinterpret_cast<float*>(big + 8192), red, reinterpret_cast<float*>(big));
 }
 
@@ -521,13 +524,14 @@ static hipError_t launch_wide_g(const fasa_shape& s, bool dense, const AttendPla
   const int rows = s.batch * s.n_kv_heads;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
   const dim3 grid(rows * p.n_splits), block(kWideNT);
+  const uint32_t m_splits = div_magic(p.n_splits, (long long)rows * p.n_splits), m_hkv = div_magic(s.n_kv_heads, rows);
   const uint16_t *q16 = (const uint16_t*)q, *k16 = (const uint16_t*)K, *v16 = (const uint16_t*)V;
   const long long sb = s.kv_stride_b, sh = s.kv_stride_h, sn = s.kv_stride_n;
   if (dense)
     return launch("fasa_dense_attend", attend_wide_kernel<G, NoList>, grid, block, st, q16, k16, v16, O, ctl, part_acc, part_ml,
-                  rows, p.n_splits, s.n_q_heads, s.n_kv_heads, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e, NoList{});
+                  rows, p.n_splits, m_splits, s.n_kv_heads, m_hkv, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e, NoList{});
   return launch("fasa_sparse_attend", attend_wide_kernel<G, SparseList>, grid, block, st, q16, k16, v16, O, ctl, part_acc, part_ml,
-                rows, p.n_splits, s.n_q_heads, s.n_kv_heads, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e,
+                rows, p.n_splits, m_splits, s.n_kv_heads, m_hkv, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e,
                 SparseList{T, rl.n_ctx, rl.budget, p.count, pm});
 }
 static hipError_t launch_wide(const fasa_shape& s, bool dense, const AttendPlan& p, const void* q, const void* K, const void* V,
@@ -559,7 +563,7 @@ static hipError_t launch_attend_g(const fasa_shape& s, bool dense, const AttendP
   }();
   return launch(dense ? "fasa_dense_attend" : "fasa_sparse_attend", kernel, dim3(rows * p.n_splits), dim3(256), st,
                 (const ET*)q, (const ET*)K, (const ET*)V, T, O, ctl, part_acc, part_ml, rows, p.n_splits,
-                s.n_q_heads, s.n_kv_heads, p.count, s.n_ctx, p.tok_per_split, (long long)s.kv_stride_b,
+                div_magic(p.n_splits, (long long)rows * p.n_splits), s.n_kv_heads, div_magic(s.n_kv_heads, rows), p.count, s.n_ctx, p.tok_per_split, (long long)s.kv_stride_b,
                 (long long)s.kv_stride_h, (long long)s.kv_stride_n, scale_log2e, rl.n_ctx, rl.budget, pm);
 }
 

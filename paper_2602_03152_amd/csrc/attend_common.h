@@ -85,7 +85,7 @@ template <int G, typename UnderLoads = NothingUnderLoads, int RS = 32 /* splits 
           int MS = kMaxSplitsLds>
 __device__ __forceinline__ void combine_row(const float* __restrict__ part_acc,
                                             const float* __restrict__ part_ml,
-                                            float* __restrict__ O, int row, int b, int h, int Hq,
+                                            float* __restrict__ O, int row,
                                             int n_splits, int stride, float* wsm /* [G][MS] */,
                                             float* red /* [G] */, float* xbuf /* [P - 1][C][4] */,
                                             const ExtraSplit ex = {nullptr, nullptr, nullptr, nullptr},
@@ -222,7 +222,7 @@ __device__ __forceinline__ void combine_row(const float* __restrict__ part_acc,
       a.x = fmaf(e.x, wx, a.x); a.y = fmaf(e.y, wx, a.y); a.z = fmaf(e.z, wx, a.z); a.w = fmaf(e.w, wx, a.w);
     }
     const float r = red[g];
-    *reinterpret_cast<float4*>(O + ((size_t)b * Hq + (size_t)h * G + g) * D + 4 * d4) =
+    *reinterpret_cast<float4*>(O + ((size_t)row * G + g) * D + 4 * d4) =
         make_float4(a.x * r, a.y * r, a.z * r, a.w * r);
   }
 }

@@ -42,16 +42,16 @@ __device__ __forceinline__ void set_bit(uint32_t* bits, uint32_t tok) { atomicOr
 template <typename ET, int PAIR_SHIFT, int PAIR_ADD>
 __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict__ q, const ET* __restrict__ Kp,
                                                          float* __restrict__ S, CalibSets sets, int rows, int nslices,
-                                                         int Hq, int Hkv, int N, int n_cap) {
+                                                         uint32_t m_slices, int G, int N, int n_cap) {
   constexpr int D = kHeadDim, F = D / 2, NW = 16;
   constexpr int TPT = ScoreTraits<ET>::TPT;
   __shared__ float ql[kMaxGroup][D];
   __shared__ float2 qs[F];
   int row, slice;
-  row_slice_of_block(rows, nslices, row, slice);
-  const int G = Hq / Hkv, t = threadIdx.x;
+  row_slice_of_block(rows, nslices, m_slices, row, slice);
+  const int t = threadIdx.x;
   if (slice == 0) sets.clear<256>(row);                       // for the launch behind this one
-  const ET* qh = q + ((size_t)(row / Hkv) * Hq + (size_t)(row % Hkv) * G) * D + (t & (D - 1));
+  const ET* qh = q + (size_t)row * G * D + (t & (D - 1));
   ET qcol[kMaxGroup / 2];                                   // head dim t mod 128 of query heads t / 128, + 2, ...
 #pragma unroll
   for (int j = 0; j < kMaxGroup / 2; ++j) qcol[j] = qh[(size_t)min((t >> 7) + 2 * j, G - 1) * D];
@@ -342,7 +342,7 @@ __device__ __forceinline__ void calib_top(CalibLds<NT, WORDS>& sm, uint32_t* bit
 template <typename ET, int NT, int WORDS, int PAIR_SHIFT, int PAIR_ADD>
 __global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCalibWords1 ? 8 : 4) void calib_fc_kernel(
     const ET* __restrict__ q, const ET* __restrict__ Kp, const float* __restrict__ S, CalibSets sets, float* __restrict__ CA_sum,
-    int rows, int Hq, int Hkv, int N, int n_cap, int kk) {
+    int rows, int G, int N, int n_cap, int kk) {
   constexpr int D = kHeadDim, F = D / 2, WPT = (WORDS + NT - 1) / NT;
   constexpr int TPT = ScoreTraits<ET>::TPT;
   __shared__ CalibLds<NT, WORDS> sm;
@@ -353,9 +353,8 @@ __global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCali
   }
   const int id = (int)blockIdx.x - rows, words = sets.words;
   const int row = id / F, f = id % F, t = threadIdx.x;
-  const int G = Hq / Hkv;
   if (t == 0) { sm.count = 0; sm.missing = 0; }
-  const ET* qh = q + ((size_t)(row / Hkv) * Hq + (size_t)(row % Hkv) * G) * D + (f << PAIR_SHIFT);
+  const ET* qh = q + (size_t)row * G * D + (f << PAIR_SHIFT);
   float qlo = 0.f, qhi = 0.f;
   {
     ET a[kMaxGroup], b[kMaxGroup];
@@ -473,12 +472,13 @@ static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void*
   const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2;
   const int per = 256 * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per - 1) / per;
   hipError_t e = launch("fasa_calib_full", calib_full_kernel<ET, PS, PA>, dim3(rows * nslices), dim3(256), st, (const ET*)q,
-                        (const ET*)Kp_all, S, sets, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap);
+                        (const ET*)Kp_all, S, sets, rows, nslices, div_magic(nslices, (long long)rows * nslices),
+                        s.n_q_heads / s.n_kv_heads, s.n_ctx, s.n_cap);
   if (e != hipSuccess) return e;
   const auto stage = [&](auto nt_c, auto words_c) {
     constexpr int NT = decltype(nt_c)::value, WORDS = decltype(words_c)::value;
     return launch("fasa_calib_fc", calib_fc_kernel<ET, NT, WORDS, PS, PA>, dim3(rows * (1 + half)), dim3(NT), st, (const ET*)q,
-                  (const ET*)Kp_all, S, sets, CA_sum, rows, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap, kk);
+                  (const ET*)Kp_all, S, sets, CA_sum, rows, s.n_q_heads / s.n_kv_heads, s.n_ctx, s.n_cap, kk);
   };
   // rows that fit in the registers of 256 threads: several workgroups per compute unit instead of one of
   // 1024 each; rows that fit in those of 1024: a set small enough for two

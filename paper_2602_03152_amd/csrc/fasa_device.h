@@ -151,20 +151,28 @@ __device__ __forceinline__ void block256_prefix2(uint32_t a, uint32_t b, uint32_
   pb = ob + ib - b;
 }
 
+// Quotients by a divisor that is the same for the whole launch: with m = div_magic(d, most) they are exact up to `most`.  The
+// compiler's division is a chain of some 30 instructions, ahead of a kernel's first load: the list form of a step, the one-launch step and
+// the attention kernels begin with two to four of them.  us per step, with the first arguments in registers (build.py) as well: 8 rows of
+// 32768, B = 2048: 17.2 -> 16.8; 32 of 32905, 7 heads: 45.3 -> 44.7; 128 of 16384: 38.7 -> 38.0; 1 float32 row of 4096: 11.55 -> 11.2.
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t m) { return m ? __umulhi(n << 1, m) : n / d; }
+
 // Maps the linear workgroup id of a 1-D grid of rows * nslices workgroups to (row, slice).
 // Workgroups are handed to the 8 XCDs round-robin, so when the row count is a multiple of 8 the
 // mapping keeps every workgroup of a row on one XCD: the row's counters, histogram and score
 // slice then live in that XCD's L2 and its atomics do not bounce between dies.
-__device__ __forceinline__ void row_slice_of_block(int rows, int nslices, int& row, int& slice) {
+// m: div_magic(nslices, rows * nslices)
+__device__ __forceinline__ void row_slice_of_block(int rows, int nslices, uint32_t m, int& row, int& slice) {
   const unsigned id = blockIdx.x;
-  if ((rows & 7) == 0) {
-    const unsigned xcd = id & 7u, k = id >> 3;
-    slice = (int)(k % (unsigned)nslices);
-    row = (int)(k / (unsigned)nslices) * 8 + (int)xcd;
-  } else {
-    row = (int)(id / (unsigned)nslices);
-    slice = (int)(id % (unsigned)nslices);
-  }
+  const bool by8 = (rows & 7) == 0;
+  const unsigned k = by8 ? id >> 3 : id, r = fast_div(k, (unsigned)nslices, m);
+  slice = (int)(k - r * (unsigned)nslices);
+  row = (int)(by8 ? r * 8 + (id & 7u) : r);
+}
+// (batch entry, KV head) of a row.  m: div_magic(Hkv, rows)
+__device__ __forceinline__ void head_of_row(int row, int Hkv, uint32_t m, int& b, int& h) {
+  b = (int)fast_div((uint32_t)row, (uint32_t)Hkv, m);
+  h = row - b * Hkv;
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256, 2) void select_attend_kernel(
     const ET* __restrict__ q, const ET* __restrict__ K, const ET* __restrict__ V,
     const float* __restrict__ S, uint32_t* __restrict__ hist, RowCtl* __restrict__ ctl,
     uint2* __restrict__ cand, int32_t* __restrict__ T, float* __restrict__ O, float* __restrict__ part_acc,
-    float* __restrict__ part_ml, unsigned char* __restrict__ rec, int rows, int nslices, int slice_len, int Hq, int Hkv, int N_max,
+    float* __restrict__ part_ml, unsigned char* __restrict__ rec, int rows, int nslices, uint32_t m_slices, int slice_len, int Hkv, uint32_t m_hkv, int N_max,
     int n_cap, int budget_max, int t_pitch, long long sb, long long sh, long long sn, float scale_log2e,
     const int32_t* __restrict__ n_ctx_seq, const int32_t* __restrict__ budget_seq, PageMap pm) {
   constexpr int D = kHeadDim;
@@ -88,8 +88,9 @@ __global__ __launch_bounds__(256, 2) void select_attend_kernel(
   float* wsm = reinterpret_cast<float*>(big + 8192);
 
   int row, slice;
-  row_slice_of_block(rows, nslices, row, slice);
-  const int b = row / Hkv, h = row % Hkv;
+  row_slice_of_block(rows, nslices, m_slices, row, slice);
+  int b, h;
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int lo = lane & 15, hi = lane >> 4;
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(256, 2) void select_attend_kernel(
   const uint4 h4 = *reinterpret_cast<const uint4*>(gh + 4 * t);
   const float bin_mu = ctl[row].bin_mu, bin_inv = ctl[row].bin_inv;
   MfmaTile<G, ET> tile;
-  tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
+  tile.load_q(q + ((size_t)row * G) * D, lo, hi);
   const bool paged = pm.table != nullptr;
   int slot[PT];
   if (paged) {
@@ -394,7 +395,7 @@ __global__ __launch_bounds__(256, 2) void select_attend_kernel(
       __syncthreads();
       FASA_T(8);
     };
-    combine_row<G, decltype(under_loads)&, kFuseMergeInFlight>(part_acc, part_ml, O, row, b, h, Hq, nvalid, nslices, wsm, red,
+    combine_row<G, decltype(under_loads)&, kFuseMergeInFlight>(part_acc, part_ml, O, row, nvalid, nslices, wsm, red,
                                                                reinterpret_cast<float*>(big), ex_lds, under_loads);
     FASA_T(9);
     FASA_T_PRINT(t == 0 && row == 0, "fused last(row0, slice %d): loads %llu rank(%d of %d) %llu records %llu merge %llu (x10ns)\n",
@@ -466,7 +467,7 @@ __global__ __launch_bounds__(256, 2) void select_attend_kernel(
   FASA_T(8);
 
   // ---- 6. merge ----
-  combine_row<G, NothingUnderLoads, kFuseMergeInFlight>(part_acc, part_ml, O, row, b, h, Hq, nvalid, nslices, wsm, red,
+  combine_row<G, NothingUnderLoads, kFuseMergeInFlight>(part_acc, part_ml, O, row, nvalid, nslices, wsm, red,
                                                         reinterpret_cast<float*>(big), ex);
   FASA_T(9);
   FASA_T_PRINT(t == 0 && row == 0, "fused last(row0, slice %d): candload %llu resolve %llu attend(%d of %d) %llu combine %llu (x10ns)\n",
@@ -519,7 +520,8 @@ static hipError_t launch_fused_gt(const fasa_shape& s, const FusePlan& p, const 
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)s.head_dim);
   return launch("fasa_select_attend", select_attend_kernel<ET, G, TPB>, dim3(rows * p.nslices), dim3(256), st,
                 (const ET*)q, (const ET*)K, (const ET*)V, S, hist, ctl, cand, T, O, part_acc,
-                part_ml, rec, rows, p.nslices, p.slice_len, s.n_q_heads, s.n_kv_heads, s.n_ctx, s.n_cap, s.budget, t_pitch,
+                part_ml, rec, rows, p.nslices, div_magic(p.nslices, (long long)rows * p.nslices), p.slice_len, s.n_kv_heads,
+                div_magic(s.n_kv_heads, rows), s.n_ctx, s.n_cap, s.budget, t_pitch,
                 (long long)s.kv_stride_b, (long long)s.kv_stride_h, (long long)s.kv_stride_n, scale_log2e,
                 rl.n_ctx, rl.budget, pm);
 }

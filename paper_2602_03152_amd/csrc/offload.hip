@@ -168,8 +168,8 @@ __global__ __launch_bounds__(256) void offload_attend_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ Kp, const uint16_t* __restrict__ Knd,
     const uint16_t* __restrict__ Vh, const int32_t* __restrict__ fc_idx, const int32_t* __restrict__ T,
     uint16_t* __restrict__ KT, uint16_t* __restrict__ VT, float* __restrict__ O, RowCtl* __restrict__ ctl,
-    float* __restrict__ part_acc, float* __restrict__ part_ml, int rows, int n_splits, int tiles_per_split, int Hq,
-    int Hkv, int F, int n_cap, int n_ctx, int count, long long sb, long long sh, long long sn, int pairing,
+    float* __restrict__ part_acc, float* __restrict__ part_ml, int rows, int n_splits, uint32_t m_splits,
+    int tiles_per_split, int Hkv, uint32_t m_hkv, int F, int n_cap, int n_ctx, int count, long long sb, long long sh, long long sn, int pairing,
     float scale_log2e) {
   constexpr int D = kHeadDim;
   constexpr int ACC_BYTES = 4 * G * D * 4;
@@ -186,8 +186,9 @@ __global__ __launch_bounds__(256) void offload_attend_kernel(
   float* wsm = reinterpret_cast<float*>(big + 8192);
 
   int row, split;
-  row_slice_of_block(rows, n_splits, row, split);
-  const int b = row / Hkv, h = row % Hkv;
+  row_slice_of_block(rows, n_splits, m_splits, row, split);
+  int b, h;
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int lo = lane & 15, hi = lane >> 4;
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(256) void offload_attend_kernel(
   int tile_no = split * tiles_per_split + wave;
   int tok = token_of(min(tile_no, n_tiles - 1));
   MfmaTile<G> tile;
-  tile.load_q(q + ((size_t)b * Hq + (size_t)h * G) * D, lo, hi);
+  tile.load_q(q + ((size_t)row * G) * D, lo, hi);
   tile.reset();
   build_dim_map(fc_idx + h * F, F, pairing, src, is_dom);
   uint32_t pick[4][2];                            // where dims 8 (hi + 4i) + k of an entry lie: element numbers, a byte each
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(256) void offload_attend_kernel(
     float4 a;
     tile_wg_totals<G>(&sm_m[0][0], &sm_l[0][0], &sm_o[0][0][0], g, d4, mn, ls, a);
     if (n_splits == 1) {
-      *reinterpret_cast<float4*>(O + ((size_t)b * Hq + (size_t)h * G + g) * D + 4 * d4) =
+      *reinterpret_cast<float4*>(O + ((size_t)row * G + g) * D + 4 * d4) =
           make_float4(a.x / ls, a.y / ls, a.z / ls, a.w / ls);
     } else {
       float2* pa = reinterpret_cast<float2*>(part_acc + (pbase + g) * D + 4 * d4);
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(256) void offload_attend_kernel(
   __syncthreads();
   if (ticket != (uint32_t)n_splits - 1u) return;
   if (t == 0) ctl[row].done_att = 0;
-  combine_row<G>(part_acc, part_ml, O, row, b, h, Hq, n_splits, n_splits, wsm, red, reinterpret_cast<float*>(big));
+  combine_row<G>(part_acc, part_ml, O, row, n_splits, n_splits, wsm, red, reinterpret_cast<float*>(big));
 }
 
 hipError_t launch_offload_split(const fasa_shape& s, const void* K, const int32_t* fc_idx, void* Kp,
@@ -354,7 +355,7 @@ static hipError_t launch_offload_attend_g(const fasa_shape& s, int n_splits, int
   return launch("fasa_offload_attend", s.n_fc % 4 == 0 ? offload_attend_kernel<G, true> : offload_attend_kernel<G, false>,
                 dim3(rows * n_splits), dim3(256), st, (const uint16_t*)q, (const uint16_t*)Kp, (const uint16_t*)Knd,
                 (const uint16_t*)Vh, fc_idx, T, (uint16_t*)KT, (uint16_t*)VT, O, ctl, part_acc, part_ml, rows, n_splits,
-                tiles_per_split, s.n_q_heads, s.n_kv_heads, s.n_fc, s.n_cap, s.n_ctx, count, (long long)s.kv_stride_b,
+                div_magic(n_splits, (long long)rows * n_splits), tiles_per_split, s.n_kv_heads, div_magic(s.n_kv_heads, rows), s.n_fc, s.n_cap, s.n_ctx, count, (long long)s.kv_stride_b,
                 (long long)s.kv_stride_h, (long long)s.kv_stride_n, s.pairing, 1.4426950408889634f / sqrtf((float)s.head_dim));
 }
 

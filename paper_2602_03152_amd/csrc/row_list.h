@@ -647,6 +647,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, int 
     from = klo;
     if (!narrow(klo)) { clear(); return none; }                // (NaNs only)
   }
+  FASA_T(1);
   const int n_above = bsel - need;
   const uint32_t span = khi - klo;
   uint32_t n_win = 0;

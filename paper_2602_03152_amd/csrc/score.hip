@@ -55,8 +55,8 @@ template <typename ET, int HIST, int NB, bool APPEND, int PAIR>
 __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET* Kp,
                                                     const int32_t* __restrict__ fc_idx,
                                                     float* __restrict__ S,
-                                                    uint32_t* __restrict__ hist, int rows,
-                                                    int nslices, int Hq, int Hkv, int F, int N_max,
+                                                    uint32_t* __restrict__ hist, int rows, int nslices,
+                                                    uint32_t m_slices, int Hkv, uint32_t m_hkv, int G, int F, int N_max,
                                                     int n_cap, const int32_t* __restrict__ n_ctx_seq,
                                                     const ET* __restrict__ k_new,
                                                     const ET* __restrict__ v_new, ET* Kc, ET* Vc,
@@ -80,15 +80,15 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
   __shared__ uint2 kpair[APPEND ? D / 2 : 1];  // per plane: the new key's (lo, hi) as stored in Kp
 
   int row, slice;
-  row_slice_of_block(rows, nslices, row, slice);
-  const int b = row / Hkv, h = row % Hkv;
-  const int G = Hq / Hkv;
+  row_slice_of_block(rows, nslices, m_slices, row, slice);
+  int b, h;
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x;
   const int N = seq_n_ctx(n_ctx_seq, b, N_max);
   if (slice * 256 * TPT >= N) return;   // whole workgroup beyond this sequence (ragged batches only)
 
   // ---- 1 ----
-  const ET* qh = q + ((size_t)b * Hq + (size_t)h * G) * D + (t & (D - 1));
+  const ET* qh = q + (size_t)row * G * D + (t & (D - 1));
   ET qcol[kMaxGroup];
 #pragma unroll
   for (int g = 0; g < kMaxGroup; ++g) qcol[g] = qh[(size_t)min(g, G - 1) * D];   // beyond the group: its last head, not added
@@ -334,9 +334,9 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
 constexpr int kListScoreNT = 256;
 template <typename ET, int NB, bool APPEND, int PAIR>
 __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
-    const ET* __restrict__ q, ET* Kp, const int32_t* __restrict__ fc_idx, float* __restrict__ S, int rows, int nslices, int Hq, int Hkv,
-    int F, int N_max, int n_cap, const int32_t* __restrict__ n_ctx_seq, const ET* __restrict__ k_new, const ET* __restrict__ v_new,
-    ET* Kc, ET* Vc, long long sb, long long sh, long long sn, PageMap pm, int budget_max,
+    const ET* __restrict__ q, ET* Kp, const int32_t* __restrict__ fc_idx, int rows, int nslices, uint32_t m_slices, int Hkv, uint32_t m_hkv,
+    int G, int F, int N_max, int n_cap, const int32_t* __restrict__ n_ctx_seq, float* __restrict__ S, const ET* __restrict__ k_new,
+    const ET* __restrict__ v_new, ET* Kc, ET* Vc, long long sb, long long sh, long long sn, PageMap pm, int budget_max,
     const int32_t* __restrict__ budget_seq, ListOut lists) {
   constexpr int D = kHeadDim;
   constexpr int TPT = ScoreTraits<ET>::TPT, NT = kListScoreNT, SL = NT * TPT;
@@ -353,14 +353,14 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
   __shared__ uint32_t kpair[APPEND ? D / 2 : 1];
 
   int row, slice;
-  row_slice_of_block(rows, nslices, row, slice);
-  const int b = row / Hkv, h = row % Hkv;
-  const int G = Hq / Hkv;
+  row_slice_of_block(rows, nslices, m_slices, row, slice);
+  int b, h;
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x;
   const int N = seq_n_ctx(n_ctx_seq, b, N_max);
   if (slice * SL >= N) return;
 
-  const ET* qh = q + ((size_t)b * Hq + (size_t)h * G) * D + (t & (D - 1));
+  const ET* qh = q + (size_t)row * G * D + (t & (D - 1));
   ET qcol[kMaxGroup];
 #pragma unroll
   for (int g = 0; g < kMaxGroup; ++g) qcol[g] = qh[(size_t)min(g, G - 1) * D];
@@ -509,7 +509,7 @@ static hipError_t launch_score_v(const fasa_shape& s, const void* q, void* Kp, c
   const int nslices = (s.n_ctx + per_block - 1) / per_block;
   return launch(HIST ? "fasa_score_hist" : "fasa_score", score_kernel<ET, HIST, NB, APPEND, PAIR>,
                 dim3(rows * nslices), dim3(256), st, (const ET*)q, (ET*)Kp, fc_idx, S, hist, rows, nslices,
-                s.n_q_heads, s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, (const ET*)ap.k_new,
+                div_magic(nslices, (long long)rows * nslices), s.n_kv_heads, div_magic(s.n_kv_heads, rows), s.n_q_heads / s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, (const ET*)ap.k_new,
                 (const ET*)ap.v_new, (ET*)ap.K, (ET*)ap.V, (long long)s.kv_stride_b, (long long)s.kv_stride_h,
                 (long long)s.kv_stride_n, ap.pm, ctl, s.budget, rl.budget, ap.split ? 1 : 0);
 }
@@ -579,8 +579,8 @@ static hipError_t launch_score_list_v(const fasa_shape& s, const void* q, void* 
   const int rows = s.batch * s.n_kv_heads;
   const int per_block = kListScoreNT * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per_block - 1) / per_block;
   return launch("fasa_score_list", score_list_kernel<ET, NB, APPEND, PAIR>, dim3(rows * nslices), dim3(kListScoreNT), st,
-                (const ET*)q, (ET*)Kp,
-                fc_idx, S, rows, nslices, s.n_q_heads, s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, (const ET*)ap.k_new,
+                (const ET*)q, (ET*)Kp, fc_idx, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_kv_heads,
+                div_magic(s.n_kv_heads, rows), s.n_q_heads / s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, S, (const ET*)ap.k_new,
                 (const ET*)ap.v_new, (ET*)ap.K, (ET*)ap.V, (long long)s.kv_stride_b, (long long)s.kv_stride_h,
                 (long long)s.kv_stride_n, ap.pm, s.budget, rl.budget, lists);
 }

@@ -46,14 +46,11 @@ struct StepArgs {
   const int32_t* budget_seq;
   long long sb, sh, sn;    // K/V element strides
   PageMap pm;
-  int rows, nslices, Hq, Hkv, F, N_max, n_cap, budget_max, t_pitch, append, pairing;
+  int rows, nslices, G, Hkv, F, N_max, n_cap, budget_max, t_pitch, append, pairing;
+  uint32_t m_slices, m_hkv;  // div_magic of nslices (list_kernel: of nwgs) and Hkv
   float scale_log2e;
-  // list_kernel: the rows' lists (row_list.h), workgroups per row, their partials [row][nwgs]
-  uint2* list;             // [row][n_cap]
-  uint2* lims;             // [row][kListLimPitch]
-  int room;                // places of a segment's list; 0: sequences have lengths and budgets of their own (list_room)
-  int cap;                 // places that a workgroup's threads hold
-  int nwgs;
+  // list_kernel: places of a row's list that a workgroup's threads hold; the workgroups' partials [row][nwgs]
+  int cap;
   float* part_acc;
   float* part_ml;
 };
@@ -140,7 +137,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
   constexpr int D = kHeadDim;
   constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const ET* q = (const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D;
+  const ET* q = (const ET*)a.q + (size_t)row * G * D;
   // T, and what the gather reads: the row's element offset / 8, padded to whole tiles with the last row
   const bool paged = a.pm.table != nullptr;
   int32_t* trow = a.T + (size_t)row * a.t_pitch + p0;
@@ -321,7 +318,7 @@ __device__ __forceinline__ void wave_totals(const Lds& sm, int g, int d4, float&
   }
 }
 template <typename Lds>
-__device__ __forceinline__ void write_output(const StepArgs& a, const Lds& sm, int b, int h, int G) {
+__device__ __forceinline__ void write_output(const StepArgs& a, const Lds& sm, int row, int G) {
   constexpr int D = kHeadDim;
   const int t = threadIdx.x;
   if (t < G * (D / 4)) {
@@ -330,7 +327,7 @@ __device__ __forceinline__ void write_output(const StepArgs& a, const Lds& sm, i
     float4 o;
     wave_totals(sm, g, d4, mn, ls, o);
     const float inv = 1.0f / ls;
-    *reinterpret_cast<float4*>(a.O + ((size_t)b * a.Hq + (size_t)h * G + g) * D + 4 * d4) =
+    *reinterpret_cast<float4*>(a.O + ((size_t)row * G + g) * D + 4 * d4) =
         make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
   }
 }
@@ -382,9 +379,17 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
   return (int)sm.n_list;
 }
 
-// MULTI: rows of several slices (scores handed over through S and a ticket); else one slice per row.
+constexpr uint32_t kStepGroup = 15, kStepPairing = 16, kStepAppend = 64, kStepRagged = 128;
+struct StepGrid {
+  int rows, nslices;
+  uint32_t m_slices;
+};
+// MULTI: rows of several slices (scores handed over through S and a ticket); else one slice per row.  flags: query heads per KV
+// head | kStepPairing * pairing | kStepAppend | kStepRagged.
 template <typename ET, int NB, int GM, bool MULTI>
-__global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
+__device__ __forceinline__ void step_row(const void* q0, void* Kp0, const int32_t* fc_idx, const void* k_new, const void* v_new,
+                                         uint32_t flags, int Hkv, uint32_t m_hkv, int N_max, int n_cap, int F0, const StepGrid& grid,
+                                         const StepArgs& a) {
   constexpr int D = kHeadDim;
   constexpr int TPT = ScoreTraits<ET>::TPT;
   constexpr int SL = kStepNT * TPT;
@@ -401,32 +406,30 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
   __shared__ __align__(16) float srow_lds[MULTI ? 4 : SL];     // scores of a single-slice row, for the sample
   __shared__ uint32_t ticket;
 
-  int row, slice;
-  row_slice_of_block(a.rows, MULTI ? a.nslices : 1, row, slice);
-  const int b = row / a.Hkv, h = row % a.Hkv;
-  const int G = min(a.Hq / a.Hkv, GM);
+  int row = blockIdx.x, slice = 0, b, h;
+  if constexpr (MULTI) row_slice_of_block(grid.rows, grid.nslices, grid.m_slices, row, slice);
+  head_of_row(row, Hkv, m_hkv, b, h);
+  const int G = min((int)(flags & kStepGroup), GM), pairing = (int)(flags / kStepPairing % 4);
   const int t = threadIdx.x;
-  const int N = seq_n_ctx(a.n_ctx_seq, b, a.N_max);
+  const int N = flags & kStepRagged ? seq_n_ctx(a.n_ctx_seq, b, N_max) : N_max;
   if (slice * SL >= N) return;                                // beyond this sequence (ragged batches only)
   const int nvalid = (N + SL - 1) / SL;
-  const int bsel = min(seq_bsel(a.budget_seq, b, N, a.budget_max), kStepMaxBudget);
-  const ET* q = (const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D;
+  const ET* q = (const ET*)q0 + (size_t)row * G * D;
 
   // ---- scores.  Order of issue as in score_kernel: what the planes do not depend on first, then all
   // plane loads unconditionally, then a wait for the former only ----
   ET qcol[2];                                                 // head dim t mod 128 of query heads t / 128 and + 4
 #pragma unroll
   for (int j = 0; j < 2; ++j) qcol[j] = q[(size_t)min((t >> 7) + 4 * j, G - 1) * D + (t & (D - 1))];
-  const int fe = min(t, a.F - 1);
-  const int32_t fci = a.fc_idx[list_word(a.pairing, a.F, h, fe, 0)];
-  const int32_t fcj = a.fc_idx[list_word(a.pairing, a.F, h, fe, 1)];
-  const ET newkv = ((const ET*)((t & 255) < D ? a.k_new : a.v_new))[(size_t)row * D + (t & (D - 1))];
+  const int F = NB ? NB * 8 : F0, fe = min(t, F - 1);
+  const int32_t fci = fc_idx[list_word(pairing, F, h, fe, 0)];
+  const int32_t fcj = fc_idx[list_word(pairing, F, h, fe, 1)];
+  const ET newkv = ((const ET*)((t & 255) < D ? k_new : v_new))[(size_t)row * D + (t & (D - 1))];
   const int n0 = (slice * kStepNT + t) * TPT;
   const bool active = n0 < N;
-  ET* Kp = (ET*)a.Kp + (size_t)row * a.F * a.n_cap * 2;
+  ET* Kp = (ET*)Kp0 + (size_t)row * F * n_cap * 2;
   const ET* p = Kp + (size_t)(active ? n0 : 0) * 2;
-  const size_t plane = (size_t)a.n_cap * 2;
-  const int F = NB ? NB * 8 : a.F;
+  const size_t plane = (size_t)n_cap * 2;
   uint4 w[NW];
 #pragma unroll
   for (int u = 0; u < NW; ++u)
@@ -439,7 +442,7 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
     sm.ql[(t >> 7) + 4 * j][t & (D - 1)] = x;                 // heads beyond the group: copies, not added
   }
   const int n_app = N - 1;
-  const bool own_wg = a.append && n_app / SL == slice;
+  const bool append = (flags & kStepAppend) != 0, own_wg = append && n_app / SL == slice;
   if (t < D) {
     if constexpr (sizeof(ET) == 2) sm.knew[t] = (uint32_t)newkv;
     else sm.knew[t] = __float_as_uint(newkv);
@@ -447,7 +450,7 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
   __syncthreads();
   uint32_t pair_x = 0, pair_y = 0;
   if (t < F) {   // sum_g (q_g . k) = (sum_g q_g) . k, g ascending
-    const int pr = pair_dims(a.pairing, fci, fcj);
+    const int pr = pair_dims(pairing, fci, fcj);
     float lo = 0.f, hi = 0.f;
 #pragma unroll
     for (int g = 0; g < kMaxGroup; ++g) {
@@ -495,7 +498,8 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
 #pragma unroll
     for (int k = 0; k < TPT; ++k) acc[k] = n_app % TPT == k ? s : acc[k];
   }
-  float* srow = a.S + (size_t)row * a.n_cap;
+  float* srow = a.S + (size_t)row * n_cap;
+  const int bsel = min(seq_bsel(a.budget_seq, b, N, a.budget_max), kStepMaxBudget);
   const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
   if (active) {
     float* out = srow + n0;
@@ -517,9 +521,9 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
   if (own_wg) {
     if (t < F) {
       if constexpr (sizeof(ET) == 2)
-        *reinterpret_cast<uint32_t*>(Kp + ((size_t)t * a.n_cap + n_app) * 2) = pair_x | (pair_y << 16);
+        *reinterpret_cast<uint32_t*>(Kp + ((size_t)t * n_cap + n_app) * 2) = pair_x | (pair_y << 16);
       else
-        *reinterpret_cast<uint2*>(Kp + ((size_t)t * a.n_cap + n_app) * 2) = make_uint2(pair_x, pair_y);
+        *reinterpret_cast<uint2*>(Kp + ((size_t)t * n_cap + n_app) * 2) = make_uint2(pair_x, pair_y);
     }
     if (t < 2 * D) {
       ET* dst = (ET*)(t < D ? a.K : a.V) + kv_row_offset(a.pm, b, n_app, a.sb, a.sn) + h * a.sh + (t & (D - 1));
@@ -557,8 +561,24 @@ __global__ __launch_bounds__(kStepNT, 4) void step_kernel(const StepArgs a) {
                        kcut, ktop);
   }
   select_row(sm.row, M, kcut, ktop, bsel, srow, N);
-  row_attend<ET, GM>(a, sm.row, row, b, h, G, bsel, a.append ? n_app : -1);
-  write_output(a, sm.row, b, h, G);
+  row_attend<ET, GM>(a, sm.row, row, b, h, G, bsel, append ? n_app : -1);
+  write_output(a, sm.row, row, G);
+}
+
+// What the first loads depend on comes first and one by one: sixteen words of such arguments are in registers when a kernel starts.
+template <typename ET, int NB, int GM>
+__global__ __launch_bounds__(kStepNT, 4) void step_kernel(const void* q, void* Kp, const int32_t* fc_idx, const void* k_new, const void* v_new,
+                                                          uint32_t flags, int Hkv, uint32_t m_hkv, int N_max, int n_cap, int F,
+                                                          const StepArgs a) {
+  step_row<ET, NB, GM, false>(q, Kp, fc_idx, k_new, v_new, flags, Hkv, m_hkv, N_max, n_cap, F, StepGrid{}, a);
+}
+// (1 float32 row of 4096 with k_new and v_new ahead of the rest, as above: 11.65 us, like this 11.24)
+template <typename ET, int NB, int GM>
+__global__ __launch_bounds__(kStepNT, 4) void step_multi_kernel(const void* q, void* Kp, const int32_t* fc_idx, uint32_t flags, int Hkv,
+                                                                uint32_t m_hkv, int N_max, int n_cap, int rows, int nslices,
+                                                                uint32_t m_slices, int F, const void* k_new, const void* v_new,
+                                                                const StepArgs a) {
+  step_row<ET, NB, GM, true>(q, Kp, fc_idx, k_new, v_new, flags, Hkv, m_hkv, N_max, n_cap, F, StepGrid{rows, nslices, m_slices}, a);
 }
 
 // One workgroup per row; the scores lie in S (an earlier launch).
@@ -567,8 +587,9 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
   using ET = float;
   __shared__ RowLds<kRowNT, GM> sm;
   const int row = blockIdx.x;
-  const int b = row / a.Hkv, h = row % a.Hkv;
-  const int G = min(a.Hq / a.Hkv, GM);
+  int b, h;
+  head_of_row(row, a.Hkv, a.m_hkv, b, h);
+  const int G = min(a.G, GM);
   const int t = threadIdx.x;
   const int N = seq_n_ctx(a.n_ctx_seq, b, a.N_max);
   const int bsel = min(seq_bsel(a.budget_seq, b, N, a.budget_max), kStepMaxBudget);
@@ -592,7 +613,7 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
                                          [&](int k, int c0) { return c0 + ((k >> 2) * kRowNT + t) * 4 + (k & 3); }, load_scores, kcut, ktop);
   select_row(sm, M, kcut, ktop, bsel, srow, N);
   row_attend<ET, GM>(a, sm, row, b, h, G, bsel, -1);
-  write_output(a, sm, b, h, G);
+  write_output(a, sm, row, G);
 }
 
 // nwgs workgroups per row; the scores lie in S, the lists of the largest in `list` (score_list_kernel).  Every workgroup of a
@@ -604,30 +625,38 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // workgroups ahead of the gather / like this: 8 rows of 32768, 4 heads, B = 2048: 17.8 / 16.9; 32 rows, 7 heads, B = 6219: 49.9 / 45.2;
 // 8 rows of 131072, F = 32, B = 1024: 40.5 / 37.4; 128 rows of 16384, B = 256: 41.3 / 38.4; 64 rows of 126490, 7 heads, B = 6250 (which had
 // the split form): 57.3 / 43.9; 3 rows of 96425, 4 heads, B = 3490: 26.4 / 20.6; 2 rows of 6987, F = 32, B = 911: 15.9 / 16.3.
+// (What the lists' loads depend on comes first and one by one: such arguments are in registers when a kernel starts.  room: 0 where
+// sequences have lengths and budgets of their own; share: tokens of a workgroup, whole tiles.)
 template <int G, int Q>
-__global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
+__global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* lims, int rows, int nwgs, uint32_t m_wgs, int N_max, int n_cap,
+                                                          int room, int budget, int share_max, int Hkv, uint32_t m_hkv,
+                                                          const StepArgs a) {
   using ET = uint16_t;
   constexpr int D = kHeadDim;
   __shared__ RowLds<kListNT, G, 1, kListMaxShare> sm;
   __shared__ float red[G];
   __shared__ uint32_t ticket;
-  int row, wg;
-  row_slice_of_block(a.rows, a.nwgs, row, wg);
-  const int b = row / a.Hkv, h = row % a.Hkv;
+  int row, wg, b, h;
+  row_slice_of_block(rows, nwgs, m_wgs, row, wg);
+  head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x, lane = t & 63;
-  const int N = seq_n_ctx(a.n_ctx_seq, b, a.N_max);
-  const int bsel = seq_bsel(a.budget_seq, b, N, a.budget_max);
-  const int share = ((bsel + a.nwgs - 1) / a.nwgs + 15) & ~15;      // whole tiles
-  const int p0 = wg * share, p1 = min(bsel, p0 + share), nvalid = (bsel + share - 1) / share;
+  int N = N_max, bsel = budget, share = share_max;
+  if (room == 0) {
+    N = seq_n_ctx(a.n_ctx_seq, b, N_max);
+    bsel = seq_bsel(a.budget_seq, b, N, budget);
+    share = ((bsel + nwgs - 1) / nwgs + 15) & ~15;
+    room = list_room(bsel, N, a.cap);
+  }
+  const int p0 = wg * share, p1 = min(bsel, p0 + share);
   if (p0 >= bsel) return;
   FASA_T_DECL(8);
   FASA_T(0);
-  const float* srow = a.S + (size_t)row * a.n_cap;
-  const ListRow list = ListRow::at(a.list, a.lims, row, a.n_cap, N, a.room ? a.room : list_room(bsel, N, a.cap));
+  const float* srow = a.S + (size_t)row * n_cap;
+  const ListRow list = ListRow::at(lists, lims, row, n_cap, N, room);
   MfmaTile<G> tile;
   if (t == 0) sm.p_new = -1;
   const ListSet set = select_listed<false, Q>(sm, list, bsel, srow, N, p0, p1);
-  tile.load_q((const ET*)a.q + ((size_t)b * a.Hq + (size_t)h * G) * D, lane & 15, lane >> 4);
+  tile.load_q((const ET*)a.q + (size_t)row * G * D, lane & 15, lane >> 4);
   int ready = set.n_above - p0;
   if (!set.usable) {
     row_select<false>(sm, bsel, srow, N, p0, p1);
@@ -648,11 +677,11 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
   });
   FASA_T(2);
   if (wg == 0 && t == 0) a.ctl[row].list_cut = set.from;      // (here: what waits for a load would wait for a store ahead of it too)
-  if (nvalid == 1) {
-    write_output(a, sm, b, h, G);
+  if (share >= bsel) {
+    write_output(a, sm, row, G);
     return;
   }
-  const size_t pbase = ((size_t)row * a.nwgs + wg) * G;
+  const size_t pbase = ((size_t)row * nwgs + wg) * G;
   if (t < G * (D / 4)) {
     const int g = t / (D / 4), d4 = t % (D / 4);
     float mn, ls;
@@ -666,6 +695,7 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
   FASA_T(3);
   publish_barrier();
   if (t == 0) ticket = atomicAdd(&a.ctl[row].done_att, 1u);
+  const int nvalid = (bsel + share - 1) / share;              // (under the ticket's round trip)
   __syncthreads();
   FASA_T(4);
   FASA_T_PRINT(t == 0 && row == 0 && (wg == 0 || ticket == (uint32_t)nvalid - 1u),
@@ -673,7 +703,7 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(const StepArgs a) {
                FASA_T_D(2, 1), FASA_T_D(3, 2), FASA_T_D(4, 3));
   if (ticket != (uint32_t)nvalid - 1u) return;
   if (t == 0) a.ctl[row].done_att = 0;                        // clean for the next call
-  combine_row<G, NothingUnderLoads, 16, kListNT, kListMaxWgs>(a.part_acc, a.part_ml, a.O, row, b, h, a.Hq, nvalid, a.nwgs,
+  combine_row<G, NothingUnderLoads, 16, kListNT, kListMaxWgs>(a.part_acc, a.part_ml, a.O, row, nvalid, nwgs,
                                                               reinterpret_cast<float*>(sm.merge + 8192), red,
                                                               reinterpret_cast<float*>(sm.merge));
 }
@@ -738,10 +768,16 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
 
 template <typename ET, int NB, int GM>
 static hipError_t launch_step_v(const StepArgs& a, hipStream_t st) {
-  if (a.nslices == 1) return launch("fasa_step", step_kernel<ET, NB, GM, false>, dim3(a.rows), dim3(kStepNT), st, a);
+  const uint32_t flags = (uint32_t)a.G | kStepPairing * (uint32_t)a.pairing | (a.append ? kStepAppend : 0u) |
+                         (a.n_ctx_seq || a.budget_seq ? kStepRagged : 0u);
+  const dim3 grid(a.rows * a.nslices), block(kStepNT);
+  if (a.nslices == 1)
+    return launch("fasa_step", step_kernel<ET, NB, GM>, grid, block, st, a.q, a.Kp, a.fc_idx, a.k_new, a.v_new, flags, a.Hkv, a.m_hkv,
+                  a.N_max, a.n_cap, a.F, a);
   // float32 rows of several slices: with one query head only (plan_step)
   if constexpr (sizeof(ET) == 2 || GM == 1)
-    return launch("fasa_step", step_kernel<ET, NB, GM, true>, dim3(a.rows * a.nslices), dim3(kStepNT), st, a);
+    return launch("fasa_step", step_multi_kernel<ET, NB, GM>, grid, block, st, a.q, a.Kp, a.fc_idx, flags, a.Hkv, a.m_hkv, a.N_max, a.n_cap,
+                  a.rows, a.nslices, a.m_slices, a.F, a.k_new, a.v_new, a);
   return hipErrorInvalidValue;
 }
 // The list lengths in use have an instance each, where no load of the planes stands under a test.  float32, us, with the
@@ -773,9 +809,11 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
                                   : (long long)s.n_ctx * s.kv_stride_n;
   if ((most >> 3) >= 0xfffffff0ll) return p;
   const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx, rows = s.batch * s.n_kv_heads;
-  // 32 entries a thread, which is what its registers hold beside the tiles: rows of up to 22000 tokens with half of them
-  // selected, 49000 with 18.9 %, 67000 with 12.5 %.
-  const int cap = list_cap(s.n_ctx, bsel, kListNT, 8);
+  // 32 entries a thread, which is what its registers hold beside the tiles: rows of up to 49000 tokens with 18.9 % of them selected,
+  // 67000 with 12.5 %; with more than a third selected, where a list is hardly shorter than the row, 24: 17400 tokens with half.  us, split form /
+  // lists: 32 rows of 20000, 7 heads, B = 8000: 52.5 / 46.8; 8 rows of 22000, 8 heads, 7500: 27.6 / 21.1; of 45000, 4 heads, 9000:
+  // 33.4 / 26.1; on the other side of the line, of 20000, B = 9000: 28.2 / 26.5, 1 row 23.6 / 22.3.
+  const int cap = list_cap(s.n_ctx, bsel, kListNT, bsel > s.n_ctx / 3 ? 6 : 8);
   if (!cap) return p;
   // One workgroup up to B = 256: what it gathers (50 KB per us) takes less than a hand-over and a merge.  us with 1 / 2 / as many as
   // fit: 8 rows of 16384, B = 128: 12.7 / 14.3 / 14.3, 256: 14.6 / 15.5 / 15.1, 320: 15.3 / 16.0 / 15.1; 128 rows, 256: 41.7 / 42.9.
@@ -793,15 +831,26 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   return p;
 }
 
+struct ListLaunch {
+  uint2 *list, *lims;
+  int nwgs, room;
+};
+template <int G, int Q>
+static hipError_t launch_list_q(const fasa_shape& s, const ListLaunch& l, const StepArgs& a, hipStream_t st) {
+  const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx;
+  return launch("fasa_list", list_kernel<G, Q>, dim3(a.rows * l.nwgs), dim3(kListNT), st, l.list, l.lims, a.rows, l.nwgs,
+                div_magic(l.nwgs, (long long)a.rows * l.nwgs), a.N_max, a.n_cap, l.room, bsel,
+                ((bsel + l.nwgs - 1) / l.nwgs + 15) & ~15, a.Hkv, a.m_hkv, a);
+}
 template <int G>
-static hipError_t launch_list_g(const StepArgs& a, hipStream_t st) {
+static hipError_t launch_list_g(const fasa_shape& s, const ListLaunch& l, const StepArgs& a, hipStream_t st) {
   switch (a.cap / (4 * kListNT)) {
-    case 1: return launch("fasa_list", list_kernel<G, 1>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 2: return launch("fasa_list", list_kernel<G, 2>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 3: return launch("fasa_list", list_kernel<G, 3>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 4: return launch("fasa_list", list_kernel<G, 4>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 6: return launch("fasa_list", list_kernel<G, 6>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
-    case 8: return launch("fasa_list", list_kernel<G, 8>, dim3(a.rows * a.nwgs), dim3(kListNT), st, a);
+    case 1: return launch_list_q<G, 1>(s, l, a, st);
+    case 2: return launch_list_q<G, 2>(s, l, a, st);
+    case 3: return launch_list_q<G, 3>(s, l, a, st);
+    case 4: return launch_list_q<G, 4>(s, l, a, st);
+    case 6: return launch_list_q<G, 6>(s, l, a, st);
+    case 8: return launch_list_q<G, 8>(s, l, a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -818,19 +867,18 @@ hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* 
                                          AppendArgs{k_new, v_new, K, V, pm, false});
   if (e != hipSuccess) return e;
   StepArgs a = step_args(s, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, rl, pm);
-  a.list = list; a.lims = lims;
-  a.room = room; a.cap = p.cap;
-  a.nwgs = p.nwgs;
+  a.cap = p.cap;
   a.part_acc = part_acc; a.part_ml = part_ml;
+  const ListLaunch l{list, lims, p.nwgs, room};
   switch (s.n_q_heads / s.n_kv_heads) {
-    case 1: return launch_list_g<1>(a, st);
-    case 2: return launch_list_g<2>(a, st);
-    case 3: return launch_list_g<3>(a, st);
-    case 4: return launch_list_g<4>(a, st);
-    case 5: return launch_list_g<5>(a, st);
-    case 6: return launch_list_g<6>(a, st);
-    case 7: return launch_list_g<7>(a, st);
-    case 8: return launch_list_g<8>(a, st);
+    case 1: return launch_list_g<1>(s, l, a, st);
+    case 2: return launch_list_g<2>(s, l, a, st);
+    case 3: return launch_list_g<3>(s, l, a, st);
+    case 4: return launch_list_g<4>(s, l, a, st);
+    case 5: return launch_list_g<5>(s, l, a, st);
+    case 6: return launch_list_g<6>(s, l, a, st);
+    case 7: return launch_list_g<7>(s, l, a, st);
+    case 8: return launch_list_g<8>(s, l, a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -849,7 +897,8 @@ static StepArgs step_args(const fasa_shape& s, const void* q, void* K, void* V, 
   a.rows = s.batch * s.n_kv_heads;
   const int per = kStepNT * (s.dtype == FASA_BF16 ? 4 : 2);
   a.nslices = (s.n_ctx + per - 1) / per;
-  a.Hq = s.n_q_heads; a.Hkv = s.n_kv_heads; a.F = s.n_fc; a.N_max = s.n_ctx; a.n_cap = s.n_cap;
+  a.m_slices = div_magic(a.nslices, (long long)a.rows * a.nslices);
+  a.G = s.n_q_heads / s.n_kv_heads; a.Hkv = s.n_kv_heads; a.m_hkv = div_magic(s.n_kv_heads, a.rows); a.F = s.n_fc; a.N_max = s.n_ctx; a.n_cap = s.n_cap;
   a.budget_max = s.budget;
   a.t_pitch = s.budget < s.n_ctx ? s.budget : s.n_ctx;
   a.pairing = s.pairing;

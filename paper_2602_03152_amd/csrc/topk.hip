@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ S
                                                      uint32_t* __restrict__ hist,
                                                      RowCtl* __restrict__ ctl,
                                                      uint2* __restrict__ cand,
-                                                     int32_t* __restrict__ T, int rows, int nslices,
+                                                     int32_t* __restrict__ T, int rows, int nslices, uint32_t m_slices,
                                                      int N_max, int n_cap, int budget_max, int t_pitch,
                                                      int Hkv, const int32_t* __restrict__ n_ctx_seq,
                                                      const int32_t* __restrict__ budget_seq, PageMap pm,
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ S
   __shared__ uint2 lc[kCandLds];
 
   int row, slice;
-  row_slice_of_block(rows, nslices, row, slice);
+  row_slice_of_block(rows, nslices, m_slices, row, slice);
   const int t = threadIdx.x;
   const int N = seq_n_ctx(n_ctx_seq, row / Hkv, N_max);
   const int bsel = seq_bsel(budget_seq, row / Hkv, N, budget_max);
@@ -217,12 +217,12 @@ struct TopkLds {
 };
 
 template <int Q, bool ONE>
-__global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int32_t* __restrict__ T, uint2* list, uint2* lims,
-                                                       uint32_t* tickets, int ticket_stride, int rows, int nsegs,
-                                                       int N, int n_cap, int bsel, int room) {
+__global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int rows, int nsegs, uint32_t m_segs, int N,
+                                                       int n_cap, int bsel, int room, uint2* list, uint2* lims, uint32_t* tickets,
+                                                       int ticket_stride, int32_t* __restrict__ T) {
   __shared__ TopkLds sm;
   int row, seg;
-  row_slice_of_block(rows, nsegs, row, seg);
+  row_slice_of_block(rows, nsegs, m_segs, row, seg);
   const int t = threadIdx.x;
   const float* srow = S + (size_t)row * n_cap;
   const int n0 = seg * kTopkSeg + 4 * t;
@@ -292,8 +292,8 @@ hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bs
   const int nsegs = (n_ctx + kTopkSeg - 1) / kTopkSeg, q = p.cap / (4 * kTopkNT);
   auto kernel = nsegs == 1 ? topk_kernel<1, true> : q == 1 ? topk_kernel<1, false>
                 : q == 2 ? topk_kernel<2, false> : q == 3 ? topk_kernel<3, false> : topk_kernel<4, false>;
-  return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, T, list, lims, tickets, ticket_stride, rows,
-                nsegs, n_ctx, n_cap, bsel, list_room(bsel, n_ctx, p.cap));
+  return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, rows, nsegs, div_magic(nsegs, (long long)rows * nsegs),
+                n_ctx, n_cap, bsel, list_room(bsel, n_ctx, p.cap), list, lims, tickets, ticket_stride, T);
 }
 
 // zeroes the histogram and the row counters: 1-D grid, one uint4 per thread
@@ -315,11 +315,11 @@ hipError_t launch_select(const fasa_shape& s, const float* S, const uint32_t* hi
   const int n_short = (s.n_ctx + kSelTokShort - 1) / kSelTokShort;
   if ((long long)rows * n_short <= kSelShortMaxBlocks)
     return launch("fasa_select", select_kernel<kSelTokShort>, dim3(rows * n_short), dim3(256), st, S,
-                  const_cast<uint32_t*>(hist), ctl, cand, T, rows, n_short, s.n_ctx, s.n_cap, s.budget,
+                  const_cast<uint32_t*>(hist), ctl, cand, T, rows, n_short, div_magic(n_short, (long long)rows * n_short), s.n_ctx, s.n_cap, s.budget,
                   t_pitch, s.n_kv_heads, rl.n_ctx, rl.budget, pm, Tslot);
   const int nslices = (s.n_ctx + kSelTokLong - 1) / kSelTokLong;
   return launch("fasa_select", select_kernel<kSelTokLong>, dim3(rows * nslices), dim3(256), st, S,
-                const_cast<uint32_t*>(hist), ctl, cand, T, rows, nslices, s.n_ctx, s.n_cap, s.budget,
+                const_cast<uint32_t*>(hist), ctl, cand, T, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_ctx, s.n_cap, s.budget,
                 t_pitch, s.n_kv_heads, rl.n_ctx, rl.budget, pm, Tslot);
 }
 
