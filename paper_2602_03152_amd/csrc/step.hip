@@ -822,6 +822,13 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   int w = bsel <= 256 ? 1 : kAssumedCUs / rows;
   if (w > (bsel + 63) / 64) w = (bsel + 63) / 64;
   if (w > kListMaxWgs) w = kListMaxWgs;
+  // ... and no more than the row's last workgroup merges in one go (combine_row: eight partials in flight for each of 512 / 32 G threads, four
+  // times over at most), for up to 400 tokens each.  us, as many as fit / so: 4 rows, 8 heads, B = 3205 (50 / 16): 22.4 / 20.2; 1 row, 8 heads, 4748
+  // (64 / 16): 19.1 / 17.9, 8000 (64 / 16 / 32): 23.5 / 23.0 / 21.8; 8 rows, 7 heads, 1821 (28 / 16): 18.6 / 17.8; 8 rows, 8 heads, 1500 (24 /
+  // 16): 15.9 / 15.3; 3 rows, 4 heads, 3490 (55 / 32): 19.8 / 19.3; 4 rows, 1 head, 8000 (64 / 32): 21.7 / 21.4; 2 rows, 2 heads, 4000
+  // (63 / 32): 17.5 / 16.7
+  const int chunk = s.n_q_heads / s.n_kv_heads <= 4 ? 32 : 16, merged = chunk * ((bsel + 400 * chunk - 1) / (400 * chunk));
+  if (w > merged) w = merged;
   if (w > max_splits) w = max_splits;
   if (w < 1) w = 1;
   const int share = ((bsel + w - 1) / w + 15) / 16 * 16;
