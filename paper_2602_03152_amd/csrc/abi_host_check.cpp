@@ -60,9 +60,9 @@ int main() {
             if (form == fasa::kStepRow) EXPECT(bsel <= fasa::kStepMaxBudget && dtype == FASA_F32 && g <= 4);
             // the lists' loads fit the threads that make them, and the shares cover the budget
             const fasa::ListPlan l = fasa::plan_list(s, fasa::kNoPaging, 256);
-            if (l.cap) {
-              const int nsegs = (n + 255) / 256, share = ((bsel + l.nwgs - 1) / l.nwgs + 15) / 16 * 16, q = l.cap / 2048;
-              EXPECT(dtype == FASA_BF16 && nsegs <= 2048 && l.cap % 2048 == 0);
+            if (l.quads) {
+              const int nsegs = (n + 255) / 256, share = ((bsel + l.nwgs - 1) / l.nwgs + 15) / 16 * 16, q = l.quads;
+              EXPECT(dtype == FASA_BF16 && nsegs <= 2048);
               EXPECT((q == 1 || q == 2 || q == 3 || q == 4 || q == 6 || q == 8) && l.nwgs >= 1 &&
                      l.nwgs <= 64 && share <= 2048 && (long long)share * l.nwgs >= bsel && share * (l.nwgs - 1) < bsel);
               ++lists;

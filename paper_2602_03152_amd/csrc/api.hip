@@ -303,7 +303,7 @@ int fasa_topk(const fasa_shape* shape, const float* S, int32_t* T, void* ws, siz
   uint2* cand = (uint2*)(base + w.cand_off);
   hipStream_t st = (hipStream_t)stream;
   const TopkPlan tp = plan_topk(shape->n_ctx, shape->budget);
-  if (tp.cap != 0) {
+  if (tp.quads != 0) {
     // lists go where the candidates go, the segments' descriptions where the records go
     FASA_HIP(launch_topk(tp, w.rows, shape->n_ctx, shape->n_cap, shape->budget, S, T, cand, (uint2*)(base + w.rec_off),
                          &ctl->done_sel, (int)(sizeof(RowCtl) / sizeof(uint32_t)), st));
@@ -381,7 +381,7 @@ static int decode_step_common(const fasa_shape* shape, const fasa_paging* paging
   const AppendArgs ap{k_new, v_new, K, V, pm, false};
   const StepForm form = plan_step(*shape, pm);
   const ListPlan lp = form == kStepOne || select_all ? ListPlan{0, 0} : plan_list(*shape, pm, w.max_splits);
-  if (lp.cap != 0) {
+  if (lp.quads != 0) {
     // two launches: scores + lists of the largest, then selection out of the lists and attention by equal shares
     FASA_HIP(launch_list_step(*shape, lp, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, cand,
                               (uint2*)(base + w.rec_off), (float*)(base + w.part_acc_off), (float*)(base + w.part_ml_off), st,

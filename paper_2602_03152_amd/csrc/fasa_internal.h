@@ -177,11 +177,11 @@ struct AppendArgs {
 };
 constexpr AppendArgs kNoAppend = {nullptr, nullptr, nullptr, nullptr, {nullptr, 0, 0, 0}, false};
 // Where the scoring kernel leaves the lists of a row's largest scores (row_list.h: ListRow): [row][n_cap] 8 bytes a token, and
-// [row][kListLimPitch] segments.  room: places of a segment's list, or 0 where list_room() gives each row its own; cap: what it fits into.
+// [row][kListLimPitch] segments; pitch: places of a segment.
 struct ListOut {
   uint2* list;
   uint2* lims;
-  int room, cap;
+  int pitch;
 };
 // hist == nullptr: scores only.  adaptive_ctl != nullptr (with hist): the adaptive histogram of the
 // fused step (bins of lin_bin, location and scale left in the row counters) instead of the
@@ -194,10 +194,10 @@ hipError_t launch_score_list(const fasa_shape& s, const void* q, void* Kp, const
                              const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap);
 // zeroes the histogram and the row counters (workspace initialisation)
 hipError_t launch_ws_clear(const fasa_shape& s, uint32_t* hist, RowCtl* ctl, hipStream_t st);
-// TopK-I of given scores in one launch (topk.hip): the set of every row to T.  cap == 0: not for this shape.
+// TopK-I of given scores in one launch (topk.hip): the set of every row to T.  quads == 0: not for this shape.
 // list, lims: as ListOut; tickets [row * ticket_stride], zero.
 struct TopkPlan {
-  int cap;         // places of a row's list that the selecting threads hold
+  int quads;       // of places of a row's list that a selecting thread holds
 };
 TopkPlan plan_topk(int n_ctx, int bsel);
 hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint2* list,
@@ -231,14 +231,14 @@ hipError_t launch_step(const fasa_shape& s, StepForm form, const void* q, void* 
                        RowCtl* ctl, hipStream_t st, RaggedLens rl = {nullptr, nullptr}, PageMap pm = kNoPaging);
 
 // Selection out of lists and attention by one or several workgroups per row, after a scoring launch that makes the
-// lists (step.hip).  cap == 0: not for this shape.
+// lists (step.hip).  quads == 0: not for this shape.
 struct ListPlan {
   int nwgs;        // workgroups per row
-  int cap;         // places of a row's list that a workgroup's threads hold
+  int quads;       // of places of a row's list that each of a workgroup's threads holds
 };
 ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits);
-// Places of a row's list that nt threads hold, at most `most` quads each; 0: more than fit.
-int list_cap(int n, int bsel, int nt, int most);
+// Quads of places of a row's list that each of nt threads holds (1 - 4, 6 or 8 of them); 0: more than `most`, or than there are segments.
+int list_quads(int n, int bsel, int nt, int most);
 hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* q, void* K, void* V, void* Kp,
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                             RowCtl* ctl, uint2* list, uint2* lims, float* part_acc, float* part_ml, hipStream_t st,

@@ -33,18 +33,13 @@ __host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m) {
   return (int)(ps + 4.0f * sqrtf(ps) + 3.0f);
 }
 
-// Places of a segment's list (a multiple of 4): four standard deviations and five above the 256 B / N of its scores that are expected among
-// the B best.  Of independent scores hardly one segment in 10^6 has more of them than that, and a row's list is 1.7 B long
-// for 6219 of 32905 tokens, 2.5 B for 2048 of 32768, 5 B for 256 of 16384, 6 B for 1024 of 131072.  cap: places that the
-// selecting threads hold.  The launch that lists and the one that selects both come to the same number: nothing is contracted.
-__host__ __device__ __forceinline__ int list_room(int bsel, int n, int cap) {
-#pragma clang fp contract(off)
-  const int nsegs = (n + kListSeg - 1) / kListSeg;
-  const float p = (float)bsel * ((float)kListSeg / (float)n), r = p + 4.0f * sqrtf(p);
-  int room = ((int)r + 5 + 3) & ~3;
-  room = room < kListSeg ? room : kListSeg;
-  const int most = (cap / nsegs) & ~3;
-  return room < most ? room : most;
+// How many scores of a segment are worth listing (a multiple of 4): four standard deviations and five above the 256 B / N of them that
+// are expected among the B best.  Of independent scores hardly one segment in 10^6 has more of them than that, and a row's list is 1.7 B long
+// for 6219 of 32905 tokens, 2.5 B for 2048 of 32768, 5 B for 256 of 16384, 6 B for 1024 of 131072.
+__host__ __device__ __forceinline__ int list_room(int bsel, int n) {
+  const float p = (float)bsel * ((float)kListSeg / (float)n);
+  const int room = ((int)(p + 4.0f * sqrtf(p)) + 5 + 3) & ~3;
+  return room < kListSeg ? room : kListSeg;
 }
 
 // The cut: a score that at least r (1 .. 64 KPL) of the sample's scores reach and hardly more, in steps of a 256th of
@@ -110,17 +105,18 @@ struct SegLds {
   };
 };
 
-// Where a row's lists lie: [segment][room] keys, then as many token numbers inside the segment, a byte each, and per segment the
-// key from which on it is listed completely and its largest finite score's.
+// Where a row's lists lie: [segment][pitch] keys, then as many token numbers inside the segment, a byte each, and per segment the
+// key from which on it is listed completely and its largest finite score's.  n_max: the longest row's tokens; places and pitch (a multiple of 4, at most
+// 256) are the same for all rows, so that whoever selects can ask for them before it knows how long its row is.
 struct ListRow {
   uint32_t* keys;
   uint32_t* toks;          // four a word
   uint2* lims;
-  int room;
+  int pitch;
   // 5 bytes a place: no more than the row's 8 bytes per token of capacity (a multiple of 64), however short the row
-  __host__ __device__ __forceinline__ static ListRow at(uint2* list, uint2* lims, int row, int n_cap, int n, int room) {
+  __host__ __device__ __forceinline__ static ListRow at(uint2* list, uint2* lims, int row, int n_cap, int n_max, int pitch) {
     uint32_t* keys = (uint32_t*)(list + (size_t)row * n_cap);
-    return {keys, keys + (size_t)((n + kListSeg - 1) / kListSeg) * room, lims + (size_t)row * kListLimPitch, room};
+    return {keys, keys + (size_t)((n_max + kListSeg - 1) / kListSeg) * pitch, lims + (size_t)row * kListLimPitch, pitch};
   }
 };
 
@@ -136,12 +132,12 @@ __device__ __forceinline__ int seg_bin(const uint32_t* bins, uint32_t room) {
   return 4 * last + __builtin_amdgcn_readlane(j, last);
 }
 
-// Lists the segment of `tokens` tokens whose score 4 lane + k is x[k].  The cut is the lowest edge of a bin (256 over the
+// Lists the segment of `tokens` tokens whose score 4 lane + k is x[k]: at most `room` of them, 4 .. pitch.  The cut is the lowest edge of a bin (256 over the
 // spread of the scores) that no more than `room` scores reach; where the bins are so coarse that a quarter of the room is
 // left, because one score lies far from all others, the bin below the cut is cut into 256 again.  SHARED: read in this launch.
 template <bool SHARED>
-__device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int seg, const ListRow& l, SegLds& sm) {
-  const int lane = lane_id(), room = l.room;
+__device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int seg, const ListRow& l, int room, SegLds& sm) {
+  const int lane = lane_id();
   bool in[4];
   float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
@@ -215,10 +211,10 @@ __device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int se
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   const uint2 lim = make_uint2(fits ? score_key(cut) : 0xffffffffu, top);
-  if (4 * lane < room) {
+  if (4 * lane < l.pitch) {
     const uint4 k4 = *reinterpret_cast<const uint4*>(sm.keys + 4 * lane);
     const uint32_t t4 = sm.toks4[lane];
-    const size_t at = (size_t)seg * (room / 4) + lane;
+    const size_t at = (size_t)seg * (l.pitch / 4) + lane;
     if constexpr (SHARED) {
       st_agent(reinterpret_cast<uint2*>(l.keys) + 2 * at, make_uint2(k4.x, k4.y));
       st_agent(reinterpret_cast<uint2*>(l.keys) + 2 * at + 1, make_uint2(k4.z, k4.w));
@@ -338,6 +334,33 @@ __device__ __forceinline__ void row_select(Lds& sm, int bsel, const float* srow,
   resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, p0, p1);
 }
 
+// The bin of kListBins with (entries in bins above it) < need <= (entries from it on), found by every wave for itself: a round trip
+// to LDS and a scan, where the search that shares it among all threads has four barriers.  n = 0: fewer than `need` in all.
+struct BinAt {
+  int bin, above, n;
+};
+__device__ __forceinline__ BinAt wave_find_bin(const uint32_t* hist, uint32_t need) {
+  const int lane = lane_id();
+  const uint4 a = reinterpret_cast<const uint4*>(hist)[lane], b = reinterpret_cast<const uint4*>(hist)[kWave + lane];
+  const uint32_t sa = a.x + a.y + a.z + a.w, sb = b.x + b.y + b.z + b.w;
+  const uint32_t ib = wave_suffix_sum(sb), tb = (uint32_t)__builtin_amdgcn_readlane((int)ib, 0), ia = wave_suffix_sum(sa) + tb;
+  const bool up = tb >= need;
+  const uint4 c = up ? b : a;
+  const uint32_t incl = up ? ib : ia, s4 = incl - (up ? sb : sa);         // s4: in bins above this lane's four
+  const uint32_t s3 = s4 + c.w, s2 = s3 + c.z, s1 = s2 + c.y;
+  const unsigned long long m = __ballot(s4 < need && need <= incl);
+  if (m == 0ull) return {0, 0, 0};
+  const int l = __ffsll((long long)m) - 1;
+  const int j = s3 >= need ? 3 : s2 >= need ? 2 : s1 >= need ? 1 : 0;
+  const uint32_t above = j == 3 ? s4 : j == 2 ? s3 : j == 1 ? s2 : s1, n = j == 3 ? c.w : j == 2 ? c.z : j == 1 ? c.y : c.x;
+  return {(up ? kListBins / 2 : 0) + 4 * l + __builtin_amdgcn_readlane(j, l), __builtin_amdgcn_readlane((int)above, l),
+          __builtin_amdgcn_readlane((int)n, l)};
+}
+// log2 of the bins' width for keys from klo to ktop
+__device__ __forceinline__ int list_shift(uint32_t klo, uint32_t ktop) {
+  return max(0, 23 - __clz((int)(ktop > klo ? ktop - klo : 0u)));
+}
+
 // The same among listed scores that the threads hold (key 0: none; klo > 0).  Places go by thread.
 // False: fewer than B scores are listed (the histogram is zero then).
 template <int EPT, typename Lds>
@@ -397,32 +420,6 @@ __device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EP
 // ---------------------------------------------------------------------------------------------
 // Selection of a row out of its segments' lists
 // ---------------------------------------------------------------------------------------------
-// The bin of kListBins with (entries in bins above it) < need <= (entries from it on), found by every wave for itself: a round trip
-// to LDS and a scan, where the search that shares it among all threads has four barriers.  n = 0: fewer than `need` in all.
-struct BinAt {
-  int bin, above, n;
-};
-__device__ __forceinline__ BinAt wave_find_bin(const uint32_t* hist, uint32_t need) {
-  const int lane = lane_id();
-  const uint4 a = reinterpret_cast<const uint4*>(hist)[lane], b = reinterpret_cast<const uint4*>(hist)[kWave + lane];
-  const uint32_t sa = a.x + a.y + a.z + a.w, sb = b.x + b.y + b.z + b.w;
-  const uint32_t ib = wave_suffix_sum(sb), tb = (uint32_t)__builtin_amdgcn_readlane((int)ib, 0), ia = wave_suffix_sum(sa) + tb;
-  const bool up = tb >= need;
-  const uint4 c = up ? b : a;
-  const uint32_t incl = up ? ib : ia, s4 = incl - (up ? sb : sa);         // s4: in bins above this lane's four
-  const uint32_t s3 = s4 + c.w, s2 = s3 + c.z, s1 = s2 + c.y;
-  const unsigned long long m = __ballot(s4 < need && need <= incl);
-  if (m == 0ull) return {0, 0, 0};
-  const int l = __ffsll((long long)m) - 1;
-  const int j = s3 >= need ? 3 : s2 >= need ? 2 : s1 >= need ? 1 : 0;
-  const uint32_t above = j == 3 ? s4 : j == 2 ? s3 : j == 1 ? s2 : s1, n = j == 3 ? c.w : j == 2 ? c.z : j == 1 ? c.y : c.x;
-  return {(up ? kListBins / 2 : 0) + 4 * l + __builtin_amdgcn_readlane(j, l), __builtin_amdgcn_readlane((int)above, l),
-          __builtin_amdgcn_readlane((int)n, l)};
-}
-// log2 of the bins' width for keys from klo to ktop
-__device__ __forceinline__ int list_shift(uint32_t klo, uint32_t ktop) {
-  return max(0, 23 - __clz((int)(ktop > klo ? ktop - klo : 0u)));
-}
 __device__ __forceinline__ uint32_t wave_max_key(uint32_t v) {            // (in lane 63)
   v = max(v, dpp_u32<0x111, 0xF>(v));
   v = max(v, dpp_u32<0x112, 0xF>(v));
@@ -507,32 +504,47 @@ __device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListRow& l, int
   return min(have, (uint32_t)Lds::kExtraPerWave);
 }
 
-// Selection of a row out of its list (4 Q entries a thread) by all threads: places p0 .. p1 - 1 of its set to sm.put, as far as they
-// are known without ranking the candidates.  SHARED: listed in this launch.  Ends with a block barrier.
+// What a thread holds of a row's list, requested before anything about the row but its place is known.  n_max: tokens of the longest row.
+// SHARED: listed in this launch.
+template <bool SHARED, int NT, int Q>
+struct ListHeld {
+  uint2 lim;               // of segment t
+  uint32_t key[4 * Q], tok4[Q];
+  __device__ __forceinline__ void request(const ListRow& l, int n_max) {
+    const int t = threadIdx.x, most = (n_max + kListSeg - 1) / kListSeg, nq = most * (l.pitch / 4);
+    const __amdgpu_buffer_rsrc_t rk = agent_buffer(l.keys);
+    lim = SHARED ? ld_agent(l.lims + min(t, most - 1)) : l.lims[min(t, most - 1)];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const int g = j * NT + t, at = g < nq ? g : 0;
+      uint4 x;
+      if constexpr (SHARED) x = agent_load_u128(rk, (uint32_t)at * 16u);
+      else x = reinterpret_cast<const uint4*>(l.keys)[at];
+      key[4 * j] = x.x; key[4 * j + 1] = x.y; key[4 * j + 2] = x.z; key[4 * j + 3] = x.w;
+    }
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const int g = j * NT + t, at = g < nq ? g : 0;
+      if constexpr (SHARED) tok4[j] = ld_agent(l.toks + at);
+      else tok4[j] = l.toks[at];
+    }
+  }
+};
+
+// Selection of a row out of its list by all threads: places p0 .. p1 - 1 of its set to sm.put, as far as they
+// are known without ranking the candidates.  Ends with a block barrier.
 template <bool SHARED, int Q, typename Lds>
-__device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, int bsel, const float* srow, int N, int p0, int p1) {
+__device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, ListHeld<SHARED, Lds::kThreads, Q>& held, int bsel, const float* srow,
+                                                 int N, int p0, int p1) {
   constexpr int NT = Lds::kThreads, NWV = Lds::kWaves, EPT = 4 * Q;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int nsegs = (N + kListSeg - 1) / kListSeg, per = l.room / 4, nq = nsegs * per;
-  const __amdgpu_buffer_rsrc_t rk = agent_buffer(l.keys);
-  uint2 lt = SHARED ? ld_agent(l.lims + min(t, nsegs - 1)) : l.lims[min(t, nsegs - 1)];
-  uint32_t key[EPT], tok4[Q];
-#pragma unroll
-  for (int j = 0; j < Q; ++j) {
-    const int g = j * NT + t, at = g < nq ? g : 0;
-    uint4 x;
-    if constexpr (SHARED) x = agent_load_u128(rk, (uint32_t)at * 16u);
-    else x = reinterpret_cast<const uint4*>(l.keys)[at];
-    key[4 * j] = x.x; key[4 * j + 1] = x.y; key[4 * j + 2] = x.z; key[4 * j + 3] = x.w;
-  }
-#pragma unroll
-  for (int j = 0; j < Q; ++j) {
-    const int g = j * NT + t, at = g < nq ? g : 0;
-    if constexpr (SHARED) tok4[j] = ld_agent(l.toks + at);
-    else tok4[j] = l.toks[at];
-  }
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, per = l.pitch / 4;
+  uint2& lt = held.lim;
+  uint32_t (&key)[EPT] = held.key;
+  uint32_t (&tok4)[Q] = held.tok4;
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
   if (t == 0) { sm.thr[2] = sm.thr[3] = 0; sm.n_cnd = 0; }
+  const int nsegs = (N + kListSeg - 1) / kListSeg, nq = nsegs * per;
+  if (t >= nsegs) lt = make_uint2(0u, 0u);
   for (int i = NT + t; i < nsegs; i += NT) {
     const uint2 x = SHARED ? ld_agent(l.lims + i) : l.lims[i];
     lt = make_uint2(max(lt.x, x.x), max(lt.y, x.y));
@@ -612,7 +624,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, int 
     clear();
     {
       // no listed entry lies below the lowest of the completeness keys, but for those of a short last segment that is listed whole
-      const uint32_t a = wave_max_key(lt.x <= kListAll || nsegs > NT ? 0u : ~lt.x);
+      const uint32_t a = wave_max_key(t >= nsegs || lt.x <= kListAll || nsegs > NT ? 0u : ~lt.x);
       if (lane == kWave - 1) sm.wtot[wave] = a;
       __syncthreads();
       uint32_t b = 0;

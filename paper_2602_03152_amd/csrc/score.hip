@@ -329,8 +329,10 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
 }
 
 // Scores and lists (row_list.h).  1-D grid of rows * nslices workgroups of four waves, which score 1024 tokens as above; each lists its
-// own 256, with nothing to wait for.  Eight planes in flight leave room for eight workgroups per compute unit.  The scores are stored
-// non-temporal, since little of them is read again: 0.7 us of 29.
+// own 256, with nothing to wait for.  Eight planes in flight leave room for eight workgroups per compute unit; 16, where there is no more than one
+// or two for each, gain nothing (8 rows of 32768: 16.8 / 16.8 us per step, of 34625: 16.1 / 16.6).  The scores are stored non-temporal, since little of
+// them is read again: 0.7 us of 29.  us, with a fifth wave that scored a sample of the row for a common cut / like this: 128 rows of 16384, F = 16:
+// 30.0 / 27.7 (score_kernel alone 25.3); 32 rows of 32905: 16.8 / 15.8; 8 of 131072, F = 32: 27.1 / 26.2; 8 of 32768: 5.7 / 5.9.
 constexpr int kListScoreNT = 256;
 template <typename ET, int NB, bool APPEND, int PAIR>
 __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
@@ -397,7 +399,8 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
       if (t < D) knew[t] = newkv;
     }
   }
-  const int room = lists.room ? lists.room : list_room(seq_bsel(budget_seq, b, N, budget_max), N, lists.cap);   // (under the loads)
+  int room = lists.pitch;
+  if (n_ctx_seq || budget_seq) room = min(room, list_room(seq_bsel(budget_seq, b, N, budget_max), N));          // (under the loads)
   const bool own_wg = APPEND && n_app / SL == slice;
   __syncthreads();
   if (t < D / 2) {
@@ -458,7 +461,8 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
   }
   const int ls = __builtin_amdgcn_readfirstlane(slice * (SL / kListSeg) + (t >> 6));
   if (ls * kListSeg < N)
-    seg_list<false>(acc, min(N - ls * kListSeg, kListSeg), ls, ListRow::at(lists.list, lists.lims, row, n_cap, N, room), seg[t >> 6]);
+    seg_list<false>(acc, min(N - ls * kListSeg, kListSeg), ls, ListRow::at(lists.list, lists.lims, row, n_cap, N_max, lists.pitch), room,
+                    seg[t >> 6]);
   if constexpr (APPEND) {
     if (own_wg) {   // the whole new row to K (threads 0..127) and V (threads 128..255)
       ET* dst = (t < D ? Kc : Vc) + kv_row_offset(pm, b, n_app, sb, sn) + h * sh + (t & (D - 1));

@@ -49,8 +49,7 @@ struct StepArgs {
   int rows, nslices, G, Hkv, F, N_max, n_cap, budget_max, t_pitch, append, pairing;
   uint32_t m_slices, m_hkv;  // div_magic of nslices (list_kernel: of nwgs) and Hkv
   float scale_log2e;
-  // list_kernel: places of a row's list that a workgroup's threads hold; the workgroups' partials [row][nwgs]
-  int cap;
+  // list_kernel: the workgroups' partials [row][nwgs]
   float* part_acc;
   float* part_ml;
 };
@@ -74,6 +73,7 @@ struct RowLds {
     uint32_t sample[kSample];
   };
   uint2 cand[kSelCand];
+  uint32_t cand_at[kSelCand];                                // where their rows lie
   uint32_t ssort[kSample];                                   // keys of the sample, largest first
   __align__(16) uint32_t wl[MOST + 16];            // selected tokens, then what the gather reads for them
   float m[kWaves][GM], l[kWaves][GM];
@@ -126,12 +126,13 @@ __device__ __forceinline__ void select_row(Lds& sm, int M, uint32_t kcut, uint32
 // Attention over the tokens in sm.wl[0 .. cnt): T is written, and every wave leaves its (max, sum, weighted V)
 // in LDS (a block barrier ago when this returns).  p0: place of the first of them in T; with_q: a tile that has the queries.  Wave w takes 16-row tiles w, w + waves, ... (bf16:
 // mfma_tile.h; float32: vector ALUs).
-// ready: how many of the tokens are known already; late(put), called by all threads if that is fewer than cnt, calls put(i, token) for the others.  Tiles
-// of known tokens alone are requested before that.
+// ready: how many of the tokens are known already; late(put), called by all threads if that is fewer than cnt, calls put(i, c) for the others, each
+// of which is one of the n_cand tokens sm.cand[c].y.  Tiles of known tokens alone are requested before that.
 struct NothingLate { template <typename Put> __device__ void operator()(Put&&) const {} };
 template <typename ET, int GM, typename Lds, typename Late = NothingLate>
 __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, int b, int h, int G, int cnt, int n_app,
-                                           int p0 = 0, const MfmaTile<GM>* with_q = nullptr, int ready = 1 << 30, Late&& late = Late()) {
+                                           int p0 = 0, const MfmaTile<GM>* with_q = nullptr, int ready = 1 << 30, int n_cand = 0,
+                                           Late&& late = Late()) {
   constexpr bool kLate = !std::is_same<typename std::decay<Late>::type, NothingLate>::value;
   static_assert(!kLate || sizeof(ET) == 2, "float32 steps know all tokens");
   constexpr int D = kHeadDim;
@@ -141,16 +142,39 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
   // T, and what the gather reads: the row's element offset / 8, padded to whole tiles with the last row
   const bool paged = a.pm.table != nullptr;
   int32_t* trow = a.T + (size_t)row * a.t_pitch + p0;
-  auto known = [&](int i, int n) {
-    trow[i] = n;
-    if (n == n_app) sm.p_new = i;
-    const uint32_t e = (uint32_t)((unsigned long long)kv_row_offset(a.pm, paged ? b : 0, n, a.sb, a.sn) >> 3);
-    sm.wl[i] = e;
-    if (i == cnt - 1)
-      for (int j = cnt; j & 15; ++j) sm.wl[j] = e;
+  auto place_of = [&](int n) {
+    return (uint32_t)((unsigned long long)kv_row_offset(a.pm, paged ? b : 0, n, a.sb, a.sn) >> 3);
   };
-  for (int i = t; i < (kLate ? min(ready, cnt) : cnt); i += NT) known(i, (int)sm.wl[i]);
-  __syncthreads();
+  const int n_known = kLate ? min(ready, cnt) : cnt;
+  int t_at = n_known, t_tok = 0;
+  if constexpr (kLate) {
+    // Where their rows lie, by the wave that attends over them: no barrier.  T can wait for the first tile's requests.  A last tile is filled up
+    // with the last row, whose values are in use: another's may be anything, and NaNs stay NaNs at weight 0.  The candidates of a paged cache
+    // as well: a look-up behind the rows' loads would wait for them.
+    const int end = ready >= cnt ? (cnt + 15) & ~15 : n_known;
+    for (int i0 = wave * 16; i0 < end; i0 += 64 * NWV) {
+      if (t_at < n_known) trow[t_at] = t_tok;
+      t_at = i0 + (lane >> 4) * (16 * NWV) + (lane & 15);
+      if (t_at < end) {
+        t_tok = (int)sm.wl[min(t_at, n_known - 1)];           // (of the same tile: not a place yet)
+        sm.wl[t_at] = place_of(t_tok);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (paged && ready < cnt)
+      for (int i = t; i < n_cand; i += NT) sm.cand_at[i] = place_of((int)sm.cand[i].y);
+  } else {
+    for (int i = t; i < cnt; i += NT) {
+      const int n = (int)sm.wl[i];
+      trow[i] = n;
+      if (n == n_app) sm.p_new = i;
+      const uint32_t e = place_of(n);
+      sm.wl[i] = e;
+      if (i == cnt - 1)
+        for (int j = cnt; j & 15; ++j) sm.wl[j] = e;
+    }
+    __syncthreads();
+  }
   const ET* Kb = (const ET*)a.K + (paged ? 0 : b * a.sb) + h * a.sh;
   const ET* Vb = (const ET*)a.V + (paged ? 0 : b * a.sb) + h * a.sh;
   const ET* kn = (const ET*)a.k_new + (size_t)row * D;
@@ -161,24 +185,32 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
     const int lo = lane & 15, hi = lane >> 4;
     MfmaTile<GM> tile;
     if (with_q) tile = *with_q;
+    // (The appended row by its distance: with a choice of pointers the compiler no longer knew them for global ones, and a flat load makes every wait
+    // one for all loads and all of LDS.  8 rows of 32768, B = 2048: 16.9 -> 16.6 us; 32 of 32905, 7 heads: 45.3 -> 44.9; 8 of 1531, B = 192: 10.70 -> 10.60.)
+    const long long k_app = ((const char*)kn - (const char*)Kb) / 2, v_app = ((const char*)vn - (const char*)Vb) / 2;
     auto load_k = [&](TileKV<uint16_t>& kv, int j0) {
-      const ET* kr = Kb + ((size_t)sm.wl[j0 + lo] << 3) + 8 * hi;
-      if (p_new >= j0 && p_new < j0 + 16) kr = p_new == j0 + lo ? kn + 8 * hi : kr;   // (wave-uniform test)
+      long long o = (long long)((size_t)sm.wl[j0 + lo] << 3);
+      if constexpr (!kLate) {
+        if (p_new >= j0 && p_new < j0 + 16) o = p_new == j0 + lo ? k_app : o;   // (wave-uniform test)
+      }
+      const ET* kr = Kb + o + 8 * hi;
 #pragma unroll
       for (int i = 0; i < 4; ++i) kv.kc[i] = *reinterpret_cast<const uint4*>(kr + 32 * i);
     };
     auto load_v = [&](TileKV<uint16_t>& kv, int j0) {
       const uint4 e4 = *reinterpret_cast<const uint4*>(&sm.wl[j0 + 4 * hi]);
       const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
-      const ET* vp[4];
+      long long o[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) vp[i] = Vb + ((size_t)e[i] << 3) + 8 * lo;
-      if (p_new >= j0 && p_new < j0 + 16) {
+      for (int i = 0; i < 4; ++i) o[i] = (long long)((size_t)e[i] << 3);
+      if constexpr (!kLate) {
+        if (p_new >= j0 && p_new < j0 + 16) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) vp[i] = p_new == j0 + 4 * hi + i ? vn + 8 * lo : vp[i];
+          for (int i = 0; i < 4; ++i) o[i] = p_new == j0 + 4 * hi + i ? v_app : o[i];
+        }
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) kv.vr[i] = *reinterpret_cast<const uint4*>(vp[i]);
+      for (int i = 0; i < 4; ++i) kv.vr[i] = *reinterpret_cast<const uint4*>(Vb + o[i] + 8 * lo);
     };
     const int jw = wave * 16;
     TileKV<uint16_t> kv;
@@ -188,8 +220,17 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
         load_k(kv, jw);
         load_v(kv, jw);
       }
+      if (t_at < n_known) trow[t_at] = t_tok;
       if (ready < cnt) {
-        late(known);
+        if (paged) __syncthreads();                           // (cand_at)
+        late([&](int i, int c) {
+          const int n = (int)sm.cand[c].y;
+          const uint32_t e = paged ? sm.cand_at[c] : place_of(n);
+          trow[i] = n;
+          sm.wl[i] = e;
+          if (i == cnt - 1)
+            for (int j = cnt; j & 15; ++j) sm.wl[j] = e;
+        });
         __syncthreads();
         if (!early && jw < cnt) {
           load_k(kv, jw);
@@ -622,14 +663,15 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // differ by 14 %, and leave a threshold bin to resolve at the end).  A chain of round trips and of the instructions between them.
 // The candidates of the threshold bin are ranked by the one or two workgroups whose shares end in it, while the rows of the
 // tokens already known are under way.  us per step, lists of 1024 tokens by a cut of a sample of the row, and candidates ranked by all
-// workgroups ahead of the gather / like this: 8 rows of 32768, 4 heads, B = 2048: 17.8 / 16.9; 32 rows, 7 heads, B = 6219: 49.9 / 45.2;
-// 8 rows of 131072, F = 32, B = 1024: 40.5 / 37.4; 128 rows of 16384, B = 256: 41.3 / 38.4; 64 rows of 126490, 7 heads, B = 6250 (which had
-// the split form): 57.3 / 43.9; 3 rows of 96425, 4 heads, B = 3490: 26.4 / 20.6; 2 rows of 6987, F = 32, B = 911: 15.9 / 16.3.
-// (What the lists' loads depend on comes first and one by one: such arguments are in registers when a kernel starts.  room: 0 where
-// sequences have lengths and budgets of their own; share: tokens of a workgroup, whole tiles.)
+// workgroups ahead of the gather / like this: 8 rows of 32768, 4 heads, B = 2048: 17.8 / 16.5; 32 rows, 7 heads, B = 6219: 49.9 / 44.9;
+// 8 rows of 131072, F = 32, B = 1024: 40.6 / 36.9; 128 rows of 16384, B = 256: 41.3 / 37.7; 64 rows of 126490, 7 heads, B = 6250 (which had
+// the split form): 57.3 / 43.9; 3 rows of 96425, 4 heads, B = 3490: 26.4 / 19.4; 2 rows of 6987, F = 32, B = 911: 15.9 / 15.7; paged, 32
+// sequences' rows of 1600 - 6423, B = 66: 13.9 / 14.2.
+// (What the lists' loads depend on comes first and one by one: such arguments are in registers when a kernel starts.  pitch: negative
+// where sequences have lengths and budgets of their own, which N_max and budget bound; share_max: tokens of a workgroup, whole tiles.)
 template <int G, int Q>
 __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* lims, int rows, int nwgs, uint32_t m_wgs, int N_max, int n_cap,
-                                                          int room, int budget, int share_max, int Hkv, uint32_t m_hkv,
+                                                          int pitch, int budget, int share_max, int Hkv, uint32_t m_hkv,
                                                           const StepArgs a) {
   using ET = uint16_t;
   constexpr int D = kHeadDim;
@@ -640,22 +682,23 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* l
   row_slice_of_block(rows, nwgs, m_wgs, row, wg);
   head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x, lane = t & 63;
+  const ListRow list = ListRow::at(lists, lims, row, n_cap, N_max, abs(pitch));
+  ListHeld<false, kListNT, Q> held;
+  held.request(list, N_max);
   int N = N_max, bsel = budget, share = share_max;
-  if (room == 0) {
+  if (pitch < 0) {
     N = seq_n_ctx(a.n_ctx_seq, b, N_max);
     bsel = seq_bsel(a.budget_seq, b, N, budget);
-    share = ((bsel + nwgs - 1) / nwgs + 15) & ~15;
-    room = list_room(bsel, N, a.cap);
+    share = ((int)fast_div((uint32_t)(bsel + nwgs - 1), (uint32_t)nwgs, m_wgs) + 15) & ~15;
   }
   const int p0 = wg * share, p1 = min(bsel, p0 + share);
   if (p0 >= bsel) return;
   FASA_T_DECL(8);
   FASA_T(0);
   const float* srow = a.S + (size_t)row * n_cap;
-  const ListRow list = ListRow::at(lists, lims, row, n_cap, N, room);
   MfmaTile<G> tile;
   if (t == 0) sm.p_new = -1;
-  const ListSet set = select_listed<false, Q>(sm, list, bsel, srow, N, p0, p1);
+  const ListSet set = select_listed<false, Q>(sm, list, held, bsel, srow, N, p0, p1);
   tile.load_q((const ET*)a.q + (size_t)row * G * D, lane & 15, lane >> 4);
   int ready = set.n_above - p0;
   if (!set.usable) {
@@ -667,12 +710,12 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* l
   }
   FASA_T(1);
   // the candidates are ranked while the rows of the others are under way
-  row_attend<ET, G>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile, ready, [&](auto&& put) {
+  row_attend<ET, G>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile, ready, set.n_cand, [&](auto&& put) {
     constexpr int P = kListNT / kSelCand;
     if ((t & ~(kWave - 1)) / P < set.n_cand) {                // (the waves that have any)
       const int ci = t / P;
       const int rank = rank_in_list<P>(sm.cand, set.n_cand, ci), p = set.n_above + rank;
-      if (t % P == 0 && ci < set.n_cand && rank < set.need && p >= p0 && p < p1) put(p - p0, (int)sm.cand[ci].y);
+      if (t % P == 0 && ci < set.n_cand && rank < set.need && p >= p0 && p < p1) put(p - p0, ci);
     }
   });
   FASA_T(2);
@@ -793,13 +836,12 @@ static hipError_t launch_step_f(const StepArgs& a, hipStream_t st) {
     default: return launch_step_v<ET, 0, GM>(a, st);
   }
 }
-// Places of the threads' lists, whole quads for each of nt threads, that a row's take; 0: more than `most` quads, or segments.
-int list_cap(int n, int bsel, int nt, int most) {
+int list_quads(int n, int bsel, int nt, int most) {
   const int nsegs = (n + kListSeg - 1) / kListSeg;
   if (nsegs > kListMaxSegs) return 0;
-  const int q = (nsegs * (list_room(bsel, n, 1 << 30) / 4) + nt - 1) / nt;
-  const int held = q <= 4 ? q : q <= 6 ? 6 : 8;                // (the instances there are)
-  return q <= most && held <= most ? held * 4 * nt : 0;
+  const int q = (nsegs * (list_room(bsel, n) / 4) + nt - 1) / nt;
+  if (q > most) return 0;
+  return q <= 4 ? q : q <= 6 ? 6 : 8;                          // (the instances there are)
 }
 
 ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
@@ -813,8 +855,8 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   // 67000 with 12.5 %; with more than a third selected, where a list is hardly shorter than the row, 24: 17400 tokens with half.  us, split form /
   // lists: 32 rows of 20000, 7 heads, B = 8000: 52.5 / 46.8; 8 rows of 22000, 8 heads, 7500: 27.6 / 21.1; of 45000, 4 heads, 9000:
   // 33.4 / 26.1; on the other side of the line, of 20000, B = 9000: 28.2 / 26.5, 1 row 23.6 / 22.3.
-  const int cap = list_cap(s.n_ctx, bsel, kListNT, bsel > s.n_ctx / 3 ? 6 : 8);
-  if (!cap) return p;
+  const int quads = list_quads(s.n_ctx, bsel, kListNT, bsel > s.n_ctx / 3 ? 6 : 8);
+  if (!quads) return p;
   // One workgroup up to B = 256: what it gathers (50 KB per us) takes less than a hand-over and a merge.  us with 1 / 2 / as many as
   // fit: 8 rows of 16384, B = 128: 12.7 / 14.3 / 14.3, 256: 14.6 / 15.5 / 15.1, 320: 15.3 / 16.0 / 15.1; 128 rows, 256: 41.7 / 42.9.
   // Beyond, as many as fit at once, one per compute unit, with at least 64 tokens each: 80 rows, B = 700: 36.6 / 35.6 / 34.5 (3) /
@@ -834,24 +876,25 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   const int share = ((bsel + w - 1) / w + 15) / 16 * 16;
   if (share > kListMaxShare) return p;
   p.nwgs = (bsel + share - 1) / share;
-  p.cap = cap;
+  p.quads = quads;
   return p;
 }
 
 struct ListLaunch {
   uint2 *list, *lims;
-  int nwgs, room;
+  int nwgs, quads, pitch;
 };
 template <int G, int Q>
 static hipError_t launch_list_q(const fasa_shape& s, const ListLaunch& l, const StepArgs& a, hipStream_t st) {
   const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx;
-  return launch("fasa_list", list_kernel<G, Q>, dim3(a.rows * l.nwgs), dim3(kListNT), st, l.list, l.lims, a.rows, l.nwgs,
-                div_magic(l.nwgs, (long long)a.rows * l.nwgs), a.N_max, a.n_cap, l.room, bsel,
-                ((bsel + l.nwgs - 1) / l.nwgs + 15) & ~15, a.Hkv, a.m_hkv, a);
+  const long long wgs = (long long)a.rows * l.nwgs;
+  return launch("fasa_list", list_kernel<G, Q>, dim3((unsigned)wgs), dim3(kListNT), st, l.list, l.lims, a.rows, l.nwgs,
+                div_magic(l.nwgs, wgs > bsel + l.nwgs ? wgs : bsel + l.nwgs), a.N_max, a.n_cap,
+                a.n_ctx_seq || a.budget_seq ? -l.pitch : l.pitch, bsel, ((bsel + l.nwgs - 1) / l.nwgs + 15) & ~15, a.Hkv, a.m_hkv, a);
 }
 template <int G>
 static hipError_t launch_list_g(const fasa_shape& s, const ListLaunch& l, const StepArgs& a, hipStream_t st) {
-  switch (a.cap / (4 * kListNT)) {
+  switch (l.quads) {
     case 1: return launch_list_q<G, 1>(s, l, a, st);
     case 2: return launch_list_q<G, 2>(s, l, a, st);
     case 3: return launch_list_q<G, 3>(s, l, a, st);
@@ -869,14 +912,19 @@ hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* 
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                             RowCtl* ctl, uint2* list, uint2* lims, float* part_acc, float* part_ml, hipStream_t st,
                             RaggedLens rl, PageMap pm) {
-  const int room = rl.n_ctx || rl.budget ? 0 : list_room(s.budget < s.n_ctx ? s.budget : s.n_ctx, s.n_ctx, p.cap);
-  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ListOut{list, lims, room, p.cap}, st, rl,
+  // Sequences may ask for more of their scores than the bounds do: they have all places that the threads hold
+  const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx, nsegs = (s.n_ctx + kListSeg - 1) / kListSeg;
+  int pitch = list_room(bsel, s.n_ctx);
+  if (rl.n_ctx || rl.budget) {
+    pitch = p.quads * kListNT / nsegs * 4;
+    if (pitch > kListSeg) pitch = kListSeg;
+  }
+  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ListOut{list, lims, pitch}, st, rl,
                                          AppendArgs{k_new, v_new, K, V, pm, false});
   if (e != hipSuccess) return e;
   StepArgs a = step_args(s, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, rl, pm);
-  a.cap = p.cap;
   a.part_acc = part_acc; a.part_ml = part_ml;
-  const ListLaunch l{list, lims, p.nwgs, room};
+  const ListLaunch l{list, lims, p.nwgs, p.quads, pitch};
   switch (s.n_q_heads / s.n_kv_heads) {
     case 1: return launch_list_g<1>(s, l, a, st);
     case 2: return launch_list_g<2>(s, l, a, st);

@@ -212,13 +212,13 @@ struct TopkLds {
   uint32_t thr[4];
   uint32_t ticket, n_cnd;
   float2 cut_top;
-  int32_t* out;
+  __attribute__((address_space(1))) int32_t* out;             // (a generic pointer's stores are flat: every wait is one for all of LDS)
   __device__ __forceinline__ void put(int place, uint32_t tok) { out[place] = (int32_t)tok; }
 };
 
 template <int Q, bool ONE>
 __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__ S, int rows, int nsegs, uint32_t m_segs, int N,
-                                                       int n_cap, int bsel, int room, uint2* list, uint2* lims, uint32_t* tickets,
+                                                       int n_cap, int bsel, int pitch, uint2* list, uint2* lims, uint32_t* tickets,
                                                        int ticket_stride, int32_t* __restrict__ T) {
   __shared__ TopkLds sm;
   int row, seg;
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
     for (int i = t; i < kSelBins; i += kTopkNT) sm.hist[i] = 0;
     if (t == 0) {
       sm.thr[2] = 0;
-      sm.out = T + (size_t)row * bsel;
+      sm.out = (__attribute__((address_space(1))) int32_t*)(T + (size_t)row * bsel);
     }
     __syncthreads();
     if (t < kWave) {
@@ -266,18 +266,20 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
       row_select<false>(sm, bsel, srow, N, 0, bsel);           // (NaNs that have the key of nothing)
     return;
   }
-  const ListRow l = ListRow::at(list, lims, row, n_cap, N, room);
+  const ListRow l = ListRow::at(list, lims, row, n_cap, N, pitch);
   const int ls = __builtin_amdgcn_readfirstlane(seg * (kTopkSeg / kListSeg) + (t >> 6));
-  if (ls * kListSeg < N) seg_list<true>(acc, min(N - ls * kListSeg, kListSeg), ls, l, sm.seg[t >> 6]);
+  if (ls * kListSeg < N) seg_list<true>(acc, min(N - ls * kListSeg, kListSeg), ls, l, pitch, sm.seg[t >> 6]);
   publish_barrier();
   if (t == 0) sm.ticket = atomicAdd(&tickets[(size_t)row * ticket_stride], 1u);
   __syncthreads();
   if (sm.ticket != (uint32_t)nsegs - 1u) return;
   if (t == 0) {
     tickets[(size_t)row * ticket_stride] = 0;                  // clean for the next call
-    sm.out = T + (size_t)row * bsel;
+    sm.out = (__attribute__((address_space(1))) int32_t*)(T + (size_t)row * bsel);
   }
-  const ListSet set = select_listed<true, Q>(sm, l, bsel, srow, N, 0, bsel);
+  ListHeld<true, kTopkNT, Q> held;
+  held.request(l, N);
+  const ListSet set = select_listed<true, Q>(sm, l, held, bsel, srow, N, 0, bsel);
   if (set.usable) resolve_threshold(sm, set.klo, bsel, set.need, set.n_cand, srow, N, 0, bsel);
   else row_select<false>(sm, bsel, srow, N, 0, bsel);
 }
@@ -285,15 +287,15 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
 // us, histogram and selection launch / like this: 8 rows of 8192, B = 500: 11.3 / 6.8, 16 of 20011, 1250: 12.4 / 8.2, 8 of 32768,
 // 2048: 12.0 / 8.9, 128 of 16384, 256: 14.5 / 10.0.  The last workgroup's own work ends it: beyond 16 entries a thread the row is
 // selected by many workgroups (32 rows of 32905, B = 6219: 13.7 / 17.8).
-TopkPlan plan_topk(int n_ctx, int bsel) { return TopkPlan{bsel < n_ctx ? list_cap(n_ctx, bsel, kTopkNT, 4) : 0}; }
+TopkPlan plan_topk(int n_ctx, int bsel) { return TopkPlan{bsel < n_ctx ? list_quads(n_ctx, bsel, kTopkNT, 4) : 0}; }
 
 hipError_t launch_topk(const TopkPlan& p, int rows, int n_ctx, int n_cap, int bsel, const float* S, int32_t* T, uint2* list,
                        uint2* lims, uint32_t* tickets, int ticket_stride, hipStream_t st) {
-  const int nsegs = (n_ctx + kTopkSeg - 1) / kTopkSeg, q = p.cap / (4 * kTopkNT);
+  const int nsegs = (n_ctx + kTopkSeg - 1) / kTopkSeg, q = p.quads;
   auto kernel = nsegs == 1 ? topk_kernel<1, true> : q == 1 ? topk_kernel<1, false>
                 : q == 2 ? topk_kernel<2, false> : q == 3 ? topk_kernel<3, false> : topk_kernel<4, false>;
   return launch("fasa_topk", kernel, dim3(rows * nsegs), dim3(kTopkNT), st, S, rows, nsegs, div_magic(nsegs, (long long)rows * nsegs),
-                n_ctx, n_cap, bsel, list_room(bsel, n_ctx, p.cap), list, lims, tickets, ticket_stride, T);
+                n_ctx, n_cap, bsel, list_room(bsel, n_ctx), list, lims, tickets, ticket_stride, T);
 }
 
 // zeroes the histogram and the row counters: 1-D grid, one uint4 per thread
