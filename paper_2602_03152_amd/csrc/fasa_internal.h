@@ -34,8 +34,9 @@ struct RowCtl {
   uint32_t done_att;  // attention workgroups of this row that wrote their partial
   float bin_mu;       // adaptive histogram of the fused step: written by the scoring kernel of a call,
   float bin_inv;      // read by its selection kernel (never has to be zero)
-  uint32_t list_cut;  // lists of a row (row_list.h): the key from which on the selection looked at its scores; written only
-  uint32_t pad[25];
+  uint32_t list_cut;  // lists of a row (row_list.h): the key from which on the selection looked at its scores, and how it
+  uint32_t list_how;  // went about it (ListSet); written only
+  uint32_t pad[24];
 };
 static_assert(sizeof(RowCtl) == 128, "one line per row");
 

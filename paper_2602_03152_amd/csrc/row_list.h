@@ -437,13 +437,15 @@ struct ListSet {
   uint32_t klo;
   int n_above, need, n_cand;
   uint32_t from;           // the key from which on the row's scores were looked at
+  uint32_t how;            // kList..., counts of the list << 8, waits for scores read again << 16
 };
+constexpr uint32_t kListAlone = 1, kListReread = 2, kListRow = 3;   // out of the list; with scores read again; out of all of the row's scores
 
 // Scores of segments that are not listed completely from klo on, from there to where their lists begin: f(in, key, token) for all lanes
 // of a wave, which takes 256 / waves tokens of every such segment, so that waves share what lies together; 16 segments at a time,
 // in two loads.  All threads call; there is a barrier ahead of the first f.
 template <bool SHARED, typename Lds, typename F>
-__device__ __forceinline__ void for_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo, F&& f) {
+__device__ __forceinline__ void for_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo, uint32_t& how, F&& f) {
   constexpr int NT = Lds::kThreads, LPS = kWave / Lds::kWaves, SPL = kWave / LPS;   // lanes per segment, segments per load
   const int t = threadIdx.x, lane = t & 63, off = (t >> 6) * (4 * LPS) + 4 * (lane % LPS);
   for (int c0 = 0; c0 < nsegs; c0 += NT) {
@@ -456,6 +458,7 @@ __device__ __forceinline__ void for_beyond(Lds& sm, const ListRow& l, int nsegs,
       const uint32_t lim = sm.lim[s0 + lane];
       unsigned long long m = __ballot(lim > klo);
       while (m != 0ull) {
+        how += 1u << 16;
         float4 x[2];
         int at[2];
         uint32_t end[2];
@@ -491,10 +494,11 @@ __device__ __forceinline__ void for_beyond(Lds& sm, const ListRow& l, int nsegs,
 // The same to the wave's own part of sm.extra.  Returns their number; sm.thr[3] becomes 1 if there was no room.  The caller has a barrier
 // behind it.
 template <bool SHARED, typename Lds>
-__device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo) {
+__device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo,
+                                                  uint32_t& how) {
   uint2* out = sm.extra + (threadIdx.x >> 6) * Lds::kExtraPerWave;
   uint32_t have = 0;
-  for_beyond<SHARED>(sm, l, nsegs, srow, N, klo, [&](bool in, uint32_t key, uint32_t tok) {
+  for_beyond<SHARED>(sm, l, nsegs, srow, N, klo, how, [&](bool in, uint32_t key, uint32_t tok) {
     const unsigned long long b = __ballot(in);
     const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, have));
     if (in && pos < (uint32_t)Lds::kExtraPerWave) out[pos] = make_uint2(key, tok);
@@ -563,7 +567,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
   uint32_t klo = 1, ktop = 0;
 #pragma unroll
   for (int w = 0; w < NWV; ++w) { klo = max(klo, sm.wtot[w]); ktop = max(ktop, sm.wtot2[w]); }
-  uint32_t from = klo;
+  uint32_t from = klo, how = kListAlone;
 #pragma unroll
   for (int j = 0; j < Q; ++j) {
     const bool in = j * NT + t < nq;
@@ -600,6 +604,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
   };
   // one range: true if it holds `need` entries
   auto search = [&]() {
+    how += 1u << 8;
     count();
     const BinAt b = wave_find_bin(sm.hist, (uint32_t)need);
     n_cand = b.n;
@@ -620,7 +625,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
   };
   if (__builtin_expect(!narrow(klo), false)) {
     // Segments with more of the best than they had room for.  From a key that the B-th best of the listed entries reaches:
-    const ListSet none = {false, 0u, 0, 0, 0, from};
+    auto none = [&]() { return ListSet{false, 0u, 0, 0, 0, from, how | kListRow}; };
     clear();
     {
       // no listed entry lies below the lowest of the completeness keys, but for those of a short last segment that is listed whole
@@ -636,28 +641,29 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
         enough = narrow(1u);
       }
       clear();
-      if (!enough) return none;                                // fewer than B are listed
+      if (!enough) return none();                                // fewer than B are listed
     }
-    have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo);
+    have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo, how);
     __syncthreads();
     if (sm.thr[3] != 0) {
       // ... which so many of these segments' scores reach that they don't fit: they are counted, and those gathered that reach the
       // bin of the threshold
       const uint32_t lo = klo;
       shift = list_shift(lo, ktop); need = bsel; khi = 0xffffffffu;
-      for_beyond<SHARED>(sm, l, nsegs, srow, N, lo, [&](bool in, uint32_t key, uint32_t) {
+      for_beyond<SHARED>(sm, l, nsegs, srow, N, lo, how, [&](bool in, uint32_t key, uint32_t) {
         if (in) atomicAdd(&sm.hist[min((key - lo) >> shift, (uint32_t)kListBins - 1u)], 1u);
       });
-      if (!search()) { clear(); return none; }
+      if (!search()) { clear(); return none(); }
       if (t == 0) sm.thr[3] = 0;
       clear();
-      have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo);
+      have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo, how);
       __syncthreads();
-      if (sm.thr[3] != 0) return none;                         // (ties)
+      if (sm.thr[3] != 0) return none();                         // (ties)
     }
     over = true;
+    how += kListReread - kListAlone;
     from = klo;
-    if (!narrow(klo)) { clear(); return none; }                // (NaNs only)
+    if (!narrow(klo)) { clear(); return none(); }                // (NaNs only)
   }
   FASA_T(1);
   const int n_above = bsel - need;
@@ -722,7 +728,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
   FASA_T(2);
   FASA_T_PRINT(t == 0 && blockIdx.x == 0, "listed: threshold %llu places %llu (x10ns), %d entries, %d of %d candidates\n", FASA_T_D(1, 0),
                FASA_T_D(2, 1), 4 * nq, need, n_cand);
-  return {true, klo, n_above, need, n_cand, from};
+  return {true, klo, n_above, need, n_cand, from, how};
 }
 
 }  // namespace fasa

@@ -719,7 +719,7 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* l
     }
   });
   FASA_T(2);
-  if (wg == 0 && t == 0) a.ctl[row].list_cut = set.from;      // (here: what waits for a load would wait for a store ahead of it too)
+  if (wg == 0 && t == 0) *reinterpret_cast<uint2*>(&a.ctl[row].list_cut) = make_uint2(set.from, set.how);   // (here: what waits for a load would wait for a store ahead of it too)
   if (share >= bsel) {
     write_output(a, sm, row, G);
     return;
