@@ -178,11 +178,11 @@ struct AppendArgs {
 };
 constexpr AppendArgs kNoAppend = {nullptr, nullptr, nullptr, nullptr, {nullptr, 0, 0, 0}, false};
 // Where the scoring kernel leaves the lists of a row's largest scores (row_list.h: ListRow): [row][n_cap] 8 bytes a token, and
-// [row][kListLimPitch] segments; pitch: places of a segment.
+// [row][kListLimPitch] segments; places: of a row; pitch: of a segment, where all rows have the same length and budget.
 struct ListOut {
   uint2* list;
   uint2* lims;
-  int pitch;
+  int places, pitch;
 };
 // hist == nullptr: scores only.  adaptive_ctl != nullptr (with hist): the adaptive histogram of the
 // fused step (bins of lin_bin, location and scale left in the row counters) instead of the
@@ -240,6 +240,8 @@ struct ListPlan {
 ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits);
 // Quads of places of a row's list that each of nt threads holds (1 - 4, 6 or 8 of them); 0: more than `most`, or than there are segments.
 int list_quads(int n, int bsel, int nt, int most);
+// Places of a row's list.  by_sequence: n and bsel bound the sequences' own.
+int list_places(int n, int bsel, int quads, bool by_sequence);
 hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* q, void* K, void* V, void* Kp,
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                             RowCtl* ctl, uint2* list, uint2* lims, float* part_acc, float* part_ml, hipStream_t st,

@@ -38,8 +38,15 @@ __host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m) {
 // for 6219 of 32905 tokens, 2.5 B for 2048 of 32768, 5 B for 256 of 16384, 6 B for 1024 of 131072.
 __host__ __device__ __forceinline__ int list_room(int bsel, int n) {
   const float p = (float)bsel * ((float)kListSeg / (float)n);
-  const int room = ((int)(p + 4.0f * sqrtf(p)) + 5 + 3) & ~3;
+  const int room = ((int)fmaf(4.0f, sqrtf(p), p) + 5 + 3) & ~3;    // (one rounding on both sides of the lists)
   return room < kListSeg ? room : kListSeg;
+}
+// Places of a segment in a row of n tokens that has `places` of them (a multiple of 4; at least 4 a segment).  A row with fewer
+// tokens than another and no larger budget has need of fewer places in all, so this is list_room but for its rounding up to whole quads.
+// (The quotient is exact below 256, and no place is beyond the row's.)
+__device__ __forceinline__ int list_pitch(int places, int bsel, int n) {
+  const float q = ((float)places + 0.5f) * __builtin_amdgcn_rcpf((float)((n + kListSeg - 1) / kListSeg));
+  return min(list_room(bsel, n), (int)fminf(q, (float)kListSeg) & ~3);
 }
 
 // The cut: a score that at least r (1 .. 64 KPL) of the sample's scores reach and hardly more, in steps of a 256th of
@@ -105,18 +112,21 @@ struct SegLds {
   };
 };
 
-// Where a row's lists lie: [segment][pitch] keys, then as many token numbers inside the segment, a byte each, and per segment the
-// key from which on it is listed completely and its largest finite score's.  n_max: the longest row's tokens; places and pitch (a multiple of 4, at most
-// 256) are the same for all rows, so that whoever selects can ask for them before it knows how long its row is.
+// Where a row's lists lie: [segment][pitch] keys, then, behind the keys' `places`, as many token numbers inside the segment, a byte each,
+// and per segment the key from which on it is listed completely and its largest finite score's.  The places of a row follow from the longest row
+// and the largest budget, so that whoever selects can ask for all of them, in order, before it knows how long its row is; what
+// of them is a segment's (pitch, a multiple of 4, at most 256) is the row's own: a short one among longer ones with the same budget has more of
+// its best in every segment.
 struct ListRow {
   uint32_t* keys;
   uint32_t* toks;          // four a word
   uint2* lims;
   int pitch;
-  // 5 bytes a place: no more than the row's 8 bytes per token of capacity (a multiple of 64), however short the row
-  __host__ __device__ __forceinline__ static ListRow at(uint2* list, uint2* lims, int row, int n_cap, int n_max, int pitch) {
+  // 5 bytes a place, and no more places than whole segments: no more than the row's 8 bytes per token of capacity (a multiple of 64) from 257
+  // tokens on
+  __host__ __device__ __forceinline__ static ListRow at(uint2* list, uint2* lims, int row, int n_cap, int places, int pitch) {
     uint32_t* keys = (uint32_t*)(list + (size_t)row * n_cap);
-    return {keys, keys + (size_t)((n_max + kListSeg - 1) / kListSeg) * pitch, lims + (size_t)row * kListLimPitch, pitch};
+    return {keys, keys + places, lims + (size_t)row * kListLimPitch, pitch};
   }
 };
 
@@ -132,12 +142,12 @@ __device__ __forceinline__ int seg_bin(const uint32_t* bins, uint32_t room) {
   return 4 * last + __builtin_amdgcn_readlane(j, last);
 }
 
-// Lists the segment of `tokens` tokens whose score 4 lane + k is x[k]: at most `room` of them, 4 .. pitch.  The cut is the lowest edge of a bin (256 over the
-// spread of the scores) that no more than `room` scores reach; where the bins are so coarse that a quarter of the room is
+// Lists the segment of `tokens` tokens whose score 4 lane + k is x[k]: at most as many of them as it has places, 8 or more.  The cut is the lowest edge of a bin (256 over the
+// spread of the scores) that no more scores reach; where the bins are so coarse that a quarter of the places is
 // left, because one score lies far from all others, the bin below the cut is cut into 256 again.  SHARED: read in this launch.
 template <bool SHARED>
-__device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int seg, const ListRow& l, int room, SegLds& sm) {
-  const int lane = lane_id();
+__device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int seg, const ListRow& l, SegLds& sm) {
+  const int lane = lane_id(), room = l.pitch;
   bool in[4];
   float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
@@ -508,14 +518,15 @@ __device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListRow& l, int
   return min(have, (uint32_t)Lds::kExtraPerWave);
 }
 
-// What a thread holds of a row's list, requested before anything about the row but its place is known.  n_max: tokens of the longest row.
+// What a thread holds of a row's list, requested before anything about the row but its place is known: quads t, t + NT, ... of its
+// places, whatever segments they belong to.  n_max: tokens of the longest row.
 // SHARED: listed in this launch.
 template <bool SHARED, int NT, int Q>
 struct ListHeld {
   uint2 lim;               // of segment t
   uint32_t key[4 * Q], tok4[Q];
-  __device__ __forceinline__ void request(const ListRow& l, int n_max) {
-    const int t = threadIdx.x, most = (n_max + kListSeg - 1) / kListSeg, nq = most * (l.pitch / 4);
+  __device__ __forceinline__ void request(const ListRow& l, int n_max, int places) {
+    const int t = threadIdx.x, most = (n_max + kListSeg - 1) / kListSeg, nq = places / 4;
     const __amdgpu_buffer_rsrc_t rk = agent_buffer(l.keys);
     lim = SHARED ? ld_agent(l.lims + min(t, most - 1)) : l.lims[min(t, most - 1)];
 #pragma unroll

@@ -399,8 +399,8 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
       if (t < D) knew[t] = newkv;
     }
   }
-  int room = lists.pitch;
-  if (n_ctx_seq || budget_seq) room = min(room, list_room(seq_bsel(budget_seq, b, N, budget_max), N));          // (under the loads)
+  int pitch = lists.pitch;
+  if (n_ctx_seq || budget_seq) pitch = list_pitch(lists.places, seq_bsel(budget_seq, b, N, budget_max), N);       // (under the loads)
   const bool own_wg = APPEND && n_app / SL == slice;
   __syncthreads();
   if (t < D / 2) {
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
   }
   const int ls = __builtin_amdgcn_readfirstlane(slice * (SL / kListSeg) + (t >> 6));
   if (ls * kListSeg < N)
-    seg_list<false>(acc, min(N - ls * kListSeg, kListSeg), ls, ListRow::at(lists.list, lists.lims, row, n_cap, N_max, lists.pitch), room,
+    seg_list<false>(acc, min(N - ls * kListSeg, kListSeg), ls, ListRow::at(lists.list, lists.lims, row, n_cap, lists.places, pitch),
                     seg[t >> 6]);
   if constexpr (APPEND) {
     if (own_wg) {   // the whole new row to K (threads 0..127) and V (threads 128..255)

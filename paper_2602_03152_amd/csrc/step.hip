@@ -667,11 +667,11 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // 8 rows of 131072, F = 32, B = 1024: 40.6 / 36.9; 128 rows of 16384, B = 256: 41.3 / 37.7; 64 rows of 126490, 7 heads, B = 6250 (which had
 // the split form): 57.3 / 43.9; 3 rows of 96425, 4 heads, B = 3490: 26.4 / 19.4; 2 rows of 6987, F = 32, B = 911: 15.9 / 15.7; paged, 32
 // sequences' rows of 1600 - 6423, B = 66: 13.9 / 14.2.
-// (What the lists' loads depend on comes first and one by one: such arguments are in registers when a kernel starts.  pitch: negative
-// where sequences have lengths and budgets of their own, which N_max and budget bound; share_max: tokens of a workgroup, whole tiles.)
+// (What the lists' loads depend on comes first and one by one: such arguments are in registers when a kernel starts.  places: of a row's list;
+// negative where sequences have lengths and budgets of their own, which N_max and budget bound; share_max: tokens of a workgroup, whole tiles.)
 template <int G, int Q>
 __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* lims, int rows, int nwgs, uint32_t m_wgs, int N_max, int n_cap,
-                                                          int pitch, int budget, int share_max, int Hkv, uint32_t m_hkv,
+                                                          int places, int budget, int share_max, int Hkv, uint32_t m_hkv, int pitch,
                                                           const StepArgs a) {
   using ET = uint16_t;
   constexpr int D = kHeadDim;
@@ -682,13 +682,14 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* l
   row_slice_of_block(rows, nwgs, m_wgs, row, wg);
   head_of_row(row, Hkv, m_hkv, b, h);
   const int t = threadIdx.x, lane = t & 63;
-  const ListRow list = ListRow::at(lists, lims, row, n_cap, N_max, abs(pitch));
+  ListRow list = ListRow::at(lists, lims, row, n_cap, abs(places), pitch);
   ListHeld<false, kListNT, Q> held;
-  held.request(list, N_max);
+  held.request(list, N_max, abs(places));
   int N = N_max, bsel = budget, share = share_max;
-  if (pitch < 0) {
+  if (places < 0) {
     N = seq_n_ctx(a.n_ctx_seq, b, N_max);
     bsel = seq_bsel(a.budget_seq, b, N, budget);
+    list.pitch = list_pitch(-places, bsel, N);
     share = ((int)fast_div((uint32_t)(bsel + nwgs - 1), (uint32_t)nwgs, m_wgs) + 15) & ~15;
   }
   const int p0 = wg * share, p1 = min(bsel, p0 + share);
@@ -844,6 +845,13 @@ int list_quads(int n, int bsel, int nt, int most) {
   return q <= 4 ? q : q <= 6 ? 6 : 8;                          // (the instances there are)
 }
 
+// Places of a row's list: its segments', or, where sequences have lengths and budgets of their own, all that the threads hold.
+int list_places(int n, int bsel, int quads, bool by_sequence) {
+  const int nsegs = (n + kListSeg - 1) / kListSeg, held = quads * kListNT * 4;
+  if (!by_sequence) return nsegs * list_room(bsel, n);
+  return held < nsegs * kListSeg ? held : nsegs * kListSeg;
+}
+
 ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   ListPlan p{0, 0};
   if (s.dtype != FASA_BF16) return p;                          // (float32 rows are attended on the vector ALUs here)
@@ -882,7 +890,7 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
 
 struct ListLaunch {
   uint2 *list, *lims;
-  int nwgs, quads, pitch;
+  int nwgs, quads, places, pitch;
 };
 template <int G, int Q>
 static hipError_t launch_list_q(const fasa_shape& s, const ListLaunch& l, const StepArgs& a, hipStream_t st) {
@@ -890,7 +898,7 @@ static hipError_t launch_list_q(const fasa_shape& s, const ListLaunch& l, const 
   const long long wgs = (long long)a.rows * l.nwgs;
   return launch("fasa_list", list_kernel<G, Q>, dim3((unsigned)wgs), dim3(kListNT), st, l.list, l.lims, a.rows, l.nwgs,
                 div_magic(l.nwgs, wgs > bsel + l.nwgs ? wgs : bsel + l.nwgs), a.N_max, a.n_cap,
-                a.n_ctx_seq || a.budget_seq ? -l.pitch : l.pitch, bsel, ((bsel + l.nwgs - 1) / l.nwgs + 15) & ~15, a.Hkv, a.m_hkv, a);
+                a.n_ctx_seq || a.budget_seq ? -l.places : l.places, bsel, ((bsel + l.nwgs - 1) / l.nwgs + 15) & ~15, a.Hkv, a.m_hkv, l.pitch, a);
 }
 template <int G>
 static hipError_t launch_list_g(const fasa_shape& s, const ListLaunch& l, const StepArgs& a, hipStream_t st) {
@@ -912,19 +920,14 @@ hipError_t launch_list_step(const fasa_shape& s, const ListPlan& p, const void* 
                             const int32_t* fc_idx, const void* k_new, const void* v_new, float* S, int32_t* T, float* O,
                             RowCtl* ctl, uint2* list, uint2* lims, float* part_acc, float* part_ml, hipStream_t st,
                             RaggedLens rl, PageMap pm) {
-  // Sequences may ask for more of their scores than the bounds do: they have all places that the threads hold
-  const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx, nsegs = (s.n_ctx + kListSeg - 1) / kListSeg;
-  int pitch = list_room(bsel, s.n_ctx);
-  if (rl.n_ctx || rl.budget) {
-    pitch = p.quads * kListNT / nsegs * 4;
-    if (pitch > kListSeg) pitch = kListSeg;
-  }
-  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ListOut{list, lims, pitch}, st, rl,
+  const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx;
+  const int pitch = list_room(bsel, s.n_ctx), places = list_places(s.n_ctx, bsel, p.quads, rl.n_ctx || rl.budget);
+  const hipError_t e = launch_score_list(s, q, Kp, fc_idx, S, ListOut{list, lims, places, pitch}, st, rl,
                                          AppendArgs{k_new, v_new, K, V, pm, false});
   if (e != hipSuccess) return e;
   StepArgs a = step_args(s, q, K, V, Kp, fc_idx, k_new, v_new, S, T, O, ctl, rl, pm);
   a.part_acc = part_acc; a.part_ml = part_ml;
-  const ListLaunch l{list, lims, p.nwgs, p.quads, pitch};
+  const ListLaunch l{list, lims, p.nwgs, p.quads, places, pitch};
   switch (s.n_q_heads / s.n_kv_heads) {
     case 1: return launch_list_g<1>(s, l, a, st);
     case 2: return launch_list_g<2>(s, l, a, st);

@@ -266,9 +266,10 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
       row_select<false>(sm, bsel, srow, N, 0, bsel);           // (NaNs that have the key of nothing)
     return;
   }
-  const ListRow l = ListRow::at(list, lims, row, n_cap, N, pitch);
+  const int places = (N + kListSeg - 1) / kListSeg * pitch;
+  const ListRow l = ListRow::at(list, lims, row, n_cap, places, pitch);
   const int ls = __builtin_amdgcn_readfirstlane(seg * (kTopkSeg / kListSeg) + (t >> 6));
-  if (ls * kListSeg < N) seg_list<true>(acc, min(N - ls * kListSeg, kListSeg), ls, l, pitch, sm.seg[t >> 6]);
+  if (ls * kListSeg < N) seg_list<true>(acc, min(N - ls * kListSeg, kListSeg), ls, l, sm.seg[t >> 6]);
   publish_barrier();
   if (t == 0) sm.ticket = atomicAdd(&tickets[(size_t)row * ticket_stride], 1u);
   __syncthreads();
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
     sm.out = (__attribute__((address_space(1))) int32_t*)(T + (size_t)row * bsel);
   }
   ListHeld<true, kTopkNT, Q> held;
-  held.request(l, N);
+  held.request(l, N, places);
   const ListSet set = select_listed<true, Q>(sm, l, held, bsel, srow, N, 0, bsel);
   if (set.usable) resolve_threshold(sm, set.klo, bsel, set.need, set.n_cand, srow, N, 0, bsel);
   else row_select<false>(sm, bsel, srow, N, 0, bsel);

@@ -135,6 +135,31 @@ def test_few_lists_are_short(fb, rows, n_ctx, budget, rho):
     assert (way == ALONE).all() if rho == 0.0 else (way != ROW).all()
 
 
+@pytest.mark.parametrize("equal", [False, True])
+@pytest.mark.parametrize("lens,n_ctx,budget", [
+    ([2049, 2300, 2305, 4096, 8000, 10752, 10753, 20001, 32768], 32768, 2048), ([1500, 6219, 6220, 12001, 17100, 32905, 257, 1], 32905, 6219),
+    ([1025, 1200, 8192, 21760, 50001, 99999, 131071, 1], 131072, 1024), ([2049, 5001, 9000, 16383, 16384], 16384, 256)])
+def test_short_sequences_of_one_budget(fb, lens, n_ctx, budget, equal):
+    """Sequences of other lengths with the budget of the longest: independent scores of each are selected out of its list alone."""
+    rows = len(lens)
+    dev = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")   # noqa: E731
+    run, S, T, out, V, ws = step_of(fb, make_scores("plain", rows, n_ctx, budget), budget, dev(lens), dev([budget] * rows) if equal else None)
+    print("one budget", n_ctx, budget, equal, flush=True)
+    for again in range(2):
+        T.fill_(-1)
+        out.fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        for r, n in enumerate(lens):
+            b = min(budget, n)
+            got = np.sort(T[r, 0, :b].cpu().numpy())
+            np.testing.assert_array_equal(got, O.topk(S[r:r + 1, :, :n].cpu().numpy(), b, n)[0, 0])
+            want = V.double()[torch.from_numpy(got).long().cuda()].mean(0)
+            assert (out[r, 0].double() - want).abs().max().item() <= 1e-4          # as in test_best_that_lie_together
+    way = how_selected(ws, rows)[1]
+    assert (way == ALONE).all(), dict(zip(lens, way))
+
+
 # Where NaN scores rank is unspecified, but a set has B tokens and every call ends: a list is short here (the finite scores are the
 # sample's), and the search for the threshold starts at a key below zero, from which bins are wide.  (csrc/abi_host_check.cpp
 # goes through the ranges.)
