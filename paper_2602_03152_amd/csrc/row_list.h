@@ -8,8 +8,9 @@
 //   select   select_listed: whoever selects holds the row's list in registers.  From the highest of the segments' completeness
 //            keys on the list holds all of the row's scores; if B of its entries reach that key, the B best of the row are among
 //            them.  If not, a row's best lie together, in segments with more of them than there was room for: those
-//            segments' scores are read again, from a key on that B listed ones reach, into LDS.  row_select, which reads all
-//            of a row's scores, is left for what does not fit there (ties in their thousands, NaNs).
+//            segments' scores are read again, from a key on that B scores reach, and counted with the listed ones.  row_select, which
+//            reads all of a row's scores, is left for rows of which fewer than B are listed or whose best don't fit in LDS (ties in their
+//            thousands, NaNs).
 // What the scores look like costs time, never exactness.
 #pragma once
 
@@ -144,7 +145,7 @@ __device__ __forceinline__ int seg_bin(const uint32_t* bins, uint32_t room) {
 
 // Lists the segment of `tokens` tokens whose score 4 lane + k is x[k]: at most as many of them as it has places, 8 or more.  The cut is the lowest edge of a bin (256 over the
 // spread of the scores) that no more scores reach; where the bins are so coarse that a quarter of the places is
-// left, because one score lies far from all others, the bin below the cut is cut into 256 again.  SHARED: read in this launch.
+// left, because one score lies far from all others, the scores of the bin below the cut are cut into 256 again, from their least to their largest.  SHARED: read in this launch.
 template <bool SHARED>
 __device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int seg, const ListRow& l, SegLds& sm) {
   const int lane = lane_id(), room = l.pitch;
@@ -172,7 +173,7 @@ __device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int se
       n += __popcll(m[k]);
     }
   };
-  float cut = -INFINITY;
+  float cut = -INFINITY, higher = -INFINITY;
   bool fits = true;
   if (tokens > room) {
     for (int zoom = 0;; ++zoom) {
@@ -195,14 +196,24 @@ __device__ __forceinline__ void seg_list(const float (&x)[4], int tokens, int se
       }
       fits = n <= room && cut == cut;      // (no cut: no score is finite)
       if (!fits && zoom > 0) {     // (ties: the cut that they lie below)
-        cut = hi;
+        cut = higher;
         reach(cut);
         fits = true;
         break;
       }
-      if (!fits || 4 * n >= 3 * room || zoom == 2 || !(spread < INFINITY)) break;
-      hi = cut;
-      lo = cut - step;
+      if (__builtin_expect(!fits || 4 * n >= 3 * room || zoom == 2 || !(spread < INFINITY), true)) break;
+      higher = cut;
+      hi = -INFINITY;
+      lo = INFINITY;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool below = in[k] && x[k] < cut && x[k] >= cut - step;
+        hi = below ? fmaxf(hi, x[k]) : hi;
+        lo = below ? fminf(lo, x[k]) : lo;
+      }
+      hi = wave_max(hi);
+      lo = -wave_max(-lo);
+      if (!(hi > lo)) break;       // (ties)
     }
   } else {
     reach(cut);
@@ -265,13 +276,22 @@ __device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bse
       if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
     }
   } else {                     // a tie of more than kSelCand tokens: the first `need` of them
+    const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
     int tied = 0;              // met so far
-    for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
-      const int n = i0 + t;
-      const bool tie = n < N && score_key(ld_agent(srow + min(n, N - 1))) == klo;
-      uint32_t tot;
-      const uint32_t before = block_prefix_sum<NT>(tie ? 1u : 0u, sm.wtot, tot);
-      if (tie && tied + (int)before < need) place(n_above + tied + (int)before, (uint32_t)n);
+    for (int i0 = 0; i0 < N && tied < need; i0 += 4 * NT) {
+      const int n = i0 + 4 * t;                               // (S is n_cap long, a multiple of 64)
+      const uint4 x = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
+      const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
+      uint32_t mine = 0, tot;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) mine |= n + k < N && score_key(__uint_as_float(xs[k])) == klo ? 1u << k : 0u;
+      int p = tied + (int)block_prefix_sum<NT>((uint32_t)__popc(mine), sm.wtot, tot);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool tie = (mine >> k) & 1u;
+        if (tie && p < need) place(n_above + p, (uint32_t)(n + k));
+        p += tie ? 1 : 0;
+      }
       tied += (int)tot;
     }
   }
@@ -448,75 +468,72 @@ struct ListSet {
   int n_above, need, n_cand;
   uint32_t from;           // the key from which on the row's scores were looked at
   uint32_t how;            // kList..., counts of the list << 8, waits for scores read again << 16
+  uint32_t ktop;           // the key of the row's largest finite score
 };
 constexpr uint32_t kListAlone = 1, kListReread = 2, kListRow = 3;   // out of the list; with scores read again; out of all of the row's scores
 
-// Scores of segments that are not listed completely from klo on, from there to where their lists begin: f(in, key, token) for all lanes
-// of a wave, which takes 256 / waves tokens of every such segment, so that waves share what lies together; 16 segments at a time,
-// in two loads.  All threads call; there is a barrier ahead of the first f.
-template <bool SHARED, typename Lds, typename F>
-__device__ __forceinline__ void for_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo, uint32_t& how, F&& f) {
-  constexpr int NT = Lds::kThreads, LPS = kWave / Lds::kWaves, SPL = kWave / LPS;   // lanes per segment, segments per load
-  const int t = threadIdx.x, lane = t & 63, off = (t >> 6) * (4 * LPS) + 4 * (lane % LPS);
-  for (int c0 = 0; c0 < nsegs; c0 += NT) {
-    const uint2* p = l.lims + min(c0 + t, nsegs - 1);
-    const uint32_t mine = (SHARED ? ld_agent(p) : *p).x;
-    __syncthreads();                                          // all have read the last ones
-    sm.lim[t] = c0 + t < nsegs ? mine : 0u;
+// Scores of the segments that are not listed completely from a key on.  A wave takes 256 / waves tokens of every such segment, so that waves share what
+// lies together, with kLoads 16-byte loads in flight (four: 32 segments; eight cost registers that two workgroups don't have).  All threads call.
+template <typename Lds>
+struct Beyond {
+  static constexpr int NT = Lds::kThreads, LPS = kWave / Lds::kWaves, SPL = kWave / LPS;   // lanes per segment, segments per load
+  static constexpr int LOADS = Lds::kLoads, MOST = LOADS * SPL;
+  float4 x[LOADS];
+  uint32_t end[LOADS];     // where the list of their segment begins
+  int at[LOADS];           // the first one's token
+  int n = 0;               // segments
+
+  // Those among c0 .. c0 + NT - 1, in order, to sm.lim.  lim: where the list of segment c0 + t begins (0: none).
+  __device__ __forceinline__ void find(Lds& sm, uint32_t lim, int c0, uint32_t klo) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const unsigned long long m = __ballot(lim > klo);
+    if (lane == 0) sm.wtot[wave] = (uint32_t)__popcll(m);
+    __syncthreads();                                          // (all have read the last ones, too)
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < Lds::kWaves; ++w) {
+      const uint32_t c = sm.wtot[w];
+      before += w < wave ? c : 0u;
+      all += c;
+    }
+    if (lim > klo)
+      sm.lim[__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, before))] =
+          make_uint2(lim, (uint32_t)(c0 + t));
+    n = __builtin_amdgcn_readfirstlane((int)all);
     __syncthreads();
-    for (int s0 = 0; s0 < min(nsegs - c0, NT); s0 += kWave) {
-      const uint32_t lim = sm.lim[s0 + lane];
-      unsigned long long m = __ballot(lim > klo);
-      while (m != 0ull) {
-        how += 1u << 16;
-        float4 x[2];
-        int at[2];
-        uint32_t end[2];
+  }
+  __device__ __forceinline__ void load(const Lds& sm, const float* srow, int N, int m0) {
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    uint2 e[LOADS];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          at[j] = N;
-          end[j] = 0;
+    for (int j = 0; j < LOADS; ++j) e[j] = sm.lim[min(m0 + j * SPL + lane / LPS, n - 1)];
 #pragma unroll
-          for (int i = 0; i < SPL; ++i) {
-            if (m != 0ull) {
-              const int b = __ffsll((long long)m) - 1;
-              m &= m - 1ull;
-              const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)lim, b);
-              at[j] = lane / LPS == i ? (c0 + s0 + b) * kListSeg + off : at[j];
-              end[j] = lane / LPS == i ? e : end[j];
-            }
-          }
-          x[j] = *reinterpret_cast<const float4*>(srow + (at[j] < N ? at[j] : 0));   // (S is n_cap long, a multiple of 64)
-        }
+    for (int j = 0; j < LOADS; ++j) {
+      const bool in = m0 + j * SPL + lane / LPS < n;
+      // (another part of every segment: a row that rises has its best at the end of each)
+      const int a = (int)e[j].y * kListSeg + ((wave + (int)e[j].y) & (Lds::kWaves - 1)) * (4 * LPS) + 4 * (lane & (LPS - 1));
+      x[j] = *reinterpret_cast<const float4*>(srow + (a < N ? a : 0));     // (S is n_cap long, a multiple of 64)
+      at[j] = a;
+      end[j] = in ? e[j].x : 0u;
+    }
+  }
+  // f(in, key, token) for all lanes, four times a load, from klo (> 0) on
+  template <typename F>
+  __device__ __forceinline__ void each(int N, int m0, uint32_t klo, F&& f) const {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const float xs[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
+    for (int j = 0; j < LOADS; ++j) {
+      if (m0 + j * SPL >= n) break;
+      const float xs[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
+      const uint32_t span = end[j] > klo ? end[j] - klo : 0u;
+      const int tokens = N - at[j];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const uint32_t key = score_key(xs[k]);
-            f(at[j] + k < N && key >= klo && key < end[j], key, (uint32_t)(at[j] + k));
-          }
-        }
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t key = score_key(xs[k]);
+        f(k < tokens && key - klo < span, key, (uint32_t)(at[j] + k));
       }
     }
   }
-}
-// The same to the wave's own part of sm.extra.  Returns their number; sm.thr[3] becomes 1 if there was no room.  The caller has a barrier
-// behind it.
-template <bool SHARED, typename Lds>
-__device__ __forceinline__ uint32_t gather_beyond(Lds& sm, const ListRow& l, int nsegs, const float* srow, int N, uint32_t klo,
-                                                  uint32_t& how) {
-  uint2* out = sm.extra + (threadIdx.x >> 6) * Lds::kExtraPerWave;
-  uint32_t have = 0;
-  for_beyond<SHARED>(sm, l, nsegs, srow, N, klo, how, [&](bool in, uint32_t key, uint32_t tok) {
-    const unsigned long long b = __ballot(in);
-    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, have));
-    if (in && pos < (uint32_t)Lds::kExtraPerWave) out[pos] = make_uint2(key, tok);
-    have += (uint32_t)__popcll(b);
-  });
-  if (lane_id() == 0 && have > (uint32_t)Lds::kExtraPerWave) sm.thr[3] = 1;
-  return min(have, (uint32_t)Lds::kExtraPerWave);
-}
+};
 
 // What a thread holds of a row's list, requested before anything about the row but its place is known: quads t, t + NT, ... of its
 // places, whatever segments they belong to.  n_max: tokens of the longest row.
@@ -573,7 +590,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
 #pragma unroll
   for (int j = 0; j < Q; ++j) asm volatile("" : "+v"(tok4[j]));
   __syncthreads();
-  FASA_T_DECL(5);
+  FASA_T_DECL(10);
   FASA_T(0);
   uint32_t klo = 1, ktop = 0;
 #pragma unroll
@@ -596,7 +613,15 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
   };
   uint32_t khi = 0;
   int shift = 0, need = 0, n_cand = 0;
-  auto count = [&]() {
+  auto clear = [&]() {
+    __syncthreads();                                          // all have read it
+    for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
+    __syncthreads();
+  };
+  auto whole_range = [&](uint32_t lo) { klo = lo; khi = 0xffffffffu; shift = list_shift(lo, ktop); need = bsel; };
+  // one range: true if it holds `need` entries
+  auto search = [&]() {
+    how += 1u << 8;
     const uint32_t span = khi - klo;                          // (an empty entry's 0 - klo is larger)
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
@@ -607,75 +632,160 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
       if (valid && k - klo <= span) atomicAdd(&sm.hist[min((k - klo) >> shift, (uint32_t)kListBins - 1u)], 1u);
     });
     __syncthreads();
-  };
-  auto clear = [&]() {
-    __syncthreads();                                          // all have read it
-    for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
-    __syncthreads();
-  };
-  // one range: true if it holds `need` entries
-  auto search = [&]() {
-    how += 1u << 8;
-    count();
     const BinAt b = wave_find_bin(sm.hist, (uint32_t)need);
     n_cand = b.n;
     if (b.n == 0) return false;
     need -= b.above;
     narrow_range<kListBins>(klo, khi, (uint32_t)b.bin, shift);
-    shift = max(0, 23 - __clz((int)(khi - klo)));             // (khi - klo) >> shift < kListBins
     return true;
   };
-  // the range of the threshold among what is counted: all of it has at most kSelCand entries, or one key
-  auto narrow = [&](uint32_t lo) {
-    klo = lo; khi = 0xffffffffu; shift = list_shift(lo, ktop); need = bsel;
-    for (;;) {
-      if (!search()) return false;
-      if (n_cand <= kSelCand || klo == khi) return true;
-      clear();
+  // the range of the keys that there are in it, and the histogram cleared
+  auto tighten = [&]() {
+    const uint32_t lo = klo, span = khi - klo;
+    uint32_t above = 0, below = 0;                            // of the lowest, of the highest; 0: none
+    auto look = [&](uint32_t k) {
+      const bool in = k - lo <= span;
+      above = max(above, in ? k : 0u);
+      below = max(below, in ? ~k : 0u);
+    };
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) look(key[k]);
+    if (over) more([&](bool valid, uint32_t k, uint32_t) { look(valid ? k : 0u); });
+    above = wave_max_key(above);
+    below = wave_max_key(below);
+    if (lane == kWave - 1) { sm.wtot[wave] = above; sm.wtot2[wave] = below; }
+    __syncthreads();                                          // (all have read the histogram, too)
+    for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
+    above = below = 0;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) { above = max(above, sm.wtot[w]); below = max(below, sm.wtot2[w]); }
+    klo = ~below;
+    khi = above;
+    shift = max(0, 23 - __clz((int)(khi - klo)));             // (khi - klo) >> shift < kListBins
+    __syncthreads();
+  };
+  // until it has at most kSelCand entries, or one key (ties); always true: the same entries are searched
+  auto narrow = [&]() {
+    while (n_cand > kSelCand && klo != khi) {
+      tighten();
+      if (klo == khi || !search()) break;
     }
   };
-  if (__builtin_expect(!narrow(klo), false)) {
-    // Segments with more of the best than they had room for.  From a key that the B-th best of the listed entries reaches:
-    auto none = [&]() { return ListSet{false, 0u, 0, 0, 0, from, how | kListRow}; };
-    clear();
-    {
-      // no listed entry lies below the lowest of the completeness keys, but for those of a short last segment that is listed whole
-      const uint32_t a = wave_max_key(t >= nsegs || lt.x <= kListAll || nsegs > NT ? 0u : ~lt.x);
-      if (lane == kWave - 1) sm.wtot[wave] = a;
-      __syncthreads();
-      uint32_t b = 0;
-#pragma unroll
-      for (int w = 0; w < NWV; ++w) b = max(b, sm.wtot[w]);
-      bool enough = b != 0u && narrow(~b);
-      if (!enough) {
-        clear();
-        enough = narrow(1u);
+  whole_range(klo);
+  if (__builtin_expect(!search(), false)) {
+    // Segments with more of the best than they had places for.  Lanes count in eight histograms here, one bin's side by side: neighbours that
+    // are alike would all wait for one word.  us per step, a key by two to four counts of the list and two or three passes over the segments / like
+    // this, 8 rows of 32768, B = 2048: independent scores 14.0 / 13.9, an autoregression of 0.98 22.5 / 20.1, of 0.998 33.4 / 20.6, rising
+    // 34.3 / 19.3; 32 of 32905, 6219: 33.1 / 32.2, 45.5 / 41.1, 62.3 / 42.2, 76.0 / 41.7; 8 of 131072, 1024: 17.7 / 17.7, 34.4 / 25.8, 54.8 /
+    // 26.5, 46.2 / 23.6.  Of what rising rows take longer, the failed count is 1.5, the key 1.5, the scores 1.9, counting 1.9, keeping 1.4.
+    uint32_t* const wide = reinterpret_cast<uint32_t*>(sm.extra);
+    static_assert(sizeof(sm.extra) >= kListBins * 32 && NT >= kListBins, "eight histograms, a bin of each by a thread");
+    auto none = [&](uint32_t reached) { clear(); return ListSet{false, reached, 0, 0, 0, from, how | kListRow, ktop}; };
+    auto clear_wide = [&]() {                                 // (all have read it: a barrier ago)
+      if (t < kListBins) {
+        reinterpret_cast<uint4*>(wide)[2 * t] = make_uint4(0, 0, 0, 0);
+        reinterpret_cast<uint4*>(wide)[2 * t + 1] = make_uint4(0, 0, 0, 0);
       }
-      clear();
-      if (!enough) return none();                                // fewer than B are listed
-    }
-    have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo, how);
-    __syncthreads();
-    if (sm.thr[3] != 0) {
-      // ... which so many of these segments' scores reach that they don't fit: they are counted, and those gathered that reach the
-      // bin of the threshold
-      const uint32_t lo = klo;
-      shift = list_shift(lo, ktop); need = bsel; khi = 0xffffffffu;
-      for_beyond<SHARED>(sm, l, nsegs, srow, N, lo, how, [&](bool in, uint32_t key, uint32_t) {
-        if (in) atomicAdd(&sm.hist[min((key - lo) >> shift, (uint32_t)kListBins - 1u)], 1u);
-      });
-      if (!search()) { clear(); return none(); }
-      if (t == 0) sm.thr[3] = 0;
-      clear();
-      have = gather_beyond<SHARED>(sm, l, nsegs, srow, N, klo, how);
       __syncthreads();
-      if (sm.thr[3] != 0) return none();                         // (ties)
+    };
+    auto add = [&](uint32_t k, uint32_t n) { atomicAdd(&wide[min((k - klo) >> shift, (uint32_t)kListBins - 1u) * 8u + (uint32_t)(lane & 7)], n); };
+    auto search_wide = [&]() {
+      how += 1u << 8;
+      const uint32_t lo = klo;
+#pragma unroll
+      for (int k = 0; k < EPT; ++k)
+        if (key[k] >= lo) add(key[k], 1u);
+      __syncthreads();
+      if (t < kListBins) {
+        const uint4 a = reinterpret_cast<const uint4*>(wide)[2 * t], b = reinterpret_cast<const uint4*>(wide)[2 * t + 1];
+        sm.hist[t] = a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w;
+      }
+      __syncthreads();
+      const BinAt b = wave_find_bin(sm.hist, (uint32_t)need);
+      n_cand = b.n;
+      if (b.n == 0) return false;
+      need -= b.above;
+      narrow_range<kListBins>(klo, khi, (uint32_t)b.bin, shift);
+      return true;
+    };
+    // no listed entry lies below the lowest of the completeness keys, but for those of a short last segment that is listed whole
+    uint32_t lowest = wave_max_key(t >= nsegs || lt.x <= kListAll || nsegs > NT ? 0u : ~lt.x);
+    if (lane == kWave - 1) sm.wtot[wave] = lowest;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) lowest = max(lowest, sm.wtot[w]);
+    lowest = lowest != 0u ? ~lowest : 1u;
+    FASA_T(5);
+    Beyond<Lds> beyond;
+    auto for_beyond = [&](bool held, auto&& f) {
+      for (int c0 = 0; c0 < nsegs; c0 += NT) {
+        if (!held) {
+          uint32_t lim = lt.x;
+          if (nsegs > NT) {
+            const uint2* p = l.lims + min(c0 + t, nsegs - 1);
+            lim = c0 + t < nsegs ? (SHARED ? ld_agent(p) : *p).x : 0u;
+          }
+          beyond.find(sm, lim, c0, klo);
+        }
+        for (int m0 = 0; m0 < beyond.n; m0 += Beyond<Lds>::MOST) {
+          if (!held) {
+            beyond.load(sm, srow, N, m0);
+            how += 1u << 16;
+          }
+          beyond.each(N, m0, klo, f);
+        }
+      }
+    };
+    // A key that B scores reach, and not many more: first as if a segment's scores went on below its list as they do in it, half as dense, and
+    // in the best scores' four binades, where bins are fine; should fewer than B reach that, by the listed ones alone.  The scores of the segments that are
+    // not listed completely from there on are read and counted with the listed ones.
+    const float top = key_score(ktop);
+    for (int attempt = nsegs <= NT && top > 0.f ? 0 : 1;; ++attempt) {
+      const bool guess = attempt == 0;
+      whole_range(guess ? max(lowest, score_key(top * 0.0625f)) : attempt < 2 ? lowest : 1u);
+      if (guess) need += bsel / 16;
+      clear_wide();
+      if (guess && lt.x > klo && lt.y > lt.x) {
+        const float lim = key_score(lt.x), w = 0.25f * (float)(kListSeg - l.pitch);
+        const float step = (key_score(lt.y) - lim) * w * __builtin_amdgcn_rcpf((float)l.pitch);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t k = score_key(fmaf(-step, (float)j + 0.5f, lim));
+          if (k > klo && k < lt.x) add(k, (uint32_t)(0.5f * w));
+        }
+      }
+      if (!search_wide()) {
+        if (attempt == 2) return none(0u);                    // fewer than B are listed
+        continue;
+      }
+      FASA_T(6);
+      from = klo;
+      whole_range(klo);
+      clear_wide();
+      for_beyond(false, [&](bool in, uint32_t key, uint32_t) { if (in) add(key, 1u); });
+      FASA_T(7);
+      if (search_wide()) break;
+      if (attempt == 2) return none(0u);
     }
+    FASA_T(8);
+    // What reaches the threshold's bin is kept (all would not fit: where scores rise through the row, 16 B)
+    uint2* out = sm.extra + wave * Lds::kExtraPerWave;
+    for_beyond(Lds::kLoads > 1 /* one load is not worth its registers */ && nsegs <= NT && beyond.n <= Beyond<Lds>::MOST, [&](bool in, uint32_t key, uint32_t tok) {
+      const unsigned long long b = __ballot(in);
+      const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, have));
+      if (in && pos < (uint32_t)Lds::kExtraPerWave) out[pos] = make_uint2(key, tok);
+      have += (uint32_t)__popcll(b);
+    });
+    if (lane == 0 && have > (uint32_t)Lds::kExtraPerWave) sm.thr[3] = 1;
+    __syncthreads();
+    if (sm.thr[3] != 0) return none(klo);                      // (ties)
     over = true;
     how += kListReread - kListAlone;
-    from = klo;
-    if (!narrow(klo)) { clear(); return none(); }                // (NaNs only)
+    FASA_T(9);
+    FASA_T_PRINT(t == 0 && blockIdx.x == 0, "beyond: first %llu listed key %llu read(%d) %llu search %llu keep(%d) %llu (x10ns)\n", FASA_T_D(5, 0), FASA_T_D(6, 5),
+                 beyond.n, FASA_T_D(7, 6), FASA_T_D(8, 7), (int)have, FASA_T_D(9, 8));
   }
+  narrow();
   FASA_T(1);
   const int n_above = bsel - need;
   const uint32_t span = khi - klo;
@@ -739,7 +849,7 @@ __device__ __forceinline__ ListSet select_listed(Lds& sm, const ListRow& l, List
   FASA_T(2);
   FASA_T_PRINT(t == 0 && blockIdx.x == 0, "listed: threshold %llu places %llu (x10ns), %d entries, %d of %d candidates\n", FASA_T_D(1, 0),
                FASA_T_D(2, 1), 4 * nq, need, n_cand);
-  return {true, klo, n_above, need, n_cand, from, how};
+  return {true, klo, n_above, need, n_cand, from, how, ktop};
 }
 
 }  // namespace fasa

@@ -61,6 +61,7 @@ struct RowLds {
   static constexpr int kThreads = NT;
   static constexpr int kWaves = NT / kWave;
   static constexpr int kList = LIST;
+  static constexpr int kLoads = 4;                           // of segments that are read again
   static constexpr int kExtraPerWave = LIST == 1 ? 896 : 1;  // (two workgroups still share a compute unit's LDS)
   union {
     float o[kWaves][GM][kHeadDim];                           // weighted V per wave
@@ -80,7 +81,7 @@ struct RowLds {
   float scs[kWaves][16];
   uint32_t wtot[kWaves], wtot2[kWaves];
   uint32_t thr[4];
-  uint32_t lim[NT];                                          // where lists of segments begin (list_kernel)
+  uint2 lim[LIST == 1 ? NT : 1];                             // where lists of segments begin, and which (list_kernel)
   uint32_t n_list, n_cnd;
   int p_new;                                                 // place of the appended row in wl, or -1
   __device__ __forceinline__ void put(int place, uint32_t tok) { wl[place] = tok; }
@@ -703,7 +704,7 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* l
   tile.load_q((const ET*)a.q + (size_t)row * G * D, lane & 15, lane >> 4);
   int ready = set.n_above - p0;
   if (!set.usable) {
-    row_select<false>(sm, bsel, srow, N, p0, p1);
+    row_select<false>(sm, bsel, srow, N, p0, p1, set.klo, set.ktop);
     ready = p1 - p0;
   } else if (set.n_cand > kSelCand && ready < p1 - p0) {       // ties that no list of candidates holds
     resolve_threshold(sm, set.klo, bsel, set.need, set.n_cand, srow, N, p0, p1);

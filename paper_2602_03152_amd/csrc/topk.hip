@@ -200,14 +200,14 @@ __global__ __launch_bounds__(256) void select_all_kernel(int32_t* __restrict__ T
 constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT, kTopkSample = 256;
 
 struct TopkLds {
-  static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave, kExtraPerWave = 256;
+  static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave, kExtraPerWave = 256, kLoads = 1;
   __align__(16) float sample[kTopkSample];
   __align__(16) uint32_t bins[256];
   uint32_t hist[kSelBins];
   uint2 cand[kSelCand];
   uint2 extra[kWaves * kExtraPerWave];                       // entries of lists that no thread holds
   SegLds seg[kWaves];
-  uint32_t lim[kThreads];
+  uint2 lim[kThreads];
   uint32_t wtot[kWaves], wtot2[kWaves], wcnt[kWaves];
   uint32_t thr[4];
   uint32_t ticket, n_cnd;
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
   held.request(l, N, places);
   const ListSet set = select_listed<true, Q>(sm, l, held, bsel, srow, N, 0, bsel);
   if (set.usable) resolve_threshold(sm, set.klo, bsel, set.need, set.n_cand, srow, N, 0, bsel);
-  else row_select<false>(sm, bsel, srow, N, 0, bsel);
+  else row_select<false>(sm, bsel, srow, N, 0, bsel, set.klo, set.ktop);
 }
 
 // us, histogram and selection launch / like this: 8 rows of 8192, B = 500: 11.3 / 6.8, 16 of 20011, 1250: 12.4 / 8.2, 8 of 32768,

@@ -32,6 +32,8 @@ def make_scores(kind, rows, n, budget):
             x[:, i] += rho * x[:, i - 1]
     elif kind == "rising":
         x = 0.01 * x + np.linspace(-3, 3, n, dtype=np.float32)
+    elif kind == "recent":                           # a window of the last tokens
+        x[:, n - min(1000, n // 8):] += 8.0
     elif kind == "together":                         # as many as fit, then some, in one place of every row
         for r in range(rows):
             at = rng.integers(0, n - min(n, 2 * budget) + 1)
@@ -133,6 +135,25 @@ def test_few_lists_are_short(fb, rows, n_ctx, budget, rho):
         waits.max()), flush=True)
     assert (reach >= budget).all()
     assert (way == ALONE).all() if rho == 0.0 else (way != ROW).all()
+
+
+@pytest.mark.parametrize("kind", ["ar0.98", "ar0.998", "rising", "recent"])
+@pytest.mark.parametrize("rows,n_ctx,budget", [(8, 32768, 2048), (16, 32905, 6219), (16, 16384, 256), (8, 131072, 1024)])
+def test_scores_are_read_again_once(fb, kind, rows, n_ctx, budget):
+    """Where segments have more of the best than places, the list is counted three times - from the key that all lists are complete
+    from, from the lowest such, and with the scores read again from a key on that B of them should reach - and few segments are read: 32 a
+    wait, and those of more than one wait twice."""
+    print("read again", kind, rows, n_ctx, budget, flush=True)
+    run, S, T, out, V, ws = step_of(fb, make_scores(kind, rows, n_ctx, budget), budget)
+    run()
+    torch.cuda.synchronize()
+    key, way, counts, waits = how_selected(ws, rows)
+    print("ways %s, counts %s, waits %s" % (np.bincount(way, minlength=4)[1:], counts, waits), flush=True)
+    got = np.sort(T[:2].cpu().numpy(), -1)
+    np.testing.assert_array_equal(got, O.topk(S[:2, :, :n_ctx].cpu().numpy(), budget, n_ctx))
+    assert (way == REREAD).all()
+    assert counts.max() <= 4                         # (one more where the threshold's bin is wide)
+    assert waits.max() <= 4
 
 
 @pytest.mark.parametrize("equal", [False, True])
