@@ -10,6 +10,7 @@
 
 #include "fasa.h"
 #include "fasa_internal.h"
+#include "row_list.h"
 #include "select_common.h"
 
 #define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED line %d: %s\n", __LINE__, #cond); return 1; } } while (0)
@@ -45,11 +46,11 @@ int main() {
             ++checked;
           }
   // ---- the step's forms: every plan is one the kernels are built for ----
-  int forms[3] = {0, 0, 0}, lists = 0;
+  int forms[3] = {0, 0, 0}, lists = 0, topks = 0;
   for (int dtype : {FASA_BF16, FASA_F32})
     for (int rows : {1, 3, 8, 64, 65, 72, 128, 256, 257, 512, 4096})
       for (int g : {1, 2, 3, 4, 5, 8})
-        for (int n : {1, 1024, 1025, 2048, 2049, 4097, 5119, 5120, 8192, 8193, 16385, 32768, 32769, 65536, 140000, 1 << 20, (1 << 20) + 64})
+        for (int n : {1, 257, 1024, 1025, 2048, 2049, 4097, 5119, 5120, 8192, 8193, 16385, 32768, 32769, 65536, 140000, 1 << 20, (1 << 20) + 64})
           for (int budget : {1, 63, 64, 320, 321, 512, 513, 1024, 1025, 6000}) {
             const int cap = (n + 63) / 64 * 64, bsel = budget < n ? budget : n, per = dtype == FASA_BF16 ? 2048 : 1024;
             const fasa_shape s = shape(rows, g, 1, 16, n, cap, budget, dtype);
@@ -65,13 +66,25 @@ int main() {
               EXPECT(dtype == FASA_BF16 && nsegs <= 2048);
               EXPECT((q == 1 || q == 2 || q == 3 || q == 4 || q == 6 || q == 8) && l.nwgs >= 1 &&
                      l.nwgs <= 64 && share <= 2048 && (long long)share * l.nwgs >= bsel && share * (l.nwgs - 1) < bsel);
+              // 512 threads hold four places a quad; keys and token bytes lie in 8 bytes per token of capacity
+              const int room = fasa::list_room(bsel, n), one = fasa::list_places(n, bsel, q, false), own = fasa::list_places(n, bsel, q, true);
+              EXPECT(room >= 8 && room <= 256 && room % 4 == 0 && one == nsegs * room);
+              for (int places : {one, own})
+                EXPECT(places % 4 == 0 && places >= one && places <= q * 512 * 4 && places <= nsegs * 256 && 5ll * places <= 8ll * cap);
               ++lists;
+            }
+            const fasa::TopkPlan k = fasa::plan_topk(n, bsel);
+            if (k.quads) {
+              const int nsegs = (n + 255) / 256, places = nsegs * fasa::list_room(bsel, n);
+              EXPECT(bsel < n && nsegs <= 2048 && k.quads <= 4 && places <= k.quads * 512 * 4);
+              if (n > 2048) EXPECT(5ll * places <= 8ll * cap);
+              ++topks;
             }
             const fasa::FusePlan p = fasa::plan_fused(s, true);
             if (p.tpb) EXPECT(p.slice_len <= p.tpb && p.nslices <= 256 && (long long)p.nslices * p.slice_len >= n &&
                               (long long)(p.nslices - 1) * p.slice_len < n);
           }
-  EXPECT(lists > 0 && forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
+  EXPECT(lists > 0 && topks > 0 && forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
   // ---- eight waves per compute unit: the splits cover the tokens, the workspace holds them, and they fill their rounds ----
   for (int rows = 1; rows <= 600; ++rows)
     for (int count : {1, 17, 700, 1500, 3000, 4096, 8192, 30001, 131072}) {
@@ -96,6 +109,44 @@ int main() {
           if (shift < 0) shift = 0;
         }
       }
+  // the same among 512 bins, the first of them up to the largest finite score's key (selection out of lists); after a bin the search
+  // may go on with the range of the keys in it
+  for (uint32_t key : {1u, 0x007fffffu, 0x3d3dffffu, 0x7fffffffu, 0x80000000u, 0xbf800000u, 0xc0400001u, 0xff7fffffu, 0xff800000u, 0xffffffffu})
+    for (uint32_t from : {1u, 0x007fffffu, 0x3d3dffffu, 0x7fffffffu, 0x80000001u, 0xbe4ccccdu, 0xc0000000u, 0xff800000u})
+      for (uint32_t top : {0u, 0x3fbfffffu, 0x80000001u, 0xbf800000u, 0xc0400000u, 0xff7fffffu}) {
+        if (from > key) continue;
+        uint32_t klo = from, khi = 0xffffffffu;
+        const uint32_t span = top > from ? top - from : 0u;
+        int shift = span ? 23 - __builtin_clz(span) : 0, passes = 0;
+        if (shift < 0) shift = 0;
+        EXPECT((span >> shift) < (uint32_t)fasa::kListBins);
+        while (klo != khi) {
+          const uint32_t d = (key - klo) >> shift, last = fasa::kListBins - 1, bin = d < last ? d : last, lo = klo, hi = khi;
+          fasa::narrow_range<fasa::kListBins>(klo, khi, bin, shift);
+          EXPECT(lo <= klo && klo <= key && key <= khi && khi <= hi && ++passes < 8);
+          shift = klo == khi ? 0 : 23 - __builtin_clz(khi - klo);
+          if (shift < 0) shift = 0;
+        }
+      }
+  // ---- places of a segment: the kernels' quotient, whose reciprocal is off by an ulp at most, is the whole one below 256 ----
+  for (int segs = 1; segs <= 2048; ++segs)
+    for (int places = 4; places <= 16384 && places < 256 * segs; places += places < 64 || places > 16320 ? 4 : 92)
+      for (float off : {-1.2e-7f, 0.f, 1.2e-7f}) {
+        const float r = 1.0f / (float)segs, q = ((float)places + 0.5f) * (r + r * off);
+        EXPECT((int)q == places / segs);
+      }
+  // ---- quotients by multiplication: exact up to the bound that the factor was made for, and no factor where they would not be ----
+  for (long long d : {1ll, 2ll, 3ll, 5ll, 7ll, 8ll, 31ll, 64ll, 129ll, 256ll, 1000ll, 1023ll, 2048ll, 4097ll, 8191ll, 8192ll, 46340ll, 65535ll})
+    for (long long most : {d, 2 * d + 1, 1000 * d, (1ll << 31) / d - 1, (1ll << 31) / d, (1ll << 31) / d + 1, (1ll << 31) - 1}) {
+      const uint32_t m = fasa::div_magic((int)d, most);
+      EXPECT((m != 0) == (most * d < (1ll << 31)));
+      if (!m) continue;                                        // (fast_div divides)
+      for (long long k : {0ll, 1ll, 2ll, 3ll, most / d / 3, most / d / 2, most / d - 1, most / d})
+        for (long long n : {k * d - 1, k * d, k * d + 1, k * d + d - 1, most - 1, most}) {
+          if (n < 0 || n > most) continue;
+          EXPECT((long long)(((unsigned long long)((uint32_t)n << 1) * m) >> 32) == n / d);
+        }
+    }
   // ---- bad shapes ----
   {
     fasa_shape s = shape(1, 32, 8, 16, 1000, 1024, 100);
