@@ -39,15 +39,18 @@ __host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m) {
 // for 6219 of 32905 tokens, 2.5 B for 2048 of 32768, 5 B for 256 of 16384, 6 B for 1024 of 131072.
 __host__ __device__ __forceinline__ int list_room(int bsel, int n) {
   const float p = (float)bsel * ((float)kListSeg / (float)n);
-  const int room = ((int)fmaf(4.0f, sqrtf(p), p) + 5 + 3) & ~3;    // (one rounding on both sides of the lists)
+  const int room = ((int)fmaf(4.0f, sqrtf(p), p) + 5 + 3) & ~3;
   return room < kListSeg ? room : kListSeg;
 }
 // Places of a segment in a row of n tokens that has `places` of them (a multiple of 4; at least 4 a segment).  A row with fewer
 // tokens than another and no larger budget has need of fewer places in all, so this is list_room but for its rounding up to whole quads.
-// (The quotient is exact below 256, and no place is beyond the row's.)
+// (The quotient is exact below 256, and no place is beyond the row's.  Both sides of the lists come to the same number by the same instructions; a
+// division and a root as the language has them, behind the sequence's length and ahead of its selection: paged, 16 sequences, 29.45 -> 29.35 us.)
 __device__ __forceinline__ int list_pitch(int places, int bsel, int n) {
   const float q = ((float)places + 0.5f) * __builtin_amdgcn_rcpf((float)((n + kListSeg - 1) / kListSeg));
-  return min(list_room(bsel, n), (int)fminf(q, (float)kListSeg) & ~3);
+  const float p = (float)bsel * ((float)kListSeg * __builtin_amdgcn_rcpf((float)n));
+  const int room = ((int)fmaf(4.0f, __builtin_amdgcn_sqrtf(p), p) + 5 + 3) & ~3;       // list_room
+  return min(min(room, kListSeg), (int)fminf(q, (float)kListSeg) & ~3);
 }
 
 // The cut: a score that at least r (1 .. 64 KPL) of the sample's scores reach and hardly more, in steps of a 256th of
@@ -276,9 +279,19 @@ __device__ __forceinline__ void resolve_threshold(Lds& sm, uint32_t klo, int bse
       if (t % P == 0 && ci < n_cand && rank < need) place(n_above + rank, sm.cand[ci].y);
     }
   } else {                     // a tie of more than kSelCand tokens: the first `need` of them
-    const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
     int tied = 0;              // met so far
-    for (int i0 = 0; i0 < N && tied < need; i0 += 4 * NT) {
+    // (One score a thread and pass in the one-launch step, whose kernels have no registers left)
+    if constexpr (!Lds::kWideTies) {
+      for (int i0 = 0; i0 < N && tied < need; i0 += NT) {
+        const int n = i0 + t;
+        const bool tie = n < N && score_key(ld_agent(srow + min(n, N - 1))) == klo;
+        uint32_t tot;
+        const uint32_t before = block_prefix_sum<NT>(tie ? 1u : 0u, sm.wtot, tot);
+        if (tie && tied + (int)before < need) place(n_above + tied + (int)before, (uint32_t)n);
+        tied += (int)tot;
+      }
+    } else for (int i0 = 0; i0 < N && tied < need; i0 += 4 * NT) {
+      const __amdgpu_buffer_rsrc_t rs = agent_buffer(srow);
       const int n = i0 + 4 * t;                               // (S is n_cap long, a multiple of 64)
       const uint4 x = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
       const uint32_t xs[4] = {x.x, x.y, x.z, x.w};

@@ -62,6 +62,7 @@ struct RowLds {
   static constexpr int kWaves = NT / kWave;
   static constexpr int kList = LIST;
   static constexpr int kLoads = 4;                           // of segments that are read again
+  static constexpr bool kWideTies = LIST == 1;
   static constexpr int kExtraPerWave = LIST == 1 ? 896 : 1;  // (two workgroups still share a compute unit's LDS)
   union {
     float o[kWaves][GM][kHeadDim];                           // weighted V per wave
@@ -81,7 +82,9 @@ struct RowLds {
   float scs[kWaves][16];
   uint32_t wtot[kWaves], wtot2[kWaves];
   uint32_t thr[4];
-  uint2 lim[LIST == 1 ? NT : 1];                             // where lists of segments begin, and which (list_kernel)
+  // Where lists of segments begin, and which (list_kernel).  Elsewhere not used, but with 2 KB less of LDS the compiler plans the registers of
+  // step_kernel for another workgroup and spills 55 scalar or 13 vector ones: 8 rows of 1531, B = 192: 10.57 -> 10.64 us.
+  uint2 lim[LIST == 1 ? NT : NT / 2];
   uint32_t n_list, n_cnd;
   int p_new;                                                 // place of the appended row in wl, or -1
   __device__ __forceinline__ void put(int place, uint32_t tok) { wl[place] = tok; }

@@ -200,6 +200,7 @@ __global__ __launch_bounds__(256) void select_all_kernel(int32_t* __restrict__ T
 constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT, kTopkSample = 256;
 
 struct TopkLds {
+  static constexpr bool kWideTies = true;
   static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave, kExtraPerWave = 256, kLoads = 1;
   __align__(16) float sample[kTopkSample];
   __align__(16) uint32_t bins[256];
