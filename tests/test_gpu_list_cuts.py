@@ -181,16 +181,16 @@ def test_short_sequences_of_one_budget(fb, lens, n_ctx, budget, equal):
     assert (way == ALONE).all(), dict(zip(lens, way))
 
 
-# Where NaN scores rank is unspecified, but a set has B tokens and every call ends: a list is short here (the finite scores are the
-# sample's), and the search for the threshold starts at a key below zero, from which bins are wide.  (csrc/abi_host_check.cpp
-# goes through the ranges.)
+# Where NaN scores rank is unspecified, but a set has B tokens and every call ends: fewer than B finite scores are listed here, in segments
+# of NaNs, and the search for the threshold starts at a key below zero, from which bins are wide.  (csrc/abi_host_check.cpp goes through
+# the ranges.)
 @pytest.mark.parametrize("nan", [0x7fc0, 0xffc0, 0x7fff], ids=hex)
 @pytest.mark.parametrize("n_ctx,budget", [(9001, 200), (16384, 700), (20000, 3000)])
 def test_nan_scores_end(fb, n_ctx, budget, nan):
     rows = 8
     print("lists, NaN", n_ctx, budget, hex(nan), flush=True)
     scores = np.zeros((rows, n_ctx), dtype=np.float32)
-    run, S, T, out, V, ws = step_of(fb, scores, budget, planes=lambda x: _nan_beside_the_sample(x, n_ctx, nan))
+    run, S, T, out, V, ws = step_of(fb, scores, budget, planes=lambda x: _nan_beside_clusters(x, n_ctx, nan))
     for again in range(2):
         T.fill_(-1)
         run()
@@ -202,8 +202,8 @@ def test_nan_scores_end(fb, n_ctx, budget, nan):
             assert (out[r, 0].double() - want).abs().max().item() <= 1e-4
 
 
-def _nan_beside_the_sample(x, n, nan):
-    """Scores of the 16 clusters of 16 tokens that the scoring launch samples: ordinary, one of a row far above; else NaN."""
+def _nan_beside_clusters(x, n, nan):
+    """Scores of 16 clusters of 16 neighbours, evenly spaced: ordinary, one of a row far above; else NaN."""
     rng = np.random.default_rng(n)
     x[:, 0, :n, 0] = nan
     at = np.concatenate([((n * (2 * c + 1) // 32) & ~15) + np.arange(16) for c in range(16)])

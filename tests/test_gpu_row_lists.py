@@ -1,7 +1,7 @@
 """The decode step whose second launch selects out of the lists that the scoring launch makes (bf16): lengths around its
-segments of 1024 tokens, budgets around its workgroups' shares, every number of entries per thread it is built for; winners
-that crowd a few segments (their lists are read on), a sample that misleads (the list comes out short and the whole row is
-read), sequences shorter than the sample needs.  The parity bar is the step's."""
+workgroups' 1024 tokens and their segments of 256, budgets around its workgroups' shares, every number of entries per thread it is built
+for; winners that crowd a few segments (their scores are read again), or a few places of many, and sequences of a token to a few
+segments.  The parity bar is the step's."""
 import numpy as np
 import pytest
 import torch
@@ -63,14 +63,13 @@ def test_winners_in_few_segments(fb, n_ctx, budget, first, last):  # noqa: F811
 
 
 @pytest.mark.parametrize("n_ctx,budget,batch", [(9000, 700, 1), (9000, 200, 1), (20000, 3000, 1), (6000, 700, 33)])
-def test_sample_that_misleads(fb, n_ctx, budget, batch):  # noqa: F811
-    """The tokens of the sample (16 clusters of 16, list_sample_token) score above all others: far fewer than B scores
-    reach the cut."""
+def test_clusters_above_all_others(fb, n_ctx, budget, batch):  # noqa: F811
+    """16 clusters of 16 neighbours, evenly spaced, score above all others: the cut of a segment lies far below its best."""
     w = W.WORKLOADS[1].scaled(n_ctx=n_ctx, budget=budget, batch=batch)
     x = _inputs(w)
     starts = [(n_ctx * (2 * c + 1) // 32) & ~15 for c in range(16)]
     _raise_scores(w, x, np.concatenate([np.arange(s, s + 16) for s in starts]))
-    print("misled", n_ctx, budget, batch, flush=True)
+    print("clusters", n_ctx, budget, batch, flush=True)
     d = run_step(fb, w, x)
     compare_step(w, x["q"], x["K"], x["V"], x["fc_idx"], d, w.n_ctx, w.budget, rows=_rows(w))
 
