@@ -796,12 +796,14 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
   const int per = kStepNT * (s.dtype == FASA_BF16 ? 4 : 2);
   const long long ns = (s.n_ctx + per - 1) / per;
   if (s.dtype == FASA_BF16) {
-    // one slice: 8 rows of 2048, B = 64: 14.5 / 10.2 / 15.0, B = 512: 18.2 / 14.9 / 19.8; 512 rows: 29.4 / 20.5 / 36.3
+    // one slice: 8 rows of 2048, B = 64: 14.5 / 10.2 / 15.0, B = 512: 18.2 / 14.9 / 19.8; 512 rows: 29.4 / 20.5 / 36.3.  Against lists
+    // (list_kernel): 8 rows, B = 64: 9.3 / 11.0, 128 rows, 256: 13.1 / 14.6, 512 rows, 64: 19.5 / 21.6, 512: 33.3 / 38.2; 8 rows, 512: 13.6 / 13.5,
+    // 1000: 18.9 / 14.2 (few rows with more than 500 selected would do better with lists)
     if (ns == 1) return kStepOne;
     // 8 rows of 8192, B = 256: 14.6 / 14.6 / 17.3, B = 512: 16.0 / 17.0 / 19.8; 128 rows of 4096: 22.3 / 20.4 / 21.9
-    // Several slices, where the lists of a scoring launch do not do better (list_kernel): 8 rows of 8192, F = 16 / 32: 13.6 / 14.9
-    // against 14.4 / 16.5, 32 rows: 17.1 / 19.9 against 17.0 / 20.5, 40 rows: 18.6 against 17.5; 8 rows of 6000, B = 40: 12.2
-    // against 12.3, of 3000: 12.2 against 11.8
+    // Several slices, where the lists of a scoring launch do not do better: one launch / lists, B = 256, 8 rows of 8192: 14.4 / 12.5, 32
+    // rows: 17.0 / 12.9, 40 rows: 13.7 / 13.7, 128 of 4000: 16.0 / 16.4; 8 rows of 6000, B = 40: 11.2 / 11.0, 320: 13.7 / 13.3, 256 with F = 32: 14.5 / 13.5, of
+    // 4000, 320: 13.5 / 13.3, of 3000, 40: 11.0 / 11.1
     return ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320 && (rows > 32 || ns < 4) ? kStepOne : kStepNone;
   } else {
     // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
@@ -864,15 +866,18 @@ ListPlan plan_list(const fasa_shape& s, const PageMap& pm, int max_splits) {
   if ((most >> 3) >= 0xfffffff0ll) return p;
   const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx, rows = s.batch * s.n_kv_heads;
   // 32 entries a thread, which is what its registers hold beside the tiles: rows of up to 49000 tokens with 18.9 % of them selected,
-  // 67000 with 12.5 %; with more than a third selected, where a list is hardly shorter than the row, 24: 17400 tokens with half.  us, split form /
-  // lists: 32 rows of 20000, 7 heads, B = 8000: 52.5 / 46.8; 8 rows of 22000, 8 heads, 7500: 27.6 / 21.1; of 45000, 4 heads, 9000:
-  // 33.4 / 26.1; on the other side of the line, of 20000, B = 9000: 28.2 / 26.5, 1 row 23.6 / 22.3.
+  // 67000 with 12.5 %.  us, split form / lists: 32 rows of 20000, 7 heads, B = 8000: 52.5 / 46.8; 8 rows of 22000, 8 heads, 7500: 27.6 / 21.1; of 45000,
+  // 4 heads, 9000: 33.4 / 26.1.  With more than a third selected 24: 17400 tokens with half.  That is no line of speed: with 32 on its other
+  // side, too, 1 row of 20000, B = 9000: 23.2 / 21.4, 8 rows, 4 heads: 26.5 / 25.1, 2 of 20001, 8 heads: 25.1 / 22.6.  It is where short bf16 rows still take
+  // the split form (longer lists, and shares of more than 2048 tokens, take it anyway), whose instances are tested there.
   const int quads = list_quads(s.n_ctx, bsel, kListNT, bsel > s.n_ctx / 3 ? 6 : 8);
   if (!quads) return p;
-  // One workgroup up to B = 256: what it gathers (50 KB per us) takes less than a hand-over and a merge.  us with 1 / 2 / as many as
-  // fit: 8 rows of 16384, B = 128: 12.7 / 14.3 / 14.3, 256: 14.6 / 15.5 / 15.1, 320: 15.3 / 16.0 / 15.1; 128 rows, 256: 41.7 / 42.9.
-  // Beyond, as many as fit at once, one per compute unit, with at least 64 tokens each: 80 rows, B = 700: 36.6 / 35.6 / 34.5 (3) /
-  // 36.2 (4); 8 rows of 32768, B = 2048, 4 / 8 / 16 / 32: 23.7 / 20.8 / 19.4 / 19.0; 32 rows, B = 6200, 4 / 8 / 16: 54.2 / 49.5 / 60.5
+  // One workgroup up to B = 256: what it gathers (50 KB per us) takes less than a hand-over and a merge, also where that leaves half of the
+  // compute units idle.  us with 1 / 2 / 4, 4 heads, of 16384 tokens in caches that the last-level cache holds: 8 rows, B = 128: 11.4 / 13.3 / 13.3, 256:
+  // 12.7 / 13.8 / 13.5, 320: 13.0 / 14.2 / 13.7, 512: 14.9 / 15.0 / 13.9; 32 rows, 256: 16.2 / 17.2 / 16.8, 320: 16.9 / 17.9 / 17.3; 64 rows, 256: 21.6 /
+  // 22.6 / 22.4; 128 rows, 128: 30.1 / 32.0, 256: 31.5 / 33.3, 320: 32.2 / 34.0.  (One is the best up to 400 or so.)
+  // Beyond, as many as fit at once, one per compute unit, with at least 64 tokens each: 80 rows, B = 700: 28.8 / 28.0 / 27.6 (3) /
+  // 29.5 (4); 8 rows of 32768, B = 2048, 4 / 8 / 16 / 32: 18.9 / 16.6 / 15.2 / 15.1; 32 rows, 7 heads, B = 6219, 4 / 8 / 16: 40.9 / 38.2 / 44.7
   int w = bsel <= 256 ? 1 : kAssumedCUs / rows;
   if (w > (bsel + 63) / 64) w = (bsel + 63) / 64;
   if (w > kListMaxWgs) w = kListMaxWgs;
