@@ -801,9 +801,9 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
     // 1000: 18.9 / 14.2 (few rows with more than 500 selected would do better with lists)
     if (ns == 1) return kStepOne;
     // 8 rows of 8192, B = 256: 14.6 / 14.6 / 17.3, B = 512: 16.0 / 17.0 / 19.8; 128 rows of 4096: 22.3 / 20.4 / 21.9
-    // Several slices, where the lists of a scoring launch do not do better: one launch / lists, B = 256, 8 rows of 8192: 14.4 / 12.5, 32
-    // rows: 17.0 / 12.9, 40 rows: 13.7 / 13.7, 128 of 4000: 16.0 / 16.4; 8 rows of 6000, B = 40: 11.2 / 11.0, 320: 13.7 / 13.3, 256 with F = 32: 14.5 / 13.5, of
-    // 4000, 320: 13.5 / 13.3, of 3000, 40: 11.0 / 11.1
+    // Several slices, where the lists of a scoring launch do not do better: one launch / lists, B = 256, 40 rows of 8192: 13.7 / 13.7, 128 of 4000: 16.0 /
+    // 16.4; 8 rows of 6000, B = 40: 11.2 / 11.0, 320: 13.7 / 13.3, 256 with F = 32: 14.5 / 13.5, of 4000, 320: 13.5 / 13.3, of 3000, 40: 11.0 / 11.1.  On the other
+    // side 8 rows of 8192: 14.4 / 13.6, 32 rows: 17.0 / 17.1, from caches in memory, with a selection out of lists that took 2 us longer.
     return ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320 && (rows > 32 || ns < 4) ? kStepOne : kStepNone;
   } else {
     // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
