@@ -46,7 +46,7 @@ int main() {
             ++checked;
           }
   // ---- the step's forms: every plan is one the kernels are built for ----
-  int forms[3] = {0, 0, 0}, lists = 0, topks = 0;
+  int forms[3] = {0, 0, 0}, lists = 0, topks = 0, asked = 0;
   for (int dtype : {FASA_BF16, FASA_F32})
     for (int rows : {1, 3, 8, 64, 65, 72, 128, 256, 257, 512, 4096})
       for (int g : {1, 2, 3, 4, 5, 8})
@@ -70,7 +70,11 @@ int main() {
               const int room = fasa::list_room(bsel, n), one = fasa::list_places(n, bsel, q, false), own = fasa::list_places(n, bsel, q, true);
               EXPECT(room >= 8 && room <= 256 && room % 4 == 0 && one == nsegs * room);
               for (int places : {one, own})
-                EXPECT(places % 4 == 0 && places >= one && places <= q * 512 * 4 && places <= nsegs * 256 && 5ll * places <= 8ll * cap);
+                EXPECT(places % 4 == 0 && places >= one && places <= q * 512 * 4 && places <= nsegs * 256);
+              if (form == fasa::kStepNone && bsel < n) {          // (where it is asked: no row of fewer than 257 tokens)
+                EXPECT(5ll * one <= 8ll * cap && 5ll * own <= 8ll * cap);
+                ++asked;
+              }
               ++lists;
             }
             const fasa::TopkPlan k = fasa::plan_topk(n, bsel);
@@ -84,7 +88,7 @@ int main() {
             if (p.tpb) EXPECT(p.slice_len <= p.tpb && p.nslices <= 256 && (long long)p.nslices * p.slice_len >= n &&
                               (long long)(p.nslices - 1) * p.slice_len < n);
           }
-  EXPECT(lists > 0 && topks > 0 && forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
+  EXPECT(lists > 0 && topks > 0 && asked > 0 && forms[fasa::kStepNone] > 0 && forms[fasa::kStepOne] > 0 && forms[fasa::kStepRow] > 0);
   // ---- eight waves per compute unit: the splits cover the tokens, the workspace holds them, and they fill their rounds ----
   for (int rows = 1; rows <= 600; ++rows)
     for (int count : {1, 17, 700, 1500, 3000, 4096, 8192, 30001, 131072}) {
