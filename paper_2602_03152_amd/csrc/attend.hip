@@ -384,10 +384,17 @@ __global__ __launch_bounds__(256, sizeof(ET) == 4 ? 2 : 1) void attend_kernel(co
 //
 // L = NoList: all rows; SparseList: those that T names (token numbers, or pool slots of a paged cache: block << shift | offset).
 // (An empty argument: with the list's arguments unused, full KV of 8 rows of 8192 takes 0.3 us longer.)
+// NoList<NT>: which of V (1) and K (2) are read non-temporal (kStreamBytes): V where K and V have that many bytes, K as well where it alone does.  A wave's load of K is
+// half a line of each of 16 rows, and the other half, a load later, may come from memory again if lines are not kept; V's are whole rows.  us over three sets of
+// buffers, kept / V / both: 8 rows of 24000, 4 heads (98 MB): 19.5 / 18.8 / 20.0; of 16384: 14.1 / 14.45 / 14.8; of 32768 (134 MB): 26.6 / 23.4 / 24.3; of 65536:
+// 48.5 / 44.0 / 43.0; 32 rows of 32768: 92.1 / 84.1 / 83.3; 12 sets, 8 rows of 32768: 26.7 / 25.0 / 24.7.
 constexpr int kWideNT = 512;
-struct NoList { static constexpr bool used = false; };
+template <int NT> struct NoList {
+  static constexpr bool used = false;
+  static constexpr bool nt_v = NT & 1, nt_k = (NT & 2) != 0;
+};
 struct SparseList {
-  static constexpr bool used = true;
+  static constexpr bool used = true, nt_v = false, nt_k = false;
   const int32_t* T;
   const int32_t *n_ctx_seq, *budget_seq;
   int count_max;
@@ -450,13 +457,13 @@ __global__ __launch_bounds__(kWideNT, 4) void attend_wide_kernel(
   };
   auto load_k = [&](int j0) {
     if constexpr (LIST) kv.load_k(Kr + row_off(ek));
-    else kv.load_k(Kr + (long long)min(j0 + lo, s1 - 1) * sn);
+    else kv.template load_k<L::nt_k>(Kr + (long long)min(j0 + lo, s1 - 1) * sn);
   };
   auto load_v = [&](int j0) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if constexpr (LIST) kv.load_v(i, Vr + row_off(ev[i]));
-      else kv.load_v(i, Vr + (long long)min(j0 + 4 * hi + i, s1 - 1) * sn);
+      else kv.template load_v<L::nt_v>(i, Vr + (long long)min(j0 + 4 * hi + i, s1 - 1) * sn);
     }
   };
   const int jw = s0 + wave * 16;
@@ -527,9 +534,14 @@ static hipError_t launch_wide_g(const fasa_shape& s, bool dense, const AttendPla
   const uint32_t m_splits = div_magic(p.n_splits, (long long)rows * p.n_splits), m_hkv = div_magic(s.n_kv_heads, rows);
   const uint16_t *q16 = (const uint16_t*)q, *k16 = (const uint16_t*)K, *v16 = (const uint16_t*)V;
   const long long sb = s.kv_stride_b, sh = s.kv_stride_h, sn = s.kv_stride_n;
-  if (dense)
-    return launch("fasa_dense_attend", attend_wide_kernel<G, NoList>, grid, block, st, q16, k16, v16, O, ctl, part_acc, part_ml,
-                  rows, p.n_splits, m_splits, s.n_kv_heads, m_hkv, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e, NoList{});
+  if (dense) {
+    const auto all = [&](auto list) {
+      return launch("fasa_dense_attend", attend_wide_kernel<G, decltype(list)>, grid, block, st, q16, k16, v16, O, ctl, part_acc, part_ml,
+                    rows, p.n_splits, m_splits, s.n_kv_heads, m_hkv, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e, list);
+    };
+    const long long of_k = (long long)rows * s.n_ctx * s.head_dim * 2;
+    return of_k >= kStreamBytes ? all(NoList<3>{}) : 2 * of_k >= kStreamBytes ? all(NoList<1>{}) : all(NoList<0>{});
+  }
   return launch("fasa_sparse_attend", attend_wide_kernel<G, SparseList>, grid, block, st, q16, k16, v16, O, ctl, part_acc, part_ml,
                 rows, p.n_splits, m_splits, s.n_kv_heads, m_hkv, s.n_ctx, p.tok_per_split, sb, sh, sn, scale_log2e,
                 SparseList{T, rl.n_ctx, rl.budget, p.count, pm});

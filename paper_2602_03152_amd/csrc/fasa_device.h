@@ -13,6 +13,18 @@ constexpr int kWave = 64;
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
+// 16 bytes of memory.  STREAM: of data that goes by once and leaves no trace in the caches (see kStreamBytes).
+template <bool STREAM = false>
+__device__ __forceinline__ uint4 load_u128(const void* p) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  if constexpr (STREAM) {
+    const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(x.x, x.y, x.z, x.w);
+  } else {
+    return *reinterpret_cast<const uint4*>(p);
+  }
+}
+
 // Order-preserving map float32 -> uint32 (larger score <=> larger key); -0 is folded onto +0 so
 // that the two compare equal, as they do as floats.
 __device__ __forceinline__ uint32_t score_key(float s) {

@@ -25,6 +25,12 @@ constexpr int kMaxGroup = 8;
 // fasa_workspace_bytes() has to be a pure host function; a GPU test checks it against the device.
 constexpr int kAssumedCUs = 256;
 
+// From how many bytes on that a call reads its large inputs are read non-temporal.  A third of the last-level cache: calls of
+// this size over three caches in turn (layers, say) leave nothing there for the next round, and lines that are not kept there come faster:
+// 128 MiB, never the same in 2 GB, 16-byte loads, eight workgroups of 256 on a compute unit: 21.5 -> 20.0 us (6.2 -> 6.7 TB/s).  Below that what one call has
+// left there may serve the next: the same with 64 MiB, 30 buffers: 11.15 -> 10.65 us, but three buffers: 9.9 where memory takes 10.65.
+constexpr long long kStreamBytes = 90ll << 20;
+
 // Per-(b,h) row counters, one 128-byte line per row so that rows served by different XCDs never
 // share a line.  All zero between calls: the workgroup that finishes a row resets what it used.
 struct RowCtl {
@@ -128,6 +134,16 @@ WsLayout ws_layout(const fasa_shape& s);
 // n / 2^31, which may not reach 1 / d.)
 inline uint32_t div_magic(int d, long long most) {
   return most * d < (1ll << 31) ? (uint32_t)(((1ll << 31) + d - 1) / d) : 0u;
+}
+
+// Bytes of K and V that a row's selected tokens take, over all rows, and those of a step: planes, scores, and the former
+inline long long gather_bytes(const fasa_shape& s) {
+  const long long bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx, e = s.dtype == FASA_BF16 ? 2 : 4;
+  return (long long)s.batch * s.n_kv_heads * bsel * 2 * s.head_dim * e;
+}
+inline long long step_bytes(const fasa_shape& s) {
+  const long long e = s.dtype == FASA_BF16 ? 2 : 4;
+  return (long long)s.batch * s.n_kv_heads * s.n_ctx * (2 * s.n_fc * e + 4) + gather_bytes(s);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -40,11 +40,13 @@ template <typename ET> struct TileKV;
 template <> struct TileKV<uint16_t> {
   static constexpr int kPieces = 1;      // 16-byte pieces of a lane's share of a V row
   uint4 kc[4], vr[4];
+  template <bool STREAM = false>
   __device__ __forceinline__ void load_k(const uint16_t* p) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) kc[i] = *reinterpret_cast<const uint4*>(p + 32 * i);
+    for (int i = 0; i < 4; ++i) kc[i] = load_u128<STREAM>(p + 32 * i);
   }
-  __device__ __forceinline__ void load_v(int e, const uint16_t* p) { vr[e] = *reinterpret_cast<const uint4*>(p); }
+  template <bool STREAM = false>
+  __device__ __forceinline__ void load_v(int e, const uint16_t* p) { vr[e] = load_u128<STREAM>(p); }
   __device__ __forceinline__ uint4 v_piece(int e, int) const { return vr[e]; }
 };
 template <> struct TileKV<float> {

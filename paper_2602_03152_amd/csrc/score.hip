@@ -334,7 +334,11 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
 // them is read again: 0.7 us of 29.  us, with a fifth wave that scored a sample of the row for a common cut / like this: 128 rows of 16384, F = 16:
 // 30.0 / 27.7 (score_kernel alone 25.3); 32 rows of 32905: 16.8 / 15.8; 8 of 131072, F = 32: 27.1 / 26.2; 8 of 32768: 5.7 / 5.9.
 constexpr int kListScoreNT = 256;
-template <typename ET, int NB, bool APPEND, int PAIR>
+// STREAM (a step that touches kStreamBytes or more): us per step over three sets of buffers, planes kept / non-temporal: 128 rows of 16384, F = 16, B = 256: 37.7 /
+// 35.1; 96 rows: 31.9 / 29.5; 64 rows: 22.1 / 23.2; 32 rows of 32905, 7 heads, 6219: 45.3 / 41.2; 32768, 4 heads, 2048: 28.8 / 28.2; 8 rows of 131072,
+// F = 32, 1024: 37.6 / 34.9; F = 16, 4000: 26.4 / 27.4.  Ten sets: 128 rows of 16384 37.7 / 35.6, 8 of 131072 37.6 / 35.2; 24 sets of 8 rows of 32768,
+// B = 2048 (28 MB a step), 17.8 / 17.3, three sets of it 16.4 / 16.9.
+template <typename ET, int NB, bool APPEND, int PAIR, bool STREAM>
 __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
     const ET* __restrict__ q, ET* Kp, const int32_t* __restrict__ fc_idx, int rows, int nslices, uint32_t m_slices, int Hkv, uint32_t m_hkv,
     int G, int F, int N_max, int n_cap, const int32_t* __restrict__ n_ctx_seq, float* __restrict__ S, const ET* __restrict__ k_new,
@@ -378,7 +382,7 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
   const int n0 = (slice * NT + t) * TPT;
   const uint32_t at = (uint32_t)(n0 < N ? n0 : 0) * (uint32_t)(2 * sizeof(ET));
   auto load = [&](int f) {
-    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base + (size_t)(NB ? f : min(f, F - 1)) * plane) + at);
+    return load_u128<STREAM>(reinterpret_cast<const char*>(base + (size_t)(NB ? f : min(f, F - 1)) * plane) + at);
   };
   uint4 w[NW];
 #pragma unroll
@@ -582,7 +586,10 @@ static hipError_t launch_score_list_v(const fasa_shape& s, const void* q, void* 
                                       const ListOut& lists, hipStream_t st, RaggedLens rl, const AppendArgs& ap) {
   const int rows = s.batch * s.n_kv_heads;
   const int per_block = kListScoreNT * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per_block - 1) / per_block;
-  return launch("fasa_score_list", score_list_kernel<ET, NB, APPEND, PAIR>, dim3(rows * nslices), dim3(kListScoreNT), st,
+  // (Sequences of their own lengths: half of the bounds or so is there.  Paged, 16 of 4031 - 16127 tokens, 98 MB of 157: 29.4 / 29.8 us)
+  const bool stream = step_bytes(s) >= (rl.n_ctx ? 2 : 1) * kStreamBytes;
+  const auto kernel = stream ? score_list_kernel<ET, NB, APPEND, PAIR, true> : score_list_kernel<ET, NB, APPEND, PAIR, false>;
+  return launch("fasa_score_list", kernel, dim3(rows * nslices), dim3(kListScoreNT), st,
                 (const ET*)q, (ET*)Kp, fc_idx, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_kv_heads,
                 div_magic(s.n_kv_heads, rows), s.n_q_heads / s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, S, (const ET*)ap.k_new,
                 (const ET*)ap.v_new, (ET*)ap.K, (ET*)ap.V, (long long)s.kv_stride_b, (long long)s.kv_stride_h,

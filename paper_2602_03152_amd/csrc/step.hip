@@ -133,7 +133,8 @@ __device__ __forceinline__ void select_row(Lds& sm, int M, uint32_t kcut, uint32
 // ready: how many of the tokens are known already; late(put), called by all threads if that is fewer than cnt, calls put(i, c) for the others, each
 // of which is one of the n_cand tokens sm.cand[c].y.  Tiles of known tokens alone are requested before that.
 struct NothingLate { template <typename Put> __device__ void operator()(Put&&) const {} };
-template <typename ET, int GM, typename Lds, typename Late = NothingLate>
+// STREAM: V's rows are read non-temporal (not K's: a wave's load of those is half a line of each of 16 rows).
+template <typename ET, int GM, bool STREAM = false, typename Lds, typename Late = NothingLate>
 __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, int b, int h, int G, int cnt, int n_app,
                                            int p0 = 0, const MfmaTile<GM>* with_q = nullptr, int ready = 1 << 30, int n_cand = 0,
                                            Late&& late = Late()) {
@@ -214,7 +215,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
         }
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) kv.vr[i] = *reinterpret_cast<const uint4*>(Vb + o[i] + 8 * lo);
+      for (int i = 0; i < 4; ++i) kv.template load_v<STREAM>(i, Vb + o[i] + 8 * lo);
     };
     const int jw = wave * 16;
     TileKV<uint16_t> kv;
@@ -673,7 +674,9 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
 // sequences' rows of 1600 - 6423, B = 66: 13.9 / 14.2.
 // (What the lists' loads depend on comes first and one by one: such arguments are in registers when a kernel starts.  places: of a row's list;
 // negative where sequences have lengths and budgets of their own, which N_max and budget bound; share_max: tokens of a workgroup, whole tiles.)
-template <int G, int Q>
+// STREAM: rows of kStreamBytes and more.  32 rows of 32905, 7 heads, 6219 (102 MB of them), three sets of buffers: 41.2 -> 40.1 us per step, ten: 45.0 -> 43.7, K's
+// rows as well: 42.5; half as much of 32 rows of 32768, 3000: 30.5 / 30.7.
+template <int G, int Q, bool STREAM>
 __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* lims, int rows, int nwgs, uint32_t m_wgs, int N_max, int n_cap,
                                                           int places, int budget, int share_max, int Hkv, uint32_t m_hkv, int pitch,
                                                           const StepArgs a) {
@@ -715,7 +718,7 @@ __global__ __launch_bounds__(kListNT, 2) void list_kernel(uint2* lists, uint2* l
   }
   FASA_T(1);
   // the candidates are ranked while the rows of the others are under way
-  row_attend<ET, G>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile, ready, set.n_cand, [&](auto&& put) {
+  row_attend<ET, G, STREAM>(a, sm, row, b, h, G, p1 - p0, -1, p0, &tile, ready, set.n_cand, [&](auto&& put) {
     constexpr int P = kListNT / kSelCand;
     if ((t & ~(kWave - 1)) / P < set.n_cand) {                // (the waves that have any)
       const int ci = t / P;
@@ -905,7 +908,11 @@ template <int G, int Q>
 static hipError_t launch_list_q(const fasa_shape& s, const ListLaunch& l, const StepArgs& a, hipStream_t st) {
   const int bsel = s.budget < s.n_ctx ? s.budget : s.n_ctx;
   const long long wgs = (long long)a.rows * l.nwgs;
-  return launch("fasa_list", list_kernel<G, Q>, dim3((unsigned)wgs), dim3(kListNT), st, l.list, l.lims, a.rows, l.nwgs,
+  auto kernel = list_kernel<G, Q, false>;
+  if constexpr (Q >= 3) {                                      // (as much with shorter lists takes a hundred rows and more)
+    if (gather_bytes(s) >= kStreamBytes) kernel = list_kernel<G, Q, true>;
+  }
+  return launch("fasa_list", kernel, dim3((unsigned)wgs), dim3(kListNT), st, l.list, l.lims, a.rows, l.nwgs,
                 div_magic(l.nwgs, wgs > bsel + l.nwgs ? wgs : bsel + l.nwgs), a.N_max, a.n_cap,
                 a.n_ctx_seq || a.budget_seq ? -l.places : l.places, bsel, ((bsel + l.nwgs - 1) / l.nwgs + 15) & ~15, a.Hkv, a.m_hkv, l.pitch, a);
 }
