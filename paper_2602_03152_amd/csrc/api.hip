@@ -561,7 +561,7 @@ int calib_layout(const fasa_shape* shape, int32_t top_k, CalibLayout* L) {
   // The top-K sets and how they are found (calib_scratch_bytes).  The size callers are told, and that the call insists on, has
   // room here for the scores of every single FC, and above for one set, which an earlier form of the calibration kept: what
   // fasa_calibration_workspace_bytes() returns for a shape does not change.  (256 bytes per token of capacity, at least
-  // 64 of them per row; the scratch takes 9, and 516 per row.)
+  // 64 of them per row; the scratch takes 14, and 3 KB per row.)
   L->scratch_off = off;
   L->total = off + rows * (shape->head_dim / 2) * shape->n_cap * 4;
   if (off + calib_scratch_bytes((int)rows, shape->n_cap) > L->total) return FASA_EUNSUPPORTED;

@@ -1,14 +1,14 @@
 // Offline calibration (paper Sec. 3.3 eq. ca_k and Alg. 1): contextual agreement of every single
 // frequency chunk with the full head, for one query.  Kp_all holds all d/2 FCs, FC-major.  Two launches:
 //
-//   calib_full_kernel   full-head scores alpha (all planes, fp32 chain in FC order);
+//   calib_full_kernel   full-head scores alpha (all planes, fp32 chain in FC order) and lists of the largest; every FC's cut, from a sample;
 //   calib_fc_kernel     one workgroup per (b, h): the top-K set of alpha; one per (b, h, FC): the scores of the one FC, their top-K
 //                       set, and how many of it are in that of alpha.
 //
 // The single-FC scores never exist in memory: a workgroup streams its plane once and writes one number.
-// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys): 13.6 + 26.1 us.  (The full head's set by a launch in between, one
-// workgroup a row: 13.6 + 11.3 + 21.7, several: 13.6 + 8.9 + 21.7.  Scoring all FCs to memory, 67 MB of scores, selecting them
-// with the decode step's kernels and intersecting index lists: 135.)
+// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys, read twice): 14 + 19.6 us, of which the planes are 10 and 11.  Bound by that stream, then by a
+// chain of dependent phases of a workgroup (5 us).  With the cuts made by the FCs' own workgroups of 1024, and the full head's set out of all its scores: 13 + 26: two of those fill
+// a compute unit, so eight FCs began when the full heads' sets were done, at 14.5 us, and a stretch's loads waited for the cut.
 #include <type_traits>
 
 #include "fasa_device.h"
@@ -21,7 +21,8 @@ namespace fasa {
 
 constexpr int kCalibMaxCtx = 262144;   // a row's set of an FC lives in LDS (33 KB)
 constexpr int kCalibPerThread = 16;    // scores in flight per thread
-constexpr int kCalibWords0 = (8192 + 30) / 31, kCalibWords1 = (32768 + 30) / 31;   // of a set (CalibSets)
+constexpr int kCalibShort = 8192;      // tokens of a row that the registers of 256 threads hold twice over
+constexpr int kCalibWords0 = (kCalibShort + 30) / 31, kCalibWords1 = (32768 + 30) / 31;   // of a set (CalibSets)
 
 // The top-K sets.  A word has 31 tokens, and its top bit says that it is there: the full head's set is read with no other sign.
 struct CalibSets {
@@ -29,6 +30,16 @@ struct CalibSets {
   uint32_t* fc;        // [row][FC][words]: of an FC whose workgroup did not find the full head's
   uint32_t* state;     // [row][FC]: 0; 1: the FC's set is in fc; 2: the full head's is in full
   int words;           // ceil(N / 31)
+  float4* cuts;        // [row][FC]: the cut of the FC's list, the largest of the scores it is from, the sums of the queries' two components
+  // The full head's largest scores by segments (row_list.h); pitch 0: none (float32, or where they would be half of the row)
+  uint32_t* lists;
+  uint2* lims;
+  int pitch, nsegs;
+  __host__ __device__ __forceinline__ size_t list_words() const { return ((size_t)nsegs * (pitch + pitch / 4) + 3) & ~(size_t)3; }
+  __device__ __forceinline__ ListRow list(int row) const {
+    uint32_t* keys = lists + row * list_words();
+    return {keys, keys + nsegs * pitch, lims + (size_t)row * nsegs, pitch};
+  }
   template <int NT>
   __device__ __forceinline__ void clear(int row) const {
     for (int i = threadIdx.x; i < words; i += NT) full[(size_t)row * words + i] = 0;
@@ -36,20 +47,82 @@ struct CalibSets {
   }
 };
 constexpr uint32_t kCalibThere = 0x80000000u;
+constexpr int kCalibLooks = 32;        // for the full head's set, some 25 us
 __device__ __forceinline__ void set_bit(uint32_t* bits, uint32_t tok) { atomicOr(&bits[tok / 31u], 1u << (tok % 31u)); }
 
-// Full-head scores of a slice of 256 * TPT tokens: 1-D grid of rows * nslices workgroups.
+// The cut of an FC's list, by a wave: of 1024 scores (float32: 512; a fourth of that for rows that one workgroup of 256 holds), four (two) neighbours at each of
+// kSpots places, the one that the K best reach and a good many more.  Made where the planes go by anyway, beside the full head's scores: an FC's workgroup that began with it
+// had its first 64 KB in flight, and nothing behind them, until its sample had come, was counted and the cut known (8 rows of 32768: 8.8 us).
+template <typename ET, int SPOTS>
+__device__ __forceinline__ void calib_cut(const ET* p, float qlo, float qhi, int N, int kk, uint32_t* bins, float& cut, float& top) {
+  constexpr int TPT = ScoreTraits<ET>::TPT, L = SPOTS / kWave, SMP = SPOTS * TPT;
+  const int lane = lane_id();
+  uint4 w[L];
+  int n[L];
+#pragma unroll
+  for (int i = 0; i < L; ++i) {
+    n[i] = (int)(((long long)(i * kWave + lane) * N) / SPOTS) & ~(TPT - 1);
+    w[i] = *reinterpret_cast<const uint4*>(p + (size_t)n[i] * 2);
+  }
+  float x[L * TPT];
+#pragma unroll
+  for (int i = 0; i < L; ++i) {
+    float s[TPT];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) s[k] = 0.f;
+    fma_pairs<ET>(w[i], qlo, qhi, s);
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) x[i * TPT + k] = n[i] + k < N ? s[k] : s[0];
+  }
+  // neighbours may be alike: a wider margin than independent ones would need
+  const float ps = (float)kk * ((float)SMP / (float)N);
+  const int r = (int)(ps + 5.0f * sqrtf(ps) + 3.0f);
+  cut = -INFINITY;
+  top = 0.f;
+  if (r <= SMP) cut = list_cut(x, r, bins, top);
+}
+
+// Full-head scores of a slice of 256 * TPT tokens: 1-D grid of rows * 16 workgroups whose waves find an FC's cut each, and rows * nslices.
 template <typename ET, int PAIR_SHIFT, int PAIR_ADD>
 __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict__ q, const ET* __restrict__ Kp,
                                                          float* __restrict__ S, CalibSets sets, int rows, int nslices,
-                                                         uint32_t m_slices, int G, int N, int n_cap) {
+                                                         uint32_t m_slices, int G, int N, int n_cap, int kk) {
   constexpr int D = kHeadDim, F = D / 2, NW = 16;
   constexpr int TPT = ScoreTraits<ET>::TPT;
+  __shared__ SegLds seg[4];
   __shared__ float ql[kMaxGroup][D];
   __shared__ float2 qs[F];
+  const int t = threadIdx.x, n_cuts = rows * (F / 4);
+  if ((int)blockIdx.x < n_cuts) {
+    int r, part;                                              // (on the die of the row's full head, which reads the same lines)
+    constexpr uint32_t m_cuts = div_magic(F / 4, 65535);
+    row_slice_of_block(rows, F / 4, m_cuts, r, part);
+    const int f = part * 4 + __builtin_amdgcn_readfirstlane(t >> 6), id = r * F + f;
+    const ET* qh = q + (size_t)r * G * D + (f << PAIR_SHIFT);
+    ET a[kMaxGroup], b[kMaxGroup];
+#pragma unroll
+    for (int g = 0; g < kMaxGroup; ++g) {
+      a[g] = qh[(size_t)min(g, G - 1) * D];
+      b[g] = qh[(size_t)min(g, G - 1) * D + PAIR_ADD];
+    }
+    float qlo = 0.f, qhi = 0.f;
+#pragma unroll
+    for (int g = 0; g < kMaxGroup; ++g) {   // g ascending, as everywhere
+      float x, y;
+      if constexpr (sizeof(ET) == 2) { x = __uint_as_float((uint32_t)a[g] << 16); y = __uint_as_float((uint32_t)b[g] << 16); }
+      else { x = a[g]; y = b[g]; }
+      qlo += g < G ? x : 0.f;
+      qhi += g < G ? y : 0.f;
+    }
+    const ET* p = Kp + (size_t)id * n_cap * 2;
+    float cut, top;
+    if (N <= kCalibShort) calib_cut<ET, 64>(p, qlo, qhi, N, kk, seg[t >> 6].bins, cut, top);
+    else calib_cut<ET, 256>(p, qlo, qhi, N, kk, seg[t >> 6].bins, cut, top);
+    if ((t & 63) == 0) sets.cuts[id] = make_float4(cut, top, qlo, qhi);
+    return;
+  }
   int row, slice;
-  row_slice_of_block(rows, nslices, m_slices, row, slice);
-  const int t = threadIdx.x;
+  row_slice_of_block(rows, nslices, m_slices, row, slice, blockIdx.x - (unsigned)n_cuts);
   if (slice == 0) sets.clear<256>(row);                       // for the launch behind this one
   const ET* qh = q + (size_t)row * G * D + (t & (D - 1));
   ET qcol[kMaxGroup / 2];                                   // head dim t mod 128 of query heads t / 128, + 2, ...
@@ -97,25 +170,30 @@ __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict
     for (int k = 0; k < TPT; ++k)
       if (n0 + k < N) out[k] = acc[k];
   }
+  if constexpr (TPT * kWave == kListSeg) {
+    const int ls = __builtin_amdgcn_readfirstlane(slice * (256 * TPT / kListSeg) + (t >> 6));
+    if (sets.pitch && ls * kListSeg < N)
+      seg_list<false>(acc, min(N - ls * kListSeg, kListSeg), ls, sets.list(row), seg[t >> 6]);
+  }
 }
 
-template <int NT, int WORDS>
+// LIST: entries of a row's list.
+template <int NT, int WORDS, int LIST>
 struct CalibLds {
-  static constexpr int kThreads = NT;
-  // (two workgroups of 1024 share a compute unit's LDS, or one has it)
-  static constexpr int kList = NT != 1024 ? 4096 : WORDS <= kCalibWords1 ? 8192 : 13312;   // (8 rows of 131072, K = 4096: 212 -> 137 us)
-  uint2 list[kList];                                          // scores at or above the cut: (score bits, token)
-  uint32_t hist[kSelBins];
-  // Places of the row that are sampled, the TPT consecutive tokens of one load each.  With 256 single tokens, ranked by counting,
-  // the list of K = 4096 of 32768 was 7000 entries long and one FC in twenty overflowed: 54.6 us, like this 45.6 (K = 2048: 42.9 / 42.7;
-  // 8 rows of 8192, 512, 128 single tokens: 22.2 / 20.8).
-  static constexpr int kSpots = NT == 1024 ? 256 : 64;
-  union {                                                     // (the sample is spent before there are candidates)
-    uint2 cand[kSelCand];
+  static constexpr int kThreads = NT, kWords = WORDS, kList = LIST;
+  static constexpr int kSpots = NT == 256 ? 64 : 256;         // of calib_top's sample
+  using Tok = typename std::conditional<WORDS <= kCalibWords1, uint16_t, uint32_t>::type;
+  union {
+    struct { uint32_t score[kList]; Tok tok[kList]; };        // what reaches the cut
     struct { __align__(16) float sample[4 * kSpots]; __align__(16) uint32_t bins[256]; };
   };
+  union {                                                     // (the set is made when there is nothing left to count)
+    uint32_t hist[kSelBins];
+    uint32_t bits[WORDS];
+  };
+  uint2 cand[kSelCand];
   float2 cut_top;
-  uint32_t wtot[NT / kWave];
+  uint32_t wtot[NT / kWave], wtot2[NT / kWave];
   uint32_t thr[4];
   uint32_t n_list, n_cnd, count, missing;
   uint32_t early[kHeadDim / 2];
@@ -126,56 +204,36 @@ struct CalibLds {
 // get(c0, i, t, x, full) makes those of tokens c0 + (i * NT + t) * TPT + k, a NaN beyond the row unless it is said to
 // be full (cheap: made again in every pass, which keeps 16 registers free and two workgroups of 1024 on a
 // compute unit); opaque() hides the pieces from the compiler, which would otherwise keep the scores.
-// sample(n) requests the TPT tokens from n on, scores_of() makes their scores.  score_at(n): one token's score.  take_one(n): token n is in the set; early() and ready() run before it, with a barrier of the
-// workgroup between them.
+// pick(klo, ktop): the list has been made already, from elsewhere, out of all scores from klo on.  cut(top) is the cut, and a score at the upper end.  score_at(n): one token's score.  The set goes to sm.bits.
 // What reaches the cut is gathered into a list in LDS first (some 7 instructions a score per wave, where counting
 // and classifying all scores under a test takes 30); a list that comes out short of K or beyond its
 // room is not used.  Infinite scores rank like any others; where NaNs rank is unspecified, but the set has K tokens.
-template <int NT, int WORDS, int TPT, typename Load1, typename Get, typename Opaque, typename Sample, typename ScoresOf, typename ScoreAt,
-          typename Early, typename Ready, typename TakeOne>
-__device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int kk, Load1&& load1, Get&& get,
-                                             Opaque&& opaque, Sample&& sample, ScoresOf&& scores_of, ScoreAt&& score_at,
-                                             Early&& early, Ready&& ready, TakeOne&& take_one) {
+template <int TPT, typename Lds, typename Load1, typename Get, typename Opaque, typename Pick, typename Cut, typename ScoreAt>
+__device__ __forceinline__ void calib_select(Lds& sm, int N, int kk, Load1&& load1, Get&& get, Opaque&& opaque, Pick&& pick, Cut&& cut,
+                                             ScoreAt&& score_at) {
   const int t = threadIdx.x;
-  constexpr int R = NT * kCalibPerThread, NP = kCalibPerThread / TPT;
+  constexpr int NT = Lds::kThreads, R = NT * kCalibPerThread, NP = kCalibPerThread / TPT;
   auto load = [&](int c0) {
 #pragma unroll
     for (int i = 0; i < NP; ++i) load1(i, c0);
   };
   const bool resident = N <= R;
-  constexpr int SP = CalibLds<NT, WORDS>::kSpots, SMP = SP * TPT;
-  float sx[TPT];
-  const int n_spot = (int)(((long long)(t & (SP - 1)) * N) / SP) & ~(TPT - 1);
-  auto spot = sample(n_spot);                                 // (requested ahead of the stretch)
-  load(0);
   if (t == 0) { sm.n_list = 0; sm.n_cnd = 0; sm.thr[2] = 0; }
   for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
-  scores_of(spot, sx);
-  if (t < SP) {
-#pragma unroll
-    for (int k = 0; k < TPT; ++k) sm.sample[k * SP + t] = n_spot + k < N ? sx[k] : sx[0];
-  }
-  __syncthreads();
-  if (t < kWave) {
-    float x[SMP / kWave], top = 0.f, cut = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < SMP / kWave; ++k) x[k] = sm.sample[k * kWave + t];
-    // neighbours may be alike: a wider margin than independent ones would need
-    const float ps = (float)kk * ((float)SMP / (float)N);
-    const int r = (int)(ps + 5.0f * sqrtf(ps) + 3.0f);
-    if (r <= SMP) cut = list_cut(x, r, sm.bins, top);
-    if (t == 0) sm.cut_top = make_float2(cut, top);
-  }
-  __syncthreads();
-  const float flo = sm.cut_top.x;
-  early();
-  uint32_t klo = 0, khi = 0xffffffffu;
+  uint32_t klo = 0, khi = 0xffffffffu, ktop = 0;
   int shift = 22, need = kk, n_cand;
-  if (flo > -INFINITY) {
-    klo = score_key(flo);
-    shift = first_shift(klo, score_key(sm.cut_top.y));
-  }
-  {
+  if (pick(klo, ktop)) {
+    shift = first_shift(klo, ktop);
+  } else {
+    load(0);
+    float top;
+    const float flo = cut(top);
+    __syncthreads();
+    klo = 0;
+    if (flo > -INFINITY) {
+      klo = score_key(flo);
+      shift = first_shift(klo, score_key(top));
+    }
     const int lane = lane_id();
     // One addition to the list's length per wave and piece: its latency hides behind the other waves, where
     // counting first would make every score twice.
@@ -200,8 +258,10 @@ __device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int
 #pragma unroll
         for (int k = 0; k < TPT; ++k) {
           const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
-          if (x[k] >= flo && pos < (uint32_t)CalibLds<NT, WORDS>::kList)
-            sm.list[pos] = make_uint2(__float_as_uint(x[k]), (uint32_t)(c0 + (i * NT + tt) * TPT + k));
+          if (x[k] >= flo && pos < (uint32_t)Lds::kList) {
+            sm.score[pos] = __float_as_uint(x[k]);
+            sm.tok[pos] = (typename Lds::Tok)(c0 + (i * NT + tt) * TPT + k);
+          }
           base += (uint32_t)__popcll(m[k]);
         }
         __builtin_amdgcn_sched_barrier(0);                    // (piece by piece: registers)
@@ -214,7 +274,7 @@ __device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int
     __syncthreads();
   }
   const int M = (int)sm.n_list;
-  const bool listed = M >= kk && M <= CalibLds<NT, WORDS>::kList;
+  const bool listed = M >= kk && M <= Lds::kList;
   // Without a list: all scores of the row, told from what lies beyond it by index.  As keys throughout: a NaN score has
   // a place in the order of keys like any other.
   auto for_scores = [&](int c0, auto&& f) {
@@ -232,13 +292,14 @@ __device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  bool none = false;
   for (;;) {
     const bool whole = klo == 0 && khi == 0xffffffffu;
     auto count = [&](uint32_t key) {
       if (key >= klo && key <= khi) atomicAdd(&sm.hist[min((key - klo) >> shift, (uint32_t)kSelBins - 1u)], 1u);
     };
     if (listed) {
-      for (int i = t; i < M; i += NT) count(score_key(__uint_as_float(sm.list[i].x)));
+      for (int i = t; i < M; i += NT) count(score_key(__uint_as_float(sm.score[i])));
     } else for (int c0 = 0; c0 < N; c0 += R) {
       if (!resident) load(c0);
       opaque();
@@ -247,11 +308,15 @@ __device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int
     if (find_threshold(sm, klo, khi, shift, need, n_cand)) break;
     if (t == 0) sm.thr[2] = 0;                                     // (all have read it)
     if (n_cand == 0) {
-      if (whole) return;                                           // (fewer than K scores: the callers pass K < N)
+      none = whole;                                                // (fewer than K scores: the callers pass K < N)
+      if (none) break;
       klo = 0; khi = 0xffffffffu; shift = 22;                      // the sample misled: the whole range
     }
   }
-  ready();
+  for (int i = t; i < Lds::kWords; i += NT) sm.bits[i] = 0;
+  __syncthreads();
+  if (none) return;
+  auto take_one = [&](int n) { set_bit(sm.bits, (uint32_t)n); };
   const bool ranked = n_cand <= kSelCand;
   auto place = [&](uint32_t key, int n) {
     if (key > khi) take_one(n);
@@ -262,8 +327,7 @@ __device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int
   };
   if (listed) {
     for (int i = t; i < M; i += NT) {
-      const uint2 e = sm.list[i];
-      place(score_key(__uint_as_float(e.x)), (int)e.y);
+      place(score_key(__uint_as_float(sm.score[i])), (int)sm.tok[i]);
     }
   } else for (int c0 = 0; c0 < N; c0 += R) {
     if (!resident) load(c0);
@@ -291,17 +355,84 @@ __device__ __forceinline__ void calib_select(CalibLds<NT, WORDS>& sm, int N, int
 }
 
 // The full head's top-K set, by one workgroup of calib_fc_kernel's launch per row, which then counts for the FCs that came first (a
-// wave each).
-template <int NT, int WORDS>
-__device__ __forceinline__ void calib_top(CalibLds<NT, WORDS>& sm, uint32_t* bits, const float* __restrict__ S, const CalibSets& sets,
-                                          float* CA_sum, int row, int N, int n_cap, int kk) {
-  constexpr int F = kHeadDim / 2;
+// wave each).  Out of the row's lists, whose entries from the highest of their completeness keys on are all there are; if fewer than K of them are (a row's best lie
+// together), or there are none, out of all scores by the cut of a sample.
+template <typename Lds>
+__device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, const CalibSets& sets, float* CA_sum, int row, int N, int n_cap,
+                                          int kk) {
+  constexpr int NT = Lds::kThreads, F = kHeadDim / 2, NWV = NT / kWave;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, words = sets.words;
   const float* s = S + (size_t)row * n_cap;
   __builtin_amdgcn_s_setprio(3);                              // (64 workgroups may end up waiting to be counted)
-  for (int i = t; i < words; i += NT) bits[i] = 0;
+  constexpr int SP = Lds::kSpots, SMP = SP * 4;
+  const int n_spot = (int)(((long long)(t & (SP - 1)) * N) / SP) & ~3;
+  const float4 spot = *reinterpret_cast<const float4*>(s + n_spot);   // (ahead of all that a wait for it would be one for, too)
+  const auto pick = [&](uint32_t& klo, uint32_t& ktop) {
+    if (!sets.pitch) return false;
+    const ListRow l = sets.list(row);
+    const int per = sets.pitch / 4, nq = sets.nsegs * per;
+    uint32_t a = 0, b = 0;
+    for (int i = t; i < sets.nsegs; i += NT) {
+      const uint2 x = l.lims[i];
+      a = max(a, x.x);
+      b = max(b, x.y);
+    }
+    constexpr int U = 2048 / NT;                              // quads in flight
+    uint4 k4[U];
+    uint32_t t4[U];
+    const auto request = [&](int g0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int g = min(g0 + u * NT + t, nq - 1);
+        k4[u] = reinterpret_cast<const uint4*>(l.keys)[g];
+        t4[u] = l.toks[g];
+      }
+    };
+    request(0);
+    a = wave_max_key(a);
+    b = wave_max_key(b);
+    if (lane == kWave - 1) { sm.wtot[wave] = a; sm.wtot2[wave] = b; }
+    __syncthreads();
+    klo = 1;
+    ktop = 0;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) { klo = max(klo, sm.wtot[w]); ktop = max(ktop, sm.wtot2[w]); }
+    for (int g0 = 0; g0 < nq; g0 += U * NT) {
+      if (g0) request(g0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int g = g0 + u * NT + t;
+        const uint32_t keys[4] = {k4[u].x, k4[u].y, k4[u].z, k4[u].w};
+        unsigned long long m[4];
+        uint32_t cnt = 0, base = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          m[k] = __ballot(g < nq && keys[k] >= klo);
+          cnt += (uint32_t)__popcll(m[k]);
+        }
+        if (lane == 0 && cnt) base = atomicAdd(&sm.n_list, cnt);
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        const int n0 = g / per * kListSeg;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
+          if (((m[k] >> lane) & 1ull) && pos < (uint32_t)Lds::kList) {
+            sm.score[pos] = __float_as_uint(key_score(keys[k]));
+            sm.tok[pos] = (typename Lds::Tok)min((uint32_t)n0 + (t4[u] >> (8 * k) & 255u), (uint32_t)N - 1u);
+          }
+          base += (uint32_t)__popcll(m[k]);
+        }
+      }
+    }
+    __syncthreads();
+    const uint32_t M = sm.n_list;
+    if (M >= (uint32_t)kk && M <= (uint32_t)Lds::kList) return true;
+    __syncthreads();                                          // (all have read it)
+    if (t == 0) sm.n_list = 0;
+    return false;
+  };
   float4 w[kCalibPerThread / 4];
-  calib_select<NT, WORDS, 4>(
+  calib_select<4>(
       sm, N, kk,
       [&](int i, int c0) {
         const int n = c0 + (i * NT + t) * 4;
@@ -312,76 +443,80 @@ __device__ __forceinline__ void calib_top(CalibLds<NT, WORDS>& sm, uint32_t* bit
         x[0] = full || n < N ? w[i].x : NAN; x[1] = full || n + 1 < N ? w[i].y : NAN;
         x[2] = full || n + 2 < N ? w[i].z : NAN; x[3] = full || n + 3 < N ? w[i].w : NAN;
       },
-      []() {}, [&](int n) { return *reinterpret_cast<const float4*>(s + n); },
-      [](const float4& v, float (&x)[4]) { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }, [&](int n) { return s[n]; }, []() {},
-      []() {}, [&](int n) { set_bit(bits, (uint32_t)n); });
+      []() {}, pick,
+      [&](float& top) {
+        if (t < SP) {
+          const float x[4] = {spot.x, spot.y, spot.z, spot.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) sm.sample[k * SP + t] = n_spot + k < N ? x[k] : x[0];
+        }
+        __syncthreads();
+        if (t < kWave) {
+          float x[SMP / kWave], best = 0.f, cut = -INFINITY;
+#pragma unroll
+          for (int k = 0; k < SMP / kWave; ++k) x[k] = sm.sample[k * kWave + t];
+          const float ps = (float)kk * ((float)SMP / (float)N);
+          const int r = (int)(ps + 5.0f * sqrtf(ps) + 3.0f);  // (as calib_cut)
+          if (r <= SMP) cut = list_cut(x, r, sm.bins, best);
+          if (t == 0) sm.cut_top = make_float2(cut, best);
+        }
+        __syncthreads();
+        top = sm.cut_top.y;
+        return sm.cut_top.x;
+      },
+      [&](int n) { return s[n]; });
   __syncthreads();
-  for (int i = t; i < words; i += NT) st_agent(sets.full + (size_t)row * words + i, bits[i] | kCalibThere);
+  for (int i = t; i < words; i += NT) st_agent(sets.full + (size_t)row * words + i, sm.bits[i] | kCalibThere);
   publish_barrier();
   if (t < F) sm.early[t] = atomicExch(&sets.state[row * F + t], 2u);
   __syncthreads();
-  for (int f = wave; f < F; f += NT / kWave) {
-    if (sm.early[f] != 1u) continue;
-    const uint32_t* p = sets.fc + ((size_t)row * F + f) * words;
-    uint32_t sum = 0;
-#pragma unroll 8
-    for (int i = lane; i < words; i += kWave) sum += (uint32_t)__popc(ld_agent(p + i) & bits[i]);
-    sum = wave_prefix_sum(sum);
-    if (lane == kWave - 1) CA_sum[row * F + f] += (float)sum / (float)kk;
+  // four FCs at a time, those that have left their sets
+  const unsigned long long left = __ballot(lane < F && sm.early[lane & (F - 1)] == 1u);
+  static_assert(F == kWave, "a lane per FC");
+  for (int n0 = 4 * wave, n = __popcll(left); n0 < n; n0 += 4 * NWV) {
+    int f[4];
+    unsigned long long m = left;
+    for (int i = 0; i < n0; ++i) m &= m - 1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f[j] = m ? __ffsll((long long)m) - 1 : -1;
+      m &= m - 1;
+    }
+    uint32_t sum[4] = {};
+    for (int i = lane; i < words; i += kWave) {
+      const uint32_t x = sm.bits[i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sum[j] += (uint32_t)__popc(ld_agent(sets.fc + ((size_t)row * F + max(f[j], 0)) * words + i) & x);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t all = wave_prefix_sum(sum[j]);
+      if (lane == kWave - 1 && f[j] >= 0) CA_sum[row * F + f[j]] += (float)all / (float)kk;
+    }
   }
 }
 
 // One workgroup per (row, FC): CA_sum[row][i] += |top-K of FC i's scores & the full head's| / K.  The first `rows` workgroups find
-// the full head's set meanwhile, which an FC needs at its end only.  Nobody waits: an FC that finds the set there when it starts
-// (a later round of workgroups) tests its tokens against it; one that does not makes its own set and compares the two at
+// the full head's set meanwhile, which an FC needs at its end only.  Nobody waits: an FC makes its own set and compares the two at
 // its end; if the other is not there even then it leaves its own in memory, says so in its state word, and whoever of the
 // two comes second to that word counts.
-// us, with launches for the full head's set (the better of one or several workgroups a row) / like this: 8 rows of 32768, K = 2048:
-// 46.8 / 42.8, of 8192, 512: 26.9 / 21.6; 64 rows of 4096: 54.0 / 50.7; 1 row of 20000: 28.5 / 21.8; 2 of 100000: 108 / 77.  With
-// several workgroups a row here: 8 rows of 32768: 46.3, of 8192: 21.0 - they take the places of FCs where the chip is full.
-template <typename ET, int NT, int WORDS, int PAIR_SHIFT, int PAIR_ADD>
-__global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCalibWords1 ? 8 : 4) void calib_fc_kernel(
-    const ET* __restrict__ q, const ET* __restrict__ Kp, const float* __restrict__ S, CalibSets sets, float* __restrict__ CA_sum,
-    int rows, int G, int N, int n_cap, int kk) {
-  constexpr int D = kHeadDim, F = D / 2, WPT = (WORDS + NT - 1) / NT;
-  constexpr int TPT = ScoreTraits<ET>::TPT;
-  __shared__ CalibLds<NT, WORDS> sm;
-  __shared__ uint32_t bits[WORDS];
+// us, cuts made here, the FCs tested against the full head's set where it was there / like this: 8 rows of 32768, K = 2048: 39.9 / 34.9; of 16384, 1500: 29.2 / 24.8; of
+// 12000, 7 heads: 28.6 / 23.9; 4 rows of 32000, 3500: 30.6 / 28.2; 2 of 20011, 700: 21.4 / 20.0; 8 of 8192, 512: 20.6 / 18.9; of 1015: 15.5 / 14.4.
+template <typename ET, typename Lds, int WAVES>
+__global__ __launch_bounds__(Lds::kThreads, WAVES) void calib_fc_kernel(const ET* __restrict__ Kp, const float* __restrict__ S, CalibSets sets,
+                                                                       float* __restrict__ CA_sum, int rows, int N, int n_cap, int kk) {
+  constexpr int NT = Lds::kThreads, F = kHeadDim / 2, TPT = ScoreTraits<ET>::TPT;
+  __shared__ Lds sm;
+  const int t = threadIdx.x, words = sets.words;
   if ((int)blockIdx.x < rows) {
-    calib_top<NT, WORDS>(sm, bits, S, sets, CA_sum, (int)blockIdx.x, N, n_cap, kk);
+    calib_top(sm, S, sets, CA_sum, (int)blockIdx.x, N, n_cap, kk);
     return;
   }
-  const int id = (int)blockIdx.x - rows, words = sets.words;
-  const int row = id / F, f = id % F, t = threadIdx.x;
+  const int id = (int)blockIdx.x - rows, row = id / F;
   if (t == 0) { sm.count = 0; sm.missing = 0; }
-  const ET* qh = q + (size_t)row * G * D + (f << PAIR_SHIFT);
-  float qlo = 0.f, qhi = 0.f;
-  {
-    ET a[kMaxGroup], b[kMaxGroup];
-#pragma unroll
-    for (int g = 0; g < kMaxGroup; ++g) {
-      a[g] = qh[(size_t)min(g, G - 1) * D];
-      b[g] = qh[(size_t)min(g, G - 1) * D + PAIR_ADD];
-    }
-#pragma unroll
-    for (int g = 0; g < kMaxGroup; ++g) {
-      float x, y;
-      if constexpr (sizeof(ET) == 2) { x = __uint_as_float((uint32_t)a[g] << 16); y = __uint_as_float((uint32_t)b[g] << 16); }
-      else { x = a[g]; y = b[g]; }
-      qlo += g < G ? x : 0.f;
-      qhi += g < G ? y : 0.f;
-    }
-  }
+  const float4 cq = sets.cuts[id];
+  const float qlo = cq.z, qhi = cq.w;
   const ET* p = Kp + (size_t)id * n_cap * 2;
-  const uint32_t* full = sets.full + (size_t)row * words;
-  uint32_t there = kCalibThere;
-#pragma unroll
-  for (int j = 0; j < WPT; ++j) {
-    const int i = min(j * NT + t, words - 1);
-    const uint32_t x = ld_agent(full + i);
-    bits[i] = x;
-    there &= x;
-  }
   uint4 w[kCalibPerThread / TPT];
   auto load1 = [&](int i, int c0) {
     const int n = c0 + (i * NT + t) * TPT;
@@ -410,49 +545,35 @@ __global__ __launch_bounds__(NT, sizeof(ET) == 2 && NT == 1024 && WORDS == kCali
     }
     return fmaf(qhi, hi, fmaf(qlo, lo, 0.f));
   };
-  uint32_t mine = 0;
-  bool have = true;
-  calib_select<NT, WORDS, TPT>(
-      sm, N, kk, load1, get, opaque, [&](int n) { return *reinterpret_cast<const uint4*>(p + (size_t)n * 2); },
-      [&](const uint4& v, float (&x)[TPT]) {
-#pragma unroll
-        for (int k = 0; k < TPT; ++k) x[k] = 0.f;
-        fma_pairs<ET>(v, qlo, qhi, x);
-      },
-      score_at, [&]() { if (there == 0) sm.missing = 1; },
-      [&]() {
-        have = sm.missing == 0;
-        if (have) return;
-        for (int i = t; i < words; i += NT) bits[i] = 0;
-        __syncthreads();
-      },
-      [&](int n) {
-        if (have) mine += (bits[(uint32_t)n / 31u] >> ((uint32_t)n % 31u)) & 1u;
-        else set_bit(bits, (uint32_t)n);
-      });
-  if (!have) {
-    auto meet = [&]() {
-      there = kCalibThere;
-      mine = 0;
-      for (int i = t; i < words; i += NT) {
-        const uint32_t x = ld_agent(full + i);
-        there &= x;
-        mine += (uint32_t)__popc(x & bits[i]);
-      }
-    };
-    if (t == 0) sm.missing = 0;
-    __syncthreads();
-    meet();
-    if (there == 0) sm.missing = 1;
-    __syncthreads();
-    if (sm.missing) {
-      for (int i = t; i < words; i += NT) st_agent(sets.fc + (size_t)id * words + i, bits[i]);
-      publish_barrier();
-      if (t == 0) sm.missing = atomicExch(&sets.state[id], 1u);
-      __syncthreads();
-      if (sm.missing != 2u) return;                           // (counted by whoever publishes the full head's)
-      meet();
+  calib_select<TPT>(sm, N, kk, load1, get, opaque, [](uint32_t&, uint32_t&) { return false; }, [&](float& top) { top = cq.y; return cq.x; }, score_at);
+  const uint32_t* full = sets.full + (size_t)row * words;
+  uint32_t mine, there;
+  const auto meet = [&]() {
+    there = kCalibThere;
+    mine = 0;
+    for (int i = t; i < words; i += NT) {
+      const uint32_t x = ld_agent(full + i);
+      there &= x;
+      mine += (uint32_t)__popc(x & sm.bits[i]);
     }
+  };
+  // The other is as long in the making, and longer where a row's best lie together, so a wave looks for it for a while: what is left here for the workgroup that makes
+  // it is counted by that alone (8 rows of 32768, an autoregression of 0.98, six looks: 50 us).
+  if (t < kWave) {
+    int looks = kCalibLooks;
+    while (ld_agent(full + words - 1) == 0u && looks-- > 0) __builtin_amdgcn_s_sleep(8);
+  }
+  __syncthreads();
+  meet();
+  if (there == 0) sm.missing = 1;
+  __syncthreads();
+  if (sm.missing) {
+    for (int i = t; i < words; i += NT) st_agent(sets.fc + (size_t)id * words + i, sm.bits[i]);
+    publish_barrier();
+    if (t == 0) sm.missing = atomicExch(&sets.state[id], 1u);
+    __syncthreads();
+    if (sm.missing != 2u) return;                             // (counted by whoever publishes the full head's)
+    meet();
   }
   mine = wave_prefix_sum(mine);
   if (lane_id() == kWave - 1) atomicAdd(&sm.count, mine);
@@ -471,24 +592,28 @@ static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void*
                                  float* CA_sum, hipStream_t st) {
   const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2;
   const int per = 256 * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per - 1) / per;
-  hipError_t e = launch("fasa_calib_full", calib_full_kernel<ET, PS, PA>, dim3(rows * nslices), dim3(256), st, (const ET*)q,
+  hipError_t e = launch("fasa_calib_full", calib_full_kernel<ET, PS, PA>, dim3(rows * (half / 4 + nslices)), dim3(256), st, (const ET*)q,
                         (const ET*)Kp_all, S, sets, rows, nslices, div_magic(nslices, (long long)rows * nslices),
-                        s.n_q_heads / s.n_kv_heads, s.n_ctx, s.n_cap);
+                        s.n_q_heads / s.n_kv_heads, s.n_ctx, s.n_cap, kk);
   if (e != hipSuccess) return e;
-  const auto stage = [&](auto nt_c, auto words_c) {
-    constexpr int NT = decltype(nt_c)::value, WORDS = decltype(words_c)::value;
-    return launch("fasa_calib_fc", calib_fc_kernel<ET, NT, WORDS, PS, PA>, dim3(rows * (1 + half)), dim3(NT), st, (const ET*)q,
-                  (const ET*)Kp_all, S, sets, CA_sum, rows, s.n_q_heads / s.n_kv_heads, s.n_ctx, s.n_cap, kk);
+  const auto stage = [&](auto kernel, int nt) {
+    return launch("fasa_calib_fc", kernel, dim3(rows * (1 + half)), dim3(nt), st, (const ET*)Kp_all, S, sets, CA_sum, rows, s.n_ctx, s.n_cap, kk);
   };
-  // rows that fit in the registers of 256 threads: several workgroups per compute unit instead of one of
-  // 1024 each; rows that fit in those of 1024: a set small enough for two
-  if (s.n_ctx <= 8192) return stage(std::integral_constant<int, 256>{}, std::integral_constant<int, kCalibWords0>{});
-  if (s.n_ctx <= 32768) return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, kCalibWords1>{});
-  return stage(std::integral_constant<int, 1024>{}, std::integral_constant<int, (kCalibMaxCtx + 30) / 31>{});
+  // Rows that fit in the registers of 256 threads twice over: several workgroups per compute unit.  Longer ones: two of 1024 share a compute unit, and three of
+  // 512 do where two don't hold the FCs' and the full head's workgroups at once: 8 rows of 32768, K = 2048 (520 workgroups): 35.6 / 34.9; of 16384: 27.0 / 24.8; of
+  // 12000: 26.0 / 23.9 (with 32 scores in flight per thread 36.7 / 25.6 / 24.5).
+  constexpr bool H = sizeof(ET) == 2;
+  if (s.n_ctx <= kCalibShort) return stage(calib_fc_kernel<ET, CalibLds<256, kCalibWords0, 4096>, 4>, 256);
+  if (s.n_ctx > 32768) return stage(calib_fc_kernel<ET, CalibLds<1024, (kCalibMaxCtx + 30) / 31, 13312>, 4>, 1024);
+  if (rows * (1 + half) <= 2 * kAssumedCUs) return stage(calib_fc_kernel<ET, CalibLds<1024, kCalibWords1, 8192>, H ? 8 : 4>, 1024);
+  return stage(calib_fc_kernel<ET, CalibLds<512, kCalibWords1, 7680>, H ? 6 : 4>, 512);
 }
 
+// Cuts, lists (5 bytes a place), what describes their segments, states, sets.
+static size_t calib_list_segs(int n) { return ((size_t)n + kListSeg - 1) / kListSeg; }
 size_t calib_scratch_bytes(int rows, int n_cap) {
-  return (size_t)rows * (kHeadDim / 2 + (1 + kHeadDim / 2) * (((size_t)n_cap + 30) / 31)) * sizeof(uint32_t);
+  const size_t half = kHeadDim / 2, lists = calib_list_segs(n_cap) * (kListSeg * 5 + sizeof(uint2)) + 16;
+  return rows * (half * (sizeof(float4) + sizeof(uint32_t)) + lists + (1 + half) * (((size_t)n_cap + 30) / 31) * sizeof(uint32_t));
 }
 
 hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, void* scratch, float* CA_sum,
@@ -496,7 +621,13 @@ hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, 
   const size_t rows = (size_t)s.batch * s.n_kv_heads;
   CalibSets sets;
   sets.words = (s.n_ctx + 30) / 31;
-  sets.state = (uint32_t*)scratch;
+  sets.cuts = (float4*)scratch;
+  sets.nsegs = (int)calib_list_segs(s.n_ctx);
+  sets.pitch = s.dtype == FASA_BF16 ? list_room(kk, s.n_ctx) : 0;
+  if (sets.pitch > kListSeg / 2 || s.n_ctx <= kCalibShort) sets.pitch = 0;   // (half of the row, or a row that is read as fast)
+  sets.lists = (uint32_t*)(sets.cuts + rows * (kHeadDim / 2));
+  sets.lims = (uint2*)(sets.lists + rows * sets.list_words());
+  sets.state = (uint32_t*)(sets.lims + rows * sets.nsegs);
   sets.full = sets.state + rows * (kHeadDim / 2);
   sets.fc = sets.full + rows * sets.words;
   constexpr int D = kHeadDim;

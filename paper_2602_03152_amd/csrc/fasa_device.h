@@ -174,8 +174,7 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t m)
 // mapping keeps every workgroup of a row on one XCD: the row's counters, histogram and score
 // slice then live in that XCD's L2 and its atomics do not bounce between dies.
 // m: div_magic(nslices, rows * nslices)
-__device__ __forceinline__ void row_slice_of_block(int rows, int nslices, uint32_t m, int& row, int& slice) {
-  const unsigned id = blockIdx.x;
+__device__ __forceinline__ void row_slice_of_block(int rows, int nslices, uint32_t m, int& row, int& slice, unsigned id = blockIdx.x) {
   const bool by8 = (rows & 7) == 0;
   const unsigned k = by8 ? id >> 3 : id, r = fast_div(k, (unsigned)nslices, m);
   slice = (int)(k - r * (unsigned)nslices);

@@ -132,7 +132,7 @@ WsLayout ws_layout(const fasa_shape& s);
 
 // For fast_div: ceil(2^31 / d), or 0 where quotients of up to `most` would not be exact with it.  (n m / 2^31 exceeds n / d by less than
 // n / 2^31, which may not reach 1 / d.)
-inline uint32_t div_magic(int d, long long most) {
+constexpr uint32_t div_magic(int d, long long most) {
   return most * d < (1ll << 31) ? (uint32_t)(((1ll << 31) + d - 1) / d) : 0u;
 }
 
