@@ -27,13 +27,6 @@ constexpr uint32_t kListAll = 0x007fffffu;   // the key of -inf: a segment is li
 constexpr int kListLimPitch = (int)(kFuseRecBytesPerRow / sizeof(uint2));
 static_assert(kListLimPitch >= kListMaxSegs, "a row's segments are described where the split form has its records");
 
-// Which of m sample scores a row's cut is: four standard deviations (and three) above the B m / N of them that are expected
-// among the B best, half a deviation more than sample_rank().
-__host__ __device__ __forceinline__ int list_rank(int bsel, int n, int m) {
-  const float ps = (float)bsel * ((float)m / (float)n);
-  return (int)(ps + 4.0f * sqrtf(ps) + 3.0f);
-}
-
 // How many scores of a segment are worth listing (a multiple of 4): four standard deviations and five above the 256 B / N of them that
 // are expected among the B best.  Of independent scores hardly one segment in 10^6 has more of them than that, and a row's list is 1.7 B long
 // for 6219 of 32905 tokens, 2.5 B for 2048 of 32768, 5 B for 256 of 16384, 6 B for 1024 of 131072.
@@ -457,6 +450,109 @@ __device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EP
   }
   __syncthreads();
   resolve_threshold(sm, klo, bsel, need, n_cand, srow, N, 0, bsel);
+  return true;
+}
+
+// The B best of a row whose scores all lie in the workgroup's registers: x[k] of token token(k), a NaN where the row has ended.  A histogram of 512 bins
+// between the least and the largest of them, equally wide in the score, gives the bin that the B-th lies in; the few in it are candidates, ranked by counting, and every
+// score above is in the set.  Bins are monotone in the score whatever rounds, so what the scores look like (one far above the others) costs another
+// pass over the bin's own, never exactness; after three passes, for ties by the hundred and where fewer than B scores are numbers, row_select does it.
+// Bound by the latency of a few instructions of each kind behind each other.  Four barriers, where a sample's cut, a list of what reaches it and the selection out of that had
+// eleven; and what a lane has no use for goes to a word of its own in LDS, since sixteen branches around one LDS instruction each took 1.3 us.  us: step of 8 rows of
+// 1531, B = 192, 10.6 -> 9.4; 1 float32 row of 4096, 256, 11.2 -> 10.3 (16 scores a thread, half of them beyond the row, and with branches 11.8).
+// Places go by thread.  False: not done (the histogram is zero then, a barrier before the call's end is the caller's).
+template <int NV, typename Lds, typename Token>
+__device__ __forceinline__ bool select_held(Lds& sm, const float (&x)[NV], Token&& token, int bsel, const float* srow, int N) {
+  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  static_assert(NV <= 16 && kListBins + kWave <= kSelBins, "flags in a word; words for what is not counted");
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (t == 0) sm.n_cnd = 0;
+  for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
+  uint32_t win = 0, act = 0;                                  // of the thread's scores: in the set; in the bin that is looked at
+  int need = bsel, n_cand = 0;
+  float hi = x[0], lo = x[0];
+#pragma unroll
+  for (int k = 1; k < NV; ++k) hi = fmaxf(hi, x[k]);
+  // From the lowest of the threads' highest on: a score of each thread that has any, and so B of them (the row's tokens lie in fours, at most)
+  if (bsel <= min(NT, N / 4)) lo = hi;
+  else {
+#pragma unroll
+    for (int k = 1; k < NV; ++k) lo = fminf(lo, x[k]);
+  }
+  for (int pass = 0;; ++pass) {
+    hi = wave_max(hi);
+    lo = -wave_max(-lo);
+    if (lane == 0) { sm.wtot[wave] = __float_as_uint(hi); sm.wtot2[wave] = __float_as_uint(lo); }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) {
+      hi = fmaxf(hi, __uint_as_float(sm.wtot[w]));
+      lo = fminf(lo, __uint_as_float(sm.wtot2[w]));
+    }
+    // (an infinite spread: all of them in bin 0, and the next pass leaves infinities out)
+    const float inv = (float)kListBins * __builtin_amdgcn_rcpf(hi - lo);
+    uint32_t bin[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      bin[k] = (uint32_t)fminf(fmaxf((x[k] - lo) * inv, 0.0f), (float)(kListBins - 1));
+      const bool in = x[k] >= lo && (pass == 0 || (act >> k & 1u));
+      bin[k] = in ? bin[k] : (uint32_t)(kListBins + lane);
+      atomicAdd(&sm.hist[bin[k]], 1u);
+    }
+    __syncthreads();
+    const BinAt b = wave_find_bin(sm.hist, (uint32_t)need);
+    if (b.n == 0) break;
+    need -= b.above;
+    n_cand = b.n;
+    act = 0;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      win |= bin[k] > (uint32_t)b.bin && bin[k] < (uint32_t)kListBins ? 1u << k : 0u;
+      act |= bin[k] == (uint32_t)b.bin ? 1u << k : 0u;
+    }
+    if (__builtin_expect(n_cand <= kSelCand, true)) break;
+    n_cand = 0;
+    if (pass == 2) break;
+    __syncthreads();                                          // (all have read the histogram)
+    for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
+    hi = -INFINITY;
+    lo = INFINITY;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const bool in = (act >> k & 1u) && fabsf(x[k]) < INFINITY;      // (infinite ones: the bins at the ends)
+      hi = in ? fmaxf(hi, x[k]) : hi;
+      lo = in ? fminf(lo, x[k]) : lo;
+    }
+  }
+  if (n_cand == 0) {
+    __syncthreads();
+    for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+    if (t == 0) sm.thr[2] = 0;
+    return false;
+  }
+  const uint32_t n_win = (uint32_t)__popc(win), incl = wave_prefix_sum(n_win);
+  if (lane == kWave - 1) sm.wtot[wave] = incl;                // (all have read them: a barrier lies between)
+  while (act != 0u) {                                         // (few lanes have a candidate)
+    const int j = __ffs((int)act) - 1;
+    float xj = x[0];
+    int tj = token(0);
+#pragma unroll
+    for (int k = 1; k < NV; ++k) { xj = j == k ? x[k] : xj; tj = j == k ? token(k) : tj; }
+    const uint32_t c = __builtin_amdgcn_atomic_inc32(&sm.n_cnd, 0xffffffffu, __ATOMIC_RELAXED, "workgroup");
+    sm.cand[c & (kSelCand - 1)] = make_uint2(score_key(xj), (uint32_t)tj);
+    act &= act - 1u;
+  }
+  __syncthreads();
+  uint32_t p = incl - n_win;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) p += w < wave ? sm.wtot[w] : 0u;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const bool w = win >> k & 1u;
+    sm.put_if(w, (int)p, (uint32_t)token(k));
+    p += w ? 1u : 0u;
+  }
+  resolve_threshold(sm, 0u, bsel, need, n_cand, srow, N, 0, bsel);
   return true;
 }
 

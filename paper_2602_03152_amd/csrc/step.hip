@@ -60,7 +60,7 @@ template <int NT, int GM, int LIST = kListPerThread * NT, int MOST = kStepMaxBud
 struct RowLds {
   static constexpr int kThreads = NT;
   static constexpr int kWaves = NT / kWave;
-  static constexpr int kList = LIST;
+  static constexpr int kList = LIST, kMost = MOST;
   static constexpr int kLoads = 4;                           // of segments that are read again
   static constexpr bool kWideTies = LIST == 1;
   static constexpr int kExtraPerWave = LIST == 1 ? 896 : 1;  // (two workgroups still share a compute unit's LDS)
@@ -77,7 +77,7 @@ struct RowLds {
   uint2 cand[kSelCand];
   uint32_t cand_at[kSelCand];                                // where their rows lie
   uint32_t ssort[kSample];                                   // keys of the sample, largest first
-  __align__(16) uint32_t wl[MOST + 16];            // selected tokens, then what the gather reads for them
+  __align__(16) uint32_t wl[MOST + 16 + kWave];   // selected tokens, then what the gather reads for them; a word per lane
   float m[kWaves][GM], l[kWaves][GM];
   float scs[kWaves][16];
   uint32_t wtot[kWaves], wtot2[kWaves];
@@ -88,6 +88,8 @@ struct RowLds {
   uint32_t n_list, n_cnd;
   int p_new;                                                 // place of the appended row in wl, or -1
   __device__ __forceinline__ void put(int place, uint32_t tok) { wl[place] = tok; }
+  // (no branch: a lane that has nothing to put writes a word of its own)
+  __device__ __forceinline__ void put_if(bool yes, int place, uint32_t tok) { wl[yes ? place : kMost + 16 + lane_id()] = tok; }
 };
 
 // 16-byte store that goes through to the coherence point (see st_agent), counted by the compiler.  The
@@ -449,7 +451,6 @@ __device__ __forceinline__ void step_row(const void* q0, void* Kp0, const int32_
     };
     RowLds<kStepNT, GM> row;
   } sm;
-  __shared__ __align__(16) float srow_lds[MULTI ? 4 : SL];     // scores of a single-slice row, for the sample
   __shared__ uint32_t ticket;
 
   int row = blockIdx.x, slice = 0, b, h;
@@ -576,37 +577,38 @@ __device__ __forceinline__ void step_row(const void* q0, void* Kp0, const int32_
       *dst = newkv;
     }
   }
-  int M;
-  uint32_t kcut, ktop;
+  bool done;
   if constexpr (MULTI) {
     __syncthreads();
     if (ticket != (uint32_t)nvalid - 1u) return;
     if (t == 0) a.ctl[row].done_sel = 0;                      // clean for the next call
-    const int si = (int)(((long long)(t & (kSample - 1)) * N) >> 7);
-    const float sval = ld_agent(srow + si);
-    constexpr int CH = kStepMaxCtx / (4 * kStepNT);
-    float v[4 * CH];
-    // the row is readable in 16-byte pieces: S is n_cap long, a multiple of 64
+    // (the row is readable in 16-byte pieces: S is n_cap long, a multiple of 64)
+    if (t == 0) sm.row.p_new = -1;
+    auto held = [&](auto pieces) {
+      constexpr int CH = decltype(pieces)::value;
+      float v[4 * CH];
 #pragma unroll
-    for (int it = 0; it < CH; ++it) {
-      const int n = (it * kStepNT + t) * 4;
-      const uint4 x = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
-      v[4 * it] = n < N ? __uint_as_float(x.x) : NAN; v[4 * it + 1] = n + 1 < N ? __uint_as_float(x.y) : NAN;
-      v[4 * it + 2] = n + 2 < N ? __uint_as_float(x.z) : NAN; v[4 * it + 3] = n + 3 < N ? __uint_as_float(x.w) : NAN;
-    }
-    M = make_list<4 * CH, true>(sm.row, N, bsel, sval, 0, [&](int k) { return v[k]; },
-                                [&](int k, int) { return ((k >> 2) * kStepNT + t) * 4 + (k & 3); }, [](int) {}, kcut, ktop);
+      for (int it = 0; it < CH; ++it) {
+        const int n = (it * kStepNT + t) * 4;
+        const uint4 x = agent_load_u128(rs, (uint32_t)(n < N ? n : 0) * 4u);
+        v[4 * it] = n < N ? __uint_as_float(x.x) : NAN; v[4 * it + 1] = n + 1 < N ? __uint_as_float(x.y) : NAN;
+        v[4 * it + 2] = n + 2 < N ? __uint_as_float(x.z) : NAN; v[4 * it + 3] = n + 3 < N ? __uint_as_float(x.w) : NAN;
+      }
+      return select_held(sm.row, v, [&](int k) { return ((k >> 2) * kStepNT + t) * 4 + (k & 3); }, bsel, srow, N);
+    };
+    constexpr int CH = kStepMaxCtx / (4 * kStepNT);
+    done = N <= kStepMaxCtx / 2 ? held(std::integral_constant<int, CH / 2>{}) : held(std::integral_constant<int, CH>{});
   } else {
 #pragma unroll
-    for (int k = 0; k < TPT; ++k) srow_lds[t * TPT + k] = acc[k];
-    __syncthreads();
-    const float sval = srow_lds[((t & (kSample - 1)) * N) >> 7];
-#pragma unroll
     for (int k = 0; k < TPT; ++k) acc[k] = n0 + k < N ? acc[k] : NAN;
-    M = make_list<TPT, true>(sm.row, N, bsel, sval, 0, [&](int k) { return acc[k]; }, [&](int k, int) { return n0 + k; }, [](int) {},
-                       kcut, ktop);
+    __syncthreads();                                          // (all have read the queries' sums: shared storage)
+    if (t == 0) sm.row.p_new = -1;
+    done = select_held(sm.row, acc, [&](int k) { return n0 + k; }, bsel, srow, N);
   }
-  select_row(sm.row, M, kcut, ktop, bsel, srow, N);
+  if (!done) {
+    publish_barrier();                                        // this workgroup's own scores are in memory
+    row_select<true>(sm.row, bsel, srow, N, 0, bsel);
+  }
   row_attend<ET, GM>(a, sm.row, row, b, h, G, bsel, append ? n_app : -1);
   write_output(a, sm.row, row, G);
 }

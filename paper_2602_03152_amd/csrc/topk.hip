@@ -197,24 +197,24 @@ __global__ __launch_bounds__(256) void select_all_kernel(int32_t* __restrict__ T
 // that comes last, by the row's ticket, selects out of the lists.  No workgroup waits for another.  (A row of one workgroup is selected
 // out of registers.)
 // ---------------------------------------------------------------------------------------------
-constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT, kTopkSample = 256;
+constexpr int kTopkNT = 512, kTopkSeg = 4 * kTopkNT;
 
 struct TopkLds {
   static constexpr bool kWideTies = true;
   static constexpr int kThreads = kTopkNT, kWaves = kTopkNT / kWave, kExtraPerWave = 256, kLoads = 1;
-  __align__(16) float sample[kTopkSample];
-  __align__(16) uint32_t bins[256];
-  uint32_t hist[kSelBins];
+  __align__(16) uint32_t hist[kSelBins];
   uint2 cand[kSelCand];
   uint2 extra[kWaves * kExtraPerWave];                       // entries of lists that no thread holds
   SegLds seg[kWaves];
   uint2 lim[kThreads];
-  uint32_t wtot[kWaves], wtot2[kWaves], wcnt[kWaves];
+  uint32_t wtot[kWaves], wtot2[kWaves];
   uint32_t thr[4];
   uint32_t ticket, n_cnd;
-  float2 cut_top;
   __attribute__((address_space(1))) int32_t* out;             // (a generic pointer's stores are flat: every wait is one for all of LDS)
   __device__ __forceinline__ void put(int place, uint32_t tok) { out[place] = (int32_t)tok; }
+  __device__ __forceinline__ void put_if(bool yes, int place, uint32_t tok) {
+    if (yes) put(place, tok);
+  }
 };
 
 template <int Q, bool ONE>
@@ -230,41 +230,12 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
   const float4 x = *reinterpret_cast<const float4*>(srow + (n0 < N ? n0 : 0));   // (S is n_cap long, a multiple of 64)
   const float acc[4] = {x.x, x.y, x.z, x.w};
   if constexpr (ONE) {
-    // one score out of each of 256 equal stretches, at uneven places: a mask of every second token must not hide from it
-    if (t < kTopkSample) sm.sample[t] = srow[(int)((((unsigned long long)t << 16 | (t * 40503u & 0xffffu)) * (unsigned)N) >> 24)];
-    for (int i = t; i < kSelBins; i += kTopkNT) sm.hist[i] = 0;
-    if (t == 0) {
-      sm.thr[2] = 0;
-      sm.out = (__attribute__((address_space(1))) int32_t*)(T + (size_t)row * bsel);
+    if (t == 0) sm.out = (__attribute__((address_space(1))) int32_t*)(T + (size_t)row * bsel);
+    const float held[4] = {n0 < N ? x.x : NAN, n0 + 1 < N ? x.y : NAN, n0 + 2 < N ? x.z : NAN, n0 + 3 < N ? x.w : NAN};
+    if (!select_held(sm, held, [&](int k) { return n0 + k; }, bsel, srow, N)) {
+      __syncthreads();
+      row_select<false>(sm, bsel, srow, N, 0, bsel);
     }
-    __syncthreads();
-    if (t < kWave) {
-      const float smp[4] = {sm.sample[t], sm.sample[kWave + t], sm.sample[2 * kWave + t], sm.sample[3 * kWave + t]};
-      const int r = list_rank(bsel, N, kTopkSample);
-      float top = INFINITY, cut = -INFINITY;
-      if (r <= kTopkSample) cut = list_cut(smp, r, sm.bins, top);
-      if (t == 0) sm.cut_top = make_float2(cut, top);
-    }
-    __syncthreads();
-    const float cut = sm.cut_top.x, top = sm.cut_top.y;
-    uint32_t mine = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) mine += (uint32_t)__popcll(__ballot(n0 + k < N && acc[k] >= cut));
-    if (lane_id() == 0) sm.wcnt[t >> 6] = mine;
-    __syncthreads();
-    uint32_t total = 0;
-#pragma unroll
-    for (int w = 0; w < kTopkNT / kWave; ++w) total += sm.wcnt[w];
-    const bool cut_it = (int)total >= bsel;
-    uint32_t key[4], tok[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      key[k] = n0 + k < N && (!cut_it || acc[k] >= cut) ? score_key(acc[k]) : 0u;
-      tok[k] = (uint32_t)(n0 + k);
-    }
-    const uint32_t kcut = cut_it ? score_key(cut) : 0u;
-    if (!select_entries<4>(sm, key, tok, max(kcut, 1u), kcut ? first_shift(kcut, score_key(top)) : 22, bsel, srow, N))
-      row_select<false>(sm, bsel, srow, N, 0, bsel);           // (NaNs that have the key of nothing)
     return;
   }
   const int places = (N + kListSeg - 1) / kListSeg * pitch;
