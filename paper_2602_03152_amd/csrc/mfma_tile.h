@@ -62,6 +62,20 @@ template <> struct TileKV<float> {
   }
   __device__ __forceinline__ uint4 v_piece(int e, int i) const { return __builtin_bit_cast(uint4, vr[e][i]); }
 };
+// K rows of a bf16 tile that were loaded as V's are (lane (lo, hi): chunk lo of rows 4hi .. 4hi + 3), as the matrix cores want them: through 4 KB of LDS of the wave's
+// own.  Row r's chunk c goes to place c ^ r, so that writes and reads touch all banks evenly.  A load of the latter kind is half a line of each of 16 rows, and
+// lines are what a compute unit's request rate is in: 128 rows take one 1.45 us that way, 1.0 as whole rows; 256 of K and V 3.35, 2.8 (256 compute units at
+// once: 4.45, 4.3).  Rows next to each other gain nothing: full KV of 8 rows of 32768 23.3 -> 23.7, and 24.3 with K read non-temporal.
+constexpr int kTurnWords = 16 * kHeadDim / 8;                 // uint4s
+__device__ __forceinline__ void turn_k(uint4 (&kc)[4], uint4* lds, int lo, int hi) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) lds[(4 * hi + i) * 16 + (lo ^ (4 * hi + i))] = kc[i];
+  // (the wave's LDS operations complete in order; the fences only keep the compiler from moving them)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int i = 0; i < 4; ++i) kc[i] = lds[lo * 16 + ((hi + 4 * i) ^ lo)];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
 template <typename ET> constexpr int kChunk = 16 / (int)sizeof(ET);   // head dims per chunk of a K row
 
 // G: most query heads per KV head (1 .. 8; the tile is padded to 16 heads, whose results nobody reads); kernels

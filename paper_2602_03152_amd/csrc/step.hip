@@ -65,7 +65,8 @@ struct RowLds {
   static constexpr bool kWideTies = LIST == 1;
   static constexpr int kExtraPerWave = LIST == 1 ? 896 : 1;  // (two workgroups still share a compute unit's LDS)
   union {
-    float o[kWaves][GM][kHeadDim];                           // weighted V per wave
+    float o[kWaves][kMaxGroup][kHeadDim];                    // weighted V per wave
+    uint4 k[kWaves][kTurnWords];                             // a tile's K rows, by the wave whose o lies there later
     uint2 list[kList];                                       // scores at or above the cut: (score bits, token)
     uint2 extra[kWaves * kExtraPerWave];                     // entries of lists that no thread holds
     unsigned char merge[8192 + GM * kListMaxWgs * 4];        // combine_row: partitions, then weights
@@ -195,27 +196,29 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
     // (The appended row by its distance: with a choice of pointers the compiler no longer knew them for global ones, and a flat load makes every wait
     // one for all loads and all of LDS.  8 rows of 32768, B = 2048: 16.9 -> 16.6 us; 32 of 32905, 7 heads: 45.3 -> 44.9; 8 of 1531, B = 192: 10.70 -> 10.60.)
     const long long k_app = ((const char*)kn - (const char*)Kb) / 2, v_app = ((const char*)vn - (const char*)Vb) / 2;
-    auto load_k = [&](TileKV<uint16_t>& kv, int j0) {
-      long long o = (long long)((size_t)sm.wl[j0 + lo] << 3);
-      if constexpr (!kLate) {
-        if (p_new >= j0 && p_new < j0 + 16) o = p_new == j0 + lo ? k_app : o;   // (wave-uniform test)
-      }
-      const ET* kr = Kb + o + 8 * hi;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) kv.kc[i] = *reinterpret_cast<const uint4*>(kr + 32 * i);
-    };
-    auto load_v = [&](TileKV<uint16_t>& kv, int j0) {
+    // (K's rows whole, as V's: turn_k.  us per step: 8 rows of 1531, B = 192: 9.43 -> 9.19; 128 of 16384, 256: 34.87 -> 34.70; 32 of 32905, 7 heads,
+    // 6219: 39.60 -> 39.46, with K read non-temporal as well 40.4.)
+    auto rows_of = [&](int j0, long long app, long long (&o)[4]) {
       const uint4 e4 = *reinterpret_cast<const uint4*>(&sm.wl[j0 + 4 * hi]);
       const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
-      long long o[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) o[i] = (long long)((size_t)e[i] << 3);
       if constexpr (!kLate) {
-        if (p_new >= j0 && p_new < j0 + 16) {
+        if (p_new >= j0 && p_new < j0 + 16) {                 // (wave-uniform test)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o[i] = p_new == j0 + 4 * hi + i ? v_app : o[i];
+          for (int i = 0; i < 4; ++i) o[i] = p_new == j0 + 4 * hi + i ? app : o[i];
         }
       }
+    };
+    auto load_k = [&](TileKV<uint16_t>& kv, int j0) {
+      long long o[4];
+      rows_of(j0, k_app, o);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kv.kc[i] = *reinterpret_cast<const uint4*>(Kb + o[i] + 8 * lo);
+    };
+    auto load_v = [&](TileKV<uint16_t>& kv, int j0) {
+      long long o[4];
+      rows_of(j0, v_app, o);
 #pragma unroll
       for (int i = 0; i < 4; ++i) kv.template load_v<STREAM>(i, Vb + o[i] + 8 * lo);
     };
@@ -256,6 +259,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
       }
       for (int i = 0; i + 1 < n_tiles; ++i) {
         const int j0 = jw + 16 * NWV * i;
+        turn_k(kv.kc, sm.k[wave], lo, hi);
         tile.logits(kv, a.scale_log2e, sv);
         // the next tile's K runs under this tile's P.V and its V under the next logits; the scheduler is
         // kept from moving any of it (it would need 60 registers more than a wave has here, and spill)
@@ -268,6 +272,7 @@ __device__ __forceinline__ void row_attend(const StepArgs& a, Lds& sm, int row, 
         __builtin_amdgcn_sched_barrier(0);
       }
       const int j0 = jw + 16 * NWV * (n_tiles - 1);
+      turn_k(kv.kc, sm.k[wave], lo, hi);
       tile.logits(kv, a.scale_log2e, sv);
       bool valid[4];
 #pragma unroll
