@@ -331,7 +331,9 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
 // Scores and lists (row_list.h).  1-D grid of rows * nslices workgroups of four waves, which score 1024 tokens as above; each lists its
 // own 256, with nothing to wait for.  Eight planes in flight leave room for eight workgroups per compute unit; 16, where there is no more than one
 // or two for each, gain nothing (8 rows of 32768: 16.8 / 16.8 us per step, of 34625: 16.1 / 16.6).  The scores are stored non-temporal, since little of
-// them is read again: 0.7 us of 29.  us, with a fifth wave that scored a sample of the row for a common cut / like this: 128 rows of 16384, F = 16:
+// them is read again (0.7 us of 29), but where the planes are read so: then nothing else asks for room in the caches, and memory takes 8 MB of
+// writes among the reads for 2.4 us of 26.6, behind the caches for 1.5 (128 rows of 16384 34.8 -> 34.0 us per step, 8 of 131072 34.4 -> 33.7, 32 of 32905 39.8 -> 39.35;
+// 16 paged sequences, whose planes are kept, 29.3 -> 30.25).  us, with a fifth wave that scored a sample of the row for a common cut / like this: 128 rows of 16384, F = 16:
 // 30.0 / 27.7 (score_kernel alone 25.3); 32 rows of 32905: 16.8 / 15.8; 8 of 131072, F = 32: 27.1 / 26.2; 8 of 32768: 5.7 / 5.9.
 constexpr int kListScoreNT = 256;
 // STREAM (a step that touches kStreamBytes or more): us per step over three sets of buffers, planes kept / non-temporal: 128 rows of 16384, F = 16, B = 256: 37.7 /
@@ -456,7 +458,8 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
   if (n0 < N) {
     float* out = S + (size_t)row * n_cap + n0;
     if (n0 + TPT <= N) {
-      __builtin_nontemporal_store(f32x4_t{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<f32x4_t*>(out));
+      if constexpr (STREAM) *reinterpret_cast<float4*>(out) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      else __builtin_nontemporal_store(f32x4_t{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<f32x4_t*>(out));
     } else {
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
