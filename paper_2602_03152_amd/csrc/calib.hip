@@ -1,14 +1,18 @@
 // Offline calibration (paper Sec. 3.3 eq. ca_k and Alg. 1): contextual agreement of every single
-// frequency chunk with the full head, for one query.  Kp_all holds all d/2 FCs, FC-major.  Two launches:
+// frequency chunk with the full head, for one query.  Kp_all holds all d/2 FCs, FC-major.  In one launch (bf16, 8 rows or more, of 8193 .. 32768 tokens):
 //
-//   calib_full_kernel   full-head scores alpha (all planes, fp32 chain in FC order) and lists of the largest; every FC's cut, from a sample;
-//   calib_fc_kernel     one workgroup per (b, h): the top-K set of alpha; one per (b, h, FC): the scores of the one FC, their top-K
-//                       set, and how many of it are in that of alpha.
+//   calib_kernel        workgroups that score a slice of a row's full head each (all planes, fp32 chain in FC order) and list the largest; the last of a row, by
+//                       ticket, finds the top-K set; beside them one per (b, h, FC): the scores of the one FC, their top-K set, and how many of it are in the full head's.
+//
+// or in two:
+//
+//   calib_full_kernel   the full head's scores and lists; every FC's cut, from a sample;
+//   calib_fc_kernel     one workgroup per (b, h): the top-K set of the full head; one per (b, h, FC), as above.
 //
 // The single-FC scores never exist in memory: a workgroup streams its plane once and writes one number.
-// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys, read twice): 14 + 19.6 us, of which the planes are 10 and 11.  Bound by that stream, then by a
-// chain of dependent phases of a workgroup (5 us).  With the cuts made by the FCs' own workgroups of 1024, and the full head's set out of all its scores: 13 + 26: two of those fill
-// a compute unit, so eight FCs began when the full heads' sets were done, at 14.5 us, and a stretch's loads waited for the cut.
+// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys, asked for twice): 2.3 us for a launch that clears and 29, of which the planes are 18 - 20 (7 TB/s: the second
+// read is no faster than the first); then the full head's set (5 us) and the FCs that come last.  In two launches: 14.5 + 21, the first's end and the second's, where all
+// workgroups select at once, with nothing to stream.
 #include <type_traits>
 
 #include "fasa_device.h"
@@ -29,6 +33,7 @@ struct CalibSets {
   uint32_t* full;      // [row][words]: of the full head
   uint32_t* fc;        // [row][FC][words]: of an FC whose workgroup did not find the full head's
   uint32_t* state;     // [row][FC]: 0; 1: the FC's set is in fc; 2: the full head's is in full
+  uint32_t* tickets;   // [row]: workgroups that have scored their slices of the full head
   int words;           // ceil(N / 31)
   float4* cuts;        // [row][FC]: the cut of the FC's list, the largest of the scores it is from, the sums of the queries' two components
   // The full head's largest scores by segments (row_list.h); pitch 0: none (float32, or where they would be half of the row)
@@ -44,6 +49,7 @@ struct CalibSets {
   __device__ __forceinline__ void clear(int row) const {
     for (int i = threadIdx.x; i < words; i += NT) full[(size_t)row * words + i] = 0;
     if (threadIdx.x < kHeadDim / 2) state[row * (kHeadDim / 2) + threadIdx.x] = 0;
+    if (threadIdx.x == 0) tickets[row] = 0;
   }
 };
 constexpr uint32_t kCalibThere = 0x80000000u;
@@ -54,16 +60,22 @@ __device__ __forceinline__ void set_bit(uint32_t* bits, uint32_t tok) { atomicOr
 // kSpots places, the one that the K best reach and a good many more.  Made where the planes go by anyway, beside the full head's scores: an FC's workgroup that began with it
 // had its first 64 KB in flight, and nothing behind them, until its sample had come, was counted and the cut known (8 rows of 32768: 8.8 us).
 template <typename ET, int SPOTS>
-__device__ __forceinline__ void calib_cut(const ET* p, float qlo, float qhi, int N, int kk, uint32_t* bins, float& cut, float& top) {
-  constexpr int TPT = ScoreTraits<ET>::TPT, L = SPOTS / kWave, SMP = SPOTS * TPT;
-  const int lane = lane_id();
+struct CalibSample {
+  static constexpr int TPT = ScoreTraits<ET>::TPT, L = SPOTS / kWave, SMP = SPOTS * TPT;
   uint4 w[L];
   int n[L];
+  __device__ __forceinline__ void request(const ET* p, int N) {
+    const int lane = lane_id();
 #pragma unroll
-  for (int i = 0; i < L; ++i) {
-    n[i] = (int)(((long long)(i * kWave + lane) * N) / SPOTS) & ~(TPT - 1);
-    w[i] = *reinterpret_cast<const uint4*>(p + (size_t)n[i] * 2);
+    for (int i = 0; i < L; ++i) {
+      n[i] = (int)((long long)(i * kWave + lane) * N / SPOTS) & ~(TPT - 1);
+      w[i] = *reinterpret_cast<const uint4*>(p + (size_t)n[i] * 2);
+    }
   }
+  __device__ __forceinline__ void make_cut(float qlo, float qhi, int N, int kk, uint32_t* bins, float& cut, float& top) const;
+};
+template <typename ET, int SPOTS>
+__device__ __forceinline__ void CalibSample<ET, SPOTS>::make_cut(float qlo, float qhi, int N, int kk, uint32_t* bins, float& cut, float& top) const {
   float x[L * TPT];
 #pragma unroll
   for (int i = 0; i < L; ++i) {
@@ -80,6 +92,13 @@ __device__ __forceinline__ void calib_cut(const ET* p, float qlo, float qhi, int
   cut = -INFINITY;
   top = 0.f;
   if (r <= SMP) cut = list_cut(x, r, bins, top);
+}
+
+template <typename ET, int SPOTS>
+__device__ __forceinline__ void calib_cut(const ET* p, float qlo, float qhi, int N, int kk, uint32_t* bins, float& cut, float& top) {
+  CalibSample<ET, SPOTS> sample;
+  sample.request(p, N);
+  sample.make_cut(qlo, qhi, N, kk, bins, cut, top);
 }
 
 // Full-head scores of a slice of 256 * TPT tokens: 1-D grid of rows * 16 workgroups whose waves find an FC's cut each, and rows * nslices.
@@ -177,6 +196,75 @@ __global__ __launch_bounds__(256, 4) void calib_full_kernel(const ET* __restrict
   }
 }
 
+// What calib_kernel counts in, and the words that say that a set is there: a workgroup per row.
+__global__ __launch_bounds__(256) void calib_clear_kernel(CalibSets sets) { sets.clear<256>(blockIdx.x); }
+
+// Full-head scores of a slice of 1024 tokens (bf16), two a thread: a workgroup reads twice as much as an FC's, and a compute unit with one of them and two FCs' as much as
+// any other.
+constexpr int kSliceNT = 512, kSliceTokens = 2 * kSliceNT;
+struct CalibSlice {
+  SegLds seg[4];
+  float ql[kMaxGroup][kHeadDim];
+  float2 qs[kHeadDim / 2];
+  __align__(16) float score[kSliceTokens];
+};
+template <int PAIR_SHIFT, int PAIR_ADD>
+__device__ __forceinline__ void calib_slice(CalibSlice& sm, const uint16_t* __restrict__ q, const uint16_t* __restrict__ Kp, float* __restrict__ S,
+                                            const CalibSets& sets, int row, int slice, int G, int N, int n_cap) {
+  constexpr int D = kHeadDim, F = D / 2, NW = 16, QH = kSliceNT / D, QL = kMaxGroup / QH;
+  const int t = threadIdx.x;
+  const uint16_t* qh = q + (size_t)row * G * D + (t & (D - 1));
+  uint16_t qcol[QL];                                          // head dim t mod 128 of query heads t / 128, + QH, ...
+#pragma unroll
+  for (int j = 0; j < QL; ++j) qcol[j] = qh[(size_t)min((t >> 7) + QH * j, G - 1) * D];
+  const int n0 = slice * kSliceTokens + 2 * t;
+  const uint16_t* p = Kp + ((size_t)row * F * n_cap + (n0 < N ? n0 : 0)) * 2;
+  const size_t plane = (size_t)n_cap * 2;
+  uint2 w[NW];
+#pragma unroll
+  for (int u = 0; u < NW; ++u) w[u] = *reinterpret_cast<const uint2*>(p + (size_t)u * plane);
+#pragma unroll
+  for (int j = 0; j < QL; ++j) sm.ql[(t >> 7) + QH * j][t & (D - 1)] = __uint_as_float((uint32_t)qcol[j] << 16);
+  __syncthreads();
+  if (t < F) {   // g ascending, as everywhere
+    float lo = 0.f, hi = 0.f;
+    for (int g = 0; g < G; ++g) {
+      lo += sm.ql[g][t << PAIR_SHIFT];
+      hi += sm.ql[g][(t << PAIR_SHIFT) + PAIR_ADD];
+    }
+    sm.qs[t] = make_float2(lo, hi);
+  }
+  __syncthreads();
+  float acc[2] = {0.f, 0.f};
+  // 16 planes in flight: a plane's register takes the plane 16 further on as soon as it is used.  (Not
+  // unrolled: the compiler would put all 64 loads first, and spill.)
+#pragma unroll 1
+  for (int f0 = 0; f0 < F; f0 += NW) {
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+      const float2 qf = sm.qs[f0 + u];                        // (as fma_pairs)
+      acc[0] = fmaf(qf.y, bf16_hi(w[u].x), fmaf(qf.x, bf16_lo(w[u].x), acc[0]));
+      acc[1] = fmaf(qf.y, bf16_hi(w[u].y), fmaf(qf.x, bf16_lo(w[u].y), acc[1]));
+      w[u] = *reinterpret_cast<const uint2*>(p + (size_t)min(f0 + NW + u, F - 1) * plane);
+    }
+  }
+  float* out = S + (size_t)row * n_cap + n0;
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (n0 + k < N) st_agent(out + k, acc[k]);
+  if (sets.pitch) {
+    *reinterpret_cast<float2*>(sm.score + 2 * t) = make_float2(acc[0], acc[1]);
+    __syncthreads();
+    static_assert(kSliceTokens == 4 * kListSeg, "a segment for each of four waves");
+    const int ls = __builtin_amdgcn_readfirstlane(slice * 4 + (t >> 6));
+    if (t < kListSeg && ls * kListSeg < N) {
+      const float4 x = *reinterpret_cast<const float4*>(sm.score + 4 * t);
+      const float xs[4] = {x.x, x.y, x.z, x.w};
+      seg_list<true>(xs, min(N - ls * kListSeg, kListSeg), ls, sets.list(row), sm.seg[t >> 6]);
+    }
+  }
+}
+
 // LIST: entries of a row's list.
 template <int NT, int WORDS, int LIST>
 struct CalibLds {
@@ -184,7 +272,7 @@ struct CalibLds {
   static constexpr int kSpots = NT == 256 ? 64 : 256;         // of calib_top's sample
   using Tok = typename std::conditional<WORDS <= kCalibWords1, uint16_t, uint32_t>::type;
   union {
-    struct { uint32_t score[kList]; Tok tok[kList]; };        // what reaches the cut
+    struct { uint32_t score[kList + kWave]; Tok tok[kList + kWave]; };   // what reaches the cut; a place per lane for what does not
     struct { __align__(16) float sample[4 * kSpots]; __align__(16) uint32_t bins[256]; };
   };
   union {                                                     // (the set is made when there is nothing left to count)
@@ -199,18 +287,71 @@ struct CalibLds {
   uint32_t early[kHeadDim / 2];
 };
 
+// The K best of entries that the threads hold in registers, by one histogram of 512 bins of 2^shift keys from klo on (0: no entry; klo > 0).  win: a thread's entries above
+// the K-th's bin; those in it go to sm.cand, and `taken` tells that this thread's candidate `taken_tok` is one of the K.  The histogram is zero at the call, a barrier
+// ago, and all have used it when this returns true.  False: fewer than K entries, or too many candidates (it is zero then, a barrier ago).
+// (In a loop over a list in LDS, a test around each count and each bit, threshold and set took 4 us: three workgroups on a compute unit are bound by
+// instructions there.)
+constexpr int kCalibHeld = 8;          // entries per thread of an FC's list
+template <int EPT, typename Lds, typename Token>
+__device__ __forceinline__ bool calib_held(Lds& sm, const uint32_t (&key)[EPT], Token&& token, uint32_t klo, int shift, int kk, uint32_t& win, bool& taken,
+                                           uint32_t& taken_tok) {
+  constexpr int NT = Lds::kThreads;
+  const int t = threadIdx.x, lane = t & 63;
+  uint32_t bin[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {                             // (what is not counted: a word of the lane's own)
+    bin[k] = key[k] >= klo ? min((key[k] - klo) >> shift, (uint32_t)kListBins - 1u) : (uint32_t)(kListBins + lane);
+    atomicAdd(&sm.hist[bin[k]], 1u);
+  }
+  __syncthreads();
+  const BinAt b = wave_find_bin(sm.hist, (uint32_t)kk);
+  if (b.n == 0 || b.n > kSelCand) {
+    __syncthreads();
+    for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+    __syncthreads();
+    return false;
+  }
+  const int need = kk - b.above;
+  uint32_t act = 0;
+  win = 0;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    win |= bin[k] > (uint32_t)b.bin && bin[k] < (uint32_t)kListBins ? 1u << k : 0u;
+    act |= bin[k] == (uint32_t)b.bin ? 1u << k : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {                             // (few lanes have one)
+    if (act >> k & 1u) {
+      const uint32_t c = __builtin_amdgcn_atomic_inc32(&sm.n_cnd, 0xffffffffu, __ATOMIC_RELAXED, "workgroup");
+      sm.cand[c & (kSelCand - 1)] = make_uint2(key[k], token(k));
+    }
+  }
+  __syncthreads();
+  taken = false;
+  taken_tok = 0;
+  static_assert(NT >= kSelCand, "a thread per candidate");
+  if ((t & ~(kWave - 1)) < b.n) {                             // (the waves that have any)
+    const int rank = rank_in_list<1>(sm.cand, b.n, t);
+    taken = t < b.n && rank < need;
+    taken_tok = sm.cand[min(t, b.n - 1)].y;
+  }
+  return true;
+}
+
 // Top-K of a row by one workgroup of NT threads, which hold a stretch of it as loaded: load1(i, c0) requests piece i of what the
 // scores of tokens c0 .. c0 + NT * kCalibPerThread - 1 are made of (kCalibPerThread / TPT pieces a thread),
 // get(c0, i, t, x, full) makes those of tokens c0 + (i * NT + t) * TPT + k, a NaN beyond the row unless it is said to
 // be full (cheap: made again in every pass, which keeps 16 registers free and two workgroups of 1024 on a
 // compute unit); opaque() hides the pieces from the compiler, which would otherwise keep the scores.
-// pick(klo, ktop): the list has been made already, from elsewhere, out of all scores from klo on.  cut(top) is the cut, and a score at the upper end.  score_at(n): one token's score.  The set goes to sm.bits.
+// pick(klo, ktop): the list has been made already, from elsewhere, out of all scores from klo on.  cut(top) is the cut, and a score at the upper end.  score_at(n): one token's score.  The set goes to sm.bits; or, HELD and where the
+// threads hold the list (short ones, which a loop goes through in a round or two, gain nothing: 2 rows of 20011 19.8 -> 21.0), to held(win, tok, taken, taken_tok) (calib_held).
 // What reaches the cut is gathered into a list in LDS first (some 7 instructions a score per wave, where counting
 // and classifying all scores under a test takes 30); a list that comes out short of K or beyond its
 // room is not used.  Infinite scores rank like any others; where NaNs rank is unspecified, but the set has K tokens.
-template <int TPT, typename Lds, typename Load1, typename Get, typename Opaque, typename Pick, typename Cut, typename ScoreAt>
+template <int TPT, bool HELD, typename Lds, typename Load1, typename Get, typename Opaque, typename Pick, typename Cut, typename ScoreAt, typename Held>
 __device__ __forceinline__ void calib_select(Lds& sm, int N, int kk, Load1&& load1, Get&& get, Opaque&& opaque, Pick&& pick, Cut&& cut,
-                                             ScoreAt&& score_at) {
+                                             ScoreAt&& score_at, Held&& held) {
   const int t = threadIdx.x;
   constexpr int NT = Lds::kThreads, R = NT * kCalibPerThread, NP = kCalibPerThread / TPT;
   auto load = [&](int c0) {
@@ -258,9 +399,13 @@ __device__ __forceinline__ void calib_select(Lds& sm, int N, int kk, Load1&& loa
 #pragma unroll
         for (int k = 0; k < TPT; ++k) {
           const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], base));
-          if (x[k] >= flo && pos < (uint32_t)Lds::kList) {
-            sm.score[pos] = __float_as_uint(x[k]);
-            sm.tok[pos] = (typename Lds::Tok)(c0 + (i * NT + tt) * TPT + k);
+          // (HELD, whose workgroups share a compute unit with others that need its instruction slots: no branch, and what is not listed to a place of the lane's
+          // own: 8 rows of 32768 32.15 -> 32.0)
+          const bool in = x[k] >= flo && pos < (uint32_t)Lds::kList;
+          const uint32_t at = !HELD || in ? pos : (uint32_t)(Lds::kList + lane);
+          if (HELD || in) {
+            sm.score[at] = __float_as_uint(x[k]);
+            sm.tok[at] = (typename Lds::Tok)(c0 + (i * NT + tt) * TPT + k);
           }
           base += (uint32_t)__popcll(m[k]);
         }
@@ -275,6 +420,21 @@ __device__ __forceinline__ void calib_select(Lds& sm, int N, int kk, Load1&& loa
   }
   const int M = (int)sm.n_list;
   const bool listed = M >= kk && M <= Lds::kList;
+  if (HELD && listed && M <= kCalibHeld * NT && klo > 0u) {
+    uint32_t key[kCalibHeld], tok[kCalibHeld], win, taken_tok;
+    bool taken;
+#pragma unroll
+    for (int k = 0; k < kCalibHeld; ++k) {
+      const int i = k * NT + t, at = min(i, Lds::kList - 1);  // (beyond M: whatever it holds)
+      const uint32_t x = sm.score[at];
+      tok[k] = sm.tok[at];
+      key[k] = i < M ? score_key(__uint_as_float(x)) : 0u;
+    }
+    if (calib_held<kCalibHeld>(sm, key, [&](int k) { return tok[k]; }, klo, shift + 1, kk, win, taken, taken_tok)) {
+      held(win, tok, taken, taken_tok);
+      return;
+    }
+  }
   // Without a list: all scores of the row, told from what lies beyond it by index.  As keys throughout: a NaN score has
   // a place in the order of keys like any other.
   auto for_scores = [&](int c0, auto&& f) {
@@ -354,10 +514,74 @@ __device__ __forceinline__ void calib_select(Lds& sm, int N, int kk, Load1&& loa
   }
 }
 
-// The full head's top-K set, by one workgroup of calib_fc_kernel's launch per row, which then counts for the FCs that came first (a
+template <int EPT, typename Lds>
+__device__ __forceinline__ void calib_bits(Lds& sm, uint32_t win, const uint32_t (&tok)[EPT], bool taken, uint32_t taken_tok) {
+  __syncthreads();                                            // (the histogram has been read, and its storage is the set's)
+  for (int i = threadIdx.x; i < Lds::kWords; i += Lds::kThreads) sm.bits[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < EPT; ++k)
+    if (win >> k & 1u) set_bit(sm.bits, tok[k]);
+  if (taken) set_bit(sm.bits, taken_tok);
+}
+
+// The full head's set out of the row's lists, if the threads hold them (tried): false, where they are longer, or K of their entries don't reach the highest of their
+// completeness keys.
+template <typename Lds>
+__device__ __forceinline__ bool calib_top_listed(Lds& sm, const CalibSets& sets, int row, int N, int kk, bool& tried) {
+  constexpr int NT = Lds::kThreads, NWV = NT / kWave, Q = 4;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, per = sets.pitch / 4, nq = sets.nsegs * per;
+  if (nq == 0 || nq > Q * NT) return false;
+  tried = true;
+  const ListRow l = sets.list(row);
+  const __amdgpu_buffer_rsrc_t rk = agent_buffer(l.keys);
+  uint2 lim = make_uint2(0u, 0u);
+  for (int i = t; i < sets.nsegs; i += NT) {
+    const uint2 x = ld_agent(l.lims + i);
+    lim = make_uint2(max(lim.x, x.x), max(lim.y, x.y));
+  }
+  uint4 k4[Q];
+  uint32_t t4[Q];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) {
+    const int g = min(u * NT + t, nq - 1);
+    k4[u] = agent_load_u128(rk, (uint32_t)g * 16u);
+    t4[u] = ld_agent(l.toks + g);
+  }
+  for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
+  if (t == 0) sm.n_cnd = 0;
+  const uint32_t a = wave_max_key(lim.x), b = wave_max_key(lim.y);
+  if (lane == kWave - 1) { sm.wtot[wave] = a; sm.wtot2[wave] = b; }
+  __syncthreads();
+  uint32_t klo = 1, ktop = 0;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) { klo = max(klo, sm.wtot[w]); ktop = max(ktop, sm.wtot2[w]); }
+  uint32_t key[4 * Q];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) {
+    const bool in = u * NT + t < nq;
+    key[4 * u] = in ? k4[u].x : 0u; key[4 * u + 1] = in ? k4[u].y : 0u;
+    key[4 * u + 2] = in ? k4[u].z : 0u; key[4 * u + 3] = in ? k4[u].w : 0u;
+  }
+  const float inv_per = __builtin_amdgcn_rcpf((float)per);
+  const auto token_of = [&](int quad, uint32_t byte) {        // (quotients of at most 4096 by at most 32: exact)
+    return min((uint32_t)(((float)quad + 0.5f) * inv_per) * (uint32_t)kListSeg + (byte & 255u), (uint32_t)N - 1u);
+  };
+  const auto token = [&](int e) { return token_of((e >> 2) * NT + t, t4[e >> 2] >> (8 * (e & 3))); };
+  uint32_t win, taken_tok;
+  bool taken;
+  if (!calib_held<4 * Q>(sm, key, token, klo, list_shift(klo, ktop), kk, win, taken, taken_tok)) return false;
+  uint32_t tok[4 * Q];
+#pragma unroll
+  for (int e = 0; e < 4 * Q; ++e) tok[e] = token(e);
+  calib_bits(sm, win, tok, taken, taken_tok);
+  return true;
+}
+
+// The full head's top-K set, by the workgroup that scored the last slice of its row, which then counts for the FCs that came first (a
 // wave each).  Out of the row's lists, whose entries from the highest of their completeness keys on are all there are; if fewer than K of them are (a row's best lie
 // together), or there are none, out of all scores by the cut of a sample.
-template <typename Lds>
+template <bool SHARED, typename Lds>
 __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, const CalibSets& sets, float* CA_sum, int row, int N, int n_cap,
                                           int kk) {
   constexpr int NT = Lds::kThreads, F = kHeadDim / 2, NWV = NT / kWave;
@@ -366,14 +590,21 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
   __builtin_amdgcn_s_setprio(3);                              // (64 workgroups may end up waiting to be counted)
   constexpr int SP = Lds::kSpots, SMP = SP * 4;
   const int n_spot = (int)(((long long)(t & (SP - 1)) * N) / SP) & ~3;
-  const float4 spot = *reinterpret_cast<const float4*>(s + n_spot);   // (ahead of all that a wait for it would be one for, too)
+  const __amdgpu_buffer_rsrc_t rs = agent_buffer(s);          // (SHARED: scored and listed in this launch)
+  const auto scores = [&](int n) {
+    if constexpr (SHARED) return agent_load_u128(rs, (uint32_t)n * 4u);
+    else return *reinterpret_cast<const uint4*>(s + n);
+  };
+  const uint4 spot = scores(n_spot);      // (ahead of all that a wait for it would be one for, too)
+  bool tried = false;
   const auto pick = [&](uint32_t& klo, uint32_t& ktop) {
-    if (!sets.pitch) return false;
+    if (!sets.pitch || (SHARED && tried)) return false;
     const ListRow l = sets.list(row);
+    const __amdgpu_buffer_rsrc_t rk = agent_buffer(l.keys);
     const int per = sets.pitch / 4, nq = sets.nsegs * per;
     uint32_t a = 0, b = 0;
     for (int i = t; i < sets.nsegs; i += NT) {
-      const uint2 x = l.lims[i];
+      const uint2 x = SHARED ? ld_agent(l.lims + i) : l.lims[i];
       a = max(a, x.x);
       b = max(b, x.y);
     }
@@ -384,8 +615,9 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int g = min(g0 + u * NT + t, nq - 1);
-        k4[u] = reinterpret_cast<const uint4*>(l.keys)[g];
-        t4[u] = l.toks[g];
+        if constexpr (SHARED) k4[u] = agent_load_u128(rk, (uint32_t)g * 16u);
+        else k4[u] = reinterpret_cast<const uint4*>(l.keys)[g];
+        t4[u] = SHARED ? ld_agent(l.toks + g) : l.toks[g];
       }
     };
     request(0);
@@ -431,22 +663,22 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
     if (t == 0) sm.n_list = 0;
     return false;
   };
-  float4 w[kCalibPerThread / 4];
-  calib_select<4>(
+  uint4 w[kCalibPerThread / 4];
+  if (!SHARED || !calib_top_listed(sm, sets, row, N, kk, tried)) calib_select<4, SHARED>(
       sm, N, kk,
       [&](int i, int c0) {
         const int n = c0 + (i * NT + t) * 4;
-        w[i] = *reinterpret_cast<const float4*>(s + (n < N ? n : 0));
+        w[i] = scores(n < N ? n : 0);
       },
       [&](int c0, int i, int tt, float (&x)[4], auto full) {
         const int n = c0 + (i * NT + tt) * 4;
-        x[0] = full || n < N ? w[i].x : NAN; x[1] = full || n + 1 < N ? w[i].y : NAN;
-        x[2] = full || n + 2 < N ? w[i].z : NAN; x[3] = full || n + 3 < N ? w[i].w : NAN;
+        x[0] = full || n < N ? __uint_as_float(w[i].x) : NAN; x[1] = full || n + 1 < N ? __uint_as_float(w[i].y) : NAN;
+        x[2] = full || n + 2 < N ? __uint_as_float(w[i].z) : NAN; x[3] = full || n + 3 < N ? __uint_as_float(w[i].w) : NAN;
       },
       []() {}, pick,
       [&](float& top) {
         if (t < SP) {
-          const float x[4] = {spot.x, spot.y, spot.z, spot.w};
+          const float x[4] = {__uint_as_float(spot.x), __uint_as_float(spot.y), __uint_as_float(spot.z), __uint_as_float(spot.w)};
 #pragma unroll
           for (int k = 0; k < 4; ++k) sm.sample[k * SP + t] = n_spot + k < N ? x[k] : x[0];
         }
@@ -464,7 +696,8 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
         top = sm.cut_top.y;
         return sm.cut_top.x;
       },
-      [&](int n) { return s[n]; });
+      [&](int n) { return SHARED ? ld_agent(s + n) : s[n]; },
+      [&](uint32_t win, const auto& tok, bool taken, uint32_t taken_tok) { calib_bits(sm, win, tok, taken, taken_tok); });
   __syncthreads();
   for (int i = t; i < words; i += NT) st_agent(sets.full + (size_t)row * words + i, sm.bits[i] | kCalibThere);
   publish_barrier();
@@ -502,21 +735,30 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
 // two comes second to that word counts.
 // us, cuts made here, the FCs tested against the full head's set where it was there / like this: 8 rows of 32768, K = 2048: 39.9 / 34.9; of 16384, 1500: 29.2 / 24.8; of
 // 12000, 7 heads: 28.6 / 23.9; 4 rows of 32000, 3500: 30.6 / 28.2; 2 of 20011, 700: 21.4 / 20.0; 8 of 8192, 512: 20.6 / 18.9; of 1015: 15.5 / 14.4.
-template <typename ET, typename Lds, int WAVES>
-__global__ __launch_bounds__(Lds::kThreads, WAVES) void calib_fc_kernel(const ET* __restrict__ Kp, const float* __restrict__ S, CalibSets sets,
-                                                                       float* __restrict__ CA_sum, int rows, int N, int n_cap, int kk) {
+// OWN_CUT: made here, from a sample that the first wave asks for ahead of all else; else it and the queries' sums come from the launch before.
+template <bool OWN_CUT, int PAIR_SHIFT, int PAIR_ADD, typename ET, typename Lds>
+__device__ __forceinline__ void calib_fc(Lds& sm, const ET* __restrict__ q, const ET* __restrict__ Kp, const CalibSets& sets, float* __restrict__ CA_sum,
+                                         int row, int part, int G, int N, int n_cap, int kk) {
   constexpr int NT = Lds::kThreads, F = kHeadDim / 2, TPT = ScoreTraits<ET>::TPT;
-  __shared__ Lds sm;
   const int t = threadIdx.x, words = sets.words;
-  if ((int)blockIdx.x < rows) {
-    calib_top(sm, S, sets, CA_sum, (int)blockIdx.x, N, n_cap, kk);
-    return;
-  }
-  const int id = (int)blockIdx.x - rows, row = id / F;
+  const int id = row * F + part;
   if (t == 0) { sm.count = 0; sm.missing = 0; }
-  const float4 cq = sets.cuts[id];
-  const float qlo = cq.z, qhi = cq.w;
   const ET* p = Kp + (size_t)id * n_cap * 2;
+  ET qa[kMaxGroup], qb[kMaxGroup];
+  CalibSample<ET, Lds::kSpots> sample;
+  float4 cq = make_float4(0.f, 0.f, 0.f, 0.f);
+  if constexpr (OWN_CUT) {
+    const ET* qh = q + (size_t)row * G * kHeadDim + (part << PAIR_SHIFT);
+#pragma unroll
+    for (int g = 0; g < kMaxGroup; ++g) {
+      qa[g] = qh[(size_t)min(g, G - 1) * kHeadDim];
+      qb[g] = qh[(size_t)min(g, G - 1) * kHeadDim + PAIR_ADD];
+    }
+    if (t < kWave) sample.request(p, N);
+  } else {
+    cq = sets.cuts[id];
+  }
+  float qlo = cq.z, qhi = cq.w;
   uint4 w[kCalibPerThread / TPT];
   auto load1 = [&](int i, int c0) {
     const int n = c0 + (i * NT + t) * TPT;
@@ -545,9 +787,62 @@ __global__ __launch_bounds__(Lds::kThreads, WAVES) void calib_fc_kernel(const ET
     }
     return fmaf(qhi, hi, fmaf(qlo, lo, 0.f));
   };
-  calib_select<TPT>(sm, N, kk, load1, get, opaque, [](uint32_t&, uint32_t&) { return false; }, [&](float& top) { top = cq.y; return cq.x; }, score_at);
   const uint32_t* full = sets.full + (size_t)row * words;
-  uint32_t mine, there;
+  // The other is as long in the making, and longer where a row's best lie together, so a wave looks for it for a while: what is left here for the workgroup that makes
+  // it is counted by that alone (8 rows of 32768, an autoregression of 0.98, six looks: 50 us).
+  const auto look = [&]() {
+    if (t < kWave) {
+      int looks = kCalibLooks;
+      while (ld_agent(full + words - 1) == 0u && looks-- > 0) __builtin_amdgcn_s_sleep(8);
+    }
+  };
+  uint32_t mine = 0;
+  bool counted = false;
+  calib_select<TPT, OWN_CUT>(sm, N, kk, load1, get, opaque, [](uint32_t&, uint32_t&) { return false; }, 
+                   [&](float& top) {                          // (behind the requests for the first stretch)
+                     if constexpr (!OWN_CUT) {
+                       top = cq.y;
+                       return cq.x;
+                     }
+#pragma unroll
+                     for (int g = 0; g < kMaxGroup; ++g) {    // g ascending, as everywhere
+                       float x, y;
+                       if constexpr (sizeof(ET) == 2) { x = __uint_as_float((uint32_t)qa[g] << 16); y = __uint_as_float((uint32_t)qb[g] << 16); }
+                       else { x = qa[g]; y = qb[g]; }
+                       qlo += g < G ? x : 0.f;
+                       qhi += g < G ? y : 0.f;
+                     }
+                     if (t < kWave) {
+                       float cut, best;
+                       sample.make_cut(qlo, qhi, N, kk, sm.bins, cut, best);
+                       if (t == 0) sm.cut_top = make_float2(cut, best);
+                     }
+                     __syncthreads();
+                     top = sm.cut_top.y;
+                     return sm.cut_top.x;
+                   }, score_at,
+                   [&](uint32_t win, const auto& tok, bool taken, uint32_t taken_tok) {
+                     look();
+                     __syncthreads();                         // (all have read the histogram, whose storage the sets have)
+                     uint32_t seen = kCalibThere;
+                     for (int i = t; i < words; i += NT) {
+                       const uint32_t x = ld_agent(full + i);
+                       seen &= x;
+                       sm.bits[i] = x;
+                     }
+                     if (seen == 0) sm.missing = 1;
+                     __syncthreads();
+                     if (sm.missing) {
+                       calib_bits(sm, win, tok, taken, taken_tok);
+                       return;
+                     }
+                     const auto in = [&](uint32_t n) { return sm.bits[n / 31u] >> (n % 31u) & 1u; };
+                     mine = taken ? in(taken_tok) : 0u;
+#pragma unroll
+                     for (int k = 0; k < kCalibHeld; ++k) mine += (win >> k & 1u) & in(win >> k & 1u ? tok[k] : 0u);
+                     counted = true;
+                   });
+  uint32_t there;
   const auto meet = [&]() {
     there = kCalibThere;
     mine = 0;
@@ -557,28 +852,69 @@ __global__ __launch_bounds__(Lds::kThreads, WAVES) void calib_fc_kernel(const ET
       mine += (uint32_t)__popc(x & sm.bits[i]);
     }
   };
-  // The other is as long in the making, and longer where a row's best lie together, so a wave looks for it for a while: what is left here for the workgroup that makes
-  // it is counted by that alone (8 rows of 32768, an autoregression of 0.98, six looks: 50 us).
-  if (t < kWave) {
-    int looks = kCalibLooks;
-    while (ld_agent(full + words - 1) == 0u && looks-- > 0) __builtin_amdgcn_s_sleep(8);
-  }
-  __syncthreads();
-  meet();
-  if (there == 0) sm.missing = 1;
-  __syncthreads();
-  if (sm.missing) {
-    for (int i = t; i < words; i += NT) st_agent(sets.fc + (size_t)id * words + i, sm.bits[i]);
-    publish_barrier();
-    if (t == 0) sm.missing = atomicExch(&sets.state[id], 1u);
+  if (!counted) {
     __syncthreads();
-    if (sm.missing != 2u) return;                             // (counted by whoever publishes the full head's)
+    look();
+    __syncthreads();
     meet();
+    if (there == 0) sm.missing = 1;
+    __syncthreads();
+    if (sm.missing) {
+      for (int i = t; i < words; i += NT) st_agent(sets.fc + (size_t)id * words + i, sm.bits[i]);
+      publish_barrier();
+      if (t == 0) sm.missing = atomicExch(&sets.state[id], 1u);
+      __syncthreads();
+      if (sm.missing != 2u) return;                           // (counted by whoever publishes the full head's)
+      meet();
+    }
   }
   mine = wave_prefix_sum(mine);
   if (lane_id() == kWave - 1) atomicAdd(&sm.count, mine);
   __syncthreads();
   if (t == 0) CA_sum[id] += (float)sm.count / (float)kk;
+}
+
+template <typename ET, typename Lds, int WAVES>
+__global__ __launch_bounds__(Lds::kThreads, WAVES) void calib_fc_kernel(const ET* __restrict__ Kp, const float* __restrict__ S, CalibSets sets,
+                                                                       float* __restrict__ CA_sum, int rows, int N, int n_cap, int kk) {
+  constexpr int F = kHeadDim / 2;
+  __shared__ Lds sm;
+  if ((int)blockIdx.x < rows) {
+    calib_top<false>(sm, S, sets, CA_sum, (int)blockIdx.x, N, n_cap, kk);
+    return;
+  }
+  const int id = (int)blockIdx.x - rows;
+  calib_fc<false, 0, 0, ET>(sm, (const ET*)nullptr, Kp, sets, CA_sum, id / F, id % F, 1, N, n_cap, kk);
+}
+
+// All in one launch: the first rows * nslices workgroups score the full head, and the last of a row finds its set; one per (row, FC).  The keys are asked for twice at
+// about the same time, by workgroups that share a compute unit, and a row's set is found under the FCs' streams.
+using CalibRowLds = CalibLds<kSliceNT, kCalibWords1, 7680>;
+template <int PAIR_SHIFT, int PAIR_ADD>
+__global__ __launch_bounds__(kSliceNT, 6) void calib_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ Kp, float* __restrict__ S,
+                                                            CalibSets sets, float* __restrict__ CA_sum, int rows, int nslices, uint32_t m_slices, int G,
+                                                            int N, int n_cap, int kk) {
+  constexpr int F = kHeadDim / 2;
+  __shared__ union Lds {
+    __device__ Lds() {}
+    CalibRowLds row;
+    CalibSlice slice;
+  } sm;
+  __shared__ uint32_t ticket;
+  const int n_full = rows * nslices;
+  int row, part;
+  if ((int)blockIdx.x < n_full) {
+    row_slice_of_block(rows, nslices, m_slices, row, part);
+    calib_slice<PAIR_SHIFT, PAIR_ADD>(sm.slice, q, Kp, S, sets, row, part, G, N, n_cap);
+    publish_barrier();
+    if (threadIdx.x == 0) ticket = atomicAdd(&sets.tickets[row], 1u);
+    __syncthreads();
+    if (ticket == (uint32_t)nslices - 1u) calib_top<true>(sm.row, S, sets, CA_sum, row, N, n_cap, kk);
+    return;
+  }
+  constexpr uint32_t m_fcs = div_magic(F, 65535 * F);
+  row_slice_of_block(rows, F, m_fcs, row, part, blockIdx.x - (unsigned)n_full);
+  calib_fc<true, PAIR_SHIFT, PAIR_ADD, uint16_t>(sm.row, q, Kp, sets, CA_sum, row, part, G, N, n_cap, kk);
 }
 
 // K >= N: both sets are all tokens
@@ -591,6 +927,20 @@ template <typename ET, int PS, int PA>
 static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, const CalibSets& sets,
                                  float* CA_sum, hipStream_t st) {
   const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2;
+  // One launch for all (behind one that clears) where that is the faster: bf16, 8 rows or more, of 8193 .. 32768 tokens.  us, two launches / so: 8 rows of 32768, K = 2048:
+  // 35.4 / 31.2; 1 head, 4000: 38.7 / 34.5; of 16384, 1500: 25.2 / 21.7; of 12000: 24.5 / 21.4; 32 rows of 16384: 68.1 / 64.6; rows whose best lie together (rising; neighbours
+  // alike): 8 of 32768 38.4 / 35.1, 39.0 / 36.0, of 12000 25.6 / 24.3, 25.7 / 24.0; thousands of ties 78.5 / 75.9, 37.8 / 39.0.  On the other side fewer rows, which have
+  // workgroups of 1024: 4 of 32000: 29.2 / 26.5, of 20000: 25.2 / 23.1, but rising 26.9 / 29.9; 2 of 20011: 19.9 / 20.5; 8 of 1015: 14.6 / 15.9, of 5000: 18.1 / 17.6; 4 of 3000:
+  // 15.3 / 16.9; 8 of 131072: 124 / 131; float32, 8 of 20000: 41.1 / 43.7, of 6000: 19.6 / 17.4.
+  if constexpr (sizeof(ET) == 2) {
+    if (s.n_ctx > kCalibShort && s.n_ctx <= 32768 && rows >= 8) {
+      const hipError_t e = launch("fasa_calib_clear", calib_clear_kernel, dim3(rows), dim3(256), st, sets);
+      if (e != hipSuccess) return e;
+      const int nslices = (s.n_ctx + kSliceTokens - 1) / kSliceTokens;
+      return launch("fasa_calib", calib_kernel<PS, PA>, dim3(rows * (nslices + half)), dim3(kSliceNT), st, (const ET*)q, (const ET*)Kp_all, S, sets, CA_sum, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_q_heads / s.n_kv_heads, s.n_ctx,
+                    s.n_cap, kk);
+    }
+  }
   const int per = 256 * ScoreTraits<ET>::TPT, nslices = (s.n_ctx + per - 1) / per;
   hipError_t e = launch("fasa_calib_full", calib_full_kernel<ET, PS, PA>, dim3(rows * (half / 4 + nslices)), dim3(256), st, (const ET*)q,
                         (const ET*)Kp_all, S, sets, rows, nslices, div_magic(nslices, (long long)rows * nslices),
@@ -609,11 +959,11 @@ static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void*
   return stage(calib_fc_kernel<ET, CalibLds<512, kCalibWords1, 7680>, H ? 6 : 4>, 512);
 }
 
-// Cuts, lists (5 bytes a place), what describes their segments, states, sets.
+// Cuts, lists (5 bytes a place), what describes their segments, states, tickets, sets.
 static size_t calib_list_segs(int n) { return ((size_t)n + kListSeg - 1) / kListSeg; }
 size_t calib_scratch_bytes(int rows, int n_cap) {
   const size_t half = kHeadDim / 2, lists = calib_list_segs(n_cap) * (kListSeg * 5 + sizeof(uint2)) + 16;
-  return rows * (half * (sizeof(float4) + sizeof(uint32_t)) + lists + (1 + half) * (((size_t)n_cap + 30) / 31) * sizeof(uint32_t));
+  return rows * (half * (sizeof(float4) + sizeof(uint32_t)) + sizeof(uint32_t) + lists + (1 + half) * (((size_t)n_cap + 30) / 31) * sizeof(uint32_t));
 }
 
 hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, void* scratch, float* CA_sum,
@@ -621,14 +971,15 @@ hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, 
   const size_t rows = (size_t)s.batch * s.n_kv_heads;
   CalibSets sets;
   sets.words = (s.n_ctx + 30) / 31;
-  sets.cuts = (float4*)scratch;
   sets.nsegs = (int)calib_list_segs(s.n_ctx);
   sets.pitch = s.dtype == FASA_BF16 ? list_room(kk, s.n_ctx) : 0;
   if (sets.pitch > kListSeg / 2 || s.n_ctx <= kCalibShort) sets.pitch = 0;   // (half of the row, or a row that is read as fast)
+  sets.cuts = (float4*)scratch;
   sets.lists = (uint32_t*)(sets.cuts + rows * (kHeadDim / 2));
   sets.lims = (uint2*)(sets.lists + rows * sets.list_words());
   sets.state = (uint32_t*)(sets.lims + rows * sets.nsegs);
-  sets.full = sets.state + rows * (kHeadDim / 2);
+  sets.tickets = sets.state + rows * (kHeadDim / 2);
+  sets.full = sets.tickets + rows;
   sets.fc = sets.full + rows * sets.words;
   constexpr int D = kHeadDim;
   if (kk >= s.n_ctx) {
