@@ -937,7 +937,7 @@ static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void*
       const hipError_t e = launch("fasa_calib_clear", calib_clear_kernel, dim3(rows), dim3(256), st, sets);
       if (e != hipSuccess) return e;
       const int nslices = (s.n_ctx + kSliceTokens - 1) / kSliceTokens;
-      return launch("fasa_calib", calib_kernel<PS, PA>, dim3(rows * (nslices + half)), dim3(kSliceNT), st, (const ET*)q, (const ET*)Kp_all, S, sets, CA_sum, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_q_heads / s.n_kv_heads, s.n_ctx,
+      return launch("fasa_calib_fc", calib_kernel<PS, PA>, dim3(rows * (nslices + half)), dim3(kSliceNT), st, (const ET*)q, (const ET*)Kp_all, S, sets, CA_sum, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_q_heads / s.n_kv_heads, s.n_ctx,
                     s.n_cap, kk);
     }
   }

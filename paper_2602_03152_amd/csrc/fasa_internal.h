@@ -155,8 +155,8 @@ hipError_t profile_events(const char* name, hipEvent_t* start, hipEvent_t* stop)
 void set_last_hip_error(hipError_t e);
 
 template <typename... KArgs, typename... Args>
-inline hipError_t launch(const char* name, void (*kernel)(KArgs...), dim3 grid, dim3 block,
-                         hipStream_t stream, Args&&... args) {
+inline hipError_t launch_lds(const char* name, void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds,
+                             hipStream_t stream, Args&&... args) {
   static_assert(sizeof...(KArgs) == sizeof...(Args), "kernel argument count");
   std::tuple<KArgs...> vals{static_cast<KArgs>(std::forward<Args>(args))...};
   void* ptrs[sizeof...(KArgs) ? sizeof...(KArgs) : 1];
@@ -166,12 +166,16 @@ inline hipError_t launch(const char* name, void (*kernel)(KArgs...), dim3 grid, 
     hipEvent_t a = nullptr, b = nullptr;
     e = profile_events(name, &a, &b);
     if (e == hipSuccess)
-      e = hipExtLaunchKernel((const void*)kernel, grid, block, ptrs, 0, stream, a, b, 0);
+      e = hipExtLaunchKernel((const void*)kernel, grid, block, ptrs, lds, stream, a, b, 0);
   } else {
-    e = hipLaunchKernel((const void*)kernel, grid, block, ptrs, 0, stream);
+    e = hipLaunchKernel((const void*)kernel, grid, block, ptrs, lds, stream);
   }
   if (e != hipSuccess) set_last_hip_error(e);
   return e;
+}
+template <typename... KArgs, typename... Args>
+inline hipError_t launch(const char* name, void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t stream, Args&&... args) {
+  return launch_lds(name, kernel, grid, block, 0, stream, std::forward<Args>(args)...);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -592,7 +592,12 @@ static hipError_t launch_score_list_v(const fasa_shape& s, const void* q, void* 
   // (Sequences of their own lengths: half of the bounds or so is there.  Paged, 16 of 4031 - 16127 tokens, 98 MB of 157: 29.4 / 29.8 us)
   const bool stream = step_bytes(s) >= (rl.n_ctx ? 2 : 1) * kStreamBytes;
   const auto kernel = stream ? score_list_kernel<ET, NB, APPEND, PAIR, true> : score_list_kernel<ET, NB, APPEND, PAIR, false>;
-  return launch("fasa_score_list", kernel, dim3(rows * nslices), dim3(kListScoreNT), st,
+  // Six workgroups share a compute unit where eight would fit, by LDS that nothing uses: sequences of their own lengths, whose workgroups beyond a row's end go at
+  // once, then come in more and smaller rounds.  us, eight / six / five: paged, 16 sequences of 4031 - 16127, B = 252: 29.3 / 28.45 / 28.7; 8 of 8226 - 32905, 2000: 37.0 / 35.5 /
+  // 35.5; 16 of 4000 - 16000, F = 8, 600: 25.8 / 25.1 / 25.6; of 2000 - 8000: 19.8 / 19.8 / 19.8; rows of one length within 0.1 (64 of 16384, 32 of 32768, 96 of 12001),
+  // streamed ones too, 128 of 16384 34.0 / 34.0 / 34.2.
+  const size_t lds = stream ? 0 : 18 * 1024;
+  return launch_lds("fasa_score_list", kernel, dim3(rows * nslices), dim3(kListScoreNT), lds, st,
                 (const ET*)q, (ET*)Kp, fc_idx, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_kv_heads,
                 div_magic(s.n_kv_heads, rows), s.n_q_heads / s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, S, (const ET*)ap.k_new,
                 (const ET*)ap.v_new, (ET*)ap.K, (ET*)ap.V, (long long)s.kv_stride_b, (long long)s.kv_stride_h,

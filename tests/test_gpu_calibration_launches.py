@@ -33,5 +33,5 @@ def test_counts_exact(fb, n_ctx, batch, heads, top_k, rise):  # noqa: F811
         fb.fasa_profile_enable(False)
         fb.fasa_profile_reset()
     one = 8192 < n_ctx <= 32768 and batch * heads[1] >= 8
-    assert ("fasa_calib" in names) == one and ("fasa_calib_fc" in names) != one, names
+    assert ("fasa_calib_clear" in names) == one and ("fasa_calib_full" in names) != one, names
     np.testing.assert_array_equal(np.rint(got * top_k).astype(int), _exact_counts(fb, w, x, queries, top_k))
