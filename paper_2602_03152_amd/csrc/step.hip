@@ -119,8 +119,7 @@ __device__ __forceinline__ bool select_list(Lds& sm, int M, uint32_t kcut, uint3
 template <typename Lds>
 __device__ __forceinline__ void select_row(Lds& sm, int M, uint32_t kcut, uint32_t ktop, int bsel, const float* srow, int N) {
   if (M >= bsel && M <= Lds::kList) {
-    // Instances for short lists, which nearly all are: 1 row of 4096, B = 256, float32: 13.0 -> 12.6 us, 8 rows of 1531, B = 192:
-    // 11.55 -> 11.28, 128 rows of 16384, 4 heads, B = 256, float32: 70.6 -> 69.7
+    // (Instances for short lists, which nearly all are: 128 float32 rows of 16384, 4 heads, B = 256: 70.6 -> 69.7 us)
     const bool ok = M <= 2 * Lds::kThreads ? select_list<2>(sm, M, kcut, ktop, bsel, srow, N)
                     : M <= 4 * Lds::kThreads ? select_list<4>(sm, M, kcut, ktop, bsel, srow, N)
                                              : select_list<kListPerThread>(sm, M, kcut, ktop, bsel, srow, N);
@@ -386,13 +385,11 @@ __device__ __forceinline__ void write_output(const StepArgs& a, const Lds& sm, i
 }
 
 // The list of a row whose scores the caller's threads hold in registers: score(k), k < NV, of token
-// token(k, c0) (a NaN where the row has ended).  WHOLE: they hold the whole row, c0 is 0.  Else with more than
-// `resident` tokens in the row they hold one stretch of it at a time, and reload(c0) brings in the stretch that
-// starts at c0.  (A loop that never comes round costs the one-launch step 0.3 - 0.5 us: 8 rows of 6000 tokens, B = 250,
-// 14.85 us with it, 14.53 without.)
+// token(k, c0) (a NaN where the row has ended).  With more than `resident` tokens in the row they hold one stretch of it at a time, c0 its
+// first token, and reload(c0) brings it in.
 // 128 scores of the row, evenly spaced (`sval` of thread i < 128), are ranked; the sample_rank-th best is the cut.
 // Returns the list's length; kcut, ktop: keys of the cut (0: none) and of the sample's best.
-template <int NV, bool WHOLE, typename Lds, typename Score, typename Token, typename Reload>
+template <int NV, typename Lds, typename Score, typename Token, typename Reload>
 __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, int resident, Score&& score, Token&& token,
                                          Reload&& reload, uint32_t& kcut, uint32_t& ktop) {
   constexpr int NT = Lds::kThreads;
@@ -423,8 +420,7 @@ __device__ __forceinline__ int make_list(Lds& sm, int N, int bsel, float sval, i
       base += (uint32_t)__popcll(m[k]);
     }
   };
-  if constexpr (WHOLE) stretch(0);
-  else for (int c0 = 0; c0 < N; c0 += resident) {
+  for (int c0 = 0; c0 < N; c0 += resident) {
     if (N > resident) reload(c0);
     stretch(c0);
   }
@@ -662,7 +658,7 @@ __global__ __launch_bounds__(kRowNT) void row_kernel(const StepArgs a) {
   constexpr int R = CH * kRowNT * 4;
   if (N <= R) load_scores(0);
   uint32_t kcut, ktop;
-  const int M = make_list<4 * CH, false>(sm, N, bsel, sval, R, [&](int k) { return v[k]; },
+  const int M = make_list<4 * CH>(sm, N, bsel, sval, R, [&](int k) { return v[k]; },
                                          [&](int k, int c0) { return c0 + ((k >> 2) * kRowNT + t) * 4 + (k & 3); }, load_scores, kcut, ktop);
   select_row(sm, M, kcut, ktop, bsel, srow, N);
   row_attend<ET, GM>(a, sm, row, b, h, G, bsel, -1);
