@@ -42,26 +42,26 @@ LLC_BYTES = 256 << 20         # last-level (memory-side) cache the rotation has 
 # what the same counters read for a plain copy kernel of known size (see profiles/).  Keyed by
 # (workload config id, kernel name); bytes per launch.  None = not measured yet.
 MEASURED_TRAFFIC = {
-    "source_hash": "75f65e51b8ac122a",   # source_hash() of the kernels the counters were taken on
+    "source_hash": "ebb8bf517c5d2b28",   # source_hash() of the kernels the counters were taken on
     # profiles/decode_step_tiny_1head_f32_n4096_hbm_counters.txt  (read + written)
-    (0, "fasa_dense_attend"): 4330064 + 39456,
-    (0, "fasa_step"): 870696 + 18080,
+    (0, "fasa_dense_attend"): 4336550 + 39456,
+    (0, "fasa_step"): 869640 + 18080,
     # profiles/decode_step_llama3_8b_layer_n32768_b2048_hbm_counters.txt  (read + written)
-    (1, "fasa_dense_attend"): 134884795 + 1089792,
-    (1, "fasa_list"): 9487677 + 1155588,
-    (1, "fasa_score_list"): 16905472 + 1261568,
+    (1, "fasa_dense_attend"): 134899038 + 1089792,
+    (1, "fasa_list"): 9479740 + 1155595,
+    (1, "fasa_score_list"): 16899442 + 1261568,
     # profiles/decode_step_batch16_n16384_b256_hbm_counters.txt  (read + written)
-    (2, "fasa_dense_attend"): 1074436886 + 1339392,
-    (2, "fasa_list"): 18063306 + 397313,
-    (2, "fasa_score_list"): 134456323 + 9293633,
+    (2, "fasa_dense_attend"): 1087399519 + 1339392,
+    (2, "fasa_list"): 18045302 + 397313,
+    (2, "fasa_score_list"): 134457423 + 9274011,
     # profiles/decode_step_longcot_batch8_gqa7_n32768_hbm_counters.txt  (read + written)
-    (3, "fasa_dense_attend"): 537976403 + 1997824,
-    (3, "fasa_list"): 104586186 + 2798330,
-    (3, "fasa_score_list"): 67280609 + 5947572,
+    (3, "fasa_dense_attend"): 546143531 + 1997824,
+    (3, "fasa_list"): 104594291 + 2794753,
+    (3, "fasa_score_list"): 67281583 + 5947401,
     # profiles/decode_step_verylong_n131072_f32fc_b1024_hbm_counters.txt  (read + written)
-    (4, "fasa_dense_attend"): 537493365 + 1089792,
-    (4, "fasa_list"): 5093027 + 586240,
-    (4, "fasa_score_list"): 134359675 + 4474603,
+    (4, "fasa_dense_attend"): 543608555 + 1089792,
+    (4, "fasa_list"): 5084103 + 586240,
+    (4, "fasa_score_list"): 134360505 + 4473564,
 }
 
 
