@@ -42,7 +42,7 @@ LLC_BYTES = 256 << 20         # last-level (memory-side) cache the rotation has 
 # what the same counters read for a plain copy kernel of known size (see profiles/).  Keyed by
 # (workload config id, kernel name); bytes per launch.  None = not measured yet.
 MEASURED_TRAFFIC = {
-    "source_hash": "ebb8bf517c5d2b28",   # source_hash() of the kernels the counters were taken on
+    "source_hash": "cbc1252ab5846d4b",   # source_hash() of the kernels the counters were taken on
     # profiles/decode_step_tiny_1head_f32_n4096_hbm_counters.txt  (read + written)
     (0, "fasa_dense_attend"): 4336550 + 39456,
     (0, "fasa_step"): 869640 + 18080,

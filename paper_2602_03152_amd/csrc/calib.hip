@@ -729,12 +729,12 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
   }
 }
 
-// One workgroup per (row, FC): CA_sum[row][i] += |top-K of FC i's scores & the full head's| / K.  The first `rows` workgroups find
-// the full head's set meanwhile, which an FC needs at its end only.  Nobody waits: an FC makes its own set and compares the two at
-// its end; if the other is not there even then it leaves its own in memory, says so in its state word, and whoever of the
+// A (row, FC), by a workgroup: CA_sum[row][i] += |top-K of FC i's scores & the full head's| / K.  Another workgroup finds the full head's set meanwhile, which an FC needs at
+// its end only.  It looks for it for a bounded while; if it is not there even then the FC leaves its own set in memory, says so in its state word, and whoever of the
 // two comes second to that word counts.
-// us, cuts made here, the FCs tested against the full head's set where it was there / like this: 8 rows of 32768, K = 2048: 39.9 / 34.9; of 16384, 1500: 29.2 / 24.8; of
-// 12000, 7 heads: 28.6 / 23.9; 4 rows of 32000, 3500: 30.6 / 28.2; 2 of 20011, 700: 21.4 / 20.0; 8 of 8192, 512: 20.6 / 18.9; of 1015: 15.5 / 14.4.
+// us, in two launches, cuts made here and the FCs tested against the full head's set where it was there / cuts made in the launch before, with a look for a while: 8 rows of 32768,
+// K = 2048: 39.9 / 34.9; of 16384, 1500: 29.2 / 24.8; of 12000, 7 heads: 28.6 / 23.9; 4 rows of 32000, 3500: 30.6 / 28.2; 2 of 20011, 700: 21.4 / 20.0; 8 of 8192, 512: 20.6 /
+// 18.9; of 1015: 15.5 / 14.4.  In one launch there is none before that could make cuts at no cost: 8 rows of 32768 with a launch for them 32.0, made here 31.25.
 // OWN_CUT: made here, from a sample that the first wave asks for ahead of all else; else it and the queries' sums come from the launch before.
 template <bool OWN_CUT, int PAIR_SHIFT, int PAIR_ADD, typename ET, typename Lds>
 __device__ __forceinline__ void calib_fc(Lds& sm, const ET* __restrict__ q, const ET* __restrict__ Kp, const CalibSets& sets, float* __restrict__ CA_sum,
