@@ -53,7 +53,7 @@ struct CalibSets {
   }
 };
 constexpr uint32_t kCalibThere = 0x80000000u;
-constexpr int kCalibLooks = 32;        // for the full head's set, some 25 us
+constexpr int kCalibLooks = 64;        // for the full head's set, some 50 us
 __device__ __forceinline__ void set_bit(uint32_t* bits, uint32_t tok) { atomicOr(&bits[tok / 31u], 1u << (tok % 31u)); }
 
 // The cut of an FC's list, by a wave: of 1024 scores (float32: 512; a fourth of that for rows that one workgroup of 256 holds), four (two) neighbours at each of
@@ -789,15 +789,17 @@ __device__ __forceinline__ void calib_fc(Lds& sm, const ET* __restrict__ q, cons
   };
   const uint32_t* full = sets.full + (size_t)row * words;
   // The other is as long in the making, and longer where a row's best lie together, so a wave looks for it for a while: what is left here for the workgroup that makes
-  // it is counted by that alone (8 rows of 32768, an autoregression of 0.98, six looks: 50 us).
+  // it is counted by that alone.  us, 32 looks / 64: 8 rows of 32768 whose best lie together (rising; neighbours alike) 37.3 / 34.35, 36.3 / 34.75, of 12000 25.95 / 23.85, 25.5 /
+  // 23.6; 128 looks as 64 (an autoregression of 0.98, six looks: 50).
   const auto look = [&]() {
     if (t < kWave) {
       int looks = kCalibLooks;
       while (ld_agent(full + words - 1) == 0u && looks-- > 0) __builtin_amdgcn_s_sleep(8);
     }
   };
-  uint32_t mine = 0;
-  bool counted = false;
+  // What the threads hold of the FC's set, if they do (calib_held)
+  uint32_t win = 0, tok[kCalibHeld], taken_tok = 0;
+  bool holds = false, taken = false;
   calib_select<TPT, OWN_CUT>(sm, N, kk, load1, get, opaque, [](uint32_t&, uint32_t&) { return false; }, 
                    [&](float& top) {                          // (behind the requests for the first stretch)
                      if constexpr (!OWN_CUT) {
@@ -821,28 +823,17 @@ __device__ __forceinline__ void calib_fc(Lds& sm, const ET* __restrict__ q, cons
                      top = sm.cut_top.y;
                      return sm.cut_top.x;
                    }, score_at,
-                   [&](uint32_t win, const auto& tok, bool taken, uint32_t taken_tok) {
-                     look();
-                     __syncthreads();                         // (all have read the histogram, whose storage the sets have)
-                     uint32_t seen = kCalibThere;
-                     for (int i = t; i < words; i += NT) {
-                       const uint32_t x = ld_agent(full + i);
-                       seen &= x;
-                       sm.bits[i] = x;
-                     }
-                     if (seen == 0) sm.missing = 1;
-                     __syncthreads();
-                     if (sm.missing) {
-                       calib_bits(sm, win, tok, taken, taken_tok);
-                       return;
-                     }
-                     const auto in = [&](uint32_t n) { return sm.bits[n / 31u] >> (n % 31u) & 1u; };
-                     mine = taken ? in(taken_tok) : 0u;
+                   [&](uint32_t w, const auto& toks, bool cand, uint32_t cand_tok) {
+                     holds = true;
+                     win = w;
+                     taken = cand;
+                     taken_tok = cand_tok;
 #pragma unroll
-                     for (int k = 0; k < kCalibHeld; ++k) mine += (win >> k & 1u) & in(win >> k & 1u ? tok[k] : 0u);
-                     counted = true;
+                     for (int k = 0; k < kCalibHeld; ++k) tok[k] = toks[k];
                    });
-  uint32_t there;
+  look();                                                     // (the only time: what is not there by then is met through the state word)
+  __syncthreads();                                            // (all have made their part of the set, or read the histogram, whose storage the sets have)
+  uint32_t mine = 0, there = kCalibThere;
   const auto meet = [&]() {
     there = kCalibThere;
     mine = 0;
@@ -852,21 +843,33 @@ __device__ __forceinline__ void calib_fc(Lds& sm, const ET* __restrict__ q, cons
       mine += (uint32_t)__popc(x & sm.bits[i]);
     }
   };
-  if (!counted) {
-    __syncthreads();
-    look();
-    __syncthreads();
-    meet();
-    if (there == 0) sm.missing = 1;
-    __syncthreads();
-    if (sm.missing) {
-      for (int i = t; i < words; i += NT) st_agent(sets.fc + (size_t)id * words + i, sm.bits[i]);
-      publish_barrier();
-      if (t == 0) sm.missing = atomicExch(&sets.state[id], 1u);
-      __syncthreads();
-      if (sm.missing != 2u) return;                           // (counted by whoever publishes the full head's)
-      meet();
+  if (holds) {
+    for (int i = t; i < words; i += NT) {
+      const uint32_t x = ld_agent(full + i);
+      there &= x;
+      sm.bits[i] = x;
     }
+  } else {
+    meet();
+  }
+  if (there == 0) sm.missing = 1;
+  __syncthreads();
+  if (sm.missing) {
+    if (holds) {
+      calib_bits(sm, win, tok, taken, taken_tok);
+      __syncthreads();
+    }
+    for (int i = t; i < words; i += NT) st_agent(sets.fc + (size_t)id * words + i, sm.bits[i]);
+    publish_barrier();
+    if (t == 0) sm.missing = atomicExch(&sets.state[id], 1u);
+    __syncthreads();
+    if (sm.missing != 2u) return;                             // (counted by whoever publishes the full head's)
+    meet();
+  } else if (holds) {
+    const auto in = [&](uint32_t n) { return sm.bits[n / 31u] >> (n % 31u) & 1u; };
+    mine = taken ? in(taken_tok) : 0u;
+#pragma unroll
+    for (int k = 0; k < kCalibHeld; ++k) mine += (win >> k & 1u) & in(win >> k & 1u ? tok[k] : 0u);
   }
   mine = wave_prefix_sum(mine);
   if (lane_id() == kWave - 1) atomicAdd(&sm.count, mine);
