@@ -36,7 +36,7 @@ struct CalibSets {
   uint32_t* tickets;   // [row]: workgroups that have scored their slices of the full head
   int words;           // ceil(N / 31)
   float4* cuts;        // [row][FC]: the cut of the FC's list, the largest of the scores it is from, the sums of the queries' two components
-  // The full head's largest scores by segments (row_list.h); pitch 0: none (float32, or where they would be half of the row)
+  // The full head's largest scores by segments (row_list.h); pitch 0: none (launch_calib)
   uint32_t* lists;
   uint2* lims;
   int pitch, nsegs;
@@ -598,13 +598,16 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
   const uint4 spot = scores(n_spot);      // (ahead of all that a wait for it would be one for, too)
   bool tried = false;
   const auto pick = [&](uint32_t& klo, uint32_t& ktop) {
+    if constexpr (!SHARED && Lds::kWords <= kCalibWords1) return false;   // (no lists: launch_calib)
     if (!sets.pitch || (SHARED && tried)) return false;
     const ListRow l = sets.list(row);
     const __amdgpu_buffer_rsrc_t rk = agent_buffer(l.keys);
     const int per = sets.pitch / 4, nq = sets.nsegs * per;
+    uint2 x = make_uint2(0u, 0u);                             // of this thread's segment
+    static_assert(NT * kListSeg >= (Lds::kWords - 1) * 31, "one at most");
     uint32_t a = 0, b = 0;
     for (int i = t; i < sets.nsegs; i += NT) {
-      const uint2 x = SHARED ? ld_agent(l.lims + i) : l.lims[i];
+      x = SHARED ? ld_agent(l.lims + i) : l.lims[i];
       a = max(a, x.x);
       b = max(b, x.y);
     }
@@ -629,6 +632,22 @@ __device__ __forceinline__ void calib_top(Lds& sm, const float* __restrict__ S, 
     ktop = 0;
 #pragma unroll
     for (int w = 0; w < NWV; ++w) { klo = max(klo, sm.wtot[w]); ktop = max(ktop, sm.wtot2[w]); }
+    if constexpr (!SHARED) {
+      // Where a row's best lie together hardly a segment's list reaches the highest of the keys.  How many entries do is told by what is here already, as if
+      // a segment had fewer scores by the same factor for every step up from its cut, where it has `pitch`, to its largest.  us, lists read all the same / like this: 4 rows of 70000,
+      // K = 3000, rising 56.3 / 54.1, neighbours alike 57.0 / 55.0, independent 47.2 / 47.3 (no lists: 51.5, 52.4, 52.0); 8 of 131072, 4096: 137.4 / 135.8, 184.1 / 182.3, 124.4 /
+      // 124.3 (133.8, 179.6, 133.1); 1 of 33000, 1000: 25.1 / 24.2, 25.2 / 24.4, 22.1 / 22.1 (21.65, 21.9, 21.65).
+      const float xk = key_score(klo), xc = key_score(x.x), xt = key_score(x.y);
+      const float n = t < sets.nsegs && xt > xk ? exp2f(__log2f((float)sets.pitch) * (xt - xk) * __builtin_amdgcn_rcpf(xt - xc)) : 0.f;
+      const uint32_t e = wave_prefix_sum((uint32_t)(16.f * n));
+      __syncthreads();                                        // (all have read the keys)
+      if (lane == kWave - 1) sm.wtot[wave] = e;
+      __syncthreads();
+      uint32_t reach = 0;
+#pragma unroll
+      for (int w = 0; w < NWV; ++w) reach += sm.wtot[w];
+      if (reach < 16u * (uint32_t)kk) return false;
+    }
     for (int g0 = 0; g0 < nq; g0 += U * NT) {
       if (g0) request(g0);
 #pragma unroll
@@ -926,17 +945,21 @@ __global__ __launch_bounds__(256) void calib_all_kernel(float* __restrict__ CA_s
   if (i < n) CA_sum[i] += 1.0f;
 }
 
+// One launch for all (behind one that clears) where that is the faster: bf16, 8 rows or more, of 8193 .. 32768 tokens.  us, two launches / so: 8 rows of 32768, K = 2048:
+// 35.4 / 31.2; 1 head, 4000: 38.7 / 34.5; of 16384, 1500: 25.2 / 21.7; of 12000: 24.5 / 21.4; 32 rows of 16384: 68.1 / 64.6; rows whose best lie together (rising; neighbours
+// alike): 8 of 32768 38.4 / 35.1, 39.0 / 36.0, of 12000 25.6 / 24.3, 25.7 / 24.0; thousands of ties 78.5 / 75.9, 37.8 / 39.0.  On the other side fewer rows, which have
+// workgroups of 1024: 4 of 32000: 29.2 / 26.5, of 20000: 25.2 / 23.1, but rising 26.9 / 29.9; 2 of 20011: 19.9 / 20.5; 8 of 1015: 14.6 / 15.9, of 5000: 18.1 / 17.6; 4 of 3000:
+// 15.3 / 16.9; 8 of 131072: 124 / 131; float32, 8 of 20000: 41.1 / 43.7, of 6000: 19.6 / 17.4.
+static bool calib_one_launch(const fasa_shape& s) {
+  return s.dtype == FASA_BF16 && s.n_ctx > kCalibShort && s.n_ctx <= 32768 && s.batch * s.n_kv_heads >= 8;
+}
+
 template <typename ET, int PS, int PA>
 static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void* Kp_all, int kk, float* S, const CalibSets& sets,
                                  float* CA_sum, hipStream_t st) {
   const int rows = s.batch * s.n_kv_heads, half = s.head_dim / 2;
-  // One launch for all (behind one that clears) where that is the faster: bf16, 8 rows or more, of 8193 .. 32768 tokens.  us, two launches / so: 8 rows of 32768, K = 2048:
-  // 35.4 / 31.2; 1 head, 4000: 38.7 / 34.5; of 16384, 1500: 25.2 / 21.7; of 12000: 24.5 / 21.4; 32 rows of 16384: 68.1 / 64.6; rows whose best lie together (rising; neighbours
-  // alike): 8 of 32768 38.4 / 35.1, 39.0 / 36.0, of 12000 25.6 / 24.3, 25.7 / 24.0; thousands of ties 78.5 / 75.9, 37.8 / 39.0.  On the other side fewer rows, which have
-  // workgroups of 1024: 4 of 32000: 29.2 / 26.5, of 20000: 25.2 / 23.1, but rising 26.9 / 29.9; 2 of 20011: 19.9 / 20.5; 8 of 1015: 14.6 / 15.9, of 5000: 18.1 / 17.6; 4 of 3000:
-  // 15.3 / 16.9; 8 of 131072: 124 / 131; float32, 8 of 20000: 41.1 / 43.7, of 6000: 19.6 / 17.4.
   if constexpr (sizeof(ET) == 2) {
-    if (s.n_ctx > kCalibShort && s.n_ctx <= 32768 && rows >= 8) {
+    if (calib_one_launch(s)) {
       const hipError_t e = launch("fasa_calib_clear", calib_clear_kernel, dim3(rows), dim3(256), st, sets);
       if (e != hipSuccess) return e;
       const int nslices = (s.n_ctx + kSliceTokens - 1) / kSliceTokens;
@@ -953,13 +976,13 @@ static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void*
     return launch("fasa_calib_fc", kernel, dim3(rows * (1 + half)), dim3(nt), st, (const ET*)Kp_all, S, sets, CA_sum, rows, s.n_ctx, s.n_cap, kk);
   };
   // Rows that fit in the registers of 256 threads twice over: several workgroups per compute unit.  Longer ones: two of 1024 share a compute unit, and three of
-  // 512 do where two don't hold the FCs' and the full head's workgroups at once: 8 rows of 32768, K = 2048 (520 workgroups): 35.6 / 34.9; of 16384: 27.0 / 24.8; of
-  // 12000: 26.0 / 23.9 (with 32 scores in flight per thread 36.7 / 25.6 / 24.5).
-  constexpr bool H = sizeof(ET) == 2;
+  // 512 do where two don't hold the FCs' and the full head's workgroups at once, which fewer than 8 rows' are.  float32, us,
+  // 1024 / 512: 8 rows of 9000 31.9 / 26.4, of 20000 51.0 / 41.1, of 32768, K = 2048, 63.6 / 59.8; 16 of 12000 60.7 / 48.9.
   if (s.n_ctx <= kCalibShort) return stage(calib_fc_kernel<ET, CalibLds<256, kCalibWords0, 4096>, 4>, 256);
   if (s.n_ctx > 32768) return stage(calib_fc_kernel<ET, CalibLds<1024, (kCalibMaxCtx + 30) / 31, 13312>, 4>, 1024);
-  if (rows * (1 + half) <= 2 * kAssumedCUs) return stage(calib_fc_kernel<ET, CalibLds<1024, kCalibWords1, 8192>, H ? 8 : 4>, 1024);
-  return stage(calib_fc_kernel<ET, CalibLds<512, kCalibWords1, 7680>, H ? 6 : 4>, 512);
+  if constexpr (sizeof(ET) == 2) return stage(calib_fc_kernel<ET, CalibLds<1024, kCalibWords1, 8192>, 8>, 1024);
+  else if (rows * (1 + half) <= 2 * kAssumedCUs) return stage(calib_fc_kernel<ET, CalibLds<1024, kCalibWords1, 8192>, 4>, 1024);
+  else return stage(calib_fc_kernel<ET, CalibLds<512, kCalibWords1, 7680>, 4>, 512);
 }
 
 // Cuts, lists (5 bytes a place), what describes their segments, states, tickets, sets.
@@ -976,7 +999,11 @@ hipError_t launch_calib(const fasa_shape& s, const void* q, const void* Kp_all, 
   sets.words = (s.n_ctx + 30) / 31;
   sets.nsegs = (int)calib_list_segs(s.n_ctx);
   sets.pitch = s.dtype == FASA_BF16 ? list_room(kk, s.n_ctx) : 0;
-  if (sets.pitch > kListSeg / 2 || s.n_ctx <= kCalibShort) sets.pitch = 0;   // (half of the row, or a row that is read as fast)
+  // None for half of a row, nor in two launches up to 32768 tokens: so few rows all have their places at once, the full head's set is found while the FCs stream, and
+  // lists that turn out to be of no use hold it up.  us, lists / none, independent scores; rising; neighbours alike: 1 row of 9000, K = 300: 16.6 / 16.6; 20.2 / 16.5; 20.2 / 16.6; 2 of 20011,
+  // 700: 19.95 / 20.05; 23.3 / 20.0; 23.3 / 20.05; 4 of 12000, 1000: 20.9 / 19.9; 22.4 / 20.0; 22.6 / 20.0; of 32000, 3500: 28.9 / 28.95; 31.3 / 29.25; 32.25 / 30.3; 7 of 32768, 2048:
+  // 34.2 / 33.3; 35.0 / 33.2; 35.2 / 33.55.  Longer rows, whose FCs wait for a place: beside calib_top's use of them.
+  if (sets.pitch > kListSeg / 2 || !(calib_one_launch(s) || s.n_ctx > 32768)) sets.pitch = 0;
   sets.cuts = (float4*)scratch;
   sets.lists = (uint32_t*)(sets.cuts + rows * (kHeadDim / 2));
   sets.lims = (uint2*)(sets.lists + rows * sets.list_words());
