@@ -3,6 +3,7 @@
 // launch plans over a sweep of shapes, the dominant-list checker, the dominant-FC choice - without a
 // GPU.  Compiled together with the library's sources with AddressSanitizer and
 // UndefinedBehaviorSanitizer on the host side (device code is untouched); any report fails the run.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -151,6 +152,72 @@ int main() {
           EXPECT((long long)(((unsigned long long)((uint32_t)n << 1) * m) >> 32) == n / d);
         }
     }
+  // ---- bins of scores held in registers: monotone, whatever the ends are; and where one score lies far from all others few share the B-th's bin, as if it did not ----
+  {
+    const float inf = __builtin_inff(), most = 3.4028235e38f;
+    const std::vector<float> xs = {-inf, -most, -1e30f, -100.f, -20.5f, -20.f, -1e-3f, -1e-44f, 0.f, 1e-44f, 1e-38f, 1e-3f, 19.f, 20.f, 20.000002f, 64.f, 1e4f, 1e30f, 1.7e38f, most, inf};
+    for (float lo : xs)
+      for (float mid : xs)
+        for (float hi : xs) {
+          if (!(lo <= mid && mid <= hi)) continue;
+          const fasa::LinBins lin = fasa::lin_bins(lo, mid, hi);
+          const fasa::LogBins log = fasa::log_bins(lo, mid, hi);
+          uint32_t last_lin = 0, last_log = 0;
+          for (float x : xs) {
+            const uint32_t a = fasa::held_bin(lin, x), b = fasa::held_bin(log, x);
+            EXPECT(last_lin <= a && a < (uint32_t)fasa::kListBins && last_log <= b && b < (uint32_t)fasa::kListBins);
+            last_lin = a;
+            last_log = b;
+          }
+        }
+    constexpr int NT = 512;
+    uint32_t seed = 12345u;
+    auto normal = [&]() {
+      float z = -6.f;
+      for (int i = 0; i < 12; ++i) { seed = seed * 1664525u + 1013904223u; z += (float)(seed >> 8) * 0x1p-24f; }
+      return z;
+    };
+    for (int n : {257, 600, 1531, 2048, 4096, 6000, 8192})
+      for (int b : {16, n / 8, n / 2})
+        for (float far : {0.f, 1e4f, 1e12f, 3e38f, inf, -1e4f, -1e12f, -3e38f, -inf}) {
+          if (far != 0.f && n < fasa::kHeldPairs) continue;
+          std::vector<float> x(n);
+          for (float& v : x) v = 20.f * normal();
+          if (far != 0.f) x[n / 3] = far;
+          const bool few = b <= (NT < n / 4 ? NT : n / 4);
+          float hi_t[NT], lo_t[NT], h[8], l[8];
+          for (int t = 0; t < NT; ++t) { hi_t[t] = -inf; lo_t[t] = inf; }
+          for (int i = 0; i < n; ++i) {
+            const int t = i / 4 % NT;
+            if (x[i] > hi_t[t]) hi_t[t] = x[i];
+            if (x[i] < lo_t[t]) lo_t[t] = x[i];
+          }
+          for (int w = 0; w < 8; ++w) {
+            h[w] = -inf; l[w] = inf;
+            for (int t = 64 * w; t < 64 * w + 64; ++t) {
+              if (hi_t[t] > h[w]) h[w] = hi_t[t];
+              const float v = few ? (4 * t < n ? hi_t[t] : inf) : lo_t[t];
+              if (v < l[w]) l[w] = v;
+            }
+          }
+          float lo = inf, low = inf, mid = -inf, hi = -inf;
+          for (int w = 0; w < 8; w += 2) {
+            hi = std::max({hi, h[w], h[w + 1]});
+            lo = std::min({lo, l[w], l[w + 1]});
+            mid = std::max(mid, std::min(h[w], h[w + 1]));
+            low = std::min(low, std::max(l[w], l[w + 1]));
+          }
+          if (low == inf) low = lo;
+          const bool pairs = n >= fasa::kHeldPairs;
+          const fasa::LinBins bins = fasa::lin_bins(few || !pairs ? lo : low, pairs ? mid : hi, hi);
+          std::vector<int> count(fasa::kListBins);
+          for (float v : x)
+            if (v >= (few ? lo : -inf)) ++count[fasa::held_bin(bins, v)];
+          int bin = fasa::kListBins - 1, above = 0;
+          while (bin > 0 && above + count[bin] < b) above += count[bin--];
+          EXPECT(above + count[bin] >= b && count[bin] <= fasa::kHeldMany);
+        }
+  }
   // ---- bad shapes ----
   {
     fasa_shape s = shape(1, 32, 8, 16, 1000, 1024, 100);

@@ -453,106 +453,249 @@ __device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EP
   return true;
 }
 
-// The B best of a row whose scores all lie in the workgroup's registers: x[k] of token token(k), a NaN where the row has ended.  A histogram of 512 bins
-// between the least and the largest of them, equally wide in the score, gives the bin that the B-th lies in; the few in it are candidates, ranked by counting, and every
-// score above is in the set.  Bins are monotone in the score whatever rounds, so what the scores look like (one far above the others) costs another
-// pass over the bin's own, never exactness; after three passes, for ties by the hundred and where fewer than B scores are numbers, row_select does it.
+// ---------------------------------------------------------------------------------------------
+// Selection of a row whose scores all lie in the workgroup's registers
+// ---------------------------------------------------------------------------------------------
+constexpr int kHeldMany = 128;          // candidates that take longer to rank than another pass
+constexpr int kHeldPairs = 512;         // tokens from which on the first two waves are full, and of two waves one says what is usual (HeldEnds)
+
+// The first pass' bins: equally wide, from `lo` up to `hi`, or no further beyond `mid` than that is from `lo`.  What is above shares the last bin, what is below the first.
+// Monotone whatever rounds or overflows: the ends decide how many scores share a bin, never which bin is above which.
+struct LinBins {
+  float lo, inv;
+};
+__host__ __device__ __forceinline__ LinBins lin_bins(float lo, float mid, float hi) {
+  constexpr float most = 3.4028235e38f;
+  lo = fmaxf(lo, -most);
+  const float top = fminf(mid > lo ? fminf(hi, mid + (mid - lo)) : hi, most), bin = (top - lo) * (1.0f / kListBins);
+#ifdef __HIP_DEVICE_COMPILE__
+  return {lo, __builtin_amdgcn_rcpf(bin)};
+#else
+  return {lo, 1.0f / bin};
+#endif
+}
+__host__ __device__ __forceinline__ uint32_t held_bin(const LinBins& b, float x) {
+  return (uint32_t)fminf(fmaxf((x - b.lo) * b.inv, 0.0f), (float)(kListBins - 1));
+}
+
+// Bins for what those don't tell apart: from `lo` to `mid` 64 to 256 of them next to each other, as many for twice that distance, and so on: the upper bits of a float.  A
+// score far above all others costs bins no more than it is binary orders of magnitude away, eight of them at most, and what lies beyond shares the last bin.
+struct LogBins {
+  float lo, c;
+  uint32_t base;
+  int shift;
+};
+__host__ __device__ __forceinline__ LogBins log_bins(float lo, float mid, float hi) {
+  constexpr float most = 3.4028235e38f;
+  LogBins b;
+  b.lo = fminf(fmaxf(lo, -most), most);
+  const float spread = hi - b.lo, c = mid - b.lo;
+  b.c = fminf(c > 0.f ? c : spread, most);
+  b.base = __builtin_bit_cast(uint32_t, b.c);
+  const uint32_t span = __builtin_bit_cast(uint32_t, spread + b.c) - b.base;
+  const int shift = span ? 23 - __builtin_clz(span) : 0;
+  b.shift = shift < 0 ? 0 : shift > 17 ? 17 : shift;          // 512 bins are eight binary orders of magnitude then
+  return b;
+}
+__host__ __device__ __forceinline__ uint32_t held_bin(const LogBins& b, float x) {
+  const uint32_t bin = (__builtin_bit_cast(uint32_t, fmaxf(x - b.lo, 0.f) + b.c) - b.base) >> b.shift;
+  return bin < (uint32_t)kListBins - 1u ? bin : (uint32_t)kListBins - 1u;
+}
+
+// Between what scores lie: the largest and the least of the threads' own `hi` and `lo`; and what few exceed, and few fall below: of two waves the one whose best
+// (least) is less far out, so that a few scores far away don't show.  A block barrier.
+struct HeldEnds {
+  float lo, low, mid, hi;
+};
+template <typename Lds>
+__device__ __forceinline__ HeldEnds held_ends(Lds& sm, float lo, float hi) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  hi = fmaxf(wave_max(hi), -INFINITY);                        // (a wave without a score)
+  lo = fminf(-wave_max(-lo), INFINITY);
+  if (lane == 0) { sm.wtot[wave] = __float_as_uint(hi); sm.wtot2[wave] = __float_as_uint(lo); }
+  __syncthreads();
+  HeldEnds e{lo, INFINITY, -INFINITY, hi};
+#pragma unroll
+  for (int w = 0; w < Lds::kWaves; w += 2) {
+    const float h0 = __uint_as_float(sm.wtot[w]), h1 = __uint_as_float(sm.wtot[w + 1]), l0 = __uint_as_float(sm.wtot2[w]), l1 = __uint_as_float(sm.wtot2[w + 1]);
+    e.hi = fmaxf(e.hi, fmaxf(h0, h1));
+    e.lo = fminf(e.lo, fminf(l0, l1));
+    e.mid = fmaxf(e.mid, fminf(h0, h1));
+    e.low = fminf(e.low, fmaxf(l0, l1));
+  }
+  if (e.low == INFINITY) e.low = e.lo;                        // (one wave has them all)
+  return e;
+}
+
+// Of the thread's scores those in bins above the `need`-th best's, which are in the set, and those in it.
+struct Held {
+  uint32_t win, act;
+  int need, n;
+  uint32_t at;             // that bin
+};
+// How the first pass went, of the scores from `from` on.
+struct HeldFound {
+  LinBins bins;
+  float from;
+  uint32_t at;
+  int need, n;
+};
+// Counts bin_of(k), the bin of the k-th; bins from kListBins on: not counted.  A block barrier.  n = 0: fewer than `need` are.
+template <int NV, typename Lds, typename BinOf>
+__device__ __forceinline__ Held held_count(Lds& sm, Held h, BinOf&& bin_of) {
+  uint32_t bin[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    bin[k] = bin_of(k);
+    atomicAdd(&sm.hist[bin[k]], 1u);
+  }
+  __syncthreads();
+  const BinAt b = wave_find_bin(sm.hist, (uint32_t)h.need);
+  const uint32_t at = b.n ? (uint32_t)b.bin : (uint32_t)kListBins;
+  h.act = 0;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    h.win |= bin[k] > at && bin[k] < (uint32_t)kListBins ? 1u << k : 0u;
+    h.act |= bin[k] == at ? 1u << k : 0u;
+  }
+  h.need -= b.above;
+  h.n = b.n;
+  h.at = at;
+  return h;
+}
+// The set's places: the winners' by thread, then, if there are no more than can be ranked, the candidates'.  Ends with a block barrier.
+template <int NV, typename Lds, typename Token>
+__device__ __forceinline__ void held_place(Lds& sm, const float (&x)[NV], Token&& token, Held h, int bsel, const float* srow, int N) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const uint32_t n_win = (uint32_t)__popc(h.win), incl = wave_prefix_sum(n_win);
+  if (lane == kWave - 1) sm.wtot[wave] = incl;                // (all have read them: a barrier lies between)
+  float v[NV];                                                // (or a choice of places to load from is made of the choice below, and x is kept in memory for it)
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = x[k];
+  while (h.act != 0u) {                                       // (few lanes have a candidate)
+    const int j = __ffs((int)h.act) - 1;
+    float xj = v[0];
+    int tj = token(0);
+#pragma unroll
+    for (int k = 1; k < NV; ++k) { xj = j == k ? v[k] : xj; tj = j == k ? token(k) : tj; }
+    const uint32_t c = __builtin_amdgcn_atomic_inc32(&sm.n_cnd, 0xffffffffu, __ATOMIC_RELAXED, "workgroup");
+    sm.cand[c & (kSelCand - 1)] = make_uint2(score_key(xj), (uint32_t)tj);
+    h.act &= h.act - 1u;
+  }
+  __syncthreads();
+  uint32_t p = incl - n_win;
+#pragma unroll
+  for (int w = 0; w < Lds::kWaves; ++w) p += w < wave ? sm.wtot[w] : 0u;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const bool w = h.win >> k & 1u;
+    sm.put_if(w, (int)p, (uint32_t)token(k));
+    p += w ? 1u : 0u;
+  }
+  if (h.n <= kSelCand) resolve_threshold(sm, 0u, bsel, h.need, h.n, srow, N, 0, bsel);
+  else __syncthreads();
+}
+
+// The B best of such a row: x[k] of token token(k), a NaN where the row has ended.  A histogram of 512 bins gives the bin that the B-th lies in; the few in it are candidates,
+// ranked by counting, and every score above is in the set.  False where that bin has more than are ranked in the time of another pass, or fewer than B scores are numbers:
+// select_held_again goes on.  What the scores look like costs time, never exactness.
 // Bound by the latency of a few instructions of each kind behind each other.  Four barriers, where a sample's cut, a list of what reaches it and the selection out of that had
-// eleven; and what a lane has no use for goes to a word of its own in LDS, since sixteen branches around one LDS instruction each took 1.3 us.  us: step of 8 rows of
-// 1531, B = 192, 10.6 -> 9.4; 1 float32 row of 4096, 256, 11.2 -> 10.3 (16 scores a thread, half of them beyond the row, and with branches 11.8).
-// Places go by thread.  False: not done (the histogram is zero then, a barrier before the call's end is the caller's).
+// eleven; and what a lane has no use for goes to a word of its own in LDS, since sixteen branches around one LDS instruction each took 1.3 us.  us per step: 8 rows of
+// 1531, B = 192, 10.6 -> 9.25; 1 float32 row of 4096, 256, 11.25 -> 9.95 (16 scores a thread, half of them beyond the row, and with branches 11.8).
+// With bins from the least to the largest, whatever they are, one score far above all others left the rest in one bin: 8 rows of 6000, B = 256, 16.85, like this 11.95; 1 float32 row of
+// 4096 12.5 / 9.95; fasa_topk of 16 rows of 2048 with one far above and one far below 5.8 / 3.45.
 template <int NV, typename Lds, typename Token>
 __device__ __forceinline__ bool select_held(Lds& sm, const float (&x)[NV], Token&& token, int bsel, const float* srow, int N) {
-  constexpr int NT = Lds::kThreads, NWV = Lds::kWaves;
+  constexpr int NT = Lds::kThreads;
   static_assert(NV <= 16 && kListBins + kWave <= kSelBins, "flags in a word; words for what is not counted");
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int t = threadIdx.x;
   if (t == 0) sm.n_cnd = 0;
   for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
-  uint32_t win = 0, act = 0;                                  // of the thread's scores: in the set; in the bin that is looked at
-  int need = bsel, n_cand = 0;
   float hi = x[0], lo = x[0];
 #pragma unroll
   for (int k = 1; k < NV; ++k) hi = fmaxf(hi, x[k]);
   // From the lowest of the threads' highest on: a score of each thread that has any, and so B of them (the row's tokens lie in fours, at most)
-  if (bsel <= min(NT, N / 4)) lo = hi;
+  const bool few = bsel <= min(NT, N / 4);
+  if (few) lo = hi;
   else {
 #pragma unroll
     for (int k = 1; k < NV; ++k) lo = fminf(lo, x[k]);
   }
-  for (int pass = 0;; ++pass) {
-    hi = wave_max(hi);
-    lo = -wave_max(-lo);
-    if (lane == 0) { sm.wtot[wave] = __float_as_uint(hi); sm.wtot2[wave] = __float_as_uint(lo); }
-    __syncthreads();
+  const HeldEnds e = held_ends(sm, lo, hi);
+  const bool pairs = N >= kHeldPairs;
+  const LinBins bins = lin_bins(few || !pairs ? e.lo : e.low, pairs ? e.mid : e.hi, e.hi);
+  const float from = few ? e.lo : -INFINITY;
+  const Held h = held_count<NV>(sm, Held{0u, 0u, bsel, 0, 0u}, [&](int k) { return x[k] >= from ? held_bin(bins, x[k]) : (uint32_t)(kListBins + lane_id()); });
+  // For select_held_again, which makes its flags anew: kept in registers for what hardly ever comes they cost the one-launch step 0.1 - 0.8 us, and left in LDS in the
+  // unlikely branch alone 0.2 - 0.5.
+  if (t == 0) sm.found = {bins, from, h.at, h.need, h.n};
+  if (__builtin_expect((uint32_t)(h.n - 1) >= (uint32_t)kHeldMany, false)) return false;
+  held_place<NV>(sm, x, token, h, bsel, srow, N);
+  return true;
+}
+
+// Up to two more passes, over what is left in the bin, and ties by the hundred by index, out of pieces of four tokens (or as many as a thread has), a piece's thread after
+// thread.  False: they were too few, or fewer than B scores are numbers (the histogram is zero then, a barrier before the call's end is the caller's).  us, two passes of equally wide
+// bins and row_select / this: fasa_topk of 16 rows of 2048, B = 256, ties by the hundred 19.0 / 5.25, a half at the type's lowest value 17.7 / 6.5; 8 of 1000, 500, every second score
+// so 13.4 / 5.65.
+template <int NV, typename Lds, typename Token>
+__device__ __forceinline__ bool select_held_again(Lds& sm, const float (&x)[NV], Token&& token, int bsel, const float* srow, int N) {
+  constexpr int NT = Lds::kThreads, P = NV < 4 ? NV : 4;
+  const int t = threadIdx.x;
+  __syncthreads();
+  const HeldFound f = sm.found;
+  Held h{0u, 0u, f.need, f.n, f.at};
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) {
-      hi = fmaxf(hi, __uint_as_float(sm.wtot[w]));
-      lo = fminf(lo, __uint_as_float(sm.wtot2[w]));
-    }
-    // (an infinite spread: all of them in bin 0, and the next pass leaves infinities out)
-    const float inv = (float)kListBins * __builtin_amdgcn_rcpf(hi - lo);
-    uint32_t bin[NV];
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      bin[k] = (uint32_t)fminf(fmaxf((x[k] - lo) * inv, 0.0f), (float)(kListBins - 1));
-      const bool in = x[k] >= lo && (pass == 0 || (act >> k & 1u));
-      bin[k] = in ? bin[k] : (uint32_t)(kListBins + lane);
-      atomicAdd(&sm.hist[bin[k]], 1u);
-    }
-    __syncthreads();
-    const BinAt b = wave_find_bin(sm.hist, (uint32_t)need);
-    if (b.n == 0) break;
-    need -= b.above;
-    n_cand = b.n;
-    act = 0;
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      win |= bin[k] > (uint32_t)b.bin && bin[k] < (uint32_t)kListBins ? 1u << k : 0u;
-      act |= bin[k] == (uint32_t)b.bin ? 1u << k : 0u;
-    }
-    if (__builtin_expect(n_cand <= kSelCand, true)) break;
-    n_cand = 0;
-    if (pass == 2) break;
-    __syncthreads();                                          // (all have read the histogram)
-    for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
-    hi = -INFINITY;
-    lo = INFINITY;
+  for (int k = 0; k < NV; ++k) {
+    const uint32_t bin = held_bin(f.bins, x[k]);
+    h.win |= x[k] >= f.from && bin > f.at ? 1u << k : 0u;
+    h.act |= x[k] >= f.from && bin == f.at ? 1u << k : 0u;
+  }
+  bool tied = false;
+#pragma unroll 1
+  for (int pass = 0; pass < 2 && h.n > kHeldMany; ++pass) {
+    float hi = -INFINITY, lo = INFINITY;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const bool in = (act >> k & 1u) && fabsf(x[k]) < INFINITY;      // (infinite ones: the bins at the ends)
+      const bool in = h.act >> k & 1u;
       hi = in ? fmaxf(hi, x[k]) : hi;
       lo = in ? fminf(lo, x[k]) : lo;
     }
+    __syncthreads();                                          // (all have read the histogram, and the last ends)
+    for (int i = t; i < kListBins; i += NT) sm.hist[i] = 0;
+    const HeldEnds e = held_ends(sm, lo, hi);
+    tied = e.hi == e.lo;
+    if (tied) break;
+    const LogBins bins = log_bins(e.low, e.mid, e.hi);
+    const uint32_t act = h.act;
+    h = held_count<NV>(sm, h, [&](int k) { return act >> k & 1u ? held_bin(bins, x[k]) : (uint32_t)(kListBins + lane_id()); });
   }
-  if (n_cand == 0) {
+  if (h.n == 0 || (h.n > kSelCand && !tied)) {
     __syncthreads();
     for (int i = t; i < kSelBins; i += NT) sm.hist[i] = 0;
     if (t == 0) sm.thr[2] = 0;
     return false;
   }
-  const uint32_t n_win = (uint32_t)__popc(win), incl = wave_prefix_sum(n_win);
-  if (lane == kWave - 1) sm.wtot[wave] = incl;                // (all have read them: a barrier lies between)
-  while (act != 0u) {                                         // (few lanes have a candidate)
-    const int j = __ffs((int)act) - 1;
-    float xj = x[0];
-    int tj = token(0);
+  if (tied) {                                                 // the first `need` of them
+    int p = bsel - h.need;
 #pragma unroll
-    for (int k = 1; k < NV; ++k) { xj = j == k ? x[k] : xj; tj = j == k ? token(k) : tj; }
-    const uint32_t c = __builtin_amdgcn_atomic_inc32(&sm.n_cnd, 0xffffffffu, __ATOMIC_RELAXED, "workgroup");
-    sm.cand[c & (kSelCand - 1)] = make_uint2(score_key(xj), (uint32_t)tj);
-    act &= act - 1u;
+    for (int k0 = 0; k0 < NV; k0 += P) {
+      const uint32_t m = h.act >> k0 & ((1u << P) - 1u);
+      uint32_t all;
+      int at = p + (int)block_prefix_sum<NT>((uint32_t)__popc(m), sm.wtot, all);
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        const bool in = m >> k & 1u;
+        if (in && at < bsel) sm.put(at, (uint32_t)token(k0 + k));
+        at += in ? 1 : 0;
+      }
+      p += (int)all;
+    }
+    h.act = 0;
+    h.n = kSelCand + 1;                                       // (nothing to rank)
   }
-  __syncthreads();
-  uint32_t p = incl - n_win;
-#pragma unroll
-  for (int w = 0; w < NWV; ++w) p += w < wave ? sm.wtot[w] : 0u;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const bool w = win >> k & 1u;
-    sm.put_if(w, (int)p, (uint32_t)token(k));
-    p += w ? 1u : 0u;
-  }
-  resolve_threshold(sm, 0u, bsel, need, n_cand, srow, N, 0, bsel);
+  __syncthreads();                                            // (all have read the waves' counts, and how the first pass went)
+  held_place<NV>(sm, x, token, h, bsel, srow, N);
   return true;
 }
 

@@ -88,6 +88,7 @@ struct RowLds {
   uint2 lim[LIST == 1 ? NT : NT / 2];
   uint32_t n_list, n_cnd;
   int p_new;                                                 // place of the appended row in wl, or -1
+  HeldFound found;
   __device__ __forceinline__ void put(int place, uint32_t tok) { wl[place] = tok; }
   // (no branch: a lane that has nothing to put writes a word of its own)
   __device__ __forceinline__ void put_if(bool yes, int place, uint32_t tok) { wl[yes ? place : kMost + 16 + lane_id()] = tok; }
@@ -583,8 +584,13 @@ __device__ __forceinline__ void step_row(const void* q0, void* Kp0, const int32_
     __syncthreads();
     if (ticket != (uint32_t)nvalid - 1u) return;
     if (t == 0) a.ctl[row].done_sel = 0;                      // clean for the next call
-    // (the row is readable in 16-byte pieces: S is n_cap long, a multiple of 64)
     if (t == 0) sm.row.p_new = -1;
+  } else {
+    __syncthreads();                                          // (all have read the queries' sums: shared storage)
+    if (t == 0) sm.row.p_new = -1;
+  }
+  if constexpr (MULTI) {
+    // (the row is readable in 16-byte pieces: S is n_cap long, a multiple of 64)
     auto held = [&](auto pieces) {
       constexpr int CH = decltype(pieces)::value;
       float v[4 * CH];
@@ -595,16 +601,18 @@ __device__ __forceinline__ void step_row(const void* q0, void* Kp0, const int32_
         v[4 * it] = n < N ? __uint_as_float(x.x) : NAN; v[4 * it + 1] = n + 1 < N ? __uint_as_float(x.y) : NAN;
         v[4 * it + 2] = n + 2 < N ? __uint_as_float(x.z) : NAN; v[4 * it + 3] = n + 3 < N ? __uint_as_float(x.w) : NAN;
       }
-      return select_held(sm.row, v, [&](int k) { return ((k >> 2) * kStepNT + t) * 4 + (k & 3); }, bsel, srow, N);
+      const auto token = [&](int k) { return ((k >> 2) * kStepNT + t) * 4 + (k & 3); };
+      if (select_held(sm.row, v, token, bsel, srow, N)) return true;
+      return select_held_again(sm.row, v, token, bsel, srow, N);
     };
     constexpr int CH = kStepMaxCtx / (4 * kStepNT);
     done = N <= kStepMaxCtx / 2 ? held(std::integral_constant<int, CH / 2>{}) : held(std::integral_constant<int, CH>{});
   } else {
 #pragma unroll
     for (int k = 0; k < TPT; ++k) acc[k] = n0 + k < N ? acc[k] : NAN;
-    __syncthreads();                                          // (all have read the queries' sums: shared storage)
-    if (t == 0) sm.row.p_new = -1;
-    done = select_held(sm.row, acc, [&](int k) { return n0 + k; }, bsel, srow, N);
+    const auto token = [&](int k) { return n0 + k; };
+    done = select_held(sm.row, acc, token, bsel, srow, N);
+    if (!done) done = select_held_again(sm.row, acc, token, bsel, srow, N);
   }
   if (!done) {
     publish_barrier();                                        // this workgroup's own scores are in memory

@@ -210,6 +210,7 @@ struct TopkLds {
   uint32_t wtot[kWaves], wtot2[kWaves];
   uint32_t thr[4];
   uint32_t ticket, n_cnd;
+  HeldFound found;
   __attribute__((address_space(1))) int32_t* out;             // (a generic pointer's stores are flat: every wait is one for all of LDS)
   __device__ __forceinline__ void put(int place, uint32_t tok) { out[place] = (int32_t)tok; }
   __device__ __forceinline__ void put_if(bool yes, int place, uint32_t tok) {
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(kTopkNT) void topk_kernel(const float* __restrict__
   if constexpr (ONE) {
     if (t == 0) sm.out = (__attribute__((address_space(1))) int32_t*)(T + (size_t)row * bsel);
     const float held[4] = {n0 < N ? x.x : NAN, n0 + 1 < N ? x.y : NAN, n0 + 2 < N ? x.z : NAN, n0 + 3 < N ? x.w : NAN};
-    if (!select_held(sm, held, [&](int k) { return n0 + k; }, bsel, srow, N)) {
+    if (!select_held(sm, held, [&](int k) { return n0 + k; }, bsel, srow, N) && !select_held_again(sm, held, [&](int k) { return n0 + k; }, bsel, srow, N)) {
       __syncthreads();
       row_select<false>(sm, bsel, srow, N, 0, bsel);
     }
