@@ -336,6 +336,18 @@ __global__ __launch_bounds__(256) void score_kernel(const ET* __restrict__ q, ET
 // 16 paged sequences, whose planes are kept, 29.3 -> 30.25).  us, with a fifth wave that scored a sample of the row for a common cut / like this: 128 rows of 16384, F = 16:
 // 30.0 / 27.7 (score_kernel alone 25.3); 32 rows of 32905: 16.8 / 15.8; 8 of 131072, F = 32: 27.1 / 26.2; 8 of 32768: 5.7 / 5.9.
 constexpr int kListScoreNT = 256;
+template <typename ET, bool APPEND>
+struct ScoreListLds {
+  SegLds seg[kListScoreNT / kWave];
+  float qsum[kListScoreNT];
+  int32_t fcl[kListScoreNT];
+  float2 qs[kHeadDim / 2];
+  ET knew[APPEND ? kHeadDim : 1];
+  uint32_t kpair[APPEND ? kHeadDim / 2 : 1];
+};
+// LDS of a workgroup of which six share a compute unit
+constexpr size_t kLdsPerCU = 160 * 1024, kLdsOfSix = 26 * 1024;
+static_assert(6 * kLdsOfSix <= kLdsPerCU && 7 * kLdsOfSix > kLdsPerCU, "six, and no more");
 // STREAM (a step that touches kStreamBytes or more): us per step over three sets of buffers, planes kept / non-temporal: 128 rows of 16384, F = 16, B = 256: 37.7 /
 // 35.1; 96 rows: 31.9 / 29.5; 64 rows: 22.1 / 23.2; 32 rows of 32905, 7 heads, 6219: 45.3 / 41.2; 32768, 4 heads, 2048: 28.8 / 28.2; 8 rows of 131072,
 // F = 32, 1024: 37.6 / 34.9; F = 16, 4000: 26.4 / 27.4.  Ten sets: 128 rows of 16384 37.7 / 35.6, 8 of 131072 37.6 / 35.2; 24 sets of 8 rows of 32768,
@@ -353,12 +365,13 @@ __global__ __launch_bounds__(kListScoreNT, 8) void score_list_kernel(
   constexpr bool PAIRS = PAIR == FASA_PAIR_LIST;
   constexpr int PAIR_SHIFT = PAIR == FASA_PAIR_INTERLEAVED ? 1 : 0;
   constexpr int PAIR_ADD = PAIR == FASA_PAIR_INTERLEAVED ? 1 : D / 2;
-  __shared__ SegLds seg[NT / kWave];
-  __shared__ float qsum[NT];
-  __shared__ int32_t fcl[NT];
-  __shared__ float2 qs[D / 2];
-  __shared__ ET knew[APPEND ? D : 1];
-  __shared__ uint32_t kpair[APPEND ? D / 2 : 1];
+  __shared__ ScoreListLds<ET, APPEND> sm;
+  auto& seg = sm.seg;
+  auto& qsum = sm.qsum;
+  auto& fcl = sm.fcl;
+  auto& qs = sm.qs;
+  auto& knew = sm.knew;
+  auto& kpair = sm.kpair;
 
   int row, slice;
   row_slice_of_block(rows, nslices, m_slices, row, slice);
@@ -596,7 +609,8 @@ static hipError_t launch_score_list_v(const fasa_shape& s, const void* q, void* 
   // once, then come in more and smaller rounds.  us, eight / six / five: paged, 16 sequences of 4031 - 16127, B = 252: 29.3 / 28.45 / 28.7; 8 of 8226 - 32905, 2000: 37.0 / 35.5 /
   // 35.5; 16 of 4000 - 16000, F = 8, 600: 25.8 / 25.1 / 25.6; of 2000 - 8000: 19.8 / 19.8 / 19.8; rows of one length within 0.1 (64 of 16384, 32 of 32768, 96 of 12001),
   // streamed ones too, 128 of 16384 34.0 / 34.0 / 34.2.
-  const size_t lds = stream ? 0 : 18 * 1024;
+  static_assert(sizeof(ScoreListLds<ET, APPEND>) <= kLdsOfSix, "what is padded to a sixth");
+  const size_t lds = stream ? 0 : kLdsOfSix - sizeof(ScoreListLds<ET, APPEND>);
   return launch_lds("fasa_score_list", kernel, dim3(rows * nslices), dim3(kListScoreNT), lds, st,
                 (const ET*)q, (ET*)Kp, fc_idx, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_kv_heads,
                 div_magic(s.n_kv_heads, rows), s.n_q_heads / s.n_kv_heads, s.n_fc, s.n_ctx, s.n_cap, rl.n_ctx, S, (const ET*)ap.k_new,
