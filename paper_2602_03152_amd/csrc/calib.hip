@@ -11,7 +11,7 @@
 //
 // The single-FC scores never exist in memory: a workgroup streams its plane once and writes one number.
 // One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys, asked for twice): 2.3 us for a launch that clears and 29, of which the planes are 18 - 20 (7 TB/s: the second
-// read is no faster than the first); then the full head's set (5 us) and the FCs that come last.  In two launches: 14.5 + 21, the first's end and the second's, where all
+// read is no faster than the first); then the full head's set (5 us) and the FCs that come last.  In two launches 36.85: the first's end and the second's, where all
 // workgroups select at once, with nothing to stream.
 #include <type_traits>
 
@@ -953,11 +953,12 @@ __global__ __launch_bounds__(256) void calib_all_kernel(float* __restrict__ CA_s
   if (i < n) CA_sum[i] += 1.0f;
 }
 
-// One launch for all (behind one that clears) where that is the faster: bf16, 8 rows or more, of 8193 .. 32768 tokens.  us, two launches / so: 8 rows of 32768, K = 2048:
-// 35.4 / 31.2; 1 head, 4000: 38.7 / 34.5; of 16384, 1500: 25.2 / 21.7; of 12000: 24.5 / 21.4; 32 rows of 16384: 68.1 / 64.6; rows whose best lie together (rising; neighbours
-// alike): 8 of 32768 38.4 / 35.1, 39.0 / 36.0, of 12000 25.6 / 24.3, 25.7 / 24.0; thousands of ties 78.5 / 75.9, 37.8 / 39.0.  On the other side fewer rows, which have
-// workgroups of 1024: 4 of 32000: 29.2 / 26.5, of 20000: 25.2 / 23.1, but rising 26.9 / 29.9; 2 of 20011: 19.9 / 20.5; 8 of 1015: 14.6 / 15.9, of 5000: 18.1 / 17.6; 4 of 3000:
-// 15.3 / 16.9; 8 of 131072: 124 / 131; float32, 8 of 20000: 41.1 / 43.7, of 6000: 19.6 / 17.4.
+// One launch for all (behind one that clears) where that is the faster: bf16, 8 rows or more, of 8193 .. 32768 tokens.  us, two launches / so, independent scores; rising; neighbours alike;
+// thousands of ties: 8 rows of 32768, K = 2048: 36.85 / 31.45; 37.0 / 34.5; 36.9 / 34.7; 72.4 / 69.1; of 16384, 1500: 24.35 / 21.75; 24.4 / 24.6; 24.4 / 24.35; 42.3 / 43.3; of 12000, 1000: 23.2 /
+// 21.4; 23.2 / 24.2; 23.25 / 23.7; 34.25 / 36.8; 32 of 16384, 1024: 67.7 / 65.2; 67.4 / 67.2; 67.8 / 67.1; 109.6 / 122.8.  On the other side fewer rows, which have workgroups of 1024: 4 of
+// 32000, 3500: 29.2 / 26.1; 29.5 / 31.85; 30.3 / 32.3; 68.4 / 73.6; 4 of 20000, 1500: 24.95 / 19.6; 24.85 / 26.0; 25.25 / 25.9; 36.1 / 34.4; 2 of 20011, 700: 20.2 / 18.1; 20.0 / 23.9; 20.1 / 23.95;
+// 27.2 / 25.45; 7 of 32768, 2048: 33.55 / 34.2; 33.75 / 36.9; 34.05 / 37.3; 61.8 / 71.9; and shorter ones: 8 of 8192, 512: 18.95 / 18.3; 18.9 / 21.3; 19.1 / 21.25; 37.85 / 27.8; of 5000: 18.05 / 17.15;
+// 18.0 / 20.45; of 1015: 14.5 / 17.25; 14.5 / 19.7; 4 of 3000: 15.5 / 17.2; 15.4 / 19.7.  Measured before FCs waited as long: 8 of 131072: 124 / 131; float32, 8 of 20000: 41.1 / 43.7, of 6000: 19.6 / 17.4.
 static bool calib_one_launch(const fasa_shape& s) {
   return s.dtype == FASA_BF16 && s.n_ctx > kCalibShort && s.n_ctx <= 32768 && s.batch * s.n_kv_heads >= 8;
 }
@@ -971,6 +972,7 @@ static hipError_t launch_calib_p(const fasa_shape& s, const void* q, const void*
       const hipError_t e = launch("fasa_calib_clear", calib_clear_kernel, dim3(rows), dim3(256), st, sets);
       if (e != hipSuccess) return e;
       const int nslices = (s.n_ctx + kSliceTokens - 1) / kSliceTokens;
+      // (the profiler has one name for the launch that counts the FCs, and the full head's work in it is the FCs' there)
       return launch("fasa_calib_fc", calib_kernel<PS, PA>, dim3(rows * (nslices + half)), dim3(kSliceNT), st, (const ET*)q, (const ET*)Kp_all, S, sets, CA_sum, rows, nslices, div_magic(nslices, (long long)rows * nslices), s.n_q_heads / s.n_kv_heads, s.n_ctx,
                     s.n_cap, kk);
     }

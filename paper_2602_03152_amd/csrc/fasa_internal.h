@@ -29,6 +29,11 @@ constexpr int kAssumedCUs = 256;
 // this size over three caches in turn (layers, say) leave nothing there for the next round, and lines that are not kept there come faster:
 // 128 MiB, never the same in 2 GB, 16-byte loads, eight workgroups of 256 on a compute unit: 21.5 -> 20.0 us (6.2 -> 6.7 TB/s).  Below that what one call has
 // left there may serve the next: the same with 64 MiB, 30 buffers: 11.15 -> 10.65 us, but three buffers: 9.9 where memory takes 10.65.
+// The line suits three buffers in turn.  A walk over more (a model's layers) leaves the caches nothing whatever one call reads, and loses by the line what stands below it.  us,
+// kept / non-temporal, 3 | 8 | 24 sets of buffers: step of 8 rows of 32768, B = 2048 (28 MB) 16.65 / 17.3 | 16.5 / 17.1 | 17.65 / 17.05; of 65536 (46 MB) 18.95 / 19.6 | 20.0 / 19.65 |
+// 20.35 / 19.5; 32 rows of 16384, 256 (40 MB) 16.4 / 16.5 | 17.7 / 16.85 | 18.25 / 17.15; 64 rows (80 MB) 21.55 / 22.35 | 24.5 / 22.45 | 24.55 / 23.65; full KV of 8 rows of 8192 (34 MB)
+// 9.8 / 10.0 | 10.05 / 10.4 | 10.7 / 10.5, of 16384 (67 MB) 14.0 / 14.85 | 16.1 / 15.05 | 16.2 / 15.25.  Above it: 128 rows of 16384 (160 MB) 37.4 / 34.15 | 37.3 / 34.55 | 37.4 / 36.45; full KV of 8 rows of
+// 32768 (134 MB) 26.5 / 23.35 | 26.5 / 24.8 | 26.6 / 24.9.
 constexpr long long kStreamBytes = 90ll << 20;
 
 // Per-(b,h) row counters, one 128-byte line per row so that rows served by different XCDs never

@@ -98,8 +98,8 @@ struct MfmaTile {
     for (int i = 0; i < (F32 ? 8 : 4); ++i) qb[i] = __builtin_bit_cast(QT, *reinterpret_cast<const uint4*>(p + 4 * i * kChunk<ET>));
   }
   // With a run-time group size: only the lanes that have a head load, the others carry zeros.  The kernels that use this
-  // have 8 or 16 waves on a compute unit at it, whose requests for the copies would take longer than the wait
-  // (decode step in one launch, 8 rows of 1531, 192 selected: 11.59 us, with copies 11.75; of 6000, 250: 14.80 / 15.08).
+  // have 8 or 16 waves on a compute unit at it, whose requests for the copies take as long as the wait
+  // (decode step in one launch, 8 rows of 1531, 192 selected: 9.27 us, with copies 9.30; of 6000, 250: 11.95 / 11.98).
   __device__ __forceinline__ void load_q(const ET* q_group /* [heads][128] */, int lo, int hi, int heads) {
 #pragma unroll
     for (int i = 0; i < (F32 ? 8 : 4); ++i) {

@@ -456,7 +456,7 @@ __device__ __forceinline__ bool select_entries(Lds& sm, const uint32_t (&key)[EP
 // ---------------------------------------------------------------------------------------------
 // Selection of a row whose scores all lie in the workgroup's registers
 // ---------------------------------------------------------------------------------------------
-constexpr int kHeldMany = 128;          // candidates that take longer to rank than another pass
+constexpr int kHeldMany = 128;          // candidates that take longer to rank than another pass (244 by the pass: a step of 8 float32 rows of 1000 12.4 -> 10.2 us)
 constexpr int kHeldPairs = 512;         // tokens from which on the first two waves are full, and of two waves one says what is usual (HeldEnds)
 
 // The first pass' bins: equally wide, from `lo` up to `hi`, or no further beyond `mid` than that is from `lo`.  What is above shares the last bin, what is below the first.

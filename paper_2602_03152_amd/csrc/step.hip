@@ -83,9 +83,7 @@ struct RowLds {
   float scs[kWaves][16];
   uint32_t wtot[kWaves], wtot2[kWaves];
   uint32_t thr[4];
-  // Where lists of segments begin, and which (list_kernel).  Elsewhere not used, but with 2 KB less of LDS the compiler plans the registers of
-  // step_kernel for another workgroup and spills 55 scalar or 13 vector ones: 8 rows of 1531, B = 192: 10.57 -> 10.64 us.
-  uint2 lim[LIST == 1 ? NT : NT / 2];
+  uint2 lim[LIST == 1 ? NT : 1];                             // where lists of segments begin, and which (list_kernel)
   uint32_t n_list, n_cnd;
   int p_new;                                                 // place of the appended row in wl, or -1
   HeldFound found;
@@ -803,24 +801,22 @@ StepForm plan_step(const fasa_shape& s, const PageMap& pm) {
   const long long most = pm.table ? (long long)pm.n_pool * s.kv_stride_b + (1ll << pm.shift) * s.kv_stride_n
                                   : (long long)s.n_ctx * s.kv_stride_n;
   if ((most >> 3) >= 0xfffffff0ll) return kStepNone;
-  // Lines of the one-launch form, measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step as
-  // (fused.hip / one launch / row_kernel).  One compute unit gathers about 50 KB per us, which is what ends its reach
+  // Lines of the one-launch form, measured over 1 .. 512 rows, 1k .. 64k tokens, 64 .. 1024 selected, us per step.
+  // One compute unit gathers about 50 KB per us, which is what ends its reach
   // in B; reading a row's scores back is what ends it in N.
   const long long rows = (long long)s.batch * s.n_kv_heads;
   const int per = kStepNT * (s.dtype == FASA_BF16 ? 4 : 2);
   const long long ns = (s.n_ctx + per - 1) / per;
   if (s.dtype == FASA_BF16) {
-    // one slice: 8 rows of 2048, B = 64: 14.5 / 10.2 / 15.0, B = 512: 18.2 / 14.9 / 19.8; 512 rows: 29.4 / 20.5 / 36.3.  Against lists
-    // (list_kernel): 8 rows, B = 64: 9.3 / 11.0, 128 rows, 256: 13.1 / 14.6, 512 rows, 64: 19.5 / 21.6, 512: 33.3 / 38.2; 8 rows, 512: 13.6 / 13.5,
-    // 1000: 18.9 / 14.2 (few rows with more than 500 selected would do better with lists)
+    // one slice, against lists (list_kernel), one launch / lists: 8 rows of 2048, B = 64: 8.1 / 11.05, 512: 11.35 / 13.45, 1000: 14.75 / 14.45; 128 rows, 256: 12.05 / 14.75;
+    // 512 rows, 64: 19.0 / 26.0, 512: 45.2 / 49.9
     if (ns == 1) return kStepOne;
-    // 8 rows of 8192, B = 256: 14.6 / 14.6 / 17.3, B = 512: 16.0 / 17.0 / 19.8; 128 rows of 4096: 22.3 / 20.4 / 21.9
-    // Several slices, where the lists of a scoring launch do not do better: one launch / lists, B = 256, 40 rows of 8192: 13.7 / 13.7, 128 of 4000: 16.0 /
-    // 16.4; 8 rows of 6000, B = 40: 11.2 / 11.0, 320: 13.7 / 13.3, 256 with F = 32: 14.5 / 13.5, of 4000, 320: 13.5 / 13.3, of 3000, 40: 11.0 / 11.1.  On the other
-    // side 8 rows of 8192: 14.4 / 13.6, 32 rows: 17.0 / 17.1, from caches in memory, with a selection out of lists that took 2 us longer.
+    // Several slices, where the lists of a scoring launch do not do better: B = 256, 40 rows of 8192: 14.15 / 15.0, 128 of 4000: 15.3 / 16.65; 8 rows of 6000, B = 40: 10.45 / 11.2, 256:
+    // 11.9 / 12.3, 320: 12.3 / 13.4, 256 with F = 32: 13.05 / 13.25; of 4000, 320: 11.5 / 13.4; of 3000, 40: 9.65 / 11.25.  The line was drawn when the one launch selected out of a list
+    // of its own.  On its other side today: 8 rows of 8192, 256: 11.85 / 12.4, 32 rows: 13.6 / 14.15; 8 rows of 4000, 400: 12.2 / 13.25, 512: 12.9 / 13.4; of 6000, 512: 13.65 / 13.5.
     return ns <= 4 && rows * ns <= kAssumedCUs && bsel <= 320 && (rows > 32 || ns < 4) ? kStepOne : kStepNone;
   } else {
-    // float32: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
+    // float32, fused.hip / one launch / row_kernel: the vector ALUs attend, in proportion to the query heads, where fused.hip has the matrix cores.  1 head:
     // 1 row of 4096, B = 256: 17.3 / 12.7 / 15.5, 32 rows of 8192, B = 600: 22.2 / 22.1 / 26.3.  4 heads, 8 rows, B = 64:
     // of 1024: 17.1 / 12.9 / 17.2, of 4096: 15.4 / 15.2 / 17.3, 32 rows of 4096: 17.0 / 18.1 / 19.1; 8 heads, 8 rows of
     // 1024, B = 64: 18.1 / 16.5 / 21.5
