@@ -42,26 +42,26 @@ LLC_BYTES = 256 << 20         # last-level (memory-side) cache the rotation has 
 # what the same counters read for a plain copy kernel of known size (see profiles/).  Keyed by
 # (workload config id, kernel name); bytes per launch.  None = not measured yet.
 MEASURED_TRAFFIC = {
-    "source_hash": "cbc1252ab5846d4b",   # source_hash() of the kernels the counters were taken on
+    "source_hash": "fa67e29550198423",   # source_hash() of the kernels the counters were taken on
     # profiles/decode_step_tiny_1head_f32_n4096_hbm_counters.txt  (read + written)
-    (0, "fasa_dense_attend"): 4336550 + 39456,
-    (0, "fasa_step"): 869640 + 18080,
+    (0, "fasa_dense_attend"): 4336559 + 39456,
+    (0, "fasa_step"): 866966 + 18080,
     # profiles/decode_step_llama3_8b_layer_n32768_b2048_hbm_counters.txt  (read + written)
-    (1, "fasa_dense_attend"): 134899038 + 1089792,
-    (1, "fasa_list"): 9479740 + 1155595,
-    (1, "fasa_score_list"): 16899442 + 1261568,
+    (1, "fasa_dense_attend"): 134899658 + 1089792,
+    (1, "fasa_list"): 9479633 + 1155592,
+    (1, "fasa_score_list"): 16903528 + 1261568,
     # profiles/decode_step_batch16_n16384_b256_hbm_counters.txt  (read + written)
-    (2, "fasa_dense_attend"): 1087399519 + 1339392,
-    (2, "fasa_list"): 18045302 + 397313,
-    (2, "fasa_score_list"): 134457423 + 9274011,
+    (2, "fasa_dense_attend"): 1087789984 + 1339392,
+    (2, "fasa_list"): 18045168 + 397312,
+    (2, "fasa_score_list"): 134456777 + 9274005,
     # profiles/decode_step_longcot_batch8_gqa7_n32768_hbm_counters.txt  (read + written)
-    (3, "fasa_dense_attend"): 546143531 + 1997824,
-    (3, "fasa_list"): 104594291 + 2794753,
-    (3, "fasa_score_list"): 67281583 + 5947401,
+    (3, "fasa_dense_attend"): 545829940 + 1997824,
+    (3, "fasa_list"): 104594827 + 2794613,
+    (3, "fasa_score_list"): 67280939 + 5947405,
     # profiles/decode_step_verylong_n131072_f32fc_b1024_hbm_counters.txt  (read + written)
-    (4, "fasa_dense_attend"): 543608555 + 1089792,
-    (4, "fasa_list"): 5084103 + 586240,
-    (4, "fasa_score_list"): 134360505 + 4473564,
+    (4, "fasa_dense_attend"): 543593552 + 1089792,
+    (4, "fasa_list"): 5084153 + 586240,
+    (4, "fasa_score_list"): 134361126 + 4473401,
 }
 
 

@@ -10,8 +10,8 @@
 //   calib_fc_kernel     one workgroup per (b, h): the top-K set of the full head; one per (b, h, FC), as above.
 //
 // The single-FC scores never exist in memory: a workgroup streams its plane once and writes one number.
-// One Llama-3-8B layer at 32768 tokens, K = 2048 (67 MB of keys, asked for twice): 2.3 us for a launch that clears and 29, of which the planes are 18 - 20 (7 TB/s: the second
-// read is no faster than the first); then the full head's set (5 us) and the FCs that come last.  In two launches 36.85: the first's end and the second's, where all
+// One Llama-3-8B layer at 32768 tokens, K = 2048: 2.3 us for a launch that clears and 29.  The 67 MB of keys are asked for twice, and 123 MB come from memory: 18 us
+// at the rate of a large read; then the full head's set and the FCs that come last.  In two launches 36.85: the first's end and the second's, where all
 // workgroups select at once, with nothing to stream.
 #include <type_traits>
 
